@@ -161,43 +161,28 @@ def _query_log(g, n, d, dtype):
     return rows[torch.randperm(n, device=DEV, generator=g)].contiguous()
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """The tensors of a case, from the seed alone."""
     g = torch.Generator(device=DEV)
     g.manual_seed(seed)
     op, d = case["op"], case["d"]
-    kind, dtype, _ = DTYPES[case["dtype"]]
-    s = {"op": op, "case": case}
+    dtype = DTYPES[case["dtype"]][1]
+    s = {}
     if op in ("step", "copy", "lookup", "topk"):
-        K, n = case["K"], case["n"]
-        cents, of = _mixture(g, K, d, 16, 0.08, dtype)
-        s["cache"] = siso.SisoCache(d, K, kind)
-        s["cache"].load(cents)
-        if op == "copy":
-            s["master"] = siso.SisoCache(d, K, siso.BF16)
-            s["master"].load(cents)
-        for c in (s["cache"], s.get("master")):
-            if c is not None:
-                c.reserve(n)  # a serving loop sizes its workspaces once
-        q = _requests(g, cents, of, n * case.get("batches", 1), case["fresh"])
-        s["batches"] = list(q.split(n))
+        n = case["n"]
+        s["cents"], of = _mixture(g, case["K"], d, 16, 0.08, dtype)
+        s["batches"] = list(_requests(g, s["cents"], of, n * case.get("batches", 1), case["fresh"]).split(n))
     elif op == "merge":
         s["rows"], _ = _mixture(g, case["K"], d, case["copies"], 0.03, dtype)
         s["counts"] = torch.randint(1, 40, (case["K"],), device=DEV, generator=g, dtype=torch.int32)
-        s["cache"] = siso.SisoCache(d, case["K"], kind)
-        s["cap"] = case["K"] * (case["copies"] - 1) // 2 + 1024
-        s["cache"].set_option("second_set", 1)  # (a cache that is rebuilt now and then keeps its second set)
     elif op == "cluster":
         s["log"] = _query_log(g, case["n"], d, dtype)
-        s["cache"] = siso.SisoCache(d, case["n"], kind)
     elif op == "refresh":
         K, r = case["K"], case["r"]
-        cents, of = _mixture(g, K, d, 16, 0.08, dtype)
-        s["cache"] = siso.SisoCache(d, K + r, kind)
-        s["cache"].set_option("second_set", 1)
-        s["cache"].load(cents, torch.randint(1, 40, (K,), device=DEV, generator=g, dtype=torch.int32))
-        for q in _requests(g, cents, of, min(K, 16384), 0.3).split(4096):  # references: they decide who leaves
-            s["cache"].lookup(q, THETA)
-        s["snapshot"] = s["cache"].export() + s["cache"].export_meta()
+        s["cents"], of = _mixture(g, K, d, 16, 0.08, dtype)
+        cents = s["cents"]
+        s["counts"] = torch.randint(1, 40, (K,), device=DEV, generator=g, dtype=torch.int32)
+        s["references"] = list(_requests(g, cents, of, min(K, 16384), 0.3).split(4096))
         near = torch.randint(0, K, (r // 2,), device=DEV, generator=g)
         repo = torch.cat([_near(g, cents, near, 0.06, dtype), _directions(g, r - r // 2, d).to(dtype)])
         s["repo"] = repo[torch.randperm(r, device=DEV, generator=g)].contiguous()
@@ -206,6 +191,36 @@ def prepare(case, seed):
         m = max(64, K // 20)
         length = torch.rand(m, device=DEV, generator=g) * 1.2 + 0.1
         s["sample"] = _near(g, cents, torch.randint(0, K, (m,), device=DEV, generator=g), length, dtype)
+    return s
+
+
+def prepare(case, seed):
+    op, d, kind = case["op"], case["d"], DTYPES[case["dtype"]][0]
+    s = {"op": op, "case": case, **_inputs(case, seed)}
+    if op in ("step", "copy", "lookup", "topk"):
+        K, n = case["K"], case["n"]
+        cents = s.pop("cents")
+        s["cache"] = siso.SisoCache(d, K, kind)
+        s["cache"].load(cents)
+        if op == "copy":
+            s["master"] = siso.SisoCache(d, K, siso.BF16)
+            s["master"].load(cents)
+        for c in (s["cache"], s.get("master")):
+            if c is not None:
+                c.reserve(n)  # a serving loop sizes its workspaces once
+    elif op == "merge":
+        s["cache"] = siso.SisoCache(d, case["K"], kind)
+        s["cap"] = case["K"] * (case["copies"] - 1) // 2 + 1024
+        s["cache"].set_option("second_set", 1)  # (a cache that is rebuilt now and then keeps its second set)
+    elif op == "cluster":
+        s["cache"] = siso.SisoCache(d, case["n"], kind)
+    elif op == "refresh":
+        s["cache"] = siso.SisoCache(d, case["K"] + case["r"], kind)
+        s["cache"].set_option("second_set", 1)
+        s["cache"].load(s.pop("cents"), s.pop("counts"))
+        for q in s.pop("references"):  # they decide who leaves
+            s["cache"].lookup(q, THETA)
+        s["snapshot"] = s["cache"].export() + s["cache"].export_meta()
     torch.cuda.synchronize()
     return s
 
@@ -269,3 +284,151 @@ def tolerance(case):
     if case["op"] in ("merge", "cluster", "refresh"):
         return {"rel": 2e-4, "max": 0.01, "differ": 1e-4}
     return {"rel": 1e-5 if case["op"] == "copy" else 3e-6, "max": 1e-4, "differ": 5e-4}
+
+
+# ------------------------------------------------------------------------------------------------------------------
+# the same passes in 64 bits, by plain torch
+# ------------------------------------------------------------------------------------------------------------------
+def _dir64(x):
+    """Rows at unit length, in 64 bits."""
+    return _unit(x.double())
+
+
+def _codes64(x):
+    """The E4M3 codes of 8-bit rows (scale = largest element / 448, in single precision), as 64-bit numbers."""
+    x = x.float()
+    most = x.abs().amax(1, keepdim=True)
+    return (x / (most / torch.full_like(most, 448.0))).to(torch.float8_e4m3fn).double()
+
+
+def _best64(q, c, k=1):
+    """(index, cosine) of the k closest rows of c for every row of q; both hold unit rows."""
+    best_i, best_s = [], []
+    block = max(1, (1 << 30) // c.shape[0])
+    for lo in range(0, q.shape[0], block):
+        p = q[lo:lo + block] @ c.T
+        v, i = p.topk(k, dim=1) if k > 1 else p.max(1, keepdim=True)
+        best_i.append(i)
+        best_s.append(v)
+    return torch.cat(best_i), torch.cat(best_s)
+
+
+def _first_neighbour64(u, theta):
+    """Per row the lowest index among itself and the rows closer than theta, and their number (u: unit rows)."""
+    n = u.shape[0]
+    first, degree = [], []
+    block = max(1, (1 << 29) // n)
+    for lo in range(0, n, block):
+        near = u[lo:lo + block] @ u.T > theta
+        i = torch.arange(near.shape[0], device=DEV)
+        near[i, i + lo] = True
+        first.append(near.to(torch.uint8).argmax(1))
+        degree.append(near.sum(1))
+    return torch.cat(first), torch.cat(degree)
+
+
+def _exact_steps(case, s):
+    dtype, theta = DTYPES[case["dtype"]][1], torch.tensor(THETA, dtype=torch.float32).double().to(DEV)
+    stored = (lambda x: _unit(_codes64(x))) if case["dtype"] == "fp8" else _dir64
+    mean = _dir64(s["cents"])
+    weight = torch.ones(case["K"], 1, dtype=torch.float64, device=DEV)
+    c = stored(s["cents"])
+    out = []
+    for q in s["batches"]:
+        idx, sim = _best64(stored(q), c)
+        idx, sim = idx[:, 0], sim[:, 0]
+        hit = sim > theta
+        out.append((idx.int(), sim, hit.to(torch.uint8)))
+        rows, at = idx[hit].unique(return_inverse=True)
+        if rows.numel():
+            total = (mean[rows] * weight[rows]).index_add_(0, at, _dir64(q[hit]))
+            weight[rows] += torch.bincount(at, minlength=rows.numel()).double()[:, None]
+            mean[rows] = total / weight[rows]
+            c[rows] = stored(_unit(mean[rows]).to(dtype))
+    return out
+
+
+def _exact_refresh(case, s):
+    K, r = case["K"], case["r"]
+    mean = _dir64(s["cents"])
+    access = torch.zeros(K, dtype=torch.int64, device=DEV)
+    for q in s["references"]:
+        idx, sim = _best64(_dir64(q), mean)
+        access += torch.bincount(idx[:, 0][sim[:, 0] > float(np.float32(THETA))], minlength=K)
+    repo = _dir64(s["repo"])
+    theta = float(np.float32(THETA_MERGE))
+    idx, sim = (x[:, 0].tolist() for x in _best64(repo, mean))
+    candidates = [[] for _ in range(r)]  # earlier rows of the repository above the threshold
+    block = max(1, (1 << 29) // r)
+    for lo in range(0, r, block):
+        p = repo[lo:lo + block] @ repo.T
+        for i, j in (p > theta).nonzero().tolist():
+            if j < i + lo:
+                candidates[i + lo].append((p[i, j].item(), j))
+    size = s["counts"].double().tolist()
+    refs = access.tolist()
+    source, place, merged = list(range(K)), {}, 0
+    for i, w in enumerate(s["sizes"].tolist()):
+        best, at = sim[i], idx[i]
+        for v, j in candidates[i]:
+            if j in place and v > best:
+                best, at = v, place[j]
+        if best > theta:
+            size[at] += w
+            merged += 1
+        else:
+            place[i] = len(source)
+            source.append(K + i)
+            size.append(w)
+            refs.append(0xFFFFFFFF)
+    order = sorted(range(len(source)), key=lambda j: (size[j], refs[j], j))
+    evicted = max(0, len(source) - (K + K // 50))
+    kept = sorted(order[evicted:])
+    src = torch.tensor([source[j] for j in kept], device=DEV)
+    weight = torch.cat([s["counts"], s["sizes"].round().int()])[src]
+    loc = torch.tensor([size[j] for j in kept], dtype=torch.float64, device=DEV) / 1.1
+    cents = torch.cat([s["cents"], s["repo"]])[src]
+    new = torch.cat([mean, repo])[src]
+    _, best = _best64(_dir64(s["sample"]), _dir64(cents))
+    hits = np.array([int((best > float(t)).sum()) for t in SWEEP], dtype=np.int64)
+    return (merged, len(place), evicted), hits, (cents.double(), new, weight), (loc, torch.zeros_like(loc, dtype=torch.int64))
+
+
+def exact(case, seed):
+    op, s = case["op"], _inputs(case, seed)
+    if op in ("step", "copy", "lookup"):
+        return _exact_steps(case, s)  # (a lookup is one batch: what would follow it is not looked at)
+    if op == "topk":
+        rows = (lambda x: _unit(_codes64(x))) if case["dtype"] == "fp8" else _dir64
+        idx, sim = _best64(rows(s["batches"][0]), rows(s["cents"]), case["k"])
+        return idx.int(), sim
+    if op == "refresh":
+        return _exact_refresh(case, s)
+    # merge and cluster: groups whose rows are all neighbours of each other
+    rows = s["rows"] if op == "merge" else s["log"]
+    u = _dir64(rows)
+    n = rows.shape[0]
+    first, degree = _first_neighbour64(u, THETA_MERGE if op == "merge" else THETA_LOG)
+    total = (int(degree.sum()) - n) // 2
+    if op == "merge":
+        leaders, group = first.unique(return_inverse=True)
+        count = s["counts"].double()
+    else:
+        leaders, group = first.unique(return_inverse=True)
+        members = torch.bincount(group)
+        order = torch.argsort(members, descending=True, stable=True)
+        order = order[members[order] > 1]
+        number = torch.full_like(members, -1)
+        number[order] = torch.arange(order.numel(), device=DEV)
+        labels, group, leaders = number[group], number[group], leaders[order]
+        count = torch.ones(n, dtype=torch.float64, device=DEV)
+    keep = group >= 0
+    weight = torch.zeros(leaders.numel(), dtype=torch.float64, device=DEV).index_add_(0, group[keep], count[keep])
+    mean = torch.zeros(leaders.numel(), case["d"], dtype=torch.float64, device=DEV)
+    mean = mean.index_add_(0, group[keep], u[keep] * count[keep, None]) / weight[:, None]
+    cents = _unit(mean)
+    if op == "merge":
+        alone = torch.bincount(group) == 1
+        cents[alone] = rows[leaders[alone]].double()
+    state = (cents, mean, weight.int()), (weight, torch.zeros(leaders.numel(), dtype=torch.int64, device=DEV))
+    return (total, group.int(), *state) if op == "merge" else (labels.int(), leaders.numel(), total, *state)
