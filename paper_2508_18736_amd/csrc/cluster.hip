@@ -269,7 +269,7 @@ static long cluster_impl(siso_cache *c, const void *vectors, long n, float theta
             if (siso_pairs_mfma_supported(c, n))
                 rc = siso_pairs_mfma_launch(c, d_rows.p, d_inv.as<float>(), n, theta_c, d_pairs.as<int>(), cap, c->counters + 1);
             else
-                rc = siso_pairs_scalar_launch(c, d_rows.p, d_inv.as<float>(), n, theta_c, d_pairs.as<int>(), cap, c->counters + 1);
+                rc = siso_pairs_tile_launch(c, d_rows.p, d_inv.as<float>(), n, theta_c, d_pairs.as<int>(), cap, c->counters + 1);
             if (rc != SISO_OK) return rc;
             u64 total = 0;
             rc = siso_read_counter(c, 1, &total);

@@ -1780,7 +1780,7 @@ int siso_topk_mfma_collect(siso_cache *c, const void *queries, long n, int slice
 // pair search (siso_merge) on the same kernel
 // ----------------------------------------------------------------------------
 int siso_pairs_mfma_supported(const siso_cache *c, long count) {
-    if (c->opt_merge_config == 1) return 0;  // 1 = force the scalar kernel
+    if (c->opt_merge_config == 1) return 0;  // 1 = force the kernel of lookup_tile.hip
     return c->dtype == SISO_BF16 && c->dim % 64 == 0 && c->dim >= 128 && count >= 2;
 }
 

@@ -1,6 +1,5 @@
 // C ABI of the centroid cache (include/siso.h): state management, the kernels
-// that are not matrix-shaped (row norms, finalize, update, group merge) and the
-// LDS-tiled fp32 kernels that serve any element type and dimension.
+// that are not matrix-shaped (row norms, finalize, update, group merge).
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -264,173 +263,6 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
             }
         }
     }
-}
-
-// ============================================================================
-// LDS-tiled fp32 GEMM core shared by the scalar lookup and scalar merge kernels:
-// a 64 x 64 tile of dot products per 256-thread block, thread (ty, tx) owning
-// rows ty*4..+4 of A and rows tx*4..+4 of B.
-// ============================================================================
-#define ST_M 64
-#define ST_K 16
-
-template <typename T>
-__device__ __forceinline__ void scalar_tile(const T *__restrict__ A, long a0, long a_end, const T *__restrict__ B,
-                                            long b0, long b_end, int d, float (*As)[ST_M + 4],
-                                            float (*Bs)[ST_M + 4], float acc[4][4]) {
-    const int t = threadIdx.x;
-    const int tx = t & 15, ty = t >> 4;
-    const int lr = t >> 2, lk = (t & 3) * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    for (int k0 = 0; k0 < d; k0 += ST_K) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = k0 + lk + e;
-            const long ar = a0 + lr, br = b0 + lr;
-            As[lk + e][lr] = (ar < a_end && k < d) ? widen(A[(size_t)ar * d + k]) : 0.f;
-            Bs[lk + e][lr] = (br < b_end && k < d) ? widen(B[(size_t)br * d + k]) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < ST_K; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-}
-
-// Phase 1, scalar path: block (x = query tile, y = slice of the centroid range).
-template <typename T>
-__global__ __launch_bounds__(256) void k_lookup_scalar(const T *__restrict__ Q, const T *__restrict__ cent,
-                                                        const float *__restrict__ invn, long n, long K, int d,
-                                                        long rows_per_slice, int slices, u64 *keys, u64 *board) {
-    __shared__ float As[ST_K][ST_M + 4];
-    __shared__ float Bs[ST_K][ST_M + 4];
-    // (a step that ends in k_finalize_update: the slots of its board are emptied here, a kernel ahead)
-    if (board != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < SISO_FOLD_BOARD) board[threadIdx.x] = 0;
-    const long q0 = (long)blockIdx.x * ST_M;
-    const int s = blockIdx.y;
-    const long c_begin = (long)s * rows_per_slice;
-    const long c_end = (c_begin + rows_per_slice < K) ? c_begin + rows_per_slice : K;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float best[4];
-    long bidx[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        best[i] = -INFINITY;
-        bidx[i] = -1;
-    }
-    for (long c0 = c_begin; c0 < c_end; c0 += ST_M) {
-        float acc[4][4];
-        scalar_tile(Q, q0, n, cent, c0, c_end, d, As, Bs, acc);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const long cidx = c0 + tx * 4 + j;
-            if (cidx < c_end) {
-                const float w = invn[cidx];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float v = acc[i][j] * w;
-                    if (v > best[i]) {
-                        best[i] = v;
-                        bidx[i] = cidx;
-                    }
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-            const float ov = __shfl_xor(best[i], off);
-            const long oi = __shfl_xor(bidx[i], off);
-            if (oi >= 0 && (bidx[i] < 0 || ov > best[i] || (ov == best[i] && oi < bidx[i]))) {
-                best[i] = ov;
-                bidx[i] = oi;
-            }
-        }
-        const long q = q0 + ty * 4 + i;
-        if (tx == 0 && q < n)
-            keys[(size_t)q * slices + s] = bidx[i] < 0 ? 0ull : pack_key(best[i], (unsigned)bidx[i]);
-    }
-}
-
-int siso_scalar_slices(const siso_cache *c, long n) {
-    // enough blocks to fill the chip, at least one 64-row tile per slice
-    const long qtiles = (n + ST_M - 1) / ST_M;
-    const long ctiles = (c->count + ST_M - 1) / ST_M;
-    long want = (2048 + qtiles - 1) / qtiles;
-    if (want > ctiles) want = ctiles;
-    if (want < 1) want = 1;
-    if (want > 65535) want = 65535;
-    return (int)want;
-}
-
-template <typename T>
-static int scalar_launch_t(siso_cache *c, const void *queries, long n, int slices, u64 *keys) {
-    const long ctiles = (c->count + ST_M - 1) / ST_M;
-    const long rows_per_slice = ((ctiles + slices - 1) / slices) * ST_M;
-    dim3 grid((unsigned)((n + ST_M - 1) / ST_M), (unsigned)slices);
-    hipLaunchKernelGGL(k_lookup_scalar<T>, grid, dim3(256), 0, c->stream, (const T *)queries, (const T *)c->cent,
-                       c->invn, n, c->count, c->dim, rows_per_slice, slices, keys, c->board_to_clear);
-    c->board_to_clear = nullptr;  // taken
-    return siso_check_hip(c, hipGetLastError(), "k_lookup_scalar");
-}
-
-int siso_scalar_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys) {
-    return c->dtype == SISO_F32 ? scalar_launch_t<float>(c, queries, n, slices, keys)
-                                : scalar_launch_t<bf16_t>(c, queries, n, slices, keys);
-}
-
-// Self-similarity, scalar path: block (x, y) = tile pair, upper triangle only.
-template <typename T>
-__global__ __launch_bounds__(256) void k_merge_scalar(const T *__restrict__ cent, const float *__restrict__ invn, long K,
-                                                       int d, float threshold, int *out_pairs, long cap, u64 *counter) {
-    if (blockIdx.x > blockIdx.y) return;
-    __shared__ float As[ST_K][ST_M + 4];
-    __shared__ float Bs[ST_K][ST_M + 4];
-    const long i0 = (long)blockIdx.x * ST_M, j0 = (long)blockIdx.y * ST_M;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4];
-    scalar_tile(cent, i0, K, cent, j0, K, d, As, Bs, acc);
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const long i = i0 + ty * 4 + a;
-        const float wi = i < K ? invn[i] : 0.f;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const long j = j0 + tx * 4 + b;
-            const float wj = j < K ? invn[j] : 0.f;
-            const float s = acc[a][b] * wi * wj;
-            emit_pair(i < j && j < K && s > threshold, (int)i, (int)j, out_pairs, cap, counter);
-        }
-    }
-}
-
-int siso_pairs_scalar_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold,
-                             int *out_pairs, long cap, u64 *counter) {
-    const unsigned tiles = (unsigned)((count + ST_M - 1) / ST_M);
-    if (tiles > 65535u) return siso_fail(c, SISO_EINVAL, "scalar pair search handles at most %d rows", 65535 * ST_M);
-    dim3 grid(tiles, tiles);
-    if (c->dtype == SISO_F32)
-        hipLaunchKernelGGL(k_merge_scalar<float>, grid, dim3(256), 0, c->stream, (const float *)rows, invn, count, c->dim,
-                           threshold, out_pairs, cap, counter);
-    else
-        hipLaunchKernelGGL(k_merge_scalar<bf16_t>, grid, dim3(256), 0, c->stream, (const bf16_t *)rows, invn, count,
-                           c->dim, threshold, out_pairs, cap, counter);
-    return siso_check_hip(c, hipGetLastError(), "k_merge_scalar");
 }
 
 // ============================================================================
@@ -1330,7 +1162,7 @@ static long keys_needed(const siso_cache *c, long n) {
     if (n < 1 || c->count < 1) return n > 0 ? n : 0;
     int slices = 0;
     switch (choose_path(c, n)) {
-        case SISO_PATH_SCALAR: slices = siso_scalar_slices(c, n); break;
+        case SISO_PATH_SCALAR: slices = siso_tile_slices(c, n); break;
         case SISO_PATH_MFMA: slices = siso_mfma_slices(c, n); break;
         case SISO_PATH_SKINNY: slices = siso_skinny_slices(c, n); break;
     }
@@ -1407,7 +1239,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
         return siso_fail(c, SISO_EINVAL, "siso_lookup: the 8-bit storage has no scalar kernel");
     if (c->count > 0) {
         switch (path) {
-            case SISO_PATH_SCALAR: slices = siso_scalar_slices(c, n); break;
+            case SISO_PATH_SCALAR: slices = siso_tile_slices(c, n); break;
             case SISO_PATH_MFMA: slices = siso_mfma_slices(c, n); break;
             case SISO_PATH_SKINNY: slices = siso_skinny_slices(c, n); break;
         }
@@ -1445,7 +1277,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
     if (c->count > 0) {
         if (!static_keys) siso_prof_begin(c);
         switch (path) {
-            case SISO_PATH_SCALAR: rc = siso_scalar_launch(c, queries, n, slices, keys); break;
+            case SISO_PATH_SCALAR: rc = siso_tile_launch(c, queries, n, slices, keys); break;
             case SISO_PATH_MFMA: rc = siso_mfma_launch(c, kernel_queries, n, slices, keys, &row_keys); break;
             case SISO_PATH_SKINNY: rc = siso_skinny_launch(c, kernel_queries, n, slices, keys, &row_keys); break;
         }
@@ -1637,7 +1469,7 @@ extern "C" long siso_merge(siso_cache *c, float threshold, int *out_pairs, long 
     if (siso_pairs_mfma_supported(c, c->count))
         rc = siso_pairs_mfma_launch(c, c->cent, c->invn, c->count, threshold, out_pairs, cap, c->counters + 1);
     else
-        rc = siso_pairs_scalar_launch(c, c->cent, c->invn, c->count, threshold, out_pairs, cap, c->counters + 1);
+        rc = siso_pairs_tile_launch(c, c->cent, c->invn, c->count, threshold, out_pairs, cap, c->counters + 1);
     siso_prof_end(c);
     if (rc != SISO_OK) return rc;
     u64 total = 0;

@@ -379,8 +379,8 @@ int siso_check_hip(siso_cache *c, hipError_t e, const char *what);
 // nothing has to be cleared beforehand).
 // *_slices returns the number of slices the launcher will use (0 = path cannot
 // handle this cache / batch).
-int siso_scalar_slices(const siso_cache *c, long n);
-int siso_scalar_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys);
+int siso_tile_slices(const siso_cache *c, long n);
+int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys);
 int siso_mfma_slices(const siso_cache *c, long n);
 int siso_mfma_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
 int siso_skinny_slices(const siso_cache *c, long n);
@@ -400,7 +400,7 @@ int siso_topk_mfma_collect(siso_cache *c, const void *queries, long n, int slice
 // Self-similarity pair search over `count` rows of the cache's element type and dimension with
 // their inverse lengths (counter already zeroed).  The MFMA kernel reads whole tiles: rows and invn
 // must be readable for SISO_PAD_ROWS entries past count, the invn entries there holding NaN.
-int siso_pairs_scalar_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold,
+int siso_pairs_tile_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold,
                              int *out_pairs, long cap, u64 *counter);
 int siso_pairs_mfma_supported(const siso_cache *c, long count);
 int siso_pairs_mfma_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold,
