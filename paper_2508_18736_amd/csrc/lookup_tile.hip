@@ -200,11 +200,12 @@ __device__ __forceinline__ long xcd_run(long total) {
 inline unsigned xcd_grid(long total) { return (unsigned)((total + 7) / 8 * 8); }
 
 // Phase 1 of a lookup: the best scaled product of every query of a tile with the rows of a slice, as a key that names
-// the row.
-template <class Cfg, int W, typename T>
+// the row.  GROUPS: of a top-k lookup: the two largest products of every group of 16 rows instead (see siso_internal.h).
+template <class Cfg, int W, typename T, bool GROUPS = false>
 __global__ __launch_bounds__(256, 2) void k_lookup_tile(const T *__restrict__ Q, const T *__restrict__ cent,
                                                       const float *__restrict__ invn, long n, long K, int d,
-                                                      int tiles_per_slice, int slices, int qtiles, u64 *keys, u64 *board) {
+                                                      int tiles_per_slice, int slices, int qtiles, u64 *keys, u64 *board,
+                                                      float2 *groups, int ng) {
     __shared__ __align__(16) char lds[2 * Cfg::STAGE];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wc = wave / Cfg::NWQ, wq = wave % Cfg::NWQ, h = lane >> 5;
@@ -229,6 +230,25 @@ __global__ __launch_bounds__(256, 2) void k_lookup_tile(const T *__restrict__ Q,
 #pragma unroll
         for (int i = 0; i < Cfg::WC; ++i) {
             const long r0 = c0 + (wc * Cfg::WC + i) * 32 + 4 * h;
+            if constexpr (GROUPS) {
+                TwoLargest most[Cfg::WQ];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 w4 = *(const float4 *)(invn + r0 + 8 * g);  // (NaN behind the live rows)
+                    const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int j = 0; j < Cfg::WQ; ++j) most[j].take(acc[i][j][4 * g + e] * w[e], (unsigned)(4 * g + e));
+                }
+                const int grp = (int)(r0 >> 5) * 2 + h;
+#pragma unroll
+                for (int j = 0; j < Cfg::WQ; ++j) {
+                    const long q = q0 + (wq * Cfg::WQ + j) * 32 + (lane & 31);
+                    if (q < n && grp < ng) groups[(size_t)q * ng + grp] = make_float2(most[j].first, most[j].second);
+                }
+                continue;
+            }
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const float4 w4 = *(const float4 *)(invn + r0 + 8 * g);  // (NaN behind the live rows: those never win)
@@ -246,6 +266,7 @@ __global__ __launch_bounds__(256, 2) void k_lookup_tile(const T *__restrict__ Q,
             }
         }
     });
+    if constexpr (GROUPS) return;
     lds_barrier();  // everyone is done with the stages: the keys of the waves that share a query meet there
     u64(*red)[Cfg::BQ] = (u64(*)[Cfg::BQ])lds;
 #pragma unroll
@@ -336,12 +357,13 @@ TilePlan tile_plan(const siso_cache *c, long n) {
     return p;
 }
 
-template <typename T, int W>
-int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys) {
+template <typename T, int W, bool GROUPS>
+int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng) {
     const dim3 grid(xcd_grid((long)p.qtiles * p.slices)), block(256);
 #define SISO_LAUNCH_TILE(Cfg)                                                                                            \
-    hipLaunchKernelGGL((k_lookup_tile<Cfg, W, T>), grid, block, 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
-                       n, c->count, c->dim, p.tiles_per_slice, p.slices, p.qtiles, keys, c->board_to_clear)
+    hipLaunchKernelGGL((k_lookup_tile<Cfg, W, T, GROUPS>), grid, block, 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
+                       n, c->count, c->dim, p.tiles_per_slice, p.slices, p.qtiles, keys, c->board_to_clear, \
+                       groups, ng)
     if (p.cfg == 0) SISO_LAUNCH_TILE(TileFew);
     else if (p.cfg == 1) SISO_LAUNCH_TILE(TileSmall);
     else SISO_LAUNCH_TILE(TileLarge);
@@ -350,12 +372,12 @@ int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p,
     return siso_check_hip(c, hipGetLastError(), "k_lookup_tile");
 }
 
-template <typename T>
-int lookup_launch_t(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys) {
+template <typename T, bool GROUPS>
+int lookup_launch_t(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng) {
     switch (row_alignment<T>(queries, c->cent, c->dim)) {
-        case 16: return lookup_launch<T, 16>(c, queries, n, p, keys);
-        case 8: return lookup_launch<T, 8>(c, queries, n, p, keys);
-        default: return lookup_launch<T, (int)sizeof(T)>(c, queries, n, p, keys);
+        case 16: return lookup_launch<T, 16, GROUPS>(c, queries, n, p, keys, groups, ng);
+        case 8: return lookup_launch<T, 8, GROUPS>(c, queries, n, p, keys, groups, ng);
+        default: return lookup_launch<T, (int)sizeof(T), GROUPS>(c, queries, n, p, keys, groups, ng);
     }
 }
 
@@ -392,8 +414,14 @@ int siso_tile_slices(const siso_cache *c, long n) { return c->count < 1 || n < 1
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys) {
     const TilePlan p = tile_plan(c, n);
     if (p.slices != slices) return siso_fail(c, SISO_EINVAL, "tiled lookup: plan mismatch");
-    return c->dtype == SISO_F32 ? lookup_launch_t<float>(c, queries, n, p, keys)
-                                : lookup_launch_t<bf16_t>(c, queries, n, p, keys);
+    return c->dtype == SISO_F32 ? lookup_launch_t<float, false>(c, queries, n, p, keys, nullptr, 0)
+                                : lookup_launch_t<bf16_t, false>(c, queries, n, p, keys, nullptr, 0);
+}
+
+int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng) {
+    const TilePlan p = tile_plan(c, n);
+    return c->dtype == SISO_F32 ? lookup_launch_t<float, true>(c, queries, n, p, nullptr, groups, ng)
+                                : lookup_launch_t<bf16_t, true>(c, queries, n, p, nullptr, groups, ng);
 }
 
 int siso_pairs_tile_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs,

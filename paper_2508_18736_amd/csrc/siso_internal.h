@@ -79,13 +79,10 @@ struct siso_cache {
     float *fp8_qinv;
     long fp8_q_cap;
 
-    // top-k lookups: per query the bound, the number of listed rows, a flag "scan this query row by row" and
-    // the listed rows ([topk_cap] floats / ints / ints, [topk_cap][SISO_TOPK_CAND] ints), grown on demand
-    float *topk_tau;
-    int *topk_cnt;
-    int *topk_cand;
-    long topk_cap;
-    int plan_min_slices;  // > 0 while a top-k lookup plans its passes: at least this many slices (if the tiles allow)
+    // top-k lookups: the two largest products of every group of 16 rows, per query ([topk_groups_cap] pairs, at most
+    // about SISO_TOPK_GROUP_BYTES: larger batches go in pieces), grown on demand
+    float2 *topk_groups;
+    long topk_groups_cap;
     const siso_cache *fold_master;  // not NULL while siso_fp8_lookup_update runs its lookup on this 8-bit copy
     int mark_in_finalize;  // siso_lookup_update on a large batch: 1 = the finalize step shall take the update's notes
                            // (first member and number of members per centroid), 2 = it has; 0 otherwise
@@ -155,6 +152,17 @@ __device__ __forceinline__ u64 pack_key(float value, unsigned block) {
     return ((u64)ordered_bits(value) << 32) | (u64)(0xFFFFFFFFu - block);
 }
 
+// The two largest of the products a lane meets, each tagged with a number in its lowest four bits (top-k lookups).  A NaN
+// is passed over by the maximum, and by the median of three, which then is the smallest of the other two.
+struct TwoLargest {
+    float first = -INFINITY, second = -INFINITY;
+    __device__ __forceinline__ void take(float v, unsigned tag) {
+        v = __uint_as_float((__float_as_uint(v) & ~15u) | tag);
+        second = __builtin_amdgcn_fmed3f(first, second, v);
+        first = fmaxf(first, v);
+    }
+};
+
 // 1/|x| from the sum of squares: 0 for a zero vector, NaN if the sum is not finite
 __device__ __forceinline__ float inv_length(float sumsq) {
     if (!(sumsq == sumsq) || sumsq > 3.0e38f) return __uint_as_float(0x7FC00000u);
@@ -200,12 +208,16 @@ __device__ __forceinline__ float chunk_dot(u32x4_t x, u32x4_t y, bf16_t) {
     return s;
 }
 
-__device__ __forceinline__ float chunk_dot(u32x4_t x, u32x4_t y, fp8_t) {  // sixteen codes
+__device__ __forceinline__ float chunk_dot(u32x4_t x, u32x4_t y, fp8_t) {  // sixteen codes, two decoded per instruction
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int b = 0; b < 32; b += 8) s += e4m3_to_f32((x[i] >> b) & 0xFFu) * e4m3_to_f32((y[i] >> b) & 0xFFu);
+        const auto xl = __builtin_amdgcn_cvt_pk_f32_fp8((int)x[i], false), xh = __builtin_amdgcn_cvt_pk_f32_fp8((int)x[i], true);
+        const auto yl = __builtin_amdgcn_cvt_pk_f32_fp8((int)y[i], false), yh = __builtin_amdgcn_cvt_pk_f32_fp8((int)y[i], true);
+        s += xl[0] * yl[0];
+        s += xl[1] * yl[1];
+        s += xh[0] * yh[0];
+        s += xh[1] * yh[1];
     }
     return s;
 }
@@ -386,16 +398,15 @@ int siso_mfma_launch(siso_cache *c, const void *queries, long n, int slices, u64
 int siso_skinny_slices(const siso_cache *c, long n);
 int siso_skinny_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
 
-// Top-k lookups on the MFMA kernels: pass 1 = the phase-1 keys of a lookup planned with c->plan_min_slices;
-// pass 2 lists, per query q, the rows whose scaled product <q, c> / |c| reaches tau[q] (cand[q * cap + i],
-// i < min(cnt[q], cap); cnt counts all of them; cnt must be zero before).  Both passes sum every product in
-// the same order, so a row that set a key in pass 1 compares equal to it in pass 2.
+// Top-k lookups, first phase: groups[q * ng + g].x = the largest scaled product <q, c> / |c| among the 16 rows of group g
+// (-inf if none is finite), its lowest four bits replaced by the row's number in the group; .y = the second largest (its
+// lowest bits are anything).  Row r of group g = 2 * (row / 32) + h is the row 32 * (g / 2) + 4 * (g % 2) + 8 * (r / 4) +
+// r % 4.  ng = 2 * ceil(count / 32); every entry is written.
 #define SISO_TOPK_MAX 32
-#define SISO_TOPK_CAND 128
-int siso_topk_mfma_slices(const siso_cache *c, long n);  // slices of the plan (0 = these kernels cannot serve the cache)
-int siso_topk_mfma_pass1(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
-int siso_topk_mfma_collect(siso_cache *c, const void *queries, long n, int slices, const float *tau, int *cand,
-                           int *cnt, int cap);
+#define SISO_TOPK_GROUP_BYTES (128l << 20)
+int siso_mfma_groups_supported(const siso_cache *c, long n);
+int siso_mfma_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng);
+int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng);
 
 // Self-similarity pair search over `count` rows of the cache's element type and dimension with
 // their inverse lengths (counter already zeroed).  The MFMA kernel reads whole tiles: rows and invn

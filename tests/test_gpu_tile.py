@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import DEV, check_lookup, siso_dtype, to_dev
+from gpu_util import DEV, check_lookup, check_topk, siso_dtype, to_dev
 from paper_2508_18736_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -100,3 +100,20 @@ def test_pairs_at_the_edges_of_the_tiles(siso, dtype, dim, K):
     want = (p > theta).nonzero()
     got = torch.sort(pairs[:, 0].long() * K + pairs[:, 1].long())[0]
     assert total == want.shape[0] and torch.equal(got, torch.sort(want[:, 0] * K + want[:, 1])[0])
+
+
+@pytest.mark.parametrize("dtype,dim,K,n,k", [("f32", 300, 7000, 33, 10), ("bf16", 300, 3100, 130, 32), ("f32", 33, 31, 5, 32),
+                                             ("f32", 384, 16400, 3, 1), ("bf16", 256, 33, 64, 2), ("bf16", 512, 70000, 40, 5)])
+def test_topk_at_the_edges_of_the_groups(siso, oracle, dtype, dim, K, n, k):
+    """Rows one past a group of 32, fewer groups than k, more groups than a list, rows that tie inside a group of 16."""
+    print(f"case: tile topk {dtype} dim={dim} K={K} n={n} k={k}", flush=True)
+    wl = _workload(dtype, dim, K, n)
+    for a in range(0, K - 9, max(9, K // 50)):
+        wl.centroids[a + 8] = wl.centroids[a]     # both in one group of 16
+    cache = siso.SisoCache(dim, K, siso_dtype(dtype))
+    cache.load(to_dev(wl.centroids, dtype))
+    out = cache.lookup_topk(to_dev(wl.queries, dtype), k)
+    oc = oracle.OracleCache(dim, K, dtype)
+    oc.load(wl.centroids)
+    st = check_topk(out, oc.lookup_topk(wl.queries, k + 1 if k < min(K, 32) else k), dtype, "topk")
+    assert st["max_err"] < max(2e-6, dim * 2.0 ** -24)
