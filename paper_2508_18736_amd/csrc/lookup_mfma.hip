@@ -345,12 +345,17 @@ __device__ __forceinline__ void pipe_reduce_keys(float (&bv)[WQ], unsigned (&bb)
 // GROUPS: instead of a running maximum over the slice, the two largest products of every group of 16 rows (the rows one
 // lane holds of a block of 32) go to groups[q * ng + 2 * (row / 32) + h]: the first phase of a top-k lookup
 // (topk.hip).  A store puts 8 bytes into each of 32 lines, which the L2 fills up before it writes them out.
+// COLLECT: every product that reaches the bound of its query is listed (second pass of a top-k lookup over codes):
+// tau[q] = the bound of query q in the units of the products, cand[q * cand_cap + i] = the i-th listed row, cand_cnt[q] = how
+// many rows reached the bound (also beyond cand_cap).  A row is listed exactly once: every product is formed by one lane.
 // STREAM: the centroid loads carry the non-temporal hint (see stream_hint below).
-template <class Cfg, bool GROUPS = false, bool STREAM = false>
+enum { PIPE_KEYS, PIPE_GROUPS, PIPE_COLLECT };  // what k_lookup_pipe does with its products
+template <class Cfg, int MODE = PIPE_KEYS, bool STREAM = false>
 __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_lookup_pipe(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ C, const float *__restrict__ invn, long n, long K, int d,
     int tiles_per_slice, int slices, int nqt, int qb, u64 *__restrict__ keys, float2 *__restrict__ groups,
-    int ng, u64 *__restrict__ board) {
+    int ng, const float *__restrict__ tau, int *__restrict__ cand, int *__restrict__ cand_cnt, int cand_cap,
+    u64 *__restrict__ board) {
     constexpr int WC = Cfg::WC, WQ = Cfg::WQ, NWC = Cfg::NWC, BC = Cfg::BC, BQ = Cfg::BQ, NT = Cfg::NT, NW = Cfg::NW,
                   STAGE = Cfg::STAGE, NLA = Cfg::NLA, NLB = Cfg::NLB, NL = Cfg::NL, NSTAGE = Cfg::NSTAGE, BK = Cfg::BK,
                   RB = Cfg::RB, CPR = Cfg::CPR, RPI = Cfg::RPI, RP = Cfg::RP, KK = Cfg::KK, SUB = 32 * Cfg::RB, ES = Cfg::ES;
@@ -414,6 +419,15 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
     Acc<false, WC, WQ, ES == 1> acc;  // every tile starts from a zero operand, so nothing to clear
     acc.reserve();
+    float tq[WQ];  // COLLECT: the bounds of this lane's query columns (nothing reaches +inf: rows past the batch)
+    if constexpr (MODE == PIPE_COLLECT) {
+#pragma unroll
+        for (int b = 0; b < WQ; ++b) {
+            const long q = q0 + (wq * WQ + b) * 32 + l32;
+            tq[b] = q < n ? tau[q] : INFINITY;
+        }
+    }
+
     // slab t lives in stage t % NSTAGE; (ld_ct, ld_ks, ld_stage) name the slab the next issue fetches.
     // With slab 0 of a tile travel the inverse lengths of the tile's centroids (the rows past the
     // live ones hold NaN), one 4-byte direct load per lane of the first BC/64 waves.
@@ -489,7 +503,24 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             static_for<0, WQ>([&](auto ib) {
                 constexpr int B = decltype(ib)::value;
                 float m = -INFINITY;
-                if constexpr (GROUPS) {
+                if constexpr (MODE == PIPE_COLLECT) {
+                    static_for<0, 16>([&](auto ii) {
+                        constexpr int I = decltype(ii)::value;
+                        m = fmaxf(m, acc.template get<A, B, I>() * w[I >> 2][I & 3]);
+                    });
+                    if (__ballot(m >= tq[B]) != 0) {
+                        const long q = q0 + (wq * WQ + B) * 32 + l32;
+                        const int row0 = (int)(c0 + rb) + 4 * h;  // register I holds row row0 + 8 * (I / 4) + I % 4
+                        static_for<0, 16>([&](auto ii) {
+                            constexpr int I = decltype(ii)::value;
+                            // (the weights of rows past the end are NaN: never listed)
+                            if (acc.template get<A, B, I>() * w[I >> 2][I & 3] >= tq[B]) {
+                                const int slot = atomicAdd(cand_cnt + q, 1);
+                                if (slot < cand_cap) cand[(size_t)q * cand_cap + slot] = row0 + 8 * (I >> 2) + (I & 3);
+                            }
+                        });
+                    }
+                } else if constexpr (MODE == PIPE_GROUPS) {
                     TwoLargest best;
                     static_for<0, 16>([&](auto ii) {
                         constexpr int I = decltype(ii)::value;
@@ -667,7 +698,7 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             sto = sto_next;
         }
     }
-    if constexpr (!GROUPS) {
+    if constexpr (MODE == PIPE_KEYS) {
         __syncthreads();
         pipe_reduce_keys<WQ, NWC, BQ, NT, Cfg::ROWS>(bv, bb, smem, wc, wq, h, l32, tid, q0, n, slices, s, keys);
     }
@@ -1504,6 +1535,11 @@ static bool pipe_plan(const siso_cache *c, long n, int cfg, long want_wgs, PipeP
         const long mall_tps = 8192 / c->dim > 2 ? 8192 / c->dim : 2;
         if (nqt > 1 && tps > mall_tps) tps = mall_tps;
     }
+    if (c->plan_min_slices > 0) {  // a top-k lookup wants many slices: each contributes one row to its bound
+        const long want_s = c->plan_min_slices < ct ? c->plan_min_slices : ct;
+        const long t2 = ct / want_s > 1 ? ct / want_s : 1;
+        if (tps > t2) tps = t2;
+    }
     if (tps > ct) tps = ct;
     // query tiles per unit: 8 when there are that many (a centroid tile fetched into an XCD's L2 then
     // serves 8 workgroups, and 8 query tiles are about what stays resident in a 4 MB L2), fewer when the
@@ -1527,7 +1563,7 @@ static bool pipe_plan(const siso_cache *c, long n, int cfg, long want_wgs, PipeP
     // (3 query tiles over 1,024 centroid tiles: 11 groups of 6-tile slices put twice the work on three XCDs, 482 us;
     // 8 groups of 8-tile slices, 336 us).  Among the lengths up to the one chosen above, take the one with the
     // fewest tile periods on the busiest XCD, a round counted as its tiles plus half a tile for getting started.
-    if (c->opt_tiles_per_slice <= 0 && nqt > 1) {
+    if (c->opt_tiles_per_slice <= 0 && c->plan_min_slices <= 0 && nqt > 1) {
         const long sb = 32 / qb;
         const long lo = tps / 4 > 2 ? tps / 4 : (tps < 2 ? tps : 2);
         auto periods = [&](long t) -> double {  // < 0: the other mapping (every XCD has a share of every group)
@@ -1593,11 +1629,11 @@ static bool stream_hint(const siso_cache *c, const PipePlan &p) {
     return p.nqt == 1 && bytes > SISO_STREAM_BYTES;
 }
 
-template <class Cfg, bool GROUPS, bool STREAM>
+template <class Cfg, int MODE, bool STREAM>
 static int pipe_attr(siso_cache *c) {
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_lookup_pipe<Cfg, GROUPS, STREAM>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_lookup_pipe<Cfg, MODE, STREAM>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
         if (e != hipSuccess) return siso_check_hip(c, e, "hipFuncSetAttribute(k_lookup_pipe)");
         attr_done = true;
@@ -1607,12 +1643,12 @@ static int pipe_attr(siso_cache *c) {
 
 template <class Cfg, bool STREAM>
 static int launch_cfg2(siso_cache *c, const void *queries, long n, const PipePlan &p, u64 *keys) {
-    const int rc = pipe_attr<Cfg, false, STREAM>(c);
+    const int rc = pipe_attr<Cfg, PIPE_KEYS, STREAM>(c);
     if (rc != SISO_OK) return rc;
-    hipLaunchKernelGGL((k_lookup_pipe<Cfg, false, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
+    hipLaunchKernelGGL((k_lookup_pipe<Cfg, PIPE_KEYS, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
                        c->stream, (const bf16_t *)queries, (const bf16_t *)c->cent, c->invn, n, c->count, c->dim,
                        p.tiles_per_slice, p.slices, p.nqt, p.qb, keys, (float2 *)nullptr, 0,
-                       c->board_to_clear);
+                       (const float *)nullptr, (int *)nullptr, (int *)nullptr, 0, c->board_to_clear);
     c->board_to_clear = nullptr;  // taken
     return siso_check_hip(c, hipGetLastError(), "k_lookup_pipe");
 }
@@ -1623,17 +1659,36 @@ static int launch_cfg(siso_cache *c, const void *queries, long n, const PipePlan
 
 template <class Cfg, bool STREAM>
 static int launch_groups2(siso_cache *c, const void *queries, long n, const PipePlan &p, float2 *groups, int ng) {
-    const int rc = pipe_attr<Cfg, true, STREAM>(c);
+    const int rc = pipe_attr<Cfg, PIPE_GROUPS, STREAM>(c);
     if (rc != SISO_OK) return rc;
-    hipLaunchKernelGGL((k_lookup_pipe<Cfg, true, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
+    hipLaunchKernelGGL((k_lookup_pipe<Cfg, PIPE_GROUPS, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
                        c->stream, (const bf16_t *)queries, (const bf16_t *)c->cent, c->invn, n, c->count, c->dim,
-                       p.tiles_per_slice, p.slices, p.nqt, p.qb, (u64 *)nullptr, groups, ng, (u64 *)nullptr);
+                       p.tiles_per_slice, p.slices, p.nqt, p.qb, (u64 *)nullptr, groups, ng, (const float *)nullptr,
+                       (int *)nullptr, (int *)nullptr, 0, (u64 *)nullptr);
     return siso_check_hip(c, hipGetLastError(), "k_lookup_pipe (groups)");
 }
 template <class Cfg>
 static int launch_groups(siso_cache *c, const void *queries, long n, const PipePlan &p, float2 *groups, int ng) {
     return stream_hint(c, p) ? launch_groups2<Cfg, true>(c, queries, n, p, groups, ng)
                              : launch_groups2<Cfg, false>(c, queries, n, p, groups, ng);
+}
+
+template <class Cfg, bool STREAM>
+static int launch_collect2(siso_cache *c, const void *queries, long n, const PipePlan &p, const float *tau, int *cand,
+                           int *cnt, int cap) {
+    const int rc = pipe_attr<Cfg, PIPE_COLLECT, STREAM>(c);
+    if (rc != SISO_OK) return rc;
+    hipLaunchKernelGGL((k_lookup_pipe<Cfg, PIPE_COLLECT, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
+                       c->stream, (const bf16_t *)queries, (const bf16_t *)c->cent, c->invn, n, c->count, c->dim,
+                       p.tiles_per_slice, p.slices, p.nqt, p.qb, (u64 *)nullptr, (float2 *)nullptr, 0, tau, cand, cnt,
+                       cap, (u64 *)nullptr);
+    return siso_check_hip(c, hipGetLastError(), "k_lookup_pipe (collect)");
+}
+template <class Cfg>
+static int launch_collect(siso_cache *c, const void *queries, long n, const PipePlan &p, const float *tau, int *cand,
+                          int *cnt, int cap) {
+    return stream_hint(c, p) ? launch_collect2<Cfg, true>(c, queries, n, p, tau, cand, cnt, cap)
+                             : launch_collect2<Cfg, false>(c, queries, n, p, tau, cand, cnt, cap);
 }
 
 // The wide kernel runs with several query tiles: its workgroups share the centroid lines in L2 either way.  A set
@@ -1740,6 +1795,31 @@ int siso_mfma_groups_launch(siso_cache *c, const void *queries, long n, float2 *
         case 3: return launch_groups<PipeSmall>(c, queries, n, p, groups, ng);
         case 4: return launch_groups<PipeLarge32>(c, queries, n, p, groups, ng);
         default: return launch_groups<PipeLarge>(c, queries, n, p, groups, ng);  // also for the wide kernel's plan: same tiles
+    }
+}
+
+// ----------------------------------------------------------------------------
+// the two passes of a top-k lookup over codes (the caller has set c->plan_min_slices)
+// ----------------------------------------------------------------------------
+int siso_topk_fp8_slices(const siso_cache *c, long n) {
+    PipePlan p;
+    return mfma_plan(c, n, &p) && p.cfg >= 6 && p.cfg <= 8 ? p.slices : 0;
+}
+
+int siso_topk_fp8_pass1(siso_cache *c, long n, int slices, u64 *keys) {
+    PipePlan p;
+    if (!mfma_plan(c, n, &p) || p.slices != slices) return siso_fail(c, SISO_EINVAL, "top-k lookup: plan mismatch");
+    return pipe_launch(c, c->fp8_q, n, p, keys);
+}
+
+int siso_topk_fp8_collect(siso_cache *c, long n, int slices, const float *tau, int *cand, int *cnt, int cap) {
+    PipePlan p;
+    if (!mfma_plan(c, n, &p) || p.slices != slices) return siso_fail(c, SISO_EINVAL, "top-k lookup: plan mismatch");
+    switch (p.cfg) {
+        case 6: return launch_collect<F8Large64>(c, c->fp8_q, n, p, tau, cand, cnt, cap);
+        case 7: return launch_collect<F8Mid64>(c, c->fp8_q, n, p, tau, cand, cnt, cap);
+        case 8: return launch_collect<F8Small64>(c, c->fp8_q, n, p, tau, cand, cnt, cap);
+        default: return siso_fail(c, SISO_EINVAL, "top-k lookup: no collecting kernel for configuration %d", p.cfg);
     }
 }
 

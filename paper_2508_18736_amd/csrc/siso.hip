@@ -1041,6 +1041,9 @@ extern "C" void siso_destroy(siso_cache *c) {
     if (c->fp8_q) (void)hipFree(c->fp8_q);
     if (c->fp8_qinv) (void)hipFree(c->fp8_qinv);
     if (c->topk_groups) (void)hipFree(c->topk_groups);
+    if (c->topk_tau) (void)hipFree(c->topk_tau);
+    if (c->topk_cnt) (void)hipFree(c->topk_cnt);
+    if (c->topk_cand) (void)hipFree(c->topk_cand);
     if (c->counters) (void)hipFree(c->counters);
     if (c->host_pin) (void)hipHostFree(c->host_pin);
     if (c->prof_ev) {

@@ -83,6 +83,13 @@ struct siso_cache {
     // about SISO_TOPK_GROUP_BYTES: larger batches go in pieces), grown on demand
     float2 *topk_groups;
     long topk_groups_cap;
+    // over the codes of a large 8-bit cache: per query the bound, the number of listed rows, a flag "scan this query row by
+    // row" and the listed rows ([topk_cap] floats / ints / ints, [topk_cap][SISO_TOPK_CAND] ints), grown on demand
+    float *topk_tau;
+    int *topk_cnt;
+    int *topk_cand;
+    long topk_cap;
+    int plan_min_slices;  // > 0 while such a lookup plans its passes: at least this many slices (if the tiles allow)
     const siso_cache *fold_master;  // not NULL while siso_fp8_lookup_update runs its lookup on this 8-bit copy
     int mark_in_finalize;  // siso_lookup_update on a large batch: 1 = the finalize step shall take the update's notes
                            // (first member and number of members per centroid), 2 = it has; 0 otherwise
@@ -406,6 +413,13 @@ int siso_skinny_launch(siso_cache *c, const void *queries, long n, int slices, u
 #define SISO_TOPK_GROUP_BYTES (128l << 20)
 int siso_mfma_groups_supported(const siso_cache *c, long n);
 int siso_mfma_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng);
+// Over the codes of a large 8-bit cache, two passes: the phase-1 keys of a lookup planned with c->plan_min_slices (0 slices =
+// these kernels cannot serve the cache), then the rows whose scaled product reaches tau[q] are listed (cand[q * cap + i],
+// i < min(cnt[q], cap); cnt counts all of them; cnt must be zero before).  Both passes sum every product in the same order.
+#define SISO_TOPK_CAND 128
+int siso_topk_fp8_slices(const siso_cache *c, long n);
+int siso_topk_fp8_pass1(siso_cache *c, long n, int slices, u64 *keys);
+int siso_topk_fp8_collect(siso_cache *c, long n, int slices, const float *tau, int *cand, int *cnt, int cap);
 int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng);
 
 // Self-similarity pair search over `count` rows of the cache's element type and dimension with

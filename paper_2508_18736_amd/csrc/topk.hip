@@ -10,7 +10,7 @@
 // this halves the matrix work: 1,000 queries x 60,000 bf16 rows of 768, k = 8: 201 -> 115 us.  With the group maxima
 // alone all 16 rows of a group had to be formed anew: 220 MB of them, 55 us of 144; now 20 us.
 // For an 8-bit cache the batch is quantised first, as in a lookup, and everything here sees codes and the inverse
-// lengths of code rows.
+// lengths of code rows; large 8-bit caches take two passes (siso_lookup_topk tells why).
 // Queries whose candidates do not fit the lists (hundreds of rows equal to the k-th best, a query without length) are
 // taken row by row by their workgroups.
 #include "siso_internal.h"
@@ -125,10 +125,11 @@ __device__ __forceinline__ void write_nan(long q, int k, int *out_idx, float *ou
 //   1. every thread takes the maximum of its share of the groups, and every wave the ceil(k / 4)-th largest of its 64: the
 //      least of the four is reached by at least k groups (a first bound, cheap);
 //   2. the groups that reach it (some more than k) are listed, and the k-th largest of them is the bound that counts;
-//   3. the rows that reach that, less the margin, are multiplied with the query: 16 lanes a row, four rows a wave;
+//   3. the rows that reach that, less the margin, are multiplied with the query, four rows a wave at a time;
 //   4. those that still reach it are ranked by counting.
 // The sums of the first phase and those of step 3 take the same products in another order: they differ by some 1e-7 of
-// |q|, and the row in the lowest bits of a maximum moves it by up to 1.8e-6 of itself; the margin is 8e-6 of |q|.
+// |q| (codes: the products of the 8-bit matrix instructions are off by up to some 1e-5), and the row in the lowest bits of a
+// maximum moves it by up to 1.8e-6 of itself; the margin is 8e-6 of |q| (codes: 1e-4).
 // `vec` = rows are 16-byte aligned and a whole number of 16-byte chunks.
 template <typename T>
 __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, const T *__restrict__ cent,
@@ -209,10 +210,10 @@ __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, cons
         }
         __syncthreads();
         // 1 / |q| = 0 for a query without length: every product is 0, nothing is cut off
-        const float margin = qi > 0.f ? 8e-6f / qi : 0.f;
+        const float slack = sizeof(T) == 1 ? 1e-4f : 8e-6f;
+        const float margin = qi > 0.f ? slack / qi : 0.f;
         const float bound = listed < k ? -INFINITY : bound_s - margin;
-        const float row_bound = bound * qi - 8e-6f;  // (in cosines; -inf * 0 is NaN, and nothing is below a NaN)
-        const int sub = lane >> 4, l16 = lane & 15;
+        const float row_bound = bound * qi - slack;  // (in cosines; -inf * 0 is NaN, and nothing is below a NaN)
         // groups within the margin below the first bound do not stand in the list: they are looked for now (rarely: the
         // first bound is usually further below the k-th largest maximum than that)
         if (first_bound > bound) {
@@ -245,27 +246,48 @@ __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, cons
         __syncthreads();
         const int cands = cand_s;
         if (cands > TOPK_CAND) return false;
-        for (int i = 4 * wave; i < cands; i += 16) {  // four rows a wave
-            const int r = cand[i + sub < cands ? i + sub : i];
-            const bool real = i + sub < cands && r < K;
-            const T *crow = cent + (size_t)(r < K ? r : K - 1) * d;
-            const float w = real ? invn[r] : __uint_as_float(0x7FC00000u);
-            float acc = 0.f;
+        // four rows a wave, their loads in flight together; each is summed as the scan does it (a chunk per lane, then over
+        // the lanes), so that a query's cosines do not depend on which of the two takes it
+        for (int i = 4 * wave; i < cands; i += 16) {
+            const T *crow[4];
+            float acc[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const int r = cand[i + p < cands ? i + p : i];
+                crow[p] = cent + (size_t)(r < K ? r : K - 1) * d;
+                acc[p] = 0.f;
+            }
             if (vec) {
-#pragma unroll 8
-                for (int e = l16 * EPC; e < d; e += 16 * EPC) acc += chunk_dot(sh_q[e / EPC], *(const u32x4_t *)(crow + e), T());
+#pragma unroll 2
+                for (int e = lane * EPC; e < d; e += 64 * EPC) {
+                    u32x4_t x[4];
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) x[p] = *(const u32x4_t *)(crow[p] + e);
+                    const u32x4_t y = sh_q[e / EPC];
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) acc[p] += chunk_dot(y, x[p], T());
+                }
             } else {
-#pragma unroll 8
-                for (int e = l16; e < d; e += 16) acc += widen(((const T *)sh_q)[e]) * widen(crow[e]);
+#pragma unroll 2
+                for (int e = lane; e < d; e += 64) {
+                    const float y = widen(((const T *)sh_q)[e]);
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) acc[p] += y * widen(crow[p][e]);
+                }
             }
 #pragma unroll
-            for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-            const float sv = acc * qi * w;
-            if (l16 == 0 && sv == sv && !(sv < row_bound)) {  // a NaN is never chosen
-                const int at = atomicAdd(&rows_s, 1);
-                if (at < TOPK_ROWS) {
-                    val[at] = sv;
-                    idx[at] = r;
+            for (int p = 0; p < 4; ++p) {
+                acc[p] = wave_sum(acc[p]);
+                if (lane == 0 && i + p < cands && cand[i + p] < K) {
+                    const int r = cand[i + p];
+                    const float sv = acc[p] * qi * invn[r];
+                    if (sv == sv && !(sv < row_bound)) {  // a NaN is never chosen
+                        const int at = atomicAdd(&rows_s, 1);
+                        if (at < TOPK_ROWS) {
+                            val[at] = sv;
+                            idx[at] = r;
+                        }
+                    }
                 }
             }
         }
@@ -291,16 +313,142 @@ __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, cons
     if (!from_lists()) scan_query(sh_q, qi, cent, invn, K, d, k, vec, q, val, idx, out_idx, out_sim);
 }
 
-// Every query row by row, where no first phase serves the cache.
+// Codes of a large cache, pass 1 -> bound: tau[q] = value of the k-th largest key of query q (-inf with fewer than k keys: every
+// row is wanted then).  One 256-thread block per query; the keys sit in LDS, k rounds of "largest left".
+__global__ __launch_bounds__(256) void k_topk_bound(const u64 *__restrict__ keys, int slices, int k, float *tau, int *cnt,
+                                                     int *scan) {
+    extern __shared__ u64 sk[];  // [slices]
+    __shared__ u64 wmax[4];
+    __shared__ int wpos[4];
+    const long q = blockIdx.x;
+    const int t = threadIdx.x;
+    for (int s = t; s < slices; s += 256) sk[s] = keys[(size_t)q * slices + s];
+    __syncthreads();
+    u64 kth = 0;
+    for (int r = 0; r < k; ++r) {
+        u64 best = 0;
+        int pos = -1;
+        for (int s = t; s < slices; s += 256)
+            if (sk[s] > best) {
+                best = sk[s];
+                pos = s;
+            }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const u64 ob = __shfl_xor(best, off);
+            const int op = __shfl_xor(pos, off);
+            if (ob > best) {  // keys of different slices differ (they name different rows)
+                best = ob;
+                pos = op;
+            }
+        }
+        if ((t & 63) == 0) {
+            wmax[t >> 6] = best;
+            wpos[t >> 6] = pos;
+        }
+        __syncthreads();
+        best = wmax[0];
+        pos = wpos[0];
+        for (int w = 1; w < 4; ++w)
+            if (wmax[w] > best) {
+                best = wmax[w];
+                pos = wpos[w];
+            }
+        kth = best;
+        __syncthreads();
+        if (best == 0) break;  // fewer than k keys
+        if (t == 0) sk[pos] = 0;
+        __syncthreads();
+    }
+    if (t == 0) {
+        tau[q] = kth == 0 ? -INFINITY : unordered_bits((unsigned)(kth >> 32));
+        cnt[q] = 0;
+        scan[q] = 0;
+    }
+}
+
+// Listed rows -> result: exact cosines of the listed rows of query q (one wave per row), ranked; queries
+// whose list overflowed are marked for the scan instead.  One 256-thread block per query.
+template <typename T>
+__global__ __launch_bounds__(256) void k_topk_select(const T *__restrict__ Q, const T *__restrict__ cent,
+                                                      const float *__restrict__ invn, long K, int d, int k,
+                                                      const int *__restrict__ cand, const int *__restrict__ cnt, int cap,
+                                                      const float *__restrict__ q_inv, int *scan, int *out_idx,
+                                                      float *out_sim) {
+    constexpr int EPC = 16 / (int)sizeof(T);
+    __shared__ float sh_f[4];
+    __shared__ u32x4_t sh_q[SISO_MAX_DIM / EPC];
+    __shared__ float val[SISO_TOPK_CAND];
+    __shared__ int idx[SISO_TOPK_CAND];
+    const long q = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const T *qrow = Q + (size_t)q * d;
+    float ss = 0.f;
+    for (int e = t * EPC; e < d; e += 256 * EPC) {
+        const u32x4_t v = *(const u32x4_t *)(qrow + e);
+        sh_q[e / EPC] = v;
+        if (!q_inv) ss += chunk_dot(v, v, T());
+    }
+    ss = wave_sum(ss);
+    if (lane == 0) sh_f[wave] = ss;
+    __syncthreads();
+    // (q_inv: the inverse lengths that came with the quantised batch)
+    const float qi = q_inv ? q_inv[q] : inv_length((sh_f[0] + sh_f[1]) + (sh_f[2] + sh_f[3]));
+    const int listed = cnt[q];
+    if (!(qi == qi)) {  // a query holding a NaN or an infinity
+        for (int r = t; r < k; r += 256) {
+            out_idx[(size_t)q * k + r] = -1;
+            out_sim[(size_t)q * k + r] = __uint_as_float(0x7FC00000u);
+        }
+        return;
+    }
+    if (listed > cap) {  // more rows at the bound than the list holds: the scan takes this query
+        if (t == 0) scan[q] = 1;
+        return;
+    }
+    for (int i = wave; i < listed; i += 4) {
+        const int r = cand[(size_t)q * cap + i];
+        const T *crow = cent + (size_t)r * d;
+        float acc = 0.f;
+        for (int e0 = lane * EPC; e0 < d; e0 += 64 * EPC) acc += chunk_dot(sh_q[e0 / EPC], *(const u32x4_t *)(crow + e0), T());
+        acc = wave_sum(acc);
+        const float sv = acc * qi * invn[r];
+        if (lane == 0) {
+            val[i] = sv;
+            idx[i] = sv == sv ? r : -1;  // a NaN is never chosen
+        }
+    }
+    __syncthreads();
+    // rank by counting the entries that come before (all differ in their index)
+    if (t < listed && idx[t] >= 0) {
+        int before = 0;
+        for (int j = 0; j < listed; ++j) before += ranks_before(val[j], idx[j], val[t], idx[t]) ? 1 : 0;
+        if (before < k) {
+            out_idx[(size_t)q * k + before] = idx[t];
+            out_sim[(size_t)q * k + before] = val[t];
+        }
+    }
+    // fewer usable rows than k: the rest is empty
+    int usable = 0;
+    for (int j = 0; j < listed; ++j) usable += idx[j] >= 0 ? 1 : 0;
+    for (int r = usable + t; r < k; r += 256) {
+        out_idx[(size_t)q * k + r] = -1;
+        out_sim[(size_t)q * k + r] = -INFINITY;
+    }
+}
+
+// Every query row by row, where no first phase serves the cache (with `scan`: those with scan[q] != 0).
 template <typename T>
 __global__ __launch_bounds__(256) void k_topk_scan(const T *__restrict__ Q, const T *__restrict__ cent,
                                                     const float *__restrict__ invn, long K, int d, int k, int vec,
-                                                    const float *__restrict__ q_inv, int *out_idx, float *out_sim) {
+                                                    const float *__restrict__ q_inv, const int *__restrict__ scan, int *out_idx,
+                                                    float *out_sim) {
     __shared__ float sh_f[4];
     __shared__ u32x4_t sh_q[SISO_MAX_DIM * sizeof(T) / 16];
     __shared__ float val[4 * SISO_TOPK_MAX];
     __shared__ int idx[4 * SISO_TOPK_MAX];
     const long q = blockIdx.x;
+    if (scan && !scan[q]) return;
     const float ss = wave_sum(stage_query(Q + (size_t)q * d, d, vec, true, sh_q));
     if ((threadIdx.x & 63) == 0) sh_f[threadIdx.x >> 6] = ss;
     __syncthreads();
@@ -325,6 +473,55 @@ int ensure_topk_workspace(siso_cache *c, long cells) {
     return SISO_OK;
 }
 
+int ensure_two_pass_workspace(siso_cache *c, long n) {
+    if (n <= c->topk_cap) return SISO_OK;
+    if (c->topk_tau) {
+        const int rc = siso_check_hip(c, hipStreamSynchronize(c->stream), "siso_lookup_topk: synchronize");
+        if (rc != SISO_OK) return rc;
+        (void)hipFree(c->topk_tau);
+        (void)hipFree(c->topk_cnt);
+        (void)hipFree(c->topk_cand);
+        c->topk_tau = nullptr;
+        c->topk_cnt = nullptr;
+        c->topk_cand = nullptr;
+        c->topk_cap = 0;
+    }
+    bool ok = hipMalloc((void **)&c->topk_tau, (size_t)n * sizeof(float)) == hipSuccess;
+    ok = ok && hipMalloc((void **)&c->topk_cnt, (size_t)n * 2 * sizeof(int)) == hipSuccess;  // counts, then scan flags
+    ok = ok && hipMalloc((void **)&c->topk_cand, (size_t)n * SISO_TOPK_CAND * sizeof(int)) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        if (c->topk_tau) (void)hipFree(c->topk_tau);
+        if (c->topk_cnt) (void)hipFree(c->topk_cnt);
+        c->topk_tau = nullptr;
+        c->topk_cnt = nullptr;
+        c->topk_cand = nullptr;
+        return siso_fail(c, SISO_ENOMEM, "siso_lookup_topk: workspace for %ld queries", n);
+    }
+    c->topk_cap = n;
+    return SISO_OK;
+}
+
+// Codes of a large cache: see siso_lookup_topk.
+int two_pass_launch(siso_cache *c, long n, int k, int slices, int *out_idx, float *out_sim) {
+    int rc = ensure_two_pass_workspace(c, n);
+    if (rc == SISO_OK) rc = siso_ensure_keys(c, n * (long)slices);
+    if (rc == SISO_OK) rc = siso_topk_fp8_pass1(c, n, slices, c->keys);
+    if (rc != SISO_OK) return rc;
+    const fp8_t *Q = (const fp8_t *)c->fp8_q, *cent = (const fp8_t *)c->cent;
+    int *cnt = c->topk_cnt, *flags = c->topk_cnt + c->topk_cap;
+    hipLaunchKernelGGL(k_topk_bound, dim3((unsigned)n), dim3(256), (size_t)slices * sizeof(u64), c->stream, c->keys, slices, k,
+                       c->topk_tau, cnt, flags);
+    rc = siso_check_hip(c, hipGetLastError(), "k_topk_bound");
+    if (rc == SISO_OK) rc = siso_topk_fp8_collect(c, n, slices, c->topk_tau, c->topk_cand, cnt, SISO_TOPK_CAND);
+    if (rc != SISO_OK) return rc;
+    hipLaunchKernelGGL(k_topk_select<fp8_t>, dim3((unsigned)n), dim3(256), 0, c->stream, Q, cent, c->invn, c->count, c->dim, k,
+                       c->topk_cand, cnt, SISO_TOPK_CAND, c->fp8_qinv, flags, out_idx, out_sim);
+    hipLaunchKernelGGL(k_topk_scan<fp8_t>, dim3((unsigned)n), dim3(256), 0, c->stream, Q, cent, c->invn, c->count, c->dim, k, 1,
+                       c->fp8_qinv, flags, out_idx, out_sim);
+    return siso_check_hip(c, hipGetLastError(), "k_topk_select, k_topk_scan");
+}
+
 // what the first phase runs on: the pipelined kernels, the tiled kernel, or neither (then every query is scanned)
 enum { PHASE_NONE, PHASE_MFMA, PHASE_TILE };
 
@@ -334,7 +531,7 @@ int topk_launch(siso_cache *c, const T *Q, long n, int k, int phase, const float
     const int vec = ((c->dim * sizeof(T)) % 16 == 0 && ((uintptr_t)Q & 15) == 0) ? 1 : 0;
     if (phase == PHASE_NONE) {
         hipLaunchKernelGGL(k_topk_scan<T>, dim3((unsigned)n), dim3(256), 0, c->stream, Q, cent, c->invn, c->count, c->dim, k, vec,
-                           q_inv, out_idx, out_sim);
+                           q_inv, (const int *)nullptr, out_idx, out_sim);
         return siso_check_hip(c, hipGetLastError(), "k_topk_scan");
     }
     // pieces of the batch whose maxima take about SISO_TOPK_GROUP_BYTES: they stay in the memory-side cache
@@ -371,6 +568,19 @@ extern "C" int siso_lookup_topk(siso_cache *c, const void *queries, long n, int 
         if (rc == SISO_OK) rc = siso_fp8_quantize_batch(c, queries, n);
         if (rc != SISO_OK) return rc;
         rows = c->fp8_q;
+    }
+    // Codes of a cache of at least 512 * k rows: two passes, the second of which lists the rows at a bound from the first.  The
+    // products of the 8-bit matrix instructions are some 1e-5 off, which decides between neighbours at that bound; one
+    // pass with a margin for that would rank about one entry in a thousand otherwise than it has been.
+    if (fp8 && c->count >= 512L * k) {
+        c->plan_min_slices = 8 * k;
+        const int slices = siso_topk_fp8_slices(c, n);
+        if (slices >= 2 * k && slices <= 4096) {  // (the bound kernel keeps a query's keys in LDS)
+            const int rc = two_pass_launch(c, n, k, slices, out_idx, out_sim);
+            c->plan_min_slices = 0;
+            return rc;
+        }
+        c->plan_min_slices = 0;
     }
     // (pieces of a batch start whole rows further on, so where the batch is aligned they are)
     int phase = PHASE_NONE;
