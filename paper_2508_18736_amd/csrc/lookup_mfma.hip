@@ -1828,6 +1828,10 @@ int siso_topk_fp8_collect(siso_cache *c, long n, int slices, const float *tau, i
 // ----------------------------------------------------------------------------
 int siso_pairs_mfma_supported(const siso_cache *c, long count) {
     if (c->opt_merge_config == 1) return 0;  // 1 = force the kernel of lookup_tile.hip
+    // Up to 4,096 rows there are at most 136 pairs of tiles for 256 compute units: the smaller tiles of lookup_tile.hip serve
+    // more of them (a search with its read-back, rows of 768 elements, pipelined against tiled: 1,000 rows 36.6 / 25.0 us,
+    // 2,000 38.2 / 30.1, 4,000 57.6 / 50.8, 8,000 95.0 / 95.5; of 256 elements: 26.7 / 22.5, 27.2 / 24.1, 34.9 / 35.4, 47.8 / 55.9)
+    if (c->opt_merge_config == 0 && count <= 4096) return 0;
     return c->dtype == SISO_BF16 && c->dim % 64 == 0 && c->dim >= 128 && count >= 2;
 }
 

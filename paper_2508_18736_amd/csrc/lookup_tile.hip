@@ -23,19 +23,25 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <int WC_, int WQ_, int NWC_, int NWQ_>
+template <int WC_, int WQ_, int NWC_, int NWQ_, int DEPTH_, int CHAINS_>
 struct TileCfg {
     static constexpr int WC = WC_, WQ = WQ_, NWC = NWC_, NWQ = NWQ_;  // 32-row blocks per wave, waves, on either side
     static constexpr int BC = 32 * WC * NWC, BQ = 32 * WQ * NWQ;
     static constexpr int JC = BC / 32, JQ = BQ / 32;                  // 16-byte chunks per thread and slab
     static constexpr int STAGE = (BC + BQ) * 128;
+    static constexpr int DEPTH = DEPTH_;                              // slabs on their way in registers
+    // Partial sums of a product, added at the end: two (half as many roundings in a row) where the registers allow it and
+    // the sums need not be those of the pipelined kernels.  With one the products are added in their order, and batches of
+    // at most 64 give the same bits whichever kernel a cache's size sends them to.
+    static constexpr int CHAINS = CHAINS_;
+    static_assert(DEPTH % 2 == 0, "slab number i of a round goes to stage i % 2");
     static_assert(NWC * NWQ == 4, "four waves");
     static_assert(BC <= SISO_PAD_ROWS, "the inverse lengths of a whole last tile are readable");
     static_assert(NWC * BQ * 8 <= 2 * STAGE, "the reduction fits in the stages");
 };
-typedef TileCfg<2, 2, 2, 2> TileLarge;  // 128 x 128
-typedef TileCfg<1, 1, 2, 2> TileSmall;  // 64 x 64
-typedef TileCfg<1, 1, 4, 1> TileFew;    // 128 centroids x 32 queries
+typedef TileCfg<2, 2, 2, 2, 2, 1> TileLarge;  // 128 x 128
+typedef TileCfg<1, 1, 2, 2, 4, 2> TileSmall;  // 64 x 64
+typedef TileCfg<1, 1, 4, 1, 4, 1> TileFew;    // 128 centroids x 32 queries
 
 // One 16-byte chunk of a row at element k; W = bytes every row is aligned to (16, 8, or the element).  Elements at
 // d and beyond are read from the row's start and zeroed later (zero_tail), so that nothing waits here.
@@ -114,7 +120,7 @@ __device__ __forceinline__ void tile_stream(const T *__restrict__ A, long a_rows
     const T *ap[Cfg::JC];
     long la = a0;   // first row of the tile being loaded
     int ls = 0;     // its slab
-    u32x4_t reg[2][Cfg::JC + Cfg::JQ];
+    u32x4_t reg[Cfg::DEPTH][Cfg::JC + Cfg::JQ];
     auto load = [&](u32x4_t(&r)[Cfg::JC + Cfg::JQ]) __attribute__((always_inline)) {
         if (ls == 0) {
 #pragma unroll
@@ -136,13 +142,18 @@ __device__ __forceinline__ void tile_stream(const T *__restrict__ A, long a_rows
     const int put = row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4);
     const int swz = (lane >> 1) & 7, h = lane >> 5;
     const int get_a = (wc * 32 * Cfg::WC + (lane & 31)) * 128, get_b = (Cfg::BC + wq * 32 * Cfg::WQ + (lane & 31)) * 128;
-    f32x16 acc[Cfg::WC][Cfg::WQ];
+    f32x16 acc[Cfg::CHAINS][Cfg::WC][Cfg::WQ];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < Cfg::WC; ++i)
+        for (int h2 = 0; h2 < Cfg::CHAINS; ++h2)
 #pragma unroll
-        for (int j = 0; j < Cfg::WQ; ++j)
+            for (int i = 0; i < Cfg::WC; ++i)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                for (int j = 0; j < Cfg::WQ; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[h2][i][j][e] = 0.f;
+    };
+    clear();
     long ca = a0;  // first row of the tile being multiplied
     int cs = 0;    // its slab
     // one slab: out of the registers into LDS, the load after next on its way, multiply.  One barrier: a stage is
@@ -168,25 +179,24 @@ __device__ __forceinline__ void tile_stream(const T *__restrict__ A, long a_rows
 #pragma unroll
             for (int i = 0; i < Cfg::WC; ++i)
 #pragma unroll
-                for (int j = 0; j < Cfg::WQ; ++j) acc[i][j] = product(a[i], b[j], acc[i][j], T());
+                for (int j = 0; j < Cfg::WQ; ++j)
+                    acc[s % Cfg::CHAINS][i][j] = product(a[i], b[j], acc[s % Cfg::CHAINS][i][j], T());
         }
         if (++cs == nslab) {
-            done(ca, acc);
+            if constexpr (Cfg::CHAINS == 2) acc[0][0][0] += acc[1][0][0];
+            done(ca, acc[0]);
             cs = 0;
             ca += Cfg::BC;
-#pragma unroll
-            for (int i = 0; i < Cfg::WC; ++i)
-#pragma unroll
-                for (int j = 0; j < Cfg::WQ; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            clear();
         }
     };
-    if (total > 0) load(reg[0]);
-    if (total > 1) load(reg[1]);
-    for (long it = 0; it < total; it += 2) {
-        step(reg[0], lds, it + 2 < total);
-        if (it + 1 < total) step(reg[1], lds + Cfg::STAGE, it + 3 < total);
+#pragma unroll
+    for (int i = 0; i < Cfg::DEPTH; ++i)
+        if (i < total) load(reg[i]);
+    for (long it = 0; it < total; it += Cfg::DEPTH) {
+#pragma unroll
+        for (int i = 0; i < Cfg::DEPTH; ++i)
+            if (it + i < total) step(reg[i], lds + (i & 1) * Cfg::STAGE, it + i + Cfg::DEPTH < total);
     }
 }
 
@@ -202,7 +212,7 @@ inline unsigned xcd_grid(long total) { return (unsigned)((total + 7) / 8 * 8); }
 // Phase 1 of a lookup: the best scaled product of every query of a tile with the rows of a slice, as a key that names
 // the row.  GROUPS: of a top-k lookup: the two largest products of every group of 16 rows instead (see siso_internal.h).
 template <class Cfg, int W, typename T, bool GROUPS = false>
-__global__ __launch_bounds__(256, 2) void k_lookup_tile(const T *__restrict__ Q, const T *__restrict__ cent,
+__global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_tile(const T *__restrict__ Q, const T *__restrict__ cent,
                                                       const float *__restrict__ invn, long n, long K, int d,
                                                       int tiles_per_slice, int slices, int qtiles, u64 *keys, u64 *board,
                                                       float2 *groups, int ng) {
@@ -344,7 +354,8 @@ TilePlan tile_plan(const siso_cache *c, long n) {
     TilePlan p;
     auto tiles = [](long rows, int per) { return (rows + per - 1) / per; };
     // the large tile needs at least two of them per compute unit to be worth its fewer reads
-    p.cfg = n <= 32 ? 0 : tiles(c->count, 128) * tiles(n, 128) >= 512 ? 2 : 1;
+    // (few queries: up to 64 in bf16 and in codes, see TileCfg; a second tile of them finds the rows in L2)
+    p.cfg = n <= (c->dtype == SISO_F32 ? 32 : 64) ? 0 : tiles(c->count, 128) * tiles(n, 128) >= 512 ? 2 : 1;
     const int bc = p.cfg == 1 ? 64 : 128, bq = p.cfg == 0 ? 32 : p.cfg == 1 ? 64 : 128;
     const long resident = p.cfg == 2 ? 512 : 1024;  // workgroups the chip holds at a time
     const long ct = tiles(c->count, bc), qt = tiles(n, bq);
@@ -408,6 +419,17 @@ int pairs_launch_t(siso_cache *c, const void *rows, const float *invn, long coun
 }
 
 }  // namespace
+
+// Is a bf16 batch that the pipelined kernels could take better off here?  Their workgroups have tiles of 256 rows x up to
+// 256 queries, one per compute unit: a small problem leaves most units without one, and the few that work pass through
+// the whole dimension at the pace of a single workgroup.  Measured, lookup of n queries among K rows of 768 elements, pipelined
+// against tiled, us: K 1,000: n 1 13.5 / 11.5, n 64 14.7 / 12.0, n 256 26.3 / 11.6, n 1,024 28.7 / 12.5; K 16,000:
+// n 32 18.6 / 12.1, n 128 21.1 / 13.7, n 256 31.8 / 19.7, n 1,024 32.3 / 35.3; K 64,000: n 64 22.0 / 25.1, n 256 33.2 / 35.7.
+// With about half the units busy (126 such tiles: 31.8 against 32.3; of 256 elements 17.9 against 16.5) the two meet.
+int siso_tile_preferred(const siso_cache *c, long n) {
+    const long tiles = (c->count + 255) / 256 * ((n + 255) / 256);
+    return c->dtype == SISO_BF16 && c->opt_mfma_config == 0 && tiles < 112;
+}
 
 int siso_tile_slices(const siso_cache *c, long n) { return c->count < 1 || n < 1 ? 1 : tile_plan(c, n).slices; }
 

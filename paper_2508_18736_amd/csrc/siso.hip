@@ -1140,6 +1140,7 @@ extern "C" int siso_import(siso_cache *c, const void *centroids, const float *me
 
 static int choose_path(const siso_cache *c, long n) {
     if (c->path != SISO_PATH_AUTO) return c->path;
+    if (siso_tile_preferred(c, n)) return SISO_PATH_SCALAR;
     if (n <= 64 && siso_skinny_slices(c, n) > 0) return SISO_PATH_SKINNY;
     if (siso_mfma_slices(c, n) > 0) return SISO_PATH_MFMA;
     return SISO_PATH_SCALAR;

@@ -585,7 +585,7 @@ extern "C" int siso_lookup_topk(siso_cache *c, const void *queries, long n, int 
     // (pieces of a batch start whole rows further on, so where the batch is aligned they are)
     int phase = PHASE_NONE;
     if (c->count > 0) {
-        if (((uintptr_t)rows & 15) == 0 && siso_mfma_groups_supported(c, n)) phase = PHASE_MFMA;
+        if (((uintptr_t)rows & 15) == 0 && !siso_tile_preferred(c, n) && siso_mfma_groups_supported(c, n)) phase = PHASE_MFMA;
         else if (!fp8) phase = PHASE_TILE;
     }
     return c->dtype == SISO_F32 ? topk_launch<float>(c, (const float *)rows, n, k, phase, nullptr, out_idx, out_sim)
