@@ -79,29 +79,62 @@ __device__ __forceinline__ float block_sum256(float v, float *sh) {
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// siso_load: store rows verbatim, mean = row / |row|, size = counts or 1, invn = 1/|row|.
+// siso_load: store rows verbatim, mean = row / |row|, size = counts or 1, invn = 1/|row|.  One wave per row, whole
+// 16-byte chunks per lane if the rows allow it (`vec`); the second pass finds the row in the caches.  Bound by memory: 131,072
+// rows of 768 bf16 elements move 805 MB; element by element, a block per row, they took 341 us, this way 170 us.
 template <typename T>
 __global__ __launch_bounds__(256) void k_load_rows(const T *__restrict__ src, const int *__restrict__ counts, T *cent,
                                                     float *mean, int *size, float *invn, float *locality,
-                                                    unsigned *access, int d) {
-    __shared__ float sh[4];
-    const long k = blockIdx.x;
+                                                    unsigned *access, long K, int d, int vec) {
+    constexpr int EPC = 16 / (int)sizeof(T);
+    const long k = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (k >= K) return;
     const T *row = src + (size_t)k * d;
+    T *cent_row = cent + (size_t)k * d;
+    float *mean_row = mean + (size_t)k * d;
     float ss = 0.f;
-    for (int e = threadIdx.x; e < d; e += 256) {
-        float x = widen(row[e]);
-        ss += x * x;
+    if (vec) {
+#pragma unroll 4
+        for (int e = lane * EPC; e < d; e += 64 * EPC) {
+            const u32x4_t v = *(const u32x4_t *)(row + e);
+            ss += chunk_dot(v, v, T());
+        }
+    } else {
+        for (int e = lane; e < d; e += 64) ss += widen(row[e]) * widen(row[e]);
     }
-    const float n2 = block_sum256(ss, sh);
+    const float n2 = wave_sum(ss);
     const float inv = inv_length(n2);
     const bool ok = (inv == inv) && inv > 0.f;
     const float nrm = sqrtf(n2);
-    for (int e = threadIdx.x; e < d; e += 256) {
-        T x = row[e];
-        cent[(size_t)k * d + e] = x;
-        mean[(size_t)k * d + e] = ok ? widen(x) / nrm : 0.f;
+    if (vec) {
+#pragma unroll 2
+        for (int e = lane * EPC; e < d; e += 64 * EPC) {
+            const u32x4_t v = *(const u32x4_t *)(row + e);
+            *(u32x4_t *)(cent_row + e) = v;
+            float x[EPC];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (sizeof(T) == 4) {
+                    x[i] = __uint_as_float(v[i]);
+                } else {
+                    x[2 * i] = __uint_as_float(v[i] << 16);
+                    x[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < EPC; i += 4)
+                *(float4 *)(mean_row + e + i) = ok ? make_float4(x[i] / nrm, x[i + 1] / nrm, x[i + 2] / nrm, x[i + 3] / nrm)
+                                                   : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    } else {
+        for (int e = lane; e < d; e += 64) {
+            const T x = row[e];
+            cent_row[e] = x;
+            mean_row[e] = ok ? widen(x) / nrm : 0.f;
+        }
     }
-    if (threadIdx.x == 0) {
+    if (lane == 0) {
         int s = counts ? counts[k] : 1;
         size[k] = s < 1 ? 1 : s;
         invn[k] = inv;
@@ -643,13 +676,6 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
 // group merge: lock-free union-find (the lower index becomes the root), group
 // means by the group's root, stable compaction.
 // ============================================================================
-__global__ void k_pairs_validate(const int *__restrict__ pairs, long n_pairs, long K, u64 *bad) {
-    const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_pairs) return;
-    const int a = pairs[2 * p], b = pairs[2 * p + 1];
-    if (a < 0 || b < 0 || a >= K || b >= K || a == b) atomicAdd(bad, 1ull);
-}
-
 __global__ void k_uf_init(int *parent, unsigned char *touched, int *members_of, int *cursor, long K) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < K) {
@@ -660,14 +686,9 @@ __global__ void k_uf_init(int *parent, unsigned char *touched, int *members_of, 
     }
 }
 
-// Member lists of the groups: how many rows each root leads (itself included), then, once the counts
-// have been scanned into list starts, the rows themselves (in the order they arrive; the root's block
-// sorts its list).  Only rows that occur in a pair take part.
-__global__ void k_group_count(const int *__restrict__ root, const unsigned char *__restrict__ touched, long K,
-                              int *members_of) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < K && touched[i]) atomicAdd(&members_of[root[i]], 1);
-}
+// Member lists of the groups: how many rows each root leads (k_uf_roots counts them, itself included), then, once the
+// counts have been scanned into list starts, the rows themselves (in the order they arrive; the root's block sorts
+// its list).  Only rows that occur in a pair take part.
 __global__ void k_group_fill(const int *__restrict__ root, const unsigned char *__restrict__ touched, long K,
                              const int *__restrict__ first, int *cursor, int *list) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -685,11 +706,16 @@ __device__ __forceinline__ int uf_find(const int *parent, int x) {
     return x;
 }
 
-// Parents only ever decrease, so every retry makes progress and the loop ends.
-__global__ void k_uf_hook(const int *__restrict__ pairs, long n_pairs, int *parent, unsigned char *touched) {
+// Parents only ever decrease, so every retry makes progress and the loop ends.  Pairs that name a row twice or one that
+// is not there are passed over and counted: the host looks at the count before anything of the cache is touched.
+__global__ void k_uf_hook(const int *__restrict__ pairs, long n_pairs, long K, int *parent, unsigned char *touched, u64 *bad) {
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n_pairs) return;
     int a = pairs[2 * p], b = pairs[2 * p + 1];
+    if (a < 0 || b < 0 || a >= K || b >= K || a == b) {
+        atomicAdd(bad, 1ull);
+        return;
+    }
     touched[a] = 1;
     touched[b] = 1;
     for (;;) {
@@ -704,153 +730,240 @@ __global__ void k_uf_hook(const int *__restrict__ pairs, long n_pairs, int *pare
     }
 }
 
-__global__ void k_uf_roots(const int *__restrict__ parent, int *root, long K) {
+__global__ void k_uf_roots(const int *__restrict__ parent, const unsigned char *__restrict__ touched, int *root, int *members_of,
+                           long K) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < K) root[i] = uf_find(parent, (int)i);
+    if (i >= K) return;
+    const int r = uf_find(parent, (int)i);
+    root[i] = r;
+    if (touched[i]) atomicAdd(&members_of[r], 1);
 }
 
-// One block per row; only roots of groups with at least two rows work.
+// A block looks after rows_per_block (at most 64) consecutive rows: those that are the root of a group of at least two rows are
+// given their group's mean, one after the other, four members' loads in flight.  (A block per row has nothing to do in
+// most of them: 131,072 rows in groups of eight took 252 us, 16 rows per block 152 us; 403 MB of means are read.  A few
+// thousand rows are better off with a block each: all groups at the same time.)
+// UPD_MAXE_T = elements of a row per thread (4 for dim <= 1024, else 16).
 #define GROUP_LIST_MAX 1024  // members of a group that its block sorts in LDS; larger groups are searched for
-template <typename T>
+template <typename T, int UPD_MAXE_T>
 __global__ __launch_bounds__(256) void k_group_mean(const int *__restrict__ root, const unsigned char *__restrict__ touched,
                                                      long K, const int *__restrict__ members_of,
                                                      const int *__restrict__ first, const int *__restrict__ list,
                                                      T *cent, float *mean, int *size, float *invn,
-                                                     float *locality, unsigned *access, int d) {
+                                                     float *locality, unsigned *access, int d, int rows_per_block) {
     __shared__ float sh[4];
     __shared__ u64 masks[4];
     __shared__ int raw[GROUP_LIST_MAX], sorted[GROUP_LIST_MAX];
-    const long r = blockIdx.x;
-    const int t = threadIdx.x;
-    if (!touched[r] || root[r] != (int)r) return;
-    float acc[UPD_MAXE];
+    const int t = threadIdx.x, lane = t & 63;
+    const long r_lane = (long)blockIdx.x * rows_per_block + lane;
+    u64 roots = __ballot(lane < rows_per_block && r_lane < K && touched[r_lane] && root[r_lane] == (int)r_lane);  // the same in every wave
+    for (; roots != 0; roots &= roots - 1) {
+        const long r = (long)blockIdx.x * rows_per_block + __ffsll((long long)roots) - 1;
+        float acc[UPD_MAXE_T];
 #pragma unroll
-    for (int e = 0; e < UPD_MAXE; ++e) acc[e] = 0.f;
-    double wsum = 0.0;
-    int members = 0;
-    float loc = 0.f;  // cluster sizes of Algorithm 1 add up, in ascending order of the members
-    u64 refs = 0;     // so do the access counts, saturating at infinity
-    auto take = [&](long jj) {
-        const float wgt = (float)size[jj];
+        for (int e = 0; e < UPD_MAXE_T; ++e) acc[e] = 0.f;
+        double wsum = 0.0;
+        int members = 0;
+        float loc = 0.f;  // cluster sizes of Algorithm 1 add up, in ascending order of the members
+        u64 refs = 0;     // so do the access counts, saturating at infinity
+        // up to four members at a time: their loads are in flight together, the sums take them in order
+        auto take = [&](const long(&jj)[4], int many) __attribute__((always_inline)) {
+            float x[4][UPD_MAXE_T], lo[4];
+            int sz[4];
+            unsigned ac[4];
 #pragma unroll
-        for (int e = 0; e < UPD_MAXE; ++e) {
-            const int col = t + e * 256;
-            if (col < d) acc[e] += wgt * mean[(size_t)jj * d + col];
-        }
-        wsum += (double)size[jj];
-        loc = loc + locality[jj];
-        refs += access[jj];
-        ++members;
-    };
-    const int listed = members_of[r];
-    if (listed <= GROUP_LIST_MAX) {
-        // the list arrives in no particular order; the sums take the members in ascending order, so the
-        // result does not depend on scheduling: every thread places its entries by counting the smaller ones
-        const int lo = first[r];
-        for (int i = t; i < listed; i += 256) raw[i] = list[lo + i];
-        __syncthreads();
-        for (int i = t; i < listed; i += 256) {
-            const int mine = raw[i];
-            int below = 0;
-            for (int k = 0; k < listed; ++k) below += raw[k] < mine ? 1 : 0;
-            sorted[below] = mine;
-        }
-        __syncthreads();
-        for (int p = 0; p < listed; ++p) take(sorted[p]);
-    } else
-    for (long base = r - (r & 255); base < K; base += 256) {
-        const long j = base + t;
-        const bool m = j < K && j >= r && root[j] == (int)r;
-        const u64 mask = __ballot(m);
-        __syncthreads();
-        if ((t & 63) == 0) masks[t >> 6] = mask;
-        __syncthreads();
-        for (int w = 0; w < 4; ++w) {
-            u64 mm = masks[w];
-            while (mm) {
-                const int b = __ffsll((long long)mm) - 1;
-                mm &= mm - 1;
-                take(base + w * 64 + b);
+            for (int m = 0; m < 4; ++m) {
+#pragma unroll
+                for (int e = 0; e < UPD_MAXE_T; ++e) {
+                    const int col = t + e * 256;
+                    x[m][e] = mean[(size_t)jj[m] * d + (col < d ? col : 0)];
+                }
+                sz[m] = size[jj[m]];
+                lo[m] = locality[jj[m]];
+                ac[m] = access[jj[m]];
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                if (m >= many) break;
+                const float wgt = (float)sz[m];
+#pragma unroll
+                for (int e = 0; e < UPD_MAXE_T; ++e) acc[e] += wgt * x[m][e];
+                wsum += (double)sz[m];
+                loc = loc + lo[m];
+                refs += ac[m];
+            }
+            members += many;
+        };
+        const int listed = members_of[r];
+        if (listed <= GROUP_LIST_MAX) {
+            // the list arrives in no particular order; the sums take the members in ascending order, so the
+            // result does not depend on scheduling: every thread places its entries by counting the smaller ones
+            const int lo = first[r];
+            for (int i = t; i < listed; i += 256) raw[i] = list[lo + i];
+            __syncthreads();
+            for (int i = t; i < listed; i += 256) {
+                const int mine = raw[i];
+                int below = 0;
+                for (int k = 0; k < listed; ++k) below += raw[k] < mine ? 1 : 0;
+                sorted[below] = mine;
+            }
+            __syncthreads();
+            for (int p = 0; p < listed; p += 4) {
+                const int many = listed - p < 4 ? listed - p : 4;
+                const long jj[4] = {sorted[p], sorted[p + (many > 1 ? 1 : 0)], sorted[p + (many > 2 ? 2 : 0)],
+                                    sorted[p + (many > 3 ? 3 : 0)]};
+                take(jj, many);
+            }
+        } else {
+            for (long base = r - (r & 255); base < K; base += 256) {
+                const long j = base + t;
+                const bool m = j < K && j >= r && root[j] == (int)r;
+                const u64 mask = __ballot(m);
+                __syncthreads();
+                if (lane == 0) masks[t >> 6] = mask;
+                __syncthreads();
+                for (int w = 0; w < 4; ++w) {
+                    u64 mm = masks[w];
+                    while (mm) {
+                        long jj[4];
+                        int many = 0;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if (mm) {
+                                jj[i] = base + w * 64 + __ffsll((long long)mm) - 1;
+                                mm &= mm - 1;
+                                ++many;
+                            } else {
+                                jj[i] = r;
+                            }
+                        }
+                        take(jj, many);
+                    }
+                }
             }
         }
-    }
-    if (members < 2) return;
-    const float wtot = (float)wsum;
-    float m[UPD_MAXE];
-    float ss = 0.f;
+        if (members >= 2) {
+            const float wtot = (float)wsum;
+            float m[UPD_MAXE_T];
+            float ss = 0.f;
 #pragma unroll
-    for (int e = 0; e < UPD_MAXE; ++e) {
-        const int col = t + e * 256;
-        m[e] = 0.f;
-        if (col < d) {
-            m[e] = acc[e] / wtot;
-            mean[(size_t)r * d + col] = m[e];
-            ss += m[e] * m[e];
-        }
-    }
-    const float n2 = block_sum256(ss, sh);
-    if (t == 0) {
-        size[r] = wsum > 2147483647.0 ? 2147483647 : (int)wsum;
-        locality[r] = loc;
-        access[r] = refs >= (u64)SISO_ACCESS_INF ? SISO_ACCESS_INF : (unsigned)refs;
-    }
-    if (!(n2 > 0.f) || n2 > 3.0e38f) return;
-    const float nrm = sqrtf(n2);
-    float cs = 0.f;
+            for (int e = 0; e < UPD_MAXE_T; ++e) {
+                const int col = t + e * 256;
+                m[e] = 0.f;
+                if (col < d) {
+                    m[e] = acc[e] / wtot;
+                    mean[(size_t)r * d + col] = m[e];
+                    ss += m[e] * m[e];
+                }
+            }
+            const float n2 = block_sum256(ss, sh);
+            if (t == 0) {
+                size[r] = wsum > 2147483647.0 ? 2147483647 : (int)wsum;
+                locality[r] = loc;
+                access[r] = refs >= (u64)SISO_ACCESS_INF ? SISO_ACCESS_INF : (unsigned)refs;
+            }
+            if ((n2 > 0.f) && n2 <= 3.0e38f) {
+                const float nrm = sqrtf(n2);
+                float cs = 0.f;
 #pragma unroll
-    for (int e = 0; e < UPD_MAXE; ++e) {
-        const int col = t + e * 256;
-        if (col < d) {
-            T v;
-            narrow(m[e] / nrm, &v);
-            cent[(size_t)r * d + col] = v;
-            const float back = widen(v);
-            cs += back * back;
+                for (int e = 0; e < UPD_MAXE_T; ++e) {
+                    const int col = t + e * 256;
+                    if (col < d) {
+                        T v;
+                        narrow(m[e] / nrm, &v);
+                        cent[(size_t)r * d + col] = v;
+                        const float back = widen(v);
+                        cs += back * back;
+                    }
+                }
+                const float c2 = block_sum256(cs, sh);
+                if (t == 0) invn[r] = inv_length(c2);
+            }
         }
+        __syncthreads();  // the lists of this group have been read
     }
-    const float c2 = block_sum256(cs, sh);
-    if (t == 0) invn[r] = inv_length(c2);
 }
 
-// Exclusive scan by one 1024-thread block, four entries per thread and trip; total -> *total.
-// The entries are vals[i], or, without vals, the flags "row i survives" (root[i] == i).
-__global__ __launch_bounds__(1024) void k_scan_exclusive(const int *__restrict__ vals, const int *__restrict__ root, long K,
-                                                          int *out, u64 *total) {
-    __shared__ int wsum[16];
-    __shared__ int carry_s;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (t == 0) carry_s = 0;
-    __syncthreads();
-    for (long base = 0; base < K; base += 4096) {
-        const long i0 = base + 4 * t;
-        int v[4];
+// Exclusive scans of the group sizes (into the starts of the member lists) and of the survivors (root[i] == i, into their
+// new places) together, SCAN_ROWS rows per 1024-thread block: the sums of the blocks first, then every block adds up
+// those before its own.  (One block for everything took 73 us a scan for 131,072 rows; two launches take 11 us for both.)
+#define SCAN_ROWS 4096
+__device__ __forceinline__ void scan_load(const int *__restrict__ members_of, const int *__restrict__ root, long K, long i0,
+                                          int (&m)[4], int (&f)[4]) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const long i = i0 + k;
-            v[k] = i < K ? (vals ? vals[i] : (root[i] == (int)i ? 1 : 0)) : 0;
-        }
-        const int mine = (v[0] + v[1]) + (v[2] + v[3]);
-        int incl = mine;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off);
-            if (lane >= off) incl += o;
-        }
-        if (lane == 63) wsum[w] = incl;
-        __syncthreads();
-        int before = carry_s;
-        for (int k = 0; k < w; ++k) before += wsum[k];
-        int run = before + incl - mine;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (i0 + k < K) out[i0 + k] = run;
-            run += v[k];
-        }
-        __syncthreads();
-        if (t == 1023) carry_s = before + incl;
-        __syncthreads();
+    for (int k = 0; k < 4; ++k) {
+        const long i = i0 + k;
+        m[k] = i < K ? members_of[i] : 0;
+        f[k] = i < K && root[i] == (int)i ? 1 : 0;
     }
-    if (total && t == 0) *total = (u64)carry_s;
+}
+// sum over a 1024-thread block of two numbers; every thread gets both
+__device__ __forceinline__ int2 block_sum1024(int a, int b, int2 *sh) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_xor(a, off);
+        b += __shfl_xor(b, off);
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = make_int2(a, b);
+    __syncthreads();
+    int2 s = make_int2(0, 0);
+    for (int w = 0; w < 16; ++w) {
+        s.x += sh[w].x;
+        s.y += sh[w].y;
+    }
+    return s;
+}
+__global__ __launch_bounds__(1024) void k_scan_sums(const int *__restrict__ members_of, const int *__restrict__ root, long K,
+                                                     int2 *sums) {
+    __shared__ int2 sh[16];
+    int m[4], f[4];
+    scan_load(members_of, root, K, (long)blockIdx.x * SCAN_ROWS + 4 * threadIdx.x, m, f);
+    const int2 s = block_sum1024((m[0] + m[1]) + (m[2] + m[3]), (f[0] + f[1]) + (f[2] + f[3]), sh);
+    if (threadIdx.x == 0) sums[blockIdx.x] = s;
+}
+__global__ __launch_bounds__(1024) void k_scan_exclusive(const int *__restrict__ members_of, const int *__restrict__ root,
+                                                          long K, const int2 *__restrict__ sums, int *first, int *newpos,
+                                                          u64 *total) {
+    __shared__ int2 sh[16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int a = 0, b = 0;
+    for (int k = t; k < (int)blockIdx.x; k += 1024) {
+        a += sums[k].x;
+        b += sums[k].y;
+    }
+    const int2 before = block_sum1024(a, b, sh);
+    const long i0 = (long)blockIdx.x * SCAN_ROWS + 4 * t;
+    int m[4], f[4];
+    scan_load(members_of, root, K, i0, m, f);
+    const int mine_m = (m[0] + m[1]) + (m[2] + m[3]), mine_f = (f[0] + f[1]) + (f[2] + f[3]);
+    int incl_m = mine_m, incl_f = mine_f;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int om = __shfl_up(incl_m, off), of = __shfl_up(incl_f, off);
+        if (lane >= off) {
+            incl_m += om;
+            incl_f += of;
+        }
+    }
+    __syncthreads();
+    if (lane == 63) sh[w] = make_int2(incl_m, incl_f);
+    __syncthreads();
+    int run_m = before.x + incl_m - mine_m, run_f = before.y + incl_f - mine_f;
+    for (int k = 0; k < w; ++k) {
+        run_m += sh[k].x;
+        run_f += sh[k].y;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (i0 + k < K) {
+            first[i0 + k] = run_m;
+            newpos[i0 + k] = run_f;
+        }
+        run_m += m[k];
+        run_f += f[k];
+    }
+    if (blockIdx.x == gridDim.x - 1 && t == 1023) *total = (u64)run_f;
 }
 template <typename T>
 __global__ __launch_bounds__(256) void k_gather_rows(const int *__restrict__ root, const int *__restrict__ newpos,
@@ -1100,13 +1213,14 @@ extern "C" int siso_load(siso_cache *c, const void *centroids, const int *counts
         const int rc = siso_fp8_load(c, centroids, counts, k);
         if (rc != SISO_OK) return rc;
     } else if (k > 0) {
+        const dim3 grid((unsigned)((k + 3) / 4));
+        const int vec = (c->dim * elem_bytes(c->dtype)) % 16 == 0 && ((uintptr_t)centroids & 15) == 0 ? 1 : 0;
         if (c->dtype == SISO_F32)
-            hipLaunchKernelGGL(k_load_rows<float>, dim3((unsigned)k), dim3(256), 0, c->stream, (const float *)centroids,
-                               counts, (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, c->dim);
+            hipLaunchKernelGGL(k_load_rows<float>, grid, dim3(256), 0, c->stream, (const float *)centroids, counts,
+                               (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, k, c->dim, vec);
         else
-            hipLaunchKernelGGL(k_load_rows<bf16_t>, dim3((unsigned)k), dim3(256), 0, c->stream,
-                               (const bf16_t *)centroids, counts, (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality,
-                               c->access, c->dim);
+            hipLaunchKernelGGL(k_load_rows<bf16_t>, grid, dim3(256), 0, c->stream, (const bf16_t *)centroids, counts,
+                               (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, k, c->dim, vec);
         HIP_TRY(c, hipGetLastError());
     }
     hipLaunchKernelGGL(k_fill_nan, dim3(1), dim3(SISO_PAD_ROWS), 0, c->stream, c->invn + k, SISO_PAD_ROWS);
@@ -1487,27 +1601,18 @@ extern "C" int siso_merge_apply(siso_cache *c, const int *pairs, long n_pairs, i
     if (K == 0) return SISO_OK;
     const int d = c->dim;
     const unsigned pb = (unsigned)((n_pairs + 255) / 256), kb = (unsigned)((K + 255) / 256);
-    u64 v = 0;
-    if (n_pairs > 0) {
-        hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, c->stream, c->counters + 2);
-        hipLaunchKernelGGL(k_pairs_validate, dim3(pb), dim3(256), 0, c->stream, pairs, n_pairs, K, c->counters + 2);
-        HIP_TRY(c, hipGetLastError());
-        int rc = siso_read_counter(c, 2, &v);
-        if (rc != SISO_OK) return rc;
-        if (v != 0) return siso_fail(c, SISO_EINVAL, "siso_merge_apply: %llu invalid pairs", v);
-    }
     int *parent = nullptr, *root = nullptr, *newpos = nullptr, *members_of = nullptr, *cursor = nullptr, *first = nullptr,
         *list = nullptr;
     unsigned char *touched = nullptr;
-    // every valid pair joins two rows, so the survivors will be gathered into the second set of arrays: make
-    // sure it exists before anything is changed in place (a failure here leaves the cache as it was)
-    int rc = n_pairs > 0 ? siso_second_set(c) : SISO_OK;
-    if (rc != SISO_OK) return rc;
+    int rc = SISO_OK;
+    const unsigned sb = (unsigned)((K + SCAN_ROWS - 1) / SCAN_ROWS);
+    int2 *sums = nullptr;
     bool ok = hipMalloc((void **)&parent, (size_t)K * sizeof(int)) == hipSuccess;
     ok = ok && hipMalloc((void **)&root, (size_t)K * sizeof(int)) == hipSuccess;
     ok = ok && hipMalloc((void **)&newpos, (size_t)K * sizeof(int)) == hipSuccess;
     ok = ok && hipMalloc((void **)&touched, (size_t)K) == hipSuccess;
-    ok = ok && hipMalloc((void **)&members_of, (size_t)K * 4 * sizeof(int)) == hipSuccess;  // four arrays of K
+    // four arrays of K, and the sums of the scan's blocks
+    ok = ok && hipMalloc((void **)&members_of, (size_t)K * 4 * sizeof(int) + sb * sizeof(int2)) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         rc = siso_fail(c, SISO_ENOMEM, "siso_merge_apply: temporaries");
@@ -1515,27 +1620,43 @@ extern "C" int siso_merge_apply(siso_cache *c, const int *pairs, long n_pairs, i
         cursor = members_of + K;
         first = cursor + K;
         list = first + K;
+        sums = (int2 *)(list + K);  // (16 K bytes into the allocation)
     }
     long live = K;
     if (rc == SISO_OK) {
+        hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, c->stream, c->counters + 2);
         hipLaunchKernelGGL(k_uf_init, dim3(kb), dim3(256), 0, c->stream, parent, touched, members_of, cursor, K);
         if (n_pairs > 0)
-            hipLaunchKernelGGL(k_uf_hook, dim3(pb), dim3(256), 0, c->stream, pairs, n_pairs, parent, touched);
-        hipLaunchKernelGGL(k_uf_roots, dim3(kb), dim3(256), 0, c->stream, parent, root, K);
-        hipLaunchKernelGGL(k_group_count, dim3(kb), dim3(256), 0, c->stream, root, touched, K, members_of);
-        hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, c->stream, members_of, root, K, first, (u64 *)nullptr);
-        hipLaunchKernelGGL(k_group_fill, dim3(kb), dim3(256), 0, c->stream, root, touched, K, first, cursor, list);
-        if (c->dtype == SISO_F32)
-            hipLaunchKernelGGL(k_group_mean<float>, dim3((unsigned)K), dim3(256), 0, c->stream, root, touched, K, members_of,
-                               first, list, (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, d);
-        else
-            hipLaunchKernelGGL(k_group_mean<bf16_t>, dim3((unsigned)K), dim3(256), 0, c->stream, root, touched, K, members_of,
-                               first, list, (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, d);
-        hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, c->stream, (const int *)nullptr, root, K, newpos,
+            hipLaunchKernelGGL(k_uf_hook, dim3(pb), dim3(256), 0, c->stream, pairs, n_pairs, K, parent, touched, c->counters + 2);
+        hipLaunchKernelGGL(k_uf_roots, dim3(kb), dim3(256), 0, c->stream, parent, touched, root, members_of, K);
+        hipLaunchKernelGGL(k_scan_sums, dim3(sb), dim3(1024), 0, c->stream, members_of, root, K, sums);
+        hipLaunchKernelGGL(k_scan_exclusive, dim3(sb), dim3(1024), 0, c->stream, members_of, root, K, sums, first, newpos,
                            c->counters + 3);
+        hipLaunchKernelGGL(k_group_fill, dim3(kb), dim3(256), 0, c->stream, root, touched, K, first, cursor, list);
         rc = siso_check_hip(c, hipGetLastError(), "merge_apply kernels");
-        if (rc == SISO_OK) rc = siso_read_counter(c, 3, &v);
-        if (rc == SISO_OK) live = (long)v;
+        u64 bad = 0;
+        if (rc == SISO_OK) rc = siso_read_counter(c, 2, &bad);  // (all four counters come at once)
+        live = (long)c->host_pin[3];
+        if (rc == SISO_OK && bad != 0) rc = siso_fail(c, SISO_EINVAL, "siso_merge_apply: %llu invalid pairs", bad);
+        // every valid pair joins two rows, so the survivors will be gathered into the second set of arrays: make
+        // sure it exists before anything is changed in place (a failure here leaves the cache as it was)
+        if (rc == SISO_OK && n_pairs > 0) rc = siso_second_set(c);
+    }
+    if (rc == SISO_OK && n_pairs > 0) {
+        const int per = K <= 16384 ? 1 : K <= 65536 ? 4 : 16;
+        const dim3 grid((unsigned)((K + per - 1) / per)), block(256);
+#define SISO_LAUNCH_MEAN(T, E)                                                                                           \
+    hipLaunchKernelGGL((k_group_mean<T, E>), grid, block, 0, c->stream, root, touched, K, members_of, first, list, (T *)c->cent, \
+                       c->mean, c->size, c->invn, c->locality, c->access, d, per)
+        if (c->dtype == SISO_F32) {
+            if (d <= 1024) SISO_LAUNCH_MEAN(float, 4);
+            else SISO_LAUNCH_MEAN(float, 16);
+        } else {
+            if (d <= 1024) SISO_LAUNCH_MEAN(bf16_t, 4);
+            else SISO_LAUNCH_MEAN(bf16_t, 16);
+        }
+#undef SISO_LAUNCH_MEAN
+        rc = siso_check_hip(c, hipGetLastError(), "k_group_mean");
     }
     if (rc == SISO_OK && out_survivor) {
         hipLaunchKernelGGL(k_survivor_map, dim3(kb), dim3(256), 0, c->stream, root, newpos, K, out_survivor);
