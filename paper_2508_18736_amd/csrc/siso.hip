@@ -344,6 +344,56 @@ __device__ __forceinline__ bool fold_member(const float (&x)[UPD_MAXE_T], float 
     return true;
 }
 
+// The members list[0 .. count) of a centroid but for the first, which the caller has folded: M at a time, so that
+// their rows are on their way together and their lengths share two barriers; the sums take them in the order of the
+// list, with the arithmetic of fold_member.
+template <typename T, int UPD_MAXE_T>
+__device__ __forceinline__ int fold_list(const int *list, int from, int to, const T *__restrict__ Q, int d,
+                                         float (&acc)[UPD_MAXE_T], float4 *sh4) {
+    constexpr int M = UPD_MAXE_T <= 4 ? 4 : 2;  // members at a time (two of the longest rows)
+    const int t = threadIdx.x;
+    int members = 0;
+    for (int p = from; p < to; p += M) {
+        float x[M][UPD_MAXE_T], n2[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const T *row = Q + (size_t)list[p + m < to ? p + m : p] * d;
+#pragma unroll
+            for (int e = 0; e < UPD_MAXE_T; ++e) {
+                const int col = t + e * 256;
+                const float v = widen(row[col < d ? col : 0]);
+                x[m][e] = col < d ? v : 0.f;
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            float ss = 0.f;
+#pragma unroll
+            for (int e = 0; e < UPD_MAXE_T; ++e) ss = __fmaf_rn(x[m][e], x[m][e], ss);
+            n2[m] = wave_sum(ss);
+        }
+        __syncthreads();
+        if ((t & 63) == 0) sh4[t >> 6] = make_float4(n2[0], n2[1], n2[2], n2[3]);
+        __syncthreads();
+        const float4 a = sh4[0], b = sh4[1], c = sh4[2], e4 = sh4[3];
+        n2[0] = (a.x + b.x) + (c.x + e4.x);
+        n2[1] = (a.y + b.y) + (c.y + e4.y);
+        n2[2] = (a.z + b.z) + (c.z + e4.z);
+        n2[3] = (a.w + b.w) + (c.w + e4.w);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            if (p + m >= to) break;
+            const float inv = inv_length(n2[m]);
+            if (!(inv == inv && inv > 0.f)) continue;
+            const float nrm = sqrtf(n2[m]);
+#pragma unroll
+            for (int e = 0; e < UPD_MAXE_T; ++e) acc[e] = __fadd_rn(acc[e], __fdiv_rn(x[m][e], nrm));
+            ++members;
+        }
+    }
+    return members;
+}
+
 // The end of an update, by the block that leads centroid k: acc = the sum of its `members` unit-length members
 // (this thread's elements t + 256 e), m_old / size_old = the mean and its weight as they were.  Writes the
 // new mean and weight, the stored row (the mean at unit length, rounded to the storage type; left alone when
@@ -391,17 +441,21 @@ __device__ __forceinline__ bool update_write(int k, int d, int size_old, int mem
     return true;
 }
 
+#define UPD_SCAN 4096  // entries of the index array that a block looks through at a time
 // UPD_MAXE_T = elements of a row per thread (4 for dim <= 1024, else 16).  owner / marked = the notes
 // of k_update_mark, or NULL: then every block finds out by itself whether it is the first member.
 template <typename T, int UPD_MAXE_T>
-__global__ __launch_bounds__(256) void k_update(const T *__restrict__ Q, const int *__restrict__ idx,
+__global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T *__restrict__ Q, const int *__restrict__ idx,
                                                  const unsigned char *__restrict__ hit, long n, T *cent, float *mean,
                                                  int *size, float *invn, long count, int d, u64 *bad, int *owner,
                                                  int *marked) {
     __shared__ float sh[4];
+    __shared__ float4 sh4[4];
     __shared__ u64 masks[4];
+    __shared__ int cells[UPD_SCAN / 64];
+    __shared__ int list[UPD_SCAN];
     const long me = blockIdx.x;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     // what does not depend on anything else is asked for first: the first 256 entries of the index
     // array (all of it in a small batch), this block's own entry
     const bool first_ok = !owner && t < n;
@@ -437,9 +491,7 @@ __global__ __launch_bounds__(256) void k_update(const T *__restrict__ Q, const i
         // where they would only start once the notes have arrived
         asm volatile("" ::"v"(x_me[e]), "v"(m_old[e]));
     }
-    const long scan_from = 0, scan_to = n;
     if (owner && lead_raw != (int)me) return;  // an earlier member leads this centroid
-    const bool alone = owner && noted_raw == 1;  // the only member: nothing to look for
     if (owner) {
         __syncthreads();  // everyone has read the notes
         if (t == 0) {     // leave them as they were found
@@ -451,47 +503,60 @@ __global__ __launch_bounds__(256) void k_update(const T *__restrict__ Q, const i
 #pragma unroll
     for (int e = 0; e < UPD_MAXE_T; ++e) acc[e] = 0.f;
     int members = 0;
-    // fold one query (its elements of this thread in x) into the sum; uniform over the block
-    auto fold = [&](const float(&x)[UPD_MAXE_T]) {
-        if (fold_member<UPD_MAXE_T>(x, acc, sh)) ++members;
-    };
-    if (alone) {
-        fold(x_me);
+    if (!owner) {
+        // at most 256 queries: one look tells who leads and who follows
+        const u64 mask = __ballot(first_ok && first_idx == k && first_hit);
+        if (lane == 0) masks[wave] = mask;
+        __syncthreads();
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) before += __popcll(masks[w]);
+            all += __popcll(masks[w]);
+        }
+        if (mask >> lane & 1) list[before + __popcll(mask & ((1ull << lane) - 1))] = t;
+        __syncthreads();
+        if (list[0] != (int)me) return;  // an earlier member leads this centroid
+        if (fold_member<UPD_MAXE_T>(x_me, acc, sh)) ++members;
+        members += fold_list<T, UPD_MAXE_T>(list, 1, all, Q, d, acc, sh4);
     } else {
-        for (long base = scan_from; base < scan_to; base += 256) {
-            const long j = base + t;
-            bool m;
-            if (base == 0 && !owner)
-                m = first_ok && first_idx == k && first_hit;
-            else
-                m = j < scan_to && idx[j] == k && (!hit || hit[j]);
-            const u64 mask = __ballot(m);
-            __syncthreads();
-            if ((t & 63) == 0) masks[t >> 6] = mask;
-            __syncthreads();
-            for (int w = 0; w < 4; ++w) {
-                u64 mm = masks[w];
-                while (mm) {
-                    const int b = __ffsll((long long)mm) - 1;
-                    mm &= mm - 1;
-                    const long jj = base + w * 64 + b;
-                    if (jj < me) return;  // an earlier member leads this centroid (uniform over the block)
-                    if (jj == me) {
-                        fold(x_me);
-                        continue;
-                    }
-                    T xr[UPD_MAXE_T];
-                    float x[UPD_MAXE_T];
-#pragma unroll
-                    for (int e = 0; e < UPD_MAXE_T; ++e) {
-                        const int col = t + e * 256;
-                        xr[e] = Q[(size_t)jj * d + (col < d ? col : 0)];
-                    }
-#pragma unroll
-                    for (int e = 0; e < UPD_MAXE_T; ++e) x[e] = t + e * 256 < d ? widen(xr[e]) : 0.f;
-                    fold(x);
-                }
+        if (fold_member<UPD_MAXE_T>(x_me, acc, sh)) ++members;
+        // the others lie behind: UPD_SCAN entries of the index array at a time, all of them on their way together, the
+        // members in ascending order into the list
+        int found = 1;
+        for (long base = me + 1; found < noted_raw && base < n; base += UPD_SCAN) {
+            unsigned mine = 0;  // bit i: entry base + 256 i + t is a member
+#pragma unroll 8
+            for (int i = 0; i < UPD_SCAN / 256; ++i) {
+                const long j = base + 256 * i + t;
+                const int at = idx[j < n ? j : me];
+                if (at == k && j < n && (!hit || hit[j])) mine |= 1u << i;
             }
+            __syncthreads();  // (the list of the last round has been read)
+#pragma unroll
+            for (int i = 0; i < UPD_SCAN / 256; ++i) {
+                const u64 mask = __ballot(mine >> i & 1);
+                if (lane == 0) cells[4 * i + wave] = __popcll(mask);
+            }
+            __syncthreads();
+            int at = lane < UPD_SCAN / 64 ? cells[lane] : 0;  // exclusive sums over the cells, in every wave
+            const int own = at;
+#pragma unroll
+            for (int off = 1; off < UPD_SCAN / 64; off <<= 1) {
+                const int o = __shfl_up(at, off);
+                if (lane >= off) at += o;
+            }
+            const int all = __shfl(at, UPD_SCAN / 64 - 1);
+            at -= own;
+#pragma unroll
+            for (int i = 0; i < UPD_SCAN / 256; ++i) {
+                const u64 mask = __ballot(mine >> i & 1);
+                const int to = __shfl(at, 4 * i + wave) + __popcll(mask & ((1ull << lane) - 1));
+                if (mine >> i & 1) list[to] = (int)(base + 256 * i + t);
+            }
+            __syncthreads();
+            members += fold_list<T, UPD_MAXE_T>(list, 0, all, Q, d, acc, sh4);
+            found += all;
         }
     }
     if (members == 0) return;
@@ -535,6 +600,8 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     __shared__ u64 sh_k[4];
     __shared__ u64 masks[4];
     __shared__ u64 sh_board[SISO_FOLD_BOARD];
+    __shared__ float4 sh4[4];
+    __shared__ int list[SISO_FOLD_BOARD];
     __shared__ int sh_all;
     const long me = blockIdx.x;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -630,38 +697,22 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     float acc[UPD_MAXE_T];
 #pragma unroll
     for (int e = 0; e < UPD_MAXE_T; ++e) acc[e] = 0.f;
-    int members = 0;
-    auto fold = [&](const float(&x)[UPD_MAXE_T]) {
-        if (fold_member<UPD_MAXE_T>(x, acc, sh)) ++members;
-    };
     // the members of centroid k in ascending order (a hit whose index is k)
     const bool m = t < (int)n && sh_board[t] == board_entry(true, k);
     const u64 mask = __ballot(m);
     if (lane == 0) masks[wave] = mask;
     __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
     for (int w = 0; w < 4; ++w) {
-        u64 mm = masks[w];
-        while (mm) {
-            const int b = __ffsll((long long)mm) - 1;
-            mm &= mm - 1;
-            const long jj = w * 64 + b;
-            if (jj < me) return;  // an earlier member leads this centroid (uniform over the block)
-            if (jj == me) {
-                fold(x_me);
-                continue;
-            }
-            T yr[UPD_MAXE_T];
-            float x[UPD_MAXE_T];
-#pragma unroll
-            for (int e = 0; e < UPD_MAXE_T; ++e) {
-                const int col = t + e * 256;
-                yr[e] = Q[(size_t)jj * d + (col < d ? col : 0)];
-            }
-#pragma unroll
-            for (int e = 0; e < UPD_MAXE_T; ++e) x[e] = t + e * 256 < d ? widen(yr[e]) : 0.f;
-            fold(x);
-        }
+        if (w < wave) before += __popcll(masks[w]);
+        all += __popcll(masks[w]);
     }
+    if (m) list[before + __popcll(mask & ((1ull << lane) - 1))] = t;
+    __syncthreads();
+    if (list[0] != (int)me) return;  // an earlier member leads this centroid (uniform over the block)
+    int members = fold_member<UPD_MAXE_T>(x_me, acc, sh) ? 1 : 0;
+    members += fold_list<T, UPD_MAXE_T>(list, 1, all, Q, d, acc, sh4);
     if (members == 0) return;
     float stored[UPD_MAXE_T];
     const bool rewritten = update_write<T, UPD_MAXE_T>(k, d, size_old, members, m_old, acc, cent, mean, size, invn, sh, stored);
