@@ -264,7 +264,8 @@ long siso_merge(siso_cache *c, float threshold, int *out_pairs, long cap);
  * the first call that rebuilds the cache (this one or siso_refresh) allocates
  * that set, as much device memory again as siso_create took (option
  * "second_set" of siso_bench.h does it ahead of time), before anything is
- * changed: if that fails the cache is as it was.  Allocates small temporaries per call.
+ * changed: if that fails the cache is as it was.  Its temporaries are kept for the next such
+ * call (the cache keeps up to 512 MiB of device and 64 MiB of pinned memory for them).
  * Synchronises.
  */
 int siso_merge_apply(siso_cache *c, const int *pairs, long n_pairs, int *out_survivor);
@@ -358,7 +359,7 @@ int siso_fp8_resync(siso_cache *copy, const siso_cache *master);
  * update step (bad arguments, a non-finite row, a cluster size <= 0).
  * The new set is gathered into the second set of the cache's arrays (see
  * siso_merge_apply), which then becomes the cache: nothing is copied back.
- * Allocates temporary device memory for the repository.  Synchronises.
+ * Its temporaries (the repository once more) are kept as siso_merge_apply's.  Synchronises.
  *
  * siso_export_meta: copy out cluster_size [count] floats and access_count
  * [count] unsigned ints (device pointers, either may be NULL).  Asynchronous.
@@ -462,7 +463,7 @@ long siso_choose_communities(const int *pairs, long n_pairs, long n, int min_siz
  *             whose top-1 similarity exceeds thetas[j] (strictly, compared as
  *             floats like the hit test of siso_lookup); h(theta_j) = out_hits[j] / n.
  * One lookup serves all thresholds (the similarity does not depend on them).
- * Allocates temporary device memory.  Synchronises.
+ * Its temporaries are kept as siso_merge_apply's.  Synchronises.
  */
 int siso_t2h(siso_cache *c, const void *queries, long n, const float *thetas, int m, long *out_hits);
 

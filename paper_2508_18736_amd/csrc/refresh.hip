@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "siso_internal.h"
@@ -29,7 +30,30 @@ namespace {
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
-__global__ void k_clear(u64 *p) { *p = 0; }
+// both counters of the call: rows that cannot be taken, pairs found
+__global__ void k_clear(u64 *bad, u64 *pairs) {
+    *bad = 0;
+    *pairs = 0;
+}
+
+// What the host decides on, to pinned host memory (a copy engine takes longer to get going than these few hundred
+// kilobytes take): five arrays of r or K0 numbers, one behind the other.
+__global__ void k_report(const int *__restrict__ idx, const float *__restrict__ sim, const float *__restrict__ rsize, long r,
+                         const float *__restrict__ loc, const unsigned *__restrict__ acc, long K0, int *h_idx, float *h_sim,
+                         float *h_rsize, float *h_loc, unsigned *h_acc) {
+    const long n = r > K0 ? r : K0;
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
+        if (i < r) {
+            h_idx[i] = idx[i];
+            h_sim[i] = sim[i];
+            h_rsize[i] = rsize[i];
+        }
+        if (i < K0) {
+            h_loc[i] = loc[i];
+            h_acc[i] = acc[i];
+        }
+    }
+}
 
 __global__ void k_nan_tail(float *p, int count) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -62,18 +86,26 @@ __global__ __launch_bounds__(256) void k_stage_repo(const T *__restrict__ src, c
 }
 
 // cosine of the two rows of every listed pair, one wave per pair (the arithmetic of the lookup's
-// last step: fp32 products summed per lane, then over the lanes, then scaled by both inverse lengths)
+// last step: fp32 products summed per lane, then over the lanes, then scaled by both inverse lengths); the pairs and
+// their cosines go to the host.  The number of pairs is read from the device, so that the host need not know it yet; at
+// most `most` are looked at from `from` on.
 template <typename T>
 __global__ __launch_bounds__(256) void k_pair_cosines(const T *__restrict__ rows, const float *__restrict__ invn,
-                                                       const int *__restrict__ pairs, long n_pairs, int d, float *out) {
-    const long p = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (p >= n_pairs) return;
+                                                       const int *__restrict__ pairs, const u64 *__restrict__ n_pairs, long from,
+                                                       long most, int d, int *h_pairs, float *h_cos) {
+    const long n = *n_pairs < (u64)(from + most) ? (long)*n_pairs : from + most;
     const int lane = threadIdx.x & 63;
-    const long a = pairs[2 * p], b = pairs[2 * p + 1];
-    float acc = 0.f;
-    for (int e = lane; e < d; e += 64) acc += widen(rows[(size_t)a * d + e]) * widen(rows[(size_t)b * d + e]);
-    acc = wave_sum(acc);
-    if (lane == 0) out[p] = acc * invn[a] * invn[b];
+    for (long p = from + (long)blockIdx.x * 4 + (threadIdx.x >> 6); p < n; p += (long)gridDim.x * 4) {
+        const long a = pairs[2 * p], b = pairs[2 * p + 1];
+        float acc = 0.f;
+        for (int e = lane; e < d; e += 64) acc += widen(rows[(size_t)a * d + e]) * widen(rows[(size_t)b * d + e]);
+        acc = wave_sum(acc);
+        if (lane == 0) {
+            h_pairs[2 * p] = (int)a;
+            h_pairs[2 * p + 1] = (int)b;
+            h_cos[p] = acc * invn[a] * invn[b];
+        }
+    }
 }
 
 // New row j <- source src[j]: a cached row (src < K0) with all it carries, or repository row
@@ -84,10 +116,15 @@ __global__ __launch_bounds__(256) void k_refresh_gather(const int *__restrict__ 
                                                          const float *__restrict__ mean, const int *__restrict__ size,
                                                          const float *__restrict__ invn, const T *__restrict__ repo,
                                                          const float *__restrict__ repo_invn,
-                                                         const float *__restrict__ repo_size, T *cent2, float *mean2,
-                                                         int *size2, float *invn2, int d) {
+                                                         const float *__restrict__ repo_size,
+                                                         const float *__restrict__ loc, T *cent2, float *mean2,
+                                                         int *size2, float *invn2, float *loc2, unsigned *acc2, int d) {
     const long j = blockIdx.x;
     const long s = src[j];
+    if (threadIdx.x == 0) {
+        loc2[j] = loc[j];
+        acc2[j] = 0u;
+    }
     if (s < K0) {
         for (int e = threadIdx.x; e < d; e += 256) {
             cent2[(size_t)j * d + e] = cent[(size_t)s * d + e];
@@ -153,9 +190,11 @@ void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const f
         }
     }
     std::vector<long> place((size_t)r, -1);  // position in C_new of a repository row that joined
-    std::vector<int> src;                    // C_new: source of every row (cached row, or K0 + repository row)
+    std::vector<int> src((size_t)K0);        // C_new: source of every row (cached row, or K0 + repository row)
     src.reserve((size_t)(K0 + r));
-    for (long j = 0; j < K0; ++j) src.push_back((int)j);
+    for (long j = 0; j < K0; ++j) src[(size_t)j] = (int)j;
+    loc.reserve((size_t)(K0 + r));
+    acc.reserve((size_t)(K0 + r));
     merged = added = 0;
     for (long i = 0; i < r; ++i) {
         long best = h_idx[(size_t)i];
@@ -187,27 +226,50 @@ void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const f
 
     // ---- filtering step: the smallest (cluster_size, access_count) go, the first such first ----
     const long n_new = (long)src.size();
-    evicted = 0;
-    std::vector<unsigned char> gone((size_t)n_new, 0);
-    if (n_new > max_centroids) {
-        evicted = n_new - max_centroids;
-        std::vector<int> order((size_t)n_new);
-        for (long j = 0; j < n_new; ++j) order[(size_t)j] = (int)j;
-        auto before = [&](int x, int y) {
-            if (loc[(size_t)x] != loc[(size_t)y]) return loc[(size_t)x] < loc[(size_t)y];
-            if (acc[(size_t)x] != acc[(size_t)y]) return acc[(size_t)x] < acc[(size_t)y];
-            return x < y;
-        };
-        std::nth_element(order.begin(), order.begin() + evicted, order.end(), before);
-        for (long v = 0; v < evicted; ++v) gone[(size_t)order[(size_t)v]] = 1;
+    // (cluster_size, access_count) as one number that orders alike; -0 and 0 are the same size
+    auto key_of = [&](long j) -> u64 {
+        const float f = loc[(size_t)j] + 0.0f;
+        unsigned u;
+        memcpy(&u, &f, 4);
+        u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+        return ((u64)u << 32) | acc[(size_t)j];
+    };
+    evicted = n_new > max_centroids ? n_new - max_centroids : 0;
+    u64 last = 0;    // rows with a smaller number go,
+    long at_last = 0;  // and of those with this one so many, the first ones
+    if (evicted > 0) {
+        // the evicted-th smallest number: its upper 16 bits from a count of them, the rest among the rows that share those
+        std::vector<u64> key((size_t)n_new);
+        std::vector<long> with((size_t)1 << 16, 0);
+        for (long j = 0; j < n_new; ++j) {
+            key[(size_t)j] = key_of(j);
+            with[(size_t)(key[(size_t)j] >> 48)] += 1;
+        }
+        long below = 0;
+        size_t top = 0;
+        while (below + with[top] < evicted) below += with[top++];
+        std::vector<u64> same;
+        same.reserve((size_t)with[top]);
+        for (long j = 0; j < n_new; ++j)
+            if ((key[(size_t)j] >> 48) == top) same.push_back(key[(size_t)j]);
+        std::nth_element(same.begin(), same.begin() + (evicted - below - 1), same.end());
+        last = same[(size_t)(evicted - below - 1)];
+        at_last = evicted - below;
+        for (u64 v : same) at_last -= v < last ? 1 : 0;
+        keep.resize((size_t)(n_new - evicted));
+        loc2.resize((size_t)(n_new - evicted));
+        size_t out = 0;
+        for (long j = 0; j < n_new; ++j) {
+            const u64 v = key[(size_t)j];
+            if (v < last || (v == last && at_last-- > 0)) continue;
+            keep[out] = src[(size_t)j];
+            loc2[out++] = loc[(size_t)j] / 1.1f;
+        }
+        return;
     }
-    keep.reserve((size_t)(n_new - evicted));
-    loc2.reserve((size_t)(n_new - evicted));
-    for (long j = 0; j < n_new; ++j) {
-        if (gone[(size_t)j]) continue;
-        keep.push_back(src[(size_t)j]);
-        loc2.push_back(loc[(size_t)j] / 1.1f);
-    }
+    keep = std::move(src);
+    loc2.resize((size_t)n_new);
+    for (long j = 0; j < n_new; ++j) loc2[(size_t)j] = loc[(size_t)j] / 1.1f;
 }
 
 }  // namespace
@@ -233,122 +295,147 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
     } while (0)
 
     // ---- device side of the merge step -------------------------------------------------
-    DeviceBuf d_rows, d_rinv, d_idx, d_sim, d_pairs, d_cos;
-    std::vector<int> h_idx((size_t)r);
-    std::vector<float> h_sim((size_t)r), h_rsize((size_t)r), h_cos;
-    std::vector<int> h_pairs;
+    // Everything the host decides on is on its way before it waits for the first time: the lookups, the pair search and
+    // the cosines of the first pairs do no harm if the check of the repository rows, read at the same time, then fails.
+    long cap = r * 4 > (1L << 20) ? r * 4 : (1L << 20);  // room for pairs
+    const long early = 16384;                            // of which the cosines are formed before their number is known
+    char *d_rows;
+    float *d_rinv, *d_sim, *d_loc2, *h_sim, *h_rsize, *h_loc, *h_cos, *h_loc2;
+    int *d_idx, *d_pairs, *d_src, *h_idx, *h_pairs, *h_src;
+    unsigned *h_acc;
+    auto layout = [&](Carver a, Carver h) {
+        d_rows = a.take<char>((size_t)(r + SISO_PAD_ROWS) * d * eb);
+        d_rinv = a.take<float>(r + SISO_PAD_ROWS);
+        d_idx = a.take<int>(r);
+        d_sim = a.take<float>(r);
+        d_pairs = a.take<int>(2 * cap);
+        d_src = a.take<int>(2 * (K0 + r));
+        h_idx = h.take<int>(r);
+        h_sim = h.take<float>(r);
+        h_rsize = h.take<float>(r);
+        h_loc = h.take<float>(K0);
+        h_acc = h.take<unsigned>(K0);
+        h_pairs = h.take<int>(2 * early);
+        h_cos = h.take<float>(early);
+        h_src = h.take<int>(2 * (K0 + r));
+        return std::pair<size_t, size_t>(a.used, h.used);
+    };
+    {
+        const std::pair<size_t, size_t> need = layout(Carver{nullptr}, Carver{nullptr});
+        const int rc = siso_arena(c, need.first, need.second);
+        if (rc != SISO_OK) return rc;
+        layout(Carver{c->arena}, Carver{c->pinned});
+    }
+    DeviceBuf more_pairs;  // a list that turned out too short
+    std::vector<int> all_pairs;
+    std::vector<float> all_cos;
     long n_pairs = 0;
+    u64 *bad_at = c->counters + 2, *found_at = c->counters + 1;
+    auto search = [&](int *pairs, long room) {
+        return siso_pairs_mfma_supported(c, r)
+                   ? siso_pairs_mfma_launch(c, d_rows, d_rinv, r, theta_c, pairs, room, found_at)
+                   : siso_pairs_tile_launch(c, d_rows, d_rinv, r, theta_c, pairs, room, found_at);
+    };
+    auto cosines = [&](const int *pairs, long from, long most, int *to_pairs, float *to_cos) {
+        const dim3 grid((unsigned)(most < 4096 ? (most + 3) / 4 : 1024)), block(256);
+        if (c->dtype == SISO_F32)
+            hipLaunchKernelGGL(k_pair_cosines<float>, grid, block, 0, st, (const float *)d_rows, d_rinv, pairs, found_at, from, most,
+                               d, to_pairs, to_cos);
+        else
+            hipLaunchKernelGGL(k_pair_cosines<bf16_t>, grid, block, 0, st, (const bf16_t *)d_rows, d_rinv, pairs, found_at, from, most,
+                               d, to_pairs, to_cos);
+        return siso_check_hip(c, hipGetLastError(), "k_pair_cosines");
+    };
     if (r > 0) {
-        if (!d_rows.alloc((size_t)(r + SISO_PAD_ROWS) * d * eb) || !d_rinv.alloc((size_t)(r + SISO_PAD_ROWS) * sizeof(float)) ||
-            !d_idx.alloc((size_t)r * sizeof(int)) || !d_sim.alloc((size_t)r * sizeof(float))) {
-            (void)hipGetLastError();
-            return siso_fail(c, SISO_ENOMEM, "siso_refresh: staging for %ld repository rows", r);
-        }
-        REFRESH_TRY(hipMemsetAsync((char *)d_rows.p + (size_t)r * d * eb, 0, (size_t)SISO_PAD_ROWS * d * eb, st), "clear pad rows");
-        hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, st, c->counters + 2);
+        REFRESH_TRY(hipMemsetAsync(d_rows + (size_t)r * d * eb, 0, (size_t)SISO_PAD_ROWS * d * eb, st), "clear pad rows");
+        hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, st, bad_at, found_at);
         if (c->dtype == SISO_F32)
             hipLaunchKernelGGL(k_stage_repo<float>, dim3((unsigned)r), dim3(256), 0, st, (const float *)repo, repo_size,
-                               d_rows.as<float>(), d_rinv.as<float>(), d, c->counters + 2);
+                               (float *)d_rows, d_rinv, d, bad_at);
         else
             hipLaunchKernelGGL(k_stage_repo<bf16_t>, dim3((unsigned)r), dim3(256), 0, st, (const bf16_t *)repo, repo_size,
-                               d_rows.as<bf16_t>(), d_rinv.as<float>(), d, c->counters + 2);
-        hipLaunchKernelGGL(k_nan_tail, dim3(1), dim3(SISO_PAD_ROWS), 0, st, d_rinv.as<float>() + r, SISO_PAD_ROWS);
+                               (bf16_t *)d_rows, d_rinv, d, bad_at);
+        hipLaunchKernelGGL(k_nan_tail, dim3(1), dim3(SISO_PAD_ROWS), 0, st, d_rinv + r, SISO_PAD_ROWS);
         REFRESH_TRY(hipGetLastError(), "stage repository rows");
-        u64 bad = 0;
-        int rc = siso_read_counter(c, 2, &bad);
-        if (rc != SISO_OK) return rc;
-        if (bad != 0)
-            return siso_fail(c, SISO_EINVAL, "siso_refresh: %llu repository rows are not finite or have no positive cluster size", bad);
-
         // every repository row against the cache (test lookups: no references are counted)
-        rc = siso_lookup_impl(c, d_rows.p, r, &theta_c, 1, -1, d_idx.as<int>(), d_sim.as<float>(), nullptr);
-        if (rc != SISO_OK) return rc;
-
+        int rc = siso_lookup_impl(c, d_rows, r, &theta_c, 1, -1, d_idx, d_sim, nullptr);
         // repository rows among themselves: the pairs above the threshold, then their cosines
-        long cap = r * 4 > (1L << 20) ? r * 4 : (1L << 20);
-        for (int attempt = 0; attempt < 2 && r >= 2; ++attempt) {
-            if (d_pairs.p) {
-                (void)hipFree(d_pairs.p);
-                d_pairs.p = nullptr;
-            }
-            if (!d_pairs.alloc((size_t)cap * 2 * sizeof(int))) {
-                (void)hipGetLastError();
-                return siso_fail(c, SISO_ENOMEM, "siso_refresh: room for %ld pairs", cap);
-            }
-            hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, st, c->counters + 1);
-            REFRESH_TRY(hipGetLastError(), "k_clear");
-            if (siso_pairs_mfma_supported(c, r))
-                rc = siso_pairs_mfma_launch(c, d_rows.p, d_rinv.as<float>(), r, theta_c, d_pairs.as<int>(), cap, c->counters + 1);
-            else
-                rc = siso_pairs_tile_launch(c, d_rows.p, d_rinv.as<float>(), r, theta_c, d_pairs.as<int>(), cap, c->counters + 1);
-            if (rc != SISO_OK) return rc;
-            u64 total = 0;
-            rc = siso_read_counter(c, 1, &total);
-            if (rc != SISO_OK) return rc;
-            n_pairs = (long)total;
-            if (n_pairs <= cap) break;
-            if (attempt == 1) return siso_fail(c, SISO_ENOMEM, "siso_refresh: %ld pairs above the threshold", n_pairs);
-            cap = n_pairs;  // once more with room for all of them
-        }
-        if (n_pairs > 0) {
-            if (!d_cos.alloc((size_t)n_pairs * sizeof(float))) {
-                (void)hipGetLastError();
-                return siso_fail(c, SISO_ENOMEM, "siso_refresh: cosines of %ld pairs", n_pairs);
-            }
-            const unsigned blocks = (unsigned)((n_pairs + 3) / 4);
-            if (c->dtype == SISO_F32)
-                hipLaunchKernelGGL(k_pair_cosines<float>, dim3(blocks), dim3(256), 0, st, d_rows.as<float>(), d_rinv.as<float>(),
-                                   d_pairs.as<int>(), n_pairs, d, d_cos.as<float>());
-            else
-                hipLaunchKernelGGL(k_pair_cosines<bf16_t>, dim3(blocks), dim3(256), 0, st, d_rows.as<bf16_t>(), d_rinv.as<float>(),
-                                   d_pairs.as<int>(), n_pairs, d, d_cos.as<float>());
-            REFRESH_TRY(hipGetLastError(), "k_pair_cosines");
-            h_pairs.resize((size_t)n_pairs * 2);
-            h_cos.resize((size_t)n_pairs);
-            REFRESH_TRY(hipMemcpyAsync(h_pairs.data(), d_pairs.p, (size_t)n_pairs * 2 * sizeof(int), hipMemcpyDeviceToHost, st), "pairs to host");
-            REFRESH_TRY(hipMemcpyAsync(h_cos.data(), d_cos.p, (size_t)n_pairs * sizeof(float), hipMemcpyDeviceToHost, st), "cosines to host");
-        }
-        REFRESH_TRY(hipMemcpyAsync(h_idx.data(), d_idx.p, (size_t)r * sizeof(int), hipMemcpyDeviceToHost, st), "idx to host");
-        REFRESH_TRY(hipMemcpyAsync(h_sim.data(), d_sim.p, (size_t)r * sizeof(float), hipMemcpyDeviceToHost, st), "sim to host");
-        REFRESH_TRY(hipMemcpyAsync(h_rsize.data(), repo_size, (size_t)r * sizeof(float), hipMemcpyDeviceToHost, st), "sizes to host");
+        if (rc == SISO_OK && r >= 2) rc = search(d_pairs, cap);
+        if (rc == SISO_OK && r >= 2) rc = cosines(d_pairs, 0, early, h_pairs, h_cos);
+        if (rc != SISO_OK) return rc;
     }
-    std::vector<float> loc((size_t)K0);
-    std::vector<unsigned> acc((size_t)K0);
-    if (K0 > 0) {
-        REFRESH_TRY(hipMemcpyAsync(loc.data(), c->locality, (size_t)K0 * sizeof(float), hipMemcpyDeviceToHost, st), "cluster sizes to host");
-        REFRESH_TRY(hipMemcpyAsync(acc.data(), c->access, (size_t)K0 * sizeof(unsigned), hipMemcpyDeviceToHost, st), "access counts to host");
+    if (r > 0 || K0 > 0) {
+        const long widest = r > K0 ? r : K0;
+        hipLaunchKernelGGL(k_report, dim3((unsigned)(widest < 262144 ? (widest + 255) / 256 : 1024)), dim3(256), 0, st, d_idx, d_sim,
+                           repo_size, r, c->locality, c->access, K0, h_idx, h_sim, h_rsize, h_loc, h_acc);
+        REFRESH_TRY(hipGetLastError(), "k_report");
+        u64 bad = 0;
+        int rc = siso_read_counter(c, 2, &bad);  // (all counters come at once)
+        if (rc != SISO_OK) return rc;
+        if (r > 0 && bad != 0)
+            return siso_fail(c, SISO_EINVAL, "siso_refresh: %llu repository rows are not finite or have no positive cluster size", bad);
+        n_pairs = r >= 2 ? (long)c->host_pin[1] : 0;
     }
-    REFRESH_TRY(hipStreamSynchronize(st), "siso_refresh: synchronize");
+    if (n_pairs > cap) {  // once more with room for all of them
+        const long need = n_pairs;
+        if (!more_pairs.alloc((size_t)need * 2 * sizeof(int))) {
+            (void)hipGetLastError();
+            return siso_fail(c, SISO_ENOMEM, "siso_refresh: room for %ld pairs", need);
+        }
+        hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, st, bad_at, found_at);
+        int rc = search(more_pairs.as<int>(), need);
+        u64 total = 0;
+        if (rc == SISO_OK) rc = siso_read_counter(c, 1, &total);
+        if (rc != SISO_OK) return rc;
+        if ((long)total > need) return siso_fail(c, SISO_ENOMEM, "siso_refresh: %llu pairs above the threshold", total);
+        n_pairs = (long)total;
+        cap = need;
+    }
+    if (n_pairs > early || more_pairs.p) {
+        DeviceBuf d_found;  // pairs and cosines, to be copied
+        if (!d_found.alloc((size_t)n_pairs * (2 * sizeof(int) + sizeof(float)))) {
+            (void)hipGetLastError();
+            return siso_fail(c, SISO_ENOMEM, "siso_refresh: cosines of %ld pairs", n_pairs);
+        }
+        int *found_pairs = d_found.as<int>();
+        float *found_cos = (float *)(found_pairs + 2 * n_pairs);
+        const int rc = cosines(more_pairs.p ? more_pairs.as<int>() : d_pairs, 0, n_pairs, found_pairs, found_cos);
+        if (rc != SISO_OK) return rc;
+        all_pairs.resize((size_t)n_pairs * 2);
+        all_cos.resize((size_t)n_pairs);
+        REFRESH_TRY(hipMemcpyAsync(all_pairs.data(), found_pairs, (size_t)n_pairs * 2 * sizeof(int), hipMemcpyDeviceToHost, st), "pairs to host");
+        REFRESH_TRY(hipMemcpyAsync(all_cos.data(), found_cos, (size_t)n_pairs * sizeof(float), hipMemcpyDeviceToHost, st), "cosines to host");
+        REFRESH_TRY(hipStreamSynchronize(st), "siso_refresh: synchronize");
+        h_pairs = all_pairs.data();
+        h_cos = all_cos.data();
+    }
 
     // ---- merge step and filtering step: bookkeeping on the host ----------------------------------
     std::vector<int> keep;
     std::vector<float> loc2;
     long merged = 0, added = 0, evicted = 0;
-    plan_refresh(K0, r, h_idx.data(), h_sim.data(), h_rsize.data(), h_pairs.data(), h_cos.data(), n_pairs, loc, acc, theta_c,
-                 max_centroids, keep, loc2, merged, added, evicted);
+    plan_refresh(K0, r, h_idx, h_sim, h_rsize, h_pairs, h_cos, n_pairs, std::vector<float>(h_loc, h_loc + K0),
+                 std::vector<unsigned>(h_acc, h_acc + K0), theta_c, max_centroids, keep, loc2, merged, added, evicted);
     const long live = (long)keep.size();
 
     // ---- update step: gather the new set, then it becomes the cache ---------------------------
-    DeviceBuf d_src;
     if (live > 0) {
         const int rc2 = siso_second_set(c);
         if (rc2 != SISO_OK) return rc2;
-        if (!d_src.alloc((size_t)live * sizeof(int))) {
-            (void)hipGetLastError();
-            return siso_fail(c, SISO_ENOMEM, "siso_refresh: sources of %ld centroids", live);
-        }
-        REFRESH_TRY(hipMemcpyAsync(d_src.p, keep.data(), (size_t)live * sizeof(int), hipMemcpyHostToDevice, st), "sources to device");
+        memcpy(h_src, keep.data(), (size_t)live * sizeof(int));
+        h_loc2 = (float *)(h_src + live);
+        memcpy(h_loc2, loc2.data(), (size_t)live * sizeof(float));
+        REFRESH_TRY(hipMemcpyAsync(d_src, h_src, (size_t)live * 2 * sizeof(int), hipMemcpyHostToDevice, st), "sources to device");
+        d_loc2 = (float *)(d_src + live);
         if (c->dtype == SISO_F32)
-            hipLaunchKernelGGL(k_refresh_gather<float>, dim3((unsigned)live), dim3(256), 0, st, d_src.as<int>(), K0,
-                               (const float *)c->cent, c->mean, c->size, c->invn, d_rows.as<float>(), d_rinv.as<float>(),
-                               repo_size, (float *)c->cent_b, c->mean_b, c->size_b, c->invn_b, d);
+            hipLaunchKernelGGL(k_refresh_gather<float>, dim3((unsigned)live), dim3(256), 0, st, d_src, K0, (const float *)c->cent,
+                               c->mean, c->size, c->invn, (const float *)d_rows, d_rinv, repo_size, d_loc2, (float *)c->cent_b,
+                               c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, d);
         else
-            hipLaunchKernelGGL(k_refresh_gather<bf16_t>, dim3((unsigned)live), dim3(256), 0, st, d_src.as<int>(), K0,
-                               (const bf16_t *)c->cent, c->mean, c->size, c->invn, d_rows.as<bf16_t>(), d_rinv.as<float>(),
-                               repo_size, (bf16_t *)c->cent_b, c->mean_b, c->size_b, c->invn_b, d);
+            hipLaunchKernelGGL(k_refresh_gather<bf16_t>, dim3((unsigned)live), dim3(256), 0, st, d_src, K0, (const bf16_t *)c->cent,
+                               c->mean, c->size, c->invn, (const bf16_t *)d_rows, d_rinv, repo_size, d_loc2, (bf16_t *)c->cent_b,
+                               c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, d);
         REFRESH_TRY(hipGetLastError(), "k_refresh_gather");
-        REFRESH_TRY(hipMemcpyAsync(c->locality_b, loc2.data(), (size_t)live * sizeof(float), hipMemcpyHostToDevice, st), "new cluster sizes");
-        REFRESH_TRY(hipMemsetAsync(c->access_b, 0, (size_t)live * sizeof(unsigned), st), "reset access counts");
         siso_swap_sets(c);  // lookups enqueued from here on see the new set
     }
     hipLaunchKernelGGL(k_nan_tail, dim3(1), dim3(SISO_PAD_ROWS), 0, st, c->invn + live, SISO_PAD_ROWS);
@@ -367,11 +454,14 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
 extern "C" int siso_refresh(siso_cache *c, const void *repo, const float *repo_size, long r, float theta_c,
                             long max_centroids, long *out_stats) {
     if (!c) return SISO_EINVAL;
+    int rc;
     try {
-        return refresh_impl(c, repo, repo_size, r, theta_c, max_centroids, out_stats);
+        rc = refresh_impl(c, repo, repo_size, r, theta_c, max_centroids, out_stats);
     } catch (const std::bad_alloc &) {  // the host lists; they are all built before the update step
-        return siso_fail(c, SISO_ENOMEM, "siso_refresh: host memory for the bookkeeping");
+        rc = siso_fail(c, SISO_ENOMEM, "siso_refresh: host memory for the bookkeeping");
     }
+    siso_arena_done(c);
+    return rc;
 }
 
 // The host part of siso_refresh alone (all pointers are HOST pointers).

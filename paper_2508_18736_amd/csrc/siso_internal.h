@@ -65,6 +65,13 @@ struct siso_cache {
     u64 *keys;     // [keys_cap] phase-1 keys, n * slices
     long keys_cap;
 
+    // temporaries of the calls that rebuild the cache (group merge, refresh, clustering): device memory, and pinned host
+    // memory that kernels write their findings to; kept from one such call to the next (siso_arena)
+    char *arena;
+    size_t arena_cap;
+    char *pinned;
+    size_t pinned_cap;
+
     u64 *static_keys;  // this device's copy of the library's static key array (siso_lookup_static)
 
     u64 *counters;  // device: [0] bad update indices, [1] merge pair count, [2] scratch, [3] scratch; behind them the
@@ -448,5 +455,22 @@ int siso_fp8_ensure_batch(siso_cache *c, long n);
 int siso_fp8_quantize_batch(siso_cache *c, const void *queries, long n);  // bf16 queries -> c->fp8_q, c->fp8_qinv
 int siso_read_counter(siso_cache *c, int which, u64 *value);
 int siso_ensure_keys(siso_cache *c, long need);  // room for `need` phase-1 keys in c->keys (may synchronise and allocate)
+// Temporaries of a call that rebuilds the cache.  siso_arena makes room for `device_bytes` and `host_bytes` (c->arena,
+// c->pinned; earlier contents are lost: it synchronises before it lets go of them); siso_arena_done, at the
+// call's end, gives back what is larger than the library keeps between calls.
+#define SISO_ARENA_KEEP (512l << 20)
+#define SISO_PINNED_KEEP (64l << 20)
+int siso_arena(siso_cache *c, size_t device_bytes, size_t host_bytes);
+void siso_arena_done(siso_cache *c);
+struct Carver {  // hands out aligned pieces; with a null base it only adds up
+    char *base;
+    size_t used = 0;
+    template <class U>
+    U *take(size_t count) {
+        U *at = (U *)(base + used);
+        used += (count * sizeof(U) + 255) & ~(size_t)255;
+        return at;
+    }
+};
 int siso_second_set(siso_cache *c);    // make sure the second set of arrays exists (allocates once; synchronises then)
 void siso_swap_sets(siso_cache *c);    // the second set becomes the cache, the old arrays the second set  // synchronises
