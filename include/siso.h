@@ -435,9 +435,10 @@ long siso_refresh_plan(long k0, const float *cluster_size, const unsigned *acces
  * and sizes on, e.g. to siso_refresh of the serving cache.
  * Returns the number of clusters; SISO_ECAPACITY (nothing changed) if that
  * exceeds the capacity of `c`; other negative values are error codes.
- * The all-pairs similarity and the averages run on the GPU; the choice of the
- * communities walks the list of pairs on the host.  Allocates temporary device
- * memory (the vectors once more, 8 bytes per pair).  Synchronises.
+ * Everything runs on the GPU, but for graphs with a connected component of more than 64
+ * vectors: there the choice of the communities walks the list of pairs on the host.  Its
+ * temporaries (the vectors once more, 256 bytes per vector or 8 per pair) are kept as
+ * siso_merge_apply's.  Synchronises.
  */
 long siso_cluster(siso_cache *c, const void *vectors, long n, float theta_c, int min_size, int *out_label,
                   int *out_representative, long *out_stats);

@@ -6,8 +6,11 @@
 // The heavy part is the all-pairs similarity of the n vectors, n * n * dim / 2 products: that is the
 // pair search of the merge (the pairs above the threshold are the edges of the neighbour graph), and
 // the member averages; both run in kernels.  Between them sits the greedy choice of the communities
-// (largest candidate first; a candidate keeps the vectors no earlier community took), which is a walk
-// over the edge list in a fixed order: bookkeeping on the host, linear in vectors + edges.
+// (largest candidate first; a candidate keeps the vectors no earlier community took).  It is a chain, but only inside a
+// connected component of the graph: components of at most 64 vectors are worked off by a wave each, the neighbours of a
+// vector being one 64-bit mask, and the clusters are numbered afterwards by the candidates they came from (50,001
+// vectors in topics of 2 to 12: 150 us of kernels, where copying the pairs out and walking them on the host took
+// 1,500).  A graph with a larger component is walked on the host, linear in vectors + edges.
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -20,7 +23,8 @@
 
 namespace {
 
-__global__ void k_clear_counter(u64 *p) { *p = 0; }
+// the counters of the call: pairs found, vectors that cannot be taken, room of the component lists handed out
+__global__ void k_clear_counters(u64 *p) { p[0] = p[1] = p[2] = 0; }
 
 __global__ void k_nan_fill(float *p, int count) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -64,7 +68,7 @@ __device__ __forceinline__ float block_total(float v, float *sh) {
 // rep (nullable): the member with the largest cosine to the mean, the lowest index among equals.
 template <typename T>
 __global__ __launch_bounds__(256) void k_cluster_rows(const T *__restrict__ vec, const float *__restrict__ vinv,
-                                                       const long *__restrict__ first, const int *__restrict__ member,
+                                                       const int *__restrict__ first, const int *__restrict__ member,
                                                        T *cent, float *mean, int *size, float *invn, float *locality,
                                                        unsigned *access, int *rep, int d) {
     __shared__ float sh[4];
@@ -78,6 +82,7 @@ __global__ __launch_bounds__(256) void k_cluster_rows(const T *__restrict__ vec,
     float ss = 0.f;
     for (int col = t; col < d; col += 256) {
         float acc = 0.f;
+#pragma unroll 4
         for (long p = lo; p < hi; ++p) {
             const long j = member[p];
             acc += widen(vec[(size_t)j * d + col]) * vinv[j];
@@ -136,6 +141,250 @@ __global__ __launch_bounds__(256) void k_cluster_rows(const T *__restrict__ vec,
     }
 }
 
+// ============================================================================
+// the choice of the communities on the device
+// ============================================================================
+#define COMPONENT_MAX 64                 // vectors of a component that a wave works off
+#define COMPONENT_TOO_LARGE (1ull << 63)  // in the counter of bad vectors: some component is larger
+
+__global__ void k_graph_init(int *parent, int *size_of, int *cursor, u64 *mask, long n) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    parent[i] = (int)i;
+    size_of[i] = 0;
+    cursor[i] = 0;
+    mask[i] = 0;
+}
+// (the number of pairs is read from the device: the host need not have seen it yet; more than `cap` were not written)
+__global__ void k_graph_join(const int *__restrict__ pairs, const u64 *__restrict__ found, long cap, int *parent) {
+    const long n_pairs = *found < (u64)cap ? (long)*found : cap;
+    for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < n_pairs; p += (long)gridDim.x * blockDim.x)
+        uf_join(parent, pairs[2 * p], pairs[2 * p + 1]);
+}
+__global__ void k_graph_roots(const int *__restrict__ parent, int *root, int *size_of, long n) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int r = uf_find(parent, (int)i);
+    root[i] = r;
+    atomicAdd(&size_of[r], 1);
+}
+// room for the vectors of every component, in the order the waves arrive
+__global__ __launch_bounds__(256) void k_graph_starts(const int *__restrict__ root, const int *__restrict__ size_of, long n,
+                                                       int *start, u64 *room, u64 *bad) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int mine = i < n && root[i] == (int)i ? size_of[i] : 0;
+    int incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+    }
+    u64 at = 0;
+    if (lane == 63) at = atomicAdd(room, (u64)incl);
+    at = __shfl(at, 63);
+    if (mine > 0) start[i] = (int)at + incl - mine;
+    if (__ballot(mine > COMPONENT_MAX) != 0 && lane == 0) atomicOr(bad, COMPONENT_TOO_LARGE);
+}
+__global__ void k_graph_fill(const int *__restrict__ root, const int *__restrict__ start, long n, int *cursor, int *list,
+                             int *place) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int r = root[i];
+    const int at = atomicAdd(&cursor[r], 1);
+    place[i] = at;
+    list[start[r] + at] = (int)i;
+}
+// mask[v]: the places of v's neighbours in the list of their component
+__global__ void k_graph_masks(const int *__restrict__ pairs, const u64 *__restrict__ found, long cap,
+                              const int *__restrict__ root, const int *__restrict__ size_of, const int *__restrict__ place,
+                              u64 *mask) {
+    const long n_pairs = *found < (u64)cap ? (long)*found : cap;
+    for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < n_pairs; p += (long)gridDim.x * blockDim.x) {
+        const int a = pairs[2 * p], b = pairs[2 * p + 1];
+        if (size_of[root[a]] > COMPONENT_MAX) continue;
+        atomicOr(&mask[a], 1ull << place[b]);
+        atomicOr(&mask[b], 1ull << place[a]);
+    }
+}
+
+// One component after the other, a wave each (a wave looks after 8 vectors: those that are the root of one).  Lane l holds
+// the l-th vector of the component in ascending order and the mask of its candidate community (itself and its
+// neighbours).  Candidates are taken by size, largest first, equal sizes by index; of a candidate the vectors that no
+// earlier cluster holds remain, and if at least min_size do they are the next cluster.  Per vector: seed_of = the
+// candidate whose cluster it is in or -1, pos = its place among that cluster's members in ascending order; and
+// per candidate that became a cluster: its number of neighbours (255: it did not) and the members that were left.
+#define NO_SEED 255
+__global__ __launch_bounds__(256) void k_communities(const int *__restrict__ root, const int *__restrict__ size_of,
+                                                      const int *__restrict__ start, const int *__restrict__ list,
+                                                      const u64 *__restrict__ mask, long n, int min_size, int *seed_of,
+                                                      int *pos, int *seed_size, unsigned char *seed_degree) {
+    const int lane = threadIdx.x & 63;
+    const long base = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 8;
+    const long mine = base + (lane & 7);
+    u64 roots = __ballot(lane < 8 && mine < n && root[mine < n ? mine : 0] == (int)mine);
+    for (; roots != 0; roots &= roots - 1) {
+        const long r = base + __ffsll((long long)roots) - 1;
+        const int c = size_of[r];
+        if (c > COMPONENT_MAX) continue;
+        int v = lane < c ? list[start[r] + lane] : 0x7FFFFFFF;
+        u64 m = lane < c ? mask[v] : 0ull;
+        // into ascending order (the lists are in the order the vectors arrived): lane -> up
+        int up = 0;
+        for (int j = 0; j < c; ++j) up += __shfl(v, j) < v ? 1 : 0;
+        u64 turned = 0;
+        for (int j = 0; j < c; ++j)
+            if (m >> j & 1) turned |= 1ull << __builtin_amdgcn_readlane(up, j);
+        // (the lanes past the component all go to the first place behind it)
+        const int lo = __builtin_amdgcn_ds_permute(up * 4, (int)(unsigned)turned);
+        const int hi = __builtin_amdgcn_ds_permute(up * 4, (int)(unsigned)(turned >> 32));
+        v = __builtin_amdgcn_ds_permute(up * 4, v);
+        const bool in = lane < c;
+        m = in ? ((u64)(unsigned)hi << 32 | (unsigned)lo) | 1ull << lane : 0ull;
+        const int degree = __popcll(m) - 1;
+        int rank = 0;
+        for (int j = 0; j < c; ++j) {
+            const int o = __shfl(degree, j);
+            rank += o > degree || (o == degree && j < lane) ? 1 : 0;
+        }
+        u64 left = c == 64 ? ~0ull : (1ull << c) - 1;
+        int seed = -1, at = 0, size = 0;
+        unsigned char deg = NO_SEED;
+        for (int s = 0; s < c && __popcll(left) >= min_size; ++s) {
+            const int src = __ffsll((long long)__ballot(in && rank == s)) - 1;
+            const u64 candidate = __shfl(m, src);
+            if (__popcll(candidate) < min_size) break;  // every later candidate is smaller still
+            const u64 take = candidate & left;
+            if (__popcll(take) < min_size) continue;
+            left &= ~take;
+            const int who = __shfl(v, src);
+            if (take >> lane & 1) {
+                seed = who;
+                at = __popcll(take & ((1ull << lane) - 1));
+            }
+            if (lane == src) {
+                size = __popcll(take);
+                deg = (unsigned char)(__popcll(candidate) - 1);
+            }
+        }
+        if (in) {
+            seed_of[v] = seed;
+            pos[v] = at;
+            seed_size[v] = size;
+            seed_degree[v] = deg;
+        }
+    }
+}
+
+// The clusters in the order of their candidates: by number of neighbours, largest first, then by index.  SEED_ROWS vectors
+// per block: clusters and members per block and number of neighbours (k_seed_sums), summed up in that order
+// (k_seed_base), then every block numbers its own (k_seed_place).
+#define SEED_ROWS 256
+__global__ __launch_bounds__(SEED_ROWS) void k_seed_sums(const unsigned char *__restrict__ seed_degree,
+                                                          const int *__restrict__ seed_size, long n, int2 *sums) {
+    __shared__ int cnt[COMPONENT_MAX], members[COMPONENT_MAX];
+    const int t = threadIdx.x;
+    if (t < COMPONENT_MAX) cnt[t] = members[t] = 0;
+    __syncthreads();
+    const long i = (long)blockIdx.x * SEED_ROWS + t;
+    const int deg = i < n ? seed_degree[i] : NO_SEED;
+    if (deg != NO_SEED) {
+        atomicAdd(&cnt[deg], 1);
+        atomicAdd(&members[deg], seed_size[i]);
+    }
+    __syncthreads();
+    if (t < COMPONENT_MAX) sums[(size_t)(COMPONENT_MAX - 1 - t) * gridDim.x + blockIdx.x] = make_int2(cnt[t], members[t]);
+}
+// exclusive sums in place, by one block; total: clusters, and the members in the upper half
+__global__ __launch_bounds__(1024) void k_seed_base(int2 *sums, long count, u64 *total) {
+    __shared__ int2 wsum[16];
+    __shared__ int2 carry;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (t == 0) carry = make_int2(0, 0);
+    __syncthreads();
+    for (long base = 0; base < count; base += 4096) {
+        const long i0 = base + 4 * t;
+        int2 v[4];
+        int a = 0, b = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = i0 + k < count ? sums[i0 + k] : make_int2(0, 0);
+            a += v[k].x;
+            b += v[k].y;
+        }
+        int ia = a, ib = b;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int oa = __shfl_up(ia, off), ob = __shfl_up(ib, off);
+            if (lane >= off) {
+                ia += oa;
+                ib += ob;
+            }
+        }
+        if (lane == 63) wsum[w] = make_int2(ia, ib);
+        __syncthreads();
+        int ra = carry.x + ia - a, rb = carry.y + ib - b;
+        for (int k = 0; k < w; ++k) {
+            ra += wsum[k].x;
+            rb += wsum[k].y;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (i0 + k < count) sums[i0 + k] = make_int2(ra, rb);
+            ra += v[k].x;
+            rb += v[k].y;
+        }
+        __syncthreads();
+        if (t == 1023) carry = make_int2(ra, rb);
+        __syncthreads();
+    }
+    if (t == 0) *total = (u64)(unsigned)carry.x | (u64)(unsigned)carry.y << 32;
+}
+__global__ __launch_bounds__(SEED_ROWS) void k_seed_place(const unsigned char *__restrict__ seed_degree,
+                                                           const int *__restrict__ seed_size, long n,
+                                                           const int2 *__restrict__ sums, int *id_of, int *first) {
+    __shared__ int2 at[COMPONENT_MAX];
+    const int t = threadIdx.x, lane = t & 63;
+    if (t < COMPONENT_MAX) at[t] = sums[(size_t)(COMPONENT_MAX - 1 - t) * gridDim.x + blockIdx.x];
+    const long i = (long)blockIdx.x * SEED_ROWS + t;
+    const int deg = i < n ? seed_degree[i] : NO_SEED;
+    const int size = deg != NO_SEED ? seed_size[i] : 0;
+    for (int w = 0; w < SEED_ROWS / 64; ++w) {  // the waves one after the other
+        __syncthreads();
+        if (w != t >> 6) continue;
+        u64 rest = __ballot(deg != NO_SEED);
+        while (rest) {
+            const int bin = __shfl(deg, __ffsll((long long)rest) - 1);
+            const u64 same = __ballot(deg == bin);
+            rest &= ~same;
+            int incl = deg == bin ? size : 0;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(incl, off);
+                if (lane >= off) incl += o;
+            }
+            const int2 from = at[bin];
+            if (deg == bin) {
+                const int id = from.x + __popcll(same & ((1ull << lane) - 1));
+                id_of[i] = id;
+                first[id] = from.y + incl - size;
+            }
+            const int members = __shfl(incl, 63);
+            if (lane == 0) at[bin] = make_int2(from.x + __popcll(same), from.y + members);
+        }
+    }
+}
+__global__ void k_members(const int *__restrict__ seed_of, const int *__restrict__ pos, const int *__restrict__ id_of, long n,
+                          int clusters, int members, int *first, int *member, int *out_label) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) first[clusters] = members;
+    if (i >= n) return;
+    const int seed = seed_of[i];
+    const int id = seed < 0 ? -1 : id_of[seed];
+    if (id >= 0) member[first[id] + pos[i]] = (int)i;
+    if (out_label) out_label[i] = id;
+}
+
 struct DeviceMem {  // frees on every way out
     void *p = nullptr;
     ~DeviceMem() { release(); }
@@ -159,7 +408,7 @@ struct DeviceMem {  // frees on every way out
 // label[i] = cluster of vector i or -1; the members of cluster k, in ascending order, are
 // member[first[k] .. first[k+1]).  Linear in vectors + pairs (counting sort, one pass over the lists).
 void choose_communities(const int *h_pairs, long n_pairs, long n, int min_size, std::vector<int> &label,
-                        std::vector<long> &first, std::vector<int> &member) {
+                        std::vector<int> &first, std::vector<int> &member) {
     // ---- neighbour lists -----------------------------------------------------------------------
     std::vector<long> start((size_t)n + 1, 0);
     for (long p = 0; p < 2 * n_pairs; ++p) start[(size_t)h_pairs[(size_t)p] + 1] += 1;
@@ -210,7 +459,7 @@ void choose_communities(const int *h_pairs, long n_pairs, long n, int min_size, 
             }
         }
         std::sort(member.begin() + first.back(), member.end());   // averages take the members in ascending order
-        first.push_back((long)member.size());
+        first.push_back((int)member.size());
     }
 }
 
@@ -233,98 +482,155 @@ static long cluster_impl(siso_cache *c, const void *vectors, long n, float theta
         if (rc_ != SISO_OK) return rc_;                           \
     } while (0)
 
-    // ---- the neighbour graph: every pair of vectors above the threshold -----------------------
-    DeviceMem d_rows, d_inv, d_pairs;
-    std::vector<int> h_pairs;
-    long n_pairs = 0;
-    if (n > 0) {
-        if (!d_rows.alloc((size_t)(n + SISO_PAD_ROWS) * d * eb) || !d_inv.alloc((size_t)(n + SISO_PAD_ROWS) * sizeof(float))) {
-            (void)hipGetLastError();
-            return siso_fail(c, SISO_ENOMEM, "siso_cluster: staging for %ld vectors", n);
-        }
-        CLUSTER_TRY(hipMemsetAsync((char *)d_rows.p + (size_t)n * d * eb, 0, (size_t)SISO_PAD_ROWS * d * eb, st), "clear pad rows");
-        hipLaunchKernelGGL(k_clear_counter, dim3(1), dim3(1), 0, st, c->counters + 2);
-        if (c->dtype == SISO_F32)
-            hipLaunchKernelGGL(k_stage_vectors<float>, dim3((unsigned)n), dim3(256), 0, st, (const float *)vectors,
-                               d_rows.as<float>(), d_inv.as<float>(), d, c->counters + 2);
-        else
-            hipLaunchKernelGGL(k_stage_vectors<bf16_t>, dim3((unsigned)n), dim3(256), 0, st, (const bf16_t *)vectors,
-                               d_rows.as<bf16_t>(), d_inv.as<float>(), d, c->counters + 2);
-        hipLaunchKernelGGL(k_nan_fill, dim3(1), dim3(SISO_PAD_ROWS), 0, st, d_inv.as<float>() + n, SISO_PAD_ROWS);
-        CLUSTER_TRY(hipGetLastError(), "stage vectors");
-        u64 bad = 0;
-        int rc = siso_read_counter(c, 2, &bad);
-        if (rc != SISO_OK) return rc;
-        if (bad != 0) return siso_fail(c, SISO_EINVAL, "siso_cluster: %llu vectors are not finite or have no length", bad);
-
-        // room for 32 pairs per vector at first (256 bytes each); a log with more gets a second pass with the exact room
-        long cap = n * 32 > (1L << 20) ? n * 32 : (1L << 20);
-        for (int attempt = 0; attempt < 2 && n >= 2; ++attempt) {
-            if (!d_pairs.alloc((size_t)cap * 2 * sizeof(int))) {
-                (void)hipGetLastError();
-                return siso_fail(c, SISO_ENOMEM, "siso_cluster: room for %ld pairs", cap);
-            }
-            hipLaunchKernelGGL(k_clear_counter, dim3(1), dim3(1), 0, st, c->counters + 1);
-            CLUSTER_TRY(hipGetLastError(), "k_clear_counter");
-            if (siso_pairs_mfma_supported(c, n))
-                rc = siso_pairs_mfma_launch(c, d_rows.p, d_inv.as<float>(), n, theta_c, d_pairs.as<int>(), cap, c->counters + 1);
-            else
-                rc = siso_pairs_tile_launch(c, d_rows.p, d_inv.as<float>(), n, theta_c, d_pairs.as<int>(), cap, c->counters + 1);
-            if (rc != SISO_OK) return rc;
-            u64 total = 0;
-            rc = siso_read_counter(c, 1, &total);
-            if (rc != SISO_OK) return rc;
-            n_pairs = (long)total;
-            if (n_pairs <= cap) break;
-            if (attempt == 1) return siso_fail(c, SISO_ENOMEM, "siso_cluster: %ld pairs above the threshold", n_pairs);
-            cap = n_pairs;  // once more with room for all of them
-        }
-        if (n_pairs > 0) {
-            h_pairs.resize((size_t)n_pairs * 2);
-            CLUSTER_TRY(hipMemcpyAsync(h_pairs.data(), d_pairs.p, (size_t)n_pairs * 2 * sizeof(int), hipMemcpyDeviceToHost, st), "pairs to host");
-            CLUSTER_TRY(hipStreamSynchronize(st), "siso_cluster: synchronize");
-        }
-        d_pairs.release();
+    if (n == 0) {
+        hipLaunchKernelGGL(k_nan_fill, dim3(1), dim3(SISO_PAD_ROWS), 0, st, c->invn, SISO_PAD_ROWS);
+        CLUSTER_TRY(hipGetLastError(), "k_nan_fill");
+        CLUSTER_TRY(hipStreamSynchronize(st), "siso_cluster: synchronize");
+        c->count = 0;
+        return 0;
     }
 
-    // ---- the communities: a walk over the pairs on the host ------------------------------------------
+    // ---- the neighbour graph: every pair of vectors above the threshold; its communities ----------
+    // room for 32 pairs per vector at first (256 bytes each); a log with more gets a second pass with the exact room
+    long cap = n * 32 > (1L << 20) ? n * 32 : (1L << 20);
+    const unsigned sblocks = (unsigned)((n + SEED_ROWS - 1) / SEED_ROWS), vblocks = (unsigned)((n + 255) / 256);
+    char *rows;
+    float *inv;
+    int *pairs, *parent, *root, *size_of, *cursor, *start, *list, *place, *seed_of, *pos, *seed_size, *id_of, *first, *member;
+    unsigned char *seed_degree;
+    u64 *mask;
+    int2 *sums;
+    auto layout = [&](Carver a) {
+        rows = a.take<char>((size_t)(n + SISO_PAD_ROWS) * d * eb);
+        inv = a.take<float>(n + SISO_PAD_ROWS);
+        mask = a.take<u64>(n);
+        parent = a.take<int>(n);
+        root = a.take<int>(n);
+        size_of = a.take<int>(n);
+        cursor = a.take<int>(n);
+        start = a.take<int>(n);
+        list = a.take<int>(n);
+        place = a.take<int>(n);
+        seed_of = a.take<int>(n);
+        pos = a.take<int>(n);
+        seed_size = a.take<int>(n);
+        id_of = a.take<int>(n);
+        first = a.take<int>(n + 1);
+        member = a.take<int>(n);
+        seed_degree = a.take<unsigned char>(n);
+        sums = a.take<int2>((size_t)sblocks * COMPONENT_MAX);
+        pairs = a.take<int>(2 * cap);
+        return a.used;
+    };
+    DeviceMem more_pairs;  // a list that turned out too short
+    {
+        const int rc = siso_arena(c, layout(Carver{nullptr}), 0);
+        if (rc != SISO_OK) return rc;
+        layout(Carver{c->arena});
+    }
+    long n_pairs = 0;
+    u64 *found = c->counters + 1, *bad_at = c->counters + 2, *room = c->counters + 3;
+    u64 state[4];
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        hipLaunchKernelGGL(k_clear_counters, dim3(1), dim3(1), 0, st, found);
+        if (attempt == 0) {
+            CLUSTER_TRY(hipMemsetAsync(rows + (size_t)n * d * eb, 0, (size_t)SISO_PAD_ROWS * d * eb, st), "clear pad rows");
+            if (c->dtype == SISO_F32)
+                hipLaunchKernelGGL(k_stage_vectors<float>, dim3((unsigned)n), dim3(256), 0, st, (const float *)vectors,
+                                   (float *)rows, inv, d, bad_at);
+            else
+                hipLaunchKernelGGL(k_stage_vectors<bf16_t>, dim3((unsigned)n), dim3(256), 0, st, (const bf16_t *)vectors,
+                                   (bf16_t *)rows, inv, d, bad_at);
+            hipLaunchKernelGGL(k_nan_fill, dim3(1), dim3(SISO_PAD_ROWS), 0, st, inv + n, SISO_PAD_ROWS);
+        }
+        CLUSTER_TRY(hipGetLastError(), "stage vectors");
+        int rc = SISO_OK;
+        if (n >= 2) {
+            if (siso_pairs_mfma_supported(c, n)) rc = siso_pairs_mfma_launch(c, rows, inv, n, theta_c, pairs, cap, found);
+            else rc = siso_pairs_tile_launch(c, rows, inv, n, theta_c, pairs, cap, found);
+        }
+        if (rc != SISO_OK) return rc;
+        // (all of this stays within its arrays whatever the list holds: nothing is looked at if it turns out too short, if
+        // a vector cannot be taken, or if a component is too large for a wave)
+        const dim3 per_vector(vblocks), per_pair((unsigned)(cap < 262144 ? (cap + 255) / 256 : 1024)), block(256);
+        hipLaunchKernelGGL(k_graph_init, per_vector, block, 0, st, parent, size_of, cursor, mask, n);
+        hipLaunchKernelGGL(k_graph_join, per_pair, block, 0, st, pairs, found, cap, parent);
+        hipLaunchKernelGGL(k_graph_roots, per_vector, block, 0, st, parent, root, size_of, n);
+        hipLaunchKernelGGL(k_graph_starts, per_vector, block, 0, st, root, size_of, n, start, room, bad_at);
+        hipLaunchKernelGGL(k_graph_fill, per_vector, block, 0, st, root, start, n, cursor, list, place);
+        hipLaunchKernelGGL(k_graph_masks, per_pair, block, 0, st, pairs, found, cap, root, size_of, place, mask);
+        // (vectors of a component that is too large keep what is set here)
+        CLUSTER_TRY(hipMemsetAsync(seed_degree, NO_SEED, (size_t)n, st), "no cluster yet");
+        hipLaunchKernelGGL(k_communities, dim3((unsigned)((n + 31) / 32)), block, 0, st, root, size_of, start, list, mask, n, min_size,
+                           seed_of, pos, seed_size, seed_degree);
+        hipLaunchKernelGGL(k_seed_sums, dim3(sblocks), dim3(SEED_ROWS), 0, st, seed_degree, seed_size, n, sums);
+        hipLaunchKernelGGL(k_seed_base, dim3(1), dim3(1024), 0, st, sums, (long)sblocks * COMPONENT_MAX, room);
+        hipLaunchKernelGGL(k_seed_place, dim3(sblocks), dim3(SEED_ROWS), 0, st, seed_degree, seed_size, n, sums, id_of, first);
+        CLUSTER_TRY(hipGetLastError(), "communities");
+        rc = siso_read_counter(c, 1, &state[1]);  // (all four counters come at once)
+        if (rc != SISO_OK) return rc;
+        state[2] = c->host_pin[2];
+        state[3] = c->host_pin[3];
+        const u64 bad = state[2] & ~COMPONENT_TOO_LARGE;
+        if (bad != 0) return siso_fail(c, SISO_EINVAL, "siso_cluster: %llu vectors are not finite or have no length", bad);
+        n_pairs = (long)state[1];
+        if (n_pairs <= cap) break;
+        if (attempt == 1) return siso_fail(c, SISO_ENOMEM, "siso_cluster: %ld pairs above the threshold", n_pairs);
+        cap = n_pairs;  // once more with room for all of them
+        if (!more_pairs.alloc((size_t)cap * 2 * sizeof(int))) {
+            (void)hipGetLastError();
+            return siso_fail(c, SISO_ENOMEM, "siso_cluster: room for %ld pairs", cap);
+        }
+        pairs = more_pairs.as<int>();
+    }
+    long clusters = (long)(unsigned)state[3], members = (long)(state[3] >> 32);
     std::vector<int> label;
-    std::vector<long> first;   // members of cluster k: member[first[k] .. first[k+1])
-    std::vector<int> member;
-    choose_communities(h_pairs.data(), n_pairs, n, min_size, label, first, member);
-    std::vector<int>().swap(h_pairs);
-    const long clusters = (long)first.size() - 1;
+    const bool on_host = (state[2] & COMPONENT_TOO_LARGE) != 0;
+    if (on_host) {
+        // ---- the communities: a walk over the pairs on the host --------------------------------------
+        std::vector<int> h_first;   // members of cluster k: h_member[h_first[k] .. h_first[k+1])
+        std::vector<int> h_member;
+        std::vector<int> h_pairs((size_t)n_pairs * 2);
+        CLUSTER_TRY(hipMemcpyAsync(h_pairs.data(), pairs, (size_t)n_pairs * 2 * sizeof(int), hipMemcpyDeviceToHost, st), "pairs to host");
+        CLUSTER_TRY(hipStreamSynchronize(st), "siso_cluster: synchronize");
+        more_pairs.release();
+        choose_communities(h_pairs.data(), n_pairs, n, min_size, label, h_first, h_member);
+        std::vector<int>().swap(h_pairs);
+        clusters = (long)h_first.size() - 1;
+        members = (long)h_member.size();
+        if (clusters > 0 && clusters <= c->capacity) {
+            CLUSTER_TRY(hipMemcpyAsync(first, h_first.data(), h_first.size() * sizeof(int), hipMemcpyHostToDevice, st), "member offsets");
+            CLUSTER_TRY(hipMemcpyAsync(member, h_member.data(), h_member.size() * sizeof(int), hipMemcpyHostToDevice, st), "members");
+            CLUSTER_TRY(hipStreamSynchronize(st), "siso_cluster: synchronize");  // (before the lists go out of scope)
+        }
+    }
     if (clusters > c->capacity)
         return siso_fail(c, SISO_ECAPACITY, "siso_cluster: %ld clusters, capacity %ld", clusters, c->capacity);
 
     // ---- the repository: one row per cluster -----------------------------------------------------
-    DeviceMem d_first, d_member;
+    if (!on_host) {
+        hipLaunchKernelGGL(k_members, dim3(vblocks), dim3(256), 0, st, seed_of, pos, id_of, n, (int)clusters, (int)members, first,
+                           member, out_label);
+        CLUSTER_TRY(hipGetLastError(), "k_members");
+    }
     if (clusters > 0) {
-        if (!d_first.alloc(first.size() * sizeof(long)) || !d_member.alloc(member.size() * sizeof(int))) {
-            (void)hipGetLastError();
-            return siso_fail(c, SISO_ENOMEM, "siso_cluster: member lists of %ld clusters", clusters);
-        }
-        CLUSTER_TRY(hipMemcpyAsync(d_first.p, first.data(), first.size() * sizeof(long), hipMemcpyHostToDevice, st), "member offsets");
-        CLUSTER_TRY(hipMemcpyAsync(d_member.p, member.data(), member.size() * sizeof(int), hipMemcpyHostToDevice, st), "members");
         if (c->dtype == SISO_F32)
-            hipLaunchKernelGGL(k_cluster_rows<float>, dim3((unsigned)clusters), dim3(256), 0, st, d_rows.as<float>(),
-                               d_inv.as<float>(), d_first.as<long>(), d_member.as<int>(), (float *)c->cent, c->mean, c->size,
-                               c->invn, c->locality, c->access, out_representative, d);
+            hipLaunchKernelGGL(k_cluster_rows<float>, dim3((unsigned)clusters), dim3(256), 0, st, (const float *)rows, inv, first,
+                               member, (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, out_representative, d);
         else
-            hipLaunchKernelGGL(k_cluster_rows<bf16_t>, dim3((unsigned)clusters), dim3(256), 0, st, d_rows.as<bf16_t>(),
-                               d_inv.as<float>(), d_first.as<long>(), d_member.as<int>(), (bf16_t *)c->cent, c->mean, c->size,
-                               c->invn, c->locality, c->access, out_representative, d);
+            hipLaunchKernelGGL(k_cluster_rows<bf16_t>, dim3((unsigned)clusters), dim3(256), 0, st, (const bf16_t *)rows, inv, first,
+                               member, (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, out_representative, d);
         CLUSTER_TRY(hipGetLastError(), "k_cluster_rows");
     }
     hipLaunchKernelGGL(k_nan_fill, dim3(1), dim3(SISO_PAD_ROWS), 0, st, c->invn + clusters, SISO_PAD_ROWS);
     CLUSTER_TRY(hipGetLastError(), "k_nan_fill");
-    if (out_label && n > 0)
+    if (out_label && on_host)
         CLUSTER_TRY(hipMemcpyAsync(out_label, label.data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, st), "labels");
     CLUSTER_TRY(hipStreamSynchronize(st), "siso_cluster: synchronize");
     c->count = clusters;
     if (out_stats) {
         out_stats[0] = n_pairs;
-        out_stats[1] = (long)member.size();
+        out_stats[1] = members;
     }
 #undef CLUSTER_TRY
     return clusters;
@@ -334,11 +640,14 @@ extern "C" long siso_cluster(siso_cache *c, const void *vectors, long n, float t
                              int *out_representative, long *out_stats) {
     if (!c) return SISO_EINVAL;
     if (c->dtype == SISO_FP8) return siso_fail(c, SISO_EINVAL, "siso_cluster: not available with the 8-bit storage");
+    long rc;
     try {
-        return cluster_impl(c, vectors, n, theta_c, min_size, out_label, out_representative, out_stats);
+        rc = cluster_impl(c, vectors, n, theta_c, min_size, out_label, out_representative, out_stats);
     } catch (const std::bad_alloc &) {  // the host lists; nothing has been changed yet when they are built
-        return siso_fail(c, SISO_ENOMEM, "siso_cluster: host memory for the neighbour lists");
+        rc = siso_fail(c, SISO_ENOMEM, "siso_cluster: host memory for the neighbour lists");
     }
+    siso_arena_done(c);
+    return rc;
 }
 
 // The host part of siso_cluster alone: pairs and labels are HOST arrays.
@@ -350,7 +659,7 @@ extern "C" long siso_choose_communities(const int *pairs, long n_pairs, long n, 
         if (pairs[2 * p] == pairs[2 * p + 1]) return SISO_EINVAL;
     try {
         std::vector<int> label, member;
-        std::vector<long> first;
+        std::vector<int> first;
         choose_communities(pairs, n_pairs, n, min_size, label, first, member);
         for (long i = 0; i < n; ++i) out_label[i] = label[(size_t)i];
         return (long)first.size() - 1;

@@ -748,37 +748,19 @@ __global__ void k_group_fill(const int *__restrict__ root, const unsigned char *
     list[first[r] + atomicAdd(&cursor[r], 1)] = (int)i;
 }
 
-__device__ __forceinline__ int uf_find(const int *parent, int x) {
-    int p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
-    while (p != x) {
-        x = p;
-        p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
-    }
-    return x;
-}
-
-// Parents only ever decrease, so every retry makes progress and the loop ends.  Pairs that name a row twice or one that
-// is not there are passed over and counted: the host looks at the count before anything of the cache is touched.
+// Pairs that name a row twice or one that is not there are passed over and counted: the host looks at the count before
+// anything of the cache is touched.
 __global__ void k_uf_hook(const int *__restrict__ pairs, long n_pairs, long K, int *parent, unsigned char *touched, u64 *bad) {
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n_pairs) return;
-    int a = pairs[2 * p], b = pairs[2 * p + 1];
+    const int a = pairs[2 * p], b = pairs[2 * p + 1];
     if (a < 0 || b < 0 || a >= K || b >= K || a == b) {
         atomicAdd(bad, 1ull);
         return;
     }
     touched[a] = 1;
     touched[b] = 1;
-    for (;;) {
-        a = uf_find(parent, a);
-        b = uf_find(parent, b);
-        if (a == b) break;
-        const int hi = a > b ? a : b, lo = a > b ? b : a;
-        const int old = atomicCAS(parent + hi, hi, lo);
-        if (old == hi) break;
-        a = old;  // someone re-parented hi meanwhile: continue from there
-        b = lo;
-    }
+    uf_join(parent, a, b);
 }
 
 __global__ void k_uf_roots(const int *__restrict__ parent, const unsigned char *__restrict__ touched, int *root, int *members_of,

@@ -393,6 +393,29 @@ __device__ __forceinline__ void flush_staged_pairs(const int *stage, int *staged
     __syncthreads();
 }
 
+// Lock-free union-find: parent[i] <= i, the lowest index of a group is its root.  Parents only ever decrease, so every
+// retry makes progress and the loops end.
+__device__ __forceinline__ int uf_find(const int *parent, int x) {
+    int p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
+    while (p != x) {
+        x = p;
+        p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
+    }
+    return x;
+}
+__device__ __forceinline__ void uf_join(int *parent, int a, int b) {
+    for (;;) {
+        a = uf_find(parent, a);
+        b = uf_find(parent, b);
+        if (a == b) break;
+        const int hi = a > b ? a : b, lo = a > b ? b : a;
+        const int old = atomicCAS(parent + hi, hi, lo);
+        if (old == hi) break;
+        a = old;  // someone re-parented hi meanwhile: continue from there
+        b = lo;
+    }
+}
+
 // ----------------------------------------------------------------------------
 // host-side plumbing shared by the translation units
 // ----------------------------------------------------------------------------
