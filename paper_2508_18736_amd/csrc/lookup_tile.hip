@@ -62,7 +62,7 @@ __device__ __forceinline__ u32x4_t load_chunk(const T *row, int k, int d) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if constexpr (sizeof(T) == 4) v[i] = __float_as_uint(x[i]);
-            else v[i] = (unsigned)x[2 * i] | ((unsigned)x[2 * i + 1] << 16);
+            else if constexpr (sizeof(T) == 2) v[i] = (unsigned)x[2 * i] | ((unsigned)x[2 * i + 1] << 16);
         }
         return v;
     }
@@ -94,6 +94,16 @@ __device__ __forceinline__ f32x16 product(u32x4_t a, u32x4_t b, f32x16 acc, floa
 }
 __device__ __forceinline__ f32x16 product(u32x4_t a, u32x4_t b, f32x16 acc, bf16_t) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+
+// (codes: the 16-deep form takes the two halves of a chunk one after the other, on both sides alike)
+__device__ __forceinline__ f32x16 product(u32x4_t a, u32x4_t b, f32x16 acc, fp8_t) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int j = 0; j < 4; j += 2)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(__builtin_bit_cast(long, u32x2{a[j], a[j + 1]}),
+                                                         __builtin_bit_cast(long, u32x2{b[j], b[j + 1]}), acc, 0, 0, 0);
+    return acc;
 }
 
 // Everything the wave holds in LDS is written or read before the workgroup goes on; loads from memory stay in flight.
@@ -428,7 +438,10 @@ int pairs_launch_t(siso_cache *c, const void *rows, const float *invn, long coun
 // With about half the units busy (126 such tiles: 31.8 against 32.3; of 256 elements 17.9 against 16.5) the two meet.
 int siso_tile_preferred(const siso_cache *c, long n) {
     const long tiles = (c->count + 255) / 256 * ((n + 255) / 256);
-    return c->dtype == SISO_BF16 && c->opt_mfma_config == 0 && tiles < 112;
+    // Codes (twice the rate of the matrix cores in the pipelined kernels): n 64, K 32,000: 19.4 / 16.7; n 256, K 16,000:
+    // 23.5 / 20.6, K 32,000: 24.2 / 28.7; n 512, K 16,000: 23.5 / 29.0; n 1,024, K 4,000: 24.2 / 21.5.
+    const long limit = c->dtype == SISO_FP8 && n > 128 ? 70 : 112;
+    return c->dtype != SISO_F32 && c->opt_mfma_config == 0 && tiles < limit;
 }
 
 int siso_tile_slices(const siso_cache *c, long n) { return c->count < 1 || n < 1 ? 1 : tile_plan(c, n).slices; }
@@ -436,12 +449,14 @@ int siso_tile_slices(const siso_cache *c, long n) { return c->count < 1 || n < 1
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys) {
     const TilePlan p = tile_plan(c, n);
     if (p.slices != slices) return siso_fail(c, SISO_EINVAL, "tiled lookup: plan mismatch");
+    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, false>(c, queries, n, p, keys, nullptr, 0);  // (whole slabs)
     return c->dtype == SISO_F32 ? lookup_launch_t<float, false>(c, queries, n, p, keys, nullptr, 0)
                                 : lookup_launch_t<bf16_t, false>(c, queries, n, p, keys, nullptr, 0);
 }
 
 int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng) {
     const TilePlan p = tile_plan(c, n);
+    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, true>(c, queries, n, p, nullptr, groups, ng);
     return c->dtype == SISO_F32 ? lookup_launch_t<float, true>(c, queries, n, p, nullptr, groups, ng)
                                 : lookup_launch_t<bf16_t, true>(c, queries, n, p, nullptr, groups, ng);
 }

@@ -1430,7 +1430,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
     int slices = 1;
     const int path = c->count > 0 ? choose_path(c, n) : SISO_PATH_SCALAR;
     const bool fp8 = c->dtype == SISO_FP8;
-    if (fp8 && c->count > 0 && path == SISO_PATH_SCALAR)
+    if (fp8 && c->count > 0 && path == SISO_PATH_SCALAR && !siso_tile_preferred(c, n))
         return siso_fail(c, SISO_EINVAL, "siso_lookup: the 8-bit storage has no scalar kernel");
     if (c->count > 0) {
         switch (path) {
@@ -1472,7 +1472,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
     if (c->count > 0) {
         if (!static_keys) siso_prof_begin(c);
         switch (path) {
-            case SISO_PATH_SCALAR: rc = siso_tile_launch(c, queries, n, slices, keys); break;
+            case SISO_PATH_SCALAR: rc = siso_tile_launch(c, kernel_queries, n, slices, keys); break;
             case SISO_PATH_MFMA: rc = siso_mfma_launch(c, kernel_queries, n, slices, keys, &row_keys); break;
             case SISO_PATH_SKINNY: rc = siso_skinny_launch(c, kernel_queries, n, slices, keys, &row_keys); break;
         }

@@ -586,7 +586,7 @@ extern "C" int siso_lookup_topk(siso_cache *c, const void *queries, long n, int 
     int phase = PHASE_NONE;
     if (c->count > 0) {
         if (((uintptr_t)rows & 15) == 0 && !siso_tile_preferred(c, n) && siso_mfma_groups_supported(c, n)) phase = PHASE_MFMA;
-        else if (!fp8) phase = PHASE_TILE;
+        else if (!fp8 || siso_tile_preferred(c, n)) phase = PHASE_TILE;
     }
     return c->dtype == SISO_F32 ? topk_launch<float>(c, (const float *)rows, n, k, phase, nullptr, out_idx, out_sim)
            : fp8              ? topk_launch<fp8_t>(c, (const fp8_t *)rows, n, k, phase, c->fp8_qinv, out_idx, out_sim)
