@@ -372,6 +372,23 @@ TilePlan tile_plan(const siso_cache *c, long n) {
     long tps = (ct * qt + resident - 1) / resident;
     if (tps > ct) tps = ct;
     if (tps < 1) tps = 1;
+    if (p.cfg == 2) {
+        // The large tiles keep the matrix cores of a compute unit busy two at a time, so what counts is the number of tiles
+        // the busiest unit gets: among the slice lengths, the one with the least of them, a workgroup counted as its
+        // tiles and a fifth for getting started (8 query tiles x 469 centroid tiles: 94 slices of 5 leave the busiest
+        // unit 15 tiles, 59 of 8 leave it 16: 844 -> 814 us for two batches of 1,000 x 60,000 x 384 floats).
+        double least = 1e30;
+        for (long t = 1; t <= ct && t <= 64; ++t) {
+            const long groups = tiles(ct, (int)t) * qt;
+            if (groups < 512 && t > 1) break;
+            if (groups > 4096) continue;  // (the keys of a lookup stay within half of the library's static workspace)
+            const double cost = (double)tiles(groups, 256) * ((double)t + 0.2);
+            if (cost < least) {
+                least = cost;
+                tps = t;
+            }
+        }
+    }
     p.tiles_per_slice = (int)tps;
     p.slices = (int)tiles(ct, (int)tps);
     p.qtiles = (int)qt;
@@ -445,6 +462,13 @@ int siso_tile_preferred(const siso_cache *c, long n) {
 }
 
 int siso_tile_slices(const siso_cache *c, long n) { return c->count < 1 || n < 1 ? 1 : tile_plan(c, n).slices; }
+
+// No more keys than this, for n queries and any number of rows up to the capacity (the slices are not monotone in it): the
+// slices of a query tile are at most 4,096 workgroups' worth (tile_plan), and no more than there are tiles.
+long siso_tile_keys_bound(const siso_cache *c, long n) {
+    const long all = (c->capacity + 63) / 64, most = 4096 / ((n + 127) / 128) + 1;
+    return n * (all < most ? all : most);
+}
 
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys) {
     const TilePlan p = tile_plan(c, n);

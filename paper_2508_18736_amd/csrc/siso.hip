@@ -1394,6 +1394,8 @@ extern "C" int siso_reserve(siso_cache *c, long n) {
         const long a = keys_needed(c, b), f = keys_needed(&full, b);
         need = a > need ? a : need;
         need = f > need ? f : need;
+        const long t = siso_tile_keys_bound(c, b);
+        need = t > need ? t : need;
         if (b == n) break;
     }
     if (need > c->keys_cap) {

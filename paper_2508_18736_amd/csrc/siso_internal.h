@@ -430,6 +430,7 @@ int siso_check_hip(siso_cache *c, hipError_t e, const char *what);
 // handle this cache / batch).
 int siso_tile_preferred(const siso_cache *c, long n);  // 1 = small: rather these kernels, also where siso_mfma_* could
 int siso_tile_slices(const siso_cache *c, long n);
+long siso_tile_keys_bound(const siso_cache *c, long n);
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys);
 int siso_mfma_slices(const siso_cache *c, long n);
 int siso_mfma_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
