@@ -155,15 +155,16 @@ int siso_lookup_multi(siso_cache *c, const void *queries, long n, const float *t
  * the remaining entries are (-1, -inf); a query holding a NaN or an infinity gets
  * (-1, NaN) throughout; a query without length has similarity 0 to every centroid.
  * No threshold is involved and no access is counted.
- * bf16 caches whose dimension is a multiple of 64, and 8-bit caches (the batch is
- * quantised as in a lookup; similarities are those of the stored code vectors), take
- * two passes of the fused MFMA kernel (the k-th largest of the per-slice maxima of
- * the first pass bounds the k-th best similarity from below; the second pass lists
- * the few rows that reach the bound;
- * their cosines are then recomputed and ranked); other caches, caches of fewer than
- * 512 * k centroids and queries with more than 128 rows at the bound (many exact
- * duplicates) are scanned row by row.  Asynchronous; grows a workspace of the cache
- * (about 530 bytes per query) the first time a larger n is seen, which allocates.
+ * One pass of the products keeps the two largest of every 16 rows; the rows that can be
+ * among the k closest are then multiplied again and ranked (8-bit caches: the batch is
+ * quantised as in a lookup, similarities are those of the stored code vectors; those of
+ * at least 512 * k centroids take two passes, the k-th largest of the per-slice maxima of
+ * the first bounding the k-th best similarity from below, the second listing the rows
+ * that reach the bound).  Queries with hundreds of rows at the bound (many exact
+ * duplicates) are scanned row by row.  Asynchronous; grows a workspace of the cache (half
+ * a byte per query and centroid, in all about 128 MiB at most: larger batches go in
+ * pieces; two passes: about 530 bytes per query) the first time a larger need is seen,
+ * which allocates.
  */
 int siso_lookup_topk(siso_cache *c, const void *queries, long n, int k, int *out_idx, float *out_sim);
 
