@@ -1604,7 +1604,12 @@ static bool pipe_plan(const siso_cache *c, long n, int cfg, long want_wgs, PipeP
 static bool mfma_plan(const siso_cache *c, long n, PipePlan *p) {
     int cfg = c->opt_mfma_config;
     if (cfg == 0 && c->dtype == SISO_FP8) cfg = n <= 64 ? 8 : n <= 128 ? 7 : 6;  // the 64-deep MFMAs
-    if (cfg == 0) cfg = n <= 64 ? 3 : n <= 128 ? 2 : 5;
+    // Large batches: eight waves (1) or the four wide ones (5), the same tile and the same sums.  The end of a tile, where its
+    // products are scaled and compared, is hidden behind the other wave of the SIMD with eight and stands alone with
+    // four, and the shorter the dimension the more it weighs; the wide kernel reads less from LDS and runs at the power
+    // limit from 1,024 elements on.  Eight waves / wide, us, random rows: 120,000 x 2,048 x 128 74.7 / 92.7, x 256
+    // 121.6 / 137.7, x 384 168.9 / 182.9, x 512 218 / 232, x 768 314 / 325, x 1,024 411 / 419; 200,000 x 4,096 x 1,024 1,407 / 1,415.
+    if (cfg == 0) cfg = n <= 64 ? 3 : n <= 128 ? 2 : c->dim < 1024 ? 1 : 5;
     // about two workgroups per compute unit when there is enough work
     return pipe_plan(c, n, cfg, 512, p);
 }
