@@ -79,9 +79,11 @@ __device__ __forceinline__ float block_sum256(float v, float *sh) {
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// siso_load: store rows verbatim, mean = row / |row|, size = counts or 1, invn = 1/|row|.  One wave per row, whole
-// 16-byte chunks per lane if the rows allow it (`vec`); the second pass finds the row in the caches.  Bound by memory: 131,072
-// rows of 768 bf16 elements move 805 MB; element by element, a block per row, they took 341 us, this way 170 us.
+// siso_load: store rows verbatim, mean = row / |row|, size = counts or 1, invn = 1/|row|.  One wave per row; the rows are
+// copied in whole 16-byte chunks per lane if they allow it (`vec`), on a second pass that finds them in the caches.  A lane
+// sums the squares of the elements lane + 64 v + 256 e, one sum for every v, and the four are added as a block of 256
+// threads adds its waves (block_sum256): import and update find lengths in that order too.  Bound by memory: 131,072
+// rows of 768 bf16 elements move 805 MB; element by element, a block per row, they took 341 us, this way 183 us.
 template <typename T>
 __global__ __launch_bounds__(256) void k_load_rows(const T *__restrict__ src, const int *__restrict__ counts, T *cent,
                                                     float *mean, int *size, float *invn, float *locality,
@@ -93,17 +95,27 @@ __global__ __launch_bounds__(256) void k_load_rows(const T *__restrict__ src, co
     const T *row = src + (size_t)k * d;
     T *cent_row = cent + (size_t)k * d;
     float *mean_row = mean + (size_t)k * d;
-    float ss = 0.f;
-    if (vec) {
+    float ss[4] = {0.f, 0.f, 0.f, 0.f};
+    const int whole = d / 256 * 256;
 #pragma unroll 4
-        for (int e = lane * EPC; e < d; e += 64 * EPC) {
-            const u32x4_t v = *(const u32x4_t *)(row + e);
-            ss += chunk_dot(v, v, T());
+    for (int e = lane; e < whole; e += 256) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float x = widen(row[e + 64 * v]);
+            ss[v] += x * x;
         }
-    } else {
-        for (int e = lane; e < d; e += 64) ss += widen(row[e]) * widen(row[e]);
     }
-    const float n2 = wave_sum(ss);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int e = whole + lane + 64 * v;
+        if (e < d) {
+            const float x = widen(row[e]);
+            ss[v] += x * x;
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) ss[v] = wave_sum(ss[v]);
+    const float n2 = (ss[0] + ss[1]) + (ss[2] + ss[3]);
     const float inv = inv_length(n2);
     const bool ok = (inv == inv) && inv > 0.f;
     const float nrm = sqrtf(n2);
