@@ -209,11 +209,10 @@ __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, cons
             if (before == k - 1) bound_s = gval[i];
         }
         __syncthreads();
-        // 1 / |q| = 0 for a query without length: every product is 0, nothing is cut off
         const float slack = sizeof(T) == 1 ? 1e-4f : 8e-6f;
-        const float margin = qi > 0.f ? slack / qi : 0.f;
+        const float margin = slack / qi;
         const float bound = listed < k ? -INFINITY : bound_s - margin;
-        const float row_bound = bound * qi - slack;  // (in cosines; -inf * 0 is NaN, and nothing is below a NaN)
+        const float row_bound = bound * qi - slack;  // (in cosines)
         // groups within the margin below the first bound do not stand in the list: they are looked for now (rarely: the
         // first bound is usually further below the k-th largest maximum than that)
         if (first_bound > bound) {
@@ -310,7 +309,11 @@ __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, cons
         }
         return true;
     };
-    if (!from_lists()) scan_query(sh_q, qi, cent, invn, K, d, k, vec, q, val, idx, out_idx, out_sim);
+    // Queries without length (1 / |q| = 0: every cosine is 0, but the maxima still differ in their lowest bits, and those
+    // of a query whose squares underflow in more) and queries whose products come near the smallest numbers, where
+    // errors are no longer a share of |q|, are taken row by row.
+    const bool measurable = qi > 0.f && qi < 1e15f;
+    if (!measurable || !from_lists()) scan_query(sh_q, qi, cent, invn, K, d, k, vec, q, val, idx, out_idx, out_sim);
 }
 
 // Codes of a large cache, pass 1 -> bound: tau[q] = value of the k-th largest key of query q (-inf with fewer than k keys: every
