@@ -127,14 +127,14 @@ __device__ __forceinline__ void write_nan(long q, int k, int *out_idx, float *ou
 //   2. the groups that reach it (some more than k) are listed, and the k-th largest of them is the bound that counts;
 //   3. the rows that reach that, less the margin, are multiplied with the query, four rows a wave at a time;
 //   4. those that still reach it are ranked by counting.
-// The sums of the first phase and those of step 3 take the same products in another order: they differ by some 1e-7 of
-// |q| (codes: the products of the 8-bit matrix instructions are off by up to some 1e-5), and the row in the lowest bits of a
-// maximum moves it by up to 1.8e-6 of itself; the margin is 8e-6 of |q| (codes: 1e-4).
+// The sums of the first phase and those of step 3 take the same products in another order.  `slack` bounds how far a group
+// maximum can be from the cosine formed in step 3, as a share of |q| (topk_slack): at least k rows come within it of the
+// k-th largest maximum, so a row that belongs to the k best has a product within twice that.
 // `vec` = rows are 16-byte aligned and a whole number of 16-byte chunks.
 template <typename T>
 __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, const T *__restrict__ cent,
                                                     const float *__restrict__ invn, long K, int d, int k, int vec,
-                                                    const float2 *__restrict__ groups, int ng,
+                                                    const float2 *__restrict__ groups, int ng, float slack,
                                                     const float *__restrict__ q_inv, int *out_idx, float *out_sim) {
     constexpr int EPC = 16 / (int)sizeof(T);
     __shared__ u32x4_t sh_q[SISO_MAX_DIM / EPC];
@@ -209,10 +209,8 @@ __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, cons
             if (before == k - 1) bound_s = gval[i];
         }
         __syncthreads();
-        const float slack = sizeof(T) == 1 ? 1e-4f : 8e-6f;
-        const float margin = slack / qi;
-        const float bound = listed < k ? -INFINITY : bound_s - margin;
-        const float row_bound = bound * qi - slack;  // (in cosines)
+        const float bound = listed < k ? -INFINITY : bound_s - 2.f * slack / qi;
+        const float row_bound = bound * qi;  // (in cosines: slack below what the k-th of them can be)
         // groups within the margin below the first bound do not stand in the list: they are looked for now (rarely: the
         // first bound is usually further below the k-th largest maximum than that)
         if (first_bound > bound) {
@@ -292,7 +290,7 @@ __global__ __launch_bounds__(256) void k_topk_pick(const T *__restrict__ Q, cons
         }
         __syncthreads();
         const int rows = rows_s;
-        if (rows > TOPK_ROWS) return false;
+        if (rows > TOPK_ROWS || (rows < k && listed >= k)) return false;  // (the bound left k rows, or it is no bound)
         // rank by counting the entries that come before (all differ in their index)
         for (int i = t; i < rows; i += 256) {
             int before = 0;
@@ -525,6 +523,20 @@ int two_pass_launch(siso_cache *c, long n, int k, int slices, int *out_idx, floa
     return siso_check_hip(c, hipGetLastError(), "k_topk_select, k_topk_scan");
 }
 
+// How far the largest product of a group, as the first phase keeps it, can be from the cosine that k_topk_pick forms, as a
+// share of |q|.  Measured on single instructions: one of two fp32 products is off by at most 2^-23 of the magnitudes it adds,
+// the accumulator's among them, one of sixteen bf16 products by 2^-21.7.  Over d / 2 or d / 16 of them that stays below
+// d * 2^-24 of the sum of all magnitudes, which |q| |c| bounds (whole sums, the worst found: d / 4 * 2^-24 for fp32 rows with
+// elements +-c, where all roundings go the same way, d / 32 * 2^-24 in bf16).  The sum formed anew adds d / 64 + 8 roundings,
+// the row number in the lowest four bits up to 15 * 2^-23.  Codes: the 8-bit instructions cut the products of eight elements at
+// 2^-13 of the largest of them before they add them (seven are cut, by less than that each; the worst found: 1.9e-4 of |q|,
+// on rows of one large and many small elements), and the sums at 2^-23 of the accumulator.
+// 768 elements: 6.1e-5 (codes 9.0e-4); a row more or less among the candidates costs nothing to speak of.
+float topk_slack(int d, bool codes) {
+    const float rounding = (1.25f * (float)d + 64.f) * 5.9604645e-8f;  // 2^-24
+    return codes ? rounding + 7.f / 8192.f : rounding;
+}
+
 // what the first phase runs on: the pipelined kernels, the tiled kernel, or neither (then every query is scanned)
 enum { PHASE_NONE, PHASE_MFMA, PHASE_TILE };
 
@@ -549,7 +561,8 @@ int topk_launch(siso_cache *c, const T *Q, long n, int k, int phase, const float
                                  : siso_tile_groups_launch(c, rows, m, c->topk_groups, ng);
         if (rc != SISO_OK) return rc;
         hipLaunchKernelGGL(k_topk_pick<T>, dim3((unsigned)m), dim3(256), 0, c->stream, rows, cent, c->invn, c->count, c->dim, k, vec,
-                           c->topk_groups, ng, q_inv ? q_inv + lo : nullptr, out_idx + lo * k, out_sim + lo * k);
+                           c->topk_groups, ng, topk_slack(c->dim, sizeof(T) == 1),
+                           q_inv ? q_inv + lo : nullptr, out_idx + lo * k, out_sim + lo * k);
         rc = siso_check_hip(c, hipGetLastError(), "k_topk_pick");
     }
     return rc;
