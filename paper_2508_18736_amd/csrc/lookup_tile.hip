@@ -306,16 +306,19 @@ __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_
 }
 
 // Pairs (i, j), i < j, of rows whose cosine exceeds the threshold: one pair of tiles per workgroup, upper triangle
-// only; the rows j are A, the rows i are B (a lane holds one i and 16 rows j of every block).
+// only; the rows j are A, the rows i are B (a lane holds one i and 16 rows j of every block).  A launch takes the `pairs`
+// pairs of tiles from number `first` on.
 template <class Cfg, int W, typename T>
 __global__ __launch_bounds__(256, 2) void k_pairs_tile(const T *__restrict__ rows, const float *__restrict__ invn, long K, int d,
-                                                     float threshold, long pairs, int *out_pairs, long cap, u64 *counter) {
+                                                     float threshold, long first, long pairs, int *out_pairs, long cap,
+                                                     u64 *counter) {
     static_assert(Cfg::BC == Cfg::BQ, "square tiles");
     __shared__ __align__(16) char lds[2 * Cfg::STAGE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wc = wave / Cfg::NWQ, wq = wave % Cfg::NWQ, h = lane >> 5;
-    const long id = xcd_run(pairs);
-    if (id < 0) return;
+    const long run = xcd_run(pairs);
+    if (run < 0) return;
+    const long id = first + run;
     // id = y (y + 1) / 2 + x, x <= y
     long y = (long)((sqrt(8.0 * (double)id + 1.0) - 1.0) * 0.5);
     while (y * (y + 1) / 2 > id) --y;
@@ -419,6 +422,7 @@ int lookup_launch_t(siso_cache *c, const void *queries, long n, const TilePlan &
     }
 }
 
+#define PAIR_TILES_PER_LAUNCH (1L << 22)
 template <typename T, int W>
 int pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
                  u64 *counter) {
@@ -426,13 +430,20 @@ int pairs_launch(siso_cache *c, const void *rows, const float *invn, long count,
     const long large = (count + TileLarge::BC - 1) / TileLarge::BC, small = (count + TileSmall::BC - 1) / TileSmall::BC;
     const bool few = large * (large + 1) / 2 < 512;
     const long tiles = few ? small : large, pairs = tiles * (tiles + 1) / 2;
-    if (few)
-        hipLaunchKernelGGL((k_pairs_tile<TileSmall, W, T>), dim3(xcd_grid(pairs)), dim3(256), 0, c->stream, (const T *)rows, invn,
-                           count, c->dim, threshold, pairs, out_pairs, cap, counter);
-    else
-        hipLaunchKernelGGL((k_pairs_tile<TileLarge, W, T>), dim3(xcd_grid(pairs)), dim3(256), 0, c->stream, (const T *)rows, invn,
-                           count, c->dim, threshold, pairs, out_pairs, cap, counter);
-    return siso_check_hip(c, hipGetLastError(), "k_pairs_tile");
+    // a launch holds fewer than 2^32 threads: 128-row tiles of more than 741,000 rows are more workgroups than that
+    for (long first = 0; first < pairs; first += PAIR_TILES_PER_LAUNCH) {
+        const long many = pairs - first < PAIR_TILES_PER_LAUNCH ? pairs - first : PAIR_TILES_PER_LAUNCH;
+        const dim3 grid(xcd_grid(many)), block(256);
+        if (few)
+            hipLaunchKernelGGL((k_pairs_tile<TileSmall, W, T>), grid, block, 0, c->stream, (const T *)rows, invn, count, c->dim,
+                               threshold, first, many, out_pairs, cap, counter);
+        else
+            hipLaunchKernelGGL((k_pairs_tile<TileLarge, W, T>), grid, block, 0, c->stream, (const T *)rows, invn, count, c->dim,
+                               threshold, first, many, out_pairs, cap, counter);
+        const int rc = siso_check_hip(c, hipGetLastError(), "k_pairs_tile");
+        if (rc != SISO_OK) return rc;
+    }
+    return SISO_OK;
 }
 
 template <typename T>

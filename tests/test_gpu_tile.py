@@ -102,6 +102,24 @@ def test_pairs_at_the_edges_of_the_tiles(siso, dtype, dim, K):
     assert total == want.shape[0] and torch.equal(got, torch.sort(want[:, 0] * K + want[:, 1])[0])
 
 
+@pytest.mark.parametrize("dtype,dim,K", [("f32", 8, 760000), ("bf16", 12, 1048577)])
+def test_pairs_of_more_tiles_than_one_launch_holds(siso, dtype, dim, K):
+    """17.6 million pairs of 128-row tiles, and 33.6 million: 5 and 9 launches.  Almost all rows have no length and are near
+    nothing; the others are copies of one row, in the first and last tiles, on both sides of a tile's edge, and in tiles
+    whose pairs lie in every launch."""
+    print(f"case: tile pairs {dtype} dim={dim} K={K}", flush=True)
+    rows = torch.zeros(K, dim, device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    at = torch.tensor(sorted({0, 1, 127, 128, K // 3, K // 2, K // 2 + 129, 4 * K // 5, K // 128 * 128 - 1, K - 2, K - 1}), device=DEV)
+    rows[at] = torch.arange(1, dim + 1, device=DEV).to(rows.dtype)
+    cache = siso.SisoCache(dim, K, siso_dtype(dtype))
+    cache.load(rows)
+    pairs, total = cache.merge(0.9, 1000)
+    want = torch.combinations(at, 2)
+    assert total == want.shape[0]
+    got = pairs.long()
+    assert torch.equal(torch.sort(got[:, 0] * K + got[:, 1])[0], torch.sort(want[:, 0] * K + want[:, 1])[0])
+
+
 @pytest.mark.parametrize("dtype,dim,K,n,k", [("f32", 300, 7000, 33, 10), ("bf16", 300, 3100, 130, 32), ("f32", 33, 31, 5, 32),
                                              ("f32", 384, 16400, 3, 1), ("bf16", 256, 33, 64, 2), ("bf16", 512, 70000, 40, 5)])
 def test_topk_at_the_edges_of_the_groups(siso, oracle, dtype, dim, K, n, k):
