@@ -161,10 +161,12 @@ int siso_lookup_multi(siso_cache *c, const void *queries, long n, const float *t
  * at least 512 * k centroids take two passes, the k-th largest of the per-slice maxima of
  * the first bounding the k-th best similarity from below, the second listing the rows
  * that reach the bound).  Queries with hundreds of rows at the bound (many exact
- * duplicates) are scanned row by row.  Asynchronous; grows a workspace of the cache (half
- * a byte per query and centroid, in all about 128 MiB at most: larger batches go in
- * pieces; two passes: about 530 bytes per query) the first time a larger need is seen,
- * which allocates.
+ * duplicates) are scanned row by row, and so are queries without length.  Asynchronous;
+ * grows a workspace of the cache (half a byte per query and centroid, in all up to 128 MiB
+ * or, if that is more, 128 bytes per centroid: larger batches go in pieces; two passes:
+ * about 530 bytes per query) the first time a larger need is seen, which allocates.  With
+ * less memory the pieces are smaller, without any every query is scanned; under graph
+ * capture the call works with the workspace it finds, in the same way.
  */
 int siso_lookup_topk(siso_cache *c, const void *queries, long n, int k, int *out_idx, float *out_sim);
 

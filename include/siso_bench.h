@@ -39,6 +39,9 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *   "stream_hint"     0 = default (the centroid loads of a lookup are marked non-temporal when the batch is one
  *                     tile of queries and the centroids exceed 288 MiB, or, four-wave kernel, when they exceed
  *                     288 MiB); 1 = always, 2 = never
+ *   "topk_room"       0 = default; > 0 = KiB that the workspace of siso_lookup_topk's first pass may take: larger
+ *                     batches go in more pieces, and without room for one query every row is scanned (what
+ *                     the call does by itself where memory is short)
  *   "second_set"      1 = allocate now the second set of arrays that siso_merge_apply and siso_refresh
  *                     gather the rebuilt cache into (otherwise their first call does); synchronises
  * Unknown names or values out of range give SISO_EINVAL.

@@ -86,8 +86,8 @@ struct siso_cache {
     float *fp8_qinv;
     long fp8_q_cap;
 
-    // top-k lookups: the two largest products of every group of 16 rows, per query ([topk_groups_cap] pairs, at most
-    // about SISO_TOPK_GROUP_BYTES: larger batches go in pieces), grown on demand
+    // top-k lookups: the two largest products of every group of 16 rows, per query ([topk_groups_cap] pairs; larger batches
+    // go in pieces of at least 256 queries that take at most SISO_TOPK_GROUP_BYTES if they can), grown on demand
     float2 *topk_groups;
     long topk_groups_cap;
     // over the codes of a large 8-bit cache: per query the bound, the number of listed rows, a flag "scan this query row by
@@ -109,6 +109,7 @@ struct siso_cache {
     int opt_merge_config;
     int opt_mfma_qblock;
     int opt_fold_spin_limit;  // -1 = default
+    int opt_topk_room;        // KiB that topk_groups may take
     int opt_stream_hint;      // 0 = default; 1 = mark the centroid loads of the eight-wave lookups as streaming, 2 = never
 
     // kernel timing (siso_profile_enable / siso_profile_read)

@@ -540,20 +540,45 @@ float topk_slack(int d, bool codes) {
 // what the first phase runs on: the pipelined kernels, the tiled kernel, or neither (then every query is scanned)
 enum { PHASE_NONE, PHASE_MFMA, PHASE_TILE };
 
+// Room for the group maxima (ng pairs a query) of `piece` queries, or of as many as it gets: fewer where the memory is short
+// or the option says so; under capture, where nothing can be allocated, as many as fit what is there.  *piece = 0: none.
+int topk_room(siso_cache *c, int ng, long *piece) {
+    const long limit = c->opt_topk_room ? c->opt_topk_room * 1024L / (long)sizeof(float2) / ng : *piece;
+    if (*piece > limit) *piece = limit;
+    if (*piece * ng <= c->topk_groups_cap) return SISO_OK;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
+    if (status != hipStreamCaptureStatusNone) {
+        *piece = c->topk_groups_cap / ng;
+        return SISO_OK;
+    }
+    int rc = SISO_ENOMEM;
+    for (; *piece > 0; *piece /= 2) {
+        rc = ensure_topk_workspace(c, *piece * ng);
+        if (rc != SISO_ENOMEM) return rc;
+    }
+    return SISO_OK;
+}
+
 template <typename T>
 int topk_launch(siso_cache *c, const T *Q, long n, int k, int phase, const float *q_inv, int *out_idx, float *out_sim) {
     const T *cent = (const T *)c->cent;
     const int vec = ((c->dim * sizeof(T)) % 16 == 0 && ((uintptr_t)Q & 15) == 0) ? 1 : 0;
-    if (phase == PHASE_NONE) {
+    // pieces of the batch whose maxima take about SISO_TOPK_GROUP_BYTES: they stay in the memory-side cache
+    const int ng = (int)(2 * ((c->count + 31) / 32));
+    long piece = 0;
+    if (phase != PHASE_NONE) {
+        const long most = SISO_TOPK_GROUP_BYTES / ((long)ng * 8) / 256 * 256;
+        piece = n <= most ? n : n <= 256 ? n : most > 256 ? most : 256;
+        const int rc = topk_room(c, ng, &piece);
+        if (rc != SISO_OK) return rc;
+    }
+    if (piece == 0) {
         hipLaunchKernelGGL(k_topk_scan<T>, dim3((unsigned)n), dim3(256), 0, c->stream, Q, cent, c->invn, c->count, c->dim, k, vec,
                            q_inv, (const int *)nullptr, out_idx, out_sim);
         return siso_check_hip(c, hipGetLastError(), "k_topk_scan");
     }
-    // pieces of the batch whose maxima take about SISO_TOPK_GROUP_BYTES: they stay in the memory-side cache
-    const int ng = (int)(2 * ((c->count + 31) / 32));
-    const long most = SISO_TOPK_GROUP_BYTES / ((long)ng * 8) / 256 * 256;
-    const long piece = n <= most ? n : n <= 256 ? n : most > 256 ? most : 256;
-    int rc = ensure_topk_workspace(c, piece * ng);
+    int rc = SISO_OK;
     for (long lo = 0; lo < n && rc == SISO_OK; lo += piece) {
         const long m = n - lo < piece ? n - lo : piece;
         const T *rows = Q + (size_t)lo * c->dim;
@@ -561,8 +586,8 @@ int topk_launch(siso_cache *c, const T *Q, long n, int k, int phase, const float
                                  : siso_tile_groups_launch(c, rows, m, c->topk_groups, ng);
         if (rc != SISO_OK) return rc;
         hipLaunchKernelGGL(k_topk_pick<T>, dim3((unsigned)m), dim3(256), 0, c->stream, rows, cent, c->invn, c->count, c->dim, k, vec,
-                           c->topk_groups, ng, topk_slack(c->dim, sizeof(T) == 1),
-                           q_inv ? q_inv + lo : nullptr, out_idx + lo * k, out_sim + lo * k);
+                           c->topk_groups, ng, topk_slack(c->dim, sizeof(T) == 1), q_inv ? q_inv + lo : nullptr, out_idx + lo * k,
+                           out_sim + lo * k);
         rc = siso_check_hip(c, hipGetLastError(), "k_topk_pick");
     }
     return rc;
@@ -570,7 +595,7 @@ int topk_launch(siso_cache *c, const T *Q, long n, int k, int phase, const float
 
 }  // namespace
 
-// siso_reserve's part for top-k lookups is not needed: the call says that it may allocate.
+// (siso_reserve has no part for top-k lookups: the call says that it may allocate.)
 extern "C" int siso_lookup_topk(siso_cache *c, const void *queries, long n, int k, int *out_idx, float *out_sim) {
     if (!c) return SISO_EINVAL;
     if (n < 0 || k < 1 || k > SISO_TOPK_MAX || (n > 0 && (!queries || !out_idx || !out_sim)))

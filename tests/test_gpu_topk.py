@@ -154,3 +154,66 @@ def test_topk_of_codes_beside_a_large_one(siso, oracle, d, K, n, k):
     codes, scales = cache.export_fp8()[:2]
     ora = oracle.fp8_lookup_topk_rows(codes.cpu().numpy(), scales.cpu().numpy(), to_host(q[:5].contiguous(), "bf16"), k + 1)
     check_topk((idx[:5], sim[:5]), ora, "bf16", "codes")
+
+
+# ---- the workspace of the first pass: less than it asks for, or none
+@pytest.mark.parametrize("dtype,d,K,n", [("f32", 300, 5000, 70), ("bf16", 768, 33000, 300), ("bf16", 300, 2000, 41), ("fp8", 384, 4000, 600)])
+def test_topk_with_little_room(siso, dtype, d, K, n):
+    """The answers do not depend on the room: all of it, room for some queries (the last piece is smaller), none."""
+    print(f"case: topk room {dtype} d={d} K={K} n={n}", flush=True)
+    k = 8
+    rows, q = directions(K, d, 41).to(TORCH[dtype]), directions(n, d, 42).to(TORCH[dtype])
+    per_query = 2 * ((K + 31) // 32) * 8
+    cache = siso.SisoCache(d, K, kind(siso, dtype))
+    cache.load(rows)
+    want = cache.lookup_topk(q, k)
+    for kib in (max(1, 17 * per_query // 1024 + 1), max(1, n * per_query // 3 // 1024), per_query // 1024 if per_query > 1024 else 0):
+        if kib == 0:
+            continue
+        small = siso.SisoCache(d, K, kind(siso, dtype))
+        small.load(rows)
+        small.set_option("topk_room", kib)
+        got = small.lookup_topk(q, k)
+        # (a smaller piece may run on another kernel of the first pass; what is ranked is formed the same way)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), kib
+
+
+@pytest.mark.parametrize("dtype,d,K,n,before", [("f32", 300, 5000, 70, 0), ("bf16", 300, 2000, 41, 0), ("bf16", 768, 9000, 200, 0),
+                                                ("f32", 384, 3000, 100, 30)])
+def test_topk_captured_before_its_workspace_exists(siso, dtype, d, K, n, before):
+    """The first call of a cache, or the first of a larger batch, under capture: nothing is allocated, the graph replays."""
+    print(f"case: topk captured {dtype} d={d} K={K} n={n} before={before}", flush=True)
+    k = 8
+    rows = directions(K, d, 51).to(TORCH[dtype])
+    batches = [directions(n, d, 52 + b).to(TORCH[dtype]) for b in range(3)]
+    eager = siso.SisoCache(d, K, kind(siso, dtype))
+    eager.load(rows)
+    want = [eager.lookup_topk(q, k) for q in batches]
+    side = torch.cuda.Stream()
+    warm = siso.SisoCache(d, K, kind(siso, dtype))   # (kernels are loaded by an earlier use)
+    cache = siso.SisoCache(d, K, kind(siso, dtype))
+    q_in = batches[0].clone()
+    torch.cuda.synchronize()
+    warm.set_stream(side)
+    cache.set_stream(side)
+    with torch.cuda.stream(side):
+        warm.load(rows)
+        warm.set_option("topk_room", 1)
+        warm.lookup_topk(q_in, k)
+        cache.load(rows)
+        if before:
+            cache.lookup_topk(q_in[:before], k)
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        idx, sim = cache.lookup_topk(q_in, k)
+    for b, q in enumerate(batches):
+        q_in.copy_(q)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(idx, want[b][0]) and torch.equal(sim, want[b][1]), b
+    for c in (warm, cache):
+        c.set_stream(torch.cuda.current_stream())
+    got = cache.lookup_topk(batches[0], k)
+    assert torch.equal(got[0], want[0][0]) and torch.equal(got[1], want[0][1])
