@@ -526,15 +526,20 @@ int two_pass_launch(siso_cache *c, long n, int k, int slices, int *out_idx, floa
 // How far the largest product of a group, as the first phase keeps it, can be from the cosine that k_topk_pick forms, as a
 // share of |q|.  Measured on single instructions: one of two fp32 products is off by at most 2^-23 of the magnitudes it adds,
 // the accumulator's among them, one of sixteen bf16 products by 2^-21.7.  Over d / 2 or d / 16 of them that stays below
-// d * 2^-24 of the sum of all magnitudes, which |q| |c| bounds (whole sums, the worst found: d / 4 * 2^-24 for fp32 rows with
-// elements +-c, where all roundings go the same way, d / 32 * 2^-24 in bf16).  The sum formed anew adds d / 64 + 8 roundings,
-// the row number in the lowest four bits up to 15 * 2^-23.  Codes: the 8-bit instructions cut the products of eight elements at
-// 2^-13 of the largest of them before they add them (seven are cut, by less than that each; the worst found: 1.9e-4 of |q|,
-// on rows of one large and many small elements), and the sums at 2^-23 of the accumulator.
-// 768 elements: 6.1e-5 (codes 9.0e-4); a row more or less among the candidates costs nothing to speak of.
-float topk_slack(int d, bool codes) {
-    const float rounding = (1.25f * (float)d + 64.f) * 5.9604645e-8f;  // 2^-24
-    return codes ? rounding + 7.f / 8192.f : rounding;
+// d * 2^-24 (bf16: half of that) of the sum of all magnitudes, which |q| |c| bounds (whole sums, the worst found: d / 4 * 2^-24
+// for fp32 rows with elements +-c, where all roundings go the same way, d / 32 * 2^-24 in bf16).  The sum formed anew adds
+// d / 64 + 8 roundings, the row number in the lowest four bits up to 15 * 2^-23.  Codes: the 8-bit instructions cut the
+// products of eight elements at 2^-13 of the largest of them before they add them (seven are cut, by less than that each; the
+// worst found: 1.9e-4 of |q|, on rows of one large and many small elements), and the sums at 2^-23 of the accumulator.
+// 768 elements: 5.0e-5, bf16 2.7e-5, codes 8.8e-4.  1,000 queries x 60,000 bf16 rows, k = 8: 121.0 us with a margin of 8e-6
+// that did not hold, 121.9 us with this one (fp32 and bf16 alike at d * 2^-24: 118.2 against 119.5).
+template <typename T>
+float topk_slack(int d) {
+    const float unit = 5.9604645e-8f, f = (float)d;  // 2^-24
+    const float again = (f / 64.f + 64.f) * unit;    // the sum formed anew, the row number, the scaling
+    if (sizeof(T) == 4) return f * unit + again;
+    if (sizeof(T) == 2) return 0.5f * f * unit + again;
+    return 0.25f * f * unit + 7.f / 8192.f + again;
 }
 
 // what the first phase runs on: the pipelined kernels, the tiled kernel, or neither (then every query is scanned)
@@ -586,7 +591,7 @@ int topk_launch(siso_cache *c, const T *Q, long n, int k, int phase, const float
                                  : siso_tile_groups_launch(c, rows, m, c->topk_groups, ng);
         if (rc != SISO_OK) return rc;
         hipLaunchKernelGGL(k_topk_pick<T>, dim3((unsigned)m), dim3(256), 0, c->stream, rows, cent, c->invn, c->count, c->dim, k, vec,
-                           c->topk_groups, ng, topk_slack(c->dim, sizeof(T) == 1), q_inv ? q_inv + lo : nullptr, out_idx + lo * k,
+                           c->topk_groups, ng, topk_slack<T>(c->dim), q_inv ? q_inv + lo : nullptr, out_idx + lo * k,
                            out_sim + lo * k);
         rc = siso_check_hip(c, hipGetLastError(), "k_topk_pick");
     }
