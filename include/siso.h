@@ -227,13 +227,17 @@ int siso_update_hits(siso_cache *c, const void *queries, const int *idx, const u
  * FindClosestCentroid of Algorithm 1 found a match).  Arguments as siso_lookup (out_hit
  * may not be NULL); outputs and state are bit for bit those of the two calls.
  * Batches of at most 256 queries whose lookup runs on kernels that name the winning
- * row (bf16 batches of at most 128 on the MFMA kernels, fp32 caches) finish in one
+ * row (fp32 caches, bf16 caches whose dimension is no multiple of 64 or below 128, small
+ * bf16 problems, bf16 batches of at most 128) finish in one
  * kernel that ends the lookup and applies the update: the workgroups of the batch tell
  * each other their (index, hit) through 256 slots of device memory of the cache (emptied
  * by the kernel before, so the call can be captured in a graph and replayed), and each
- * waits, a bounded time, until all slots of the batch are written; one that gives up
- * (never observed: all workgroups are resident together) leaves its centroid as it was
- * and is counted by siso_bad_indices.  Other batches run the two calls.  Asynchronous;
+ * waits, a bounded time (262,144 looks at the slots, a quarter of a second or more), until
+ * all slots of the batch are written; one that gives up leaves its centroid as it was
+ * and is counted by siso_bad_indices.  On a GPU of its own all workgroups are resident
+ * together and none has been seen to; a kernel of another stream that fills the GPU for
+ * longer than that can bring it about, on a cache of any type: siso_lookup and
+ * siso_update_hits, the two calls, wait for nothing.  Other batches run the two calls.  Asynchronous;
  * allocates what siso_lookup and siso_update_hits would (siso_reserve avoids that).
  */
 int siso_lookup_update(siso_cache *c, const void *queries, long n, float threshold, int *out_idx, float *out_sim,

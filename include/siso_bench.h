@@ -14,8 +14,8 @@ extern "C" {
 
 /* Lookup kernel selection for siso_set_lookup_path. */
 enum {
-    SISO_PATH_AUTO = 0,   /* choose by element type, dimension and batch size       */
-    SISO_PATH_SCALAR = 1, /* tiled kernel on the matrix cores; bf16, f32, any dimension*/
+    SISO_PATH_AUTO = 0,   /* choose by element type, dimension, rows and batch      */
+    SISO_PATH_SCALAR = 1, /* tiled kernel on the matrix cores; bf16, f32       */
     SISO_PATH_MFMA = 2,   /* fused bf16 MFMA GEMM + running arg-max (large batches)  */
     SISO_PATH_SKINNY = 3  /* bandwidth-bound bf16 path for batches of at most 64     */
 };
@@ -31,8 +31,10 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *                     5 = 256x256 with four waves of 128x128; 8-bit caches: 6, 7, 8 = the tiles of 1, 2, 3 on the
  *                     64-deep fp8 MFMA (their default), 1, 2, 3 = the same on the 16-deep one
  *   "tiles_per_slice" 0 = default; >0 = centroid tiles one workgroup walks through
- *   "merge_config"    0 = default (bf16: the eight-wave MFMA pair search); 1 = use the general tiled pair search;
- *                     2 = the four-wave MFMA pair search (128x128 per wave)
+ *   "merge_config"    0 = default (bf16 rows whose dimension is a multiple of 64, at least 128: the eight-wave MFMA pair
+ *                     search from 4,097 rows on; else the general tiled one); 1 = the general tiled pair search; bf16 rows
+ *                     of such a dimension: 2 = the four-wave MFMA pair search (128x128 per wave), 3 = the
+ *                     eight-wave one at any number of rows
  *   "mfma_qblock"     0 = default; 1, 2, 4, 8, 16, 32 = query tiles that share an XCD's centroid tiles
  *   "fold_spin_limit" -1 = default; >= 0: how often a workgroup of siso_lookup_update's one-kernel end looks at the
  *                     board before it gives up (0: at once - for tests of that path)

@@ -43,10 +43,10 @@ def run_both(siso, oracle, x, dtype, dim, theta, min_size, capacity=None):
 
 
 @pytest.mark.parametrize("dtype,dim,chains,min_size,seed", [
-    ("bf16", 256, 24, 1, 31),     # MFMA pair search; every vector ends somewhere
+    ("bf16", 256, 24, 1, 31),     # every vector ends somewhere
     ("bf16", 256, 40, 3, 32),     # small candidates dropped, vectors left over
-    ("bf16", 768, 60, 2, 33),     # several 256-row tiles with a ragged tail
-    ("f32", 160, 12, 2, 34),      # scalar pair search
+    ("bf16", 768, 60, 2, 33),     # several tiles with a ragged tail
+    ("f32", 160, 12, 2, 34),
 ])
 def test_cluster_vs_oracle(siso, oracle, dtype, dim, chains, min_size, seed):
     print(f"case: cluster dtype={dtype} dim={dim} chains={chains} min_size={min_size}", flush=True)
@@ -120,7 +120,7 @@ def test_cluster_edge_cases(siso, oracle):
 
 @pytest.mark.parametrize("dtype,dim", [("f32", 98), ("bf16", 100), ("f32", 7), ("bf16", 4096)])
 def test_cluster_odd_dimensions(siso, oracle, dtype, dim):
-    """Dimensions that the MFMA pair search does not take (scalar kernels), the smallest and the largest."""
+    """Dimensions that the pipelined pair search does not take (the tiled one does), the smallest and the largest."""
     print(f"case: cluster dtype={dtype} dim={dim}", flush=True)
     if dim >= 64:
         x, _ = W.query_log_chains(n_chains=6, dim=dim, dtype=dtype, seed=dim)

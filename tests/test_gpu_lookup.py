@@ -65,7 +65,7 @@ def test_mfma_path_vs_oracle(siso, oracle, cfg, dim, K, n, tps):
                             capacity=K + 7)
     st = check_lookup(out, ora, 0.85, "bf16", f"mfma cfg {cfg}")
     assert st["max_err"] < 1e-4  # fp32 accumulation of exact bf16 products is far inside the bar
-    # scalar path on the same data agrees on everything the bar fixes
+    # the tiled kernel on the same data agrees on everything the bar fixes
     cache.set_lookup_path(siso.PATH_SCALAR)
     out_s = cache.lookup(to_dev(wl.queries, "bf16"), 0.85)
     check_lookup(out_s, ora, 0.85, "bf16", "scalar on mfma data")
@@ -81,8 +81,7 @@ def test_mfma_path_vs_oracle(siso, oracle, cfg, dim, K, n, tps):
 def test_numbers_of_query_tiles_that_do_not_fill_the_blocks(siso, oracle, n, K, dim):
     """3, 6, 7, 10 and 20 tiles of queries: the blocks of query tiles that share an XCD's centroid tiles are of even
     size then (a number that need not divide the 32 places of a unit), and the slice length is chosen for an even
-    load on the XCDs.  Every query against the oracle, also through the k closest (whose second pass lists each
-    row once)."""
+    load on the XCDs.  Every query against the oracle, also through the k closest."""
     print(f"case: ragged query tiles n={n} K={K} dim={dim}", flush=True)
     wl = W.c2_mid(n_clusters=64, per_cluster=(K + 63) // 64, n_queries=n, dim=dim, seed=47)
     wl.centroids = wl.centroids[:K].copy()
@@ -155,7 +154,7 @@ def test_skinny_path_vs_oracle(siso, oracle, dim, K, n):
     cache, out = run_lookup(siso, wl, 0.85, siso.PATH_SKINNY, capacity=K + 3)
     st = check_lookup(out, ora, 0.85, "bf16", "skinny")
     assert st["max_err"] < 1e-4
-    # the automatic choice for a small batch is this path and gives the same bits
+    # the automatic choice for a small batch, this path or (small caches) the tiled kernel, gives the same bits
     cache.set_lookup_path(siso.PATH_AUTO)
     out2 = cache.lookup(to_dev(wl.queries, "bf16"), 0.85)
     torch.cuda.synchronize()

@@ -57,9 +57,9 @@ def clustered_case(dtype, dim, n_groups, copies, n_cur, seed):
 
 
 @pytest.mark.parametrize("dtype,dim,n_groups,copies,n_cur,M,seed", [
-    ("bf16", 128, 150, 6, 400, 10_000, 842),   # MFMA pair search, nothing evicted
+    ("bf16", 128, 150, 6, 400, 10_000, 842),   # nothing evicted
     ("bf16", 256, 300, 4, 500, 520, 960),      # evictions
-    ("f32", 96, 60, 5, 100, 120, 796),         # scalar kernels
+    ("f32", 96, 60, 5, 100, 120, 796),         # single precision
     ("bf16", 128, 100, 3, 0, 10_000, 828),     # empty cache: the repository clusters itself
 ])
 def test_refresh_vs_oracle(siso, oracle, dtype, dim, n_groups, copies, n_cur, M, seed):

@@ -206,18 +206,20 @@ def test_merge_pairs_and_groups_match_oracle(siso, oracle, dtype, dim, groups, c
         gs, ws = set(map(tuple, got)), set(map(tuple, want))
         assert all(edge[i, j] for i, j in gs ^ ws)
     assert np.all(got[:, 0] < got[:, 1]) and len(np.unique(got, axis=0)) == len(got)
-    # the scalar kernel finds the same set (up to the pairs at the edge of the threshold)
+    # the general tiled kernel finds the same set (up to the pairs at the edge of the threshold; up to 4,096 rows it is
+    # the default as well)
     cache.set_option("merge_config", 1)
     got_s, total_s = cache.merge(theta, cap=total + 100)
     cache.set_option("merge_config", 0)
     got_s = sorted_pairs(got_s.cpu().numpy())
     assert all(edge[i, j] for i, j in set(map(tuple, got_s)) ^ set(map(tuple, got)))
-    # and so does the four-wave MFMA kernel (where the MFMA kernels apply at all, it is the other one)
-    cache.set_option("merge_config", 2)
-    got_8, total_8 = cache.merge(theta, cap=total + 100)
-    cache.set_option("merge_config", 0)
-    got_8 = sorted_pairs(got_8.cpu().numpy())
-    assert total_8 == len(got_8) and all(edge[i, j] for i, j in set(map(tuple, got_8)) ^ set(map(tuple, got)))
+    # and so do the four-wave MFMA kernel and the eight-wave one, the default of larger sets (where they apply at all)
+    for config in (2, 3):
+        cache.set_option("merge_config", config)
+        got_8, total_8 = cache.merge(theta, cap=total + 100)
+        cache.set_option("merge_config", 0)
+        got_8 = sorted_pairs(got_8.cpu().numpy())
+        assert total_8 == len(got_8) and all(edge[i, j] for i, j in set(map(tuple, got_8)) ^ set(map(tuple, got))), config
     # a second run gives the same set (the order of emission is free)
     again, total_a = cache.merge(theta, cap=total + 100)
     assert total_a == gtotal and np.array_equal(sorted_pairs(again.cpu().numpy()), got)
@@ -270,7 +272,8 @@ def test_merge_apply_chains_and_errors(siso, oracle):
 
 def test_merge_dense_pairs_overflow_the_staging_buffer(siso, oracle):
     """Four groups of 300 exact copies: every tile pair holds tens of thousands of pairs, far more than a
-    workgroup stages at a time, so the staging buffer fills, spills and is flushed again and again."""
+    workgroup of the pipelined kernels stages at a time, so the staging buffer fills, spills and is flushed again and
+    again (the tiled kernel, the default of so few rows, has none)."""
     dim, groups, copies = 128, 4, 300
     print(f"case: dense merge dim={dim} K={groups * copies}", flush=True)
     base = W.to_storage(W.uniform_directions(61, 3, groups, dim), "bf16")
@@ -282,17 +285,19 @@ def test_merge_dense_pairs_overflow_the_staging_buffer(siso, oracle):
     oc.load(rows)
     want, total = oc.merge(0.9)
     assert total == groups * copies * (copies - 1) // 2
-    for config in (0, 2):  # the eight-wave kernel and the four-wave one
+    for config in (0, 1, 2, 3):  # the tiled kernel twice, the four-wave kernel, the eight-wave one
         cache.set_option("merge_config", config)
         got, gtotal = cache.merge(0.9, cap=total)
         assert gtotal == total, config
         assert np.array_equal(sorted_pairs(got.cpu().numpy()), want), config
     cache.set_option("merge_config", 0)
     # a cap in the middle of it all: full count, exactly cap valid pairs, no duplicates
-    few, t2 = cache.merge(0.9, cap=5000)
-    few = few.cpu().numpy()
-    assert t2 == total and few.shape[0] == 5000 and len(np.unique(few, axis=0)) == 5000
-    assert set(map(tuple, few)) <= set(map(tuple, want))
+    for config in (0, 2, 3):
+        cache.set_option("merge_config", config)
+        few, t2 = cache.merge(0.9, cap=5000)
+        few = few.cpu().numpy()
+        assert t2 == total and few.shape[0] == 5000 and len(np.unique(few, axis=0)) == 5000
+        assert set(map(tuple, few)) <= set(map(tuple, want))
 
 
 def test_merge_apply_groups_of_many_sizes(siso, oracle):
@@ -384,8 +389,9 @@ def same_state(a, b):
     ("bf16", 768, 5000, 64, 256),      # batches of 64: the streaming shape (256 x 64 tiles)
     ("bf16", 256, 3000, 100, 8),       # 256 x 128 tiles; few clusters: many queries share a centroid
     ("bf16", 1024, 2000, 1, 16), ("bf16", 2048, 900, 37, 4),
-    ("f32", 384, 1024, 256, 16),       # the scalar kernel, a full board
-    ("bf16", 768, 5000, 200, 64),      # the wide kernel names groups of rows: the two calls
+    ("f32", 384, 1024, 256, 16),       # fp32 on the tiled kernel, a full board
+    ("bf16", 768, 5000, 200, 64),      # a small bf16 problem on the tiled kernel
+    ("bf16", 256, 30000, 200, 256),    # the 256 x 256 tiles name groups of rows: the two calls
     ("f32", 96, 700, 300, 16),         # more queries than the board has slots: the two calls, the notes of the
     ("bf16", 256, 4000, 700, 8),       # update taken by the end of the lookup (large batches, many members per
     ("bf16", 1024, 3000, 1500, 64)])   # centroid)

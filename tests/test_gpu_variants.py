@@ -60,13 +60,13 @@ def test_lookup_multi_vs_oracle(siso, oracle, dtype, dim, K, n):
 
 # -------------------------------------------------------------------- the k closest
 @pytest.mark.parametrize("dtype,dim,K,n,k", [
-    ("bf16", 768, 40000, 300, 8),     # two passes of the 256 x 256 kernel
-    ("bf16", 256, 70000, 64, 16),     # two passes, small batch
-    ("bf16", 512, 33000, 100, 32),    # two passes, mid batch, largest k
-    ("bf16", 128, 9000, 130, 1),      # k = 1
-    ("bf16", 768, 2100, 65, 5),       # too few centroids for the two passes: row by row
-    ("f32", 384, 1024, 256, 10),      # fp32 cache: row by row
-    ("bf16", 72, 700, 33, 7),         # a dimension the MFMA kernels do not take
+    ("bf16", 768, 40000, 300, 8),     # the pipelined kernels: 256 x 256 tiles
+    ("bf16", 256, 70000, 64, 16),     # 256 x 64
+    ("bf16", 512, 33000, 100, 32),    # 256 x 128, largest k
+    ("bf16", 128, 9000, 130, 1),      # k = 1; from here on the tiled kernels
+    ("bf16", 768, 2100, 65, 5),       # few centroids
+    ("f32", 384, 1024, 256, 10),      # single precision
+    ("bf16", 72, 700, 33, 7),         # a dimension the pipelined kernels do not take
 ])
 def test_lookup_topk_vs_oracle(siso, oracle, dtype, dim, K, n, k):
     print(f"case: lookup_topk {dtype} dim={dim} K={K} n={n} k={k}", flush=True)
@@ -100,7 +100,7 @@ def test_lookup_topk_degenerate_cases(siso, oracle):
     dim, K, k = 256, 20000, 6
     wl = W.c2_mid(n_clusters=64, per_cluster=(K + 63) // 64, n_queries=40, dim=dim, sigma=0.3, seed=312)
     wl.centroids = wl.centroids[:K].copy()
-    wl.centroids[100:400] = wl.centroids[50]               # 301 equal rows: more than the list of the second pass holds
+    wl.centroids[100:400] = wl.centroids[50]               # 301 equal rows, all at the bound
     c = wl.centroids_f32().copy()
     c[10] = 0.0                                            # a centroid without length: similarity 0
     c[11, 3] = np.nan                                      # never chosen
