@@ -1606,9 +1606,12 @@ static bool mfma_plan(const siso_cache *c, long n, PipePlan *p) {
     if (cfg == 0 && c->dtype == SISO_FP8) cfg = n <= 64 ? 8 : n <= 128 ? 7 : 6;  // the 64-deep MFMAs
     // Large batches: eight waves (1) or the four wide ones (5), the same tile and the same sums.  The end of a tile, where its
     // products are scaled and compared, is hidden behind the other wave of the SIMD with eight and stands alone with
-    // four, and the shorter the dimension the more it weighs; the wide kernel reads less from LDS and runs at the power
-    // limit from 1,024 elements on.  Eight waves / wide, us, random rows: 120,000 x 2,048 x 128 74.7 / 92.7, x 256
-    // 121.6 / 137.7, x 384 168.9 / 182.9, x 512 218 / 232, x 768 314 / 325, x 1,024 411 / 419; 200,000 x 4,096 x 1,024 1,407 / 1,415.
+    // four, and the shorter the dimension the more it weighs; the wide kernel reads less from LDS.  Eight waves / wide, us,
+    // random rows: 120,000 x 2,048 x 128 74.7 / 92.7, x 256 121.6 / 137.7, x 384 168.9 / 182.9, x 512 218 / 232, x 768
+    // 314 / 319, x 2,048 853 / 831; 200,000 x 4,096 x 2,048 3,030 / 2,960; 100,000 x 4,096 x 4,096 3,040 / 2,910.  At 1,024
+    // elements the eight waves are still ahead, by one to three parts in a hundred (120,000 x 2,048 411 / 415, 200,000 x 4,096
+    // 1,397 / 1,408, 1,048,576 x 16,384 28,590 / 29,290): the two meet between 1,024 and 2,048, and what the line
+    // leaves to the wide kernel at 1,024 is that much.
     if (cfg == 0) cfg = n <= 64 ? 3 : n <= 128 ? 2 : c->dim < 1024 ? 1 : 5;
     // about two workgroups per compute unit when there is enough work
     return pipe_plan(c, n, cfg, 512, p);

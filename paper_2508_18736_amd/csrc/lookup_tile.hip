@@ -31,8 +31,9 @@ struct TileCfg {
     static constexpr int STAGE = (BC + BQ) * 128;
     static constexpr int DEPTH = DEPTH_;                              // slabs on their way in registers
     // Partial sums of a product, added at the end: two (half as many roundings in a row) where the registers allow it and
-    // the sums need not be those of the pipelined kernels.  With one the products are added in their order, and batches of
-    // at most 64 give the same bits whichever kernel a cache's size sends them to.
+    // the sums need not be those of the pipelined kernels.  With one the products are added in their order, and bf16 batches
+    // of at most 64 give the same bits whichever kernel a cache's size sends them to.  (Codes do not: the pipelined
+    // kernels take 64 to an instruction, these 16.)
     static constexpr int CHAINS = CHAINS_;
     static_assert(DEPTH % 2 == 0, "slab number i of a round goes to stage i % 2");
     static_assert(NWC * NWQ == 4, "four waves");
@@ -367,7 +368,7 @@ TilePlan tile_plan(const siso_cache *c, long n) {
     TilePlan p;
     auto tiles = [](long rows, int per) { return (rows + per - 1) / per; };
     // the large tile needs at least two of them per compute unit to be worth its fewer reads
-    // (few queries: up to 64 in bf16 and in codes, see TileCfg; a second tile of them finds the rows in L2)
+    // (few queries: up to 64 in bf16, see TileCfg, and in codes, where a second tile of them finds the rows in L2)
     p.cfg = n <= (c->dtype == SISO_F32 ? 32 : 64) ? 0 : tiles(c->count, 128) * tiles(n, 128) >= 512 ? 2 : 1;
     const int bc = p.cfg == 1 ? 64 : 128, bq = p.cfg == 0 ? 32 : p.cfg == 1 ? 64 : 128;
     const long resident = p.cfg == 2 ? 512 : 1024;  // workgroups the chip holds at a time

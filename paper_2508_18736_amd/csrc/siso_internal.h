@@ -297,28 +297,10 @@ __device__ __forceinline__ void fp8_store_row(const float (&x)[E], int d, unsign
     }
 }
 
-// Wave-ballot compaction of (i, j) pairs into out[cap][2]; every lane of the wave
-// must call it.  counter accumulates the total number of pairs, also beyond cap.
-__device__ __forceinline__ void emit_pair(bool pred, int i, int j, int *out, long cap, u64 *counter) {
-    const u64 mask = __ballot(pred);
-    if (mask == 0) return;
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((long long)mask) - 1;
-    u64 base = 0;
-    if (lane == leader) base = atomicAdd(counter, (u64)__popcll(mask));
-    base = __shfl(base, leader);
-    if (pred) {
-        const u64 pos = base + (u64)__popcll(mask & ((1ull << lane) - 1ull));
-        if (pos < (u64)cap) {
-            out[2 * pos] = i;
-            out[2 * pos + 1] = j;
-        }
-    }
-}
-
-// The same for up to 32 candidates per lane at once: bit I of `mask` says that this lane has the
-// pair (i, j0 + row_of(I)); the wave takes one slot range with a single atomic and every lane
-// writes its pairs behind those of the lanes before it.  Every lane of the wave must call it.
+// Pairs (i, j) into out[cap][2], up to 32 candidates per lane at once: bit I of `mask` says that this lane has the
+// pair (i, j0 + row_of(I)); the wave takes one slot range with a single atomic and every lane writes its pairs behind
+// those of the lanes before it.  counter accumulates the total number of pairs, also beyond cap.  Every lane of the wave
+// must call it.
 template <class RowOf>
 __device__ __forceinline__ void emit_pairs(unsigned mask, int i, RowOf row_of, int *out, long cap, u64 *counter) {
     const int lane = threadIdx.x & 63;

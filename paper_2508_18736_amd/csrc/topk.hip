@@ -368,33 +368,23 @@ __global__ __launch_bounds__(256) void k_topk_bound(const u64 *__restrict__ keys
     }
 }
 
-// Listed rows -> result: exact cosines of the listed rows of query q (one wave per row), ranked; queries
+// Listed rows of codes -> result: exact cosines of the listed rows of query q (one wave per row), ranked; queries
 // whose list overflowed are marked for the scan instead.  One 256-thread block per query.
-template <typename T>
-__global__ __launch_bounds__(256) void k_topk_select(const T *__restrict__ Q, const T *__restrict__ cent,
+__global__ __launch_bounds__(256) void k_topk_select(const fp8_t *__restrict__ Q, const fp8_t *__restrict__ cent,
                                                       const float *__restrict__ invn, long K, int d, int k,
                                                       const int *__restrict__ cand, const int *__restrict__ cnt, int cap,
                                                       const float *__restrict__ q_inv, int *scan, int *out_idx,
                                                       float *out_sim) {
-    constexpr int EPC = 16 / (int)sizeof(T);
-    __shared__ float sh_f[4];
+    constexpr int EPC = 16;
     __shared__ u32x4_t sh_q[SISO_MAX_DIM / EPC];
     __shared__ float val[SISO_TOPK_CAND];
     __shared__ int idx[SISO_TOPK_CAND];
     const long q = blockIdx.x;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const T *qrow = Q + (size_t)q * d;
-    float ss = 0.f;
-    for (int e = t * EPC; e < d; e += 256 * EPC) {
-        const u32x4_t v = *(const u32x4_t *)(qrow + e);
-        sh_q[e / EPC] = v;
-        if (!q_inv) ss += chunk_dot(v, v, T());
-    }
-    ss = wave_sum(ss);
-    if (lane == 0) sh_f[wave] = ss;
+    const fp8_t *qrow = Q + (size_t)q * d;
+    for (int e = t * EPC; e < d; e += 256 * EPC) sh_q[e / EPC] = *(const u32x4_t *)(qrow + e);
     __syncthreads();
-    // (q_inv: the inverse lengths that came with the quantised batch)
-    const float qi = q_inv ? q_inv[q] : inv_length((sh_f[0] + sh_f[1]) + (sh_f[2] + sh_f[3]));
+    const float qi = q_inv[q];  // (the inverse lengths that came with the quantised batch)
     const int listed = cnt[q];
     if (!(qi == qi)) {  // a query holding a NaN or an infinity
         for (int r = t; r < k; r += 256) {
@@ -409,9 +399,9 @@ __global__ __launch_bounds__(256) void k_topk_select(const T *__restrict__ Q, co
     }
     for (int i = wave; i < listed; i += 4) {
         const int r = cand[(size_t)q * cap + i];
-        const T *crow = cent + (size_t)r * d;
+        const fp8_t *crow = cent + (size_t)r * d;
         float acc = 0.f;
-        for (int e0 = lane * EPC; e0 < d; e0 += 64 * EPC) acc += chunk_dot(sh_q[e0 / EPC], *(const u32x4_t *)(crow + e0), T());
+        for (int e0 = lane * EPC; e0 < d; e0 += 64 * EPC) acc += chunk_dot(sh_q[e0 / EPC], *(const u32x4_t *)(crow + e0), fp8_t());
         acc = wave_sum(acc);
         const float sv = acc * qi * invn[r];
         if (lane == 0) {
@@ -516,7 +506,7 @@ int two_pass_launch(siso_cache *c, long n, int k, int slices, int *out_idx, floa
     rc = siso_check_hip(c, hipGetLastError(), "k_topk_bound");
     if (rc == SISO_OK) rc = siso_topk_fp8_collect(c, n, slices, c->topk_tau, c->topk_cand, cnt, SISO_TOPK_CAND);
     if (rc != SISO_OK) return rc;
-    hipLaunchKernelGGL(k_topk_select<fp8_t>, dim3((unsigned)n), dim3(256), 0, c->stream, Q, cent, c->invn, c->count, c->dim, k,
+    hipLaunchKernelGGL(k_topk_select, dim3((unsigned)n), dim3(256), 0, c->stream, Q, cent, c->invn, c->count, c->dim, k,
                        c->topk_cand, cnt, SISO_TOPK_CAND, c->fp8_qinv, flags, out_idx, out_sim);
     hipLaunchKernelGGL(k_topk_scan<fp8_t>, dim3((unsigned)n), dim3(256), 0, c->stream, Q, cent, c->invn, c->count, c->dim, k, 1,
                        c->fp8_qinv, flags, out_idx, out_sim);
