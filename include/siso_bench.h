@@ -31,7 +31,7 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *                     5 = 256x256 with four waves of 128x128; 8-bit caches: 6, 7, 8 = the tiles of 1, 2, 3 on the
  *                     64-deep fp8 MFMA (their default), 1, 2, 3 = the same on the 16-deep one
  *   "tiles_per_slice" 0 = default; >0 = centroid tiles one workgroup walks through
- *   "merge_config"    0 = default (bf16 rows whose dimension is a multiple of 64, at least 128: the eight-wave MFMA pair
+ *   "merge_config"    0 = default (see "screen"; otherwise bf16 rows whose dimension is a multiple of 64, at least 128: the eight-wave MFMA pair
  *                     search from 4,097 rows on; else the general tiled one); 1 = the general tiled pair search; bf16 rows
  *                     of such a dimension: 2 = the four-wave MFMA pair search (128x128 per wave), 3 = the
  *                     eight-wave one at any number of rows
@@ -44,6 +44,9 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *   "topk_room"       0 = default; > 0 = KiB that the workspace of siso_lookup_topk's first pass may take: larger
  *                     batches go in more pieces, and without room for one query every row is scanned (what
  *                     the call does by itself where memory is short)
+ *   "screen"          0 = default (large lookups and pair searches of fp32 and bf16 caches rule most rows out by products
+ *                     of bytes, see siso.h); 1 = wherever the kernels can (dimensions up to 1,024; pair searches
+ *                     at thresholds from 0.25 on), 2 = never
  *   "second_set"      1 = allocate now the second set of arrays that siso_merge_apply and siso_refresh
  *                     gather the rebuilt cache into (otherwise their first call does); synchronises
  * Unknown names or values out of range give SISO_EINVAL.

@@ -546,8 +546,7 @@ static long cluster_impl(siso_cache *c, const void *vectors, long n, float theta
         CLUSTER_TRY(hipGetLastError(), "stage vectors");
         int rc = SISO_OK;
         if (n >= 2) {
-            if (siso_pairs_mfma_supported(c, n)) rc = siso_pairs_mfma_launch(c, rows, inv, n, theta_c, pairs, cap, found);
-            else rc = siso_pairs_tile_launch(c, rows, inv, n, theta_c, pairs, cap, found);
+            rc = siso_pairs_launch(c, rows, inv, n, theta_c, pairs, cap, found);
         }
         if (rc != SISO_OK) return rc;
         // (all of this stays within its arrays whatever the list holds: nothing is looked at if it turns out too short, if

@@ -226,7 +226,7 @@ template <class Cfg, int W, typename T, bool GROUPS = false>
 __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_tile(const T *__restrict__ Q, const T *__restrict__ cent,
                                                       const float *__restrict__ invn, long n, long K, int d,
                                                       int tiles_per_slice, int slices, int qtiles, u64 *keys, u64 *board,
-                                                      float2 *groups, int ng) {
+                                                      float2 *groups, int ng, const int *__restrict__ many) {
     __shared__ __align__(16) char lds[2 * Cfg::STAGE];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wc = wave / Cfg::NWQ, wq = wave % Cfg::NWQ, h = lane >> 5;
@@ -235,6 +235,7 @@ __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_
     const long id = xcd_run((long)qtiles * slices);
     if (id < 0) return;
     const long q0 = id % qtiles * Cfg::BQ;
+    if (many != nullptr && q0 >= *many) return;
     const int s = (int)(id / qtiles);
     const long ctiles = (K + Cfg::BC - 1) / Cfg::BC;
     const long first = (long)s * tiles_per_slice;
@@ -312,7 +313,8 @@ __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_
 template <class Cfg, int W, typename T>
 __global__ __launch_bounds__(256, 2) void k_pairs_tile(const T *__restrict__ rows, const float *__restrict__ invn, long K, int d,
                                                      float threshold, long first, long pairs, int *out_pairs, long cap,
-                                                     u64 *counter) {
+                                                     u64 *counter, PairsRedo redo) {
+    if (redo.count != nullptr && *redo.count <= redo.above) return;  // (a screened search has found them all)
     static_assert(Cfg::BC == Cfg::BQ, "square tiles");
     __shared__ __align__(16) char lds[2 * Cfg::STAGE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -400,12 +402,12 @@ TilePlan tile_plan(const siso_cache *c, long n) {
 }
 
 template <typename T, int W, bool GROUPS>
-int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng) {
+int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng, const int *many) {
     const dim3 grid(xcd_grid((long)p.qtiles * p.slices)), block(256);
 #define SISO_LAUNCH_TILE(Cfg)                                                                                            \
     hipLaunchKernelGGL((k_lookup_tile<Cfg, W, T, GROUPS>), grid, block, 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
                        n, c->count, c->dim, p.tiles_per_slice, p.slices, p.qtiles, keys, c->board_to_clear, \
-                       groups, ng)
+                       groups, ng, many)
     if (p.cfg == 0) SISO_LAUNCH_TILE(TileFew);
     else if (p.cfg == 1) SISO_LAUNCH_TILE(TileSmall);
     else SISO_LAUNCH_TILE(TileLarge);
@@ -415,18 +417,19 @@ int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p,
 }
 
 template <typename T, bool GROUPS>
-int lookup_launch_t(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng) {
+int lookup_launch_t(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng,
+                    const int *many = nullptr) {
     switch (row_alignment<T>(queries, c->cent, c->dim)) {
-        case 16: return lookup_launch<T, 16, GROUPS>(c, queries, n, p, keys, groups, ng);
-        case 8: return lookup_launch<T, 8, GROUPS>(c, queries, n, p, keys, groups, ng);
-        default: return lookup_launch<T, (int)sizeof(T), GROUPS>(c, queries, n, p, keys, groups, ng);
+        case 16: return lookup_launch<T, 16, GROUPS>(c, queries, n, p, keys, groups, ng, many);
+        case 8: return lookup_launch<T, 8, GROUPS>(c, queries, n, p, keys, groups, ng, many);
+        default: return lookup_launch<T, (int)sizeof(T), GROUPS>(c, queries, n, p, keys, groups, ng, many);
     }
 }
 
 #define PAIR_TILES_PER_LAUNCH (1L << 22)
 template <typename T, int W>
 int pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
-                 u64 *counter) {
+                 u64 *counter, PairsRedo redo) {
     // small sets: more and smaller tiles, so that every compute unit has one
     const long large = (count + TileLarge::BC - 1) / TileLarge::BC, small = (count + TileSmall::BC - 1) / TileSmall::BC;
     const bool few = large * (large + 1) / 2 < 512;
@@ -437,10 +440,10 @@ int pairs_launch(siso_cache *c, const void *rows, const float *invn, long count,
         const dim3 grid(xcd_grid(many)), block(256);
         if (few)
             hipLaunchKernelGGL((k_pairs_tile<TileSmall, W, T>), grid, block, 0, c->stream, (const T *)rows, invn, count, c->dim,
-                               threshold, first, many, out_pairs, cap, counter);
+                               threshold, first, many, out_pairs, cap, counter, redo);
         else
             hipLaunchKernelGGL((k_pairs_tile<TileLarge, W, T>), grid, block, 0, c->stream, (const T *)rows, invn, count, c->dim,
-                               threshold, first, many, out_pairs, cap, counter);
+                               threshold, first, many, out_pairs, cap, counter, redo);
         const int rc = siso_check_hip(c, hipGetLastError(), "k_pairs_tile");
         if (rc != SISO_OK) return rc;
     }
@@ -449,11 +452,11 @@ int pairs_launch(siso_cache *c, const void *rows, const float *invn, long count,
 
 template <typename T>
 int pairs_launch_t(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
-                   u64 *counter) {
+                   u64 *counter, PairsRedo redo) {
     switch (row_alignment<T>(rows, rows, c->dim)) {
-        case 16: return pairs_launch<T, 16>(c, rows, invn, count, threshold, out_pairs, cap, counter);
-        case 8: return pairs_launch<T, 8>(c, rows, invn, count, threshold, out_pairs, cap, counter);
-        default: return pairs_launch<T, (int)sizeof(T)>(c, rows, invn, count, threshold, out_pairs, cap, counter);
+        case 16: return pairs_launch<T, 16>(c, rows, invn, count, threshold, out_pairs, cap, counter, redo);
+        case 8: return pairs_launch<T, 8>(c, rows, invn, count, threshold, out_pairs, cap, counter, redo);
+        default: return pairs_launch<T, (int)sizeof(T)>(c, rows, invn, count, threshold, out_pairs, cap, counter, redo);
     }
 }
 
@@ -482,25 +485,25 @@ long siso_tile_keys_bound(const siso_cache *c, long n) {
     return n * (all < most ? all : most);
 }
 
-int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys) {
+int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, const int *many) {
     const TilePlan p = tile_plan(c, n);
     if (p.slices != slices) return siso_fail(c, SISO_EINVAL, "tiled lookup: plan mismatch");
-    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, false>(c, queries, n, p, keys, nullptr, 0);  // (whole slabs)
-    return c->dtype == SISO_F32 ? lookup_launch_t<float, false>(c, queries, n, p, keys, nullptr, 0)
-                                : lookup_launch_t<bf16_t, false>(c, queries, n, p, keys, nullptr, 0);
+    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, false>(c, queries, n, p, keys, nullptr, 0, nullptr);  // (whole slabs)
+    return c->dtype == SISO_F32 ? lookup_launch_t<float, false>(c, queries, n, p, keys, nullptr, 0, many)
+                                : lookup_launch_t<bf16_t, false>(c, queries, n, p, keys, nullptr, 0, many);
 }
 
 int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng) {
     const TilePlan p = tile_plan(c, n);
-    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, true>(c, queries, n, p, nullptr, groups, ng);
+    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, true>(c, queries, n, p, nullptr, groups, ng, nullptr);
     return c->dtype == SISO_F32 ? lookup_launch_t<float, true>(c, queries, n, p, nullptr, groups, ng)
                                 : lookup_launch_t<bf16_t, true>(c, queries, n, p, nullptr, groups, ng);
 }
 
 int siso_pairs_tile_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs,
-                           long cap, u64 *counter) {
+                           long cap, u64 *counter, PairsRedo redo) {
     if (count < 2) return SISO_OK;
     if (count > 65535L * 64) return siso_fail(c, SISO_EINVAL, "tiled pair search handles at most %d rows", 65535 * 64);
-    return c->dtype == SISO_F32 ? pairs_launch_t<float>(c, rows, invn, count, threshold, out_pairs, cap, counter)
-                                : pairs_launch_t<bf16_t>(c, rows, invn, count, threshold, out_pairs, cap, counter);
+    return c->dtype == SISO_F32 ? pairs_launch_t<float>(c, rows, invn, count, threshold, out_pairs, cap, counter, redo)
+                                : pairs_launch_t<bf16_t>(c, rows, invn, count, threshold, out_pairs, cap, counter, redo);
 }

@@ -331,11 +331,7 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
     std::vector<float> all_cos;
     long n_pairs = 0;
     u64 *bad_at = c->counters + 2, *found_at = c->counters + 1;
-    auto search = [&](int *pairs, long room) {
-        return siso_pairs_mfma_supported(c, r)
-                   ? siso_pairs_mfma_launch(c, d_rows, d_rinv, r, theta_c, pairs, room, found_at)
-                   : siso_pairs_tile_launch(c, d_rows, d_rinv, r, theta_c, pairs, room, found_at);
-    };
+    auto search = [&](int *pairs, long room) { return siso_pairs_launch(c, d_rows, d_rinv, r, theta_c, pairs, room, found_at); };
     auto cosines = [&](const int *pairs, long from, long most, int *to_pairs, float *to_cos) {
         const dim3 grid((unsigned)(most < 4096 ? (most + 3) / 4 : 1024)), block(256);
         if (c->dtype == SISO_F32)

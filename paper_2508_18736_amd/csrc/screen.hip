@@ -1,0 +1,1195 @@
+// Lookups and pair searches that form most products in eight bits.
+//
+// A large lookup is bound by the matrix cores and by the power they draw, and almost all of its products are of rows
+// that are nowhere near the best.  So the rows and the queries, at unit length, are first written as signed bytes (the
+// largest element of 32 rows, or of one query, becomes 127); v_mfma_i32_32x32x32_i8 forms the products of the bytes at
+// twice the rate of bf16 from half the bytes, and exactly: sums of integers have no rounding.  What the bytes leave out
+// is known: for unit vectors u, w and what their bytes stand for, u', w',
+//     | u.w - u'.w' |  <=  |u - u'| |w| + |u'| |w - w'|  <=  e_u + (1 + e_u) e_w,     e = the length of the difference,
+// and both lengths are measured when the bytes are written (0.0073 for Gaussian directions of 768 elements).  A row is
+// passed over only if the upper end of its cosine lies below the lower end of some other row's: what is left, some tens of
+// rows a query, is multiplied again from the stored rows in single precision, as the end of a lookup does, and the
+// largest of those cosines (lowest index among equal ones) is the result.  No result is made of bytes.
+//
+// Queries and rows for which the bound says nothing (no length, non-finite, more rows near the best than the list
+// holds) are left to the kernels of lookup_mfma.hip and lookup_tile.hip: every call ends with a launch of those over the
+// gathered rows of such queries, whose workgroups leave at once if there are none.
+//
+// Rows are grouped by 32 (the rows of one MFMA): one scale and one error for each.  One outlier costs its 32 rows some
+// precision and nobody else; and the end of a tile works on integers: a maximum of 16, one conversion, three operations
+// in floating point for 16 products, against some two for each where every row has a weight.
+#include "mfma_pipe.h"
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+
+typedef PipeCfg<4, 2, 2, 4, 2, 128, true, 1> ByteCfg;  // 256 x 256 tile, waves of 128 x 64, two stages of 128 bytes a row
+
+#define SCREEN_LIST 1024          // rows a query's list holds
+#define SCREEN_WORK 96            // rows a query on average can have multiplied again
+#define SCREEN_TILES 16           // tiles of a slice: a row of it is 12 bits
+#define SCREEN_STAGE 896          // rows a wave collects in LDS before they are handed to the queries' lists
+#define SCREEN_MAYBE (1L << 20)   // pairs whose cosine has to be formed anew
+#define SCREEN_SLACK 2e-5f        // roundings of the lengths, of the unit rows and of the sums formed anew (about 4e-6 in all)
+#define SCREEN_PLAIN (-2)         // instead of a list's length: this query is left to the other kernels
+#define SCREEN_NAN (-1)           // and this one holds a NaN or an infinity
+
+struct ScreenQuery {
+    float scale, err;
+};
+
+// ---- bytes -------------------------------------------------------------------------------------------------------
+// A float near 1.5 * 2^23 holds its nearest integer in its low bits, in two's complement.
+#define SCREEN_ROUND 12582912.f
+__device__ __forceinline__ unsigned pack_bytes(float a, float b, float c, float d) {  // the lowest bytes, a's first
+    const unsigned ab = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x0C0C0400u);
+    const unsigned cd = __builtin_amdgcn_perm(__float_as_uint(d), __float_as_uint(c), 0x04000C0Cu);
+    return ab | cd;
+}
+
+// One workgroup per 32 rows, a wave for eight of them, which it holds in registers: NCH times four elements a lane.
+// ROWS: rows of the cache, meta = (scale, error, error for lower ends, 1 / scale); a block with a row that cannot be judged
+// (past the end, non-finite, length near the ends of the range) has an infinite error for lower ends, and one with a
+// length near the ends of the range is never ruled out.  Otherwise queries, each with its own scale.
+template <typename T, int NCH, bool ROWS>
+__device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict__ src, const float *__restrict__ invn, long have,
+                                                  int vec, signed char *__restrict__ codes, float4 *__restrict__ meta,
+                                                  ScreenQuery *__restrict__ qm, unsigned *__restrict__ low, u64 *__restrict__ seed,
+                                                  int *__restrict__ cnt, int *__restrict__ totals, int d, int dp) {
+    constexpr int R = 8;
+    __shared__ float sh[4][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long r0 = blk * 32 + wave * R;
+
+    constexpr int W = (int)sizeof(T);  // words of four elements
+    typedef unsigned chunk_t __attribute__((ext_vector_type(W)));
+    unsigned v[R][NCH][W];
+    float inv[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int i = 0; i < W; ++i) v[j][c][i] = 0u;
+    if (vec) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const T *row = src + (size_t)(r0 + j < have ? r0 + j : 0) * d + lane * 4;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+                if (r0 + j < have && c * 256 + lane * 4 < d) {
+                    const chunk_t x = *(const chunk_t *)(row + c * 256);
+                    v[j][c][0] = x[0];
+                    v[j][c][1] = x[1];
+                    if constexpr (W == 4) {
+                        v[j][c][2] = x[2];
+                        v[j][c][3] = x[3];
+                    }
+                }
+        }
+    } else {
+        for (int j = 0; j < R; ++j) {
+            if (r0 + j >= have) break;
+            const T *row = src + (size_t)(r0 + j) * d;
+            unsigned x[NCH * 4];
+#pragma unroll
+            for (int i = 0; i < NCH * 4; ++i) {
+                const int e = (i / 4) * 256 + lane * 4 + i % 4;
+                const T y = row[e < d ? e : 0];
+                if constexpr (sizeof(T) == 4) x[i] = e < d ? __float_as_uint(y) : 0u;
+                else x[i] = e < d ? (unsigned)y : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < R; ++k)  // (registers are not addressed by a variable)
+#pragma unroll
+                for (int i = 0; i < NCH * W; ++i) {
+                    const unsigned word = sizeof(T) == 4 ? x[i] : x[(2 * i) % (NCH * 4)] | (x[(2 * i + 1) % (NCH * 4)] << 16);
+                    v[k][i / W][i % W] = k == j ? word : v[k][i / W][i % W];
+                }
+        }
+    }
+    if constexpr (ROWS) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) inv[j] = invn[r0 + j < have ? r0 + j : 0];
+    }
+    auto element = [&](int j, int c, int i) __attribute__((always_inline)) {
+        if constexpr (sizeof(T) == 4) return __uint_as_float(v[j][c][i]);
+        else return (i & 1) ? __uint_as_float(v[j][c][i >> 1] & 0xFFFF0000u) : __uint_as_float(v[j][c][i >> 1] << 16);
+    };
+    // largest element at unit length; what cannot be judged counts as zero.  (Magnitudes compare as integers, those of two
+    // bf16 elements in one instruction; a NaN or an infinity shows in the inverse length.)
+    float top[R], most = 0.f;
+    int kind[R];  // 0 judged, SCREEN_PLAIN length near the ends of the range (or none, for a query), SCREEN_NAN
+    bool all = true, plain = false;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        float a;
+        if constexpr (sizeof(T) == 4) {
+            unsigned m = 0;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int i = 0; i < W; ++i) m = max(m, v[j][c][i] & 0x7FFFFFFFu);
+            a = __uint_as_float(m);
+        } else {
+            typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+            u16x2 m = {0, 0};
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int i = 0; i < W; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v[j][c][i] & 0x7FFF7FFFu));
+            a = __uint_as_float((unsigned)max(m[0], m[1]) << 16);
+        }
+        if constexpr (!ROWS) {
+            float ss = 0.f;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ss = fmaf(element(j, c, i), element(j, c, i), ss);
+            inv[j] = inv_length(wave_sum(ss));
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off));
+        kind[j] = !(inv[j] == inv[j]) ? SCREEN_NAN : inv[j] > 1e15f || (inv[j] != 0.f && inv[j] < 1e-15f) ? SCREEN_PLAIN : 0;
+        // (an inverse length of 0 is that of a row without length, all of whose cosines are 0 - or of one whose squares vanish)
+        if (inv[j] == 0.f && (!ROWS || a > 0.f)) kind[j] = SCREEN_PLAIN;
+        if (r0 + j >= have) {
+            kind[j] = 0;
+            all = false;
+            a = 0.f;
+        }
+        if (kind[j] != 0) {
+            inv[j] = 0.f;
+            a = 0.f;
+            all = false;
+            plain = plain || kind[j] == SCREEN_PLAIN;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int i = 0; i < W; ++i) v[j][c][i] = 0u;
+        }
+        top[j] = a == 0.f ? 0.f : a * inv[j];
+        most = fmaxf(most, top[j]);
+    }
+    float scale = 0.f, to = 0.f;
+    if constexpr (ROWS) {
+        if (lane == 0) sh[0][wave] = most;
+        __syncthreads();
+        most = fmaxf(fmaxf(sh[0][0], sh[0][1]), fmaxf(sh[0][2], sh[0][3]));
+        scale = most / 127.f;
+        to = most > 0.f ? 127.f / most : 0.f;
+    }
+    float err = 0.f;
+    signed char *dst = codes + (size_t)r0 * dp + lane * 4;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if constexpr (!ROWS) {
+            scale = top[j] / 127.f;
+            to = top[j] > 0.f ? 127.f / top[j] : 0.f;
+        }
+        const float by = top[j] > 0.f ? inv[j] * to : 0.f;
+        float off2 = 0.f;  // in steps
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            float f[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float x = element(j, c, i);
+                f[i] = fmaf(x, by, SCREEN_ROUND);
+                const float r = fmaf(x, by, SCREEN_ROUND - f[i]);
+                off2 = fmaf(r, r, off2);
+            }
+            if (c * 256 + lane * 4 < dp) *(unsigned *)(dst + c * 256) = pack_bytes(f[0], f[1], f[2], f[3]);
+        }
+        dst += dp;
+        const float e = scale * sqrtf(wave_sum(off2)) * 1.0005f + 1e-6f;
+        err = fmaxf(err, e);
+        if (!ROWS && lane == 0) {
+            const long q = r0 + j;
+            const bool ok = q < have && kind[j] == 0;
+            qm[q] = ScreenQuery{ok ? scale : 1.f, ok ? e : -1.f};  // (grow = 0 in k_screen_lookup)
+            low[q] = ok ? ordered_bits(-INFINITY) : ordered_bits(INFINITY);  // (nothing reaches +inf: no list)
+            seed[q] = 0;
+            cnt[q] = kind[j];
+        }
+    }
+    if constexpr (!ROWS) {
+        if (blk == 0 && threadIdx.x < 2) totals[threadIdx.x] = 0;
+    } else {
+        if (lane == 0) {
+            sh[1][wave] = err;
+            sh[2][wave] = all ? 0.f : INFINITY;
+            sh[3][wave] = plain ? INFINITY : 0.f;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            err = fmaxf(fmaxf(sh[1][0], sh[1][1]), fmaxf(sh[1][2], sh[1][3]));
+            const float un = sh[2][0] + sh[2][1] + sh[2][2] + sh[2][3], pl = sh[3][0] + sh[3][1] + sh[3][2] + sh[3][3];
+            meta[blk] = make_float4(scale, err + pl, err + un, 127.f / most);
+        }
+    }
+}
+
+// Blocks below row_blocks: rows of the cache; the others: queries.
+template <typename T, int NCH>
+__global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows, const float *__restrict__ invn, long K,
+                                                      unsigned row_blocks, int row_vec, signed char *__restrict__ codes,
+                                                      float4 *__restrict__ meta, const T *__restrict__ queries, long n, int query_vec,
+                                                      signed char *__restrict__ qcodes, ScreenQuery *__restrict__ qm,
+                                                      unsigned *__restrict__ low, u64 *__restrict__ seed, int *__restrict__ cnt,
+                                                      int *__restrict__ totals, int d, int dp) {
+    if (blockIdx.x < row_blocks)
+        write_bytes_block<T, NCH, true>(blockIdx.x, rows, invn, K, row_vec, codes, meta, nullptr, nullptr, nullptr, nullptr, nullptr, d, dp);
+    else
+        write_bytes_block<T, NCH, false>(blockIdx.x - row_blocks, queries, nullptr, n, query_vec, qcodes, nullptr, qm, low, seed, cnt,
+                                         totals, d, dp);
+}
+
+// ---- products of bytes --------------------------------------------------------------------------------------------
+// The pipeline of k_pairs_stream over bytes: slab after slab of `pairs` pairs of tiles that `src` names, fold(acc) behind the
+// last slab of each; src.side() is called with a pair's first slab and loads what its fold needs.
+// The loads of a slab (64 wave instructions for a compute unit, which its texture unit takes a thousand cycles to work off)
+// are dealt out, one behind every second of the 16 MFMAs that follow the barrier.  Issued at once they hold up the waves, and
+// with them the MFMAs: 65,536 x 65,536 / 2 products of 768 bytes 1.47 -> 1.32 ms, of zeros, which the power limit does not
+// slow down, 1.17 -> 0.90 (without any loads 1.15 and 0.87; behind 8 MFMAs 1.36 and 0.99, behind 32 1.39 and 1.10).  So
+// nothing between the MFMAs may depend on a condition: behind the last slab the loads fetch it once more, into a stage nobody
+// reads again, and the fragment reads find a slab that does not exist.  What bounds it now is the power limit: 2.5 PFLOP/s on
+// random bytes, 3.7 on zeros.
+template <class Src, class Fold>
+__device__ __forceinline__ void byte_stream(unsigned char *smem, int dp, int pairs, Src &src, Fold &&fold) {
+    typedef ByteCfg Cfg;
+    constexpr int WC = Cfg::WC, WQ = Cfg::WQ, NWC = Cfg::NWC, BC = Cfg::BC, NW = Cfg::NW, STAGE = Cfg::STAGE, NLA = Cfg::NLA,
+                  NL = Cfg::NL, RB = Cfg::RB, CPR = Cfg::CPR, RPI = Cfg::RPI, RP = Cfg::RP, KK = Cfg::KK, SUB = 32 * Cfg::RB;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wc = wave % NWC, wq = wave / NWC;
+    const int h = lane >> 5, l32 = lane & 31;
+    const int nk = dp / RB, T = pairs * nk;
+    unsigned off[NLA];
+    const int lr = lane / CPR, slot = lane % CPR;
+#pragma unroll
+    for (int j = 0; j < NLA; ++j) {
+        const int row = (j * NW + wave) * RPI + lr;
+        off[j] = (unsigned)(row * dp + ((slot ^ ((row / RP) % CPR)) * 16));
+    }
+    const int sw = (l32 / RP) % CPR;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const unsigned row_a = lds0 + (unsigned)(((wc * WC) * 32 + l32) * RB);
+    const unsigned row_b = lds0 + (unsigned)(BC * RB + ((wq * WQ) * 32 + l32) * RB);
+    unsigned so[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) so[kk] = (unsigned)(((kk * 2 + h) ^ sw) * 16);
+
+    int ld_t = 0, ld_ks = 0;
+    unsigned ld_off = 0;
+    auto part = [&](auto jj) __attribute__((always_inline)) {
+        constexpr int j = decltype(jj)::value;
+        if constexpr (j == 0) {
+            if (ld_ks == 0) src.side(wave, lane);
+        }
+        unsigned o = off[j % NLA];
+        asm volatile("" : "+v"(o));
+        unsigned char *sb = smem + ld_off + wave * 1024;
+        const size_t k = (size_t)ld_ks * RB;
+        if constexpr (j < NLA) gload_lds16((const char *)src.c + k + o, sb + j * NW * 1024);
+        else gload_lds16((const char *)src.q + k + o, sb + BC * RB + (j - NLA) * NW * 1024);
+        if constexpr (j == NL - 1) {
+            ld_off ^= STAGE;
+            if (ld_t + 1 < T) {
+                ++ld_t;
+                if (++ld_ks == nk) {
+                    ld_ks = 0;
+                    src.advance();
+                }
+            }
+        }
+    };
+    constexpr int NF = WC + WQ;
+    bf16x8 af[2][WC], bf[2][WQ];
+    i32x16 acc[WC][WQ];
+    auto mac = [&](auto buf, auto firstc, auto &&extra) __attribute__((always_inline)) {
+        constexpr int U = decltype(buf)::value;
+        static_for<0, WC * WQ>([&](auto ii) __attribute__((always_inline)) {
+            constexpr int i = decltype(ii)::value, A = i / WQ, B = i % WQ;
+            const i32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            acc[A][B] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, af[U][A]), __builtin_bit_cast(i32x4, bf[U][B]),
+                                                              decltype(firstc)::value ? zero : acc[A][B], 0, 0, 0);
+            extra(ii);
+        });
+    };
+    // parts P .. P + 3, one behind every second MFMA
+    auto deal = [&](auto p) __attribute__((always_inline)) {
+        return [&](auto ii) __attribute__((always_inline)) {
+            constexpr int i = decltype(ii)::value;
+            if constexpr (i % 2 == 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                part(IC<decltype(p)::value + i / 2>{});
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+    };
+    auto none = [](auto) __attribute__((always_inline)) {};
+    static_assert(NL == 8 && WC * WQ == 8, "eight loads behind two steps of eight MFMAs");
+    // slab 0 and the first half of slab 1, as if a slab had just gone by
+    static_for<0, NL>(part);
+    static_for<0, NL / 2>(part);
+    vm_wait<NL / 2>();
+    __syncthreads();
+    lds_frags<SUB>(af[0], bf[0], row_a + so[0], row_b + so[0]);
+    int ks = 0;
+    unsigned sto = 0;
+    for (int t = 0; t < T; ++t) {
+        const unsigned sto_next = sto ^ STAGE;
+        static_for<0, KK - 1>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int kk = decltype(kc)::value;
+            lds_frags<SUB>(af[(kk + 1) & 1], bf[(kk + 1) & 1], row_a + sto + so[kk + 1], row_b + sto + so[kk + 1]);
+            lds_wait<NF>(af[kk & 1], bf[kk & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kk == 0) {
+                if (ks == 0) mac(IC<0>{}, IC<1>{}, deal(IC<4>{}));
+                else mac(IC<0>{}, IC<0>{}, deal(IC<4>{}));
+            } else {
+                mac(IC<kk & 1>{}, IC<0>{}, none);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        lds_wait<0>(af[1], bf[1]);
+        vm_wait<0>();
+        __syncthreads();
+        lds_frags<SUB>(af[0], bf[0], row_a + sto_next + so[0], row_b + sto_next + so[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        mac(IC<1>{}, IC<0>{}, deal(IC<0>{}));
+        __builtin_amdgcn_sched_barrier(0);
+        if (ks == nk - 1) {
+            fold(acc);
+            ks = 0;
+        } else {
+            ++ks;
+        }
+        sto = sto_next;
+    }
+    lds_wait<0>(af[0], bf[0]);
+    vm_wait<0>();
+    __syncthreads();
+}
+
+// direct load of four bytes per lane that other XCDs may have changed meanwhile (past the L2 of this one)
+__device__ __forceinline__ void gload_lds4_fresh(const void *g, void *lds_wave_base) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
+                                     (__attribute__((address_space(3))) void *)lds_wave_base, 4, 0, 16);
+}
+
+__device__ __forceinline__ int max16(const i32x16 &a) {
+    int m = a[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) m = a[i] > m ? a[i] : m;
+    return m;
+}
+
+// Upper ends travel in LDS as twelve bits, rounded up; the largest of them stands for anything above.
+__device__ __forceinline__ unsigned upper_bits(float v) {
+    const float x = (v + 1.25f) * (4095.f / 2.5f);
+    return x >= 4094.f ? 4095u : x <= 0.f ? 1u : (unsigned)x + 1u;
+}
+__device__ __forceinline__ float upper_value(unsigned b) { return b >= 4095u ? INFINITY : (float)b * (2.5f / 4095.f) - 1.25f + 1e-6f; }
+
+__device__ __forceinline__ void list_row(uint2 *list, int *cnt, long q, long row0, long row, long K, float upper) {
+    if (row >= K) return;  // (rows past the end are zeros)
+    const int slot = atomicAdd(cnt + q, 1);
+    if (slot < SCREEN_LIST) list[(size_t)q * SCREEN_LIST + slot] = make_uint2((unsigned)(row0 + row), __float_as_uint(upper));
+}
+
+// Products of the queries of a tile with the rows of a slice.  low[q] = the largest lower end any workgroup has found for
+// query q so far (to begin with, the cosine of the best row of a sample); a row whose upper end reaches it goes to the
+// query's list.  low only grows, and a stale value lists more rows than needed, never fewer: nothing has to be ordered.
+// Rows are collected in LDS and judged by the newest low once more when they are handed over.
+// codes, meta and the K rows are a run of the cache's, from its row number row0 on.
+// SAMPLE: one tile per workgroup, every `stride`-th of them, and only its best row counts: seed[q] = (product, row).
+struct LookupSrc {
+    const signed char *c, *q;
+    int ct, dp, buf;
+    const float4 *meta;
+    const unsigned *low;  // of the tile's queries
+    float *meta_s;        // [2][64]
+    unsigned *low_s;      // [2][256]
+    __device__ __forceinline__ void side(int wave, int lane) {
+        if (wave < 4) gload_lds4_fresh(low + wave * 64 + lane, low_s + buf * 256 + wave * 64);
+        else if (wave == 4) gload_lds4((const float *)(meta + (size_t)ct * 8) + lane, meta_s + buf * 64);  // (32 of them count)
+    }
+    __device__ __forceinline__ void advance() {
+        c += 256 * (size_t)dp;
+        buf ^= 1;
+        ++ct;
+    }
+};
+#define SCREEN_LDS (ByteCfg::NSTAGE * ByteCfg::STAGE + 2 * 256 * 4 + 2 * 64 * 4 + 8 * SCREEN_STAGE * 4)
+static_assert(SCREEN_LDS <= 160 * 1024, "fits in LDS");
+
+template <bool SAMPLE>
+__global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_screen_lookup(
+    const signed char *__restrict__ qcodes, const signed char *__restrict__ codes, const float4 *__restrict__ meta,
+    const ScreenQuery *__restrict__ qm, unsigned *__restrict__ low, u64 *__restrict__ seed, int *__restrict__ cnt,
+    uint2 *__restrict__ list, long row0, long K, int dp, int tiles_per_slice, int slices, int nqt, int qb, int stride) {
+    typedef ByteCfg Cfg;
+    constexpr int WC = Cfg::WC, WQ = Cfg::WQ, BC = Cfg::BC, BQ = Cfg::BQ;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    unsigned *low_s = (unsigned *)(smem + Cfg::NSTAGE * Cfg::STAGE);
+    float *meta_s = (float *)(low_s + 2 * 256);
+    unsigned *stages = (unsigned *)(meta_s + 2 * 64);  // [8][SCREEN_STAGE]
+    int qt, s, ct_begin, ct_end;
+    if constexpr (SAMPLE) {
+        qt = blockIdx.x % nqt;
+        ct_begin = (int)(blockIdx.x / nqt) * stride;
+        ct_end = ct_begin + 1;
+        if ((long)ct_begin * BC >= K) return;
+    } else {
+        if (!pipe_map_block<BC>(K, tiles_per_slice, slices, nqt, qb, qt, s, ct_begin, ct_end)) return;
+        if (ct_end <= ct_begin) return;
+    }
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wc = wave % Cfg::NWC, wq = wave / Cfg::NWC, h = lane >> 5, l32 = lane & 31;
+    const long q0 = (long)qt * BQ;
+    unsigned *stage = stages + wave * SCREEN_STAGE;
+    int mine = 0;  // rows this wave has collected
+
+    float scale[WQ], rscale[WQ], halfw[WQ], grow[WQ], best[WQ];  // per query: scale, 1 / scale, e + slack, (1 + e) / scale; a lower end
+#pragma unroll
+    for (int b = 0; b < WQ; ++b) {
+        const ScreenQuery m = qm[q0 + (wq * WQ + b) * 32 + l32];
+        scale[b] = m.scale;
+        rscale[b] = 1.f / m.scale;
+        halfw[b] = m.err + SCREEN_SLACK;
+        grow[b] = (1.f + m.err) * rscale[b];
+        best[b] = -INFINITY;
+    }
+    LookupSrc src;
+    src.c = codes + (size_t)ct_begin * BC * dp;
+    src.q = qcodes + (size_t)q0 * dp;
+    src.ct = ct_begin;
+    src.dp = dp;
+    src.buf = 0;
+    src.meta = meta;
+    src.low = low + q0;
+    src.meta_s = meta_s;
+    src.low_s = low_s;
+
+    if constexpr (SAMPLE) {
+        byte_stream(smem, dp, 1, src, [&](const i32x16(&acc)[WC][WQ]) __attribute__((always_inline)) {
+            const float4 *mt = (const float4 *)meta_s + wc * WC;
+            static_for<0, WQ>([&](auto ib) __attribute__((always_inline)) {
+                constexpr int B = decltype(ib)::value;
+                float top = -INFINITY;
+                int row = 0;
+                static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+                    constexpr int A = decltype(ia)::value;
+                    const int m = max16(acc[A][B]);
+                    const float p = (float)m * mt[A].x;
+                    int at = 0;
+                    static_for<0, 16>([&](auto ii) __attribute__((always_inline)) {
+                        constexpr int I = decltype(ii)::value;
+                        if (acc[A][B][I] == m) at = 8 * (I >> 2) + (I & 3);
+                    });
+                    if (p > top) {
+                        top = p;
+                        row = ct_begin * BC + (wc * WC + A) * 32 + 4 * h + at;
+                    }
+                });
+                const float ov = __uint_as_float(other_half(__float_as_uint(top)));
+                const int orow = (int)other_half((unsigned)row);
+                if (ov > top) {
+                    top = ov;
+                    row = orow;
+                }
+                if (h == 0) atomicMax(seed + q0 + (wq * WQ + B) * 32 + l32, pack_key(top, (unsigned)row));
+            });
+        });
+        return;
+    }
+
+    // the rows collected so far go to the lists of their queries (a wave's own: nothing to wait for)
+    auto flush = [&]() __attribute__((always_inline)) {
+        const int many = mine < SCREEN_STAGE ? mine : SCREEN_STAGE;
+#pragma unroll 4
+        for (int p = lane; p < many; p += 64) {
+            const unsigned e = stage[p];
+            const long q = q0 + (e >> 24);
+            const float upper = upper_value(e & 0xFFFu);
+            if (upper >= unordered_bits(__hip_atomic_load(low + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                list_row(list, cnt, q, row0, ct_begin * (long)BC + ((e >> 12) & 0xFFFu), K, upper);
+        }
+        mine = 0;
+    };
+    int tile = 0;
+    byte_stream(smem, dp, ct_end - ct_begin, src, [&](const i32x16(&acc)[WC][WQ]) __attribute__((always_inline)) {
+        const float4 *mt = (const float4 *)(meta_s + (tile & 1) * 64) + wc * WC;
+        const unsigned *lt = low_s + (tile & 1) * 256;
+        // Upper ends, over the scale of the query: the largest of a column against what it needs is all that most tiles get.
+        // (the whole end of a tile with everything below for every block: 2.9 us of 11.4, 768 bytes a row)
+        float4 m[WC];
+#pragma unroll
+        for (int a = 0; a < WC; ++a) m[a] = mt[a];
+        float seen[WQ], need[WQ], up[WC][WQ], most[WQ];
+        int top[WC][WQ];
+        static_for<0, WQ>([&](auto ib) __attribute__((always_inline)) {
+            constexpr int B = decltype(ib)::value;
+            seen[B] = unordered_bits(lt[(wq * WQ + B) * 32 + l32]);
+            need[B] = (fmaxf(seen[B], best[B]) - halfw[B]) * rscale[B];
+            most[B] = -INFINITY;
+            static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+                constexpr int A = decltype(ia)::value;
+                top[A][B] = max16(acc[A][B]);
+                // (a query that lists nothing needs +inf and has grow = 0: no NaN of a block never ruled out reaches that)
+                up[A][B] = fmaf((float)top[A][B], m[A].x, grow[B] * m[A].y);
+                most[B] = fmaxf(most[B], up[A][B]);
+            });
+        });
+        static_for<0, WQ>([&](auto ib) __attribute__((always_inline)) {
+            constexpr int B = decltype(ib)::value;
+            if (__ballot(most[B] >= need[B]) == 0) return;
+            const unsigned col = (unsigned)((wq * WQ + B) * 32 + l32);
+            float lo = -INFINITY;
+            static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+                constexpr int A = decltype(ia)::value;
+                lo = fmaxf(lo, fmaf(-grow[B], m[A].z, (float)top[A][B] * m[A].x));
+            });
+            lo = fmaxf(lo, __uint_as_float(other_half(__float_as_uint(lo))));
+            lo = fmaf(scale[B], lo, -halfw[B]);
+            if (lo > best[B] && seen[B] < INFINITY) best[B] = lo;
+            need[B] = (fmaxf(seen[B], best[B]) - halfw[B]) * rscale[B];
+            // (in steps of a thousandth: a bound that is a little low lists a few rows more)
+            if (h == 0 && lo > seen[B] + 1e-3f) atomicMax(low + q0 + col, ordered_bits(lo));
+            static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+                constexpr int A = decltype(ia)::value;
+                if (__ballot(up[A][B] >= need[B]) == 0) return;
+                // the bound as an integer (rounded down; the slack of the error is some twenty of its units).  No scale (rows
+                // of zeros): plus or minus infinity, or a NaN, which converts to 0
+                const int least = up[A][B] >= need[B] ? (int)floorf((need[B] - grow[B] * m[A].y) * m[A].w) : 0x7FFFFFFF;
+                // one upper end for the rows of a lane, mostly one: that of the largest
+                const int rel0 = tile * BC + (wc * WC + A) * 32 + 4 * h;  // register I holds row rel0 + 8 * (I / 4) + I % 4
+                const unsigned upper = upper_bits(fmaf(scale[B], up[A][B], halfw[B]));
+                const unsigned entry = (col << 24) | ((unsigned)rel0 << 12) | upper;
+                static_for<0, 16>([&](auto ii) __attribute__((always_inline)) {
+                    constexpr int I = decltype(ii)::value, ROW = 8 * (I >> 2) + (I & 3);
+                    const u64 mask = __ballot(acc[A][B][I] >= least);
+                    if (mask == 0) return;
+                    if (acc[A][B][I] >= least) {
+                        const int pos = mine + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+                        if (pos < SCREEN_STAGE) stage[pos] = entry + (ROW << 12);
+                        else list_row(list, cnt, q0 + col, row0, ct_begin * (long)BC + rel0 + ROW, K, upper_value(upper));
+                    }
+                    mine += __popcll(mask);
+                });
+            });
+        });
+        ++tile;
+        if (mine > SCREEN_STAGE / 2) flush();
+    });
+    flush();
+}
+
+// Queries of this wave: its row in LDS as chunks (or left where it is), and 1 / |q| with the sums of k_lookup_finalize (the
+// squares as its four waves add them).
+template <typename T>
+__device__ __forceinline__ float stage_query(const T *qrow, int d, int vec, u32x4_t *sh_q) {
+    constexpr int EPC = 16 / (int)sizeof(T), CH = (SISO_SCREEN_DIM / EPC + 255) / 256;  // chunks a thread of k_lookup_finalize takes
+    const int lane = threadIdx.x & 63;
+    float ss[4] = {0.f, 0.f, 0.f, 0.f};
+    if (vec) {
+        u32x4_t v[4][CH];
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int e = (w * 64 + lane + 256 * c) * EPC;
+                v[w][c] = *(const u32x4_t *)(qrow + (e < d ? e : 0));
+            }
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int e = (w * 64 + lane + 256 * c) * EPC;
+                if (e < d) {
+                    sh_q[e / EPC] = v[w][c];
+                    ss[w] += chunk_dot(v[w][c], v[w][c], T());
+                }
+            }
+    } else {
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            for (int e = w * 64 + lane; e < d; e += 256) ss[w] += widen(qrow[e]) * widen(qrow[e]);
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) ss[w] = wave_sum(ss[w]);
+    return inv_length((ss[0] + ss[1]) + (ss[2] + ss[3]));
+}
+
+// A better bound, a wave for each query: the cosine with its best row of the sample (seed), or with the row of the highest
+// upper end that is listed so far (the bound was short of it by the error).
+template <typename T, bool LISTED>
+__global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
+                                                     long n, long K, int d, int vec, const u64 *__restrict__ seed,
+                                                     const int *__restrict__ cnt, const uint2 *__restrict__ list,
+                                                     unsigned *__restrict__ low) {
+    __shared__ u32x4_t sh_q[4][SISO_SCREEN_DIM * sizeof(T) / 16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long q = (long)blockIdx.x * 4 + wave;
+    if (q >= n) return;
+    long r = K;
+    if constexpr (LISTED) {
+        const int listed = cnt[q] < SCREEN_LIST ? cnt[q] : SCREEN_LIST;
+        u64 high = 0;
+        for (int i = lane; i < listed; i += 64) {
+            const uint2 e = list[(size_t)q * SCREEN_LIST + i];
+            const u64 key = pack_key(__uint_as_float(e.y), e.x);
+            high = key > high ? key : high;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const u64 o = __shfl_xor(high, off);
+            high = o > high ? o : high;
+        }
+        if (high != 0) r = (long)(0xFFFFFFFFu - (unsigned)(high & 0xFFFFFFFFull));
+    } else {
+        if (seed[q] != 0) r = (long)(0xFFFFFFFFu - (unsigned)(seed[q] & 0xFFFFFFFFull));
+    }
+    if (r >= K || unordered_bits(low[q]) == INFINITY) return;
+    const T *qrow = Q + (size_t)q * d;
+    const float qi = stage_query(qrow, d, vec, sh_q[wave]);
+    const float cosine = row_product<T>(qrow, sh_q[wave], vec, cent + (size_t)r * d, d, lane) * qi * invn[r];
+    if (lane == 0 && cosine == cosine && cosine - 5e-6f > unordered_bits(low[q])) low[q] = ordered_bits(cosine - 5e-6f);
+}
+
+// The end of a screened lookup in three steps, so that the long lists (a query that misses leaves up to some hundred rows, one
+// that hits its 16 neighbours) are spread over the whole chip: with a workgroup for each query, or for four, the
+// longest list decided (4,096 queries, 30 % misses: 65 to 78 us; so 48).
+// First step, a wave for each query: the bound, with the cosine of the listed row of the highest upper end (the bound is
+// then no longer short of the best by twice the error but by once); the listed rows that reach it go to one list of all
+// queries.  Queries that are left to the other kernels are numbered and their rows gathered.
+struct ScreenWork {
+    int q, row;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
+                                                     long n, int d, int vec, const unsigned *__restrict__ low,
+                                                     const int *__restrict__ cnt, const uint2 *__restrict__ list,
+                                                     int *__restrict__ totals, ScreenWork *__restrict__ work, int work_room,
+                                                     u64 *__restrict__ best, float *__restrict__ qinv, int *__restrict__ plain_of,
+                                                     T *__restrict__ plain_rows) {
+    __shared__ u32x4_t sh_q[4][SISO_SCREEN_DIM * sizeof(T) / 16];
+    __shared__ int sh_n[4];
+    __shared__ int sh_base;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long q = (long)blockIdx.x * 4 + wave;
+    const T *qrow = Q + (size_t)(q < n ? q : 0) * d;
+    const uint2 *ql = list + (size_t)(q < n ? q : 0) * SCREEN_LIST;
+    const uint2 e0 = ql[lane];  // (beyond the list: anything, not looked at)
+    const int listed = q < n ? cnt[q] : 0;
+    float bound = unordered_bits(low[q < n ? q : 0]);
+    const float qi = stage_query(qrow, d, vec, sh_q[wave]);
+    bool leave = listed == SCREEN_PLAIN || listed > SCREEN_LIST;
+    u64 mine = 0;
+    int first = -1, some = 0;
+    if (!leave && listed > 0) {
+        u64 high = lane < listed ? pack_key(__uint_as_float(e0.y), e0.x) : 0;
+        for (int i = lane + 64; i < listed; i += 64) {
+            const uint2 e = ql[i];
+            const u64 key = pack_key(__uint_as_float(e.y), e.x);
+            high = key > high ? key : high;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const u64 o = __shfl_xor(high, off);
+            high = o > high ? o : high;
+        }
+        first = (int)(0xFFFFFFFFu - (unsigned)(high & 0xFFFFFFFFull));
+        const float sv = row_product<T>(qrow, sh_q[wave], vec, cent + (size_t)first * d, d, lane) * qi * invn[first];
+        if (sv == sv) {  // a NaN never wins
+            bound = fmaxf(bound, sv - 5e-6f);
+            mine = pack_key(sv, (unsigned)first);
+        }
+        for (int i = lane; i < listed; i += 64) {
+            const uint2 e = i < 64 ? e0 : ql[i];
+            some += __popcll(__ballot((int)e.x != first && __uint_as_float(e.y) >= bound));
+        }
+        some = __builtin_amdgcn_readfirstlane(some);
+    }
+    if (lane == 0) sh_n[wave] = some;
+    __syncthreads();
+    if (threadIdx.x == 0) sh_base = atomicAdd(totals, sh_n[0] + sh_n[1] + sh_n[2] + sh_n[3]);
+    __syncthreads();
+    if (q >= n) return;
+    int at = sh_base;
+    for (int w = 0; w < wave; ++w) at += sh_n[w];
+    if (at + some > work_room) leave = true;  // (the entries behind work_room are not read)
+    for (int i = lane; i < listed && some > 0; i += 64) {
+        const uint2 e = i < 64 ? e0 : ql[i];
+        const bool take = (int)e.x != first && __uint_as_float(e.y) >= bound;
+        const u64 mask = __ballot(take);
+        const int to = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+        if (take && to < work_room) work[to] = ScreenWork{(int)q, (int)e.x};
+        at += __popcll(mask);
+    }
+    int place = -1;
+    if (leave) {
+        if (lane == 0) place = atomicAdd(totals + 1, 1);
+        place = __builtin_amdgcn_readfirstlane(place);
+        T *to = plain_rows + (size_t)place * d;
+        for (int e = lane; e < d; e += 64) to[e] = qrow[e];
+        if (lane == 0) plain_of[place] = (int)q;
+    }
+    if (lane == 0) {
+        best[q] = leave ? ~0ull : mine;  // (nothing is larger, and no cosine)
+        qinv[q] = qi;
+    }
+}
+
+// Second step, a wave for four rows at a time: the cosines, with the sums of k_lookup_finalize; best[q] = (cosine, lowest row).
+template <typename T>
+__global__ __launch_bounds__(256) void k_screen_score(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
+                                                      int d, int vec, const int *__restrict__ totals,
+                                                      const ScreenWork *__restrict__ work, int work_room,
+                                                      const float *__restrict__ qinv, u64 *__restrict__ best) {
+    constexpr int EPC = 16 / (int)sizeof(T), R = 4;
+    const int lane = threadIdx.x & 63;
+    const int many = totals[0] < work_room ? totals[0] : work_room;
+    for (int i = (blockIdx.x * 4 + (threadIdx.x >> 6)) * R; i < many; i += gridDim.x * 4 * R) {
+        const T *rows[R], *qrows[R];
+        int row[R], q[R];
+        float sum[R], by[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const ScreenWork w = work[i + r < many ? i + r : i];
+            row[r] = __builtin_amdgcn_readfirstlane(w.row);
+            q[r] = __builtin_amdgcn_readfirstlane(w.q);
+            rows[r] = cent + (size_t)row[r] * d;
+            qrows[r] = Q + (size_t)q[r] * d;
+            by[r] = qinv[q[r]];
+            sum[r] = 0.f;
+        }
+        if (vec) {  // as row_products, the query from memory too
+            for (int e0 = lane * EPC; e0 < d; e0 += 2 * 64 * EPC) {
+                const int e1 = e0 + 64 * EPC, f1 = e1 < d ? e1 : 0;
+                u32x4_t c0[R], c1[R], q0[R], q1[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    c0[r] = *(const u32x4_t *)(rows[r] + e0);
+                    c1[r] = *(const u32x4_t *)(rows[r] + f1);
+                    q0[r] = *(const u32x4_t *)(qrows[r] + e0);
+                    q1[r] = *(const u32x4_t *)(qrows[r] + f1);
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    sum[r] += chunk_dot(q0[r], c0[r], T());
+                    const float part = chunk_dot(q1[r], c1[r], T());
+                    sum[r] += e1 < d ? part : 0.f;
+                }
+            }
+        } else {
+            for (int e = lane; e < d; e += 64)
+#pragma unroll
+                for (int r = 0; r < R; ++r) sum[r] += widen(qrows[r][e]) * widen(rows[r][e]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float sv = wave_sum(sum[r]) * by[r] * invn[row[r]];
+            if (lane == 0 && sv == sv) atomicMax(best + q[r], pack_key(sv, (unsigned)row[r]));
+        }
+    }
+}
+
+// Third step, a thread for each query.
+__global__ __launch_bounds__(256) void k_screen_write(long n, long q_base, const int *__restrict__ cnt, const u64 *__restrict__ best,
+                                                      ThetaList thetas, int *out_idx, float *out_sim, unsigned char *out_hit,
+                                                      unsigned *access, int *upd_owner, int *upd_members) {
+    const long q = (long)blockIdx.x * 256 + threadIdx.x;
+    if (q >= n) return;
+    const u64 key = best[q];
+    if (key == ~0ull) return;
+    const long idx = key == 0 ? -1 : (long)(0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull));
+    const float sim = cnt[q] == SCREEN_NAN ? __uint_as_float(0x7FC00000u) : key == 0 ? -INFINITY : unordered_bits((unsigned)(key >> 32));
+    write_lookup(q, q_base, idx, sim, thetas, out_idx, out_sim, out_hit, access, upd_owner, upd_members);
+}
+
+// ---- pairs ---------------------------------------------------------------------------------------------------------
+// All pairs i < j above a threshold, from bytes: a pair whose lower end exceeds it is a pair, one whose upper end does not
+// is none, and the cosines of the few between are formed anew (k_screen_pairs_check).  Error and scale belong to the two
+// blocks of 32 rows, so a block of 32 x 32 products is dismissed by one comparison of its largest integer.
+struct PairSrc {
+    const signed char *c, *q, *codes;
+    const float4 *meta;
+    float *meta_s;  // [2][2][64]: row tile, column tile
+    PairItems items;
+    int ct, qt, dp, buf;
+    __device__ __forceinline__ void side(int wave, int lane) {
+        if (wave < 2) gload_lds4((const float *)(meta + (size_t)(wave == 0 ? ct : qt) * 8) + lane, meta_s + (buf * 2 + wave) * 64);
+    }
+    __device__ __forceinline__ void take() {
+        c = codes + (size_t)ct * 256 * dp;
+        q = codes + (size_t)qt * 256 * dp;
+    }
+    __device__ __forceinline__ void advance() {
+        buf ^= 1;
+        items.next(qt, ct);
+        take();
+    }
+};
+#define SCREEN_PAIR_STAGE 2048  // pairs a workgroup collects in LDS
+#define SCREEN_PAIR_LDS (ByteCfg::NSTAGE * ByteCfg::STAGE + 4 * 64 * 4 + SCREEN_PAIR_STAGE * 8 + 16)
+static_assert(SCREEN_PAIR_LDS <= 160 * 1024, "fits in LDS");
+
+__global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_screen_pairs(
+    const signed char *__restrict__ codes, const float4 *__restrict__ meta, long K, int dp, int qb, float threshold,
+    int *__restrict__ out_pairs, long cap, u64 *__restrict__ counter, int *__restrict__ maybe, u64 *__restrict__ maybe_count) {
+    typedef ByteCfg Cfg;
+    constexpr int WC = Cfg::WC, WQ = Cfg::WQ, BC = Cfg::BC;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    float *meta_s = (float *)(smem + Cfg::NSTAGE * Cfg::STAGE);
+    int *stage = (int *)(meta_s + 4 * 64);
+    int *staged = stage + 2 * SCREEN_PAIR_STAGE;
+    u64 *flush_slot = (u64 *)(staged + 2);
+    const int tiles = (int)((K + BC - 1) / BC);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wc = wave % Cfg::NWC, wq = wave / Cfg::NWC, h = lane >> 5, l32 = lane & 31;
+    PairSrc src;
+    PairItems done;
+    src.items.init(tiles, qb);
+    done.init(tiles, qb);
+    src.codes = codes;
+    src.meta = meta;
+    src.meta_s = meta_s;
+    src.dp = dp;
+    src.buf = 0;
+    src.qt = src.ct = 0;
+    if (!src.items.next(src.qt, src.ct)) return;
+    src.take();
+    int qt = 0, ct = 0, seq = 0, pairs = 0;
+    while (done.next(qt, ct)) ++pairs;
+    done.init(tiles, qb);
+    done.next(qt, ct);
+    if (threadIdx.x == 0) *staged = 0;  // (the pipeline's first barrier is before the first use)
+    byte_stream(smem, dp, pairs, src, [&](const i32x16(&acc)[WC][WQ]) __attribute__((always_inline)) {
+        const float4 *ma = (const float4 *)(meta_s + (seq & 1) * 128) + wc * WC;
+        const float4 *mb = (const float4 *)(meta_s + (seq & 1) * 128 + 64) + wq * WQ;
+        float4 a[WC], b[WQ];
+#pragma unroll
+        for (int x = 0; x < WC; ++x) a[x] = ma[x];
+#pragma unroll
+        for (int x = 0; x < WQ; ++x) b[x] = mb[x];
+        float up[WC][WQ], most = -INFINITY;
+        static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+            constexpr int A = decltype(ia)::value;
+            static_for<0, WQ>([&](auto ib) __attribute__((always_inline)) {
+                constexpr int B = decltype(ib)::value;
+                up[A][B] = fmaf((float)max16(acc[A][B]), a[A].x * b[B].x, fmaf(1.f + a[A].y, b[B].y, a[A].y) + SCREEN_SLACK);
+                most = fmaxf(most, up[A][B]);
+            });
+        });
+        if (__ballot(most > threshold) != 0) static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+            constexpr int A = decltype(ia)::value;
+            static_for<0, WQ>([&](auto ib) __attribute__((always_inline)) {
+                constexpr int B = decltype(ib)::value;
+                if (__ballot(up[A][B] > threshold) == 0) return;
+                const float scale = a[A].x * b[B].x, err = fmaf(1.f + a[A].y, b[B].y, a[A].y) + SCREEN_SLACK;
+                const long icol = (long)qt * BC + (wq * WQ + B) * 32 + l32;
+                const long jrow0 = (long)ct * BC + (wc * WC + A) * 32 + 4 * h;  // register I holds row jrow0 + 8 * (I / 4) + I % 4
+                unsigned sure = 0, open = 0;
+                static_for<0, 16>([&](auto ii) __attribute__((always_inline)) {
+                    constexpr int I = decltype(ii)::value;
+                    const float p = (float)acc[A][B][I] * scale;
+                    const long j = jrow0 + 8 * (I >> 2) + (I & 3);
+                    if (icol < j && j < K && p + err > threshold) {
+                        if (p - err > threshold) sure |= 1u << I;
+                        else open |= 1u << I;
+                    }
+                });
+                auto row_of = [&](int I) { return (int)(jrow0 + 8 * (I >> 2) + (I & 3)); };
+                emit_pairs_staged(sure, (int)icol, row_of, stage, staged, SCREEN_PAIR_STAGE, out_pairs, cap, counter);
+                if (__ballot(open != 0) != 0) emit_pairs(open, (int)icol, row_of, maybe, SCREEN_MAYBE, maybe_count);
+            });
+        });
+        ++seq;
+        done.next(qt, ct);
+        // (own LDS traffic done, then the barrier by hand: the compiler's would also wait for the loads in flight)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (*staged > SCREEN_PAIR_STAGE / 2) flush_staged_pairs(stage, staged, SCREEN_PAIR_STAGE, flush_slot, out_pairs, cap, counter);
+    });
+    flush_staged_pairs(stage, staged, SCREEN_PAIR_STAGE, flush_slot, out_pairs, cap, counter);
+}
+
+__global__ void k_screen_clear(u64 *maybe_count) { *maybe_count = 0; }
+
+// The pairs in doubt, a wave for each.  More of them than the list holds: nothing is kept, and the kernels of all pairs
+// (which look at the same count) do the search.
+template <typename T>
+__global__ __launch_bounds__(256) void k_screen_pairs_check(const T *__restrict__ rows, const float *__restrict__ invn, int d, int vec,
+                                                            float threshold, const int *__restrict__ maybe,
+                                                            const u64 *__restrict__ maybe_count, int *__restrict__ out_pairs, long cap,
+                                                            u64 *__restrict__ counter) {
+    const u64 many = *maybe_count;
+    const int lane = threadIdx.x & 63;
+    if (many > SCREEN_MAYBE) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0;
+        return;
+    }
+    for (u64 p = (u64)blockIdx.x * 4 + (threadIdx.x >> 6); p < many; p += (u64)gridDim.x * 4) {
+        const int i = maybe[2 * p], j = maybe[2 * p + 1];
+        const T *a = rows + (size_t)i * d, *b = rows + (size_t)j * d;
+        float s = 0.f;
+        if (vec) {
+            constexpr int EPC = 16 / (int)sizeof(T);
+            for (int e = lane * EPC; e < d; e += 64 * EPC) s += chunk_dot(*(const u32x4_t *)(a + e), *(const u32x4_t *)(b + e), T());
+        } else {
+            for (int e = lane; e < d; e += 64) s += widen(a[e]) * widen(b[e]);
+        }
+        const float cosine = wave_sum(s) * invn[i] * invn[j];
+        if (lane == 0 && cosine > threshold) {
+            const u64 at = atomicAdd(counter, 1ull);
+            if (at < (u64)cap) {
+                out_pairs[2 * at] = i;
+                out_pairs[2 * at + 1] = j;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------------------------------------------------
+namespace {
+
+struct ScreenRoom {
+    signed char *codes, *qcodes;
+    float4 *meta;
+    ScreenQuery *qm;
+    unsigned *low;
+    u64 *seed, *best;
+    int *cnt, *totals, *plain_of, *maybe;
+    float *qinv;
+    uint2 *list;
+    ScreenWork *work;
+    int work_room;
+    void *plain_rows;
+    u64 *maybe_count;
+    size_t bytes;
+};
+
+int byte_dim(int d) { return d <= 256 ? 256 : (d + 127) / 128 * 128; }
+long up256(long x) { return (x + 255) / 256 * 256; }
+
+// for lookups of up to n queries (n = 0: for a pair search)
+ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
+    const int d = c->dim;
+    const int dp = byte_dim(d);
+    const long q = up256(n < SISO_SCREEN_PIECE ? n : SISO_SCREEN_PIECE);
+    Carver a{base};
+    ScreenRoom r;
+    r.codes = a.take<signed char>((size_t)up256(rows) * dp);
+    r.meta = a.take<float4>((size_t)up256(rows) / 32 + 8);
+    r.qcodes = a.take<signed char>((size_t)q * dp);
+    r.qm = a.take<ScreenQuery>(q);
+    r.low = a.take<unsigned>(q);
+    r.seed = a.take<u64>(q);
+    r.best = a.take<u64>(q);
+    r.cnt = a.take<int>(q);
+    r.totals = a.take<int>(2);  // rows to be multiplied again, queries left to the other kernels
+    r.plain_of = a.take<int>(q);
+    r.plain_rows = a.take<char>((size_t)q * d * (c->dtype == SISO_F32 ? 4 : 2));
+    r.qinv = a.take<float>(q);
+    r.work_room = (int)q * SCREEN_WORK;
+    r.work = a.take<ScreenWork>((size_t)r.work_room);
+    r.list = a.take<uint2>((size_t)q * SCREEN_LIST);
+    r.maybe_count = a.take<u64>(1);
+    r.maybe = a.take<int>(n == 0 ? 2 * SCREEN_MAYBE : 0);
+    r.bytes = a.used;
+    return r;
+}
+
+// false = there is no room, which no caller needs to fail for
+bool make_room(siso_cache *c, char *&room, size_t &cap, size_t bytes) {
+    if (bytes <= cap) return true;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
+    if (status != hipStreamCaptureStatusNone) return false;
+    if (room) {
+        if (hipStreamSynchronize(c->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        (void)hipFree(room);
+        room = nullptr;
+        cap = 0;
+    }
+    if (hipMalloc((void **)&room, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        room = nullptr;
+        return false;
+    }
+    cap = bytes;
+    return true;
+}
+
+// rows (with_rows) and n queries to bytes
+template <typename T>
+int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *invn, long count, bool with_rows, const T *queries, long n) {
+    const int d = c->dim, dp = byte_dim(d);
+    const unsigned row_blocks = with_rows ? (unsigned)(up256(count) / 32) : 0u;
+    const dim3 grid(row_blocks + (unsigned)(up256(n) / 32)), block(256);
+    const size_t four = 4 * sizeof(T);  // rows that are whole runs of four elements, aligned to them
+    const int rv = d % 4 == 0 && (uintptr_t)rows % four == 0 ? 1 : 0, qv = d % 4 == 0 && (uintptr_t)queries % four == 0 ? 1 : 0;
+#define SISO_LAUNCH_BYTES(NCH)                                                                                                  \
+    hipLaunchKernelGGL((k_screen_bytes<T, NCH>), grid, block, 0, c->stream, rows, invn, count, row_blocks, rv, r.codes, r.meta, \
+                       queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.totals, d, dp)
+    if (dp <= 256) SISO_LAUNCH_BYTES(1);
+    else if (dp <= 512) SISO_LAUNCH_BYTES(2);
+    else if (dp <= 768) SISO_LAUNCH_BYTES(3);
+    else SISO_LAUNCH_BYTES(4);
+#undef SISO_LAUNCH_BYTES
+    return siso_check_hip(c, hipGetLastError(), "k_screen_bytes");
+}
+
+template <typename T>
+int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
+                  float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, bool timed, ScreenPlain *plain) {
+    const ScreenRoom r = screen_room(c->screen, c, c->count, n);
+    const int d = c->dim, dp = byte_dim(d);
+    const long tiles = up256(c->count) / 256, nqt = up256(n) / 256;
+    static bool attr_done = false;
+    if (!attr_done) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_screen_lookup<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SCREEN_LDS);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void *)k_screen_lookup<false>, hipFuncAttributeMaxDynamicSharedMemorySize, SCREEN_LDS);
+        if (e != hipSuccess) return siso_check_hip(c, e, "hipFuncSetAttribute(k_screen_lookup)");
+        attr_done = true;
+    }
+    int rc = write_bytes<T>(c, r, (const T *)c->cent, c->invn, c->count, with_rows, queries, n);
+    if (rc != SISO_OK) return rc;
+    const T *cent = (const T *)c->cent;
+    const int vec = (size_t)d * sizeof(T) % 16 == 0 && ((uintptr_t)queries & 15) == 0 ? 1 : 0;
+    const dim3 fours((unsigned)((n + 3) / 4)), block(256);
+    // A sample of the tiles supplies the first bounds: one for every compute unit, or a 128th of them, whichever is more, but no
+    // more than a quarter.
+    long some = 256 / nqt > tiles / 128 ? 256 / nqt : tiles / 128;
+    if (some > tiles / 4) some = tiles / 4;
+    if (some > 0) {
+        hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, r.codes,
+                           r.meta, r.qm, r.low, r.seed, r.cnt, r.list, 0L, c->count, dp, 1, (int)some, (int)nqt, 1, (int)(tiles / some));
+        hipLaunchKernelGGL((k_screen_seed<T, false>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.seed,
+                           r.cnt, r.list, r.low);
+    }
+    // Much work: an eighth of the tiles first, and better bounds from what it has listed, for queries that are near nothing (a
+    // bound from 2,000 rows lets some 700 of 131,072 pass, one from 16,000 some 200).
+    const long ahead = tiles * nqt >= 32 * 256 ? (tiles / 8 * nqt >= 512 ? tiles / 8 : (512 + nqt - 1) / nqt) : 0;
+    if (timed) siso_prof_begin(c);
+    for (int part = ahead > 0 ? 0 : 1; part < 2; ++part) {
+        const long t0 = part == 0 ? 0 : ahead, row0 = t0 * 256;
+        const long rows = part == 0 ? ahead * 256 : c->count - row0;
+        BytePlan p;
+        if (!siso_byte_plan(c, rows, n, dp, SCREEN_TILES, &p)) return siso_fail(c, SISO_EINVAL, "screened lookup: no plan");
+        hipLaunchKernelGGL(k_screen_lookup<false>, dim3((unsigned)p.grid), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes,
+                           r.codes + (size_t)row0 * dp, r.meta + t0 * 8, r.qm, r.low, r.seed, r.cnt, r.list, row0, rows, dp,
+                           p.tiles_per_slice, p.slices, p.nqt, p.qb, 1);
+        if (part == 0)
+            hipLaunchKernelGGL((k_screen_seed<T, true>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.seed,
+                               r.cnt, r.list, r.low);
+    }
+    if (timed) siso_prof_end(c);
+    hipLaunchKernelGGL(k_screen_pick<T>, fours, block, 0, c->stream, queries, cent, c->invn, n, d, vec, r.low, r.cnt, r.list, r.totals,
+                       r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
+    hipLaunchKernelGGL(k_screen_score<T>, dim3((unsigned)(n < 4096 ? (n + 1) / 2 : 2048)), block, 0, c->stream, queries, cent, c->invn, d, vec,
+                       r.totals, r.work, r.work_room, r.qinv, r.best);
+    hipLaunchKernelGGL(k_screen_write, dim3((unsigned)((n + 255) / 256)), block, 0, c->stream, n, q_base, r.cnt, r.best, tl, out_idx, out_sim,
+                       out_hit, access, owner, members);
+    *plain = ScreenPlain{r.totals + 1, r.plain_of, r.plain_rows};
+    return siso_check_hip(c, hipGetLastError(), "k_screen_lookup, k_screen_pick, k_screen_score");
+}
+
+template <typename T>
+int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, float threshold, int *out_pairs, long cap, u64 *counter,
+                 PairsRedo *redo) {
+    const ScreenRoom r = screen_room(c->screen_pairs, c, count, 0);
+    const int d = c->dim, dp = byte_dim(d);
+    static bool attr_done = false;
+    if (!attr_done) {
+        const hipError_t e = hipFuncSetAttribute((const void *)k_screen_pairs, hipFuncAttributeMaxDynamicSharedMemorySize, SCREEN_PAIR_LDS);
+        if (e != hipSuccess) return siso_check_hip(c, e, "hipFuncSetAttribute(k_screen_pairs)");
+        attr_done = true;
+    }
+    hipLaunchKernelGGL(k_screen_clear, dim3(1), dim3(1), 0, c->stream, r.maybe_count);
+    const int rc = write_bytes<T>(c, r, rows, invn, count, true, rows, 0);
+    if (rc != SISO_OK) return rc;
+    int qb = 8;
+    while (qb > 1 && qb > up256(count) / 256) qb >>= 1;
+    hipLaunchKernelGGL(k_screen_pairs, dim3(256), dim3(ByteCfg::NT), SCREEN_PAIR_LDS, c->stream, r.codes, r.meta, count, dp, qb, threshold,
+                       out_pairs, cap, counter, r.maybe, r.maybe_count);
+    const int vec = (size_t)d * sizeof(T) % 16 == 0 && ((uintptr_t)rows & 15) == 0 ? 1 : 0;
+    hipLaunchKernelGGL(k_screen_pairs_check<T>, dim3(512), dim3(256), 0, c->stream, rows, invn, d, vec, threshold, r.maybe, r.maybe_count,
+                       out_pairs, cap, counter);
+    *redo = PairsRedo{r.maybe_count, SCREEN_MAYBE};
+    return siso_check_hip(c, hipGetLastError(), "k_screen_pairs");
+}
+
+}  // namespace
+
+// Is a lookup worth it?  The bytes of the rows are written for every call (they may have changed), and six small kernels
+// stand around the products.  Lookups alone, no misses / 30 % misses, us, without and with:
+//   fp32  1,000 x 8,000 x 384    77 -> 65 / 77 -> 70      1,000 x 16,000 x 384   124 -> 68 / 123 -> 74
+//         300 x 16,000 x 384     56 -> 62 / 56 -> 68      2,000 x 2,000 x 768     80 -> 84 / 79 -> 99
+//         1,000 x 60,000 x 384  416 -> 103 / 417 -> 111   4,096 x 60,000 x 768  2,986 -> 283 / 2,980 -> 336
+//   bf16  4,096 x 65,536 x 768  374 -> 294 / 379 -> 334   1,000 x 400,000 x 768  601 -> 507 / 587 -> 546
+//         4,096 x 131,072 x 768 703 -> 490 / 712 -> 539   8,192 x 131,072 x 1,024  1,877 -> 1,098 / 1,859 -> 1,426
+// (of bf16 batches near 500 GFLOP half of whose queries miss, as a refresh has them, take as long either way: the line lies where
+// those are ahead, too).  Longer rows than SISO_SCREEN_DIM: the error stays what it is while the cosines of
+// unrelated rows crowd together (deviation d^-1/2), and ever more rows are near the best.
+int siso_screen_wanted(const siso_cache *c, long n) {
+    if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->count < 1 || n < 1 || c->dim > SISO_SCREEN_DIM) return 0;
+    if (c->opt_screen == 1) return 1;
+    if (c->path != SISO_PATH_AUTO || c->opt_mfma_config != 0 || c->opt_tiles_per_slice != 0 || c->opt_mfma_qblock != 0) return 0;
+    const double work = 2.0 * (double)n * (double)c->count * c->dim;
+    return c->dim >= 128 && (c->dtype == SISO_F32 ? n > 128 && work >= 8e9 : n >= 768 && work >= 7.5e11);
+}
+
+int siso_screen_reserve(siso_cache *c, long rows, long n) {
+    return make_room(c, c->screen, c->screen_cap, screen_room(nullptr, c, rows, n).bytes) ? 1 : 0;
+}
+
+int siso_screen_reserve_pairs(siso_cache *c, long rows) {
+    return make_room(c, c->screen_pairs, c->screen_pairs_cap, screen_room(nullptr, c, rows, 0).bytes) ? 1 : 0;
+}
+
+void siso_screen_done(siso_cache *c) {
+    if (c->screen_pairs_cap <= (size_t)SISO_ARENA_KEEP) return;
+    (void)hipStreamSynchronize(c->stream);
+    (void)hipFree(c->screen_pairs);
+    c->screen_pairs = nullptr;
+    c->screen_pairs_cap = 0;
+}
+
+int siso_screen_has_room(const siso_cache *c, long n) { return screen_room(nullptr, c, c->count, n).bytes <= c->screen_cap; }
+
+int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
+                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, bool timed,
+                       ScreenPlain *plain) {
+    return c->dtype == SISO_F32 ? screen_launch<float>(c, (const float *)queries, n, with_rows, tl, q_base, out_idx, out_sim, out_hit,
+                                                       access, owner, members, timed, plain)
+                                : screen_launch<bf16_t>(c, (const bf16_t *)queries, n, with_rows, tl, q_base, out_idx, out_sim, out_hit,
+                                                        access, owner, members, timed, plain);
+}
+
+// Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 56, 2,000 x 768
+// 83 -> 61, 4,000 x 256 129 -> 65, 8,000 x 768 490 -> 101; bf16 8,000 x 768 109 -> 101, 16,000 x 256 107 -> 113, 16,000 x 768
+// 235 -> 164, 50,000 x 768 1,658 -> 940.  Below a threshold of 0.25 rows of zeros and the many pairs of unrelated rows would come
+// near it.
+int siso_screen_pairs_wanted(const siso_cache *c, long count, float threshold) {
+    if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->opt_merge_config != 0 || count < 2 || c->dim > SISO_SCREEN_DIM) return 0;
+    if (!(threshold >= 0.25f)) return 0;
+    if (c->opt_screen == 1) return 1;
+    const double work = (double)count * (double)count * c->dim;
+    return c->dim >= 128 && work >= (c->dtype == SISO_F32 ? 1.5e9 : 8e10);
+}
+
+int siso_screen_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
+                             u64 *counter, PairsRedo *redo) {
+    return c->dtype == SISO_F32 ? pairs_launch<float>(c, (const float *)rows, invn, count, threshold, out_pairs, cap, counter, redo)
+                                : pairs_launch<bf16_t>(c, (const bf16_t *)rows, invn, count, threshold, out_pairs, cap, counter, redo);
+}

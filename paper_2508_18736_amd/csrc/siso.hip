@@ -184,13 +184,6 @@ __global__ __launch_bounds__(256) void k_import_rows(const T *__restrict__ src, 
 // names a group of four consecutive rows: their exact cosines (one wave per row; strict ">" in ascending
 // row order, so the lowest index keeps a tie); then the strict threshold test.  One 256-thread block
 // per query.  `vec` = rows are 16-byte aligned and a whole number of 16-byte chunks.
-// The thresholds of a call travel as kernel arguments (nothing to allocate or copy): out_hit[q * m + j] = 1 where
-// the similarity of query q exceeds v[j]; the hits at v[count_at] are the references that access counts.
-struct ThetaList {
-    float v[SISO_MULTI_MAX];
-    int m, count_at;
-};
-
 template <typename T>
 __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q, const T *__restrict__ cent,
                                                           const float *__restrict__ invn, const u64 *__restrict__ keys,
@@ -198,7 +191,8 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
                                                           int key_kind, int *out_idx, float *out_sim,
                                                           unsigned char *out_hit, unsigned *access,
                                                           const float *__restrict__ q_inv, int *upd_owner,
-                                                          int *upd_members) {
+                                                          int *upd_members, const int *__restrict__ many,
+                                                          const int *__restrict__ of, long q_base) {
     constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
     __shared__ float sh_f[4];
     __shared__ u64 sh_k[4];
@@ -206,6 +200,8 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
     __shared__ long sh_i[16];
     __shared__ u32x4_t sh_q[SISO_MAX_DIM / EPC];  // the query row
     const long q = blockIdx.x;
+    if (many && q >= *many) return;  // (see siso_tile_launch)
+    const long to = of ? of[q] : q;  // where its results go
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, grp = t >> 4, gl = t & 15;
     const T *qrow = Q + (size_t)q * d;
     // 1/|q|: 0 for a zero-length query, NaN for a non-finite one
@@ -251,26 +247,13 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
             best_s = unordered_bits((unsigned)(key >> 32)) * qi;
         }
     } else if (finite_q && K > 0 && key != 0) {
-        // the key names a group of four consecutive rows: one wave per row, its lanes share the row's chunks
-        const long r = 4L * (long)(0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull)) + wave;
-        float acc = 0.f;
-        if (vec) {
-            // both chunks of a lane in flight together; a row past the end reads the last row and is discarded
-            const T *crow = cent + (size_t)(r < K ? r : K - 1) * d;
-            for (int e0 = lane * EPC; e0 < d; e0 += 2 * 64 * EPC) {
-                const int e1 = e0 + 64 * EPC;
-                const u32x4_t c0v = *(const u32x4_t *)(crow + e0);
-                const u32x4_t c1v = *(const u32x4_t *)(crow + (e1 < d ? e1 : 0));
-                acc += chunk_dot(sh_q[e0 / EPC], c0v, T());
-                const float part = chunk_dot(sh_q[(e1 < d ? e1 : 0) / EPC], c1v, T());
-                acc += e1 < d ? part : 0.f;
-            }
-        } else if (r < K) {
-            const T *crow = cent + (size_t)r * d;
-            for (int e = lane; e < d; e += 64) acc += widen(qrow[e]) * widen(crow[e]);
-        }
-        acc = wave_sum(acc);
-        const float sv = r < K ? acc * qi * invn[r] : __uint_as_float(0x7FC00000u);
+        // the key names a group of four consecutive rows: one wave per row, its lanes share the row's chunks (a row past the
+        // end reads the last row and is discarded); or one row, whose cosine is formed anew: every wave forms the same sum
+        const long id = (long)(0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull));
+        const long r = key_kind == SISO_KEY_GROUPS4 ? 4L * id + wave : id;
+        const long at = r < K ? r : K - 1;
+        const float acc = row_product<T>(qrow, sh_q, vec, cent + (size_t)at * d, d, lane);
+        const float sv = r < K ? acc * qi * invn[at] : __uint_as_float(0x7FC00000u);
         if (sv == sv) {  // a NaN never wins
             best_s = sv;
             best_i = r;
@@ -284,7 +267,7 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
     if (t == 0) {
         // rows ascend with the group number inside a pass, and pass 1 lies above pass 0
         // (with groups of four every wave holds one row, ascending with the wave: the 16 entries repeat them)
-        for (int g = 1; g < (key_kind == SISO_KEY_ROWS ? 1 : 16); ++g) {
+        for (int g = 1; g < (key_kind == SISO_KEY_GROUPS4 ? 16 : 1); ++g) {
             const float os = sh_s[g];
             const long oi = sh_i[g];
             if (oi >= 0 && (best_i < 0 || os > best_s || (os == best_s && oi < best_i))) {
@@ -293,20 +276,7 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
             }
         }
         if (!finite_q) best_s = __uint_as_float(0x7FC00000u);
-        out_idx[q] = (int)best_i;
-        out_sim[q] = best_s;
-        for (int j = 0; j < thetas.m; ++j) {
-            const bool hit = best_i >= 0 && best_s > thetas.v[j];
-            if (out_hit) out_hit[(size_t)q * thetas.m + j] = hit ? 1 : 0;
-            // a hit is a reference to its centroid (access_count of Algorithm 1); infinity stays infinity
-            if (hit && j == thetas.count_at && access && access[best_i] != SISO_ACCESS_INF) atomicAdd(&access[best_i], 1u);
-            // siso_lookup_update on a large batch: the notes that k_update_mark would take (first member and
-            // number of members of each centroid), taken here, a launch earlier
-            if (hit && j == 0 && upd_owner) {
-                atomicMin(&upd_owner[best_i], (int)q);
-                atomicAdd(&upd_members[best_i], 1);
-            }
-        }
+        write_lookup(to, q_base, best_i, best_s, thetas, out_idx, out_sim, out_hit, access, upd_owner, upd_members);
     }
 }
 
@@ -1117,6 +1087,7 @@ int siso_arena(siso_cache *c, size_t device_bytes, size_t host_bytes) {
 }
 
 void siso_arena_done(siso_cache *c) {
+    siso_screen_done(c);
     if (c->arena_cap <= (size_t)SISO_ARENA_KEEP && c->pinned_cap <= (size_t)SISO_PINNED_KEEP) return;
     (void)hipStreamSynchronize(c->stream);
     if (c->arena_cap > (size_t)SISO_ARENA_KEEP) {
@@ -1247,6 +1218,8 @@ extern "C" void siso_destroy(siso_cache *c) {
     if (c->topk_cnt) (void)hipFree(c->topk_cnt);
     if (c->topk_cand) (void)hipFree(c->topk_cand);
     if (c->arena) (void)hipFree(c->arena);
+    if (c->screen) (void)hipFree(c->screen);
+    if (c->screen_pairs) (void)hipFree(c->screen_pairs);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->counters) (void)hipFree(c->counters);
     if (c->host_pin) (void)hipHostFree(c->host_pin);
@@ -1282,6 +1255,7 @@ extern "C" int siso_set_option(siso_cache *c, const char *name, long value) {
     if (!strcmp(name, "mfma_config")) c->opt_mfma_config = (int)value;
     else if (!strcmp(name, "tiles_per_slice")) c->opt_tiles_per_slice = (int)value;
     else if (!strcmp(name, "merge_config")) c->opt_merge_config = (int)value;
+    else if (!strcmp(name, "screen") && value <= 2) c->opt_screen = (int)value;
     else if (!strcmp(name, "mfma_qblock")) c->opt_mfma_qblock = (int)value;
     else if (!strcmp(name, "fold_spin_limit")) c->opt_fold_spin_limit = (int)value;
     else if (!strcmp(name, "topk_room")) c->opt_topk_room = (int)value;
@@ -1416,6 +1390,8 @@ extern "C" int siso_reserve(siso_cache *c, long n) {
         if (rc != SISO_OK) return rc;
     }
     if (c->dtype == SISO_FP8) return siso_fp8_ensure_batch(c, n);
+    // (no room for the bytes of a screened lookup is no error: such lookups then go without)
+    if (siso_screen_wanted(&full, n)) (void)siso_screen_reserve(c, c->capacity, n);
     if (n > 256) return ensure_update_notes(c);
     return SISO_OK;
 }
@@ -1437,15 +1413,16 @@ extern "C" int siso_lookup_multi(siso_cache *c, const void *queries, long n, con
     return siso_lookup_impl(c, queries, n, thetas, m, count_index, out_idx, out_sim, out_hit);
 }
 
-int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *thetas, int m, int count_index,
-                     int *out_idx, float *out_sim, unsigned char *out_hit, u64 *static_keys, long static_cap, int *folded) {
-    if (folded) *folded = 0;
-    if (n == 0) return SISO_OK;
-    if (n > 2147483647L / 4) return siso_fail(c, SISO_EINVAL, "siso_lookup: batch of %ld is too large", n);
+// A lookup on the kernels that form every product in the cache's own type.  Its plan: which of them, with how many slices, and
+// where the keys go.
+struct PlainLookup {
+    int path, slices;
+    u64 *keys;
+};
+static int plan_plain(siso_cache *c, long n, u64 *static_keys, long static_cap, PlainLookup *p) {
     int slices = 1;
     const int path = c->count > 0 ? choose_path(c, n) : SISO_PATH_SCALAR;
-    const bool fp8 = c->dtype == SISO_FP8;
-    if (fp8 && c->count > 0 && path == SISO_PATH_SCALAR && !siso_tile_preferred(c, n))
+    if (c->dtype == SISO_FP8 && c->count > 0 && path == SISO_PATH_SCALAR && !siso_tile_preferred(c, n))
         return siso_fail(c, SISO_EINVAL, "siso_lookup: the 8-bit storage has no scalar kernel");
     if (c->count > 0) {
         switch (path) {
@@ -1457,17 +1434,29 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
             return siso_fail(c, SISO_EINVAL, "siso_lookup: path %d cannot serve dim %d, type %d, batch %ld", path,
                              c->dim, c->dtype, n);
     }
-    int rc = SISO_OK;
     if (static_keys) {
         if (n * (long)slices > static_cap)
             return siso_fail(c, SISO_ECAPACITY,
                              "siso_lookup_static: %ld queries x %d slices of the centroids need %ld keys, the static "
                              "workspace holds %ld", n, slices, n * (long)slices, static_cap);
     } else {
-        rc = ensure_workspace(c, n, slices);
+        const int rc = ensure_workspace(c, n, slices);
         if (rc != SISO_OK) return rc;
     }
-    u64 *keys = static_keys ? static_keys : c->keys;
+    *p = PlainLookup{path, slices, static_keys ? static_keys : c->keys};
+    return SISO_OK;
+}
+
+// `timed`: a kernel of siso_profile_enable.  folded: see siso_lookup_impl.  owner, members: the notes of an update to be taken,
+// or NULL.  left: the queries that a screened lookup has left over (NULL: all are looked up).
+static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *queries, long n, const ThetaList &tl, long q_base,
+                        int *out_idx, float *out_sim, unsigned char *out_hit, bool timed, int *folded, int *owner, int *members,
+                        const ScreenPlain *left) {
+    const int path = plan.path, slices = plan.slices, m = tl.m, count_index = tl.count_at;
+    const bool fp8 = c->dtype == SISO_FP8;
+    const int *many = left ? left->many : nullptr, *of = left ? left->query : nullptr;
+    int rc = SISO_OK;
+    u64 *keys = plan.keys;
     const void *kernel_queries = queries;
     if (fp8) {  // the batch as codes, quantised like the stored rows
         rc = siso_fp8_ensure_batch(c, n);
@@ -1477,21 +1466,17 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
     }
     const unsigned qblocks = (unsigned)n;
     const int vec = ((c->dim * elem_bytes(c->dtype)) % 16 == 0 && ((uintptr_t)queries & 15) == 0) ? 1 : 0;
-    ThetaList tl;
-    tl.m = m;
-    tl.count_at = count_index;
-    for (int j = 0; j < SISO_MULTI_MAX; ++j) tl.v[j] = j < m ? thetas[j] : 0.f;
     int row_keys = SISO_KEY_ROWS;  // what the keys of the chosen kernel carry: the winning row, or its group of four rows
     const bool may_fold = folded && n <= SISO_FOLD_BOARD && c->count > 0 && (!fp8 || c->fold_master) && m == 1 && out_hit;
     c->board_to_clear = may_fold ? c->counters + 4 : nullptr;
     if (c->count > 0) {
-        if (!static_keys) siso_prof_begin(c);
+        if (timed) siso_prof_begin(c);
         switch (path) {
-            case SISO_PATH_SCALAR: rc = siso_tile_launch(c, kernel_queries, n, slices, keys); break;
-            case SISO_PATH_MFMA: rc = siso_mfma_launch(c, kernel_queries, n, slices, keys, &row_keys); break;
+            case SISO_PATH_SCALAR: rc = siso_tile_launch(c, kernel_queries, n, slices, keys, many); break;
+            case SISO_PATH_MFMA: rc = siso_mfma_launch(c, kernel_queries, n, slices, keys, &row_keys, many); break;
             case SISO_PATH_SKINNY: rc = siso_skinny_launch(c, kernel_queries, n, slices, keys, &row_keys); break;
         }
-        if (!static_keys) siso_prof_end(c);
+        if (timed) siso_prof_end(c);
         if (rc != SISO_OK) {
             c->board_to_clear = nullptr;
             return rc;
@@ -1508,7 +1493,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
         const int spin_limit = c->opt_fold_spin_limit >= 0 ? c->opt_fold_spin_limit : 1 << 18;
 #define SISO_LAUNCH_FOLD(T, E)                                                                                            \
     hipLaunchKernelGGL((k_finalize_update<T, E>), dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, keys, n, c->count, \
-                       c->dim, slices, thetas[0], vec, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr, \
+                       c->dim, slices, tl.v[0], vec, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr, \
                        (T *)tgt->cent, tgt->mean, tgt->size, tgt->invn, c->counters + 4, spin_limit, c->counters,         \
                        ms ? (const float *)c->fp8_qinv : (const float *)nullptr, ms ? (unsigned char *)c->cent : nullptr, \
                        ms ? c->scale : nullptr, ms ? c->invn : nullptr, ms ? c->size : nullptr)
@@ -1524,21 +1509,59 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
         *folded = 1;
         return SISO_OK;
     }
-    const bool mark = c->mark_in_finalize == 1 && m == 1 && c->upd_owner != nullptr;
-    if (c->dtype == SISO_F32)
-        hipLaunchKernelGGL(k_lookup_finalize<float>, dim3(qblocks), dim3(256), 0, c->stream, (const float *)queries,
-                           (const float *)c->cent, c->invn, keys, n, c->count, c->dim, slices, tl,
-                           vec, row_keys, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr,
-                           (const float *)nullptr, mark ? c->upd_owner : nullptr, mark ? c->upd_members : nullptr);
-    else
-        hipLaunchKernelGGL(k_lookup_finalize<bf16_t>, dim3(qblocks), dim3(256), 0, c->stream, (const bf16_t *)queries,
-                           (const bf16_t *)c->cent, c->invn, keys, n, c->count, c->dim, slices, tl,
-                           vec, row_keys, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr,
-                           fp8 ? (const float *)c->fp8_qinv : (const float *)nullptr, mark ? c->upd_owner : nullptr,
-                           mark ? c->upd_members : nullptr);
-    HIP_TRY(c, hipGetLastError());
-    if (mark) c->mark_in_finalize = 2;  // done
-    return SISO_OK;
+    // (the similarities of a batch are the same bits whether it is screened, as it would be with enough memory, or not)
+    if (row_keys == SISO_KEY_ROWS && siso_screen_wanted(c, n)) row_keys = SISO_KEY_ROWS_ANEW;
+#define SISO_LAUNCH_FINALIZE(T)                                                                                              \
+    hipLaunchKernelGGL(k_lookup_finalize<T>, dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
+                       keys, n, c->count, c->dim, slices, tl, vec, row_keys, out_idx, out_sim, out_hit,                        \
+                       count_index >= 0 ? c->access : nullptr, fp8 ? (const float *)c->fp8_qinv : (const float *)nullptr, owner, \
+                       members, many, of, q_base)
+    if (c->dtype == SISO_F32) SISO_LAUNCH_FINALIZE(float);
+    else SISO_LAUNCH_FINALIZE(bf16_t);
+#undef SISO_LAUNCH_FINALIZE
+    return siso_check_hip(c, hipGetLastError(), "k_lookup_finalize");
+}
+
+int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *thetas, int m, int count_index,
+                     int *out_idx, float *out_sim, unsigned char *out_hit, u64 *static_keys, long static_cap, int *folded) {
+    if (folded) *folded = 0;
+    if (n == 0) return SISO_OK;
+    if (n > 2147483647L / 4) return siso_fail(c, SISO_EINVAL, "siso_lookup: batch of %ld is too large", n);
+    ThetaList tl;
+    tl.m = m;
+    tl.count_at = count_index;
+    for (int j = 0; j < SISO_MULTI_MAX; ++j) tl.v[j] = j < m ? thetas[j] : 0.f;
+    // the notes of the update that follows are taken by whatever ends the lookup
+    int *owner = nullptr, *members = nullptr;
+    if (c->mark_in_finalize == 1 && m == 1 && c->upd_owner != nullptr) {
+        owner = c->upd_owner;
+        members = c->upd_members;
+    }
+    PlainLookup plain;
+    if (siso_screen_wanted(c, n) && (static_keys ? siso_screen_has_room(c, n) : siso_screen_reserve(c, c->count, n))) {
+        // piece by piece: screened, then what that has left over
+        const size_t row = (size_t)c->dim * elem_bytes(c->dtype);
+        int rc = plan_plain(c, n < SISO_SCREEN_PIECE ? n : SISO_SCREEN_PIECE, static_keys, static_cap, &plain);
+        for (long off = 0; off < n && rc == SISO_OK; off += SISO_SCREEN_PIECE) {
+            const long part = n - off < SISO_SCREEN_PIECE ? n - off : SISO_SCREEN_PIECE;
+            const char *q = (const char *)queries + (size_t)off * row;
+            unsigned char *hit = out_hit ? out_hit + (size_t)off * m : nullptr;
+            ScreenPlain left;
+            if (off > 0) rc = plan_plain(c, part, static_keys, static_cap, &plain);
+            if (rc != SISO_OK) break;
+            if (owner) c->mark_in_finalize = 2;
+            rc = siso_screen_lookup(c, q, part, off == 0, tl, off, out_idx + off, out_sim + off, hit,
+                                    count_index >= 0 ? c->access : nullptr, owner, members, !static_keys, &left);
+            if (rc == SISO_OK)
+                rc = plain_lookup(c, plain, left.rows, part, tl, off, out_idx + off, out_sim + off, hit, false, nullptr, owner, members, &left);
+        }
+        return rc;
+    }
+    int rc = plan_plain(c, n, static_keys, static_cap, &plain);
+    if (rc == SISO_OK)
+        rc = plain_lookup(c, plain, queries, n, tl, 0, out_idx, out_sim, out_hit, !static_keys, folded, owner, members, nullptr);
+    if (rc == SISO_OK && owner && !(folded && *folded)) c->mark_in_finalize = 2;  // done
+    return rc;
 }
 
 #define UPDATE_CHUNK 32768L
@@ -1667,6 +1690,17 @@ extern "C" long siso_bad_indices(siso_cache *c) {
     return rc != SISO_OK ? (long)rc : (long)v;
 }
 
+int siso_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
+                      u64 *counter) {
+    PairsRedo redo = {nullptr, 0};
+    if (siso_screen_pairs_wanted(c, count, threshold) && siso_screen_reserve_pairs(c, count)) {
+        const int rc = siso_screen_pairs_launch(c, rows, invn, count, threshold, out_pairs, cap, counter, &redo);
+        if (rc != SISO_OK) return rc;
+    }
+    return siso_pairs_mfma_supported(c, count) ? siso_pairs_mfma_launch(c, rows, invn, count, threshold, out_pairs, cap, counter, redo)
+                                               : siso_pairs_tile_launch(c, rows, invn, count, threshold, out_pairs, cap, counter, redo);
+}
+
 extern "C" long siso_merge(siso_cache *c, float threshold, int *out_pairs, long cap) {
     if (!c) return SISO_EINVAL;
     SISO_NOT_FP8(c, "siso_merge");
@@ -1676,14 +1710,12 @@ extern "C" long siso_merge(siso_cache *c, float threshold, int *out_pairs, long 
     int rc = siso_check_hip(c, hipGetLastError(), "k_zero_counter");
     if (rc != SISO_OK) return rc;
     siso_prof_begin(c);
-    if (siso_pairs_mfma_supported(c, c->count))
-        rc = siso_pairs_mfma_launch(c, c->cent, c->invn, c->count, threshold, out_pairs, cap, c->counters + 1);
-    else
-        rc = siso_pairs_tile_launch(c, c->cent, c->invn, c->count, threshold, out_pairs, cap, c->counters + 1);
+    rc = siso_pairs_launch(c, c->cent, c->invn, c->count, threshold, out_pairs, cap, c->counters + 1);
     siso_prof_end(c);
     if (rc != SISO_OK) return rc;
     u64 total = 0;
     rc = siso_read_counter(c, 1, &total);
+    siso_screen_done(c);
     return rc != SISO_OK ? (long)rc : (long)total;
 }
 

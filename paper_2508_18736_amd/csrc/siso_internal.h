@@ -24,7 +24,9 @@ typedef unsigned short bf16_t;  // bfloat16 bit pattern
 // the four cosines exactly and picks the lowest index among their maxima.  Ids
 // ascend with the rows, so "the lowest id among equal values" always holds the
 // lowest index among equal maxima.
-enum { SISO_KEY_ROWS = 1, SISO_KEY_GROUPS4 = 3 };
+// SISO_KEY_ROWS_ANEW: the id is the row, and its cosine is formed anew all the same, with the sums of the finalize kernel
+// (where a screened lookup of the same batch would do so: the similarities are then the same bits on either way).
+enum { SISO_KEY_ROWS = 1, SISO_KEY_ROWS_ANEW = 2, SISO_KEY_GROUPS4 = 3 };
 #define SISO_ACCESS_INF 0xFFFFFFFFu
 #define SISO_MAX_DIM 4096
 #define SISO_FOLD_BOARD 256  // queries of a siso_lookup_update that ends in one kernel: one slot each
@@ -103,7 +105,13 @@ struct siso_cache {
     u64 *board_to_clear;  // not NULL while siso_lookup_update launches its first phase: a kernel that empties these
                           // slots sets it back to NULL
 
+    // screened lookups and pair searches (screen.hip): bytes of rows and queries, bounds, lists; grown on demand.  Two
+    // workspaces, so that a pair search does not move what a captured lookup refers to.
+    char *screen, *screen_pairs;
+    size_t screen_cap, screen_pairs_cap;
+
     // tuning knobs (siso_set_option); 0 = library default
+    int opt_screen;  // 1 = screen wherever the kernels can, 2 = never
     int opt_mfma_config;
     int opt_tiles_per_slice;
     int opt_merge_config;
@@ -235,6 +243,73 @@ __device__ __forceinline__ float chunk_dot(u32x4_t x, u32x4_t y, fp8_t) {  // si
         s += xh[1] * yh[1];
     }
     return s;
+}
+
+// Products of queries with R rows, this lane's share of the sums (the whole wave must call): row r with the query whose chunks
+// are at sh_q[r] in LDS (vec: rows are 16-byte aligned and a whole number of 16-byte chunks), or with the one at
+// qrows[r].  Two chunks of every row in flight.
+template <typename T, int R>
+__device__ __forceinline__ void row_products(const T *const (&qrows)[R], const u32x4_t *const (&sh_q)[R], int vec,
+                                             const T *const (&rows)[R], int d, int lane, float (&sum)[R]) {
+    constexpr int EPC = 16 / (int)sizeof(T);
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum[r] = 0.f;
+    if (vec) {
+#pragma unroll 1
+        for (int e0 = lane * EPC; e0 < d; e0 += 2 * 64 * EPC) {
+            const int e1 = e0 + 64 * EPC;
+            u32x4_t c0[R], c1[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                c0[r] = *(const u32x4_t *)(rows[r] + e0);
+                c1[r] = *(const u32x4_t *)(rows[r] + (e1 < d ? e1 : 0));
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                sum[r] += chunk_dot(sh_q[r][e0 / EPC], c0[r], T());
+                const float part = chunk_dot(sh_q[r][(e1 < d ? e1 : 0) / EPC], c1[r], T());
+                sum[r] += e1 < d ? part : 0.f;
+            }
+        }
+    } else {
+        for (int e = lane; e < d; e += 64)
+#pragma unroll
+            for (int r = 0; r < R; ++r) sum[r] += widen(qrows[r][e]) * widen(rows[r][e]);
+    }
+}
+template <typename T>
+__device__ __forceinline__ float row_product(const T *qrow, const u32x4_t *sh_q, int vec, const T *row, int d, int lane) {
+    const T *const rows[1] = {row}, *const qrows[1] = {qrow};
+    const u32x4_t *const chunks[1] = {sh_q};
+    float sum[1];
+    row_products<T, 1>(qrows, chunks, vec, rows, d, lane, sum);
+    return wave_sum(sum[0]);
+}
+
+// The thresholds of a call travel as kernel arguments (nothing to allocate or copy): out_hit[q * m + j] = 1 where
+// the similarity of query q exceeds v[j]; the hits at v[count_at] are the references that access counts.
+struct ThetaList {
+    float v[SISO_MULTI_MAX];
+    int m, count_at;
+};
+// What a lookup leaves of query q, by one thread (q_base + q = its number in the whole batch).
+__device__ __forceinline__ void write_lookup(long q, long q_base, long best_i, float best_s, const ThetaList &thetas, int *out_idx,
+                                             float *out_sim, unsigned char *out_hit, unsigned *access, int *upd_owner,
+                                             int *upd_members) {
+    out_idx[q] = (int)best_i;
+    out_sim[q] = best_s;
+    for (int j = 0; j < thetas.m; ++j) {
+        const bool hit = best_i >= 0 && best_s > thetas.v[j];
+        if (out_hit) out_hit[(size_t)q * thetas.m + j] = hit ? 1 : 0;
+        // a hit is a reference to its centroid (access_count of Algorithm 1); infinity stays infinity
+        if (hit && j == thetas.count_at && access && access[best_i] != SISO_ACCESS_INF) atomicAdd(&access[best_i], 1u);
+        // siso_lookup_update on a large batch: the notes that k_update_mark would take (first member and
+        // number of members of each centroid), taken here, a launch earlier
+        if (hit && j == 0 && upd_owner) {
+            atomicMin(&upd_owner[best_i], (int)(q_base + q));
+            atomicAdd(&upd_members[best_i], 1);
+        }
+    }
 }
 
 // ---- the quantiser of the 8-bit storage (k_fp8_quantize, and the end of siso_fp8_lookup_update)
@@ -411,12 +486,14 @@ int siso_check_hip(siso_cache *c, hipError_t e, const char *what);
 // nothing has to be cleared beforehand).
 // *_slices returns the number of slices the launcher will use (0 = path cannot
 // handle this cache / batch).
+//
+// `many` (NULL = n): on the device, how many of the n queries there are: a workgroup beyond them leaves at once.
 int siso_tile_preferred(const siso_cache *c, long n);  // 1 = small: rather these kernels, also where siso_mfma_* could
 int siso_tile_slices(const siso_cache *c, long n);
 long siso_tile_keys_bound(const siso_cache *c, long n);
-int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys);
+int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, const int *many = nullptr);
 int siso_mfma_slices(const siso_cache *c, long n);
-int siso_mfma_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
+int siso_mfma_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys, const int *many = nullptr);
 int siso_skinny_slices(const siso_cache *c, long n);
 int siso_skinny_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
 
@@ -437,14 +514,53 @@ int siso_topk_fp8_pass1(siso_cache *c, long n, int slices, u64 *keys);
 int siso_topk_fp8_collect(siso_cache *c, long n, int slices, const float *tau, int *cand, int *cnt, int cap);
 int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng);
 
+// Screened lookups and pair searches (screen.hip).
+// siso_screen_wanted: is a lookup of n queries to be screened?  If so, and if siso_screen_reserve finds room (0 = there is
+// none: the lookup goes without), siso_screen_lookup takes siso_screen_piece() queries at a time (with_rows: the rows have to
+// be written as bytes, for the first piece of a call) and leaves some to the other kernels: *plain names them (all on the
+// device, written by the launch): how many, which, and their rows one behind the other.
+#define SISO_SCREEN_DIM 1024  // largest dimension
+#define SISO_SCREEN_PIECE 16384L
+struct ScreenPlain {
+    const int *many, *query;
+    const void *rows;
+};
+int siso_screen_wanted(const siso_cache *c, long n);
+int siso_screen_reserve(siso_cache *c, long rows, long n);  // may synchronise and allocate, but not under capture
+int siso_screen_reserve_pairs(siso_cache *c, long rows);
+void siso_screen_done(siso_cache *c);
+int siso_screen_has_room(const siso_cache *c, long n);
+int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
+                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, bool timed,
+                       ScreenPlain *plain);
+// The same for pairs above a threshold (room: siso_screen_reserve_pairs; siso_screen_done, at the end of a call, gives
+// back what is larger than the library keeps between calls).  Behind it the search of all pairs has to be
+// launched with `redo`: its workgroups leave at once unless more than redo_above pairs were in doubt.
+struct PairsRedo {
+    const u64 *count;  // NULL = search all pairs
+    u64 above;
+};
+int siso_screen_pairs_wanted(const siso_cache *c, long count, float threshold);
+int siso_screen_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
+                             u64 *counter, PairsRedo *redo);
+struct BytePlan {
+    int tiles_per_slice, slices, nqt, qb;
+    long grid;
+};
+int siso_byte_plan(const siso_cache *c, long rows, long n, int dp, int most_tiles, BytePlan *p);  // 256 x 256 tiles of dp bytes a row
+
+// All pairs above a threshold, on the kernels that serve the cache best.
+int siso_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
+                      u64 *counter);
+
 // Self-similarity pair search over `count` rows of the cache's element type and dimension with
 // their inverse lengths (counter already zeroed).  The MFMA kernel reads whole tiles: rows and invn
 // must be readable for SISO_PAD_ROWS entries past count, the invn entries there holding NaN.
 int siso_pairs_tile_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold,
-                             int *out_pairs, long cap, u64 *counter);
+                           int *out_pairs, long cap, u64 *counter, PairsRedo redo);
 int siso_pairs_mfma_supported(const siso_cache *c, long count);
 int siso_pairs_mfma_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold,
-                           int *out_pairs, long cap, u64 *counter);
+                           int *out_pairs, long cap, u64 *counter, PairsRedo redo);
 
 // siso_lookup without the argument checks of the ABI, against m thresholds (host pointer, 1 <= m <=
 // SISO_MULTI_MAX; out_hit is [n][m] or NULL); the hits at thetas[count_index] are references to their

@@ -1,0 +1,238 @@
+"""Screened lookups and pair searches (products of bytes rule rows out, the others are formed anew) against plain torch in
+64 bits, forced on by an option at sizes where they can go wrong: edges of tiles and blocks of 32 rows, dimensions that
+no slab divides, one row, one query; and the rows and queries that the bound says nothing about."""
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
+# the similarities are single-precision sums of the stored rows' products: d / 64 + 8 roundings of 2^-24, of 1 in all
+TOL = 2e-6
+
+
+@pytest.fixture(scope="module")
+def siso():
+    from paper_2508_18736_amd import siso as m
+    return m
+
+
+def make(siso, rows, dtype, screen=1):
+    cache = siso.SisoCache(rows.shape[1], rows.shape[0], siso.F32 if dtype == "f32" else siso.BF16)
+    cache.set_option("screen", screen)
+    cache.load(rows)
+    return cache
+
+
+def rows_near(g, base, n, noise, dtype):
+    """n rows near random ones of base, of random lengths."""
+    pick = torch.randint(0, base.shape[0], (n,), device=DEV, generator=g)
+    x = base[pick].float()
+    x = x / x.norm(dim=1, keepdim=True) + noise / base.shape[1] ** 0.5 * torch.randn(n, base.shape[1], device=DEV, generator=g)
+    return (x * (0.5 + torch.rand(n, 1, device=DEV, generator=g))).to(dtype)
+
+
+def unit(x):
+    x = x.double()
+    return x / x.norm(dim=1, keepdim=True)
+
+
+def check(idx, sim, q, c):
+    """The named row's cosine is the value given, and no row's is larger by more than the roundings."""
+    s = unit(q) @ unit(c).T
+    own = s.gather(1, idx.long()[:, None])[:, 0]
+    assert (own - sim.double()).abs().max() <= TOL
+    best = s.nan_to_num(nan=-2.0).max(1).values
+    assert (best - own).max() <= 2 * TOL
+    clear = s.topk(2, 1).values if s.shape[1] > 1 else None
+    if clear is not None:
+        sure = clear[:, 0] - clear[:, 1] > 4 * TOL
+        assert torch.equal(idx.long()[sure], s.argmax(1)[sure])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("K,n,d", [(1, 1, 128), (31, 257, 128), (33, 3, 130), (256, 256, 256), (257, 300, 300), (5000, 33, 384),
+                                   (5003, 1025, 768), (20011, 700, 1000), (9000, 513, 1024), (4096 * 5 + 1, 64, 257)])
+def test_lookup(siso, dtype, K, n, d):
+    print(f"case: screen lookup {dtype} K={K} n={n} d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K + n + d)
+    base = torch.randn(max(1, K // 8), d, device=DEV, generator=g)
+    c = rows_near(g, base, K, 0.1, TYPES[dtype])
+    q = torch.cat([rows_near(g, c, n - n // 3, 0.1, TYPES[dtype]), torch.randn(n // 3, d, device=DEV, generator=g).to(TYPES[dtype])])
+    q = q[torch.randperm(n, device=DEV, generator=g)].contiguous()
+    cache = make(siso, c, dtype)
+    idx, sim, hit = cache.lookup(q, 0.85)
+    check(idx, sim, q, c)
+    assert torch.equal(hit, (sim > 0.85).to(torch.uint8))
+    # the same bits as without the bytes, up to rows whose cosines are equal within the roundings
+    other = make(siso, c, dtype, screen=2).lookup(q, 0.85)
+    assert (other[1] - sim).abs().max() <= 2 * TOL
+
+
+def test_rows_and_queries_the_bound_says_nothing_about(siso):
+    g = torch.Generator(device=DEV).manual_seed(5)
+    d, K, n = 384, 3000, 600
+    for dtype in ("f32", "bf16"):
+        print(f"case: screen odd rows {dtype}", flush=True)
+        t = TYPES[dtype]
+        c = torch.randn(K, d, device=DEV, generator=g).to(t)
+        c[5] = 0
+        c[77, 3] = float("nan")
+        c[1000, 9] = float("inf")
+        c[1500] *= 1e-17    # lengths whose squares are near the end of the range
+        c[1501] *= 1e17
+        c[2990, 0] = 1000   # one element far above the others
+        q = torch.randn(n, d, device=DEV, generator=g).to(t)
+        q[0] = 0
+        q[1, 1] = float("nan")
+        q[2, 2] = float("-inf")
+        q[3] = c[2990]
+        q[4] = c[1500]
+        q[5] = c[1501]
+        q[6] *= 1e-17
+        idx, sim, _ = make(siso, c, dtype).lookup(q, 0.5)
+        want = make(siso, c, dtype, screen=2).lookup(q, 0.5)
+        assert torch.equal(torch.isnan(sim), torch.isnan(want[1]))
+        fine = ~torch.isnan(sim)
+        assert (sim - want[1])[fine].abs().max() <= 2 * TOL
+        assert torch.equal(idx[:7], want[0][:7]) and idx[1] == -1 and idx[0] == 0
+        rest = torch.arange(n, device=DEV) >= 7
+        usable = torch.ones(K, dtype=torch.bool, device=DEV)
+        usable[[77, 1000]] = False
+        s = unit(q[rest]) @ unit(c.double().clamp(-1e30, 1e30)).T.nan_to_num(nan=0.0)
+        s[:, ~usable] = -2
+        top = s.topk(2, 1)
+        sure = top.values[:, 0] - top.values[:, 1] > 4 * TOL
+        assert torch.equal(idx[rest].long()[sure], top.indices[sure, 0])
+        # every cosine below zero, and rows past the end or without a cosine must not count as zero
+        far = -q[7:8].expand(40, d).contiguous() * (1 + 0.1 * torch.rand(40, 1, device=DEV, generator=g)).to(t)
+        far[3, 0] = float("nan")
+        i2, s2, _ = make(siso, far, dtype).lookup(q[7:8].expand(300, d).contiguous(), 0.5)
+        assert bool((s2 < -0.9).all()) and bool((i2 != 3).all()) and bool((i2 >= 0).all())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_more_equal_rows_than_a_list_holds(siso, dtype):
+    """Queries whose best row is there some thousand times go to the other kernels, the others do not; lowest index wins."""
+    print(f"case: screen duplicates {dtype}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    d, n = 256, 700
+    c = torch.randn(9000, d, device=DEV, generator=g).to(TYPES[dtype])
+    c[2000:5000] = c[2000]
+    q = torch.randn(n, d, device=DEV, generator=g).to(TYPES[dtype])
+    q[40:45] = c[2000]
+    q[690] = c[2000]
+    idx, sim, _ = make(siso, c, dtype).lookup(q, 0.5)
+    assert idx[40:45].tolist() == [2000] * 5 and idx[690] == 2000
+    want = make(siso, c, dtype, screen=2).lookup(q, 0.5)
+    assert torch.equal(idx, want[0]) and (sim - want[1]).abs().max() <= 2 * TOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_more_rows_near_the_best_than_are_multiplied_again(siso, dtype):
+    """Hundreds of near-equal rows for every query: the first queries of the batch fill the list of rows to be multiplied
+    again, the others go to the other kernels."""
+    print(f"case: screen crowd {dtype}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(10)
+    d, n = 384, 500
+    base = torch.randn(4, d, device=DEV, generator=g)
+    c = rows_near(g, base, 3600, 0.02, TYPES[dtype])
+    q = rows_near(g, base, n, 0.05, TYPES[dtype])
+    idx, sim, _ = make(siso, c, dtype).lookup(q, 0.5)
+    check(idx, sim, q, c)
+
+
+def test_batches_of_several_pieces_and_the_update_behind_them(siso):
+    print("case: screen pieces", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    d, K, n = 128, 2000, 16384 + 300
+    c = rows_near(g, torch.randn(500, d, device=DEV, generator=g), K, 0.2, torch.bfloat16)
+    q = rows_near(g, c, n, 0.1, torch.bfloat16)
+    one, two = make(siso, c, "bf16"), make(siso, c, "bf16")
+    idx, sim, hit = one.lookup_update(q, 0.85)
+    check(idx, sim, q, c)
+    i2, s2, h2 = two.lookup(q, 0.85)
+    two.update(q, i2, h2)
+    assert torch.equal(idx, i2) and torch.equal(sim, s2) and torch.equal(hit, h2)
+    for a, b in zip(one.export() + one.export_meta(), two.export() + two.export_meta()):
+        assert torch.equal(a, b)
+
+
+def test_static_and_captured_lookups(siso):
+    """Neither allocates: with the room of an earlier call (or siso_reserve) they are screened, without it they are not;
+    the similarities are the same bits."""
+    print("case: screen static and graph", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(13)
+    d, K, n = 300, 3000, 400
+    c = torch.randn(K, d, device=DEV, generator=g)
+    q = torch.randn(n, d, device=DEV, generator=g)
+    cache = make(siso, c, "f32")
+    out = (torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV), torch.empty(n, dtype=torch.uint8, device=DEV))
+    cache.lookup_static(q, 0.1, *out)
+    without = [t.clone() for t in out]
+    idx, sim, hit = cache.lookup(q, 0.1)
+    cache.lookup_static(q, 0.1, *out)
+    for a, b, w in zip((idx, sim, hit), out, without):
+        assert torch.equal(a, b) and torch.equal(a, w)
+    side = torch.cuda.Stream()
+    cache.set_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        cache.lookup(q, 0.1, *out)
+    for seed in range(3):
+        q.copy_(torch.randn(n, d, device=DEV, generator=g))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in out]
+        want = cache.lookup(q, 0.1)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+        check(got[0], got[1], q, c)
+
+
+def pair_set(pairs, total):
+    got = pairs[:total].tolist()
+    assert len(got) == total
+    return set(map(tuple, got))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("K,d,theta", [(2, 128, 0.5), (255, 130, 0.8), (257, 256, 0.9), (3000, 300, 0.9), (5001, 768, 0.3), (2600, 1024, 0.95)])
+def test_pairs(siso, dtype, K, d, theta):
+    """Cosines spread over both sides of the threshold, many of them closer to it than the bytes can tell."""
+    print(f"case: screen pairs {dtype} K={K} d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K + d)
+    a = torch.randn(max(1, K // 6), d, device=DEV, generator=g)
+    c = rows_near(g, a, K, (1 / theta - 1) ** 0.5, TYPES[dtype])
+    if K > 100:
+        c[7] = 0
+        c[50, 2] = float("nan")
+        c[90] *= 1e-17
+    pairs, total = make(siso, c, dtype).merge(theta, K * 40)
+    s = unit(c) @ unit(c).T
+    i, j = torch.triu_indices(K, K, 1, device=DEV)
+    v = s[i, j]
+    th = float(torch.tensor(theta, dtype=torch.float32))
+    sure = set(map(tuple, torch.stack([i, j], 1)[v > th + TOL].tolist()))
+    may = set(map(tuple, torch.stack([i, j], 1)[v > th - TOL].tolist()))
+    assert total <= K * 40
+    got = pair_set(pairs, total)
+    assert sure <= got <= may
+    assert K < 200 or len(sure) > 100
+
+
+def test_more_pairs_in_doubt_than_the_list_holds(siso):
+    print("case: screen pairs redo", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    d, K = 256, 2100
+    c = torch.randn(1, d, device=DEV, generator=g) / d ** 0.5 + torch.randn(K, d, device=DEV, generator=g) * (1 / 0.9 - 1) ** 0.5 / d ** 0.5
+    for dtype in ("f32", "bf16"):
+        x = c.to(TYPES[dtype])
+        pairs, total = make(siso, x, dtype).merge(0.9, K * K)
+        want, many = make(siso, x, dtype, screen=2).merge(0.9, K * K)
+        assert total == many > 100000
+        assert pair_set(pairs, total) == pair_set(want, many)
