@@ -231,6 +231,13 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
     };
     auto issue = [&]() { static_for<0, NL>(issue_part); };
+    // With two stages the loads of a slab are dealt out between the MFMAs that follow the barrier.  A compute unit's 64 wave
+    // instructions take its texture unit a thousand cycles to work off; issued at once they hold up the waves that long.  So
+    // nothing there depends on a condition: behind the last slab it is fetched once more, into a stage nobody reads again.
+    // Random rows, us, at once / dealt out: 120,000 x 2,048 x 384 178 / 170, x 768 320 / 307, x 1,024 411 / 397, x 2,048 853 /
+    // 780; 200,000 x 4,096 x 1,024 1,397 / 1,310.  (The 64-deep MFMAs over codes take twice as long each and cover the burst:
+    // no gain there.)
+    constexpr bool DEAL = NSTAGE == 2 && !Cfg::K64;
 
     // Pipeline:
     //   all but the last step of slab t | wait: own reads of slab t done, own loads of slab t+1 landed | barrier |
@@ -396,51 +403,64 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     } else {
         constexpr int NF = WC + WQ;  // fragment reads per step
         bf16x8 af[2][WC], bf[2][WQ];
-        for (int i = 0; i < NSTAGE && i < T; ++i) issue();
-        if (T >= NSTAGE) vm_wait<(NSTAGE - 1) * NL>();
-        else vm_wait<0>();
+        // the MFMAs of a step; with load parts dealt out: part P + i / 2 behind every second one
+        auto mma = [&](auto bufc, auto firstc, auto partc) __attribute__((always_inline)) {
+            constexpr int U = decltype(bufc)::value, P = decltype(partc)::value;
+            static_for<0, WC * WQ>([&](auto ii) __attribute__((always_inline)) {
+                constexpr int i = decltype(ii)::value, A = i / WQ, B = i % WQ;
+                if constexpr (decltype(firstc)::value != 0) acc.template first<A, B>(af[U][A], bf[U][B]);
+                else acc.template mac<A, B>(af[U][A], bf[U][B]);
+                if constexpr (DEAL && P >= 0 && i % 2 == 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue_part(IC<P + i / 2>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        };
+        if constexpr (DEAL) {  // slab 0 and the first half of slab 1, as if a slab had just gone by
+            static_assert(WC * WQ == NL && NL % 2 == 0, "two steps take the loads of a slab");
+            issue();
+            static_for<0, NL / 2>(issue_part);
+            vm_wait<NL / 2>();
+        } else {
+            for (int i = 0; i < NSTAGE && i < T; ++i) issue();
+            if (T >= NSTAGE) vm_wait<(NSTAGE - 1) * NL>();
+            else vm_wait<0>();
+        }
         __syncthreads();
         lds_frags<SUB>(af[0], bf[0], row_a + so[0], row_b + so[0]);
 
         unsigned sto = 0;  // byte offset of the stage of slab t
         for (int t = 0; t < T; ++t) {
             const unsigned sto_next = (sto + STAGE == NSTAGE * STAGE) ? 0u : sto + STAGE;
-    #pragma unroll
-            for (int kk = 0; kk < KK - 1; ++kk) {
+            static_for<0, KK - 1>([&](auto kc) __attribute__((always_inline)) {
+                constexpr int kk = decltype(kc)::value;
                 lds_frags<SUB>(af[(kk + 1) & 1], bf[(kk + 1) & 1], row_a + sto + so[kk + 1], row_b + sto + so[kk + 1]);
                 lds_wait<NF>(af[kk & 1], bf[kk & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                if (kk == 0 && ks == 0) {
+                if constexpr (kk == 0) {
                     // first step of a tile: start from zero instead of clearing the accumulators
-                    static_for<0, WC>([&](auto ia) {
-                        static_for<0, WQ>([&](auto ib) {
-                            constexpr int A = decltype(ia)::value, B = decltype(ib)::value;
-                            acc.template first<A, B>(af[0][A], bf[0][B]);
-                        });
-                    });
+                    if (ks == 0) mma(IC<0>{}, IC<1>{}, IC<NL / 2>{});
+                    else mma(IC<0>{}, IC<0>{}, IC<NL / 2>{});
                 } else {
-                    static_for<0, WC>([&](auto ia) {
-                        static_for<0, WQ>([&](auto ib) {
-                            constexpr int A = decltype(ia)::value, B = decltype(ib)::value;
-                            acc.template mac<A, B>(af[kk & 1][A], bf[kk & 1][B]);
-                        });
-                    });
+                    mma(IC<kk & 1>{}, IC<0>{}, IC<-1>{});
                 }
                 __builtin_amdgcn_sched_barrier(0);
-            }
+            });
+            static_assert(KK % 2 == 0, "the last step of a slab has the second buffer");
             lds_wait<0>(af[1], bf[1]);
             if (t + NSTAGE <= T) vm_wait<(NSTAGE - 2) * NL>();
             else vm_wait<0>();
             __syncthreads();
-            if (t + NSTAGE < T) issue();
-            if (t + 1 < T) lds_frags<SUB>(af[0], bf[0], row_a + sto_next + so[0], row_b + sto_next + so[0]);
+            if constexpr (DEAL) {
+                // (behind the last slab the stage of a slab that does not exist: within LDS, never used)
+                lds_frags<SUB>(af[0], bf[0], row_a + sto_next + so[0], row_b + sto_next + so[0]);
+            } else {
+                if (t + NSTAGE < T) issue();
+                if (t + 1 < T) lds_frags<SUB>(af[0], bf[0], row_a + sto_next + so[0], row_b + sto_next + so[0]);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            static_for<0, WC>([&](auto ia) {
-                static_for<0, WQ>([&](auto ib) {
-                    constexpr int A = decltype(ia)::value, B = decltype(ib)::value;
-                    acc.template mac<A, B>(af[1][A], bf[1][B]);
-                });
-            });
+            mma(IC<1>{}, IC<0>{}, IC<0>{});
             __builtin_amdgcn_sched_barrier(0);
             if (ks == nk - 1) {
                 fold_tile(ct, cp_inv);
@@ -452,7 +472,9 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             }
             sto = sto_next;
         }
+        if constexpr (DEAL) lds_wait<0>(af[0], bf[0]);
     }
+    if constexpr (DEAL) vm_wait<0>();  // (the loads behind the last slab: their stage is about to be used otherwise)
     if constexpr (MODE == PIPE_KEYS) {
         __syncthreads();
         pipe_reduce_keys<WQ, NWC, BQ, NT, Cfg::ROWS>(bv, bb, smem, wc, wq, h, l32, tid, q0, n, slices, s, keys);
@@ -1330,15 +1352,10 @@ static bool pipe_plan(const siso_cache *c, long n, int cfg, long want_wgs, PipeP
 static bool mfma_plan(const siso_cache *c, long n, PipePlan *p) {
     int cfg = c->opt_mfma_config;
     if (cfg == 0 && c->dtype == SISO_FP8) cfg = n <= 64 ? 8 : n <= 128 ? 7 : 6;  // the 64-deep MFMAs
-    // Large batches: eight waves (1) or the four wide ones (5), the same tile and the same sums.  The end of a tile, where its
-    // products are scaled and compared, is hidden behind the other wave of the SIMD with eight and stands alone with
-    // four, and the shorter the dimension the more it weighs; the wide kernel reads less from LDS.  Eight waves / wide, us,
-    // random rows: 120,000 x 2,048 x 128 74.7 / 92.7, x 256 121.6 / 137.7, x 384 168.9 / 182.9, x 512 218 / 232, x 768
-    // 314 / 319, x 2,048 853 / 831; 200,000 x 4,096 x 2,048 3,030 / 2,960; 100,000 x 4,096 x 4,096 3,040 / 2,910.  At 1,024
-    // elements the eight waves are still ahead, by one to three parts in a hundred (120,000 x 2,048 411 / 415, 200,000 x 4,096
-    // 1,397 / 1,408, 1,048,576 x 16,384 28,590 / 29,290): the two meet between 1,024 and 2,048, and what the line
-    // leaves to the wide kernel at 1,024 is that much.
-    if (cfg == 0) cfg = n <= 64 ? 3 : n <= 128 ? 2 : c->dim < 1024 ? 1 : 5;
+    // Large batches: eight waves.  The four wide ones (5) have the same tile and the same sums and read less from LDS, but
+    // nothing covers the end of their tiles; eight / wide, us, random rows: 120,000 x 2,048 x 384 170 / 187, x 768 307 / 332,
+    // x 1,024 397 / 430, x 2,048 780 / 830; 200,000 x 4,096 x 2,048 2,709 / 2,880; 100,000 x 4,096 x 4,096 2,725 / 2,845.
+    if (cfg == 0) cfg = n <= 64 ? 3 : n <= 128 ? 2 : 1;
     // about two workgroups per compute unit when there is enough work
     return pipe_plan(c, n, cfg, 512, p);
 }
