@@ -307,6 +307,93 @@ __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_
     }
 }
 
+// Small single-precision lookups: a tile of 32 x 32 per workgroup, and the dimension split among its four waves, whose sums meet
+// in LDS.  Such a problem does not fill the chip with larger tiles, and then takes as long as one of their waves takes for
+// the whole dimension, slab by slab: 256 queries x 1,024 rows x 384 in 64 x 64 tiles are 64 workgroups for 256 compute
+// units and 192 instructions of 64 cycles in a row for each wave; here 256 workgroups and 48.  Fragments come from memory
+// straight into registers (what the workgroups share is in L2), a group of steps ahead of the one being multiplied.
+template <int W>
+__global__ __launch_bounds__(256) void k_lookup_split(const float *__restrict__ Q, const float *__restrict__ cent,
+                                                      const float *__restrict__ invn, long n, long K, int d, int slices, int qtiles,
+                                                      u64 *keys, u64 *board, const int *__restrict__ many) {
+    constexpr int G = 6;  // steps of eight elements whose fragments are under way together
+    __shared__ float red[4][16][64];
+    __shared__ u64 best_s[4][32];
+    const int t = threadIdx.x, lane = t & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (board != nullptr && blockIdx.x == 0 && t < SISO_FOLD_BOARD) board[t] = 0;  // (see k_lookup_tile)
+    const long id = xcd_run((long)qtiles * slices);
+    if (id < 0) return;
+    const long q0 = id % qtiles * 32, c0 = id / qtiles * 32;
+    if (many != nullptr && q0 >= *many) return;
+    const long cr = c0 + (lane & 31), qr = q0 + (lane & 31);
+    const float *a_row = cent + (size_t)(cr < K ? cr : K - 1) * d, *b_row = Q + (size_t)(qr < n ? qr : n - 1) * d;
+    const int steps = (d + 31) / 32;  // of every wave; wave w has the elements from 8 * steps * w on
+    const int k0 = 8 * steps * wave + 4 * h;
+    const float4 w4 = *(const float4 *)(invn + c0 + 8 * wave + 4 * h);  // (NaN behind the live rows: those never win)
+    u32x4_t a[2][G], b[2][G];
+    auto load = [&](int buf_, int first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int buf = 0; buf < 2; ++buf)
+            if (buf == buf_) {
+#pragma unroll
+                for (int s = 0; s < G; ++s) {
+                    const int k = first + s < steps ? k0 + 8 * (first + s) : d;  // (from d on: zeros, see zero_tail)
+                    a[buf][s] = load_chunk<W>(a_row, k, d);
+                    b[buf][s] = load_chunk<W>(b_row, k, d);
+                }
+            }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    auto multiply = [&](int buf_, int first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int buf = 0; buf < 2; ++buf)
+            if (buf == buf_) {
+#pragma unroll
+                for (int s = 0; s < G; ++s) {
+                    const int k = first + s < steps ? k0 + 8 * (first + s) : d;
+                    acc = product(zero_tail<W, float>(a[buf][s], k, d), zero_tail<W, float>(b[buf][s], k, d), acc, 0.f);
+                }
+            }
+    };
+    load(0, 0);
+    load(1, G);
+    for (int first = 0; first < steps; first += 2 * G) {
+        multiply(0, first);
+        if (first + 2 * G < steps) load(0, first + 2 * G);
+        if (first + G < steps) multiply(1, first + G);
+        if (first + 3 * G < steps) load(1, first + 3 * G);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave][e][lane] = acc[e];
+    __syncthreads();
+    // wave w sums registers 4 w .. 4 w + 3: rows c0 + 8 w + 4 h + e of column lane % 32
+    const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+    float best = -INFINITY;
+    int at = -1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int r = 4 * wave + e;
+        const float v = ((red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane])) * w[e];
+        if (v > best) {  // rows ascend: the lowest index keeps a tie
+            best = v;
+            at = (int)(c0 + 8 * wave + 4 * h + e);
+        }
+    }
+    u64 key = at < 0 ? 0ull : pack_key(best, (unsigned)at);
+    const u64 other = __shfl_xor(key, 32);
+    key = other > key ? other : key;
+    if (h == 0) best_s[wave][lane] = key;
+    __syncthreads();
+    if (t < 32 && q0 + t < n) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) key = best_s[x][t] > key ? best_s[x][t] : key;
+        keys[(size_t)(q0 + t) * slices + id / qtiles] = key;
+    }
+}
+
 // Pairs (i, j), i < j, of rows whose cosine exceeds the threshold: one pair of tiles per workgroup, upper triangle
 // only; the rows j are A, the rows i are B (a lane holds one i and 16 rows j of every block).  A launch takes the `pairs`
 // pairs of tiles from number `first` on.
@@ -362,16 +449,28 @@ int row_alignment(const void *a, const void *b, int d) {
 }
 
 struct TilePlan {
-    int cfg;  // 0 = TileFew, 1 = TileSmall, 2 = TileLarge
+    int cfg;  // 0 = TileFew, 1 = TileSmall, 2 = TileLarge, 3 = k_lookup_split
     int tiles_per_slice, slices, qtiles;
 };
 
-TilePlan tile_plan(const siso_cache *c, long n) {
+TilePlan tile_plan(const siso_cache *c, long n, bool groups) {
     TilePlan p;
     auto tiles = [](long rows, int per) { return (rows + per - 1) / per; };
     // the large tile needs at least two of them per compute unit to be worth its fewer reads
     // (few queries: up to 64 in bf16, see TileCfg, and in codes, where a second tile of them finds the rows in L2)
     p.cfg = n <= (c->dtype == SISO_F32 ? 32 : 64) ? 0 : tiles(c->count, 128) * tiles(n, 128) >= 512 ? 2 : 1;
+    // One workgroup of k_lookup_split for every compute unit, or two of long rows; beyond that the larger tiles read less.  Lookup
+    // alone, 64 x 64 tiles / split, us: 1,024 rows x 256 queries x 384 14.8 / 11.3, 4,000 x 64 x 768 23.6 / 14.9, 300 x 300 x
+    // 2,048 52.0 / 23.9; 504 workgroups: 2,000 x 256 x 768 24.0 / 20.8, 4,000 x 128 x 128 9.0 / 12.4; 1,000 of them: 4,000 x
+    // 256 x 768 25.1 / 33.0, 16,000 x 64 x 384 15.1 / 20.7.
+    const long split = tiles(c->count, 32) * tiles(n, 32);
+    if (p.cfg == 1 && c->dtype == SISO_F32 && !groups && split <= (c->dim >= 512 ? 512 : 256)) {
+        p.cfg = 3;
+        p.tiles_per_slice = 1;
+        p.slices = (int)tiles(c->count, 32);
+        p.qtiles = (int)tiles(n, 32);
+        return p;
+    }
     const int bc = p.cfg == 1 ? 64 : 128, bq = p.cfg == 0 ? 32 : p.cfg == 1 ? 64 : 128;
     const long resident = p.cfg == 2 ? 512 : 1024;  // workgroups the chip holds at a time
     const long ct = tiles(c->count, bc), qt = tiles(n, bq);
@@ -416,9 +515,22 @@ int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p,
     return siso_check_hip(c, hipGetLastError(), "k_lookup_tile");
 }
 
+template <int W>
+int split_launch(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, const int *many) {
+    hipLaunchKernelGGL(k_lookup_split<W>, dim3(xcd_grid((long)p.qtiles * p.slices)), dim3(256), 0, c->stream, (const float *)queries,
+                       (const float *)c->cent, c->invn, n, c->count, c->dim, p.slices, p.qtiles, keys, c->board_to_clear, many);
+    c->board_to_clear = nullptr;  // taken
+    return siso_check_hip(c, hipGetLastError(), "k_lookup_split");
+}
+
 template <typename T, bool GROUPS>
 int lookup_launch_t(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng,
                     const int *many = nullptr) {
+    if (p.cfg == 3) switch (row_alignment<T>(queries, c->cent, c->dim)) {
+            case 16: return split_launch<16>(c, queries, n, p, keys, many);
+            case 8: return split_launch<8>(c, queries, n, p, keys, many);
+            default: return split_launch<4>(c, queries, n, p, keys, many);
+        }
     switch (row_alignment<T>(queries, c->cent, c->dim)) {
         case 16: return lookup_launch<T, 16, GROUPS>(c, queries, n, p, keys, groups, ng, many);
         case 8: return lookup_launch<T, 8, GROUPS>(c, queries, n, p, keys, groups, ng, many);
@@ -476,17 +588,17 @@ int siso_tile_preferred(const siso_cache *c, long n) {
     return c->dtype != SISO_F32 && c->opt_mfma_config == 0 && tiles < limit;
 }
 
-int siso_tile_slices(const siso_cache *c, long n) { return c->count < 1 || n < 1 ? 1 : tile_plan(c, n).slices; }
+int siso_tile_slices(const siso_cache *c, long n) { return c->count < 1 || n < 1 ? 1 : tile_plan(c, n, false).slices; }
 
 // No more keys than this, for n queries and any number of rows up to the capacity (the slices are not monotone in it): the
 // slices of a query tile are at most 4,096 workgroups' worth (tile_plan), and no more than there are tiles.
 long siso_tile_keys_bound(const siso_cache *c, long n) {
-    const long all = (c->capacity + 63) / 64, most = 4096 / ((n + 127) / 128) + 1;
+    const long all = (c->capacity + 31) / 32, most = 4096 / ((n + 127) / 128) + 1;
     return n * (all < most ? all : most);
 }
 
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, const int *many) {
-    const TilePlan p = tile_plan(c, n);
+    const TilePlan p = tile_plan(c, n, false);
     if (p.slices != slices) return siso_fail(c, SISO_EINVAL, "tiled lookup: plan mismatch");
     if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, false>(c, queries, n, p, keys, nullptr, 0, nullptr);  // (whole slabs)
     return c->dtype == SISO_F32 ? lookup_launch_t<float, false>(c, queries, n, p, keys, nullptr, 0, many)
@@ -494,7 +606,7 @@ int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64
 }
 
 int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng) {
-    const TilePlan p = tile_plan(c, n);
+    const TilePlan p = tile_plan(c, n, true);
     if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, true>(c, queries, n, p, nullptr, groups, ng, nullptr);
     return c->dtype == SISO_F32 ? lookup_launch_t<float, true>(c, queries, n, p, nullptr, groups, ng)
                                 : lookup_launch_t<bf16_t, true>(c, queries, n, p, nullptr, groups, ng);
