@@ -133,7 +133,8 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int qt, s, ct_begin, ct_end;
     if (!pipe_map_block<BC>(K, tiles_per_slice, slices, nqt, qb, qt, s, ct_begin, ct_end)) return;
     const long q0 = (long)qt * BQ;
-    if (many != nullptr && q0 >= *many) return;
+    if constexpr (BQ == 256)  // (what a screened lookup leaves over: batches of more than 128)
+        if (many != nullptr && q0 >= *many) return;
     const int nk = d / BK;
     const int T = (ct_end - ct_begin) * nk;  // slabs this workgroup walks through
     if (T <= 0) return;

@@ -265,35 +265,40 @@ __device__ __forceinline__ unsigned other_half(unsigned v) {
     return (threadIdx.x & 32) ? r[0] : r[1];
 }
 
-// The tile pairs of a pair search (see k_pairs_stream): the sequence that one workgroup walks through.
+// The tile pairs of a pair search (see k_pairs_stream): the sequence that one workgroup walks through.  In a round an XCD has
+// one group of sb row tiles; the workgroup has one row tile s of them and every qb-th column tile up to it.
 struct PairItems {
-    int xcd, i, qb, sb, nqb, groups, tiles, units, u;
+    int xcd, iq, is, qb, sb, groups, tiles, rounds, round, b, b_end, s;
     __device__ __forceinline__ void init(int tiles_, int qb_) {
         xcd = blockIdx.x & 7;
-        i = (blockIdx.x >> 3) & 31;
+        const int i = (blockIdx.x >> 3) & 31;
         tiles = tiles_;
         qb = qb_;
         sb = 32 / qb;
-        nqb = (tiles + qb - 1) / qb;
+        iq = i % qb;
+        is = i / qb;
         groups = (tiles + sb - 1) / sb;
-        units = ((groups + 7) / 8) * nqb;
-        u = 0;
+        rounds = (groups + 7) / 8;
+        round = -1;
+        b = b_end = s = 0;
     }
     // next tile pair (column tile qt <= row tile ct) of this workgroup; false = none left
     __device__ __forceinline__ bool next(int &qt, int &ct) {
-        while (u < units) {
-            const int round = u / nqb, b = u % nqb;
-            ++u;
+        while (b >= b_end) {
+            if (++round >= rounds) {
+                round = rounds;
+                return false;
+            }
             // (the groups from the bottom of the triangle upwards: the round that not every XCD takes part in is
             // then the one with the least work - 196 row tiles: 28 % more than its share on one XCD otherwise)
             const int gi = round * 8 + ((round & 1) ? 7 - xcd : xcd);
-            const int g = groups - 1 - gi;
-            const int q = b * qb + i % qb, s = g * sb + i / qb;
-            if (gi >= groups || q >= tiles || s >= tiles || s < q) continue;
-            qt = q;
-            ct = s;
-            return true;
+            s = (groups - 1 - gi) * sb + is;
+            b = 0;
+            b_end = gi >= groups || s >= tiles || s < iq ? 0 : (s - iq) / qb + 1;
         }
-        return false;
+        qt = b * qb + iq;
+        ct = s;
+        ++b;
+        return true;
     }
 };

@@ -834,8 +834,8 @@ struct PairSrc {
         take();
     }
 };
-#define SCREEN_PAIR_STAGE 2048  // pairs a workgroup collects in LDS
-#define SCREEN_PAIR_LDS (ByteCfg::NSTAGE * ByteCfg::STAGE + 4 * 64 * 4 + SCREEN_PAIR_STAGE * 8 + 16)
+#define SCREEN_PAIR_STAGE 256  // pairs a wave collects in LDS
+#define SCREEN_PAIR_LDS (ByteCfg::NSTAGE * ByteCfg::STAGE + 4 * 64 * 4 + 8 * SCREEN_PAIR_STAGE * 8)
 static_assert(SCREEN_PAIR_LDS <= 160 * 1024, "fits in LDS");
 
 __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_screen_pairs(
@@ -845,9 +845,6 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
     constexpr int WC = Cfg::WC, WQ = Cfg::WQ, BC = Cfg::BC;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     float *meta_s = (float *)(smem + Cfg::NSTAGE * Cfg::STAGE);
-    int *stage = (int *)(meta_s + 4 * 64);
-    int *staged = stage + 2 * SCREEN_PAIR_STAGE;
-    u64 *flush_slot = (u64 *)(staged + 2);
     const int tiles = (int)((K + BC - 1) / BC);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wc = wave % Cfg::NWC, wq = wave / Cfg::NWC, h = lane >> 5, l32 = lane & 31;
@@ -867,7 +864,22 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
     while (done.next(qt, ct)) ++pairs;
     done.init(tiles, qb);
     done.next(qt, ct);
-    if (threadIdx.x == 0) *staged = 0;  // (the pipeline's first barrier is before the first use)
+    // the pairs this wave has found, handed over when they may not hold those of another instruction (a wave's own: nothing to
+    // wait for, which a buffer of the workgroup would at the end of every tile)
+    int2 *stage = (int2 *)(meta_s + 4 * 64) + wave * SCREEN_PAIR_STAGE;
+    int mine = 0;
+    auto flush = [&]() __attribute__((always_inline)) {
+        u64 base = 0;
+        if (lane == 0 && mine > 0) base = atomicAdd(counter, (u64)mine);
+        base = __shfl(base, 0);
+        for (int p = lane; p < mine; p += 64)
+            if (base + (u64)p < (u64)cap) {  // (the caller's array: aligned to an int)
+                const int2 e = stage[p];
+                out_pairs[2 * (base + p)] = e.x;
+                out_pairs[2 * (base + p) + 1] = e.y;
+            }
+        mine = 0;
+    };
     byte_stream(smem, dp, pairs, src, [&](const i32x16(&acc)[WC][WQ]) __attribute__((always_inline)) {
         const float4 *ma = (const float4 *)(meta_s + (seq & 1) * 128) + wc * WC;
         const float4 *mb = (const float4 *)(meta_s + (seq & 1) * 128 + 64) + wq * WQ;
@@ -891,30 +903,36 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                 constexpr int B = decltype(ib)::value;
                 if (__ballot(up[A][B] > threshold) == 0) return;
                 const float scale = a[A].x * b[B].x, err = fmaf(1.f + a[A].y, b[B].y, a[A].y) + SCREEN_SLACK;
-                const long icol = (long)qt * BC + (wq * WQ + B) * 32 + l32;
-                const long jrow0 = (long)ct * BC + (wc * WC + A) * 32 + 4 * h;  // register I holds row jrow0 + 8 * (I / 4) + I % 4
-                unsigned sure = 0, open = 0;
+                // as an integer (see k_screen_lookup); without a scale the products are zeros, below any threshold but for a block
+                // that is never ruled out
+                const int least = scale > 0.f ? (int)floorf((threshold - err) / scale) : err > threshold ? 0 : 1;
+                const int icol = qt * BC + (wq * WQ + B) * 32 + l32;
+                const int jrow0 = ct * BC + (wc * WC + A) * 32 + 4 * h;  // register I holds row jrow0 + 8 * (I / 4) + I % 4
                 static_for<0, 16>([&](auto ii) __attribute__((always_inline)) {
                     constexpr int I = decltype(ii)::value;
+                    const bool near = acc[A][B][I] >= least;
+                    if (__ballot(near) == 0) return;
+                    const int j = jrow0 + 8 * (I >> 2) + (I & 3);
                     const float p = (float)acc[A][B][I] * scale;
-                    const long j = jrow0 + 8 * (I >> 2) + (I & 3);
-                    if (icol < j && j < K && p + err > threshold) {
-                        if (p - err > threshold) sure |= 1u << I;
-                        else open |= 1u << I;
+                    const bool sure = near && icol < j && j < K && p - err > threshold, open = near && icol < j && j < K && !sure;
+                    const u64 yes = __ballot(sure), maybe_so = __ballot(open);
+                    auto before = [&](u64 mask) { return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u)); };
+                    if (mine > SCREEN_PAIR_STAGE - 64) flush();
+                    if (sure) stage[mine + before(yes)] = make_int2(icol, j);
+                    mine += __popcll(yes);
+                    if (maybe_so != 0) {
+                        u64 base = 0;
+                        if (lane == 0) base = atomicAdd(maybe_count, (u64)__popcll(maybe_so));
+                        base = __shfl(base, 0) + (u64)before(maybe_so);
+                        if (open && base < (u64)SCREEN_MAYBE) ((int2 *)maybe)[base] = make_int2(icol, j);
                     }
                 });
-                auto row_of = [&](int I) { return (int)(jrow0 + 8 * (I >> 2) + (I & 3)); };
-                emit_pairs_staged(sure, (int)icol, row_of, stage, staged, SCREEN_PAIR_STAGE, out_pairs, cap, counter);
-                if (__ballot(open != 0) != 0) emit_pairs(open, (int)icol, row_of, maybe, SCREEN_MAYBE, maybe_count);
             });
         });
         ++seq;
         done.next(qt, ct);
-        // (own LDS traffic done, then the barrier by hand: the compiler's would also wait for the loads in flight)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (*staged > SCREEN_PAIR_STAGE / 2) flush_staged_pairs(stage, staged, SCREEN_PAIR_STAGE, flush_slot, out_pairs, cap, counter);
     });
-    flush_staged_pairs(stage, staged, SCREEN_PAIR_STAGE, flush_slot, out_pairs, cap, counter);
+    flush();
 }
 
 __global__ void k_screen_clear(u64 *maybe_count) { *maybe_count = 0; }
