@@ -26,6 +26,11 @@
 
 #include "siso_internal.h"
 
+struct RefreshCandidate {  // an earlier repository row above the threshold
+    int row;
+    float cosine;
+};
+
 namespace {
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
@@ -162,39 +167,66 @@ struct DeviceBuf {  // frees on every way out
     }
 };
 
-struct Candidate {  // an earlier repository row above the threshold
-    int row;
-    float cosine;
+}  // namespace
+
+// The lists of plan_refresh, kept by a cache from one refresh to the next: taken anew they are megabytes of fresh pages each
+// time, and touching those for the first time took longer than the bookkeeping (65,536 rows: 340 us between the last
+// kernel of the searches and the gather, 260 with kept lists).
+struct RefreshLists {
+    std::vector<long> first, fill, place;
+    std::vector<RefreshCandidate> cand;
+    std::vector<int> src, keep;      // keep = source of every surviving row in order (cached row, or K0 + repository row)
+    std::vector<float> loc, loc2;    // cluster_size before; of the survivors, after the decay
+    std::vector<unsigned> acc, with;
+    std::vector<u64> key, same;
+    size_t bytes() const {
+        return (first.capacity() + fill.capacity() + place.capacity()) * sizeof(long) + cand.capacity() * sizeof(RefreshCandidate) +
+               (src.capacity() + keep.capacity() + loc.capacity() + loc2.capacity() + acc.capacity() + with.capacity()) * 4 +
+               (key.capacity() + same.capacity()) * sizeof(u64);
+    }
 };
+
+void siso_refresh_release(siso_cache *c) {
+    delete c->refresh_lists;
+    c->refresh_lists = nullptr;
+}
+
+namespace {
 
 // The decisions of Algorithm 1 from what the kernels found.  Per repository row i: h_idx / h_sim = its closest
 // cached centroid and the cosine; h_pairs / h_cos = the pairs (a, b), a < b, of repository rows above the
-// threshold with their cosines.  loc / acc = cluster_size and access_count of the cached centroids (they grow
-// by the rows that join).  keep = source of every surviving row in order (cached row, or K0 + repository row),
-// loc2 = its cluster_size after the decay.
+// threshold with their cosines.  h_loc / h_acc = cluster_size and access_count of the cached centroids (they grow
+// by the rows that join).  The outcome is l.keep and l.loc2.
 void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const float *h_rsize, const int *h_pairs,
-                  const float *h_cos, long n_pairs, std::vector<float> loc, std::vector<unsigned> acc, float theta_c,
-                  long max_centroids, std::vector<int> &keep, std::vector<float> &loc2, long &merged, long &added,
-                  long &evicted) {
-    // ---- the chain of the merge step, in the order of the repository ---------------------
-    // candidates of row b: the earlier rows a < b with cosine above the threshold (pairs come as a < b)
-    std::vector<long> first((size_t)r + 1, 0);
-    for (long p = 0; p < n_pairs; ++p) first[(size_t)h_pairs[2 * p + 1] + 1] += 1;
-    for (long i = 0; i < r; ++i) first[(size_t)i + 1] += first[(size_t)i];
-    std::vector<Candidate> cand((size_t)n_pairs);
-    {
-        std::vector<long> fill(first.begin(), first.end() - 1);
-        for (long p = 0; p < n_pairs; ++p) {
-            const int b = h_pairs[2 * p + 1];
-            cand[(size_t)fill[(size_t)b]++] = Candidate{h_pairs[2 * p], h_cos[(size_t)p]};
-        }
-    }
-    std::vector<long> place((size_t)r, -1);  // position in C_new of a repository row that joined
-    std::vector<int> src((size_t)K0);        // C_new: source of every row (cached row, or K0 + repository row)
-    src.reserve((size_t)(K0 + r));
-    for (long j = 0; j < K0; ++j) src[(size_t)j] = (int)j;
+                  const float *h_cos, long n_pairs, const float *h_loc, const unsigned *h_acc, float theta_c,
+                  long max_centroids, RefreshLists &l, long &merged, long &added, long &evicted) {
+    std::vector<float> &loc = l.loc, &loc2 = l.loc2;
+    std::vector<unsigned> &acc = l.acc;
+    std::vector<int> &keep = l.keep, &src = l.src;
+    std::vector<long> &first = l.first, &place = l.place;
+    std::vector<RefreshCandidate> &cand = l.cand;
     loc.reserve((size_t)(K0 + r));
     acc.reserve((size_t)(K0 + r));
+    src.reserve((size_t)(K0 + r));
+    loc.assign(h_loc, h_loc + K0);
+    acc.assign(h_acc, h_acc + K0);
+    // ---- the chain of the merge step, in the order of the repository ---------------------
+    // candidates of row b: the earlier rows a < b with cosine above the threshold (pairs come as a < b)
+    first.assign((size_t)r + 1, 0);
+    for (long p = 0; p < n_pairs; ++p) first[(size_t)h_pairs[2 * p + 1] + 1] += 1;
+    for (long i = 0; i < r; ++i) first[(size_t)i + 1] += first[(size_t)i];
+    cand.resize((size_t)n_pairs);
+    {
+        std::vector<long> &fill = l.fill;
+        fill.assign(first.begin(), first.end() - 1);
+        for (long p = 0; p < n_pairs; ++p) {
+            const int b = h_pairs[2 * p + 1];
+            cand[(size_t)fill[(size_t)b]++] = RefreshCandidate{h_pairs[2 * p], h_cos[(size_t)p]};
+        }
+    }
+    place.assign((size_t)r, -1);  // position in C_new of a repository row that joined
+    src.resize((size_t)K0);       // C_new: source of every row (cached row, or K0 + repository row)
+    for (long j = 0; j < K0; ++j) src[(size_t)j] = (int)j;
     merged = added = 0;
     for (long i = 0; i < r; ++i) {
         long best = h_idx[(size_t)i];
@@ -239,8 +271,10 @@ void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const f
     long at_last = 0;  // and of those with this one so many, the first ones
     if (evicted > 0) {
         // the evicted-th smallest number: its upper 16 bits from a count of them, the rest among the rows that share those
-        std::vector<u64> key((size_t)n_new);
-        std::vector<long> with((size_t)1 << 16, 0);
+        std::vector<u64> &key = l.key, &same = l.same;
+        std::vector<unsigned> &with = l.with;
+        key.resize((size_t)n_new);
+        with.assign((size_t)1 << 16, 0);
         for (long j = 0; j < n_new; ++j) {
             key[(size_t)j] = key_of(j);
             with[(size_t)(key[(size_t)j] >> 48)] += 1;
@@ -248,7 +282,7 @@ void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const f
         long below = 0;
         size_t top = 0;
         while (below + with[top] < evicted) below += with[top++];
-        std::vector<u64> same;
+        same.clear();
         same.reserve((size_t)with[top]);
         for (long j = 0; j < n_new; ++j)
             if ((key[(size_t)j] >> 48) == top) same.push_back(key[(size_t)j]);
@@ -267,7 +301,7 @@ void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const f
         }
         return;
     }
-    keep = std::move(src);
+    keep.assign(src.begin(), src.end());
     loc2.resize((size_t)n_new);
     for (long j = 0; j < n_new; ++j) loc2[(size_t)j] = loc[(size_t)j] / 1.1f;
 }
@@ -407,11 +441,12 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
     }
 
     // ---- merge step and filtering step: bookkeeping on the host ----------------------------------
-    std::vector<int> keep;
-    std::vector<float> loc2;
     long merged = 0, added = 0, evicted = 0;
-    plan_refresh(K0, r, h_idx, h_sim, h_rsize, h_pairs, h_cos, n_pairs, std::vector<float>(h_loc, h_loc + K0),
-                 std::vector<unsigned>(h_acc, h_acc + K0), theta_c, max_centroids, keep, loc2, merged, added, evicted);
+    if (c->refresh_lists == nullptr) c->refresh_lists = new RefreshLists;
+    plan_refresh(K0, r, h_idx, h_sim, h_rsize, h_pairs, h_cos, n_pairs, h_loc, h_acc, theta_c, max_centroids, *c->refresh_lists,
+                 merged, added, evicted);
+    const std::vector<int> &keep = c->refresh_lists->keep;
+    const std::vector<float> &loc2 = c->refresh_lists->loc2;
     const long live = (long)keep.size();
 
     // ---- update step: gather the new set, then it becomes the cache ---------------------------
@@ -456,6 +491,7 @@ extern "C" int siso_refresh(siso_cache *c, const void *repo, const float *repo_s
     } catch (const std::bad_alloc &) {  // the host lists; they are all built before the update step
         rc = siso_fail(c, SISO_ENOMEM, "siso_refresh: host memory for the bookkeeping");
     }
+    if (c->refresh_lists && c->refresh_lists->bytes() > (size_t)SISO_PINNED_KEEP) siso_refresh_release(c);
     siso_arena_done(c);
     return rc;
 }
@@ -474,12 +510,12 @@ extern "C" long siso_refresh_plan(long k0, const float *cluster_size, const unsi
     for (long i = 0; i < r; ++i)
         if (best_idx[i] >= k0 || !(repo_size[i] > 0.f)) return SISO_EINVAL;
     try {
-        std::vector<float> loc(cluster_size, cluster_size + k0), loc2;
-        std::vector<unsigned> acc(access_count, access_count + k0);
-        std::vector<int> keep;
+        RefreshLists lists;
+        const std::vector<int> &keep = lists.keep;
+        const std::vector<float> &loc2 = lists.loc2;
         long merged = 0, added = 0, evicted = 0;
-        plan_refresh(k0, r, best_idx, best_sim, repo_size, pairs, pair_cosine, n_pairs, loc, acc, theta_c, max_centroids,
-                     keep, loc2, merged, added, evicted);
+        plan_refresh(k0, r, best_idx, best_sim, repo_size, pairs, pair_cosine, n_pairs, cluster_size, access_count, theta_c,
+                     max_centroids, lists, merged, added, evicted);
         for (size_t j = 0; j < keep.size(); ++j) {
             out_source[j] = keep[j];
             out_cluster_size[j] = loc2[j];

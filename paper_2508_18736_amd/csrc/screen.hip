@@ -1194,16 +1194,16 @@ int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_row
                                                         access, owner, members, timed, plain);
 }
 
-// Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 56, 2,000 x 768
-// 83 -> 61, 4,000 x 256 129 -> 65, 8,000 x 768 490 -> 101; bf16 8,000 x 768 109 -> 101, 16,000 x 256 107 -> 113, 16,000 x 768
-// 235 -> 164, 50,000 x 768 1,658 -> 940.  Below a threshold of 0.25 rows of zeros and the many pairs of unrelated rows would come
+// Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 52, 2,000 x 768
+// 82 -> 59, 4,000 x 256 130 -> 60, 8,000 x 768 500 -> 97; bf16 8,000 x 256 62 -> 71, 6,000 x 768 94 -> 86, 16,000 x 256 101 -> 99, 16,000 x 768
+// 229 -> 151, 50,000 x 768 1,666 -> 886.  Below a threshold of 0.25 rows of zeros and the many pairs of unrelated rows would come
 // near it.
 int siso_screen_pairs_wanted(const siso_cache *c, long count, float threshold) {
     if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->opt_merge_config != 0 || count < 2 || c->dim > SISO_SCREEN_DIM) return 0;
     if (!(threshold >= 0.25f)) return 0;
     if (c->opt_screen == 1) return 1;
     const double work = (double)count * (double)count * c->dim;
-    return c->dim >= 128 && work >= (c->dtype == SISO_F32 ? 1.5e9 : 8e10);
+    return c->dim >= 128 && work >= (c->dtype == SISO_F32 ? 1.5e9 : 2.5e10);
 }
 
 int siso_screen_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,

@@ -1221,6 +1221,7 @@ extern "C" void siso_destroy(siso_cache *c) {
     if (c->screen) (void)hipFree(c->screen);
     if (c->screen_pairs) (void)hipFree(c->screen_pairs);
     if (c->pinned) (void)hipHostFree(c->pinned);
+    siso_refresh_release(c);
     if (c->counters) (void)hipFree(c->counters);
     if (c->host_pin) (void)hipHostFree(c->host_pin);
     if (c->prof_ev) {

@@ -74,6 +74,8 @@ struct siso_cache {
     char *pinned;
     size_t pinned_cap;
 
+    struct RefreshLists *refresh_lists;  // host lists of siso_refresh, kept (refresh.hip)
+
     u64 *static_keys;  // this device's copy of the library's static key array (siso_lookup_static)
 
     u64 *counters;  // device: [0] bad update indices, [1] merge pair count, [2] scratch, [3] scratch; behind them the
@@ -585,6 +587,7 @@ int siso_ensure_keys(siso_cache *c, long need);  // room for `need` phase-1 keys
 #define SISO_PINNED_KEEP (64l << 20)
 int siso_arena(siso_cache *c, size_t device_bytes, size_t host_bytes);
 void siso_arena_done(siso_cache *c);
+void siso_refresh_release(siso_cache *c);
 struct Carver {  // hands out aligned pieces; with a null base it only adds up
     char *base;
     size_t used = 0;
