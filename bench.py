@@ -26,6 +26,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0  # dense bf16 MFMA, MI355X
 PEAK_FP8_TFLOPS = 5000.0   # dense fp8 MFMA
+PEAK_INT8_TFLOPS = 5000.0  # dense int8 MFMA: large bf16 lookups and pair searches rule most rows out by products of bytes
 PEAK_HBM_GBS = 8000.0      # HBM3E
 
 
@@ -199,6 +200,8 @@ def main():
         dt = time.perf_counter() - t0
         kern_ms, launches = cache.profile_read()
         flop = float(K) * K * d  # upper triangle only
+        pair_screened = cache.screened(0)  # (products of bytes, near the threshold formed anew in single precision)
+        pair_peak = PEAK_INT8_TFLOPS if pair_screened else PEAK_BF16_TFLOPS
         avg_s = kern_ms / 1e3 / max(launches, 1)
         cache.set_option("second_set", 1)  # the one-time allocation of the arrays the survivors are gathered into
         torch.cuda.synchronize()
@@ -219,8 +222,8 @@ def main():
                                "merge_apply_ms": apply_s * 1e3,
                                "cluster": {"vectors": K, "theta_c": 0.86, "min_size": 2, "clusters": clusters,
                                            "pairs": cluster_pairs, "ms": cluster_s * 1e3}},
-                    "roofline": {"bound": "mfma", "achieved": flop / avg_s / 1e12, "peak": PEAK_BF16_TFLOPS,
-                                 "unit": "TFLOP/s", "frac": flop / avg_s / 1e12 / PEAK_BF16_TFLOPS,
+                    "roofline": {"bound": "mfma", "achieved": flop / avg_s / 1e12, "peak": pair_peak,
+                                 "unit": "TFLOP/s", "frac": flop / avg_s / 1e12 / pair_peak, "screened": pair_screened,
                                  "traffic": measured_traffic(name), "kernel_ms": avg_s * 1e3}})
         add_measured_peak(siso, out["roofline"])
         if not args.no_cpu_baseline:
@@ -308,7 +311,8 @@ def main():
             c_.set_stream(torch.cuda.current_stream())
     flop = 2.0 * nb * K * d
     eb = 1.0 if fp8 else 2.0  # bytes per stored element
-    peak_tflops = PEAK_FP8_TFLOPS if fp8 else PEAK_BF16_TFLOPS
+    screened = cache.screened(nb)  # (products of bytes; the rows that can be the closest formed anew in single precision)
+    peak_tflops = PEAK_FP8_TFLOPS if fp8 else PEAK_INT8_TFLOPS if screened else PEAK_BF16_TFLOPS
     if streaming:
         bytes_alg = K * d * eb + nb * d * eb + K * 4.0  # centroids + queries + inverse lengths, read once
         roof = {"bound": "hbm", "achieved": bytes_alg / avg_s / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
@@ -324,7 +328,7 @@ def main():
         roof = {"bound": "mfma", "achieved": flop / avg_s / 1e12, "peak": peak_tflops, "unit": "TFLOP/s",
                 "frac": flop / avg_s / 1e12 / peak_tflops, "traffic": measured_traffic(name + ("_fp8" if fp8 else "")),
                 "algorithmic_bytes": K * d * eb + nb * d * eb + K * 4.0, "kernel_ms": avg_s * 1e3,
-                "launches": launches}
+                "launches": launches, "screened": screened}
 
     variants_info = None
     if not args.no_merge and name in ("c2_mid", "c3_large"):

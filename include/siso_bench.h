@@ -54,6 +54,13 @@ int siso_set_lookup_path(siso_cache *c, int path);
 int siso_set_option(siso_cache *c, const char *name, long value);
 
 /*
+ * 1 if a lookup of n queries on the cache as it stands would form most of its products in eight
+ * bits (see siso_lookup; given the room), n = 0: a pair search over its rows at a threshold of 0.25 or
+ * more; 0 if not.  Negative = error code.
+ */
+int siso_screened(const siso_cache *c, long n);
+
+/*
  * Kernel timing for benchmarks.  While enabled (on = N > 0), every N-th
  * siso_lookup / siso_merge brackets its dominant kernel (the similarity kernel,
  * without the finalize kernel) with a pair of HIP events on the cache's stream

@@ -1161,6 +1161,11 @@ int siso_screen_wanted(const siso_cache *c, long n) {
     return c->dim >= 128 && (c->dtype == SISO_F32 ? n > 128 && work >= 8e9 : n >= 768 && work >= 7.5e11);
 }
 
+extern "C" int siso_screened(const siso_cache *c, long n) {
+    if (!c || n < 0) return SISO_EINVAL;
+    return n == 0 ? siso_screen_pairs_wanted(c, c->count, 1.f) : siso_screen_wanted(c, n);
+}
+
 int siso_screen_reserve(siso_cache *c, long rows, long n) {
     return make_room(c, c->screen, c->screen_cap, screen_room(nullptr, c, rows, n).bytes) ? 1 : 0;
 }

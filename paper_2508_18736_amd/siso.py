@@ -55,6 +55,7 @@ SYMBOLS = {
     "siso_profile_read": ([_vp, C.POINTER(C.c_double), C.POINTER(C.c_long)], _it),
     "siso_last_error": ([_vp], C.c_char_p),
     "siso_probe": ([_it, C.POINTER(C.c_double)], _it),
+    "siso_screened": ([_vp, _lg], _it),
     "siso_refresh": ([_vp, _vp, _vp, _lg, _fl, _lg, _vp], _it),
     "siso_cluster": ([_vp, _vp, _lg, _fl, _it, _vp, _vp, _vp], _lg),
     "siso_choose_communities": ([_vp, _lg, _lg, _it, _vp], _lg),
@@ -233,6 +234,10 @@ class SisoCache:
 
     def set_option(self, name: str, value: int) -> None:
         self._check(_lib.siso_set_option(self._h, name.encode(), int(value)))
+
+    def screened(self, n: int) -> bool:
+        """Would a lookup of n queries (0: a pair search) form most of its products in eight bits?"""
+        return bool(self._check(_lib.siso_screened(self._h, n)))
 
     def reserve(self, n: int) -> None:
         """Room for lookups and updates of up to ``n`` queries, so that those calls never allocate."""
