@@ -173,9 +173,10 @@ int siso_lookup_topk(siso_cache *c, const void *queries, long n, int k, int *out
 /*
  * siso_lookup for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * same kernels (a large lookup uses eight bits only where siso_reserve or an earlier
- * call has left the room) and bit-identical results (but for which of two rows is named whose
- * similarities are within the rounding of each other), but the keys of the first phase go to a
+ * similarities that are the same bits and the same rows (but for which of two is named
+ * whose similarities are within the rounding of each other: every product is formed in
+ * the cache's own type here, also where a large siso_lookup passes over rows by their
+ * leading eight bits), but the keys of the first phase go to a
  * key array that is part of the library's image (1,048,576 keys = 8 MiB, held by
  * every GPU the library runs on until the process ends) instead of the cache's own
  * workspace: the call never allocates, frees or synchronises, and records no

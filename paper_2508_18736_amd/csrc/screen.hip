@@ -6,7 +6,8 @@
 // twice the rate of bf16 from half the bytes, and exactly: sums of integers have no rounding.  What the bytes leave out
 // is known: for unit vectors u, w and what their bytes stand for, u', w',
 //     | u.w - u'.w' |  <=  |u - u'| |w| + |u'| |w - w'|  <=  e_u + (1 + e_u) e_w,     e = the length of the difference,
-// and both lengths are measured when the bytes are written (0.0073 for Gaussian directions of 768 elements).  A row is
+// and both lengths are measured when the bytes are written (Gaussian directions of 768 elements: 0.0077 for a query, 0.0099 for rows
+// in blocks of 32).  A row is
 // passed over only if the upper end of its cosine lies below the lower end of some other row's: what is left, some tens of
 // rows a query, is multiplied again from the stored rows in single precision, as the end of a lookup does, and the
 // largest of those cosines (lowest index among equal ones) is the result.  No result is made of bytes.
@@ -18,6 +19,8 @@
 // Rows are grouped by 32 (the rows of one MFMA): one scale and one error for each.  One outlier costs its 32 rows some
 // precision and nobody else; and the end of a tile works on integers: a maximum of 16, one conversion, three operations
 // in floating point for 16 products, against some two for each where every row has a weight.
+#include <new>
+
 #include "mfma_pipe.h"
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -1017,18 +1020,26 @@ ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
     return r;
 }
 
-// false = there is no room, which no caller needs to fail for
-bool make_room(siso_cache *c, char *&room, size_t &cap, size_t bytes) {
-    if (bytes <= cap) return true;
+bool capturing(const siso_cache *c) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
-    if (status != hipStreamCaptureStatusNone) return false;
+    return status != hipStreamCaptureStatusNone;
+}
+
+// false = there is no room, which no caller needs to fail for.  keep: where the old room goes if it must stay (NULL: it is freed).
+bool make_room(siso_cache *c, char *&room, size_t &cap, size_t bytes, std::vector<char *> *keep) {
+    if (bytes <= cap) return true;
+    if (capturing(c)) return false;
     if (room) {
-        if (hipStreamSynchronize(c->stream) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
+        if (keep) {
+            keep->push_back(room);  // (room for it: siso_screen_lookup)
+        } else {
+            if (hipStreamSynchronize(c->stream) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
+            }
+            (void)hipFree(room);
         }
-        (void)hipFree(room);
         room = nullptr;
         cap = 0;
     }
@@ -1062,7 +1073,7 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *
 
 template <typename T>
 int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
-                  float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, bool timed, ScreenPlain *plain) {
+                  float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain) {
     const ScreenRoom r = screen_room(c->screen, c, c->count, n);
     const int d = c->dim, dp = byte_dim(d);
     const long tiles = up256(c->count) / 256, nqt = up256(n) / 256;
@@ -1092,7 +1103,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const
     // Much work: an eighth of the tiles first, and better bounds from what it has listed, for queries that are near nothing (a
     // bound from 2,000 rows lets some 700 of 131,072 pass, one from 16,000 some 200).
     const long ahead = tiles * nqt >= 32 * 256 ? (tiles / 8 * nqt >= 512 ? tiles / 8 : (512 + nqt - 1) / nqt) : 0;
-    if (timed) siso_prof_begin(c);
+    siso_prof_begin(c);
     for (int part = ahead > 0 ? 0 : 1; part < 2; ++part) {
         const long t0 = part == 0 ? 0 : ahead, row0 = t0 * 256;
         const long rows = part == 0 ? ahead * 256 : c->count - row0;
@@ -1105,7 +1116,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const
             hipLaunchKernelGGL((k_screen_seed<T, true>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.seed,
                                r.cnt, r.list, r.low);
     }
-    if (timed) siso_prof_end(c);
+    siso_prof_end(c);
     hipLaunchKernelGGL(k_screen_pick<T>, fours, block, 0, c->stream, queries, cent, c->invn, n, d, vec, r.low, r.cnt, r.list, r.totals,
                        r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
     hipLaunchKernelGGL(k_screen_score<T>, dim3((unsigned)(n < 4096 ? (n + 1) / 2 : 2048)), block, 0, c->stream, queries, cent, c->invn, d, vec,
@@ -1167,11 +1178,15 @@ extern "C" int siso_screened(const siso_cache *c, long n) {
 }
 
 int siso_screen_reserve(siso_cache *c, long rows, long n) {
-    return make_room(c, c->screen, c->screen_cap, screen_room(nullptr, c, rows, n).bytes) ? 1 : 0;
+    const size_t bytes = screen_room(nullptr, c, rows, n).bytes;
+    if (bytes <= c->screen_cap) return 1;
+    const bool room = make_room(c, c->screen, c->screen_cap, bytes, c->screen_recorded ? c->screen_kept : nullptr);
+    if (c->screen == nullptr || room) c->screen_recorded = 0;
+    return room ? 1 : 0;
 }
 
 int siso_screen_reserve_pairs(siso_cache *c, long rows) {
-    return make_room(c, c->screen_pairs, c->screen_pairs_cap, screen_room(nullptr, c, rows, 0).bytes) ? 1 : 0;
+    return make_room(c, c->screen_pairs, c->screen_pairs_cap, screen_room(nullptr, c, rows, 0).bytes, nullptr) ? 1 : 0;
 }
 
 void siso_screen_done(siso_cache *c) {
@@ -1182,15 +1197,30 @@ void siso_screen_done(siso_cache *c) {
     c->screen_pairs_cap = 0;
 }
 
-int siso_screen_has_room(const siso_cache *c, long n) { return screen_room(nullptr, c, c->count, n).bytes <= c->screen_cap; }
+void siso_screen_release(siso_cache *c) {
+    if (c->screen) (void)hipFree(c->screen);
+    if (c->screen_pairs) (void)hipFree(c->screen_pairs);
+    if (c->screen_kept)
+        for (char *room : *c->screen_kept) (void)hipFree(room);
+    delete c->screen_kept;
+}
 
 int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
-                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, bool timed,
-                       ScreenPlain *plain) {
+                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain) {
+    // A graph that records the launches goes on using the workspace when a larger call has outgrown it.
+    if (!c->screen_recorded && capturing(c)) {
+        try {
+            if (!c->screen_kept) c->screen_kept = new std::vector<char *>;
+            c->screen_kept->reserve(c->screen_kept->size() + 1);
+        } catch (const std::bad_alloc &) {
+            return siso_fail(c, SISO_ENOMEM, "siso_lookup: note of a recorded workspace");
+        }
+        c->screen_recorded = 1;
+    }
     return c->dtype == SISO_F32 ? screen_launch<float>(c, (const float *)queries, n, with_rows, tl, q_base, out_idx, out_sim, out_hit,
-                                                       access, owner, members, timed, plain)
+                                                       access, owner, members, plain)
                                 : screen_launch<bf16_t>(c, (const bf16_t *)queries, n, with_rows, tl, q_base, out_idx, out_sim, out_hit,
-                                                        access, owner, members, timed, plain);
+                                                        access, owner, members, plain);
 }
 
 // Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 52, 2,000 x 768

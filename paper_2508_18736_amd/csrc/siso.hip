@@ -1218,8 +1218,7 @@ extern "C" void siso_destroy(siso_cache *c) {
     if (c->topk_cnt) (void)hipFree(c->topk_cnt);
     if (c->topk_cand) (void)hipFree(c->topk_cand);
     if (c->arena) (void)hipFree(c->arena);
-    if (c->screen) (void)hipFree(c->screen);
-    if (c->screen_pairs) (void)hipFree(c->screen_pairs);
+    siso_screen_release(c);
     if (c->pinned) (void)hipHostFree(c->pinned);
     siso_refresh_release(c);
     if (c->counters) (void)hipFree(c->counters);
@@ -1539,20 +1538,21 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
         members = c->upd_members;
     }
     PlainLookup plain;
-    if (siso_screen_wanted(c, n) && (static_keys ? siso_screen_has_room(c, n) : siso_screen_reserve(c, c->count, n))) {
+    // (not on the static keys: the bytes live in a workspace that other calls share and a larger one moves)
+    if (!static_keys && siso_screen_wanted(c, n) && siso_screen_reserve(c, c->count, n)) {
         // piece by piece: screened, then what that has left over
         const size_t row = (size_t)c->dim * elem_bytes(c->dtype);
-        int rc = plan_plain(c, n < SISO_SCREEN_PIECE ? n : SISO_SCREEN_PIECE, static_keys, static_cap, &plain);
+        int rc = plan_plain(c, n < SISO_SCREEN_PIECE ? n : SISO_SCREEN_PIECE, nullptr, 0, &plain);
         for (long off = 0; off < n && rc == SISO_OK; off += SISO_SCREEN_PIECE) {
             const long part = n - off < SISO_SCREEN_PIECE ? n - off : SISO_SCREEN_PIECE;
             const char *q = (const char *)queries + (size_t)off * row;
             unsigned char *hit = out_hit ? out_hit + (size_t)off * m : nullptr;
             ScreenPlain left;
-            if (off > 0) rc = plan_plain(c, part, static_keys, static_cap, &plain);
+            if (off > 0) rc = plan_plain(c, part, nullptr, 0, &plain);
             if (rc != SISO_OK) break;
             if (owner) c->mark_in_finalize = 2;
             rc = siso_screen_lookup(c, q, part, off == 0, tl, off, out_idx + off, out_sim + off, hit,
-                                    count_index >= 0 ? c->access : nullptr, owner, members, !static_keys, &left);
+                                    count_index >= 0 ? c->access : nullptr, owner, members, &left);
             if (rc == SISO_OK)
                 rc = plain_lookup(c, plain, left.rows, part, tl, off, out_idx + off, out_sim + off, hit, false, nullptr, owner, members, &left);
         }

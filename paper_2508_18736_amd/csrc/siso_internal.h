@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <vector>
 
 #include "siso.h"
 #include "siso_bench.h"
@@ -112,6 +113,8 @@ struct siso_cache {
     // workspaces, so that a pair search does not move what a captured lookup refers to.
     char *screen, *screen_pairs;
     size_t screen_cap, screen_pairs_cap;
+    int screen_recorded;  // a graph holds a screened lookup on `screen`: outgrown, it stays until the cache goes (screen_kept)
+    std::vector<char *> *screen_kept;
 
     // tuning knobs (siso_set_option); 0 = library default
     int opt_screen;  // 1 = screen wherever the kernels can, 2 = never
@@ -532,10 +535,9 @@ int siso_screen_wanted(const siso_cache *c, long n);
 int siso_screen_reserve(siso_cache *c, long rows, long n);  // may synchronise and allocate, but not under capture
 int siso_screen_reserve_pairs(siso_cache *c, long rows);
 void siso_screen_done(siso_cache *c);
-int siso_screen_has_room(const siso_cache *c, long n);
+void siso_screen_release(siso_cache *c);
 int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
-                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, bool timed,
-                       ScreenPlain *plain);
+                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain);
 // The same for pairs above a threshold (room: siso_screen_reserve_pairs; siso_screen_done, at the end of a call, gives
 // back what is larger than the library keeps between calls).  Behind it the search of all pairs has to be
 // launched with `redo`: its workgroups leave at once unless more than redo_above pairs were in doubt.

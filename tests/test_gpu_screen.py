@@ -160,8 +160,8 @@ def test_batches_of_several_pieces_and_the_update_behind_them(siso):
 
 
 def test_static_and_captured_lookups(siso):
-    """Neither allocates: with the room of an earlier call (or siso_reserve) they are screened, without it they are not;
-    the similarities are the same bits."""
+    """Neither allocates.  A static lookup is not screened, a captured one is where an earlier call (or siso_reserve) has left
+    the room, and keeps that room when a larger call outgrows it; the similarities are the same bits."""
     print("case: screen static and graph", flush=True)
     g = torch.Generator(device=DEV).manual_seed(13)
     d, K, n = 300, 3000, 400
@@ -171,6 +171,9 @@ def test_static_and_captured_lookups(siso):
     out = (torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV), torch.empty(n, dtype=torch.uint8, device=DEV))
     cache.lookup_static(q, 0.1, *out)
     without = [t.clone() for t in out]
+    cache.set_option("screen", 2)
+    cache.reserve(9 * n)  # (the keys of the larger call below; nothing for bytes)
+    cache.set_option("screen", 1)
     idx, sim, hit = cache.lookup(q, 0.1)
     cache.lookup_static(q, 0.1, *out)
     for a, b, w in zip((idx, sim, hit), out, without):
@@ -181,7 +184,13 @@ def test_static_and_captured_lookups(siso):
     torch.cuda.synchronize()
     with torch.cuda.graph(graph, stream=side):
         cache.lookup(q, 0.1, *out)
+    larger = torch.randn(9 * n, d, device=DEV, generator=g)
     for seed in range(3):
+        if seed == 1:
+            torch.cuda.synchronize()
+            more = cache.lookup(larger, 0.1)  # (needs a larger workspace than the recorded one)
+            torch.cuda.synchronize()
+            check(more[0], more[1], larger, c)
         q.copy_(torch.randn(n, d, device=DEV, generator=g))
         torch.cuda.synchronize()
         graph.replay()
