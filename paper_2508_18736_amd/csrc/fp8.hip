@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void k_fp8_quantize(const bf16_t *__restrict__
                                                        float *inv, const int *__restrict__ counts, int *size,
                                                        float *locality, unsigned *access,
                                                        const int *__restrict__ rows, const unsigned char *__restrict__ pick,
-                                                       long limit, unsigned *best) {
+                                                       long limit) {
     __shared__ float sh[4];
     constexpr int E = SISO_MAX_DIM / 256;
     long r = blockIdx.x;
@@ -40,7 +40,6 @@ __global__ __launch_bounds__(256) void k_fp8_quantize(const bf16_t *__restrict__
     }
     fp8_store_row<E>(x, d, codes + (size_t)r * d, scale ? scale + r : nullptr, inv + r, sh);
     if (t == 0) {
-        if (best) best[r] = ordered_bits(-INFINITY);
         if (size) {
             const int s = counts ? counts[r] : 1;
             size[r] = s < 1 ? 1 : s;
@@ -75,7 +74,7 @@ int siso_fp8_load(siso_cache *c, const void *centroids, const int *counts, long 
     if (k > 0) {
         hipLaunchKernelGGL(k_fp8_quantize, dim3((unsigned)k), dim3(256), 0, c->stream, (const bf16_t *)centroids, c->dim,
                            (unsigned char *)c->cent, c->scale, c->invn, counts, c->size, c->locality, c->access,
-                           (const int *)nullptr, (const unsigned char *)nullptr, 0L, (unsigned *)nullptr);
+                           (const int *)nullptr, (const unsigned char *)nullptr, 0L);
         return siso_check_hip(c, hipGetLastError(), "k_fp8_quantize (load)");
     }
     return SISO_OK;
@@ -91,12 +90,11 @@ int siso_fp8_ensure_batch(siso_cache *c, long n) {
         (void)hipFree(c->fp8_qinv);
         c->fp8_q = nullptr;
         c->fp8_qinv = nullptr;
-        c->fp8_best = nullptr;
         c->fp8_q_cap = 0;
     }
     // whole tiles of 256 rows stay readable behind the batch (the kernels clamp their rows, this is slack)
     bool ok = hipMalloc((void **)&c->fp8_q, ((size_t)n + SISO_PAD_ROWS) * c->dim) == hipSuccess;
-    ok = ok && hipMalloc((void **)&c->fp8_qinv, (size_t)(n + (n + 255) / 256 * 256) * sizeof(float)) == hipSuccess;
+    ok = ok && hipMalloc((void **)&c->fp8_qinv, (size_t)n * sizeof(float)) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         if (c->fp8_q) (void)hipFree(c->fp8_q);
@@ -105,14 +103,13 @@ int siso_fp8_ensure_batch(siso_cache *c, long n) {
         return siso_fail(c, SISO_ENOMEM, "fp8 lookup: codes of %ld queries", n);
     }
     c->fp8_q_cap = n;
-    c->fp8_best = (unsigned *)(c->fp8_qinv + n);
     return SISO_OK;
 }
 
 int siso_fp8_quantize_batch(siso_cache *c, const void *queries, long n) {
     hipLaunchKernelGGL(k_fp8_quantize, dim3((unsigned)n), dim3(256), 0, c->stream, (const bf16_t *)queries, c->dim,
                        (unsigned char *)c->fp8_q, (float *)nullptr, c->fp8_qinv, (const int *)nullptr, (int *)nullptr,
-                       (float *)nullptr, (unsigned *)nullptr, (const int *)nullptr, (const unsigned char *)nullptr, 0L, c->fp8_best);
+                       (float *)nullptr, (unsigned *)nullptr, (const int *)nullptr, (const unsigned char *)nullptr, 0L);
     return siso_check_hip(c, hipGetLastError(), "k_fp8_quantize (batch)");
 }
 
@@ -139,7 +136,7 @@ extern "C" int siso_fp8_follow(siso_cache *copy, const siso_cache *master, const
     if (n > 2147483647L) return siso_fail(copy, SISO_EINVAL, "siso_fp8_follow: batch of %ld is too large", n);
     hipLaunchKernelGGL(k_fp8_quantize, dim3((unsigned)n), dim3(256), 0, copy->stream, (const bf16_t *)master->cent, copy->dim,
                        (unsigned char *)copy->cent, copy->scale, copy->invn, (const int *)master->size, copy->size,
-                       copy->locality, copy->access, idx, hit, copy->count, (unsigned *)nullptr);
+                       copy->locality, copy->access, idx, hit, copy->count);
     return siso_check_hip(copy, hipGetLastError(), "k_fp8_quantize (follow)");
 }
 

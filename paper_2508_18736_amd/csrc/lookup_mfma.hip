@@ -104,18 +104,12 @@ __device__ __forceinline__ void pipe_reduce_keys(float (&bv)[WQ], unsigned (&bb)
 // many rows reached the bound (also beyond cand_cap).  A row is listed exactly once: every product is formed by one lane.
 // STREAM: the centroid loads carry the non-temporal hint (see stream_hint below).
 enum { PIPE_KEYS, PIPE_GROUPS, PIPE_COLLECT };  // what k_lookup_pipe does with its products
-template <class Cfg>
-struct PipeShare {  // do the workgroups share best values (see k_lookup_pipe)?
-    static constexpr bool value = Cfg::K64 && Cfg::BQ == 256;
-    static constexpr int BYTES = value ? Cfg::NINV * Cfg::BQ * 4 : 0;  // of LDS
-    static_assert(Cfg::LDS_BYTES + BYTES <= 160 * 1024, "fits in LDS");
-};
 template <class Cfg, int MODE = PIPE_KEYS, bool STREAM = false>
 __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_lookup_pipe(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ C, const float *__restrict__ invn, long n, long K, int d,
     int tiles_per_slice, int slices, int nqt, int qb, u64 *__restrict__ keys, float2 *__restrict__ groups,
     int ng, const float *__restrict__ tau, int *__restrict__ cand, int *__restrict__ cand_cnt, int cand_cap,
-    u64 *__restrict__ board, const int *__restrict__ many, unsigned *__restrict__ shared_best) {
+    u64 *__restrict__ board, const int *__restrict__ many) {
     constexpr int WC = Cfg::WC, WQ = Cfg::WQ, NWC = Cfg::NWC, BC = Cfg::BC, BQ = Cfg::BQ, NT = Cfg::NT, NW = Cfg::NW,
                   STAGE = Cfg::STAGE, NLA = Cfg::NLA, NLB = Cfg::NLB, NL = Cfg::NL, NSTAGE = Cfg::NSTAGE, BK = Cfg::BK,
                   RB = Cfg::RB, CPR = Cfg::CPR, RPI = Cfg::RPI, RP = Cfg::RP, KK = Cfg::KK, SUB = 32 * Cfg::RB, ES = Cfg::ES;
@@ -130,24 +124,11 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     constexpr int NINV = Cfg::NINV;
     static_assert((NINV - 1) * 2 >= NSTAGE, "a tile's inverse lengths outlive the requests that run ahead");
     float *inv_s = (float *)(smem + NSTAGE * STAGE);
-    // Large batches over codes: the workgroups tell each other the best value of every query so far (shared_best, as ordered
-    // bits; NULL: they do not), and only a block whose largest product reaches it is looked at row by row.  The exact
-    // arg-max of every block costs four operations a product, a fifth of the kernel; the maximum alone one and a half, and
-    // after the first tiles hardly a block is looked at.  A value is fetched with its tile's inverse lengths; a stale one lets
-    // more blocks pass, never fewer, and one that is only reached passes (the lowest row among equal ones may be in it).
-    // 5,000 queries x 300,001 rows x 768 1,190 -> 1,136 us.
-    constexpr bool SHARE = PipeShare<Cfg>::value && MODE == PIPE_KEYS;
-    unsigned *best_s = (unsigned *)(inv_s + NINV * BC);  // [NINV][BQ], with SHARE
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wc = wave % NWC, wq = wave / NWC;
     const int h = lane >> 5, l32 = lane & 31;
-    if constexpr (SHARE) {
-        static_assert(BC / 64 + BQ / 64 <= NW, "one direct load per wave for inverse lengths and best values");
-        if (shared_best == nullptr)  // (the pipeline's first barrier is before the first use)
-            for (int i = tid; i < NINV * BQ; i += NT) best_s[i] = ordered_bits(-INFINITY);
-    }
 
     int qt, s, ct_begin, ct_end;
     if (!pipe_map_block<BC>(K, tiles_per_slice, slices, nqt, qb, qt, s, ct_begin, ct_end)) return;
@@ -221,9 +202,6 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         if constexpr (j == 0) {
             if (ld_ks == 0 && wave < BC / 64)
                 gload_lds4(invn + (size_t)ld_ct * BC + wave * 64 + lane, inv_s + ld_inv * BC + wave * 64);
-            if constexpr (SHARE)
-                if (ld_ks == 0 && wave >= BC / 64 && shared_best != nullptr)
-                    gload_lds4_fresh(shared_best + q0 + (wave - BC / 64) * 64 + lane, best_s + ld_inv * BQ + (wave - BC / 64) * 64);
         }
         // (the empty statement keeps the 32-bit offset next to its use, which lets the load take the
         // uniform base from scalar registers instead of a 64-bit address per lane)
@@ -314,26 +292,6 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
                     const long q = q0 + (wq * WQ + B) * 32 + l32;
                     const int grp16 = (int)((c0 + rb) >> 4) + h;
                     if (q < n && grp16 < ng) groups[(size_t)q * ng + grp16] = make_float2(best.first, best.second);
-                } else if constexpr (SHARE) {
-                    static_for<0, 16>([&](auto ii) {
-                        constexpr int I = decltype(ii)::value;
-                        m = fmaxf(m, acc.template get<A, B, I>() * w[I >> 2][I & 3]);
-                    });
-                    const int col = (wq * WQ + B) * 32 + l32;
-                    const float known = unordered_bits(best_s[inv_buf * BQ + col]);
-                    const bool better = m > bv[B] && m >= known;
-                    if (__ballot(better) != 0) {
-                        unsigned mi = 0;
-                        static_for<0, 16>([&](auto ii) {
-                            constexpr int I = 15 - decltype(ii)::value;  // (downwards: the lowest row among equal values stays)
-                            if (acc.template get<A, B, I>() * w[I >> 2][I & 3] == m) mi = (unsigned)(8 * (I >> 2) + (I & 3));
-                        });
-                        if (better) {
-                            bv[B] = m;
-                            bb[B] = (unsigned)(c0 + rb) + 4u * (unsigned)h + mi;
-                            if (shared_best != nullptr && m > known && q0 + col < n) atomicMax(shared_best + q0 + col, ordered_bits(m));
-                        }
-                    }
                 } else if constexpr (Cfg::ROWS) {
                     // the rows of a lane ascend with the register number, the tiles of a workgroup with
                     // time: ">" keeps the lowest row among equal values
@@ -1428,7 +1386,7 @@ static int pipe_attr(siso_cache *c) {
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute((const void *)k_lookup_pipe<Cfg, MODE, STREAM>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES + PipeShare<Cfg>::BYTES);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
         if (e != hipSuccess) return siso_check_hip(c, e, "hipFuncSetAttribute(k_lookup_pipe)");
         attr_done = true;
     }
@@ -1439,11 +1397,10 @@ template <class Cfg, bool STREAM>
 static int launch_cfg2(siso_cache *c, const void *queries, long n, const PipePlan &p, u64 *keys) {
     const int rc = pipe_attr<Cfg, PIPE_KEYS, STREAM>(c);
     if (rc != SISO_OK) return rc;
-    hipLaunchKernelGGL((k_lookup_pipe<Cfg, PIPE_KEYS, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES + PipeShare<Cfg>::BYTES,
+    hipLaunchKernelGGL((k_lookup_pipe<Cfg, PIPE_KEYS, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
                        c->stream, (const bf16_t *)queries, (const bf16_t *)c->cent, c->invn, n, c->count, c->dim,
                        p.tiles_per_slice, p.slices, p.nqt, p.qb, keys, (float2 *)nullptr, 0,
-                       (const float *)nullptr, (int *)nullptr, (int *)nullptr, 0, c->board_to_clear, p.many,
-                       c->plan_min_slices > 0 ? (unsigned *)nullptr : c->fp8_best);  // (a top-k lookup wants the best row of every slice)
+                       (const float *)nullptr, (int *)nullptr, (int *)nullptr, 0, c->board_to_clear, p.many);
     c->board_to_clear = nullptr;  // taken
     return siso_check_hip(c, hipGetLastError(), "k_lookup_pipe");
 }
@@ -1459,7 +1416,7 @@ static int launch_groups2(siso_cache *c, const void *queries, long n, const Pipe
     hipLaunchKernelGGL((k_lookup_pipe<Cfg, PIPE_GROUPS, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
                        c->stream, (const bf16_t *)queries, (const bf16_t *)c->cent, c->invn, n, c->count, c->dim,
                        p.tiles_per_slice, p.slices, p.nqt, p.qb, (u64 *)nullptr, groups, ng, (const float *)nullptr,
-                       (int *)nullptr, (int *)nullptr, 0, (u64 *)nullptr, (const int *)nullptr, (unsigned *)nullptr);
+                       (int *)nullptr, (int *)nullptr, 0, (u64 *)nullptr, (const int *)nullptr);
     return siso_check_hip(c, hipGetLastError(), "k_lookup_pipe (groups)");
 }
 template <class Cfg>
@@ -1476,7 +1433,7 @@ static int launch_collect2(siso_cache *c, const void *queries, long n, const Pip
     hipLaunchKernelGGL((k_lookup_pipe<Cfg, PIPE_COLLECT, STREAM>), dim3((unsigned)p.grid), dim3(Cfg::NT), Cfg::LDS_BYTES,
                        c->stream, (const bf16_t *)queries, (const bf16_t *)c->cent, c->invn, n, c->count, c->dim,
                        p.tiles_per_slice, p.slices, p.nqt, p.qb, (u64 *)nullptr, (float2 *)nullptr, 0, tau, cand, cnt,
-                       cap, (u64 *)nullptr, (const int *)nullptr, (unsigned *)nullptr);
+                       cap, (u64 *)nullptr, (const int *)nullptr);
     return siso_check_hip(c, hipGetLastError(), "k_lookup_pipe (collect)");
 }
 template <class Cfg>

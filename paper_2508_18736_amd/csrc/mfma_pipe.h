@@ -58,12 +58,6 @@ __device__ __forceinline__ void gload_lds4(const void *g, void *lds_wave_base) {
                                      (__attribute__((address_space(3))) void *)lds_wave_base, 4, 0, 0);
 }
 
-// direct load of four bytes per lane that other XCDs may have changed meanwhile (past the L2 of this one)
-__device__ __forceinline__ void gload_lds4_fresh(const void *g, void *lds_wave_base) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
-                                     (__attribute__((address_space(3))) void *)lds_wave_base, 4, 0, 16);
-}
-
 // LDS fragment reads and their waits are written out by hand: while direct loads are in
 // flight the compiler waits for *all* outstanding LDS reads before every use, which would
 // serialise the fragment double buffering.  LDS operations complete in order, so

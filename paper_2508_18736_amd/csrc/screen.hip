@@ -376,6 +376,12 @@ __device__ __forceinline__ void byte_stream(unsigned char *smem, int dp, int pai
     __syncthreads();
 }
 
+// direct load of four bytes per lane that other XCDs may have changed meanwhile (past the L2 of this one)
+__device__ __forceinline__ void gload_lds4_fresh(const void *g, void *lds_wave_base) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
+                                     (__attribute__((address_space(3))) void *)lds_wave_base, 4, 0, 16);
+}
+
 __device__ __forceinline__ int max16(const i32x16 &a) {
     int m = a[0];
 #pragma unroll

@@ -90,7 +90,6 @@ struct siso_cache {
     void *fp8_q;
     float *fp8_qinv;
     long fp8_q_cap;
-    unsigned *fp8_best;  // behind fp8_qinv: a large batch's best values so far (see k_lookup_pipe), [fp8_q_cap rounded up to 256]
 
     // top-k lookups: the two largest products of every group of 16 rows, per query ([topk_groups_cap] pairs; larger batches
     // go in pieces of at least 256 queries that take at most SISO_TOPK_GROUP_BYTES if they can), grown on demand
