@@ -1129,7 +1129,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const
                        r.totals, r.work, r.work_room, r.qinv, r.best);
     hipLaunchKernelGGL(k_screen_write, dim3((unsigned)((n + 255) / 256)), block, 0, c->stream, n, q_base, r.cnt, r.best, tl, out_idx, out_sim,
                        out_hit, access, owner, members);
-    *plain = ScreenPlain{r.totals + 1, r.plain_of, r.plain_rows};
+    *plain = ScreenPlain{r.totals + 1, r.plain_of, r.plain_rows, vec};
     return siso_check_hip(c, hipGetLastError(), "k_screen_lookup, k_screen_pick, k_screen_score");
 }
 

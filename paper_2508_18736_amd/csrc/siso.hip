@@ -1465,7 +1465,8 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
         kernel_queries = c->fp8_q;
     }
     const unsigned qblocks = (unsigned)n;
-    const int vec = ((c->dim * elem_bytes(c->dtype)) % 16 == 0 && ((uintptr_t)queries & 15) == 0) ? 1 : 0;
+    // (left-over rows are gathered, and aligned whatever the batch is: they are summed as the rest of their batch is)
+    const int vec = left ? left->vec : ((c->dim * elem_bytes(c->dtype)) % 16 == 0 && ((uintptr_t)queries & 15) == 0) ? 1 : 0;
     int row_keys = SISO_KEY_ROWS;  // what the keys of the chosen kernel carry: the winning row, or its group of four rows
     const bool may_fold = folded && n <= SISO_FOLD_BOARD && c->count > 0 && (!fp8 || c->fold_master) && m == 1 && out_hit;
     c->board_to_clear = may_fold ? c->counters + 4 : nullptr;
@@ -1510,7 +1511,7 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
         return SISO_OK;
     }
     // (the similarities of a batch are the same bits whether it is screened, as it would be with enough memory, or not)
-    if (row_keys == SISO_KEY_ROWS && siso_screen_wanted(c, n)) row_keys = SISO_KEY_ROWS_ANEW;
+    if (row_keys == SISO_KEY_ROWS && (left || siso_screen_wanted(c, n))) row_keys = SISO_KEY_ROWS_ANEW;
 #define SISO_LAUNCH_FINALIZE(T)                                                                                              \
     hipLaunchKernelGGL(k_lookup_finalize<T>, dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
                        keys, n, c->count, c->dim, slices, tl, vec, row_keys, out_idx, out_sim, out_hit,                        \
@@ -1540,15 +1541,19 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
     PlainLookup plain;
     // (not on the static keys: the bytes live in a workspace that other calls share and a larger one moves)
     if (!static_keys && siso_screen_wanted(c, n) && siso_screen_reserve(c, c->count, n)) {
-        // piece by piece: screened, then what that has left over
+        // piece by piece: screened, then what that has left over.  Pieces of as many tiles of 256 queries each: a short last one
+        // would go through the kernels for few queries, which do not know how many of them there are.
         const size_t row = (size_t)c->dim * elem_bytes(c->dtype);
-        int rc = plan_plain(c, n < SISO_SCREEN_PIECE ? n : SISO_SCREEN_PIECE, nullptr, 0, &plain);
-        for (long off = 0; off < n && rc == SISO_OK; off += SISO_SCREEN_PIECE) {
-            const long part = n - off < SISO_SCREEN_PIECE ? n - off : SISO_SCREEN_PIECE;
+        const long tiles = (n + 255) / 256, pieces = (n + SISO_SCREEN_PIECE - 1) / SISO_SCREEN_PIECE;
+        int rc = SISO_OK;
+        long off = 0, part = 0;
+        for (long p = 0; p < pieces && rc == SISO_OK; ++p, off += part) {
+            part = 256 * (tiles / pieces + (p < tiles % pieces ? 1 : 0));
+            if (part > n - off) part = n - off;
             const char *q = (const char *)queries + (size_t)off * row;
             unsigned char *hit = out_hit ? out_hit + (size_t)off * m : nullptr;
             ScreenPlain left;
-            if (off > 0) rc = plan_plain(c, part, nullptr, 0, &plain);
+            rc = plan_plain(c, part, nullptr, 0, &plain);
             if (rc != SISO_OK) break;
             if (owner) c->mark_in_finalize = 2;
             rc = siso_screen_lookup(c, q, part, off == 0, tl, off, out_idx + off, out_sim + off, hit,

@@ -521,14 +521,16 @@ int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *
 
 // Screened lookups and pair searches (screen.hip).
 // siso_screen_wanted: is a lookup of n queries to be screened?  If so, and if siso_screen_reserve finds room (0 = there is
-// none: the lookup goes without), siso_screen_lookup takes siso_screen_piece() queries at a time (with_rows: the rows have to
+// none: the lookup goes without), siso_screen_lookup takes up to SISO_SCREEN_PIECE queries at a time (with_rows: the rows have to
 // be written as bytes, for the first piece of a call) and leaves some to the other kernels: *plain names them (all on the
-// device, written by the launch): how many, which, and their rows one behind the other.
+// device, written by the launch): how many, which, and their rows one behind the other; vec: how their products are summed
+// (see k_lookup_finalize).
 #define SISO_SCREEN_DIM 1024  // largest dimension
 #define SISO_SCREEN_PIECE 16384L
 struct ScreenPlain {
     const int *many, *query;
     const void *rows;
+    int vec;
 };
 int siso_screen_wanted(const siso_cache *c, long n);
 int siso_screen_reserve(siso_cache *c, long rows, long n);  // may synchronise and allocate, but not under capture

@@ -159,6 +159,29 @@ def test_batches_of_several_pieces_and_the_update_behind_them(siso):
         assert torch.equal(a, b)
 
 
+def test_left_over_queries_of_every_piece_are_summed_alike(siso):
+    """More than 16,384 queries go in pieces.  Queries that are left to the other kernels (a list of equal rows that does not
+    hold) return the bits of siso_lookup_static, which judges the batch as one, in a last piece of any length too."""
+    print("case: screen left-over queries of several pieces", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(21)
+    d, K = 128, 200000
+    c = torch.randn(K, d, device=DEV, generator=g).to(torch.bfloat16)
+    c[2000:5000] = c[2000]
+    for n in (16384 + 1, 16384 + 100, 2 * 16384 + 300):
+        q = torch.randn(n, d, device=DEV, generator=g).to(torch.bfloat16)
+        same = torch.cat([torch.arange(40, 60, device=DEV), torch.arange(n - 70, n, device=DEV)])
+        q[same] = (c[2000].float() + 0.1 * torch.randn(same.shape[0], d, device=DEV, generator=g)).to(torch.bfloat16)
+        cache = make(siso, c, "bf16", screen=0)
+        assert cache.screened(n)
+        idx, sim, hit = cache.lookup(q, 0.5)
+        out = (torch.empty_like(idx), torch.empty_like(sim), torch.empty_like(hit))
+        cache.lookup_static(q, 0.5, *out)
+        assert idx[same].unique().tolist() == [2000] and torch.equal(out[0][same], idx[same])
+        assert torch.equal(out[1][same], sim[same])
+        named_alike = idx == out[0]
+        assert named_alike.float().mean() > 0.999 and torch.equal(sim[named_alike], out[1][named_alike])
+
+
 def test_static_and_captured_lookups(siso):
     """Neither allocates.  A static lookup is not screened, a captured one is where an earlier call (or siso_reserve) has left
     the room, and keeps that room when a larger call outgrows it; the similarities are the same bits."""
