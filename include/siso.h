@@ -107,7 +107,9 @@ long siso_count(const siso_cache *c);
 
 /*
  * Batched lookup (section 4.3; FindClosestCentroid + CosineSimilarity + hit test).
- *   queries:   device pointer, [n][dim]; need not be normalised.
+ *   queries:   device pointer, [n][dim]; need not be normalised.  bf16 batches on the MFMA
+ *              kernels (dimensions that are a multiple of 64, at least 128; all but small
+ *              problems) must be 16-byte aligned: SISO_EINVAL otherwise.
  *   threshold: the retrieval threshold for this call.
  *   out_idx:   device pointer, n ints: index of the centroid with the largest
  *              cosine similarity (the lowest index among equal maxima), whether

@@ -1471,7 +1471,7 @@ static int launch_wide(siso_cache *c, const void *queries, long n, const PipePla
 }
 
 static int pipe_launch(siso_cache *c, const void *queries, long n, const PipePlan &p, u64 *keys) {
-    if (((uintptr_t)queries & 15) != 0) return siso_fail(c, SISO_EINVAL, "bf16 lookup: queries must be 16-byte aligned");
+    if (!siso_mfma_aligned(queries)) return siso_fail(c, SISO_EINVAL, SISO_MFMA_UNALIGNED);
     if (c->dtype == SISO_FP8) {  // `queries` are codes here (the caller has quantised the batch)
         switch (p.cfg) {
             case 2: return launch_cfg<F8Mid>(c, queries, n, p, keys);

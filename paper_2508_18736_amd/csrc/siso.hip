@@ -1555,6 +1555,8 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
             ScreenPlain left;
             rc = plan_plain(c, part, nullptr, 0, &plain);
             if (rc != SISO_OK) break;
+            // (the gathered rows of left-over queries are aligned: a batch that those kernels refuse is refused here)
+            if (plain.path != SISO_PATH_SCALAR && !siso_mfma_aligned(queries)) return siso_fail(c, SISO_EINVAL, SISO_MFMA_UNALIGNED);
             if (owner) c->mark_in_finalize = 2;
             rc = siso_screen_lookup(c, q, part, off == 0, tl, off, out_idx + off, out_sim + off, hit,
                                     count_index >= 0 ? c->access : nullptr, owner, members, &left);

@@ -497,6 +497,8 @@ int siso_tile_preferred(const siso_cache *c, long n);  // 1 = small: rather thes
 int siso_tile_slices(const siso_cache *c, long n);
 long siso_tile_keys_bound(const siso_cache *c, long n);
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, const int *many = nullptr);
+#define SISO_MFMA_UNALIGNED "bf16 lookup: queries must be 16-byte aligned"
+inline bool siso_mfma_aligned(const void *queries) { return ((uintptr_t)queries & 15) == 0; }
 int siso_mfma_slices(const siso_cache *c, long n);
 int siso_mfma_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys, const int *many = nullptr);
 int siso_skinny_slices(const siso_cache *c, long n);

@@ -182,6 +182,29 @@ def test_left_over_queries_of_every_piece_are_summed_alike(siso):
         assert named_alike.float().mean() > 0.999 and torch.equal(sim[named_alike], out[1][named_alike])
 
 
+def test_unaligned_queries(siso):
+    """bf16 batches that are not 16-byte aligned: refused where the kernels of all products refuse them, screened or not, with
+    nothing written; accepted, with the values of the aligned batch, where those accept them."""
+    print("case: screen unaligned queries", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(22)
+    n = 900
+    for d, K, refused in ((128, 9000, True), (132, 9000, False)):
+        c = torch.randn(K, d, device=DEV, generator=g).to(torch.bfloat16)
+        q = torch.randn(n * d + 1, device=DEV, generator=g).to(torch.bfloat16)[1:].view(n, d)
+        want = make(siso, c, "bf16", screen=2).lookup(q.clone(), 0.2)
+        for screen in (1, 2):
+            cache = make(siso, c, "bf16", screen=screen)
+            assert cache.screened(n) == (screen == 1)
+            out = (torch.full((n,), -7, dtype=torch.int32, device=DEV), torch.full((n,), -7.0, device=DEV), torch.full((n,), 7, dtype=torch.uint8, device=DEV))
+            if refused:
+                with pytest.raises(siso.SisoError, match="16-byte aligned"):
+                    cache.lookup(q, 0.2, *out)
+                assert bool((out[0] == -7).all() and (out[1] == -7).all() and (out[2] == 7).all())
+            else:
+                cache.lookup(q, 0.2, *out)
+                assert torch.equal(out[0], want[0]) and (out[1] - want[1]).abs().max() <= 2 * TOL
+
+
 def test_static_and_captured_lookups(siso):
     """Neither allocates.  A static lookup is not screened, a captured one is where an earlier call (or siso_reserve) has left
     the room, and keeps that room when a larger call outgrows it; the similarities are the same bits."""
