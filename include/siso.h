@@ -232,7 +232,8 @@ int siso_update_hits(siso_cache *c, const void *queries, const int *idx, const u
  * FindClosestCentroid of Algorithm 1 found a match).  Arguments as siso_lookup (out_hit
  * may not be NULL); outputs and state are bit for bit those of the two calls.
  * Batches of at most 256 queries whose lookup runs on kernels that name the winning
- * row (fp32 caches, bf16 caches whose dimension is no multiple of 64 or below 128, small
+ * row (fp32 caches but for the batches that are screened, see siso_lookup; bf16 caches
+ * whose dimension is no multiple of 64 or below 128, small
  * bf16 problems, bf16 batches of at most 128) finish in one
  * kernel that ends the lookup and applies the update: the workgroups of the batch tell
  * each other their (index, hit) through 256 slots of device memory of the cache (emptied

@@ -1468,7 +1468,10 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
     // (left-over rows are gathered, and aligned whatever the batch is: they are summed as the rest of their batch is)
     const int vec = left ? left->vec : ((c->dim * elem_bytes(c->dtype)) % 16 == 0 && ((uintptr_t)queries & 15) == 0) ? 1 : 0;
     int row_keys = SISO_KEY_ROWS;  // what the keys of the chosen kernel carry: the winning row, or its group of four rows
-    const bool may_fold = folded && n <= SISO_FOLD_BOARD && c->count > 0 && (!fp8 || c->fold_master) && m == 1 && out_hit;
+    // (the similarities of a batch are the same bits whether it is screened, as it would be with enough memory, or not: then
+    // they are formed anew, which the kernel that ends a lookup together with its update does not do)
+    const bool anew = left || siso_screen_wanted(c, n);
+    const bool may_fold = folded && !anew && n <= SISO_FOLD_BOARD && c->count > 0 && (!fp8 || c->fold_master) && m == 1 && out_hit;
     c->board_to_clear = may_fold ? c->counters + 4 : nullptr;
     if (c->count > 0) {
         if (timed) siso_prof_begin(c);
@@ -1510,8 +1513,7 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
         *folded = 1;
         return SISO_OK;
     }
-    // (the similarities of a batch are the same bits whether it is screened, as it would be with enough memory, or not)
-    if (row_keys == SISO_KEY_ROWS && (left || siso_screen_wanted(c, n))) row_keys = SISO_KEY_ROWS_ANEW;
+    if (row_keys == SISO_KEY_ROWS && anew) row_keys = SISO_KEY_ROWS_ANEW;
 #define SISO_LAUNCH_FINALIZE(T)                                                                                              \
     hipLaunchKernelGGL(k_lookup_finalize<T>, dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
                        keys, n, c->count, c->dim, slices, tl, vec, row_keys, out_idx, out_sim, out_hit,                        \

@@ -205,6 +205,39 @@ def test_unaligned_queries(siso):
                 assert torch.equal(out[0], want[0]) and (out[1] - want[1]).abs().max() <= 2 * TOL
 
 
+def test_lookup_update_without_room_is_the_two_calls(siso):
+    """Up to 256 queries of single precision that would be screened, but for the room (under capture nothing is allocated):
+    siso_lookup_update returns the bits of siso_lookup, and of the screened lookup."""
+    print("case: screen lookup_update without room", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(23)
+    d, K, n = 384, 60000, 200
+    c = torch.randn(K, d, device=DEV, generator=g)
+    q = rows_near(g, c, n, 0.3, torch.float32)
+    got = []
+    for update in (False, True):
+        cache = make(siso, c, "f32", screen=2)
+        cache.reserve(n)  # (keys, no bytes)
+        cache.set_option("screen", 0)
+        assert cache.screened(n)
+        out = (torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV), torch.empty(n, dtype=torch.uint8, device=DEV))
+        side = torch.cuda.Stream()
+        cache.set_stream(side)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            cache.lookup_update(q, 0.9, *out) if update else cache.lookup(q, 0.9, *out)
+        graph.replay()
+        torch.cuda.synchronize()
+        cache.set_stream(torch.cuda.current_stream())
+        if not update:
+            cache.update(q, out[0], out[2])
+        got.append(out + cache.export() + cache.export_meta())
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    idx, sim, _ = make(siso, c, "f32", screen=0).lookup(q, 0.9)
+    assert torch.equal(idx, got[0][0]) and torch.equal(sim, got[0][1])
+
+
 def test_static_and_captured_lookups(siso):
     """Neither allocates.  A static lookup is not screened, a captured one is where an earlier call (or siso_reserve) has left
     the room, and keeps that room when a larger call outgrows it; the similarities are the same bits."""
