@@ -1032,29 +1032,47 @@ bool capturing(const siso_cache *c) {
     return status != hipStreamCaptureStatusNone;
 }
 
-// false = there is no room, which no caller needs to fail for.  keep: where the old room goes if it must stay (NULL: it is freed).
-bool make_room(siso_cache *c, char *&room, size_t &cap, size_t bytes, std::vector<char *> *keep) {
-    if (bytes <= cap) return true;
-    if (capturing(c)) return false;
-    if (room) {
-        if (keep) {
-            keep->push_back(room);  // (room for it: siso_screen_lookup)
+bool take(char **at, size_t bytes) {
+    if (hipMalloc((void **)at, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *at = nullptr;
+    return false;
+}
+
+// Room for `bytes`; false = there is none, which no caller needs to fail for.  keep: where the old room goes if it must stay
+// (NULL: it is freed).  The old room is given up only for the new one: a call that cannot have more leaves what smaller ones use.
+bool make_room(siso_cache *c, ScreenSpace &room, size_t bytes, std::vector<char *> *keep) {
+    if (bytes <= room.cap) return true;
+    if (capturing(c) || (room.refused != 0 && bytes >= room.refused)) return false;
+    if (c->opt_screen_room > 0 && bytes > (size_t)c->opt_screen_room << 10) {
+        room.refused = bytes;
+        return false;
+    }
+    char *larger = nullptr;
+    bool have = take(&larger, bytes);
+    if (room.at && (have || !keep)) {
+        if (have && keep) {
+            keep->push_back(room.at);  // (room for it: siso_screen_lookup)
         } else {
             if (hipStreamSynchronize(c->stream) != hipSuccess) {
                 (void)hipGetLastError();
+                if (larger) (void)hipFree(larger);
                 return false;
             }
-            (void)hipFree(room);
+            (void)hipFree(room.at);
         }
-        room = nullptr;
-        cap = 0;
+        room.at = nullptr;
+        if (!have) {  // perhaps with what it had
+            have = take(&larger, bytes);
+            if (!have && !take(&room.at, room.cap)) room.cap = 0;
+        }
     }
-    if (hipMalloc((void **)&room, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        room = nullptr;
+    if (!have) {
+        room.refused = bytes;
         return false;
     }
-    cap = bytes;
+    room.at = larger;
+    room.cap = bytes;
     return true;
 }
 
@@ -1080,7 +1098,7 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *
 template <typename T>
 int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
                   float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain) {
-    const ScreenRoom r = screen_room(c->screen, c, c->count, n);
+    const ScreenRoom r = screen_room(c->screen.at, c, c->count, n);
     const int d = c->dim, dp = byte_dim(d);
     const long tiles = up256(c->count) / 256, nqt = up256(n) / 256;
     static bool attr_done = false;
@@ -1136,7 +1154,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const
 template <typename T>
 int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, float threshold, int *out_pairs, long cap, u64 *counter,
                  PairsRedo *redo) {
-    const ScreenRoom r = screen_room(c->screen_pairs, c, count, 0);
+    const ScreenRoom r = screen_room(c->screen_pairs.at, c, count, 0);
     const int d = c->dim, dp = byte_dim(d);
     static bool attr_done = false;
     if (!attr_done) {
@@ -1183,29 +1201,40 @@ extern "C" int siso_screened(const siso_cache *c, long n) {
     return n == 0 ? siso_screen_pairs_wanted(c, c->count, 1.f) : siso_screen_wanted(c, n);
 }
 
-int siso_screen_reserve(siso_cache *c, long rows, long n) {
-    const size_t bytes = screen_room(nullptr, c, rows, n).bytes;
-    if (bytes <= c->screen_cap) return 1;
-    const bool room = make_room(c, c->screen, c->screen_cap, bytes, c->screen_recorded ? c->screen_kept : nullptr);
-    if (c->screen == nullptr || room) c->screen_recorded = 0;
-    return room ? 1 : 0;
+static bool lookup_room(siso_cache *c, long rows, long n) {
+    const char *before = c->screen.at;
+    const bool room = make_room(c, c->screen, screen_room(nullptr, c, rows, n).bytes, c->screen_recorded ? c->screen_kept : nullptr);
+    if (c->screen.at != before) c->screen_recorded = 0;
+    return room;
 }
 
-int siso_screen_reserve_pairs(siso_cache *c, long rows) {
-    return make_room(c, c->screen_pairs, c->screen_pairs_cap, screen_room(nullptr, c, rows, 0).bytes, nullptr) ? 1 : 0;
+int siso_screen_room(siso_cache *c, long n) {
+    // (what siso_reserve was asked for does not allocate afterwards, with or without room)
+    if (n <= c->screen_reserved) return screen_room(nullptr, c, c->count, n).bytes <= c->screen.cap;
+    return lookup_room(c, c->count, n);
+}
+
+void siso_screen_reserve(siso_cache *c, long n) {
+    c->screen.refused = c->screen_pairs.refused = 0;
+    (void)lookup_room(c, c->capacity, n);
+    if (n > c->screen_reserved) c->screen_reserved = n;
+}
+
+int siso_screen_pairs_room(siso_cache *c, long rows) {
+    return make_room(c, c->screen_pairs, screen_room(nullptr, c, rows, 0).bytes, nullptr);
 }
 
 void siso_screen_done(siso_cache *c) {
-    if (c->screen_pairs_cap <= (size_t)SISO_ARENA_KEEP) return;
+    if (c->screen_pairs.cap <= (size_t)SISO_ARENA_KEEP) return;
     (void)hipStreamSynchronize(c->stream);
-    (void)hipFree(c->screen_pairs);
-    c->screen_pairs = nullptr;
-    c->screen_pairs_cap = 0;
+    (void)hipFree(c->screen_pairs.at);
+    c->screen_pairs = ScreenSpace{nullptr, 0, 0};
+    c->screen.refused = 0;
 }
 
 void siso_screen_release(siso_cache *c) {
-    if (c->screen) (void)hipFree(c->screen);
-    if (c->screen_pairs) (void)hipFree(c->screen_pairs);
+    if (c->screen.at) (void)hipFree(c->screen.at);
+    if (c->screen_pairs.at) (void)hipFree(c->screen_pairs.at);
     if (c->screen_kept)
         for (char *room : *c->screen_kept) (void)hipFree(room);
     delete c->screen_kept;

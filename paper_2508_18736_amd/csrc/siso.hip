@@ -1256,6 +1256,7 @@ extern "C" int siso_set_option(siso_cache *c, const char *name, long value) {
     else if (!strcmp(name, "tiles_per_slice")) c->opt_tiles_per_slice = (int)value;
     else if (!strcmp(name, "merge_config")) c->opt_merge_config = (int)value;
     else if (!strcmp(name, "screen") && value <= 2) c->opt_screen = (int)value;
+    else if (!strcmp(name, "screen_room")) c->opt_screen_room = (int)value;
     else if (!strcmp(name, "mfma_qblock")) c->opt_mfma_qblock = (int)value;
     else if (!strcmp(name, "fold_spin_limit")) c->opt_fold_spin_limit = (int)value;
     else if (!strcmp(name, "topk_room")) c->opt_topk_room = (int)value;
@@ -1391,7 +1392,7 @@ extern "C" int siso_reserve(siso_cache *c, long n) {
     }
     if (c->dtype == SISO_FP8) return siso_fp8_ensure_batch(c, n);
     // (no room for the bytes of a screened lookup is no error: such lookups then go without)
-    if (siso_screen_wanted(&full, n)) (void)siso_screen_reserve(c, c->capacity, n);
+    if (siso_screen_wanted(&full, n)) siso_screen_reserve(c, n);
     if (n > 256) return ensure_update_notes(c);
     return SISO_OK;
 }
@@ -1542,7 +1543,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
     }
     PlainLookup plain;
     // (not on the static keys: the bytes live in a workspace that other calls share and a larger one moves)
-    if (!static_keys && siso_screen_wanted(c, n) && siso_screen_reserve(c, c->count, n)) {
+    if (!static_keys && siso_screen_wanted(c, n) && siso_screen_room(c, n)) {
         // piece by piece: screened, then what that has left over.  Pieces of as many tiles of 256 queries each: a short last one
         // would go through the kernels for few queries, which do not know how many of them there are.
         const size_t row = (size_t)c->dim * elem_bytes(c->dtype);
@@ -1703,7 +1704,7 @@ extern "C" long siso_bad_indices(siso_cache *c) {
 int siso_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
                       u64 *counter) {
     PairsRedo redo = {nullptr, 0};
-    if (siso_screen_pairs_wanted(c, count, threshold) && siso_screen_reserve_pairs(c, count)) {
+    if (siso_screen_pairs_wanted(c, count, threshold) && siso_screen_pairs_room(c, count)) {
         const int rc = siso_screen_pairs_launch(c, rows, invn, count, threshold, out_pairs, cap, counter, &redo);
         if (rc != SISO_OK) return rc;
     }

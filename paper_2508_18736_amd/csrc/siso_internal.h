@@ -34,6 +34,12 @@ enum { SISO_KEY_ROWS = 1, SISO_KEY_ROWS_ANEW = 2, SISO_KEY_GROUPS4 = 3 };
 #define SISO_MULTI_MAX 32  // thresholds one lookup can be judged against
 #define SISO_PAD_ROWS 256  // readable rows past the capacity of the stored-centroid array
 
+struct ScreenSpace {
+    char *at;
+    size_t cap;
+    size_t refused;  // the smallest size that could not be had (0 = none): not asked for again until siso_reserve or a release
+};
+
 struct siso_cache {
     int dim;
     long capacity;
@@ -110,13 +116,14 @@ struct siso_cache {
 
     // screened lookups and pair searches (screen.hip): bytes of rows and queries, bounds, lists; grown on demand.  Two
     // workspaces, so that a pair search does not move what a captured lookup refers to.
-    char *screen, *screen_pairs;
-    size_t screen_cap, screen_pairs_cap;
+    ScreenSpace screen, screen_pairs;
+    long screen_reserved;  // batches that siso_reserve has sized `screen` for, or tried to: their lookups leave it as it is
     int screen_recorded;  // a graph holds a screened lookup on `screen`: outgrown, it stays until the cache goes (screen_kept)
     std::vector<char *> *screen_kept;
 
     // tuning knobs (siso_set_option); 0 = library default
     int opt_screen;  // 1 = screen wherever the kernels can, 2 = never
+    int opt_screen_room;  // > 0: KiB that a workspace of screen.hip may take
     int opt_mfma_config;
     int opt_tiles_per_slice;
     int opt_merge_config;
@@ -522,7 +529,7 @@ int siso_topk_fp8_collect(siso_cache *c, long n, int slices, const float *tau, i
 int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng);
 
 // Screened lookups and pair searches (screen.hip).
-// siso_screen_wanted: is a lookup of n queries to be screened?  If so, and if siso_screen_reserve finds room (0 = there is
+// siso_screen_wanted: is a lookup of n queries to be screened?  If so, and if siso_screen_room finds room (0 = there is
 // none: the lookup goes without), siso_screen_lookup takes up to SISO_SCREEN_PIECE queries at a time (with_rows: the rows have to
 // be written as bytes, for the first piece of a call) and leaves some to the other kernels: *plain names them (all on the
 // device, written by the launch): how many, which, and their rows one behind the other; vec: how their products are summed
@@ -535,15 +542,16 @@ struct ScreenPlain {
     int vec;
 };
 int siso_screen_wanted(const siso_cache *c, long n);
-int siso_screen_reserve(siso_cache *c, long rows, long n);  // may synchronise and allocate, but not under capture
-int siso_screen_reserve_pairs(siso_cache *c, long rows);
+int siso_screen_room(siso_cache *c, long n);  // may synchronise and allocate, but not under capture
+void siso_screen_reserve(siso_cache *c, long n);  // siso_reserve: room for a full cache
+int siso_screen_pairs_room(siso_cache *c, long rows);
 void siso_screen_done(siso_cache *c);
 void siso_screen_release(siso_cache *c);
 int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
                        float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain);
-// The same for pairs above a threshold (room: siso_screen_reserve_pairs; siso_screen_done, at the end of a call, gives
+// The same for pairs above a threshold (room: siso_screen_pairs_room; siso_screen_done, at the end of a call, gives
 // back what is larger than the library keeps between calls).  Behind it the search of all pairs has to be
-// launched with `redo`: its workgroups leave at once unless more than redo_above pairs were in doubt.
+// launched with `redo`: its workgroups leave at once unless more than redo.above pairs were in doubt.
 struct PairsRedo {
     const u64 *count;  // NULL = search all pairs
     u64 above;

@@ -282,6 +282,65 @@ def test_static_and_captured_lookups(siso):
         check(got[0], got[1], q, c)
 
 
+def test_short_of_memory(siso):
+    """What cannot have its room goes without, leaves the room of smaller calls as it is, and does not ask again; a loop that was
+    reserved for never allocates."""
+    print("case: screen short of memory", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(24)
+    d, K, small, large = 256, 9000, 1000, 9000
+    c = torch.randn(K, d, device=DEV, generator=g)
+    q = torch.randn(large, d, device=DEV, generator=g)
+    out = (torch.empty(large, dtype=torch.int32, device=DEV), torch.empty(large, device=DEV), torch.empty(large, dtype=torch.uint8, device=DEV))
+
+    def lookup(cache, n):
+        cache.lookup(q[:n], 0.1, *(t[:n] for t in out))
+        torch.cuda.synchronize()
+        return [t[:n].clone() for t in out]
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()  # (all but torch's own)
+
+    def alike(a, b):  # (torch's segments are no whole pages)
+        return abs(a - b) < 4 << 20
+
+    def same(a, b):
+        return torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+
+    want = make(siso, c, "f32")
+    want = [lookup(want, n) for n in (small, large)]
+    cache = make(siso, c, "f32", screen=2)
+    cache.reserve(large)  # (keys)
+    cache.set_option("screen", 1)
+    cache.merge(0.9, 1000)
+    none = free()
+    got = lookup(cache, small)  # takes the room it needs: about 12 MiB
+    with_small = free()
+    assert same(got, want[0]) and with_small < none - (8 << 20)
+    cache.set_option("screen_room", 32 << 10)
+    for _ in range(3):  # about 90 MiB are refused
+        check(*lookup(cache, large)[:2], q, c)
+        assert alike(free(), with_small)
+        assert same(lookup(cache, small), want[0]) and alike(free(), with_small)
+    cache.set_option("screen_room", 0)
+    lookup(cache, large)  # not asked for again
+    assert alike(free(), with_small)
+    cache.reserve(large)  # but here
+    with_large = free()
+    assert with_large < with_small - (32 << 20) and same(lookup(cache, large), want[1]) and alike(free(), with_large)
+    # a reservation that found no room: what it was made for goes without, and allocates nothing
+    cache = make(siso, c, "f32", screen=2)
+    cache.reserve(large)
+    cache.set_option("screen", 1)
+    cache.set_option("screen_room", 1)
+    cache.reserve(large)
+    cache.set_option("screen_room", 0)
+    none = free()
+    for n in (large, small):
+        check(*lookup(cache, n)[:2], q[:n], c)
+        assert alike(free(), none)
+
+
 def pair_set(pairs, total):
     got = pairs[:total].tolist()
     assert len(got) == total
