@@ -16,6 +16,13 @@
 // holds) are left to the kernels of lookup_mfma.hip and lookup_tile.hip: every call ends with a launch of those over the
 // gathered rows of such queries, whose workgroups leave at once if there are none.
 //
+// Rows with a common direction (mean cosine 0.5 and more, as text embeddings have it) crowd together for queries that miss:
+// the deviation of the cosines shrinks with the part that is not common while the error stays, and a list floods.  A query
+// whose list is full lists nothing any more; k_screen_seed counts those whose lists can be foreseen to flood, from
+// the sample and again from the lists of the first eighth; and if they are too many (lost, most_lost) the batch is given up:
+// the rest of the products is not formed, and the other kernels do all of it, which by then has paid for little.  (No query
+// is given up alone: those kernels take nearly as long for one as for all.)
+//
 // Rows are grouped by 32 (the rows of one MFMA): one scale and one error for each.  One outlier costs its 32 rows some
 // precision and nobody else; and the end of a tile works on integers: a maximum of 16, one conversion, three operations
 // in floating point for 16 products, against some two for each where every row has a weight.
@@ -29,11 +36,11 @@ typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef PipeCfg<4, 2, 2, 4, 2, 128, true, 1> ByteCfg;  // 256 x 256 tile, waves of 128 x 64, two stages of 128 bytes a row
 
 #define SCREEN_LIST 1024          // rows a query's list holds
-#define SCREEN_WORK 96            // rows a query on average can have multiplied again
 #define SCREEN_TILES 16           // tiles of a slice: a row of it is 12 bits
 #define SCREEN_STAGE 896          // rows a wave collects in LDS before they are handed to the queries' lists
 #define SCREEN_MAYBE (1L << 20)   // pairs whose cosine has to be formed anew
 #define SCREEN_SLACK 2e-5f        // roundings of the lengths, of the unit rows and of the sums formed anew (about 4e-6 in all)
+#define SCREEN_WHOLE 0x7FFFFFFF   // most_lost: never given up
 #define SCREEN_PLAIN (-2)         // instead of a list's length: this query is left to the other kernels
 #define SCREEN_NAN (-1)           // and this one holds a NaN or an infinity
 
@@ -58,7 +65,8 @@ template <typename T, int NCH, bool ROWS>
 __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict__ src, const float *__restrict__ invn, long have,
                                                   int vec, signed char *__restrict__ codes, float4 *__restrict__ meta,
                                                   ScreenQuery *__restrict__ qm, unsigned *__restrict__ low, u64 *__restrict__ seed,
-                                                  int *__restrict__ cnt, int *__restrict__ totals, int d, int dp) {
+                                                  int *__restrict__ cnt, int *__restrict__ near, float *__restrict__ largest,
+                                                  int *__restrict__ totals, int d, int dp) {
     constexpr int R = 8;
     __shared__ float sh[4][4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -214,10 +222,12 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
             low[q] = ok ? ordered_bits(-INFINITY) : ordered_bits(INFINITY);  // (nothing reaches +inf: no list)
             seed[q] = 0;
             cnt[q] = kind[j];
+            near[q] = 0;
+            largest[q] = 0.f;
         }
     }
     if constexpr (!ROWS) {
-        if (blk == 0 && threadIdx.x < 2) totals[threadIdx.x] = 0;
+        if (blk == 0 && threadIdx.x < 3) totals[threadIdx.x] = 0;
     } else {
         if (lane == 0) {
             sh[1][wave] = err;
@@ -233,6 +243,12 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
     }
 }
 
+// Which rows of the cache a launch of k_screen_bytes writes, in tiles of 256 (eight workgroups): all; those that are looked at
+// before a batch may be given up (the tiles below `ahead` and the sample, `some` tiles every `stride`); or the others, and
+// none if it has been.
+struct ScreenTiles {
+    int part, ahead, some, stride;  // part 0, 1, 2
+};
 // Blocks below row_blocks: rows of the cache; the others: queries.
 template <typename T, int NCH>
 __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows, const float *__restrict__ invn, long K,
@@ -240,12 +256,25 @@ __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows
                                                       float4 *__restrict__ meta, const T *__restrict__ queries, long n, int query_vec,
                                                       signed char *__restrict__ qcodes, ScreenQuery *__restrict__ qm,
                                                       unsigned *__restrict__ low, u64 *__restrict__ seed, int *__restrict__ cnt,
-                                                      int *__restrict__ totals, int d, int dp) {
-    if (blockIdx.x < row_blocks)
-        write_bytes_block<T, NCH, true>(blockIdx.x, rows, invn, K, row_vec, codes, meta, nullptr, nullptr, nullptr, nullptr, nullptr, d, dp);
-    else
+                                                      int *__restrict__ near, float *__restrict__ largest, int *__restrict__ totals,
+                                                      int d, int dp, ScreenTiles tiles, int most_lost) {
+    if (blockIdx.x < row_blocks) {
+        long blk = blockIdx.x;
+        if (tiles.part == 1 && blk >= 8L * tiles.ahead) {
+            const long tile = (blk / 8 - tiles.ahead) * tiles.stride;
+            if (tile < tiles.ahead) return;
+            blk = tile * 8 + blk % 8;
+        } else if (tiles.part == 2) {
+            blk += 8L * tiles.ahead;
+            const long tile = blk / 8;
+            if (totals[2] > most_lost || (tile % tiles.stride == 0 && tile / tiles.stride < tiles.some)) return;
+        }
+        write_bytes_block<T, NCH, true>(blk, rows, invn, K, row_vec, codes, meta, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                        nullptr, d, dp);
+    } else {
         write_bytes_block<T, NCH, false>(blockIdx.x - row_blocks, queries, nullptr, n, query_vec, qcodes, nullptr, qm, low, seed, cnt,
-                                         totals, d, dp);
+                                         near, largest, totals, d, dp);
+    }
 }
 
 // ---- products of bytes --------------------------------------------------------------------------------------------
@@ -396,10 +425,11 @@ __device__ __forceinline__ unsigned upper_bits(float v) {
 }
 __device__ __forceinline__ float upper_value(unsigned b) { return b >= 4095u ? INFINITY : (float)b * (2.5f / 4095.f) - 1.25f + 1e-6f; }
 
-__device__ __forceinline__ void list_row(uint2 *list, int *cnt, long q, long row0, long row, long K, float upper) {
+__device__ __forceinline__ void list_row(uint2 *list, int *cnt, unsigned *low, long q, long row0, long row, long K, float upper) {
     if (row >= K) return;  // (rows past the end are zeros)
     const int slot = atomicAdd(cnt + q, 1);
     if (slot < SCREEN_LIST) list[(size_t)q * SCREEN_LIST + slot] = make_uint2((unsigned)(row0 + row), __float_as_uint(upper));
+    else if (slot == SCREEN_LIST) atomicMax(low + q, ordered_bits(INFINITY));  // no list will do: no more of it
 }
 
 // Products of the queries of a tile with the rows of a slice.  low[q] = the largest lower end any workgroup has found for
@@ -407,7 +437,8 @@ __device__ __forceinline__ void list_row(uint2 *list, int *cnt, long q, long row
 // query's list.  low only grows, and a stale value lists more rows than needed, never fewer: nothing has to be ordered.
 // Rows are collected in LDS and judged by the newest low once more when they are handed over.
 // codes, meta and the K rows are a run of the cache's, from its row number row0 on.
-// SAMPLE: one tile per workgroup, every `stride`-th of them, and only its best row counts: seed[q] = (product, row).
+// SAMPLE: one tile per workgroup, every `stride`-th of them, and only its best row counts: seed[q] = (product, row); and for
+// k_screen_seed, of 128 rows at a time, the largest cosine and how many come within the error of it (ScreenCrowd).
 struct LookupSrc {
     const signed char *c, *q;
     int ct, dp, buf;
@@ -432,7 +463,8 @@ template <bool SAMPLE>
 __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_screen_lookup(
     const signed char *__restrict__ qcodes, const signed char *__restrict__ codes, const float4 *__restrict__ meta,
     const ScreenQuery *__restrict__ qm, unsigned *__restrict__ low, u64 *__restrict__ seed, int *__restrict__ cnt,
-    uint2 *__restrict__ list, long row0, long K, int dp, int tiles_per_slice, int slices, int nqt, int qb, int stride) {
+    int *__restrict__ near_, float *__restrict__ largest, uint2 *__restrict__ list, long row0, long K, int dp, int tiles_per_slice,
+    int slices, int nqt, int qb, int stride, const int *__restrict__ lost, int most_lost) {
     typedef ByteCfg Cfg;
     constexpr int WC = Cfg::WC, WQ = Cfg::WQ, BC = Cfg::BC, BQ = Cfg::BQ;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -447,7 +479,7 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
         if ((long)ct_begin * BC >= K) return;
     } else {
         if (!pipe_map_block<BC>(K, tiles_per_slice, slices, nqt, qb, qt, s, ct_begin, ct_end)) return;
-        if (ct_end <= ct_begin) return;
+        if (ct_end <= ct_begin || *lost > most_lost) return;
     }
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -504,7 +536,19 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                     top = ov;
                     row = orow;
                 }
-                if (h == 0) atomicMax(seed + q0 + (wq * WQ + B) * 32 + l32, pack_key(top, (unsigned)row));
+                int near = 0;
+                static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+                    constexpr int A = decltype(ia)::value;
+                    // (as in a lookup's fold; a query that lists nothing has halfw < 0, and zeros for bytes: none of them counts)
+                    const int least = (int)floorf((top - halfw[B] * rscale[B] - grow[B] * mt[A].y) * mt[A].w);
+                    static_for<0, 16>([&](auto ii) __attribute__((always_inline)) { near += acc[A][B][decltype(ii)::value] >= least ? 1 : 0; });
+                });
+                near += (int)other_half((unsigned)near);
+                if (h == 0) {
+                    atomicMax(seed + q0 + (wq * WQ + B) * 32 + l32, pack_key(top, (unsigned)row));
+                    atomicAdd(near_ + q0 + (wq * WQ + B) * 32 + l32, near);
+                    atomicAdd(largest + q0 + (wq * WQ + B) * 32 + l32, top * scale[B]);
+                }
             });
         });
         return;
@@ -518,8 +562,8 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
             const unsigned e = stage[p];
             const long q = q0 + (e >> 24);
             const float upper = upper_value(e & 0xFFFu);
-            if (upper >= unordered_bits(__hip_atomic_load(low + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-                list_row(list, cnt, q, row0, ct_begin * (long)BC + ((e >> 12) & 0xFFFu), K, upper);
+            if (upper > unordered_bits(__hip_atomic_load(low + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                list_row(list, cnt, low, q, row0, ct_begin * (long)BC + ((e >> 12) & 0xFFFu), K, upper);
         }
         mine = 0;
     };
@@ -542,14 +586,15 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
             static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
                 constexpr int A = decltype(ia)::value;
                 top[A][B] = max16(acc[A][B]);
-                // (a query that lists nothing needs +inf and has grow = 0: no NaN of a block never ruled out reaches that)
+                // (a query that lists nothing needs +inf, and nothing is larger; where it never did, grow = 0 and the NaN of a
+                // block never ruled out is no number to compare)
                 up[A][B] = fmaf((float)top[A][B], m[A].x, grow[B] * m[A].y);
                 most[B] = fmaxf(most[B], up[A][B]);
             });
         });
         static_for<0, WQ>([&](auto ib) __attribute__((always_inline)) {
             constexpr int B = decltype(ib)::value;
-            if (__ballot(most[B] >= need[B]) == 0) return;
+            if (__ballot(most[B] > need[B]) == 0) return;
             const unsigned col = (unsigned)((wq * WQ + B) * 32 + l32);
             float lo = -INFINITY;
             static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
@@ -564,10 +609,10 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
             if (h == 0 && lo > seen[B] + 1e-3f) atomicMax(low + q0 + col, ordered_bits(lo));
             static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
                 constexpr int A = decltype(ia)::value;
-                if (__ballot(up[A][B] >= need[B]) == 0) return;
+                if (__ballot(up[A][B] > need[B]) == 0) return;
                 // the bound as an integer (rounded down; the slack of the error is some twenty of its units).  No scale (rows
                 // of zeros): plus or minus infinity, or a NaN, which converts to 0
-                const int least = up[A][B] >= need[B] ? (int)floorf((need[B] - grow[B] * m[A].y) * m[A].w) : 0x7FFFFFFF;
+                const int least = up[A][B] > need[B] ? (int)floorf((need[B] - grow[B] * m[A].y) * m[A].w) : 0x7FFFFFFF;
                 // one upper end for the rows of a lane, mostly one: that of the largest
                 const int rel0 = tile * BC + (wc * WC + A) * 32 + 4 * h;  // register I holds row rel0 + 8 * (I / 4) + I % 4
                 const unsigned upper = upper_bits(fmaf(scale[B], up[A][B], halfw[B]));
@@ -579,7 +624,7 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                     if (acc[A][B][I] >= least) {
                         const int pos = mine + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
                         if (pos < SCREEN_STAGE) stage[pos] = entry + (ROW << 12);
-                        else list_row(list, cnt, q0 + col, row0, ct_begin * (long)BC + rel0 + ROW, K, upper_value(upper));
+                        else list_row(list, cnt, low, q0 + col, row0, ct_begin * (long)BC + rel0 + ROW, K, upper_value(upper));
                     }
                     mine += __popcll(mask);
                 });
@@ -627,40 +672,90 @@ __device__ __forceinline__ float stage_query(const T *qrow, int d, int vec, u32x
     return inv_length((ss[0] + ss[1]) + (ss[2] + ss[3]));
 }
 
+// The deviations above the mean that a share p of a normal distribution exceeds (Abramowitz and Stegun, 26.2.23).
+__device__ __forceinline__ float normal_above(float p) {
+    const float t = sqrtf(-2.f * __logf(p < 0.5f ? p : 1.f - p));
+    const float z = t - (2.515517f + t * (0.802853f + t * 0.010328f)) / (1.f + t * (1.432788f + t * (0.189269f + t * 0.001308f)));
+    return p < 0.5f ? z : -z;
+}
+
+// The share of the rows that a query lists whose bound is `bound`, from what the sample has left of it: of 128 rows at a time
+// the mean of the largest cosine, and how many came within the error of that (`near`).  The cosines of unrelated rows are near
+// enough to normal, and only the time of a call depends on this: the largest of 128 lies where 0.56 / 128 of the
+// distribution is above it (the median), and from there the number within the error gives the error in deviations.
+__device__ __forceinline__ float listed_share(float bound, float largest, float near, float error) {
+    const float z = normal_above(0.56f / 128.f);
+    const float width = z - normal_above(fminf(near, 127.f) / 128.f);
+    return 0.5f * erfcf((z + ((bound - largest) / error - 1.f) * width) * 0.70710678f);
+}
+
+// What k_screen_seed goes by to count a query as lost.
+struct ScreenCrowd {
+    const int *near;       // per query, over the `groups` of 128 rows of the sample: how many came within the error of the largest
+    const float *largest;  // and the sum of the largest cosines
+    float groups;
+    float rows, most;      // of so many rows it may list so many
+    int heavy;             // LISTED: rows that still count
+    int *lost;
+    int most_lost;
+};
+#define SCREEN_COUNTED 8  // of so many queries one is counted in `lost` (atomic additions to one address: 10 ns each)
+
 // A better bound, a wave for each query: the cosine with its best row of the sample (seed), or with the row of the highest
-// upper end that is listed so far (the bound was short of it by the error).
+// upper end that is listed so far (the bound was short of it by the error).  And *lost counts the queries whose lists can be
+// foreseen to flood, or to take more work than the products save.
 template <typename T, bool LISTED>
 __global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
-                                                     long n, long K, int d, int vec, const u64 *__restrict__ seed,
+                                                     long n, long K, int d, int vec, const ScreenQuery *__restrict__ qm,
+                                                     const float4 *__restrict__ meta, const u64 *__restrict__ seed,
                                                      const int *__restrict__ cnt, const uint2 *__restrict__ list,
-                                                     unsigned *__restrict__ low) {
+                                                     unsigned *__restrict__ low, ScreenCrowd crowd) {
     __shared__ u32x4_t sh_q[4][SISO_SCREEN_DIM * sizeof(T) / 16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long q = (long)blockIdx.x * 4 + wave;
-    if (q >= n) return;
-    long r = K;
-    if constexpr (LISTED) {
-        const int listed = cnt[q] < SCREEN_LIST ? cnt[q] : SCREEN_LIST;
-        u64 high = 0;
-        for (int i = lane; i < listed; i += 64) {
-            const uint2 e = list[(size_t)q * SCREEN_LIST + i];
-            const u64 key = pack_key(__uint_as_float(e.y), e.x);
-            high = key > high ? key : high;
-        }
+    if (q >= n || (LISTED && *crowd.lost > crowd.most_lost)) return;
+    const float had = unordered_bits(low[q]);
+    const int many = LISTED ? cnt[q] : 0, listed = many < SCREEN_LIST ? many : SCREEN_LIST;
+    if (had == INFINITY && many <= SCREEN_LIST) return;  // (no list)
+    bool lost = many > SCREEN_LIST;
+    if (!lost) {
+        long r = K;
+        if constexpr (LISTED) {
+            u64 high = 0;
+            for (int i = lane; i < listed; i += 64) {
+                const uint2 e = list[(size_t)q * SCREEN_LIST + i];
+                const u64 key = pack_key(__uint_as_float(e.y), e.x);
+                high = key > high ? key : high;
+            }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const u64 o = __shfl_xor(high, off);
-            high = o > high ? o : high;
+            for (int off = 32; off > 0; off >>= 1) {
+                const u64 o = __shfl_xor(high, off);
+                high = o > high ? o : high;
+            }
+            if (high != 0) r = (long)(0xFFFFFFFFu - (unsigned)(high & 0xFFFFFFFFull));
+        } else {
+            if (seed[q] != 0) r = (long)(0xFFFFFFFFu - (unsigned)(seed[q] & 0xFFFFFFFFull));
         }
-        if (high != 0) r = (long)(0xFFFFFFFFu - (unsigned)(high & 0xFFFFFFFFull));
-    } else {
-        if (seed[q] != 0) r = (long)(0xFFFFFFFFu - (unsigned)(seed[q] & 0xFFFFFFFFull));
+        float bound = had;
+        if (r < K) {
+            const T *qrow = Q + (size_t)q * d;
+            const float qi = stage_query(qrow, d, vec, sh_q[wave]);
+            const float cosine = row_product<T>(qrow, sh_q[wave], vec, cent + (size_t)r * d, d, lane) * qi * invn[r];
+            if (cosine == cosine) bound = fmaxf(bound, cosine - 5e-6f);
+        }
+        if constexpr (LISTED) {
+            int left = 0;
+            for (int i = lane; i < listed; i += 64)
+                left += __popcll(__ballot(__uint_as_float(list[(size_t)q * SCREEN_LIST + i].y) > bound));
+            left = __builtin_amdgcn_readfirstlane(left);  // (lane 0 has taken part in every round)
+            lost = left > crowd.heavy;
+        } else if (r < K && crowd.most_lost != SCREEN_WHOLE) {
+            const float e = qm[q].err, error = e + (1.f + e) * meta[r >> 5].y + SCREEN_SLACK;
+            lost = listed_share(bound, crowd.largest[q] / crowd.groups, (float)crowd.near[q] / crowd.groups, error) * crowd.rows > crowd.most;
+        }
+        if (lane == 0 && bound > had) low[q] = ordered_bits(bound);
     }
-    if (r >= K || unordered_bits(low[q]) == INFINITY) return;
-    const T *qrow = Q + (size_t)q * d;
-    const float qi = stage_query(qrow, d, vec, sh_q[wave]);
-    const float cosine = row_product<T>(qrow, sh_q[wave], vec, cent + (size_t)r * d, d, lane) * qi * invn[r];
-    if (lane == 0 && cosine == cosine && cosine - 5e-6f > unordered_bits(low[q])) low[q] = ordered_bits(cosine - 5e-6f);
+    if (lane == 0 && lost && q % SCREEN_COUNTED == 0) atomicAdd(crowd.lost, 1);
 }
 
 // The end of a screened lookup in three steps, so that the long lists (a query that misses leaves up to some hundred rows, one
@@ -676,9 +771,9 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
                                                      long n, int d, int vec, const unsigned *__restrict__ low,
                                                      const int *__restrict__ cnt, const uint2 *__restrict__ list,
-                                                     int *__restrict__ totals, ScreenWork *__restrict__ work, int work_room,
-                                                     u64 *__restrict__ best, float *__restrict__ qinv, int *__restrict__ plain_of,
-                                                     T *__restrict__ plain_rows) {
+                                                     int *__restrict__ totals, int most_lost, ScreenWork *__restrict__ work,
+                                                     int work_room, u64 *__restrict__ best, float *__restrict__ qinv,
+                                                     int *__restrict__ plain_of, T *__restrict__ plain_rows) {
     __shared__ u32x4_t sh_q[4][SISO_SCREEN_DIM * sizeof(T) / 16];
     __shared__ int sh_n[4];
     __shared__ int sh_base;
@@ -690,7 +785,9 @@ __global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, co
     const int listed = q < n ? cnt[q] : 0;
     float bound = unordered_bits(low[q < n ? q : 0]);
     const float qi = stage_query(qrow, d, vec, sh_q[wave]);
-    bool leave = listed == SCREEN_PLAIN || listed > SCREEN_LIST;
+    // (a bound of +inf: no list, or one that was given up)
+    const bool all = totals[2] > most_lost;  // the whole batch was given up: it stays in its order
+    bool leave = all || (listed != SCREEN_NAN && (listed == SCREEN_PLAIN || listed > SCREEN_LIST || bound == INFINITY));
     u64 mine = 0;
     int first = -1, some = 0;
     if (!leave && listed > 0) {
@@ -713,13 +810,17 @@ __global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, co
         }
         for (int i = lane; i < listed; i += 64) {
             const uint2 e = i < 64 ? e0 : ql[i];
-            some += __popcll(__ballot((int)e.x != first && __uint_as_float(e.y) >= bound));
+            some += __popcll(__ballot((int)e.x != first && __uint_as_float(e.y) > bound));
         }
         some = __builtin_amdgcn_readfirstlane(some);
     }
     if (lane == 0) sh_n[wave] = some;
     __syncthreads();
-    if (threadIdx.x == 0) sh_base = atomicAdd(totals, sh_n[0] + sh_n[1] + sh_n[2] + sh_n[3]);
+    if (threadIdx.x == 0) {
+        const int more = sh_n[0] + sh_n[1] + sh_n[2] + sh_n[3];
+        sh_base = more > 0 ? atomicAdd(totals, more) : 0;
+        if (all && blockIdx.x == 0) totals[1] = (int)n;
+    }
     __syncthreads();
     if (q >= n) return;
     int at = sh_base;
@@ -727,7 +828,7 @@ __global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, co
     if (at + some > work_room) leave = true;  // (the entries behind work_room are not read)
     for (int i = lane; i < listed && some > 0; i += 64) {
         const uint2 e = i < 64 ? e0 : ql[i];
-        const bool take = (int)e.x != first && __uint_as_float(e.y) >= bound;
+        const bool take = (int)e.x != first && __uint_as_float(e.y) > bound;
         const u64 mask = __ballot(take);
         const int to = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
         if (take && to < work_room) work[to] = ScreenWork{(int)q, (int)e.x};
@@ -735,10 +836,13 @@ __global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, co
     }
     int place = -1;
     if (leave) {
-        if (lane == 0) place = atomicAdd(totals + 1, 1);
+        if (lane == 0) place = all ? (int)q : atomicAdd(totals + 1, 1);
         place = __builtin_amdgcn_readfirstlane(place);
         T *to = plain_rows + (size_t)place * d;
-        for (int e = lane; e < d; e += 64) to[e] = qrow[e];
+        if (vec)
+            for (int e = lane; e < d * (int)sizeof(T) / 16; e += 64) ((u32x4_t *)to)[e] = sh_q[wave][e];
+        else
+            for (int e = lane; e < d; e += 64) to[e] = qrow[e];
         if (lane == 0) plain_of[place] = (int)q;
     }
     if (lane == 0) {
@@ -985,8 +1089,8 @@ struct ScreenRoom {
     ScreenQuery *qm;
     unsigned *low;
     u64 *seed, *best;
-    int *cnt, *totals, *plain_of, *maybe;
-    float *qinv;
+    int *cnt, *near, *totals, *plain_of, *maybe;
+    float *qinv, *largest;
     uint2 *list;
     ScreenWork *work;
     int work_room;
@@ -997,6 +1101,15 @@ struct ScreenRoom {
 
 int byte_dim(int d) { return d <= 256 ? 256 : (d + 127) / 128 * 128; }
 long up256(long x) { return (x + 255) / 256 * 256; }
+
+// Rows that a query on average can have multiplied again before the kernels of all products are the better way.
+// One row takes about a nanosecond (0.1 ms for 96,000 of 768 bf16 elements), all products of a query 150 ns for 131,072 of
+// them, and 393 for 60,000 of 384 in single precision, whose matrix cores are a sixteenth as fast (1,000 such queries that miss,
+// mean cosine 0.7: 484 us with 96 rows each, 264 with 312).
+int again_per_query(const siso_cache *c, long rows) {
+    const long most = rows / (c->dtype == SISO_F32 ? 192 : 1024);
+    return (int)(most < 96 ? 96 : most > SCREEN_LIST ? SCREEN_LIST : most);
+}
 
 // for lookups of up to n queries (n = 0: for a pair search)
 ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
@@ -1013,11 +1126,13 @@ ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
     r.seed = a.take<u64>(q);
     r.best = a.take<u64>(q);
     r.cnt = a.take<int>(q);
-    r.totals = a.take<int>(2);  // rows to be multiplied again, queries left to the other kernels
+    r.near = a.take<int>(q);
+    r.largest = a.take<float>(q);
+    r.totals = a.take<int>(3);  // rows to be multiplied again, queries left to the other kernels, queries given up before that
     r.plain_of = a.take<int>(q);
     r.plain_rows = a.take<char>((size_t)q * d * (c->dtype == SISO_F32 ? 4 : 2));
     r.qinv = a.take<float>(q);
-    r.work_room = (int)q * SCREEN_WORK;
+    r.work_room = (int)q * again_per_query(c, rows);
     r.work = a.take<ScreenWork>((size_t)r.work_room);
     r.list = a.take<uint2>((size_t)q * SCREEN_LIST);
     r.maybe_count = a.take<u64>(1);
@@ -1076,17 +1191,19 @@ bool make_room(siso_cache *c, ScreenSpace &room, size_t bytes, std::vector<char 
     return true;
 }
 
-// rows (with_rows) and n queries to bytes
+// rows (those of `tiles`, if with_rows) and n queries to bytes
 template <typename T>
-int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *invn, long count, bool with_rows, const T *queries, long n) {
+int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *invn, long count, bool with_rows, const T *queries, long n,
+                const ScreenTiles &tiles, int most_lost) {
     const int d = c->dim, dp = byte_dim(d);
-    const unsigned row_blocks = with_rows ? (unsigned)(up256(count) / 32) : 0u;
+    const long all = up256(count) / 256;
+    const unsigned row_blocks = !with_rows ? 0u : 8u * (unsigned)(tiles.part == 0 ? all : tiles.part == 1 ? tiles.ahead + tiles.some : all - tiles.ahead);
     const dim3 grid(row_blocks + (unsigned)(up256(n) / 32)), block(256);
     const size_t four = 4 * sizeof(T);  // rows that are whole runs of four elements, aligned to them
     const int rv = d % 4 == 0 && (uintptr_t)rows % four == 0 ? 1 : 0, qv = d % 4 == 0 && (uintptr_t)queries % four == 0 ? 1 : 0;
 #define SISO_LAUNCH_BYTES(NCH)                                                                                                  \
     hipLaunchKernelGGL((k_screen_bytes<T, NCH>), grid, block, 0, c->stream, rows, invn, count, row_blocks, rv, r.codes, r.meta, \
-                       queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.totals, d, dp)
+                       queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.totals, d, dp, tiles, most_lost)
     if (dp <= 256) SISO_LAUNCH_BYTES(1);
     else if (dp <= 512) SISO_LAUNCH_BYTES(2);
     else if (dp <= 768) SISO_LAUNCH_BYTES(3);
@@ -1096,7 +1213,7 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *
 }
 
 template <typename T>
-int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
+int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
                   float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain) {
     const ScreenRoom r = screen_room(c->screen.at, c, c->count, n);
     const int d = c->dim, dp = byte_dim(d);
@@ -1109,8 +1226,6 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const
         if (e != hipSuccess) return siso_check_hip(c, e, "hipFuncSetAttribute(k_screen_lookup)");
         attr_done = true;
     }
-    int rc = write_bytes<T>(c, r, (const T *)c->cent, c->invn, c->count, with_rows, queries, n);
-    if (rc != SISO_OK) return rc;
     const T *cent = (const T *)c->cent;
     const int vec = (size_t)d * sizeof(T) % 16 == 0 && ((uintptr_t)queries & 15) == 0 ? 1 : 0;
     const dim3 fours((unsigned)((n + 3) / 4)), block(256);
@@ -1118,15 +1233,41 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const
     // more than a quarter.
     long some = 256 / nqt > tiles / 128 ? 256 / nqt : tiles / 128;
     if (some > tiles / 4) some = tiles / 4;
-    if (some > 0) {
-        hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, r.codes,
-                           r.meta, r.qm, r.low, r.seed, r.cnt, r.list, 0L, c->count, dp, 1, (int)some, (int)nqt, 1, (int)(tiles / some));
-        hipLaunchKernelGGL((k_screen_seed<T, false>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.seed,
-                           r.cnt, r.list, r.low);
-    }
     // Much work: an eighth of the tiles first, and better bounds from what it has listed, for queries that are near nothing (a
     // bound from 2,000 rows lets some 700 of 131,072 pass, one from 16,000 some 200).
-    const long ahead = tiles * nqt >= 32 * 256 ? (tiles / 8 * nqt >= 512 ? tiles / 8 : (512 + nqt - 1) / nqt) : 0;
+    const long ahead = tiles * nqt >= 32 * 256 ? tiles / 8 : 0;
+    // Given up (see above): never where the option asks for the bytes.
+    // A batch of which a part f is lost costs its bytes and f of all products (more, as fewer do not fill the chip): in bf16 the bytes
+    // are more than half of it, in single precision a quarter to a tenth.  Rows of mean cosine m, eight to sixteen near each
+    // other, all products / screened to the end / as it is here, us:
+    //   no query misses, m 0.5   bf16  4,096 x 131,072 x 768   623 / 489 / 493     fp32  1,000 x 60,000 x 384   393 / 103 / 106
+    //   30 % miss, m 0.5         bf16  4,096 x 131,072 x 768   621 / 788 / 770     fp32  1,000 x 60,000 x 384   393 / 119 / 122
+    //   all miss, m 0.5          bf16  4,096 x 131,072 x 768   621 / 1,094 / 748   fp32  1,000 x 60,000 x 384   393 / 158 / 159
+    //   all miss, m 0.7          bf16  8,192 x 131,072 x 1,024  1,639 / 4,460 / 1,663   fp32  4,096 x 60,000 x 768  2,968 / 3,772 / 3,058
+    //   all miss, m 0.9          bf16  4,096 x 131,072 x 768   612 / 10,899 / 659  fp32  1,000 x 60,000 x 384   393 / 1,232 / 449
+    const bool stay = c->opt_screen == 1, f32 = c->dtype == SISO_F32;
+    const int most_lost = stay ? SCREEN_WHOLE : (int)((f32 ? 3 * n / 4 : n / 2) / SCREEN_COUNTED);
+    ScreenCrowd crowd = {r.near, r.largest, 2.f * some, (float)c->count, SCREEN_LIST / 2, 0, r.totals + 2, most_lost};
+    if (ahead > 0) {
+        const long flood = SCREEN_LIST * ahead / tiles, worth = c->count / (f32 ? 800 : 6500);
+        crowd.rows = ahead * 256.f;
+        crowd.heavy = (int)(worth < flood ? worth : flood);
+    } else if (3 * again_per_query(c, c->count) < SCREEN_LIST) {  // (the bound gets better yet, some two times fewer rows count)
+        crowd.most = 1.5f * again_per_query(c, c->count);
+    }
+    int *lost = r.totals + 2;
+    // The bytes of the rows that are looked at first, and the others only once the batch is not given up (of more queries they are
+    // the smaller part: 500 / n of the time that all products take in bf16).
+    ScreenTiles which = {with_rows && whole && ahead > 0 && n <= 8192 ? 1 : 0, (int)ahead, (int)some, some > 0 ? (int)(tiles / some) : 1};
+    int rc = write_bytes<T>(c, r, cent, c->invn, c->count, with_rows, queries, n, which, most_lost);
+    if (rc != SISO_OK) return rc;
+    if (some > 0) {
+        hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, r.codes,
+                           r.meta, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, 0L, c->count, dp, 1, (int)some, (int)nqt, 1, which.stride,
+                           lost, most_lost);
+        hipLaunchKernelGGL((k_screen_seed<T, false>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.qm,
+                           r.meta, r.seed, r.cnt, r.list, r.low, crowd);
+    }
     siso_prof_begin(c);
     for (int part = ahead > 0 ? 0 : 1; part < 2; ++part) {
         const long t0 = part == 0 ? 0 : ahead, row0 = t0 * 256;
@@ -1134,15 +1275,22 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, const
         BytePlan p;
         if (!siso_byte_plan(c, rows, n, dp, SCREEN_TILES, &p)) return siso_fail(c, SISO_EINVAL, "screened lookup: no plan");
         hipLaunchKernelGGL(k_screen_lookup<false>, dim3((unsigned)p.grid), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes,
-                           r.codes + (size_t)row0 * dp, r.meta + t0 * 8, r.qm, r.low, r.seed, r.cnt, r.list, row0, rows, dp,
-                           p.tiles_per_slice, p.slices, p.nqt, p.qb, 1);
-        if (part == 0)
-            hipLaunchKernelGGL((k_screen_seed<T, true>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.seed,
-                               r.cnt, r.list, r.low);
+                           r.codes + (size_t)row0 * dp, r.meta + t0 * 8, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, row0, rows,
+                           dp,
+                           p.tiles_per_slice, p.slices, p.nqt, p.qb, 1, lost, most_lost);
+        if (part == 0) {
+            hipLaunchKernelGGL((k_screen_seed<T, true>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.qm,
+                               r.meta, r.seed, r.cnt, r.list, r.low, crowd);
+            if (which.part == 1) {
+                which.part = 2;
+                rc = write_bytes<T>(c, r, cent, c->invn, c->count, true, queries, 0, which, most_lost);
+                if (rc != SISO_OK) return rc;
+            }
+        }
     }
     siso_prof_end(c);
     hipLaunchKernelGGL(k_screen_pick<T>, fours, block, 0, c->stream, queries, cent, c->invn, n, d, vec, r.low, r.cnt, r.list, r.totals,
-                       r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
+                       most_lost, r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
     hipLaunchKernelGGL(k_screen_score<T>, dim3((unsigned)(n < 4096 ? (n + 1) / 2 : 2048)), block, 0, c->stream, queries, cent, c->invn, d, vec,
                        r.totals, r.work, r.work_room, r.qinv, r.best);
     hipLaunchKernelGGL(k_screen_write, dim3((unsigned)((n + 255) / 256)), block, 0, c->stream, n, q_base, r.cnt, r.best, tl, out_idx, out_sim,
@@ -1163,7 +1311,7 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
         attr_done = true;
     }
     hipLaunchKernelGGL(k_screen_clear, dim3(1), dim3(1), 0, c->stream, r.maybe_count);
-    const int rc = write_bytes<T>(c, r, rows, invn, count, true, rows, 0);
+    const int rc = write_bytes<T>(c, r, rows, invn, count, true, rows, 0, ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE);
     if (rc != SISO_OK) return rc;
     int qb = 8;
     while (qb > 1 && qb > up256(count) / 256) qb >>= 1;
@@ -1190,7 +1338,7 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
 // unrelated rows crowd together (deviation d^-1/2), and ever more rows are near the best.
 int siso_screen_wanted(const siso_cache *c, long n) {
     if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->count < 1 || n < 1 || c->dim > SISO_SCREEN_DIM) return 0;
-    if (c->opt_screen == 1) return 1;
+    if (c->opt_screen == 1 || c->opt_screen == 3) return 1;
     if (c->path != SISO_PATH_AUTO || c->opt_mfma_config != 0 || c->opt_tiles_per_slice != 0 || c->opt_mfma_qblock != 0) return 0;
     const double work = 2.0 * (double)n * (double)c->count * c->dim;
     return c->dim >= 128 && (c->dtype == SISO_F32 ? n > 128 && work >= 8e9 : n >= 768 && work >= 7.5e11);
@@ -1240,7 +1388,7 @@ void siso_screen_release(siso_cache *c) {
     delete c->screen_kept;
 }
 
-int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
+int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
                        float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain) {
     // A graph that records the launches goes on using the workspace when a larger call has outgrown it.
     if (!c->screen_recorded && capturing(c)) {
@@ -1252,9 +1400,9 @@ int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_row
         }
         c->screen_recorded = 1;
     }
-    return c->dtype == SISO_F32 ? screen_launch<float>(c, (const float *)queries, n, with_rows, tl, q_base, out_idx, out_sim, out_hit,
+    return c->dtype == SISO_F32 ? screen_launch<float>(c, (const float *)queries, n, with_rows, whole, tl, q_base, out_idx, out_sim, out_hit,
                                                        access, owner, members, plain)
-                                : screen_launch<bf16_t>(c, (const bf16_t *)queries, n, with_rows, tl, q_base, out_idx, out_sim, out_hit,
+                                : screen_launch<bf16_t>(c, (const bf16_t *)queries, n, with_rows, whole, tl, q_base, out_idx, out_sim, out_hit,
                                                         access, owner, members, plain);
 }
 
@@ -1265,7 +1413,7 @@ int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_row
 int siso_screen_pairs_wanted(const siso_cache *c, long count, float threshold) {
     if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->opt_merge_config != 0 || count < 2 || c->dim > SISO_SCREEN_DIM) return 0;
     if (!(threshold >= 0.25f)) return 0;
-    if (c->opt_screen == 1) return 1;
+    if (c->opt_screen == 1 || c->opt_screen == 3) return 1;
     const double work = (double)count * (double)count * c->dim;
     return c->dim >= 128 && work >= (c->dtype == SISO_F32 ? 1.5e9 : 2.5e10);
 }

@@ -1255,7 +1255,7 @@ extern "C" int siso_set_option(siso_cache *c, const char *name, long value) {
     if (!strcmp(name, "mfma_config")) c->opt_mfma_config = (int)value;
     else if (!strcmp(name, "tiles_per_slice")) c->opt_tiles_per_slice = (int)value;
     else if (!strcmp(name, "merge_config")) c->opt_merge_config = (int)value;
-    else if (!strcmp(name, "screen") && value <= 2) c->opt_screen = (int)value;
+    else if (!strcmp(name, "screen") && value <= 3) c->opt_screen = (int)value;
     else if (!strcmp(name, "screen_room")) c->opt_screen_room = (int)value;
     else if (!strcmp(name, "mfma_qblock")) c->opt_mfma_qblock = (int)value;
     else if (!strcmp(name, "fold_spin_limit")) c->opt_fold_spin_limit = (int)value;
@@ -1561,7 +1561,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
             // (the gathered rows of left-over queries are aligned: a batch that those kernels refuse is refused here)
             if (plain.path != SISO_PATH_SCALAR && !siso_mfma_aligned(queries)) return siso_fail(c, SISO_EINVAL, SISO_MFMA_UNALIGNED);
             if (owner) c->mark_in_finalize = 2;
-            rc = siso_screen_lookup(c, q, part, off == 0, tl, off, out_idx + off, out_sim + off, hit,
+            rc = siso_screen_lookup(c, q, part, off == 0, pieces == 1, tl, off, out_idx + off, out_sim + off, hit,
                                     count_index >= 0 ? c->access : nullptr, owner, members, &left);
             if (rc == SISO_OK)
                 rc = plain_lookup(c, plain, left.rows, part, tl, off, out_idx + off, out_sim + off, hit, false, nullptr, owner, members, &left);

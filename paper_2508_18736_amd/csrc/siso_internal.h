@@ -122,7 +122,7 @@ struct siso_cache {
     std::vector<char *> *screen_kept;
 
     // tuning knobs (siso_set_option); 0 = library default
-    int opt_screen;  // 1 = screen wherever the kernels can, 2 = never
+    int opt_screen;  // 1 = screen wherever the kernels can and give no batch up, 2 = never, 3 = screen wherever the kernels can
     int opt_screen_room;  // > 0: KiB that a workspace of screen.hip may take
     int opt_mfma_config;
     int opt_tiles_per_slice;
@@ -531,7 +531,7 @@ int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *
 // Screened lookups and pair searches (screen.hip).
 // siso_screen_wanted: is a lookup of n queries to be screened?  If so, and if siso_screen_room finds room (0 = there is
 // none: the lookup goes without), siso_screen_lookup takes up to SISO_SCREEN_PIECE queries at a time (with_rows: the rows have to
-// be written as bytes, for the first piece of a call) and leaves some to the other kernels: *plain names them (all on the
+// be written as bytes, for the first piece of a call; whole: it is the only one) and leaves some to the other kernels: *plain names them (all on the
 // device, written by the launch): how many, which, and their rows one behind the other; vec: how their products are summed
 // (see k_lookup_finalize).
 #define SISO_SCREEN_DIM 1024  // largest dimension
@@ -547,7 +547,7 @@ void siso_screen_reserve(siso_cache *c, long n);  // siso_reserve: room for a fu
 int siso_screen_pairs_room(siso_cache *c, long rows);
 void siso_screen_done(siso_cache *c);
 void siso_screen_release(siso_cache *c);
-int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, const ThetaList &tl, long q_base, int *out_idx,
+int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
                        float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain);
 // The same for pairs above a threshold (room: siso_screen_pairs_room; siso_screen_done, at the end of a call, gives
 // back what is larger than the library keeps between calls).  Behind it the search of all pairs has to be

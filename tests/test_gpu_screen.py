@@ -143,6 +143,76 @@ def test_more_rows_near_the_best_than_are_multiplied_again(siso, dtype):
     check(idx, sim, q, c)
 
 
+def crowded(g, K, d, n, mean, miss, dtype):
+    """Rows with a common direction (mean cosine `mean`), eight near each other at a time; a share `miss` of the queries is near
+    none of them."""
+    mu = torch.randn(1, d, device=DEV, generator=g)
+    mu = mu / mu.norm()
+
+    def vectors(k):
+        return mean ** 0.5 * mu + ((1 - mean) / d) ** 0.5 * torch.randn(k, d, device=DEV, generator=g)
+
+    c = rows_near(g, vectors(-(-K // 8)), K, 0.08, dtype)
+    q = rows_near(g, c, n, 0.08, dtype)
+    new = torch.rand(n, 1, device=DEV, generator=g) < miss
+    return c, torch.where(new, vectors(n).to(dtype), q).contiguous()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("K,n,d,mean,miss", [(20011, 1300, 384, 0.9, 1.0), (20011, 700, 768, 0.8, 0.6), (140003, 4001, 128, 0.95, 0.7),
+                                             (140003, 4001, 256, 0.9, 0.4)])
+def test_crowded_rows(siso, dtype, K, n, d, mean, miss):
+    """Lists that flood, one by one and so many that the batch is given up, after the sample and after the first eighth of the
+    rows (the last sizes): the results are those of the kernels of all products."""
+    print(f"case: screen crowded {dtype} K={K} n={n} d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K + n)
+    c, q = crowded(g, K, d, n, mean, miss, TYPES[dtype])
+    q[0] = 0
+    q[n // 2, 1] = float("nan")
+    q[n - 1] *= 1e-17
+    c[5] = 0
+    c[K - 2, 3] = float("inf")
+    want = make(siso, c, dtype, screen=2).lookup(q, 0.85)
+    rest = torch.ones(n, dtype=torch.bool, device=DEV)
+    rest[[0, n // 2, n - 1]] = False
+    u = unit(c)
+    u[[5, K - 2]] = 0
+    for screen in (3, 1):
+        idx, sim, hit = make(siso, c, dtype, screen=screen).lookup(q, 0.85)
+        assert idx[n // 2] == -1 and torch.isnan(sim[n // 2]) and idx[0] == want[0][0] and sim[0] == 0
+        assert idx[n - 1] == want[0][n - 1] and torch.equal(hit[~rest], want[2][~rest])
+        assert (sim - want[1])[rest].abs().max() <= 2 * TOL
+        assert torch.equal(hit[rest], (sim[rest] > 0.85).to(torch.uint8))
+        # 64 bits: the named row's cosine is the value, and the best to within the roundings
+        w = unit(q)[rest]
+        assert ((w * u[idx[rest].long()]).sum(1) - sim[rest].double()).abs().max() <= TOL
+        other = (w * u[want[0][rest].long()]).sum(1)
+        assert (other - sim[rest].double()).max() <= 2 * TOL
+
+
+def test_crowded_rows_do_not_pay_twice(siso):
+    """The default on rows with a common direction and queries that miss: about the time of the kernels of all products (1.05 to
+    1.15 times where it was 4 to 18 times; the line is far above what machines and runs differ by)."""
+    print("case: screen time of crowded rows", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(31)
+    for dtype, K, n, d, mean in (("bf16", 131072, 4096, 768, 0.9), ("f32", 60000, 1000, 384, 0.9)):
+        c, q = crowded(g, K, d, n, mean, 1.0, TYPES[dtype])
+        took = []
+        for screen in (2, 0):
+            cache = make(siso, c, dtype, screen=screen)
+            assert cache.screened(n) == (screen == 0)
+            cache.reserve(n)
+            cache.lookup(q, 0.85)
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            for _ in range(10):
+                cache.lookup(q, 0.85)
+            end.record()
+            torch.cuda.synchronize()
+            took.append(begin.elapsed_time(end))
+        assert took[1] < 2 * took[0], took
+
+
 def test_batches_of_several_pieces_and_the_update_behind_them(siso):
     print("case: screen pieces", flush=True)
     g = torch.Generator(device=DEV).manual_seed(11)
