@@ -1420,14 +1420,15 @@ struct PlainLookup {
     int path, slices;
     u64 *keys;
 };
-static int plan_plain(siso_cache *c, long n, u64 *static_keys, long static_cap, PlainLookup *p) {
+// left: for what a screened lookup leaves over
+static int plan_plain(siso_cache *c, long n, u64 *static_keys, long static_cap, bool left, PlainLookup *p) {
     int slices = 1;
     const int path = c->count > 0 ? choose_path(c, n) : SISO_PATH_SCALAR;
     if (c->dtype == SISO_FP8 && c->count > 0 && path == SISO_PATH_SCALAR && !siso_tile_preferred(c, n))
         return siso_fail(c, SISO_EINVAL, "siso_lookup: the 8-bit storage has no scalar kernel");
     if (c->count > 0) {
         switch (path) {
-            case SISO_PATH_SCALAR: slices = siso_tile_slices(c, n); break;
+            case SISO_PATH_SCALAR: slices = siso_tile_slices(c, n, left); break;
             case SISO_PATH_MFMA: slices = siso_mfma_slices(c, n); break;
             case SISO_PATH_SKINNY: slices = siso_skinny_slices(c, n); break;
         }
@@ -1556,7 +1557,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
             const char *q = (const char *)queries + (size_t)off * row;
             unsigned char *hit = out_hit ? out_hit + (size_t)off * m : nullptr;
             ScreenPlain left;
-            rc = plan_plain(c, part, nullptr, 0, &plain);
+            rc = plan_plain(c, part, nullptr, 0, true, &plain);
             if (rc != SISO_OK) break;
             // (the gathered rows of left-over queries are aligned: a batch that those kernels refuse is refused here)
             if (plain.path != SISO_PATH_SCALAR && !siso_mfma_aligned(queries)) return siso_fail(c, SISO_EINVAL, SISO_MFMA_UNALIGNED);
@@ -1568,7 +1569,7 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
         }
         return rc;
     }
-    int rc = plan_plain(c, n, static_keys, static_cap, &plain);
+    int rc = plan_plain(c, n, static_keys, static_cap, false, &plain);
     if (rc == SISO_OK)
         rc = plain_lookup(c, plain, queries, n, tl, 0, out_idx, out_sim, out_hit, !static_keys, folded, owner, members, nullptr);
     if (rc == SISO_OK && owner && !(folded && *folded)) c->mark_in_finalize = 2;  // done

@@ -501,7 +501,7 @@ int siso_check_hip(siso_cache *c, hipError_t e, const char *what);
 //
 // `many` (NULL = n): on the device, how many of the n queries there are: a workgroup beyond them leaves at once.
 int siso_tile_preferred(const siso_cache *c, long n);  // 1 = small: rather these kernels, also where siso_mfma_* could
-int siso_tile_slices(const siso_cache *c, long n);
+int siso_tile_slices(const siso_cache *c, long n, bool left = false);
 long siso_tile_keys_bound(const siso_cache *c, long n);
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, const int *many = nullptr);
 #define SISO_MFMA_UNALIGNED "bf16 lookup: queries must be 16-byte aligned"
