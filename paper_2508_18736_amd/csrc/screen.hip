@@ -41,6 +41,7 @@ typedef PipeCfg<4, 2, 2, 4, 2, 128, true, 1> ByteCfg;  // 256 x 256 tile, waves 
 #define SCREEN_MAYBE (1L << 20)   // pairs whose cosine has to be formed anew
 #define SCREEN_SLACK 2e-5f        // roundings of the lengths, of the unit rows and of the sums formed anew (about 4e-6 in all)
 #define SCREEN_WHOLE 0x7FFFFFFF   // most_lost: never given up
+#define SCREEN_COUNTED 8          // of so many queries one is looked at for `lost` (atomic additions to one address: 10 ns each)
 #define SCREEN_PLAIN (-2)         // instead of a list's length: this query is left to the other kernels
 #define SCREEN_NAN (-1)           // and this one holds a NaN or an infinity
 
@@ -249,8 +250,8 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
 struct ScreenTiles {
     int part, ahead, some, stride;  // part 0, 1, 2
 };
-// Blocks below row_blocks: rows of the cache; the others: queries.
-template <typename T, int NCH>
+// Blocks below row_blocks: rows of the cache; the others: queries.  PARTS: tiles.part is not 0.
+template <typename T, int NCH, bool PARTS>
 __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows, const float *__restrict__ invn, long K,
                                                       unsigned row_blocks, int row_vec, signed char *__restrict__ codes,
                                                       float4 *__restrict__ meta, const T *__restrict__ queries, long n, int query_vec,
@@ -260,14 +261,16 @@ __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows
                                                       int d, int dp, ScreenTiles tiles, int most_lost) {
     if (blockIdx.x < row_blocks) {
         long blk = blockIdx.x;
-        if (tiles.part == 1 && blk >= 8L * tiles.ahead) {
-            const long tile = (blk / 8 - tiles.ahead) * tiles.stride;
-            if (tile < tiles.ahead) return;
-            blk = tile * 8 + blk % 8;
-        } else if (tiles.part == 2) {
-            blk += 8L * tiles.ahead;
-            const long tile = blk / 8;
-            if (totals[2] > most_lost || (tile % tiles.stride == 0 && tile / tiles.stride < tiles.some)) return;
+        if constexpr (PARTS) {
+            if (tiles.part == 2) {
+                blk += 8L * tiles.ahead;
+                const long tile = blk / 8;
+                if (totals[2] > most_lost || (tile % tiles.stride == 0 && tile / tiles.stride < tiles.some)) return;
+            } else if (blk >= 8L * tiles.ahead) {
+                const long tile = (blk / 8 - tiles.ahead) * tiles.stride;
+                if (tile < tiles.ahead) return;
+                blk = tile * 8 + blk % 8;
+            }
         }
         write_bytes_block<T, NCH, true>(blk, rows, invn, K, row_vec, codes, meta, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                         nullptr, d, dp);
@@ -438,7 +441,8 @@ __device__ __forceinline__ void list_row(uint2 *list, int *cnt, unsigned *low, l
 // Rows are collected in LDS and judged by the newest low once more when they are handed over.
 // codes, meta and the K rows are a run of the cache's, from its row number row0 on.
 // SAMPLE: one tile per workgroup, every `stride`-th of them, and only its best row counts: seed[q] = (product, row); and for
-// k_screen_seed, of 128 rows at a time, the largest cosine and how many come within the error of it (ScreenCrowd).
+// k_screen_seed, of 128 rows of every tile, the largest cosine and how many come within the error of it (ScreenCrowd; every
+// SCREEN_COUNTED-th query).
 struct LookupSrc {
     const signed char *c, *q;
     int ct, dp, buf;
@@ -479,7 +483,7 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
         if ((long)ct_begin * BC >= K) return;
     } else {
         if (!pipe_map_block<BC>(K, tiles_per_slice, slices, nqt, qb, qt, s, ct_begin, ct_end)) return;
-        if (ct_end <= ct_begin || *lost > most_lost) return;
+        if (ct_end <= ct_begin) return;
     }
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -488,10 +492,14 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
     unsigned *stage = stages + wave * SCREEN_STAGE;
     int mine = 0;  // rows this wave has collected
 
+    ScreenQuery mine_q[WQ];
+#pragma unroll
+    for (int b = 0; b < WQ; ++b) mine_q[b] = qm[q0 + (wq * WQ + b) * 32 + l32];
+    if (!SAMPLE && *lost > most_lost) return;  // (the two loads on their way together)
     float scale[WQ], rscale[WQ], halfw[WQ], grow[WQ], best[WQ];  // per query: scale, 1 / scale, e + slack, (1 + e) / scale; a lower end
 #pragma unroll
     for (int b = 0; b < WQ; ++b) {
-        const ScreenQuery m = qm[q0 + (wq * WQ + b) * 32 + l32];
+        const ScreenQuery m = mine_q[b];
         scale[b] = m.scale;
         rscale[b] = 1.f / m.scale;
         halfw[b] = m.err + SCREEN_SLACK;
@@ -536,6 +544,8 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                     top = ov;
                     row = orow;
                 }
+                if (h == 0) atomicMax(seed + q0 + (wq * WQ + B) * 32 + l32, pack_key(top, (unsigned)row));
+                if (wc != 0) return;  // (half of the rows will do for the rest)
                 int near = 0;
                 static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
                     constexpr int A = decltype(ia)::value;
@@ -544,8 +554,7 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                     static_for<0, 16>([&](auto ii) __attribute__((always_inline)) { near += acc[A][B][decltype(ii)::value] >= least ? 1 : 0; });
                 });
                 near += (int)other_half((unsigned)near);
-                if (h == 0) {
-                    atomicMax(seed + q0 + (wq * WQ + B) * 32 + l32, pack_key(top, (unsigned)row));
+                if (h == 0 && l32 % SCREEN_COUNTED == 0) {
                     atomicAdd(near_ + q0 + (wq * WQ + B) * 32 + l32, near);
                     atomicAdd(largest + q0 + (wq * WQ + B) * 32 + l32, top * scale[B]);
                 }
@@ -699,7 +708,6 @@ struct ScreenCrowd {
     int *lost;
     int most_lost;
 };
-#define SCREEN_COUNTED 8  // of so many queries one is counted in `lost` (atomic additions to one address: 10 ns each)
 
 // A better bound, a wave for each query: the cosine with its best row of the sample (seed), or with the row of the highest
 // upper end that is listed so far (the bound was short of it by the error).  And *lost counts the queries whose lists can be
@@ -736,7 +744,14 @@ __global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, co
         } else {
             if (seed[q] != 0) r = (long)(0xFFFFFFFFu - (unsigned)(seed[q] & 0xFFFFFFFFull));
         }
-        float bound = had;
+        float bound = had, error = INFINITY, largest = 0.f, near = 0.f;
+        const bool counted = q % SCREEN_COUNTED == 0;
+        if (!LISTED && r < K && counted) {
+            const float e = qm[q].err;
+            error = e + (1.f + e) * meta[r >> 5].y + SCREEN_SLACK;
+            largest = crowd.largest[q] / crowd.groups;
+            near = (float)crowd.near[q] / crowd.groups;
+        }
         if (r < K) {
             const T *qrow = Q + (size_t)q * d;
             const float qi = stage_query(qrow, d, vec, sh_q[wave]);
@@ -745,13 +760,12 @@ __global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, co
         }
         if constexpr (LISTED) {
             int left = 0;
-            for (int i = lane; i < listed; i += 64)
+            for (int i = lane; i < (counted ? listed : 0); i += 64)
                 left += __popcll(__ballot(__uint_as_float(list[(size_t)q * SCREEN_LIST + i].y) > bound));
             left = __builtin_amdgcn_readfirstlane(left);  // (lane 0 has taken part in every round)
             lost = left > crowd.heavy;
-        } else if (r < K && crowd.most_lost != SCREEN_WHOLE) {
-            const float e = qm[q].err, error = e + (1.f + e) * meta[r >> 5].y + SCREEN_SLACK;
-            lost = listed_share(bound, crowd.largest[q] / crowd.groups, (float)crowd.near[q] / crowd.groups, error) * crowd.rows > crowd.most;
+        } else if (r < K && counted && crowd.most_lost != SCREEN_WHOLE) {
+            lost = listed_share(bound, largest, near, error) * crowd.rows > crowd.most;
         }
         if (lane == 0 && bound > had) low[q] = ordered_bits(bound);
     }
@@ -1201,14 +1215,23 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *
     const dim3 grid(row_blocks + (unsigned)(up256(n) / 32)), block(256);
     const size_t four = 4 * sizeof(T);  // rows that are whole runs of four elements, aligned to them
     const int rv = d % 4 == 0 && (uintptr_t)rows % four == 0 ? 1 : 0, qv = d % 4 == 0 && (uintptr_t)queries % four == 0 ? 1 : 0;
-#define SISO_LAUNCH_BYTES(NCH)                                                                                                  \
-    hipLaunchKernelGGL((k_screen_bytes<T, NCH>), grid, block, 0, c->stream, rows, invn, count, row_blocks, rv, r.codes, r.meta, \
+#define SISO_LAUNCH_BYTES2(NCH, PARTS)                                                                                        \
+    hipLaunchKernelGGL((k_screen_bytes<T, NCH, PARTS>), grid, block, 0, c->stream, rows, invn, count, row_blocks, rv, r.codes, r.meta, \
                        queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.totals, d, dp, tiles, most_lost)
-    if (dp <= 256) SISO_LAUNCH_BYTES(1);
-    else if (dp <= 512) SISO_LAUNCH_BYTES(2);
-    else if (dp <= 768) SISO_LAUNCH_BYTES(3);
-    else SISO_LAUNCH_BYTES(4);
+#define SISO_LAUNCH_BYTES(NCH)                      \
+    if (tiles.part == 0) SISO_LAUNCH_BYTES2(NCH, false); \
+    else SISO_LAUNCH_BYTES2(NCH, true)
+    if (dp <= 256) {
+        SISO_LAUNCH_BYTES(1);
+    } else if (dp <= 512) {
+        SISO_LAUNCH_BYTES(2);
+    } else if (dp <= 768) {
+        SISO_LAUNCH_BYTES(3);
+    } else {
+        SISO_LAUNCH_BYTES(4);
+    }
 #undef SISO_LAUNCH_BYTES
+#undef SISO_LAUNCH_BYTES2
     return siso_check_hip(c, hipGetLastError(), "k_screen_bytes");
 }
 
@@ -1238,22 +1261,26 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
     const long ahead = tiles * nqt >= 32 * 256 ? tiles / 8 : 0;
     // Given up (see above): never where the option asks for the bytes.
     // A batch of which a part f is lost costs its bytes and f of all products (more, as fewer do not fill the chip): in bf16 the bytes
-    // are more than half of it, in single precision a quarter to a tenth.  Rows of mean cosine m, eight to sixteen near each
-    // other, all products / screened to the end / as it is here, us:
-    //   no query misses, m 0.5   bf16  4,096 x 131,072 x 768   623 / 489 / 493     fp32  1,000 x 60,000 x 384   393 / 103 / 106
-    //   30 % miss, m 0.5         bf16  4,096 x 131,072 x 768   621 / 788 / 770     fp32  1,000 x 60,000 x 384   393 / 119 / 122
-    //   all miss, m 0.5          bf16  4,096 x 131,072 x 768   621 / 1,094 / 748   fp32  1,000 x 60,000 x 384   393 / 158 / 159
+    // are more than half of it, in single precision a quarter to a tenth, and some 75 us stand around them: `share` is where the two
+    // ways meet.  Rows of mean cosine m, sixteen near each other, all products / screened to the end / as it is here, us:
+    //   no query misses, m 0.5   bf16  4,096 x 131,072 x 768   623 / 489 / 500     fp32  1,000 x 60,000 x 384   393 / 103 / 106
+    //   30 % miss, m 0.5         bf16  4,096 x 131,072 x 768   621 / 788 / 790     fp32  1,000 x 60,000 x 384   393 / 119 / 123
+    //   all miss, m 0.5          bf16  4,096 x 131,072 x 768   621 / 1,094 / 750   fp32  1,000 x 60,000 x 384   393 / 158 / 163
+    //   30 % miss, m 0.7         bf16  4,096 x 131,072 x 768   617 / 1,097 / 770   fp32  1,000 x 16,000 x 384   118 / 116 / 150
     //   all miss, m 0.7          bf16  8,192 x 131,072 x 1,024  1,639 / 4,460 / 1,663   fp32  4,096 x 60,000 x 768  2,968 / 3,772 / 3,058
-    //   all miss, m 0.9          bf16  4,096 x 131,072 x 768   612 / 10,899 / 659  fp32  1,000 x 60,000 x 384   393 / 1,232 / 449
+    //   all miss, m 0.9          bf16  4,096 x 131,072 x 768   612 / 10,899 / 657  fp32  1,000 x 60,000 x 384   393 / 1,232 / 460
     const bool stay = c->opt_screen == 1, f32 = c->dtype == SISO_F32;
-    const int most_lost = stay ? SCREEN_WHOLE : (int)((f32 ? 3 * n / 4 : n / 2) / SCREEN_COUNTED);
-    ScreenCrowd crowd = {r.near, r.largest, 2.f * some, (float)c->count, SCREEN_LIST / 2, 0, r.totals + 2, most_lost};
+    const double products = 2.0 * (double)n * (double)c->count * d / (f32 ? 1.13e8 : 1.25e9);  // us
+    double share = f32 ? 0.9 - 75 / products : 0.55 - 150 / products;
+    share = share < 0.1 ? 0.1 : share > 0.75 ? 0.75 : share;
+    const int most_lost = stay ? SCREEN_WHOLE : (int)(share * (double)n / SCREEN_COUNTED);
+    ScreenCrowd crowd = {r.near, r.largest, (float)some, (float)c->count, SCREEN_LIST / 2, 0, r.totals + 2, most_lost};
     if (ahead > 0) {
         const long flood = SCREEN_LIST * ahead / tiles, worth = c->count / (f32 ? 800 : 6500);
         crowd.rows = ahead * 256.f;
         crowd.heavy = (int)(worth < flood ? worth : flood);
-    } else if (3 * again_per_query(c, c->count) < SCREEN_LIST) {  // (the bound gets better yet, some two times fewer rows count)
-        crowd.most = 1.5f * again_per_query(c, c->count);
+    } else if (2 * again_per_query(c, c->count) < SCREEN_LIST) {  // (the bound gets better yet: half as many will count)
+        crowd.most = (float)again_per_query(c, c->count);
     }
     int *lost = r.totals + 2;
     // The bytes of the rows that are looked at first, and the others only once the batch is not given up (of more queries they are
