@@ -38,7 +38,6 @@ typedef PipeCfg<4, 2, 2, 4, 2, 128, true, 1> ByteCfg;  // 256 x 256 tile, waves 
 #define SCREEN_LIST 1024          // rows a query's list holds
 #define SCREEN_TILES 16           // tiles of a slice: a row of it is 12 bits
 #define SCREEN_STAGE 896          // rows a wave collects in LDS before they are handed to the queries' lists
-#define SCREEN_MAYBE (1L << 20)   // pairs whose cosine has to be formed anew
 #define SCREEN_SLACK 2e-5f        // roundings of the lengths, of the unit rows and of the sums formed anew (about 4e-6 in all)
 #define SCREEN_WHOLE 0x7FFFFFFF   // most_lost: never given up
 #define SCREEN_COUNTED 8          // of so many queries one is looked at for `lost` (atomic additions to one address: 10 ns each)
@@ -955,13 +954,16 @@ struct PairSrc {
         take();
     }
 };
-#define SCREEN_PAIR_STAGE 256  // pairs a wave collects in LDS
-#define SCREEN_PAIR_LDS (ByteCfg::NSTAGE * ByteCfg::STAGE + 4 * 64 * 4 + 8 * SCREEN_PAIR_STAGE * 8)
+#define SCREEN_PAIR_STAGE 224  // pairs a wave collects in LDS, and as many in doubt
+#define SCREEN_PAIR_LDS (ByteCfg::NSTAGE * ByteCfg::STAGE + 4 * 64 * 4 + 8 * 2 * SCREEN_PAIR_STAGE * 8)
 static_assert(SCREEN_PAIR_LDS <= 160 * 1024, "fits in LDS");
+enum { PAIRS_ALL, PAIRS_FIRST, PAIRS_REST };  // what a launch takes of every workgroup's pairs of tiles
 
 __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_screen_pairs(
-    const signed char *__restrict__ codes, const float4 *__restrict__ meta, long K, int dp, int qb, float threshold,
-    int *__restrict__ out_pairs, long cap, u64 *__restrict__ counter, int *__restrict__ maybe, u64 *__restrict__ maybe_count) {
+    const signed char *__restrict__ codes, const float4 *__restrict__ meta, long K, int dp, int qb, int part, float threshold,
+    int *__restrict__ out_pairs, long cap, u64 *__restrict__ counter, int *__restrict__ maybe, u64 maybe_room,
+    u64 *__restrict__ maybe_count) {
+    if (part == PAIRS_REST && *maybe_count > maybe_room) return;  // (they will all be searched for anew)
     typedef ByteCfg Cfg;
     constexpr int WC = Cfg::WC, WQ = Cfg::WQ, BC = Cfg::BC;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -980,15 +982,30 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
     src.buf = 0;
     src.qt = src.ct = 0;
     if (!src.items.next(src.qt, src.ct)) return;
-    src.take();
     int qt = 0, ct = 0, seq = 0, pairs = 0;
     while (done.next(qt, ct)) ++pairs;
     done.init(tiles, qb);
     done.next(qt, ct);
-    // the pairs this wave has found, handed over when they may not hold those of another instruction (a wave's own: nothing to
-    // wait for, which a buffer of the workgroup would at the end of every tile)
-    int2 *stage = (int2 *)(meta_s + 4 * 64) + wave * SCREEN_PAIR_STAGE;
-    int mine = 0;
+    if (part != PAIRS_ALL) {
+        const int first = (pairs + 7) / 8;
+        if (part == PAIRS_FIRST) {
+            pairs = first;
+        } else {
+            pairs -= first;
+            if (pairs == 0) return;
+            for (int i = 0; i < first; ++i) {
+                src.items.next(src.qt, src.ct);
+                done.next(qt, ct);
+            }
+        }
+    }
+    src.take();
+    // the pairs this wave has found, and those in doubt, handed over when they may not hold those of another instruction (a wave's
+    // own: nothing to wait for, which a buffer of the workgroup would at the end of every tile; and one atomic addition for some
+    // hundred pairs: they all go to one address, 10 ns each)
+    int2 *stage = (int2 *)(meta_s + 4 * 64) + wave * 2 * SCREEN_PAIR_STAGE, *doubt = stage + SCREEN_PAIR_STAGE;
+    int mine = 0, doubts = 0;
+    int over = 0;  // more in doubt than there is room for: all of this is searched for anew
     auto flush = [&]() __attribute__((always_inline)) {
         u64 base = 0;
         if (lane == 0 && mine > 0) base = atomicAdd(counter, (u64)mine);
@@ -1000,6 +1017,15 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                 out_pairs[2 * (base + p) + 1] = e.y;
             }
         mine = 0;
+    };
+    auto flush_doubts = [&]() __attribute__((always_inline)) {
+        u64 base = 0;
+        if (lane == 0 && doubts > 0) base = atomicAdd(maybe_count, (u64)doubts);
+        base = __shfl(base, 0);
+        for (int p = lane; p < doubts; p += 64)
+            if (base + (u64)p < maybe_room) ((int2 *)maybe)[base + p] = doubt[p];
+        over = __builtin_amdgcn_readfirstlane(base + (u64)doubts > maybe_room ? 1 : 0);
+        doubts = 0;
     };
     byte_stream(smem, dp, pairs, src, [&](const i32x16(&acc)[WC][WQ]) __attribute__((always_inline)) {
         const float4 *ma = (const float4 *)(meta_s + (seq & 1) * 128) + wc * WC;
@@ -1018,7 +1044,7 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                 most = fmaxf(most, up[A][B]);
             });
         });
-        if (__ballot(most > threshold) != 0) static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
+        if (over == 0 && __ballot(most > threshold) != 0) static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
             constexpr int A = decltype(ia)::value;
             static_for<0, WQ>([&](auto ib) __attribute__((always_inline)) {
                 constexpr int B = decltype(ib)::value;
@@ -1041,12 +1067,12 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
                     if (mine > SCREEN_PAIR_STAGE - 64) flush();
                     if (sure) stage[mine + before(yes)] = make_int2(icol, j);
                     mine += __popcll(yes);
-                    if (maybe_so != 0) {
-                        u64 base = 0;
-                        if (lane == 0) base = atomicAdd(maybe_count, (u64)__popcll(maybe_so));
-                        base = __shfl(base, 0) + (u64)before(maybe_so);
-                        if (open && base < (u64)SCREEN_MAYBE) ((int2 *)maybe)[base] = make_int2(icol, j);
+                    if (doubts > SCREEN_PAIR_STAGE - 64) {
+                        if (over == 0) flush_doubts();
+                        else doubts = 0;
                     }
+                    if (open) doubt[doubts + before(maybe_so)] = make_int2(icol, j);
+                    doubts += __popcll(maybe_so);
                 });
             });
         });
@@ -1054,42 +1080,95 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
         done.next(qt, ct);
     });
     flush();
+    flush_doubts();
 }
 
 __global__ void k_screen_clear(u64 *maybe_count) { *maybe_count = 0; }
 
-// The pairs in doubt, a wave for each.  More of them than the list holds: nothing is kept, and the kernels of all pairs
-// (which look at the same count) do the search.
+// Behind the first eighth: more in doubt already than their share of the room: the list will not hold.
+__global__ void k_screen_pairs_judge(u64 *maybe_count, u64 most, u64 room) {
+    if (*maybe_count > most) *maybe_count = room + 1;
+}
+
+// The pairs in doubt, a wave for four at a time.  More of them than the list holds: nothing is kept, and the kernels of all pairs
+// (which look at the same count) do the search.  The pairs that are found are collected in LDS: additions to the one counter
+// take 10 ns each (16,000 x 768, rows in groups of eight around the threshold: 518 -> 191 us).
 template <typename T>
 __global__ __launch_bounds__(256) void k_screen_pairs_check(const T *__restrict__ rows, const float *__restrict__ invn, int d, int vec,
-                                                            float threshold, const int *__restrict__ maybe,
+                                                            float threshold, const int *__restrict__ maybe, u64 maybe_room,
                                                             const u64 *__restrict__ maybe_count, int *__restrict__ out_pairs, long cap,
                                                             u64 *__restrict__ counter) {
+    constexpr int R = 4, EPC = 16 / (int)sizeof(T);
+    __shared__ int2 found[4][64];
+    __shared__ int sh_n[4];
+    __shared__ u64 sh_base;
     const u64 many = *maybe_count;
-    const int lane = threadIdx.x & 63;
-    if (many > SCREEN_MAYBE) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (many > maybe_room) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0;
         return;
     }
-    for (u64 p = (u64)blockIdx.x * 4 + (threadIdx.x >> 6); p < many; p += (u64)gridDim.x * 4) {
-        const int i = maybe[2 * p], j = maybe[2 * p + 1];
-        const T *a = rows + (size_t)i * d, *b = rows + (size_t)j * d;
-        float s = 0.f;
-        if (vec) {
-            constexpr int EPC = 16 / (int)sizeof(T);
-            for (int e = lane * EPC; e < d; e += 64 * EPC) s += chunk_dot(*(const u32x4_t *)(a + e), *(const u32x4_t *)(b + e), T());
-        } else {
-            for (int e = lane; e < d; e += 64) s += widen(a[e]) * widen(b[e]);
+    int mine = 0;  // pairs this wave has found: at most 64
+    auto hand_over = [&](u64 base) {
+        if (lane < mine && base + (u64)lane < (u64)cap) {  // (the caller's array: aligned to an int)
+            out_pairs[2 * (base + lane)] = found[wave][lane].x;
+            out_pairs[2 * (base + lane) + 1] = found[wave][lane].y;
         }
-        const float cosine = wave_sum(s) * invn[i] * invn[j];
-        if (lane == 0 && cosine > threshold) {
-            const u64 at = atomicAdd(counter, 1ull);
-            if (at < (u64)cap) {
-                out_pairs[2 * at] = i;
-                out_pairs[2 * at + 1] = j;
+    };
+    for (u64 p = ((u64)blockIdx.x * 4 + wave) * R; p < many; p += (u64)gridDim.x * 4 * R) {
+        int i[R], j[R];
+        const T *a[R], *b[R];
+        float s[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const u64 at = p + r < many ? p + r : p;
+            i[r] = maybe[2 * at];
+            j[r] = maybe[2 * at + 1];
+            a[r] = rows + (size_t)i[r] * d;
+            b[r] = rows + (size_t)j[r] * d;
+            s[r] = 0.f;
+        }
+        if (vec) {
+            for (int e = lane * EPC; e < d; e += 64 * EPC) {
+                u32x4_t x[R], y[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    x[r] = *(const u32x4_t *)(a[r] + e);
+                    y[r] = *(const u32x4_t *)(b[r] + e);
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) s[r] += chunk_dot(x[r], y[r], T());
+            }
+        } else {
+            for (int e = lane; e < d; e += 64)
+#pragma unroll
+                for (int r = 0; r < R; ++r) s[r] += widen(a[r][e]) * widen(b[r][e]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float cosine = wave_sum(s[r]) * invn[i[r]] * invn[j[r]];
+            if (__builtin_amdgcn_readfirstlane(cosine > threshold && p + r < many ? 1 : 0) != 0) {
+                if (lane == 0) found[wave][mine] = make_int2(i[r], j[r]);
+                ++mine;
             }
         }
+        if (mine > 64 - R) {
+            u64 base = 0;
+            if (lane == 0) base = atomicAdd(counter, (u64)mine);
+            hand_over(__shfl(base, 0));
+            mine = 0;
+        }
     }
+    if (lane == 0) sh_n[wave] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int all = sh_n[0] + sh_n[1] + sh_n[2] + sh_n[3];
+        sh_base = all > 0 ? atomicAdd(counter, (u64)all) : 0;
+    }
+    __syncthreads();
+    u64 base = sh_base;
+    for (int w = 0; w < wave; ++w) base += (u64)sh_n[w];
+    hand_over(base);
 }
 
 // ---------------------------------------------------------------------------------------------------------------------
@@ -1109,7 +1188,7 @@ struct ScreenRoom {
     ScreenWork *work;
     int work_room;
     void *plain_rows;
-    u64 *maybe_count;
+    u64 *maybe_count, maybe_room;
     size_t bytes;
 };
 
@@ -1123,6 +1202,16 @@ long up256(long x) { return (x + 255) / 256 * 256; }
 int again_per_query(const siso_cache *c, long rows) {
     const long most = rows / (c->dtype == SISO_F32 ? 192 : 1024);
     return (int)(most < 96 ? 96 : most > SCREEN_LIST ? SCREEN_LIST : most);
+}
+
+// Pairs that can be in doubt before the search of all pairs is the better way: half of what that takes, at 0.6 ns for a pair of
+// bf16 rows of 768 elements (65,536 of them in groups of 32 around the threshold, a million pairs in doubt: 1,495 -> 2,025 us,
+// all pairs 3,121).
+long pairs_in_doubt(const siso_cache *c, long rows) {
+    const bool f32 = c->dtype == SISO_F32;
+    const double all = (double)rows * (double)rows * c->dim / (f32 ? 1.13e5 : 1.25e6);  // ns
+    const double most = all / 2 / (0.6 * c->dim * (f32 ? 4.0 : 2.0) / 1536);
+    return most < 65536 ? 65536 : most > 16777216 ? 16777216 : (long)most;
 }
 
 // for lookups of up to n queries (n = 0: for a pair search)
@@ -1150,7 +1239,8 @@ ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
     r.work = a.take<ScreenWork>((size_t)r.work_room);
     r.list = a.take<uint2>((size_t)q * SCREEN_LIST);
     r.maybe_count = a.take<u64>(1);
-    r.maybe = a.take<int>(n == 0 ? 2 * SCREEN_MAYBE : 0);
+    r.maybe_room = n == 0 ? (u64)pairs_in_doubt(c, rows) : 0;
+    r.maybe = a.take<int>(2 * (size_t)r.maybe_room);
     r.bytes = a.used;
     return r;
 }
@@ -1342,12 +1432,28 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
     if (rc != SISO_OK) return rc;
     int qb = 8;
     while (qb > 1 && qb > up256(count) / 256) qb >>= 1;
-    hipLaunchKernelGGL(k_screen_pairs, dim3(256), dim3(ByteCfg::NT), SCREEN_PAIR_LDS, c->stream, r.codes, r.meta, count, dp, qb, threshold,
-                       out_pairs, cap, counter, r.maybe, r.maybe_count);
+    // Where a workgroup has eight pairs of tiles and more, an eighth of them goes first and tells whether those in doubt will be too
+    // many (half as many again as their share, so that an uneven order of the rows does not decide).  It takes some 15 us more,
+    // and saves half of what all pairs take in bf16, a fifth in single precision: there, and below, the list decides when it is
+    // full.  Rows of mean cosine 0.88 at a threshold of 0.9, all pairs / before / now, us: bf16 131,072 x 768 11,512 / 1,623,000 /
+    // 12,779, 16,000 x 768 232 / 24,300 / 385; fp32 8,000 x 768 503 / 6,554 / 573.
+    const long tiles = up256(count) / 256, all = tiles * (tiles + 1) / 2;
+    auto search = [&](int part) {
+        hipLaunchKernelGGL(k_screen_pairs, dim3(256), dim3(ByteCfg::NT), SCREEN_PAIR_LDS, c->stream, r.codes, r.meta, count, dp, qb, part, threshold,
+                           out_pairs, cap, counter, r.maybe, r.maybe_room, r.maybe_count);
+    };
+    if (all >= 8 * 256 && c->dtype != SISO_F32) {
+        search(PAIRS_FIRST);
+        hipLaunchKernelGGL(k_screen_pairs_judge, dim3(1), dim3(1), 0, c->stream, r.maybe_count,
+                           (u64)(1.5 * (0.125 + 128.0 / (double)all) * (double)r.maybe_room), r.maybe_room);
+        search(PAIRS_REST);
+    } else {
+        search(PAIRS_ALL);
+    }
     const int vec = (size_t)d * sizeof(T) % 16 == 0 && ((uintptr_t)rows & 15) == 0 ? 1 : 0;
-    hipLaunchKernelGGL(k_screen_pairs_check<T>, dim3(512), dim3(256), 0, c->stream, rows, invn, d, vec, threshold, r.maybe, r.maybe_count,
-                       out_pairs, cap, counter);
-    *redo = PairsRedo{r.maybe_count, SCREEN_MAYBE};
+    hipLaunchKernelGGL(k_screen_pairs_check<T>, dim3(512), dim3(256), 0, c->stream, rows, invn, d, vec, threshold, r.maybe, r.maybe_room,
+                       r.maybe_count,                       out_pairs, cap, counter);
+    *redo = PairsRedo{r.maybe_count, r.maybe_room};
     return siso_check_hip(c, hipGetLastError(), "k_screen_pairs");
 }
 

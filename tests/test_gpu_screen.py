@@ -453,3 +453,57 @@ def test_more_pairs_in_doubt_than_the_list_holds(siso):
         want, many = make(siso, x, dtype, screen=2).merge(0.9, K * K)
         assert total == many > 100000
         assert pair_set(pairs, total) == pair_set(want, many)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cosine,crowd", [(0.9, 0.0), (0.999, 0.88)])
+def test_pairs_of_a_large_search(siso, dtype, cosine, crowd):
+    """An eighth of the tiles first (bf16): many pairs in doubt, and more of them than the list can hold, which the first eighth
+    tells.  The pairs are those of the kernels of all pairs, but for cosines within the roundings of the threshold."""
+    print(f"case: screen large pairs {dtype} {cosine} {crowd}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(41)
+    K, d, theta = 17001, 256, 0.9
+    mu = torch.randn(1, d, device=DEV, generator=g)
+    base = crowd ** 0.5 * mu / mu.norm() + ((1 - crowd) / d) ** 0.5 * torch.randn(K // 8 + 1 if crowd == 0 else K, d, device=DEV, generator=g)
+    c = rows_near(g, base, K, (1 / cosine - 1) ** 0.5, TYPES[dtype])
+    cap = 1 << 26
+    pairs, total = make(siso, c, dtype).merge(theta, cap)
+    want, many = make(siso, c, dtype, screen=2).merge(theta, cap)
+    assert 1000 < total <= cap and many <= cap
+
+    def keys(p, n):
+        p = p[:n].long()
+        assert bool((p[:, 0] < p[:, 1]).all() and (p >= 0).all() and (p < K).all())
+        k = (p[:, 0] * K + p[:, 1]).sort().values
+        assert bool((k[1:] > k[:-1]).all())
+        return k
+
+    a, b = keys(pairs, total), keys(want, many)
+    odd = torch.cat([a[~torch.isin(a, b)], b[~torch.isin(b, a)]])
+    u = unit(c)
+    th = float(torch.tensor(theta, dtype=torch.float32))
+    assert odd.numel() < 1e-4 * total + 20
+    assert odd.numel() == 0 or ((u[odd // K] * u[odd % K]).sum(1) - th).abs().max() <= TOL
+
+
+def test_pairs_near_the_threshold_do_not_pay_many_times(siso):
+    """Rows whose mean cosine is near the threshold: up to 1.7 times the time of the kernels of all pairs, where it was 13 to 140
+    times (every pair in doubt added one to the same counter)."""
+    print("case: screen time of pairs in doubt", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(42)
+    for dtype, K, d in (("bf16", 32768, 768), ("f32", 8000, 768)):
+        mu = torch.randn(1, d, device=DEV, generator=g)
+        c = (0.88 ** 0.5 * mu / mu.norm() + (0.12 / d) ** 0.5 * torch.randn(K, d, device=DEV, generator=g)).to(TYPES[dtype])
+        took = []
+        for screen in (2, 0):
+            cache = make(siso, c, dtype, screen=screen)
+            assert cache.screened(0) == (screen == 0)
+            cache.merge(0.9, 1 << 20)
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            for _ in range(4):
+                cache.merge(0.9, 1 << 20)
+            end.record()
+            torch.cuda.synchronize()
+            took.append(begin.elapsed_time(end))
+        assert took[1] < 3 * took[0], took
