@@ -367,6 +367,10 @@ __device__ __forceinline__ void byte_stream(unsigned char *smem, int dp, int pai
     // slab 0 and the first half of slab 1, as if a slab had just gone by
     static_for<0, NL>(part);
     static_for<0, NL / 2>(part);
+    if (src.leave()) {  // (looked up while the first loads are on their way; the same for all waves)
+        vm_wait<0>();
+        return;
+    }
     vm_wait<NL / 2>();
     __syncthreads();
     lds_frags<SUB>(af[0], bf[0], row_a + so[0], row_b + so[0]);
@@ -442,13 +446,17 @@ __device__ __forceinline__ void list_row(uint2 *list, int *cnt, unsigned *low, l
 // SAMPLE: one tile per workgroup, every `stride`-th of them, and only its best row counts: seed[q] = (product, row); and for
 // k_screen_seed, of 128 rows of every tile, the largest cosine and how many come within the error of it (ScreenCrowd; every
 // SCREEN_COUNTED-th query).
+template <bool LEAVE>
 struct LookupSrc {
     const signed char *c, *q;
     int ct, dp, buf;
+    const int *lost;
+    int most_lost;
     const float4 *meta;
     const unsigned *low;  // of the tile's queries
     float *meta_s;        // [2][64]
     unsigned *low_s;      // [2][256]
+    __device__ __forceinline__ bool leave() const { return LEAVE && *lost > most_lost; }
     __device__ __forceinline__ void side(int wave, int lane) {
         if (wave < 4) gload_lds4_fresh(low + wave * 64 + lane, low_s + buf * 256 + wave * 64);
         else if (wave == 4) gload_lds4((const float *)(meta + (size_t)ct * 8) + lane, meta_s + buf * 64);  // (32 of them count)
@@ -491,21 +499,19 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
     unsigned *stage = stages + wave * SCREEN_STAGE;
     int mine = 0;  // rows this wave has collected
 
-    ScreenQuery mine_q[WQ];
-#pragma unroll
-    for (int b = 0; b < WQ; ++b) mine_q[b] = qm[q0 + (wq * WQ + b) * 32 + l32];
-    if (!SAMPLE && *lost > most_lost) return;  // (the two loads on their way together)
     float scale[WQ], rscale[WQ], halfw[WQ], grow[WQ], best[WQ];  // per query: scale, 1 / scale, e + slack, (1 + e) / scale; a lower end
 #pragma unroll
     for (int b = 0; b < WQ; ++b) {
-        const ScreenQuery m = mine_q[b];
+        const ScreenQuery m = qm[q0 + (wq * WQ + b) * 32 + l32];
         scale[b] = m.scale;
         rscale[b] = 1.f / m.scale;
         halfw[b] = m.err + SCREEN_SLACK;
         grow[b] = (1.f + m.err) * rscale[b];
         best[b] = -INFINITY;
     }
-    LookupSrc src;
+    LookupSrc<!SAMPLE> src;
+    src.lost = lost;
+    src.most_lost = most_lost;
     src.c = codes + (size_t)ct_begin * BC * dp;
     src.q = qcodes + (size_t)q0 * dp;
     src.ct = ct_begin;
@@ -941,6 +947,7 @@ struct PairSrc {
     float *meta_s;  // [2][2][64]: row tile, column tile
     PairItems items;
     int ct, qt, dp, buf;
+    __device__ __forceinline__ bool leave() const { return false; }
     __device__ __forceinline__ void side(int wave, int lane) {
         if (wave < 2) gload_lds4((const float *)(meta + (size_t)(wave == 0 ? ct : qt) * 8) + lane, meta_s + (buf * 2 + wave) * 64);
     }
