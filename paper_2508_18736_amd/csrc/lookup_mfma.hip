@@ -133,7 +133,7 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int qt, s, ct_begin, ct_end;
     if (!pipe_map_block<BC>(K, tiles_per_slice, slices, nqt, qb, qt, s, ct_begin, ct_end)) return;
     const long q0 = (long)qt * BQ;
-    if constexpr (BQ == 256)  // (what a screened lookup leaves over: batches of more than 128)
+    if constexpr (BQ == 256 && ES == 2)  // (what a screened lookup leaves over: bf16 batches of more than 128)
         if (many != nullptr && q0 >= *many) return;
     const int nk = d / BK;
     const int T = (ct_end - ct_begin) * nk;  // slabs this workgroup walks through
@@ -743,7 +743,7 @@ struct WideCfg {
 template <bool STREAM>
 __global__ __launch_bounds__(WideCfg::NT) __attribute__((amdgpu_waves_per_eu(1, 1), amdgpu_num_vgpr(WIDE_FRAG0))) void k_lookup_wide(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ C, const float *__restrict__ invn, long n, long K, int d,
-    int tiles_per_slice, int slices, int nqt, int qb, u64 *__restrict__ keys, const int *__restrict__ many) {
+    int tiles_per_slice, int slices, int nqt, int qb, u64 *__restrict__ keys) {
     typedef WideCfg Cfg;
     constexpr int WC = Cfg::WC, WQ = Cfg::WQ, NWC = Cfg::NWC, BC = Cfg::BC, BQ = Cfg::BQ, NT = Cfg::NT, NW = Cfg::NW,
                   STAGE = Cfg::STAGE, NLA = Cfg::NLA, NL = Cfg::NL, BK = Cfg::BK, RB = Cfg::RB, KK = Cfg::KK,
@@ -759,7 +759,6 @@ __global__ __launch_bounds__(WideCfg::NT) __attribute__((amdgpu_waves_per_eu(1, 
     int qt, s, ct_begin, ct_end;
     if (!pipe_map_block<BC>(K, tiles_per_slice, slices, nqt, qb, qt, s, ct_begin, ct_end)) return;
     const long q0 = (long)qt * BQ;
-    if (many != nullptr && q0 >= *many) return;
     const int nk = d / BK;
     const int T = (ct_end - ct_begin) * nk;  // slabs this workgroup walks through
     if (T <= 0) return;
@@ -1463,7 +1462,7 @@ static int launch_wide2(siso_cache *c, const void *queries, long n, const PipePl
     }
     hipLaunchKernelGGL((k_lookup_wide<STREAM>), dim3((unsigned)p.grid), dim3(WideCfg::NT), WideCfg::LDS_BYTES, c->stream,
                        (const bf16_t *)queries, (const bf16_t *)c->cent, c->invn, n, c->count, c->dim, p.tiles_per_slice,
-                       p.slices, p.nqt, p.qb, keys, p.many);
+                       p.slices, p.nqt, p.qb, keys);
     return siso_check_hip(c, hipGetLastError(), "k_lookup_wide");
 }
 static int launch_wide(siso_cache *c, const void *queries, long n, const PipePlan &p, u64 *keys) {

@@ -222,7 +222,7 @@ inline unsigned xcd_grid(long total) { return (unsigned)((total + 7) / 8 * 8); }
 
 // Phase 1 of a lookup: the best scaled product of every query of a tile with the rows of a slice, as a key that names
 // the row.  GROUPS: of a top-k lookup: the two largest products of every group of 16 rows instead (see siso_internal.h).
-template <class Cfg, int W, typename T, bool GROUPS = false>
+template <class Cfg, int W, typename T, bool GROUPS, bool LEFT>  // LEFT: *many of the n queries
 __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_tile(const T *__restrict__ Q, const T *__restrict__ cent,
                                                       const float *__restrict__ invn, long n, long K, int d,
                                                       int tiles_per_slice, int slices, int qtiles, u64 *keys, u64 *board,
@@ -235,7 +235,8 @@ __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_
     const long id = xcd_run((long)qtiles * slices);
     if (id < 0) return;
     const long q0 = id % qtiles * Cfg::BQ;
-    if (many != nullptr && q0 >= *many) return;
+    if constexpr (LEFT)
+        if (q0 >= *many) return;
     const int s = (int)(id / qtiles);
     const long ctiles = (K + Cfg::BC - 1) / Cfg::BC;
     const long first = (long)s * tiles_per_slice;
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_
 // the whole dimension, slab by slab: 256 queries x 1,024 rows x 384 in 64 x 64 tiles are 64 workgroups for 256 compute
 // units and 192 instructions of 64 cycles in a row for each wave; here 256 workgroups and 48.  Fragments come from memory
 // straight into registers (what the workgroups share is in L2), a group of steps ahead of the one being multiplied.
-template <int W>
+template <int W, bool LEFT>
 __global__ __launch_bounds__(256) void k_lookup_split(const float *__restrict__ Q, const float *__restrict__ cent,
                                                       const float *__restrict__ invn, long n, long K, int d, int slices, int qtiles,
                                                       u64 *keys, u64 *board, const int *__restrict__ many) {
@@ -325,7 +326,8 @@ __global__ __launch_bounds__(256) void k_lookup_split(const float *__restrict__ 
     const long id = xcd_run((long)qtiles * slices);
     if (id < 0) return;
     const long q0 = id % qtiles * 32, c0 = id / qtiles * 32;
-    if (many != nullptr && q0 >= *many) return;
+    if constexpr (LEFT)
+        if (q0 >= *many) return;
     const long cr = c0 + (lane & 31), qr = q0 + (lane & 31);
     const float *a_row = cent + (size_t)(cr < K ? cr : K - 1) * d, *b_row = Q + (size_t)(qr < n ? qr : n - 1) * d;
     const int steps = (d + 31) / 32;  // of every wave; wave w has the elements from 8 * steps * w on
@@ -505,11 +507,11 @@ TilePlan tile_plan(const siso_cache *c, long n, bool groups, bool left) {
     return p;
 }
 
-template <typename T, int W, bool GROUPS>
+template <typename T, int W, bool GROUPS, bool LEFT>
 int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng, const int *many) {
     const dim3 grid(xcd_grid((long)p.qtiles * p.slices)), block(256);
 #define SISO_LAUNCH_TILE(Cfg)                                                                                            \
-    hipLaunchKernelGGL((k_lookup_tile<Cfg, W, T, GROUPS>), grid, block, 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
+    hipLaunchKernelGGL((k_lookup_tile<Cfg, W, T, GROUPS, LEFT>), grid, block, 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
                        n, c->count, c->dim, p.tiles_per_slice, p.slices, p.qtiles, keys, c->board_to_clear, \
                        groups, ng, many)
     if (p.cfg == 0) SISO_LAUNCH_TILE(TileFew);
@@ -520,26 +522,26 @@ int lookup_launch(siso_cache *c, const void *queries, long n, const TilePlan &p,
     return siso_check_hip(c, hipGetLastError(), "k_lookup_tile");
 }
 
-template <int W>
+template <int W, bool LEFT>
 int split_launch(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, const int *many) {
-    hipLaunchKernelGGL(k_lookup_split<W>, dim3(xcd_grid((long)p.qtiles * p.slices)), dim3(256), 0, c->stream, (const float *)queries,
+    hipLaunchKernelGGL((k_lookup_split<W, LEFT>), dim3(xcd_grid((long)p.qtiles * p.slices)), dim3(256), 0, c->stream, (const float *)queries,
                        (const float *)c->cent, c->invn, n, c->count, c->dim, p.slices, p.qtiles, keys, c->board_to_clear, many);
     c->board_to_clear = nullptr;  // taken
     return siso_check_hip(c, hipGetLastError(), "k_lookup_split");
 }
 
-template <typename T, bool GROUPS>
+template <typename T, bool GROUPS, bool LEFT = false>
 int lookup_launch_t(siso_cache *c, const void *queries, long n, const TilePlan &p, u64 *keys, float2 *groups, int ng,
                     const int *many = nullptr) {
     if (p.cfg == 3) switch (row_alignment<T>(queries, c->cent, c->dim)) {
-            case 16: return split_launch<16>(c, queries, n, p, keys, many);
-            case 8: return split_launch<8>(c, queries, n, p, keys, many);
-            default: return split_launch<4>(c, queries, n, p, keys, many);
+            case 16: return split_launch<16, LEFT>(c, queries, n, p, keys, many);
+            case 8: return split_launch<8, LEFT>(c, queries, n, p, keys, many);
+            default: return split_launch<4, LEFT>(c, queries, n, p, keys, many);
         }
     switch (row_alignment<T>(queries, c->cent, c->dim)) {
-        case 16: return lookup_launch<T, 16, GROUPS>(c, queries, n, p, keys, groups, ng, many);
-        case 8: return lookup_launch<T, 8, GROUPS>(c, queries, n, p, keys, groups, ng, many);
-        default: return lookup_launch<T, (int)sizeof(T), GROUPS>(c, queries, n, p, keys, groups, ng, many);
+        case 16: return lookup_launch<T, 16, GROUPS, LEFT>(c, queries, n, p, keys, groups, ng, many);
+        case 8: return lookup_launch<T, 8, GROUPS, LEFT>(c, queries, n, p, keys, groups, ng, many);
+        default: return lookup_launch<T, (int)sizeof(T), GROUPS, LEFT>(c, queries, n, p, keys, groups, ng, many);
     }
 }
 
@@ -605,14 +607,17 @@ long siso_tile_keys_bound(const siso_cache *c, long n) {
 int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, const int *many) {
     const TilePlan p = tile_plan(c, n, false, many != nullptr);
     if (p.slices != slices) return siso_fail(c, SISO_EINVAL, "tiled lookup: plan mismatch");
-    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, false>(c, queries, n, p, keys, nullptr, 0, nullptr);  // (whole slabs)
-    return c->dtype == SISO_F32 ? lookup_launch_t<float, false>(c, queries, n, p, keys, nullptr, 0, many)
-                                : lookup_launch_t<bf16_t, false>(c, queries, n, p, keys, nullptr, 0, many);
+    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, false, false>(c, queries, n, p, keys, nullptr, 0, nullptr);  // (whole slabs)
+    if (many != nullptr)
+        return c->dtype == SISO_F32 ? lookup_launch_t<float, false, true>(c, queries, n, p, keys, nullptr, 0, many)
+                                    : lookup_launch_t<bf16_t, false, true>(c, queries, n, p, keys, nullptr, 0, many);
+    return c->dtype == SISO_F32 ? lookup_launch_t<float, false>(c, queries, n, p, keys, nullptr, 0)
+                                : lookup_launch_t<bf16_t, false>(c, queries, n, p, keys, nullptr, 0);
 }
 
 int siso_tile_groups_launch(siso_cache *c, const void *queries, long n, float2 *groups, int ng) {
     const TilePlan p = tile_plan(c, n, true, false);
-    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, true>(c, queries, n, p, nullptr, groups, ng, nullptr);
+    if (c->dtype == SISO_FP8) return lookup_launch<fp8_t, 16, true, false>(c, queries, n, p, nullptr, groups, ng, nullptr);
     return c->dtype == SISO_F32 ? lookup_launch_t<float, true>(c, queries, n, p, nullptr, groups, ng)
                                 : lookup_launch_t<bf16_t, true>(c, queries, n, p, nullptr, groups, ng);
 }

@@ -184,7 +184,8 @@ __global__ __launch_bounds__(256) void k_import_rows(const T *__restrict__ src, 
 // names a group of four consecutive rows: their exact cosines (one wave per row; strict ">" in ascending
 // row order, so the lowest index keeps a tie); then the strict threshold test.  One 256-thread block
 // per query.  `vec` = rows are 16-byte aligned and a whole number of 16-byte chunks.
-template <typename T>
+// LEFT: what a screened lookup has left over: the first *many of the queries, whose results go to of[q].
+template <typename T, bool LEFT>
 __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q, const T *__restrict__ cent,
                                                           const float *__restrict__ invn, const u64 *__restrict__ keys,
                                                           long n, long K, int d, int slices, ThetaList thetas, int vec,
@@ -200,8 +201,11 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
     __shared__ long sh_i[16];
     __shared__ u32x4_t sh_q[SISO_MAX_DIM / EPC];  // the query row
     const long q = blockIdx.x;
-    if (many && q >= *many) return;  // (see siso_tile_launch)
-    const long to = of ? of[q] : q;  // where its results go
+    long to = q;  // where its results go
+    if constexpr (LEFT) {
+        if (q >= *many) return;
+        to = of[q];
+    }
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, grp = t >> 4, gl = t & 15;
     const T *qrow = Q + (size_t)q * d;
     // 1/|q|: 0 for a zero-length query, NaN for a non-finite one
@@ -276,7 +280,7 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
             }
         }
         if (!finite_q) best_s = __uint_as_float(0x7FC00000u);
-        write_lookup(to, q_base, best_i, best_s, thetas, out_idx, out_sim, out_hit, access, upd_owner, upd_members);
+        write_lookup(to, LEFT ? q_base : 0L, best_i, best_s, thetas, out_idx, out_sim, out_hit, access, upd_owner, upd_members);
     }
 }
 
@@ -1516,13 +1520,18 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
         return SISO_OK;
     }
     if (row_keys == SISO_KEY_ROWS && anew) row_keys = SISO_KEY_ROWS_ANEW;
-#define SISO_LAUNCH_FINALIZE(T)                                                                                              \
-    hipLaunchKernelGGL(k_lookup_finalize<T>, dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
+#define SISO_LAUNCH_FINALIZE(T, LEFT)                                                                                        \
+    hipLaunchKernelGGL((k_lookup_finalize<T, LEFT>), dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, (const T *)c->cent, c->invn, \
                        keys, n, c->count, c->dim, slices, tl, vec, row_keys, out_idx, out_sim, out_hit,                        \
                        count_index >= 0 ? c->access : nullptr, fp8 ? (const float *)c->fp8_qinv : (const float *)nullptr, owner, \
                        members, many, of, q_base)
-    if (c->dtype == SISO_F32) SISO_LAUNCH_FINALIZE(float);
-    else SISO_LAUNCH_FINALIZE(bf16_t);
+    if (c->dtype == SISO_F32) {
+        if (left) SISO_LAUNCH_FINALIZE(float, true);
+        else SISO_LAUNCH_FINALIZE(float, false);
+    } else {
+        if (left) SISO_LAUNCH_FINALIZE(bf16_t, true);
+        else SISO_LAUNCH_FINALIZE(bf16_t, false);
+    }
 #undef SISO_LAUNCH_FINALIZE
     return siso_check_hip(c, hipGetLastError(), "k_lookup_finalize");
 }
