@@ -65,9 +65,66 @@ def test_lookup(siso, dtype, K, n, d):
     idx, sim, hit = cache.lookup(q, 0.85)
     check(idx, sim, q, c)
     assert torch.equal(hit, (sim > 0.85).to(torch.uint8))
-    # the same bits as without the bytes, up to rows whose cosines are equal within the roundings
+    # the values of the kernels of all products, within the roundings of the cosines (those may leave the sums of the MFMAs)
     other = make(siso, c, dtype, screen=2).lookup(q, 0.85)
     assert (other[1] - sim).abs().max() <= 2 * TOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("screen", [1, 3])
+def test_lookup_in_two_launches(siso, dtype, screen):
+    """From 8,192 pairs of tiles on an eighth of the rows goes first and its lists supply better bounds; the rest begins at its
+    first row (17,408 here).  No size is a multiple of a tile, and what the bound says nothing about lies on both sides."""
+    print(f"case: screen two launches {dtype} {screen}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(51)
+    K, n, d, first = 140003, 4001, 128, 68 * 256
+    c = rows_near(g, torch.randn(K // 8, d, device=DEV, generator=g), K, 0.1, TYPES[dtype])
+    q = torch.cat([rows_near(g, c, n - 1500, 0.1, TYPES[dtype]), torch.randn(1500, d, device=DEV, generator=g).to(TYPES[dtype])])
+    q = q[torch.randperm(n, device=DEV, generator=g)].contiguous()
+    # rows: without length, non-finite, lengths near the ends of the range, equal ones, more of them than a list holds
+    for at in (10, first - 300, first + 300, K - 40):
+        c[at] = 0
+        c[at + 1, 3] = float("nan")
+        c[at + 2, 5] = float("inf")
+        c[at + 3] *= 1e-17
+        c[at + 4] *= 1e17
+    c[first - 1] = c[first + 1] = c[K - 1] = c[5]
+    c[first + 2000:first + 4000] = c[first + 2000]
+    c[200] = c[K - 3] = c[first + 7]
+    # queries: of every tile's end, equal to such rows, without length, non-finite, tiny
+    q[255], q[256], q[n - 1], q[n - 2] = c[5], c[K - 2], c[K - 3], c[first]
+    q[700:720] = c[first + 2000]
+    q[3000], q[3001] = c[13], c[first + 304]
+    q[1] = 0
+    q[2, 1] = float("nan")
+    q[n - 3, 2] = float("-inf")
+    q[n - 4] *= 1e-17
+    cache = make(siso, c, dtype, screen=screen)
+    assert cache.screened(n) and ((K + 255) // 256) * ((n + 255) // 256) >= 8192
+    idx, sim, hit = cache.lookup(q, 0.85)
+    assert idx[1] == 0 and sim[1] == 0 and bool((idx[[2, n - 3]] == -1).all()) and bool(torch.isnan(sim[[2, n - 3]]).all())
+    assert idx[255] == 5 and idx[n - 1] == 200 and idx[700:720].tolist() == [first + 2000] * 20
+    assert idx[256] == K - 2 and idx[n - 2] == first
+    want = make(siso, c, dtype, screen=2).lookup(q, 0.85)
+    assert bool(((sim - want[1]).abs() <= 2 * TOL)[~torch.isnan(want[1])].all())
+    assert torch.equal(idx[[n - 4, 3000, 3001]], want[0][[n - 4, 3000, 3001]])
+    ok = torch.ones(n, dtype=torch.bool, device=DEV)
+    ok[[1, 2, n - 3, n - 4]] = False
+    usable = torch.isfinite(c).all(1) & (c.double().abs().amax(1) > 0)
+    u = unit(c)
+    u[~usable] = 0
+    for lo in range(0, n, 500):
+        at = torch.arange(lo, min(n, lo + 500), device=DEV)
+        at = at[ok[at]]
+        s = unit(q[at]) @ u.T
+        s[:, ~usable] = -2
+        own = s.gather(1, idx[at].long()[:, None])[:, 0]
+        assert (own - sim[at].double()).abs().max() <= TOL
+        top = s.topk(2, 1)
+        assert (top.values[:, 0] - own).max() <= 2 * TOL
+        sure = top.values[:, 0] - top.values[:, 1] > 4 * TOL
+        assert torch.equal(idx[at][sure].long(), top.indices[sure, 0])
+    assert torch.equal(hit, (sim > 0.85).to(torch.uint8))
 
 
 def test_rows_and_queries_the_bound_says_nothing_about(siso):
