@@ -123,6 +123,19 @@ long siso_count(const siso_cache *c);
  * cache, and a call that needs more room than any before it (a larger batch, more
  * centroids) waits for the stream and allocates.  siso_reserve sizes the workspace
  * ahead of time.
+ * Large batches of fp32 and bf16 caches with 128 to 1,024 dimensions are screened (fp32:
+ * more than 128 queries and 8e9 operations, 2 * n * rows * dim; bf16: 768 queries and
+ * 7.5e11): rows and queries are written as signed bytes with a measured error, exact
+ * products of the bytes rule out the rows whose cosine cannot be the largest, and those that
+ * remain are multiplied again from the stored rows.  Similarities are sums of the stored
+ * values as ever; of two rows whose similarities are within the rounding of each other
+ * either may be named.  A batch whose queries are near too many rows (rows with a common
+ * direction, queries that miss) is given up early and looked up without the bytes.
+ * Screening takes a workspace of a byte per element of the cache (its dimension rounded up
+ * to a multiple of 128, at least 256) and 10 to 22 KB per query, of at most 16,384: 1.4 GB for
+ * 1,048,576 rows of 1,024.  It is kept until siso_destroy.  A call that cannot have it goes
+ * without, and such a size is not asked for again until siso_reserve; the workspace of a lookup
+ * that was captured in a graph stays as it is when a larger call needs more.
  */
 int siso_lookup(siso_cache *c, const void *queries, long n, float threshold, int *out_idx, float *out_sim,
                 unsigned char *out_hit);
@@ -200,7 +213,8 @@ int siso_lookup_static(siso_cache *c, const void *queries, long n, float thresho
  * so that a serving loop whose batches stay within n neither allocates nor
  * synchronises in those calls.  Synchronises and allocates itself if the room
  * grows.  (Forcing another lookup kernel or tiling afterwards, see siso_bench.h,
- * changes the need.)
+ * changes the need.)  The workspace of screened lookups is part of it; where that is
+ * not to be had the call succeeds, and such batches go without and do not ask again.
  */
 int siso_reserve(siso_cache *c, long n);
 
@@ -260,6 +274,12 @@ long siso_bad_indices(siso_cache *c);
  *   out_pairs: device pointer, [cap][2] ints, in no particular order.
  * Returns the total number of such pairs, which may exceed cap; only the first
  * cap pairs found are written.  Negative = error code.  Synchronises.
+ * Large searches (128 to 1,024 dimensions, thresholds from 0.25 on; rows * rows * dim from
+ * 1.5e9 in fp32, 2.5e10 in bf16) are screened like lookups: products of bytes tell most pairs
+ * from the others, and the cosines of those near the threshold are formed anew.  Their
+ * workspace (a byte per element of the rows, and up to 128 MiB for pairs near the threshold) is
+ * kept up to 512 MiB and given back above; without it, or with more such pairs than it
+ * holds, all products are formed.  siso_cluster and siso_refresh search in the same way.
  */
 long siso_merge(siso_cache *c, float threshold, int *out_pairs, long cap);
 

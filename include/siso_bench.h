@@ -45,7 +45,7 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *                     batches go in more pieces, and without room for one query every row is scanned (what
  *                     the call does by itself where memory is short)
  *   "screen"          0 = default (large lookups and pair searches of fp32 and bf16 caches rule most rows out by products
- *                     of bytes, see siso.h); 1 = wherever the kernels can (dimensions up to 1,024; pair searches
+ *                     of bytes, see siso_lookup and siso_merge); 1 = wherever the kernels can (dimensions up to 1,024; pair searches
  *                     at thresholds from 0.25 on) and to the end; 2 = never; 3 = wherever the kernels can, a batch
  *                     given up as by default once too many of its queries are near too many rows
  *   "screen_room"     0 = default; > 0 = KiB that a workspace of those products may take: what needs more goes without

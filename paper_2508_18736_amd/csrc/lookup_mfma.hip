@@ -189,7 +189,7 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // live ones hold NaN), one 4-byte direct load per lane of the first BC/64 waves.
     int ld_ct = ct_begin, ld_ks = 0, ld_stage = 0;
     // One part = one direct load of this wave; part NL - 1 also moves on to the next slab, but
-    // never past the last one (the wide path issues unconditionally and so fetches the last slab
+    // never past the last one (where nothing may depend on a condition, DEAL, the last slab is fetched
     // again, into a stage nobody reads any more).  With STREAM the centroid loads carry the
     // non-temporal hint (stream_hint decides per launch).
     const char *ld_c = (const char *)C + (size_t)ct_begin * BC * d * ES;  // first element of the slab, centroid side
@@ -245,7 +245,9 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     //   issue the loads of slab t+NSTAGE into the stage just vacated | read step-0 fragments of slab t+1 |
     //   last step of slab t | epilogue if the tile is complete
     // so the loads have NSTAGE-1 slabs of time to land and the MFMAs of step 3 cover the barrier's
-    // tail.  Loads complete in order: "all but the newest (NSTAGE-2)*NL" = slab t+1 has landed.  (The
+    // tail.  Where the loads are dealt out (DEAL, two stages) the first half of those of slab t+2 goes out between the MFMAs
+    // of slab t's last step and the other half between those of slab t+1's first one, and all are waited for at the
+    // barrier of slab t+1.  Loads complete in order: "all but the newest (NSTAGE-2)*NL" = slab t+1 has landed.  (The
     // inverse lengths ride along as one more load now and then, which only makes a wait stricter; they
     // are older than the slab issued with them, so they have landed one barrier later at the latest,
     // and the epilogue of their tile comes after that barrier because a tile has at least two slabs.)
@@ -726,6 +728,9 @@ __device__ __forceinline__ void lgkm_wait() {
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// The lookup and the pair search with four waves of 128 x 128 are no longer chosen by default: the eight-wave kernels are ahead at
+// every size (mfma_plan, siso_pairs_mfma_launch).  They are kept for comparison, behind the options mfma_config 5 and
+// merge_config 2.
 struct WideCfg {
     static constexpr int WC = 4, WQ = 4, NWC = 2, NWQ = 2, NW = 4, NT = 256;
     static constexpr int BC = 256, BQ = 256, BK = 64, RB = 128, KK = 4;

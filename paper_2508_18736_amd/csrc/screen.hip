@@ -624,8 +624,9 @@ __global__ __launch_bounds__(ByteCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 
             static_for<0, WC>([&](auto ia) __attribute__((always_inline)) {
                 constexpr int A = decltype(ia)::value;
                 if (__ballot(up[A][B] > need[B]) == 0) return;
-                // the bound as an integer (rounded down; the slack of the error is some twenty of its units).  No scale (rows
-                // of zeros): plus or minus infinity, or a NaN, which converts to 0
+                // the bound as an integer, rounded down: the three operations are off by some 2^-22 of the product that would
+                // be needed, a cosine of at most about one, and the slack is 2e-5 of that whatever the scale.  No scale (rows of
+                // zeros): plus or minus infinity, or a NaN, which converts to 0
                 const int least = up[A][B] > need[B] ? (int)floorf((need[B] - grow[B] * m[A].y) * m[A].w) : 0x7FFFFFFF;
                 // one upper end for the rows of a lane, mostly one: that of the largest
                 const int rel0 = tile * BC + (wc * WC + A) * 32 + 4 * h;  // register I holds row rel0 + 8 * (I / 4) + I % 4
@@ -1467,15 +1468,19 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
 }  // namespace
 
 // Is a lookup worth it?  The bytes of the rows are written for every call (they may have changed), and six small kernels
-// stand around the products.  Lookups alone, no misses / 30 % misses, us, without and with:
-//   fp32  1,000 x 8,000 x 384    77 -> 65 / 77 -> 70      1,000 x 16,000 x 384   124 -> 68 / 123 -> 74
-//         300 x 16,000 x 384     56 -> 62 / 56 -> 68      2,000 x 2,000 x 768     80 -> 84 / 79 -> 99
-//         1,000 x 60,000 x 384  416 -> 103 / 417 -> 111   4,096 x 60,000 x 768  2,986 -> 283 / 2,980 -> 336
-//   bf16  4,096 x 65,536 x 768  374 -> 294 / 379 -> 334   1,000 x 400,000 x 768  601 -> 507 / 587 -> 546
-//         4,096 x 131,072 x 768 703 -> 490 / 712 -> 539   8,192 x 131,072 x 1,024  1,877 -> 1,098 / 1,859 -> 1,426
-// (of bf16 batches near 500 GFLOP half of whose queries miss, as a refresh has them, take as long either way: the line lies where
-// those are ahead, too).  Longer rows than SISO_SCREEN_DIM: the error stays what it is while the cosines of
-// unrelated rows crowd together (deviation d^-1/2), and ever more rows are near the best.
+// stand around the products.  Lookups alone, no misses / 30 % / 60 % misses, us, without -> with:
+//   fp32  1,000 x 8,000 x 384      75 -> 69 / 72 -> 73 / 73 -> 75          300 x 16,000 x 384     54 -> 64 / 54 -> 69 / 54 -> 72
+//         1,000 x 16,000 x 384    118 -> 72 / 118 -> 77                    2,000 x 2,000 x 768    77 -> 88 / 75 -> 101 / 75 -> 111
+//         1,000 x 30,000 x 384    209 -> 80 / 209 -> 87 / 210 -> 91        200 x 60,000 x 384    114 -> 78 / 110 -> 84 / 110 -> 89
+//         4,096 x 60,000 x 768    2,964 -> 300 / 2,969 -> 351              130 x 100,000 x 384   185 -> 94 / 185 -> 99 / 184 -> 105
+//   bf16  4,096 x 65,536 x 768    336 -> 298 / 333 -> 338 / 334 -> 367     1,000 x 400,000 x 768  532 -> 513 / 531 -> 542 / 527 -> 567
+//         6,553 x 65,536 x 768    563 -> 467 / 562 -> 545 / 561 -> 595     4,096 x 131,072 x 768  648 -> 514 / 649 -> 556 / 648 -> 594
+//         8,192 x 131,072 x 1,024 1,679 -> 1,150 / 1,677 -> 1,437 / 1,678 -> 1,528
+// The lines lie where batches of which more than half misses are ahead, too.  Up to 256 queries of single precision would end
+// in one kernel with their update (k_finalize_update), which a screened batch does not: with the update, 256 x 42,000 x 384
+// 93 -> 81 / 94 -> 88 / 94 -> 90, 256 x 100,000 x 384 192 -> 102 / 191 -> 109 / 190 -> 114.  Rows with a common direction: see
+// screen_launch.  Longer rows than SISO_SCREEN_DIM: the error stays what it is while the cosines of unrelated rows crowd
+// together (deviation d^-1/2), and ever more rows are near the best.
 int siso_screen_wanted(const siso_cache *c, long n) {
     if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->count < 1 || n < 1 || c->dim > SISO_SCREEN_DIM) return 0;
     if (c->opt_screen == 1 || c->opt_screen == 3) return 1;
