@@ -21,7 +21,7 @@
 // whose list is full lists nothing any more; k_screen_seed counts those whose lists can be foreseen to flood, from
 // the sample and again from the lists of the first eighth; and if they are too many (lost, most_lost) the batch is given up:
 // the rest of the products is not formed, and the other kernels do all of it, which by then has paid for little.  (No query
-// is given up alone: those kernels take nearly as long for one as for all.)
+// is given up alone: for a few those kernels take a good part of the time that they take for all.)
 //
 // Rows are grouped by 32 (the rows of one MFMA): one scale and one error for each.  One outlier costs its 32 rows some
 // precision and nobody else; and the end of a tile works on integers: a maximum of 16, one conversion, three operations
@@ -1239,7 +1239,7 @@ ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
     r.cnt = a.take<int>(q);
     r.near = a.take<int>(q);
     r.largest = a.take<float>(q);
-    r.totals = a.take<int>(3);  // rows to be multiplied again, queries left to the other kernels, queries given up before that
+    r.totals = a.take<int>(3);  // rows to be multiplied again, queries left to the other kernels, queries counted as lost
     r.plain_of = a.take<int>(q);
     r.plain_rows = a.take<char>((size_t)q * d * (c->dtype == SISO_F32 ? 4 : 2));
     r.qinv = a.take<float>(q);
