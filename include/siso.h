@@ -124,8 +124,8 @@ long siso_count(const siso_cache *c);
  * centroids) waits for the stream and allocates.  siso_reserve sizes the workspace
  * ahead of time.
  * Large batches of fp32 and bf16 caches with 128 to 1,024 dimensions are screened (fp32:
- * more than 128 queries and 8e9 operations, 2 * n * rows * dim; bf16: 768 queries and
- * 7.5e11): rows and queries are written as signed bytes with a measured error, exact
+ * more than 128 queries, 8e9 operations, 2 * n * rows * dim, and 1e6 elements, rows * dim;
+ * bf16: 768 queries, 7.5e11 operations and 2.2e7 elements): rows and queries are written as signed bytes with a measured error, exact
  * products of the bytes rule out the rows whose cosine cannot be the largest, and those that
  * remain are multiplied again from the stored rows.  Similarities are sums of the stored
  * values as ever; of two rows whose similarities are within the rounding of each other

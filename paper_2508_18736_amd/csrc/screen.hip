@@ -1476,7 +1476,13 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
 //   bf16  4,096 x 65,536 x 768    336 -> 298 / 333 -> 338 / 334 -> 367     1,000 x 400,000 x 768  532 -> 513 / 531 -> 542 / 527 -> 567
 //         6,553 x 65,536 x 768    563 -> 467 / 562 -> 545 / 561 -> 595     4,096 x 131,072 x 768  648 -> 514 / 649 -> 556 / 648 -> 594
 //         8,192 x 131,072 x 1,024 1,679 -> 1,150 / 1,677 -> 1,437 / 1,678 -> 1,528
-// The lines lie where batches of which more than half misses are ahead, too.  Up to 256 queries of single precision would end
+// The lines lie where batches of which more than half misses are ahead, too.  A query costs its candidates, whatever the products
+// take, so a small cache is better off without at any batch:
+//   fp32  8,192 x 1,000 x 768     127 -> 146 / 134 -> 177        8,192 x 2,000 x 768    232 -> 147 / 225 -> 177 / 222 -> 202
+//         32,768 x 8,000 x 128    610 -> 426 / 608 -> 435        16,384 x 4,000 x 384   432 -> 211 / 430 -> 236 / 428 -> 255
+//   bf16  65,536 x 50,000 x 128   845 -> 1,671 / 844 -> 1,713    16,384 x 30,000 x 768  797 -> 555 / 794 -> 665 / 791 -> 763
+//         32,768 x 16,000 x 1,024 852 -> 904 / 847 -> 1,203      16,384 x 100,000 x 256 886 -> 670 / 885 -> 705 / 884 -> 729
+// Up to 256 queries of single precision would end
 // in one kernel with their update (k_finalize_update), which a screened batch does not: with the update, 256 x 42,000 x 384
 // 93 -> 81 / 94 -> 88 / 94 -> 90, 256 x 100,000 x 384 192 -> 102 / 191 -> 109 / 190 -> 114.  Rows with a common direction: see
 // screen_launch.  Longer rows than SISO_SCREEN_DIM: the error stays what it is while the cosines of unrelated rows crowd
@@ -1485,8 +1491,8 @@ int siso_screen_wanted(const siso_cache *c, long n) {
     if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->count < 1 || n < 1 || c->dim > SISO_SCREEN_DIM) return 0;
     if (c->opt_screen == 1 || c->opt_screen == 3) return 1;
     if (c->path != SISO_PATH_AUTO || c->opt_mfma_config != 0 || c->opt_tiles_per_slice != 0 || c->opt_mfma_qblock != 0) return 0;
-    const double work = 2.0 * (double)n * (double)c->count * c->dim;
-    return c->dim >= 128 && (c->dtype == SISO_F32 ? n > 128 && work >= 8e9 : n >= 768 && work >= 7.5e11);
+    const double elements = (double)c->count * c->dim, work = 2.0 * (double)n * elements;
+    return c->dim >= 128 && (c->dtype == SISO_F32 ? n > 128 && work >= 8e9 && elements >= 1e6 : n >= 768 && work >= 7.5e11 && elements >= 2.2e7);
 }
 
 extern "C" int siso_screened(const siso_cache *c, long n) {

@@ -270,6 +270,17 @@ def test_crowded_rows_do_not_pay_twice(siso):
         assert took[1] < 2 * took[0], took
 
 
+@pytest.mark.parametrize("dtype,K,d,n,wanted", [("f32", 1000, 768, 8192, False), ("f32", 8000, 128, 32768, True), ("f32", 60000, 384, 128, False),
+                                                ("bf16", 50000, 128, 65536, False), ("bf16", 16000, 1024, 32768, False),
+                                                ("bf16", 30000, 768, 16384, True), ("bf16", 65536, 768, 4096, False)])
+def test_small_caches_are_not_screened(siso, dtype, K, d, n, wanted):
+    """Each query costs its candidates, whatever its products take: up to twice the time on caches of few elements."""
+    cache = siso.SisoCache(d, K, siso.F32 if dtype == "f32" else siso.BF16)
+    assert not cache.screened(n)  # (empty)
+    cache.load(torch.ones(K, d, device=DEV, dtype=TYPES[dtype]))
+    assert cache.screened(n) == wanted
+
+
 def test_batches_of_several_pieces_and_the_update_behind_them(siso):
     print("case: screen pieces", flush=True)
     g = torch.Generator(device=DEV).manual_seed(11)
