@@ -125,7 +125,8 @@ long siso_count(const siso_cache *c);
  * ahead of time.
  * Large batches of fp32 and bf16 caches with 128 to 1,024 dimensions are screened (fp32:
  * more than 128 queries, 8e9 operations, 2 * n * rows * dim, and 1e6 elements, rows * dim;
- * bf16: 768 queries, 7.5e11 operations and 2.2e7 elements): rows and queries are written as signed bytes with a measured error, exact
+ * bf16: 768 queries, 7.5e11 operations and 2.2e7 elements, more where the dimension is no
+ * multiple of 128 or below 256): rows and queries are written as signed bytes with a measured error, exact
  * products of the bytes rule out the rows whose cosine cannot be the largest, and those that
  * remain are multiplied again from the stored rows.  Similarities are sums of the stored
  * values as ever; of two rows whose similarities are within the rounding of each other
@@ -275,7 +276,7 @@ long siso_bad_indices(siso_cache *c);
  * Returns the total number of such pairs, which may exceed cap; only the first
  * cap pairs found are written.  Negative = error code.  Synchronises.
  * Large searches (128 to 1,024 dimensions, thresholds from 0.25 on; rows * rows * dim from
- * 1.5e9 in fp32, 2.5e10 in bf16) are screened like lookups: products of bytes tell most pairs
+ * 1.5e9 and 2,000 rows in fp32; from 2.6e10 in bf16, with the same addition) are screened like lookups: products of bytes tell most pairs
  * from the others, and the cosines of those near the threshold are formed anew.  Their
  * workspace (a byte per element of the rows, and up to 128 MiB for pairs near the threshold) is
  * kept up to 512 MiB and given back above; without it, or with more such pairs than it

@@ -1202,6 +1202,8 @@ struct ScreenRoom {
 
 int byte_dim(int d) { return d <= 256 ? 256 : (d + 127) / 128 * 128; }
 long up256(long x) { return (x + 255) / 256 * 256; }
+// of a bf16 product: bytes are multiplied twice as fast, but in rows of 256 bytes and whole multiples of 128
+double saved_dim(int d) { return d - byte_dim(d) / 2.0; }
 
 // Rows that a query on average can have multiplied again before the kernels of all products are the better way.
 // One row takes about a nanosecond (0.1 ms for 96,000 of 768 bf16 elements), all products of a query 150 ns for 131,072 of
@@ -1477,11 +1479,12 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
 //         6,553 x 65,536 x 768    563 -> 467 / 562 -> 545 / 561 -> 595     4,096 x 131,072 x 768  648 -> 514 / 649 -> 556 / 648 -> 594
 //         8,192 x 131,072 x 1,024 1,679 -> 1,150 / 1,677 -> 1,437 / 1,678 -> 1,528
 // The lines lie where batches of which more than half misses are ahead, too.  A query costs its candidates, whatever the products
-// take, so a small cache is better off without at any batch:
+// take, so a small cache is better off without at any batch, and so are bf16 rows of 128 elements, whose bytes have to be filled up:
 //   fp32  8,192 x 1,000 x 768     127 -> 146 / 134 -> 177        8,192 x 2,000 x 768    232 -> 147 / 225 -> 177 / 222 -> 202
 //         32,768 x 8,000 x 128    610 -> 426 / 608 -> 435        16,384 x 4,000 x 384   432 -> 211 / 430 -> 236 / 428 -> 255
 //   bf16  65,536 x 50,000 x 128   845 -> 1,671 / 844 -> 1,713    16,384 x 30,000 x 768  797 -> 555 / 794 -> 665 / 791 -> 763
 //         32,768 x 16,000 x 1,024 852 -> 904 / 847 -> 1,203      16,384 x 100,000 x 256 886 -> 670 / 885 -> 705 / 884 -> 729
+//         8,192 x 200,000 x 192   571 -> 601 / 570 -> 624        8,192 x 200,000 x 320  870 -> 775 / 870 -> 810 / 870 -> 840
 // Up to 256 queries of single precision would end
 // in one kernel with their update (k_finalize_update), which a screened batch does not: with the update, 256 x 42,000 x 384
 // 93 -> 81 / 94 -> 88 / 94 -> 90, 256 x 100,000 x 384 192 -> 102 / 191 -> 109 / 190 -> 114.  Rows with a common direction: see
@@ -1491,8 +1494,10 @@ int siso_screen_wanted(const siso_cache *c, long n) {
     if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->count < 1 || n < 1 || c->dim > SISO_SCREEN_DIM) return 0;
     if (c->opt_screen == 1 || c->opt_screen == 3) return 1;
     if (c->path != SISO_PATH_AUTO || c->opt_mfma_config != 0 || c->opt_tiles_per_slice != 0 || c->opt_mfma_qblock != 0) return 0;
-    const double elements = (double)c->count * c->dim, work = 2.0 * (double)n * elements;
-    return c->dim >= 128 && (c->dtype == SISO_F32 ? n > 128 && work >= 8e9 && elements >= 1e6 : n >= 768 && work >= 7.5e11 && elements >= 2.2e7);
+    const double elements = (double)c->count * c->dim, saved = (double)c->count * saved_dim(c->dim);
+    if (c->dim < 128) return 0;
+    if (c->dtype == SISO_F32) return n > 128 && 2.0 * (double)n * elements >= 8e9 && elements >= 1e6;
+    return n >= 768 && 2.0 * (double)n * saved >= 3.75e11 && saved >= 1.1e7;  // (both lines: half of the bf16 work, mostly)
 }
 
 extern "C" int siso_screened(const siso_cache *c, long n) {
@@ -1559,14 +1564,16 @@ int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_row
 
 // Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 52, 2,000 x 768
 // 82 -> 59, 4,000 x 256 130 -> 60, 8,000 x 768 500 -> 97; bf16 8,000 x 256 62 -> 71, 6,000 x 768 94 -> 86, 16,000 x 256 101 -> 99, 16,000 x 768
-// 229 -> 151, 50,000 x 768 1,666 -> 886.  Below a threshold of 0.25 rows of zeros and the many pairs of unrelated rows would come
+// 229 -> 151, 50,000 x 768 1,666 -> 886; where it does not pay: fp32 1,250 x 1,000 62 -> 87, bf16 14,000 x 128 80 -> 108, 20,000 x 128
+// 129 -> 178, 10,000 x 256 80 -> 90.  Below a threshold of 0.25 rows of zeros and the many pairs of unrelated rows would come
 // near it.
 int siso_screen_pairs_wanted(const siso_cache *c, long count, float threshold) {
     if (c->dtype == SISO_FP8 || c->opt_screen == 2 || c->opt_merge_config != 0 || count < 2 || c->dim > SISO_SCREEN_DIM) return 0;
     if (!(threshold >= 0.25f)) return 0;
     if (c->opt_screen == 1 || c->opt_screen == 3) return 1;
-    const double work = (double)count * (double)count * c->dim;
-    return c->dim >= 128 && work >= (c->dtype == SISO_F32 ? 1.5e9 : 2.5e10);
+    const double squared = (double)count * (double)count;
+    if (c->dim < 128) return 0;
+    return c->dtype == SISO_F32 ? count >= 2000 && squared * c->dim >= 1.5e9 : squared * saved_dim(c->dim) >= 1.3e10;
 }
 
 int siso_screen_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,

@@ -272,9 +272,12 @@ def test_crowded_rows_do_not_pay_twice(siso):
 
 @pytest.mark.parametrize("dtype,K,d,n,wanted", [("f32", 1000, 768, 8192, False), ("f32", 8000, 128, 32768, True), ("f32", 60000, 384, 128, False),
                                                 ("bf16", 50000, 128, 65536, False), ("bf16", 16000, 1024, 32768, False),
-                                                ("bf16", 30000, 768, 16384, True), ("bf16", 65536, 768, 4096, False)])
+                                                ("bf16", 30000, 768, 16384, True), ("bf16", 65536, 768, 4096, False),
+                                                ("bf16", 400000, 128, 8192, False), ("bf16", 200000, 192, 8192, False), ("bf16", 200000, 320, 8192, True), ("f32", 1250, 1000, 0, False), ("f32", 2000, 384, 0, True),
+                                                ("bf16", 14000, 128, 0, False), ("bf16", 10000, 256, 0, False), ("bf16", 6553, 768, 0, True)])
 def test_small_caches_are_not_screened(siso, dtype, K, d, n, wanted):
-    """Each query costs its candidates, whatever its products take: up to twice the time on caches of few elements."""
+    """Each query costs its candidates, whatever its products take, and short bf16 rows are filled up: up to twice the time on
+    caches of few elements.  n = 0: pair searches."""
     cache = siso.SisoCache(d, K, siso.F32 if dtype == "f32" else siso.BF16)
     assert not cache.screened(n)  # (empty)
     cache.load(torch.ones(K, d, device=DEV, dtype=TYPES[dtype]))
@@ -302,7 +305,7 @@ def test_left_over_queries_of_every_piece_are_summed_alike(siso):
     hold) return the bits of siso_lookup_static, which judges the batch as one, in a last piece of any length too."""
     print("case: screen left-over queries of several pieces", flush=True)
     g = torch.Generator(device=DEV).manual_seed(21)
-    d, K = 128, 200000
+    d, K = 256, 100000
     c = torch.randn(K, d, device=DEV, generator=g).to(torch.bfloat16)
     c[2000:5000] = c[2000]
     for n in (16384 + 1, 16384 + 100, 2 * 16384 + 300):
