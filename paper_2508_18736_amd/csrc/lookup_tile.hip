@@ -481,10 +481,9 @@ TilePlan tile_plan(const siso_cache *c, long n, bool groups, bool left) {
     const long resident = p.cfg == 2 ? 512 : 1024;  // workgroups the chip holds at a time
     const long ct = tiles(c->count, bc), qt = tiles(n, bq);
     long tps = (ct * qt + resident - 1) / resident;
-    if (left && tps > 4) tps = ct * qt > 4 * 4096 ? (ct * qt + 4095) / 4096 : 4;
     if (tps > ct) tps = ct;
     if (tps < 1) tps = 1;
-    if (p.cfg == 2 && !left) {
+    if (p.cfg == 2) {
         // The large tiles keep the matrix cores of a compute unit busy two at a time, so what counts is the number of tiles
         // the busiest unit gets: among the slice lengths, the one with the least of them, a workgroup counted as its
         // tiles and a fifth for getting started (8 query tiles x 469 centroid tiles: 94 slices of 5 leave the busiest
@@ -500,6 +499,10 @@ TilePlan tile_plan(const siso_cache *c, long n, bool groups, bool left) {
                 tps = t;
             }
         }
+    }
+    if (left && tps > 4) {
+        const long most = (ct * qt + 4095) / 4096;
+        tps = most > 4 ? most : 4;
     }
     p.tiles_per_slice = (int)tps;
     p.slices = (int)tiles(ct, (int)tps);

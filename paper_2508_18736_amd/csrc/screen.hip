@@ -1380,7 +1380,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
         crowd.rows = ahead * 256.f;
         crowd.heavy = (int)(worth < flood ? worth : flood);
     } else if (2 * again_per_query(c, c->count) < SCREEN_LIST) {  // (the bound gets better yet: half as many will count)
-        crowd.most = (float)again_per_query(c, c->count);
+        crowd.most = 1.25f * again_per_query(c, c->count);
     }
     int *lost = r.totals + 2;
     // The bytes of the rows that are looked at first, and the others only once the batch is not given up (of more queries they are
