@@ -273,7 +273,8 @@ def test_crowded_rows_do_not_pay_twice(siso):
 @pytest.mark.parametrize("dtype,K,d,n,wanted", [("f32", 1000, 768, 8192, False), ("f32", 8000, 128, 32768, True), ("f32", 60000, 384, 128, False),
                                                 ("bf16", 50000, 128, 65536, False), ("bf16", 16000, 1024, 32768, False),
                                                 ("bf16", 30000, 768, 16384, True), ("bf16", 65536, 768, 4096, False),
-                                                ("bf16", 400000, 128, 8192, False), ("bf16", 200000, 192, 8192, False), ("bf16", 200000, 320, 8192, True), ("f32", 1250, 1000, 0, False), ("f32", 2000, 384, 0, True),
+                                                ("bf16", 400000, 128, 8192, False), ("bf16", 200000, 192, 8192, False),
+                                                ("bf16", 200000, 320, 8192, True), ("f32", 1250, 1000, 0, False), ("f32", 2000, 384, 0, True),
                                                 ("bf16", 14000, 128, 0, False), ("bf16", 10000, 256, 0, False), ("bf16", 6553, 768, 0, True)])
 def test_small_caches_are_not_screened(siso, dtype, K, d, n, wanted):
     """Each query costs its candidates, whatever its products take, and short bf16 rows are filled up: up to twice the time on
