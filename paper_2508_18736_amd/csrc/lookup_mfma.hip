@@ -373,7 +373,7 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int i = 0; i < NSTAGE && i < T; ++i) issue();
         if (T >= NSTAGE) vm_wait<(NSTAGE - 1) * NL>();
         else vm_wait<0>();
-        __syncthreads();
+        slab_barrier();
         read_b(IC<0>{}, 0u, 0);
         static_for<0, WC>([&](auto ia) __attribute__((always_inline)) { read_a(ia, 0u, 0); });
         unsigned sto = 0;  // byte offset of the stage of slab t
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             wait_all_but(IC<0>{});
             if (t + NSTAGE <= T) vm_wait<(NSTAGE - 2) * NL>();
             else vm_wait<0>();
-            __syncthreads();
+            slab_barrier();
             if (t + NSTAGE < T) issue();
             // (behind the last slab these read the stage of a slab that does not exist: within LDS, never used)
             read_b(IC<0>{}, sto_next, 0);
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             if (T >= NSTAGE) vm_wait<(NSTAGE - 1) * NL>();
             else vm_wait<0>();
         }
-        __syncthreads();
+        slab_barrier();
         lds_frags<SUB>(af[0], bf[0], row_a + so[0], row_b + so[0]);
 
         unsigned sto = 0;  // byte offset of the stage of slab t
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             lds_wait<0>(af[1], bf[1]);
             if (t + NSTAGE <= T) vm_wait<(NSTAGE - 2) * NL>();
             else vm_wait<0>();
-            __syncthreads();
+            slab_barrier();
             if constexpr (DEAL) {
                 // (behind the last slab the stage of a slab that does not exist: within LDS, never used)
                 lds_frags<SUB>(af[0], bf[0], row_a + sto_next + so[0], row_b + sto_next + so[0]);
