@@ -295,8 +295,8 @@ __global__ __launch_bounds__(256, Cfg::WC * Cfg::WQ == 1 ? 3 : 2) void k_lookup_
 #pragma unroll
     for (int j = 0; j < Cfg::WQ; ++j) {
         u64 key = at[j] < 0 ? 0ull : pack_key(best[j], (unsigned)at[j]);
-        const u64 other = __shfl_xor(key, 32);
-        key = other > key ? other : key;
+        const LanePair<u64> both = lane_pair<32>(key);
+        key = both.b > both.a ? both.b : both.a;
         if (h == 0) red[wc][(wq * Cfg::WQ + j) * 32 + lane] = key;
     }
     __syncthreads();
@@ -385,8 +385,8 @@ __global__ __launch_bounds__(256) void k_lookup_split(const float *__restrict__ 
         }
     }
     u64 key = at < 0 ? 0ull : pack_key(best, (unsigned)at);
-    const u64 other = __shfl_xor(key, 32);
-    key = other > key ? other : key;
+    const LanePair<u64> both = lane_pair<32>(key);
+    key = both.b > both.a ? both.b : both.a;
     if (h == 0) best_s[wave][lane] = key;
     __syncthreads();
     if (t < 32 && q0 + t < n) {

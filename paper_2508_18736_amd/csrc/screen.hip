@@ -159,8 +159,7 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
                 for (int i = 0; i < 4; ++i) ss = fmaf(element(j, c, i), element(j, c, i), ss);
             inv[j] = inv_length(wave_sum(ss));
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off));
+        a = wave_max(a);
         kind[j] = !(inv[j] == inv[j]) ? SCREEN_NAN : inv[j] > 1e15f || (inv[j] != 0.f && inv[j] < 1e-15f) ? SCREEN_PLAIN : 0;
         // (an inverse length of 0 is that of a row without length, all of whose cosines are 0 - or of one whose squares vanish)
         if (inv[j] == 0.f && (!ROWS || a > 0.f)) kind[j] = SCREEN_PLAIN;
@@ -741,11 +740,7 @@ __global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, co
                 const u64 key = pack_key(__uint_as_float(e.y), e.x);
                 high = key > high ? key : high;
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const u64 o = __shfl_xor(high, off);
-                high = o > high ? o : high;
-            }
+            high = wave_max(high);
             if (high != 0) r = (long)(0xFFFFFFFFu - (unsigned)(high & 0xFFFFFFFFull));
         } else {
             if (seed[q] != 0) r = (long)(0xFFFFFFFFu - (unsigned)(seed[q] & 0xFFFFFFFFull));
@@ -817,11 +812,7 @@ __global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, co
             const u64 key = pack_key(__uint_as_float(e.y), e.x);
             high = key > high ? key : high;
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const u64 o = __shfl_xor(high, off);
-            high = o > high ? o : high;
-        }
+        high = wave_max(high);
         first = (int)(0xFFFFFFFFu - (unsigned)(high & 0xFFFFFFFFull));
         const float sv = row_product<T>(qrow, sh_q[wave], vec, cent + (size_t)first * d, d, lane) * qi * invn[first];
         if (sv == sv) {  // a NaN never wins

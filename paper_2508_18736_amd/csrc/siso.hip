@@ -227,11 +227,7 @@ __global__ __launch_bounds__(256) void k_lookup_finalize(const T *__restrict__ Q
         key = k2 > key ? k2 : key;
     }
     ss = wave_sum(ss);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const u64 o = __shfl_xor(key, off);
-        key = o > key ? o : key;
-    }
+    key = wave_max(key);
     if (lane == 0) {
         sh_f[wave] = ss;
         sh_k[wave] = key;
@@ -616,11 +612,7 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
         key = k2 > key ? k2 : key;
     }
     ss = wave_sum(ss);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const u64 o = __shfl_xor(key, off);
-        key = o > key ? o : key;
-    }
+    key = wave_max(key);
     if (lane == 0) {
         sh_f[wave] = ss;
         sh_k[wave] = key;
@@ -918,11 +910,9 @@ __device__ __forceinline__ void scan_load(const int *__restrict__ members_of, co
 }
 // sum over a 1024-thread block of two numbers; every thread gets both
 __device__ __forceinline__ int2 block_sum1024(int a, int b, int2 *sh) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-    }
+    const auto sum = [](int x, int y) __attribute__((always_inline)) { return x + y; };
+    a = wave_fold(a, sum);
+    b = wave_fold(b, sum);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = make_int2(a, b);
     __syncthreads();

@@ -205,10 +205,67 @@ __device__ __forceinline__ float inv_length(float sumsq) {
     return 1.0f / sqrtf(sumsq);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
+// Reductions over the 64 lanes of a wave (all of them must call); every lane gets the result.  A butterfly over 32, 16, 8, 4, 2, 1
+// whose partners come by v_permlane32_swap, v_permlane16_swap and, within 16 lanes, DPP moves: ten vector instructions.
+// __shfl_xor sends each step through the LDS crossbar, a round trip of some hundred cycles that a compute unit's waves queue
+// for: six in a row are what the small kernels around a lookup waited for.  Pairs and order are the same, and so are the bits of
+// a sum.  Batches with their updates, us: 4 of 256 against 1,024 x 384 fp32 74.5 -> 69.8, 2 of 1,000 against 60,000 x 384 257 -> 243,
+// 16 of one against 60,000 x 768 bf16 381 -> 364 (371 of which the barrier between slabs had left), 16 of 64 against
+// 262,144 x 768 codes 771 -> 743.
+// Of a swap, the first number returned holds the lower half (the even rows of 16 lanes) in both, the second the upper.
+template <class V>
+struct LanePair {
+    V a, b;
+};
+template <int OFF, class V>
+__device__ __forceinline__ LanePair<V> lane_pair(V v) {
+    static_assert(sizeof(V) % 4 == 0, "whole registers");
+    constexpr int N = (int)sizeof(V) / 4;
+    struct Words {
+        unsigned w[N];
+    };
+    const Words in = __builtin_bit_cast(Words, v);
+    Words a, b;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    for (int i = 0; i < N; ++i) {
+        a.w[i] = in.w[i];
+        if constexpr (OFF == 32) {
+            const auto r = __builtin_amdgcn_permlane32_swap(in.w[i], in.w[i], false, false);
+            a.w[i] = r[0];
+            b.w[i] = r[1];
+        } else if constexpr (OFF == 16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(in.w[i], in.w[i], false, false);
+            a.w[i] = r[0];
+            b.w[i] = r[1];
+        } else if constexpr (OFF == 8) {
+            b.w[i] = (unsigned)__builtin_amdgcn_mov_dpp((int)in.w[i], 0x128, 0xF, 0xF, true);  // row_ror:8
+        } else if constexpr (OFF == 4) {  // l ^ 7, then l ^ 3
+            const int t = __builtin_amdgcn_mov_dpp((int)in.w[i], 0x141, 0xF, 0xF, true);  // row_half_mirror
+            b.w[i] = (unsigned)__builtin_amdgcn_mov_dpp(t, 0x1B, 0xF, 0xF, true);         // quad_perm:[3,2,1,0]
+        } else if constexpr (OFF == 2) {
+            b.w[i] = (unsigned)__builtin_amdgcn_mov_dpp((int)in.w[i], 0x4E, 0xF, 0xF, true);  // quad_perm:[2,3,0,1]
+        } else {
+            static_assert(OFF == 1, "a power of two below 64");
+            b.w[i] = (unsigned)__builtin_amdgcn_mov_dpp((int)in.w[i], 0xB1, 0xF, 0xF, true);  // quad_perm:[1,0,3,2]
+        }
+    }
+    return LanePair<V>{__builtin_bit_cast(V, a), __builtin_bit_cast(V, b)};
+}
+template <int OFF = 32, class V, class Op>
+__device__ __forceinline__ V wave_fold(V v, Op op) {
+    const LanePair<V> p = lane_pair<OFF>(v);
+    const V both = op(p.a, p.b);
+    if constexpr (OFF == 1) return both;
+    else return wave_fold<OFF / 2>(both, op);
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    return wave_fold(v, [](float a, float b) __attribute__((always_inline)) { return a + b; });
+}
+__device__ __forceinline__ float wave_max(float v) {
+    return wave_fold(v, [](float a, float b) __attribute__((always_inline)) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ u64 wave_max(u64 v) {
+    return wave_fold(v, [](u64 a, u64 b) __attribute__((always_inline)) { return b > a ? b : a; });
 }
 
 // 16-byte chunk dot products (finalize, top-k re-ranking)
@@ -335,8 +392,7 @@ __device__ __forceinline__ unsigned f32_to_e4m3(float y) {
     return sign | ((((v >> 23) - 120u) << 3) | ((v >> 20) & 7u));
 }
 __device__ __forceinline__ float block_max256(float v, float *sh) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+    v = wave_max(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();

@@ -334,15 +334,10 @@ __global__ __launch_bounds__(256) void k_topk_bound(const u64 *__restrict__ keys
                 best = sk[s];
                 pos = s;
             }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const u64 ob = __shfl_xor(best, off);
-            const int op = __shfl_xor(pos, off);
-            if (ob > best) {  // keys of different slices differ (they name different rows)
-                best = ob;
-                pos = op;
-            }
-        }
+        // keys of different slices differ (they name different rows)
+        const u64 top = wave_max(best);
+        pos = __builtin_amdgcn_readlane(pos, __ffsll((long long)__ballot(best == top)) - 1);
+        best = top;
         if ((t & 63) == 0) {
             wmax[t >> 6] = best;
             wpos[t >> 6] = pos;
