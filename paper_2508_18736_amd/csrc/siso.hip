@@ -652,9 +652,10 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
         x_me[e] = t + e * 256 < d ? widen(xr[e]) : 0.f;
         asm volatile("" ::"v"(x_me[e]), "v"(m_old[e]));  // (the loads are issued here, not behind the wait)
     }
-    // the board: wave 0 reads the slots until all of them are written
+    // the board: wave 0 reads the slots until all of them are written (one query has nobody to wait for)
     if (wave == 0) {
-        bool all = false;
+        bool all = n == 1;
+        if (all && lane == 0) sh_board[0] = board_entry(hit, k);
         for (int tries = 0; tries < spin_limit && !all; ++tries) {
             bool mine = true;
             for (int j = lane; j < (int)n; j += 64) {
@@ -1315,6 +1316,7 @@ extern "C" int siso_import(siso_cache *c, const void *centroids, const float *me
 
 static int choose_path(const siso_cache *c, long n) {
     if (c->path != SISO_PATH_AUTO) return c->path;
+    if (siso_few_slices(c, n) > 0) return SISO_PATH_FEW;
     if (siso_tile_preferred(c, n)) return SISO_PATH_SCALAR;
     if (n <= 64 && siso_skinny_slices(c, n) > 0) return SISO_PATH_SKINNY;
     if (siso_mfma_slices(c, n) > 0) return SISO_PATH_MFMA;
@@ -1342,6 +1344,7 @@ static long keys_needed(const siso_cache *c, long n) {
         case SISO_PATH_SCALAR: slices = siso_tile_slices(c, n); break;
         case SISO_PATH_MFMA: slices = siso_mfma_slices(c, n); break;
         case SISO_PATH_SKINNY: slices = siso_skinny_slices(c, n); break;
+        case SISO_PATH_FEW: slices = siso_few_slices(c, n); break;
     }
     return slices > 0 ? n * (long)slices : 0;
 }
@@ -1425,6 +1428,7 @@ static int plan_plain(siso_cache *c, long n, u64 *static_keys, long static_cap, 
             case SISO_PATH_SCALAR: slices = siso_tile_slices(c, n, left); break;
             case SISO_PATH_MFMA: slices = siso_mfma_slices(c, n); break;
             case SISO_PATH_SKINNY: slices = siso_skinny_slices(c, n); break;
+            case SISO_PATH_FEW: slices = siso_few_slices(c, n); break;
         }
         if (slices <= 0)
             return siso_fail(c, SISO_EINVAL, "siso_lookup: path %d cannot serve dim %d, type %d, batch %ld", path,
@@ -1475,6 +1479,7 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
             case SISO_PATH_SCALAR: rc = siso_tile_launch(c, kernel_queries, n, slices, keys, many); break;
             case SISO_PATH_MFMA: rc = siso_mfma_launch(c, kernel_queries, n, slices, keys, &row_keys, many); break;
             case SISO_PATH_SKINNY: rc = siso_skinny_launch(c, kernel_queries, n, slices, keys, &row_keys); break;
+            case SISO_PATH_FEW: rc = siso_few_launch(c, kernel_queries, n, slices, keys); break;
         }
         if (timed) siso_prof_end(c);
         if (rc != SISO_OK) {

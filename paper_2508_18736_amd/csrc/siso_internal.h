@@ -564,6 +564,10 @@ int siso_tile_launch(siso_cache *c, const void *queries, long n, int slices, u64
 inline bool siso_mfma_aligned(const void *queries) { return ((uintptr_t)queries & 15) == 0; }
 int siso_mfma_slices(const siso_cache *c, long n);
 int siso_mfma_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys, const int *many = nullptr);
+// Up to 32 queries in single precision: the rows straight from memory into the matrix cores (lookup_few.hip).  Keys name rows.
+#define SISO_PATH_FEW 4  // (chosen, never set)
+int siso_few_slices(const siso_cache *c, long n);
+int siso_few_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys);
 int siso_skinny_slices(const siso_cache *c, long n);
 int siso_skinny_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
 
