@@ -387,8 +387,8 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
                                (bf16_t *)d_rows, d_rinv, d, bad_at);
         hipLaunchKernelGGL(k_nan_tail, dim3(1), dim3(SISO_PAD_ROWS), 0, st, d_rinv + r, SISO_PAD_ROWS);
         REFRESH_TRY(hipGetLastError(), "stage repository rows");
-        // every repository row against the cache (test lookups: no references are counted)
-        int rc = siso_lookup_impl(c, d_rows, r, &theta_c, 1, -1, d_idx, d_sim, nullptr);
+        // every repository row against the cache (test lookups: no references are counted); what does not exceed theta_c joins
+        int rc = siso_lookup_impl(c, d_rows, r, &theta_c, 1, -1, d_idx, d_sim, nullptr, nullptr, 0, nullptr, theta_c);
         // repository rows among themselves: the pairs above the threshold, then their cosines
         if (rc == SISO_OK && r >= 2) rc = search(d_pairs, cap);
         if (rc == SISO_OK && r >= 2) rc = cosines(d_pairs, 0, early, h_pairs, h_cos);

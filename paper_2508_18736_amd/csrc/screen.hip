@@ -41,6 +41,7 @@ typedef PipeCfg<4, 2, 2, 4, 2, 128, true, 1> ByteCfg;  // 256 x 256 tile, waves 
 #define SCREEN_SLACK 2e-5f        // roundings of the lengths, of the unit rows and of the sums formed anew (about 4e-6 in all)
 #define SCREEN_WHOLE 0x7FFFFFFF   // most_lost: never given up
 #define SCREEN_COUNTED 8          // of so many queries one is looked at for `lost` (atomic additions to one address: 10 ns each)
+#define SCREEN_LEAST_FLOOR 0.5f   // below it unrelated rows come near it, and it spares nothing
 #define SCREEN_PLAIN (-2)         // instead of a list's length: this query is left to the other kernels
 #define SCREEN_NAN (-1)           // and this one holds a NaN or an infinity
 
@@ -66,7 +67,7 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
                                                   int vec, signed char *__restrict__ codes, float4 *__restrict__ meta,
                                                   ScreenQuery *__restrict__ qm, unsigned *__restrict__ low, u64 *__restrict__ seed,
                                                   int *__restrict__ cnt, int *__restrict__ near, float *__restrict__ largest,
-                                                  int *__restrict__ totals, int d, int dp) {
+                                                  int *__restrict__ totals, int d, int dp, float least) {
     constexpr int R = 8;
     __shared__ float sh[4][4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -218,7 +219,7 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
             const long q = r0 + j;
             const bool ok = q < have && kind[j] == 0;
             qm[q] = ScreenQuery{ok ? scale : 1.f, ok ? e : -1.f};  // (grow = 0 in k_screen_lookup)
-            low[q] = ok ? ordered_bits(-INFINITY) : ordered_bits(INFINITY);  // (nothing reaches +inf: no list)
+            low[q] = ordered_bits(ok ? least : INFINITY);  // (nothing reaches +inf: no list)
             seed[q] = 0;
             cnt[q] = kind[j];
             near[q] = 0;
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows
                                                       signed char *__restrict__ qcodes, ScreenQuery *__restrict__ qm,
                                                       unsigned *__restrict__ low, u64 *__restrict__ seed, int *__restrict__ cnt,
                                                       int *__restrict__ near, float *__restrict__ largest, int *__restrict__ totals,
-                                                      int d, int dp, ScreenTiles tiles, int most_lost) {
+                                                      int d, int dp, ScreenTiles tiles, int most_lost, float least) {
     if (blockIdx.x < row_blocks) {
         long blk = blockIdx.x;
         if constexpr (PARTS) {
@@ -271,10 +272,10 @@ __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows
             }
         }
         write_bytes_block<T, NCH, true>(blk, rows, invn, K, row_vec, codes, meta, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                        nullptr, d, dp);
+                                        nullptr, d, dp, least);
     } else {
         write_bytes_block<T, NCH, false>(blockIdx.x - row_blocks, queries, nullptr, n, query_vec, qcodes, nullptr, qm, low, seed, cnt,
-                                         near, largest, totals, d, dp);
+                                         near, largest, totals, d, dp, least);
     }
 }
 
@@ -1299,7 +1300,7 @@ bool make_room(siso_cache *c, ScreenSpace &room, size_t bytes, std::vector<char 
 // rows (those of `tiles`, if with_rows) and n queries to bytes
 template <typename T>
 int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *invn, long count, bool with_rows, const T *queries, long n,
-                const ScreenTiles &tiles, int most_lost) {
+                const ScreenTiles &tiles, int most_lost, float least) {
     const int d = c->dim, dp = byte_dim(d);
     const long all = up256(count) / 256;
     const unsigned row_blocks = !with_rows ? 0u : 8u * (unsigned)(tiles.part == 0 ? all : tiles.part == 1 ? tiles.ahead + tiles.some : all - tiles.ahead);
@@ -1308,7 +1309,7 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *
     const int rv = d % 4 == 0 && (uintptr_t)rows % four == 0 ? 1 : 0, qv = d % 4 == 0 && (uintptr_t)queries % four == 0 ? 1 : 0;
 #define SISO_LAUNCH_BYTES2(NCH, PARTS)                                                                                        \
     hipLaunchKernelGGL((k_screen_bytes<T, NCH, PARTS>), grid, block, 0, c->stream, rows, invn, count, row_blocks, rv, r.codes, r.meta, \
-                       queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.totals, d, dp, tiles, most_lost)
+                       queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.totals, d, dp, tiles, most_lost, least)
 #define SISO_LAUNCH_BYTES(NCH)                      \
     if (tiles.part == 0) SISO_LAUNCH_BYTES2(NCH, false); \
     else SISO_LAUNCH_BYTES2(NCH, true)
@@ -1328,7 +1329,7 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *
 
 template <typename T>
 int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
-                  float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain) {
+                  float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain, float floor) {
     const ScreenRoom r = screen_room(c->screen.at, c, c->count, n);
     const int d = c->dim, dp = byte_dim(d);
     const long tiles = up256(c->count) / 256, nqt = up256(n) / 256;
@@ -1374,10 +1375,12 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
         crowd.most = 1.25f * again_per_query(c, c->count);
     }
     int *lost = r.totals + 2;
+    // (cosines are rounded: a row that exceeds the floor by the least bit is listed whatever its bytes)
+    const float least = floor >= SCREEN_LEAST_FLOOR ? floor - 1e-5f : -INFINITY;
     // The bytes of the rows that are looked at first, and the others only once the batch is not given up (of more queries they are
     // the smaller part: 500 / n of the time that all products take in bf16).
     ScreenTiles which = {with_rows && whole && ahead > 0 && n <= 8192 ? 1 : 0, (int)ahead, (int)some, some > 0 ? (int)(tiles / some) : 1};
-    int rc = write_bytes<T>(c, r, cent, c->invn, c->count, with_rows, queries, n, which, most_lost);
+    int rc = write_bytes<T>(c, r, cent, c->invn, c->count, with_rows, queries, n, which, most_lost, least);
     if (rc != SISO_OK) return rc;
     if (some > 0) {
         hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, r.codes,
@@ -1401,7 +1404,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
                                r.meta, r.seed, r.cnt, r.list, r.low, crowd);
             if (which.part == 1) {
                 which.part = 2;
-                rc = write_bytes<T>(c, r, cent, c->invn, c->count, true, queries, 0, which, most_lost);
+                rc = write_bytes<T>(c, r, cent, c->invn, c->count, true, queries, 0, which, most_lost, least);
                 if (rc != SISO_OK) return rc;
             }
         }
@@ -1429,7 +1432,7 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
         attr_done = true;
     }
     hipLaunchKernelGGL(k_screen_clear, dim3(1), dim3(1), 0, c->stream, r.maybe_count);
-    const int rc = write_bytes<T>(c, r, rows, invn, count, true, rows, 0, ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE);
+    const int rc = write_bytes<T>(c, r, rows, invn, count, true, rows, 0, ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f);
     if (rc != SISO_OK) return rc;
     int qb = 8;
     while (qb > 1 && qb > up256(count) / 256) qb >>= 1;
@@ -1491,6 +1494,18 @@ int siso_screen_wanted(const siso_cache *c, long n) {
     return n >= 768 && 2.0 * (double)n * saved >= 3.75e11 && saved >= 1.1e7;  // (both lines: half of the bf16 work, mostly)
 }
 
+// A floor leaves queries that miss without candidates, so smaller lookups are ahead (bf16; a lookup with the rest of its call, us,
+// without -> with): a refresh of 40,000 x 768 by 5,000 rows 656 -> 639, of 100,000 x 1,024 by 2,500 912 -> 811, of 200,000 x 256 by 5,000
+// 1,041 -> 973, of 65,536 x 768 by 6,553 (553 us of it all products) 140 less; 3,276 samples of a table against 65,536 x 768
+// 372 -> 357; behind the line 1,638 rows against 65,536 x 768 432 -> 445, 3,276 against 65,536 x 384 220 -> 262.
+int siso_screen_above_wanted(const siso_cache *c, long n, float floor) {
+    if (siso_screen_wanted(c, n)) return 1;
+    if (!(floor >= SCREEN_LEAST_FLOOR) || c->dtype != SISO_BF16 || c->opt_screen == 2 || c->dim > SISO_SCREEN_DIM || c->dim < 128) return 0;
+    if (c->path != SISO_PATH_AUTO || c->opt_mfma_config != 0 || c->opt_tiles_per_slice != 0 || c->opt_mfma_qblock != 0) return 0;
+    const double saved = (double)c->count * saved_dim(c->dim);
+    return n >= 768 && 2.0 * (double)n * saved >= 1.5e11 && saved >= 1.1e7;
+}
+
 extern "C" int siso_screened(const siso_cache *c, long n) {
     if (!c || n < 0) return SISO_EINVAL;
     return n == 0 ? siso_screen_pairs_wanted(c, c->count, 1.f) : siso_screen_wanted(c, n);
@@ -1536,7 +1551,7 @@ void siso_screen_release(siso_cache *c) {
 }
 
 int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
-                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain) {
+                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain, float floor) {
     // A graph that records the launches goes on using the workspace when a larger call has outgrown it.
     if (!c->screen_recorded && capturing(c)) {
         try {
@@ -1548,9 +1563,9 @@ int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_row
         c->screen_recorded = 1;
     }
     return c->dtype == SISO_F32 ? screen_launch<float>(c, (const float *)queries, n, with_rows, whole, tl, q_base, out_idx, out_sim, out_hit,
-                                                       access, owner, members, plain)
+                                                       access, owner, members, plain, floor)
                                 : screen_launch<bf16_t>(c, (const bf16_t *)queries, n, with_rows, whole, tl, q_base, out_idx, out_sim, out_hit,
-                                                        access, owner, members, plain);
+                                                        access, owner, members, plain, floor);
 }
 
 // Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 52, 2,000 x 768

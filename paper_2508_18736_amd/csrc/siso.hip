@@ -1451,7 +1451,7 @@ static int plan_plain(siso_cache *c, long n, u64 *static_keys, long static_cap, 
 // or NULL.  left: the queries that a screened lookup has left over (NULL: all are looked up).
 static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *queries, long n, const ThetaList &tl, long q_base,
                         int *out_idx, float *out_sim, unsigned char *out_hit, bool timed, int *folded, int *owner, int *members,
-                        const ScreenPlain *left) {
+                        const ScreenPlain *left, bool screen) {
     const int path = plan.path, slices = plan.slices, m = tl.m, count_index = tl.count_at;
     const bool fp8 = c->dtype == SISO_FP8;
     const int *many = left ? left->many : nullptr, *of = left ? left->query : nullptr;
@@ -1470,7 +1470,7 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
     int row_keys = SISO_KEY_ROWS;  // what the keys of the chosen kernel carry: the winning row, or its group of four rows
     // (the similarities of a batch are the same bits whether it is screened, as it would be with enough memory, or not: then
     // they are formed anew, which the kernel that ends a lookup together with its update does not do)
-    const bool anew = left || siso_screen_wanted(c, n);
+    const bool anew = left || screen;
     const bool may_fold = folded && !anew && n <= SISO_FOLD_BOARD && c->count > 0 && (!fp8 || c->fold_master) && m == 1 && out_hit;
     c->board_to_clear = may_fold ? c->counters + 4 : nullptr;
     if (c->count > 0) {
@@ -1532,7 +1532,7 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
 }
 
 int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *thetas, int m, int count_index,
-                     int *out_idx, float *out_sim, unsigned char *out_hit, u64 *static_keys, long static_cap, int *folded) {
+                     int *out_idx, float *out_sim, unsigned char *out_hit, u64 *static_keys, long static_cap, int *folded, float floor) {
     if (folded) *folded = 0;
     if (n == 0) return SISO_OK;
     if (n > 2147483647L / 4) return siso_fail(c, SISO_EINVAL, "siso_lookup: batch of %ld is too large", n);
@@ -1548,7 +1548,8 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
     }
     PlainLookup plain;
     // (not on the static keys: the bytes live in a workspace that other calls share and a larger one moves)
-    if (!static_keys && siso_screen_wanted(c, n) && siso_screen_room(c, n)) {
+    const bool screen = siso_screen_above_wanted(c, n, floor);
+    if (!static_keys && screen && siso_screen_room(c, n)) {
         // piece by piece: screened, then what that has left over.  Pieces of as many tiles of 256 queries each: a short last one
         // would go through the kernels for few queries, which do not know how many of them there are.
         const size_t row = (size_t)c->dim * elem_bytes(c->dtype);
@@ -1567,15 +1568,15 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
             if (plain.path != SISO_PATH_SCALAR && !siso_mfma_aligned(queries)) return siso_fail(c, SISO_EINVAL, SISO_MFMA_UNALIGNED);
             if (owner) c->mark_in_finalize = 2;
             rc = siso_screen_lookup(c, q, part, off == 0, pieces == 1, tl, off, out_idx + off, out_sim + off, hit,
-                                    count_index >= 0 ? c->access : nullptr, owner, members, &left);
+                                    count_index >= 0 ? c->access : nullptr, owner, members, &left, floor);
             if (rc == SISO_OK)
-                rc = plain_lookup(c, plain, left.rows, part, tl, off, out_idx + off, out_sim + off, hit, false, nullptr, owner, members, &left);
+                rc = plain_lookup(c, plain, left.rows, part, tl, off, out_idx + off, out_sim + off, hit, false, nullptr, owner, members, &left, true);
         }
         return rc;
     }
     int rc = plan_plain(c, n, static_keys, static_cap, false, &plain);
     if (rc == SISO_OK)
-        rc = plain_lookup(c, plain, queries, n, tl, 0, out_idx, out_sim, out_hit, !static_keys, folded, owner, members, nullptr);
+        rc = plain_lookup(c, plain, queries, n, tl, 0, out_idx, out_sim, out_hit, !static_keys, folded, owner, members, nullptr, screen);
     if (rc == SISO_OK && owner && !(folded && *folded)) c->mark_in_finalize = 2;  // done
     return rc;
 }
@@ -1930,7 +1931,10 @@ extern "C" int siso_t2h(siso_cache *c, const void *queries, long n, const float 
     if (e == hipSuccess) e = hipMemsetAsync(d_hits, 0, (size_t)m * sizeof(u64), c->stream);
     if (e != hipSuccess) rc = siso_check_hip(c, e, "siso_t2h: set-up");
     const float no_theta = 0.f;
-    if (rc == SISO_OK) rc = siso_lookup_impl(c, queries, n, &no_theta, 1, -1, idx, sim, nullptr);  // test lookups are no references
+    float floor = INFINITY;  // what does not exceed the lowest threshold is not told apart
+    for (int j = 0; j < m; ++j) floor = thetas[j] < floor ? thetas[j] : floor;
+    if (rc == SISO_OK)  // (test lookups are no references)
+        rc = siso_lookup_impl(c, queries, n, &no_theta, 1, -1, idx, sim, nullptr, nullptr, 0, nullptr, floor);
     u64 host_hits[SISO_T2H_MAX];
     if (rc == SISO_OK) {
         hipLaunchKernelGGL(k_t2h_count, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, sim, n, d_th, m, d_hits);

@@ -602,13 +602,16 @@ struct ScreenPlain {
     int vec;
 };
 int siso_screen_wanted(const siso_cache *c, long n);
+// The same for a lookup that only asks for cosines above `floor`: a query that nothing exceeds it by may get any row that does not,
+// or none.  Rows below it are not even listed, so queries that miss cost nothing behind the products of the bytes.
+int siso_screen_above_wanted(const siso_cache *c, long n, float floor);
 int siso_screen_room(siso_cache *c, long n);  // may synchronise and allocate, but not under capture
 void siso_screen_reserve(siso_cache *c, long n);  // siso_reserve: room for a full cache
 int siso_screen_pairs_room(siso_cache *c, long rows);
 void siso_screen_done(siso_cache *c);
 void siso_screen_release(siso_cache *c);
 int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
-                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain);
+                       float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain, float floor);
 // The same for pairs above a threshold (room: siso_screen_pairs_room; siso_screen_done, at the end of a call, gives
 // back what is larger than the library keeps between calls).  Behind it the search of all pairs has to be
 // launched with `redo`: its workgroups leave at once unless more than redo.above pairs were in doubt.
@@ -646,9 +649,10 @@ int siso_pairs_mfma_launch(siso_cache *c, const void *rows, const float *invn, l
 // folded: NULL = a lookup and nothing else; otherwise the caller is about to fold the hits into their centroids
 // and *folded tells whether the lookup has already done it (small batches: one kernel ends the lookup and
 // applies the update).
+// floor: only cosines above it matter to the caller (see siso_screen_above_wanted).
 int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *thetas, int m, int count_index,
                      int *out_idx, float *out_sim, unsigned char *out_hit, u64 *static_keys = nullptr,
-                     long static_cap = 0, int *folded = nullptr);
+                     long static_cap = 0, int *folded = nullptr, float floor = -INFINITY);
 int siso_fp8_load(siso_cache *c, const void *centroids, const int *counts, long k);  // siso_load of an 8-bit cache
 int siso_fp8_ensure_batch(siso_cache *c, long n);
 int siso_fp8_quantize_batch(siso_cache *c, const void *queries, long n);  // bf16 queries -> c->fp8_q, c->fp8_qinv

@@ -579,3 +579,40 @@ def test_pairs_near_the_threshold_do_not_pay_many_times(siso):
             torch.cuda.synchronize()
             took.append(begin.elapsed_time(end))
         assert took[1] < 3 * took[0], took
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("K,n,d", [(1, 3, 128), (257, 300, 300), (9000, 1025, 768), (70001, 2300, 384)])
+def test_lookups_above_a_floor(siso, dtype, K, n, d):
+    """Tables and refreshes only ask for cosines above a threshold: what the bytes rule out below it changes no result."""
+    import numpy as np
+    print(f"case: floor {dtype} K={K} n={n} d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K + n + d)
+    base = torch.randn(max(1, K // 8), d, device=DEV, generator=g)
+    c = rows_near(g, base, K, 0.1, TYPES[dtype])
+    q = torch.cat([rows_near(g, c, n - n // 2, 0.45, TYPES[dtype]), torch.randn(n // 2, d, device=DEV, generator=g).to(TYPES[dtype])])
+    q = q[torch.randperm(n, device=DEV, generator=g)].contiguous()
+    best = (unit(q) @ unit(c).T).max(1).values
+    # thresholds that no cosine comes within the roundings of; floors that count, and some that do not
+    for thetas in ([0.95, 0.9, 0.85], [0.9, 0.5], [0.9, 0.3], [0.9, -2.0], [float("nan"), 0.9], [1.5], [float("nan")]):
+        th = np.array(thetas, np.float32)
+        for i, t in enumerate(th):
+            while t == t and (best - float(t)).abs().min() <= 2 * TOL:
+                t = th[i] = t + np.float32(1e-4)
+        got = make(siso, c, dtype).t2h(q, th)
+        assert got.tolist() == [int((best > float(t)).sum()) for t in th], thetas
+    sizes = torch.randint(1, 40, (n,), device=DEV, generator=g).float()
+    for theta in (0.9, 0.7, 0.3):
+        ends = []
+        for screen in (1, 2):
+            cache = siso.SisoCache(d, K + n, TYPE_CODES(siso)[dtype])
+            cache.set_option("screen", screen)
+            cache.load(c)
+            stats = cache.refresh(q, sizes, theta, K + n // 4)
+            ends.append((stats, *(x.clone() for x in cache.export() + cache.export_meta())))
+        assert ends[0][0] == ends[1][0]
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(ends[0][1:], ends[1][1:]))
+
+
+def TYPE_CODES(siso):
+    return {"f32": siso.F32, "bf16": siso.BF16}
