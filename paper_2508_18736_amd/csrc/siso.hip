@@ -308,6 +308,9 @@ __global__ void k_update_mark_init(int *owner, int *members, long capacity) {
     }
 }
 
+// a vector with this sum of squares can be scaled to unit length (inv_length is a number above 0)
+__device__ __forceinline__ bool has_length(float n2) { return n2 > 0.f && n2 <= 3.0e38f; }
+
 // One member of a centroid: x = this thread's elements (t + 256 e) of the query; the query at unit length is
 // added to acc (queries without length or with a non-finite element are passed over).  Uniform over the
 // block.  Every operation is spelled out with its rounding, here and in update_write, so that k_update and
@@ -318,34 +321,54 @@ __device__ __forceinline__ bool fold_member(const float (&x)[UPD_MAXE_T], float 
 #pragma unroll
     for (int e = 0; e < UPD_MAXE_T; ++e) ss = __fmaf_rn(x[e], x[e], ss);
     const float n2 = block_sum256(ss, sh);
-    const float inv = inv_length(n2);
-    if (!(inv == inv && inv > 0.f)) return false;
+    if (!has_length(n2)) return false;
     const float nrm = sqrtf(n2);
 #pragma unroll
     for (int e = 0; e < UPD_MAXE_T; ++e) acc[e] = __fadd_rn(acc[e], __fdiv_rn(x[e], nrm));
     return true;
 }
 
-// The members list[0 .. count) of a centroid but for the first, which the caller has folded: M at a time, so that
-// their rows are on their way together and their lengths share two barriers; the sums take them in the order of the
-// list, with the arithmetic of fold_member.
-template <typename T, int UPD_MAXE_T>
+#define FOLD_SUMS (2 * 4 * 8)
+// The members list[from .. to) of a centroid (the caller folds the first): M at a time, so that their rows are on their way
+// together (AHEAD: while the M before them are folded) and their lengths share a barrier; the sums take them in the order of the
+// list, with the arithmetic of fold_member.  A block alone works through its members one round after the other: four at a time, their rows
+// asked for when their turn had come, took 0.37 us a member, eight with the next eight on their way 0.28 (a centroid with 200 of 300
+// members, 768 elements: the update 91.6 -> 65.6 us; k_finalize_update has few members and is quicker with four, none ahead; 8,192 queries on 1,000 x 128 rows, lookup and update, 118.8 -> 93.5).
+// sums: FOLD_SUMS of them.
+template <typename T, int UPD_MAXE_T, int M, bool AHEAD>
 __device__ __forceinline__ int fold_list(const int *list, int from, int to, const T *__restrict__ Q, int d,
-                                         float (&acc)[UPD_MAXE_T], float4 *sh4) {
-    constexpr int M = UPD_MAXE_T <= 4 ? 4 : 2;  // members at a time (two of the longest rows)
-    const int t = threadIdx.x;
+                                         float (&acc)[UPD_MAXE_T], float *sums) {
+    static_assert(2 * 4 * M <= FOLD_SUMS, "two buffers of a sum for every wave and member");
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     int members = 0;
-    for (int p = from; p < to; p += M) {
-        float x[M][UPD_MAXE_T], n2[4] = {0.f, 0.f, 0.f, 0.f};
+    bool odd = false;
+    if (from >= to) return 0;
+    to = __builtin_amdgcn_readfirstlane(to);  // (the same for the whole block)
+    T raw[M][UPD_MAXE_T];
+    // (without a condition, also behind the last member: the registers of a load that may not happen are copied at the
+    // end of the round, which waits for it)
+    auto ask = [&](int p) __attribute__((always_inline)) {
+        int row[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) row[m] = list[p + m < to ? p + m : to - 1];
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            const T *row = Q + (size_t)list[p + m < to ? p + m : p] * d;
+            const T *at = Q + (size_t)__builtin_amdgcn_readfirstlane(row[m]) * d;
 #pragma unroll
-            for (int e = 0; e < UPD_MAXE_T; ++e) {
-                const int col = t + e * 256;
-                const float v = widen(row[col < d ? col : 0]);
-                x[m][e] = col < d ? v : 0.f;
-            }
+            for (int e = 0; e < UPD_MAXE_T; ++e) raw[m][e] = at[(unsigned)(t + e * 256 < d ? t + e * 256 : 0)];
+        }
+    };
+    if (AHEAD) ask(from);
+    for (int p = from; p < to; p += M) {
+        if (!AHEAD) ask(p);
+        float x[M][UPD_MAXE_T], n2[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int e = 0; e < UPD_MAXE_T; ++e) x[m][e] = t + e * 256 < d ? widen(raw[m][e]) : 0.f;
+        if (AHEAD) {
+            ask(p + M);
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int m = 0; m < M; ++m) {
@@ -354,20 +377,20 @@ __device__ __forceinline__ int fold_list(const int *list, int from, int to, cons
             for (int e = 0; e < UPD_MAXE_T; ++e) ss = __fmaf_rn(x[m][e], x[m][e], ss);
             n2[m] = wave_sum(ss);
         }
+        float *const at = sums + (odd ? 4 * M : 0);  // (two buffers in turn: one barrier a round)
+        odd = !odd;
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            if (lane == 0) at[wave * M + m] = n2[m];
         __syncthreads();
-        if ((t & 63) == 0) sh4[t >> 6] = make_float4(n2[0], n2[1], n2[2], n2[3]);
-        __syncthreads();
-        const float4 a = sh4[0], b = sh4[1], c = sh4[2], e4 = sh4[3];
-        n2[0] = (a.x + b.x) + (c.x + e4.x);
-        n2[1] = (a.y + b.y) + (c.y + e4.y);
-        n2[2] = (a.z + b.z) + (c.z + e4.z);
-        n2[3] = (a.w + b.w) + (c.w + e4.w);
+        // lane l finds the length of member l % M
+        const float n2_l = (at[lane % M] + at[M + lane % M]) + (at[2 * M + lane % M] + at[3 * M + lane % M]);
+        const float nrm_l = sqrtf(n2_l);
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             if (p + m >= to) break;
-            const float inv = inv_length(n2[m]);
-            if (!(inv == inv && inv > 0.f)) continue;
-            const float nrm = sqrtf(n2[m]);
+            if (!has_length(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(n2_l), m)))) continue;
+            const float nrm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nrm_l), m));
 #pragma unroll
             for (int e = 0; e < UPD_MAXE_T; ++e) acc[e] = __fadd_rn(acc[e], __fdiv_rn(x[m][e], nrm));
             ++members;
@@ -432,7 +455,7 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
                                                  int *size, float *invn, long count, int d, u64 *bad, int *owner,
                                                  int *marked) {
     __shared__ float sh[4];
-    __shared__ float4 sh4[4];
+    __shared__ float sums[FOLD_SUMS];
     __shared__ u64 masks[4];
     __shared__ int cells[UPD_SCAN / 64];
     __shared__ int list[UPD_SCAN];
@@ -500,7 +523,7 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
         __syncthreads();
         if (list[0] != (int)me) return;  // an earlier member leads this centroid
         if (fold_member<UPD_MAXE_T>(x_me, acc, sh)) ++members;
-        members += fold_list<T, UPD_MAXE_T>(list, 1, all, Q, d, acc, sh4);
+        members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 8 : 2, true>(list, 1, all, Q, d, acc, sums);
     } else {
         if (fold_member<UPD_MAXE_T>(x_me, acc, sh)) ++members;
         // the others lie behind: UPD_SCAN entries of the index array at a time, all of them on their way together, the
@@ -508,12 +531,27 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
         int found = 1;
         for (long base = me + 1; found < noted_raw && base < n; base += UPD_SCAN) {
             unsigned mine = 0;  // bit i: entry base + 256 i + t is a member
-#pragma unroll 8
+            int entry[UPD_SCAN / 256];
+            unsigned char is_hit[UPD_SCAN / 256];
+            // (nothing conditional, or each load would wait for the one before it: 16 x 2 of them in a row took 5 us)
+#pragma unroll
             for (int i = 0; i < UPD_SCAN / 256; ++i) {
-                const long j = base + 256 * i + t;
-                const int at = idx[j < n ? j : me];
-                if (at == k && j < n && (!hit || hit[j])) mine |= 1u << i;
+                const unsigned j = (unsigned)(base + 256 * i) + (unsigned)t;  // (32 bits: a chunk of an update at most)
+                entry[i] = *(const int *)((const char *)idx + 4u * (j < (unsigned)n ? j : (unsigned)me));
             }
+            if (hit) {
+#pragma unroll
+                for (int i = 0; i < UPD_SCAN / 256; ++i) {
+                    const unsigned j = (unsigned)(base + 256 * i) + (unsigned)t;
+                    is_hit[i] = hit[j < (unsigned)n ? j : (unsigned)me];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < UPD_SCAN / 256; ++i) is_hit[i] = 1;
+            }
+#pragma unroll
+            for (int i = 0; i < UPD_SCAN / 256; ++i)
+                mine |= (entry[i] == k && (unsigned)(base + 256 * i) + (unsigned)t < (unsigned)n && is_hit[i] != 0 ? 1u : 0u) << i;
             __syncthreads();  // (the list of the last round has been read)
 #pragma unroll
             for (int i = 0; i < UPD_SCAN / 256; ++i) {
@@ -533,11 +571,11 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
 #pragma unroll
             for (int i = 0; i < UPD_SCAN / 256; ++i) {
                 const u64 mask = __ballot(mine >> i & 1);
-                const int to = __shfl(at, 4 * i + wave) + __popcll(mask & ((1ull << lane) - 1));
+                const int to = __builtin_amdgcn_readlane(at, 4 * i + __builtin_amdgcn_readfirstlane(wave)) + __popcll(mask & ((1ull << lane) - 1));
                 if (mine >> i & 1) list[to] = (int)(base + 256 * i + t);
             }
             __syncthreads();
-            members += fold_list<T, UPD_MAXE_T>(list, 0, all, Q, d, acc, sh4);
+            members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 8 : 2, true>(list, 0, all, Q, d, acc, sums);
             found += all;
         }
     }
@@ -582,7 +620,7 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     __shared__ u64 sh_k[4];
     __shared__ u64 masks[4];
     __shared__ u64 sh_board[SISO_FOLD_BOARD];
-    __shared__ float4 sh4[4];
+    __shared__ float sums[FOLD_SUMS];
     __shared__ int list[SISO_FOLD_BOARD];
     __shared__ int sh_all;
     const long me = blockIdx.x;
@@ -691,7 +729,7 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     __syncthreads();
     if (list[0] != (int)me) return;  // an earlier member leads this centroid (uniform over the block)
     int members = fold_member<UPD_MAXE_T>(x_me, acc, sh) ? 1 : 0;
-    members += fold_list<T, UPD_MAXE_T>(list, 1, all, Q, d, acc, sh4);
+    members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 4 : 2, false>(list, 1, all, Q, d, acc, sums);
     if (members == 0) return;
     float stored[UPD_MAXE_T];
     const bool rewritten = update_write<T, UPD_MAXE_T>(k, d, size_old, members, m_old, acc, cent, mean, size, invn, sh, stored);
