@@ -510,9 +510,8 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // each walks through its share of the upper triangle: the slabs of consecutive tile pairs follow
 // each other without a gap, only the accumulators start from zero again.
 // The 32 workgroups of an XCD take the tile pairs of one unit (8 column tiles x 4 row tiles) at a
-// time, as in the lookup, so that a tile fetched into that L2 serves several of them; the XCDs own
-// the groups of four row tiles in turns, in alternating direction and from the longest rows to the
-// shortest, which gives each an equal share of the triangle.
+// time, as in the lookup, so that a tile fetched into that L2 serves several of them, and every XCD has an
+// eighth of the triangle (PairItems).
 // ----------------------------------------------------------------------------
 #define PAIR_STAGE 2048  // pairs a workgroup collects in LDS
 template <class Cfg>
@@ -1021,11 +1020,9 @@ __global__ __launch_bounds__(WideCfg::NT) __attribute__((amdgpu_waves_per_eu(1, 
     ld_items.init(tiles, qb);
     cp_items.init(tiles, qb);
     int ld_qt = 0, ld_ct = 0, cp_qt = 0, cp_ct = 0;
-    int npairs = 0;
-    while (cp_items.next(cp_qt, cp_ct)) ++npairs;
+    const int npairs = cp_items.count();
     if (npairs == 0) return;
     const int T = npairs * nk;  // slabs this workgroup walks through
-    cp_items.init(tiles, qb);
     cp_items.next(cp_qt, cp_ct);
     ld_items.next(ld_qt, ld_ct);
 

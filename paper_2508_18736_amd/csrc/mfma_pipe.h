@@ -270,40 +270,61 @@ __device__ __forceinline__ unsigned other_half(unsigned v) {
     return (threadIdx.x & 32) ? r[0] : r[1];
 }
 
-// The tile pairs of a pair search (see k_pairs_stream): the sequence that one workgroup walks through.  In a round an XCD has
-// one group of sb row tiles; the workgroup has one row tile s of them and every qb-th column tile up to it.
+// The tile pairs of a pair search (see k_pairs_stream): the sequence that one workgroup walks through.  All pairs of tiles stand
+// in one order: groups of sb row tiles, in a group column after column, in a column row after row, and behind the columns
+// that all rows of the group have the few on the diagonal.  32 pairs in a row are a block of sb rows and 32 / sb columns.  An XCD
+// has an eighth of them, and its 32 workgroups take one of 32 each: every share is as large as the next, but for one pair.
+// (Whole groups were dealt out to the XCDs before: the busiest workgroup of 196 row tiles had 79 pairs, 75.4 on average; of
+// 137 row tiles 42 and 36.9; of 20, one group for each of five XCDs, 3 and 0.8.  With the searches' ends, us: 5,000 x 768 93 -> 49, 24,576
+// 326 -> 289, 35,001 542 -> 497, 50,001 946 -> 915.)
 struct PairItems {
-    int xcd, iq, is, qb, sb, groups, tiles, rounds, round, b, b_end, s;
-    __device__ __forceinline__ void init(int tiles_, int qb_) {
-        xcd = blockIdx.x & 7;
-        const int i = (blockIdx.x >> 3) & 31;
+    long p, end;  // this workgroup's next place in the order; where its XCD's share ends
+    int sb, tiles, group, at;  // the group of place p, and p's number in it
+    __device__ __forceinline__ void init(int tiles_, int qb) {
+        const long xcd = blockIdx.x & 7, total = (long)tiles_ * (tiles_ + 1) / 2;
         tiles = tiles_;
-        qb = qb_;
         sb = 32 / qb;
-        iq = i % qb;
-        is = i / qb;
-        groups = (tiles + sb - 1) / sb;
-        rounds = (groups + 7) / 8;
-        round = -1;
-        b = b_end = s = 0;
+        p = total * xcd / 8 + ((blockIdx.x >> 3) & 31);
+        end = total * (xcd + 1) / 8;
+        find();
+    }
+    __device__ __forceinline__ void find() {  // (row r begins at r (r + 1) / 2, and so does a group that begins with it)
+        int r = (int)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
+        while ((long)r * (r + 1) / 2 > p) --r;
+        while ((long)(r + 1) * (r + 2) / 2 <= p) ++r;
+        group = __builtin_amdgcn_readfirstlane(r / sb);
+        const long r0 = (long)group * sb;
+        at = __builtin_amdgcn_readfirstlane((int)(p - r0 * (r0 + 1) / 2));
+    }
+    __device__ __forceinline__ int count() const { return p < end ? (int)((end - p + 31) / 32) : 0; }
+    __device__ __forceinline__ void skip(int n) {
+        p += 32L * n;
+        find();
     }
     // next tile pair (column tile qt <= row tile ct) of this workgroup; false = none left
     __device__ __forceinline__ bool next(int &qt, int &ct) {
-        while (b >= b_end) {
-            if (++round >= rounds) {
-                round = rounds;
-                return false;
-            }
-            // (the groups from the bottom of the triangle upwards: the round that not every XCD takes part in is
-            // then the one with the least work - 196 row tiles: 28 % more than its share on one XCD otherwise)
-            const int gi = round * 8 + ((round & 1) ? 7 - xcd : xcd);
-            s = (groups - 1 - gi) * sb + is;
-            b = 0;
-            b_end = gi >= groups || s >= tiles || s < iq ? 0 : (s - iq) / qb + 1;
+        if (p >= end) return false;
+        int r0, rows, all;
+        for (;;) {
+            r0 = group * sb;
+            rows = tiles - r0 < sb ? tiles - r0 : sb;
+            all = rows * (r0 + 1);
+            const int here = all + rows * (rows - 1) / 2;
+            if (at < here) break;
+            at -= here;
+            ++group;
         }
-        qt = b * qb + iq;
-        ct = s;
-        ++b;
+        if (at < all) {
+            qt = at / rows;
+            ct = r0 + at - qt * rows;
+        } else {
+            int e = at - all, r = 1;
+            for (; e >= r; ++r) e -= r;
+            qt = r0 + 1 + e;
+            ct = r0 + r;
+        }
+        p += 32;
+        at += 32;
         return true;
     }
 };
