@@ -276,7 +276,7 @@ long siso_bad_indices(siso_cache *c);
  * Returns the total number of such pairs, which may exceed cap; only the first
  * cap pairs found are written.  Negative = error code.  Synchronises.
  * Large searches (128 to 1,024 dimensions, thresholds from 0.25 on; rows * rows * dim from
- * 1.5e9 and 2,000 rows in fp32; from 2.6e10 in bf16, with the same addition) are screened like lookups: products of bytes tell most pairs
+ * 1.5e9 and 1,500 rows in fp32; from 2.6e10 in bf16, with the same addition) are screened like lookups: products of bytes tell most pairs
  * from the others, and the cosines of those near the threshold are formed anew.  Their
  * workspace (a byte per element of the rows, and up to 128 MiB for pairs near the threshold) is
  * kept up to 512 MiB and given back above; without it, or with more such pairs than it

@@ -1603,10 +1603,11 @@ int siso_topk_fp8_collect(siso_cache *c, long n, int slices, const float *tau, i
 // ----------------------------------------------------------------------------
 int siso_pairs_mfma_supported(const siso_cache *c, long count) {
     if (c->opt_merge_config == 1) return 0;  // 1 = force the kernel of lookup_tile.hip
-    // Up to 4,096 rows there are at most 136 pairs of tiles for 256 compute units: the smaller tiles of lookup_tile.hip serve
-    // more of them (a search with its read-back, rows of 768 elements, pipelined against tiled: 1,000 rows 36.6 / 25.0 us,
-    // 2,000 38.2 / 30.1, 4,000 57.6 / 50.8, 8,000 95.0 / 95.5; of 256 elements: 26.7 / 22.5, 27.2 / 24.1, 34.9 / 35.4, 47.8 / 55.9)
-    if (c->opt_merge_config == 0 && count <= 4096) return 0;
+    // Few rows are few pairs of tiles for 256 compute units: the smaller tiles of lookup_tile.hip serve more of them (a search with its
+    // read-back, no pairs / rows in groups of four, us, tiled against pipelined: 1,500 x 768 29.0 / 40.0 against 39.8 / 45.3,
+    // 2,500 37.3 / 59.7 against 40.4 / 44.7, 3,000 40.6 / 66.4 against 40.4 / 44.9, 4,000 54.4 / 97.9 against 43.7 / 45.5; x 256 2,000
+    // 26.4 / 44.1 against 29.4 / 34.6, 3,000 29.5 / 59.3 against 29.4 / 34.0; x 1,024 3,000 45.8 / 68.5 against 46.3 / 50.2)
+    if (c->opt_merge_config == 0 && count < 2800) return 0;
     return c->dtype == SISO_BF16 && c->dim % 64 == 0 && c->dim >= 128 && count >= 2;
 }
 

@@ -1590,8 +1590,8 @@ int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_row
                                                         access, owner, members, plain, floor);
 }
 
-// Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 52, 2,000 x 768
-// 82 -> 59, 4,000 x 256 130 -> 60, 8,000 x 768 500 -> 97; bf16 8,000 x 256 62 -> 71, 6,000 x 768 94 -> 86, 16,000 x 256 101 -> 99, 16,000 x 768
+// Searches with their read-back, rows in groups of four, us, without and with: fp32 1,000 x 384 39 -> 52, 1,500 x 768 61 -> 55
+// (no pairs 55 -> 50), 2,000 x 256 53 -> 49 (39 -> 45), 2,000 x 768 81 -> 56, 4,000 x 256 130 -> 60, 8,000 x 768 500 -> 97; bf16 8,000 x 256 62 -> 71, 6,000 x 768 94 -> 86, 16,000 x 256 101 -> 99, 16,000 x 768
 // 229 -> 151, 50,000 x 768 1,666 -> 886; where it does not pay: fp32 1,250 x 1,000 62 -> 87, bf16 14,000 x 128 80 -> 108, 20,000 x 128
 // 129 -> 178, 10,000 x 256 80 -> 90.  Below a threshold of 0.25 rows of zeros and the many pairs of unrelated rows would come
 // near it.
@@ -1601,7 +1601,7 @@ int siso_screen_pairs_wanted(const siso_cache *c, long count, float threshold) {
     if (c->opt_screen == 1 || c->opt_screen == 3) return 1;
     const double squared = (double)count * (double)count;
     if (c->dim < 128) return 0;
-    return c->dtype == SISO_F32 ? count >= 2000 && squared * c->dim >= 1.5e9 : squared * saved_dim(c->dim) >= 1.3e10;
+    return c->dtype == SISO_F32 ? count >= 1500 && squared * c->dim >= 1.5e9 : squared * saved_dim(c->dim) >= 1.3e10;
 }
 
 int siso_screen_pairs_launch(siso_cache *c, const void *rows, const float *invn, long count, float threshold, int *out_pairs, long cap,
