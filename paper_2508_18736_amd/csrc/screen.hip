@@ -779,22 +779,24 @@ __global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, co
 // longest list decided (4,096 queries, 30 % misses: 65 to 78 us; so 48).
 // First step, a wave for each query: the bound, with the cosine of the listed row of the highest upper end (the bound is
 // then no longer short of the best by twice the error but by once); the listed rows that reach it go to one list of all
-// queries.  Queries that are left to the other kernels are numbered and their rows gathered.
+// queries.  Queries that are left to the other kernels are numbered and their rows gathered.  Sixteen queries take their room in the
+// list together: the additions queue for one counter, 10 ns each (6,553 queries four at a time 23.0 us, so 10.7).
 struct ScreenWork {
     int q, row;
 };
+#define PICK_WAVES 16
 template <typename T>
-__global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
+__global__ __launch_bounds__(PICK_WAVES * 64) void k_screen_pick(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
                                                      long n, int d, int vec, const unsigned *__restrict__ low,
                                                      const int *__restrict__ cnt, const uint2 *__restrict__ list,
                                                      int *__restrict__ totals, int most_lost, ScreenWork *__restrict__ work,
                                                      int work_room, u64 *__restrict__ best, float *__restrict__ qinv,
                                                      int *__restrict__ plain_of, T *__restrict__ plain_rows) {
-    __shared__ u32x4_t sh_q[4][SISO_SCREEN_DIM * sizeof(T) / 16];
-    __shared__ int sh_n[4];
+    __shared__ u32x4_t sh_q[PICK_WAVES][SISO_SCREEN_DIM * sizeof(T) / 16];
+    __shared__ int sh_n[PICK_WAVES];
     __shared__ int sh_base;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long q = (long)blockIdx.x * 4 + wave;
+    const long q = (long)blockIdx.x * PICK_WAVES + wave;
     const T *qrow = Q + (size_t)(q < n ? q : 0) * d;
     const uint2 *ql = list + (size_t)(q < n ? q : 0) * SCREEN_LIST;
     const uint2 e0 = ql[lane];  // (beyond the list: anything, not looked at)
@@ -829,7 +831,9 @@ __global__ __launch_bounds__(256) void k_screen_pick(const T *__restrict__ Q, co
     if (lane == 0) sh_n[wave] = some;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int more = sh_n[0] + sh_n[1] + sh_n[2] + sh_n[3];
+        int more = 0;
+#pragma unroll
+        for (int w = 0; w < PICK_WAVES; ++w) more += sh_n[w];
         sh_base = more > 0 ? atomicAdd(totals, more) : 0;
         if (all && blockIdx.x == 0) totals[1] = (int)n;
     }
@@ -1432,7 +1436,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
         }
     }
     siso_prof_end(c);
-    hipLaunchKernelGGL(k_screen_pick<T>, fours, block, 0, c->stream, queries, cent, c->invn, n, d, vec, r.low, r.cnt, r.list, r.totals,
+    hipLaunchKernelGGL(k_screen_pick<T>, dim3((unsigned)((n + PICK_WAVES - 1) / PICK_WAVES)), dim3(PICK_WAVES * 64), 0, c->stream, queries, cent, c->invn, n, d, vec, r.low, r.cnt, r.list, r.totals,
                        most_lost, r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
     hipLaunchKernelGGL(k_screen_score<T>, dim3((unsigned)(n < 4096 ? (n + 1) / 2 : 2048)), block, 0, c->stream, queries, cent, c->invn, d, vec,
                        r.totals, r.work, r.work_room, r.qinv, r.best);
