@@ -175,13 +175,18 @@ struct DeviceBuf {  // frees on every way out
 struct RefreshLists {
     std::vector<long> first, fill, place;
     std::vector<RefreshCandidate> cand;
-    std::vector<int> src, keep;      // keep = source of every surviving row in order (cached row, or K0 + repository row)
-    std::vector<float> loc, loc2;    // cluster_size before; of the survivors, after the decay
+    std::vector<int> src;
+    std::vector<float> loc, decayed;  // cluster sizes, and what they are behind the decay
     std::vector<unsigned> acc, with;
     std::vector<u64> key, same;
+    bool keyed = false;  // key and with are those of loc and acc
+    hipEvent_t reported = nullptr;
+    ~RefreshLists() {
+        if (reported) (void)hipEventDestroy(reported);
+    }
     size_t bytes() const {
         return (first.capacity() + fill.capacity() + place.capacity()) * sizeof(long) + cand.capacity() * sizeof(RefreshCandidate) +
-               (src.capacity() + keep.capacity() + loc.capacity() + loc2.capacity() + acc.capacity() + with.capacity()) * 4 +
+               (src.capacity() + loc.capacity() + decayed.capacity() + acc.capacity() + with.capacity()) * 4 +
                (key.capacity() + same.capacity()) * sizeof(u64);
     }
 };
@@ -193,23 +198,51 @@ void siso_refresh_release(siso_cache *c) {
 
 namespace {
 
-// The decisions of Algorithm 1 from what the kernels found.  Per repository row i: h_idx / h_sim = its closest
+// (cluster_size, access_count) as one number that orders alike; -0 and 0 are the same size
+inline u64 refresh_key(float size, unsigned references) {
+    const float f = size + 0.0f;
+    unsigned u;
+    memcpy(&u, &f, 4);
+    u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return ((u64)u << 32) | references;
+}
+
+// What can be done before the searches have ended: the lists as they stand before the first repository row, and, if rows may have
+// to go, their numbers and how many share the upper 16 bits of one.
+void plan_prepare(long K0, long r, const float *h_loc, const unsigned *h_acc, long max_centroids, RefreshLists &l) {
+    l.loc.reserve((size_t)(K0 + r));
+    l.acc.reserve((size_t)(K0 + r));
+    l.src.reserve((size_t)(K0 + r));
+    l.key.reserve((size_t)(K0 + r));
+    l.decayed.reserve((size_t)(K0 + r));
+    l.loc.assign(h_loc, h_loc + K0);
+    l.acc.assign(h_acc, h_acc + K0);
+    l.decayed.resize((size_t)K0);
+    for (long j = 0; j < K0; ++j) l.decayed[(size_t)j] = l.loc[(size_t)j] / 1.1f;
+    l.src.resize((size_t)K0);  // C_new: source of every row (cached row, or K0 + repository row)
+    for (long j = 0; j < K0; ++j) l.src[(size_t)j] = (int)j;
+    l.keyed = K0 + r > max_centroids;
+    if (!l.keyed) return;
+    l.key.resize((size_t)K0);
+    l.with.assign((size_t)1 << 16, 0);
+    for (long j = 0; j < K0; ++j) l.key[(size_t)j] = refresh_key(l.loc[(size_t)j], l.acc[(size_t)j]);
+    for (long j = 0; j < K0; ++j) l.with[(size_t)(l.key[(size_t)j] >> 48)] += 1;
+}
+
+// The decisions of Algorithm 1 from what the kernels found, behind plan_prepare.  Per repository row i: h_idx / h_sim = its closest
 // cached centroid and the cosine; h_pairs / h_cos = the pairs (a, b), a < b, of repository rows above the
-// threshold with their cosines.  h_loc / h_acc = cluster_size and access_count of the cached centroids (they grow
-// by the rows that join).  The outcome is l.keep and l.loc2.
-void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const float *h_rsize, const int *h_pairs,
-                  const float *h_cos, long n_pairs, const float *h_loc, const unsigned *h_acc, float theta_c,
-                  long max_centroids, RefreshLists &l, long &merged, long &added, long &evicted) {
-    std::vector<float> &loc = l.loc, &loc2 = l.loc2;
-    std::vector<unsigned> &acc = l.acc;
-    std::vector<int> &keep = l.keep, &src = l.src;
+// threshold with their cosines.  l.loc / l.acc = cluster_size and access_count of the cached centroids (they grow
+// by the rows that join).  The outcome: out_src = the source of every surviving row in order (cached row, or K0 + repository
+// row), out_loc = its cluster size behind the decay; their number is returned.
+long plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const float *h_rsize, const int *h_pairs,
+                  const float *h_cos, long n_pairs, float theta_c, long max_centroids, RefreshLists &l, int *out_src, float *out_loc,
+                  long &merged, long &added, long &evicted) {
+    std::vector<float> &loc = l.loc, &decayed = l.decayed;
+    std::vector<unsigned> &acc = l.acc, &with = l.with;
+    std::vector<int> &src = l.src;
+    std::vector<u64> &key = l.key;
     std::vector<long> &first = l.first, &place = l.place;
     std::vector<RefreshCandidate> &cand = l.cand;
-    loc.reserve((size_t)(K0 + r));
-    acc.reserve((size_t)(K0 + r));
-    src.reserve((size_t)(K0 + r));
-    loc.assign(h_loc, h_loc + K0);
-    acc.assign(h_acc, h_acc + K0);
     // ---- the chain of the merge step, in the order of the repository ---------------------
     // candidates of row b: the earlier rows a < b with cosine above the threshold (pairs come as a < b)
     first.assign((size_t)r + 1, 0);
@@ -225,8 +258,6 @@ void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const f
         }
     }
     place.assign((size_t)r, -1);  // position in C_new of a repository row that joined
-    src.resize((size_t)K0);       // C_new: source of every row (cached row, or K0 + repository row)
-    for (long j = 0; j < K0; ++j) src[(size_t)j] = (int)j;
     merged = added = 0;
     for (long i = 0; i < r; ++i) {
         long best = h_idx[(size_t)i];
@@ -246,64 +277,63 @@ void plan_refresh(long K0, long r, const int *h_idx, const float *h_sim, const f
         }
         if (best >= 0 && bsim > theta_c) {
             loc[(size_t)best] = loc[(size_t)best] + h_rsize[(size_t)i];
+            decayed[(size_t)best] = loc[(size_t)best] / 1.1f;
+            if (l.keyed) {
+                with[(size_t)(key[(size_t)best] >> 48)] -= 1;
+                key[(size_t)best] = refresh_key(loc[(size_t)best], acc[(size_t)best]);
+                with[(size_t)(key[(size_t)best] >> 48)] += 1;
+            }
             ++merged;
         } else {
             place[(size_t)i] = (long)src.size();
             src.push_back((int)(K0 + i));
             loc.push_back(h_rsize[(size_t)i]);
+            decayed.push_back(loc.back() / 1.1f);
             acc.push_back(SISO_ACCESS_INF);
+            if (l.keyed) {
+                key.push_back(refresh_key(loc.back(), SISO_ACCESS_INF));
+                with[(size_t)(key.back() >> 48)] += 1;
+            }
             ++added;
         }
     }
 
     // ---- filtering step: the smallest (cluster_size, access_count) go, the first such first ----
     const long n_new = (long)src.size();
-    // (cluster_size, access_count) as one number that orders alike; -0 and 0 are the same size
-    auto key_of = [&](long j) -> u64 {
-        const float f = loc[(size_t)j] + 0.0f;
-        unsigned u;
-        memcpy(&u, &f, 4);
-        u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-        return ((u64)u << 32) | acc[(size_t)j];
-    };
     evicted = n_new > max_centroids ? n_new - max_centroids : 0;
-    u64 last = 0;    // rows with a smaller number go,
-    long at_last = 0;  // and of those with this one so many, the first ones
-    if (evicted > 0) {
-        // the evicted-th smallest number: its upper 16 bits from a count of them, the rest among the rows that share those
-        std::vector<u64> &key = l.key, &same = l.same;
-        std::vector<unsigned> &with = l.with;
-        key.resize((size_t)n_new);
-        with.assign((size_t)1 << 16, 0);
-        for (long j = 0; j < n_new; ++j) {
-            key[(size_t)j] = key_of(j);
-            with[(size_t)(key[(size_t)j] >> 48)] += 1;
-        }
-        long below = 0;
-        size_t top = 0;
-        while (below + with[top] < evicted) below += with[top++];
-        same.clear();
-        same.reserve((size_t)with[top]);
-        for (long j = 0; j < n_new; ++j)
-            if ((key[(size_t)j] >> 48) == top) same.push_back(key[(size_t)j]);
-        std::nth_element(same.begin(), same.begin() + (evicted - below - 1), same.end());
-        last = same[(size_t)(evicted - below - 1)];
-        at_last = evicted - below;
-        for (u64 v : same) at_last -= v < last ? 1 : 0;
-        keep.resize((size_t)(n_new - evicted));
-        loc2.resize((size_t)(n_new - evicted));
-        size_t out = 0;
-        for (long j = 0; j < n_new; ++j) {
-            const u64 v = key[(size_t)j];
-            if (v < last || (v == last && at_last-- > 0)) continue;
-            keep[out] = src[(size_t)j];
-            loc2[out++] = loc[(size_t)j] / 1.1f;
-        }
-        return;
+    long out = 0;
+    auto stay = [&](long from, long to) {  // these rows, one behind the other
+        if (from >= to) return;
+        memcpy(out_src + out, src.data() + from, (size_t)(to - from) * sizeof(int));
+        memcpy(out_loc + out, decayed.data() + from, (size_t)(to - from) * sizeof(float));
+        out += to - from;
+    };
+    if (evicted == 0) {
+        stay(0, n_new);
+        return out;
     }
-    keep.assign(src.begin(), src.end());
-    loc2.resize((size_t)n_new);
-    for (long j = 0; j < n_new; ++j) loc2[(size_t)j] = loc[(size_t)j] / 1.1f;
+    // the evicted-th smallest number: its upper 16 bits from the count of them, the rest among the rows that share those
+    std::vector<u64> &same = l.same;
+    long below = 0;
+    size_t top = 0;
+    while (below + with[top] < evicted) below += with[top++];
+    same.clear();
+    same.reserve((size_t)with[top]);
+    for (long j = 0; j < n_new; ++j)
+        if ((key[(size_t)j] >> 48) == top) same.push_back(key[(size_t)j]);
+    std::nth_element(same.begin(), same.begin() + (evicted - below - 1), same.end());
+    const u64 last = same[(size_t)(evicted - below - 1)];  // rows with a smaller number go,
+    long at_last = evicted - below;                        // and of those with this one so many, the first ones
+    for (u64 v : same) at_last -= v < last ? 1 : 0;
+    long from = 0;
+    for (long j = 0; j < n_new; ++j) {
+        const u64 v = key[(size_t)j];
+        if (v > last || (v == last && at_last-- <= 0)) continue;
+        stay(from, j);
+        from = j + 1;
+    }
+    stay(from, n_new);
+    return out;
 }
 
 }  // namespace
@@ -376,6 +406,24 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
                                d, to_pairs, to_cos);
         return siso_check_hip(c, hipGetLastError(), "k_pair_cosines");
     };
+    if (c->refresh_lists == nullptr) c->refresh_lists = new RefreshLists;
+    RefreshLists &lists = *c->refresh_lists;
+    if (lists.reported == nullptr) REFRESH_TRY(hipEventCreateWithFlags(&lists.reported, hipEventDisableTiming), "siso_refresh: event");
+    auto report = [&](long rows, long kept) {
+        const long widest = rows > kept ? rows : kept;
+        hipLaunchKernelGGL(k_report, dim3((unsigned)(widest < 262144 ? (widest + 255) / 256 : 1024)), dim3(256), 0, st, d_idx, d_sim,
+                           repo_size, rows, c->locality, c->access, kept, h_idx, h_sim, h_rsize, h_loc, h_acc);
+        return siso_check_hip(c, hipGetLastError(), "k_report");
+    };
+    // What the plan needs of a large cache's rows goes to the host first, which works on it while the searches run, and what is left
+    // behind them is a look at the numbers and copies (a refresh of 65,536 x 768 by 6,553 rows 925 -> 838 us; of 20,000 by 2,000 no
+    // different: a launch and an event more).
+    const bool ahead = K0 >= 16384;
+    if (ahead) {
+        const int rc = report(0, K0);
+        if (rc != SISO_OK) return rc;
+        REFRESH_TRY(hipEventRecord(lists.reported, st), "siso_refresh: event");
+    }
     if (r > 0) {
         REFRESH_TRY(hipMemsetAsync(d_rows + (size_t)r * d * eb, 0, (size_t)SISO_PAD_ROWS * d * eb, st), "clear pad rows");
         hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, st, bad_at, found_at);
@@ -394,11 +442,15 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
         if (rc == SISO_OK && r >= 2) rc = cosines(d_pairs, 0, early, h_pairs, h_cos);
         if (rc != SISO_OK) return rc;
     }
-    if (r > 0 || K0 > 0) {
-        const long widest = r > K0 ? r : K0;
-        hipLaunchKernelGGL(k_report, dim3((unsigned)(widest < 262144 ? (widest + 255) / 256 : 1024)), dim3(256), 0, st, d_idx, d_sim,
-                           repo_size, r, c->locality, c->access, K0, h_idx, h_sim, h_rsize, h_loc, h_acc);
-        REFRESH_TRY(hipGetLastError(), "k_report");
+    if (r > 0 || (K0 > 0 && !ahead)) {
+        const int rc = report(r, ahead ? 0 : K0);
+        if (rc != SISO_OK) return rc;
+    }
+    if (ahead) {
+        REFRESH_TRY(hipEventSynchronize(lists.reported), "siso_refresh: synchronize");
+        plan_prepare(K0, r, h_loc, h_acc, max_centroids, lists);
+    }
+    if (r > 0 || (K0 > 0 && !ahead)) {
         u64 bad = 0;
         int rc = siso_read_counter(c, 2, &bad);  // (all counters come at once)
         if (rc != SISO_OK) return rc;
@@ -442,22 +494,17 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
 
     // ---- merge step and filtering step: bookkeeping on the host ----------------------------------
     long merged = 0, added = 0, evicted = 0;
-    if (c->refresh_lists == nullptr) c->refresh_lists = new RefreshLists;
-    plan_refresh(K0, r, h_idx, h_sim, h_rsize, h_pairs, h_cos, n_pairs, h_loc, h_acc, theta_c, max_centroids, *c->refresh_lists,
-                 merged, added, evicted);
-    const std::vector<int> &keep = c->refresh_lists->keep;
-    const std::vector<float> &loc2 = c->refresh_lists->loc2;
-    const long live = (long)keep.size();
+    if (!ahead) plan_prepare(K0, r, h_loc, h_acc, max_centroids, lists);
+    h_loc2 = (float *)(h_src + K0 + r);
+    const long live = plan_refresh(K0, r, h_idx, h_sim, h_rsize, h_pairs, h_cos, n_pairs, theta_c, max_centroids, lists, h_src, h_loc2, merged,
+                                   added, evicted);
 
     // ---- update step: gather the new set, then it becomes the cache ---------------------------
     if (live > 0) {
         const int rc2 = siso_second_set(c);
         if (rc2 != SISO_OK) return rc2;
-        memcpy(h_src, keep.data(), (size_t)live * sizeof(int));
-        h_loc2 = (float *)(h_src + live);
-        memcpy(h_loc2, loc2.data(), (size_t)live * sizeof(float));
-        REFRESH_TRY(hipMemcpyAsync(d_src, h_src, (size_t)live * 2 * sizeof(int), hipMemcpyHostToDevice, st), "sources to device");
-        d_loc2 = (float *)(d_src + live);
+        REFRESH_TRY(hipMemcpyAsync(d_src, h_src, (size_t)(K0 + r + live) * sizeof(int), hipMemcpyHostToDevice, st), "sources to device");
+        d_loc2 = (float *)(d_src + K0 + r);
         if (c->dtype == SISO_F32)
             hipLaunchKernelGGL(k_refresh_gather<float>, dim3((unsigned)live), dim3(256), 0, st, d_src, K0, (const float *)c->cent,
                                c->mean, c->size, c->invn, (const float *)d_rows, d_rinv, repo_size, d_loc2, (float *)c->cent_b,
@@ -489,6 +536,7 @@ extern "C" int siso_refresh(siso_cache *c, const void *repo, const float *repo_s
     try {
         rc = refresh_impl(c, repo, repo_size, r, theta_c, max_centroids, out_stats);
     } catch (const std::bad_alloc &) {  // the host lists; they are all built before the update step
+        (void)hipStreamSynchronize(c->stream);  // (the searches may be running)
         rc = siso_fail(c, SISO_ENOMEM, "siso_refresh: host memory for the bookkeeping");
     }
     if (c->refresh_lists && c->refresh_lists->bytes() > (size_t)SISO_PINNED_KEEP) siso_refresh_release(c);
@@ -511,21 +559,16 @@ extern "C" long siso_refresh_plan(long k0, const float *cluster_size, const unsi
         if (best_idx[i] >= k0 || !(repo_size[i] > 0.f)) return SISO_EINVAL;
     try {
         RefreshLists lists;
-        const std::vector<int> &keep = lists.keep;
-        const std::vector<float> &loc2 = lists.loc2;
         long merged = 0, added = 0, evicted = 0;
-        plan_refresh(k0, r, best_idx, best_sim, repo_size, pairs, pair_cosine, n_pairs, cluster_size, access_count, theta_c,
-                     max_centroids, lists, merged, added, evicted);
-        for (size_t j = 0; j < keep.size(); ++j) {
-            out_source[j] = keep[j];
-            out_cluster_size[j] = loc2[j];
-        }
+        plan_prepare(k0, r, cluster_size, access_count, max_centroids, lists);
+        const long live = plan_refresh(k0, r, best_idx, best_sim, repo_size, pairs, pair_cosine, n_pairs, theta_c, max_centroids, lists, out_source,
+                                       out_cluster_size, merged, added, evicted);
         if (out_stats) {
             out_stats[0] = merged;
             out_stats[1] = added;
             out_stats[2] = evicted;
         }
-        return (long)keep.size();
+        return live;
     } catch (const std::bad_alloc &) {
         return SISO_ENOMEM;
     }
