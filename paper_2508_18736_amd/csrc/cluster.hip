@@ -156,6 +156,11 @@ __global__ void k_graph_init(int *parent, int *size_of, int *cursor, u64 *mask, 
     mask[i] = 0;
 }
 // (the number of pairs is read from the device: the host need not have seen it yet; more than `cap` were not written)
+__global__ void k_graph_first(const int *__restrict__ pairs, const u64 *__restrict__ found, long cap, int *parent) {
+    const long n_pairs = *found < (u64)cap ? (long)*found : cap;
+    for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < n_pairs; p += (long)gridDim.x * blockDim.x)
+        uf_first(parent, pairs[2 * p], pairs[2 * p + 1]);
+}
 __global__ void k_graph_join(const int *__restrict__ pairs, const u64 *__restrict__ found, long cap, int *parent) {
     const long n_pairs = *found < (u64)cap ? (long)*found : cap;
     for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < n_pairs; p += (long)gridDim.x * blockDim.x)
@@ -553,6 +558,7 @@ static long cluster_impl(siso_cache *c, const void *vectors, long n, float theta
         // a vector cannot be taken, or if a component is too large for a wave)
         const dim3 per_vector(vblocks), per_pair((unsigned)(cap < 262144 ? (cap + 255) / 256 : 1024)), block(256);
         hipLaunchKernelGGL(k_graph_init, per_vector, block, 0, st, parent, size_of, cursor, mask, n);
+        hipLaunchKernelGGL(k_graph_first, per_pair, block, 0, st, pairs, found, cap, parent);
         hipLaunchKernelGGL(k_graph_join, per_pair, block, 0, st, pairs, found, cap, parent);
         hipLaunchKernelGGL(k_graph_roots, per_vector, block, 0, st, parent, root, size_of, n);
         hipLaunchKernelGGL(k_graph_starts, per_vector, block, 0, st, root, size_of, n, start, room, bad_at);

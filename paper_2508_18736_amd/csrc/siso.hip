@@ -765,6 +765,13 @@ __global__ void k_group_fill(const int *__restrict__ root, const unsigned char *
     list[first[r] + atomicAdd(&cursor[r], 1)] = (int)i;
 }
 
+__global__ void k_uf_first(const int *__restrict__ pairs, long n_pairs, long K, int *parent) {
+    const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n_pairs) return;
+    const int a = pairs[2 * p], b = pairs[2 * p + 1];
+    if (a >= 0 && b >= 0 && a < K && b < K) uf_first(parent, a, b);
+}
+
 // Pairs that name a row twice or one that is not there are passed over and counted: the host looks at the count before
 // anything of the cache is touched.
 __global__ void k_uf_hook(const int *__restrict__ pairs, long n_pairs, long K, int *parent, unsigned char *touched, u64 *bad) {
@@ -1805,6 +1812,7 @@ extern "C" int siso_merge_apply(siso_cache *c, const int *pairs, long n_pairs, i
     if (rc == SISO_OK) {
         hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, c->stream, c->counters + 2);
         hipLaunchKernelGGL(k_uf_init, dim3(kb), dim3(256), 0, c->stream, parent, touched, members_of, cursor, K);
+        if (n_pairs > 0) hipLaunchKernelGGL(k_uf_first, dim3(pb), dim3(256), 0, c->stream, pairs, n_pairs, K, parent);
         if (n_pairs > 0)
             hipLaunchKernelGGL(k_uf_hook, dim3(pb), dim3(256), 0, c->stream, pairs, n_pairs, K, parent, touched, c->counters + 2);
         hipLaunchKernelGGL(k_uf_roots, dim3(kb), dim3(256), 0, c->stream, parent, touched, root, members_of, K);

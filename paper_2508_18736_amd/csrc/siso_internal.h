@@ -529,7 +529,12 @@ __device__ __forceinline__ int uf_find(const int *parent, int x) {
     }
     return x;
 }
+// A first pass over all pairs, in a launch of its own, leaves every row below the lowest row it is paired with (parents of
+// freshly made trees only): that is all there is to do in a group whose rows are all paired with each other, and no pair of it
+// goes through uf_join, whose every step waits for memory behind the caches.
+__device__ __forceinline__ void uf_first(int *parent, int a, int b) { atomicMin(parent + (a > b ? a : b), a > b ? b : a); }
 __device__ __forceinline__ void uf_join(int *parent, int a, int b) {
+    if (a == b || *(volatile int *)(parent + a) == *(volatile int *)(parent + b)) return;  // (old values will do: what is joined stays joined)
     for (;;) {
         a = uf_find(parent, a);
         b = uf_find(parent, b);
