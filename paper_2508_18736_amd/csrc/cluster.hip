@@ -32,23 +32,37 @@ __global__ void k_nan_fill(float *p, int count) {
 }
 
 // Copy the vectors into a buffer with readable rows behind them, with 1 / |row|; count the rows that
-// hold a NaN or an infinity or have no length.
+// hold a NaN or an infinity or have no length.  A wave for each row: its lanes sum as the threads of a block of 256 would, one sum
+// for each of the block's waves, and copy whole 16-byte chunks (`vec`), which they find in the caches.  (A block for each row,
+// element by element: 50,001 x 768 bf16 53.0 us, so 45.6.)
 template <typename T>
-__global__ __launch_bounds__(256) void k_stage_vectors(const T *__restrict__ src, T *dst, float *invn, int d, u64 *bad) {
-    __shared__ float sh[4];
-    const long k = blockIdx.x;
-    float ss = 0.f;
-    for (int e = threadIdx.x; e < d; e += 256) {
-        const T x = src[(size_t)k * d + e];
-        dst[(size_t)k * d + e] = x;
-        const float f = widen(x);
-        ss += f * f;
+__global__ __launch_bounds__(256) void k_stage_vectors(const T *__restrict__ src, T *__restrict__ dst, float *__restrict__ invn, long n,
+                                                        int d, int vec, u64 *bad) {
+    const long k = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (k >= n) return;
+    const T *row = src + (size_t)k * d;
+    T *to = dst + (size_t)k * d;
+    float ss[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int e = lane; e < d; e += 256) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float f = e + 64 * v < d ? widen(row[e + 64 * v]) : 0.f;
+            ss[v] += f * f;
+        }
     }
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const float inv = inv_length((sh[0] + sh[1]) + (sh[2] + sh[3]));
+    if (vec) {
+        constexpr int EPC = 16 / (int)sizeof(T);
+#pragma unroll 2
+        for (int e = lane * EPC; e < d; e += 64 * EPC) *(u32x4_t *)(to + e) = *(const u32x4_t *)(row + e);
+    } else {
+        for (int e = lane; e < d; e += 64) to[e] = row[e];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) ss[v] = wave_sum(ss[v]);
+    if (lane == 0) {
+        const float inv = inv_length((ss[0] + ss[1]) + (ss[2] + ss[3]));
         invn[k] = inv;
         if (!(inv == inv) || inv == 0.f) atomicAdd(bad, 1ull);
     }
@@ -173,7 +187,7 @@ __global__ void k_graph_roots(const int *__restrict__ parent, int *root, int *si
     root[i] = r;
     atomicAdd(&size_of[r], 1);
 }
-// room for the vectors of every component, in the order the waves arrive
+// room for the vectors of every component, in the order the blocks arrive
 __global__ __launch_bounds__(256) void k_graph_starts(const int *__restrict__ root, const int *__restrict__ size_of, long n,
                                                        int *start, u64 *room, u64 *bad) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -185,9 +199,16 @@ __global__ __launch_bounds__(256) void k_graph_starts(const int *__restrict__ ro
         const int o = __shfl_up(incl, off);
         if (lane >= off) incl += o;
     }
-    u64 at = 0;
-    if (lane == 63) at = atomicAdd(room, (u64)incl);
-    at = __shfl(at, 63);
+    __shared__ int wave_all[4];
+    __shared__ u64 base;
+    const int wave = threadIdx.x >> 6;
+    if (lane == 63) wave_all[wave] = incl;
+    __syncthreads();
+    if (threadIdx.x == 0) base = atomicAdd(room, (u64)(wave_all[0] + wave_all[1] + wave_all[2] + wave_all[3]));  // (10 ns each, one after the other: a
+    // wave each took 11.6 us for 50,001 vectors, so 4.7)
+    __syncthreads();
+    u64 at = base;
+    for (int w = 0; w < wave; ++w) at += (u64)wave_all[w];
     if (mine > 0) start[i] = (int)at + incl - mine;
     if (__ballot(mine > COMPONENT_MAX) != 0 && lane == 0) atomicOr(bad, COMPONENT_TOO_LARGE);
 }
@@ -540,12 +561,14 @@ static long cluster_impl(siso_cache *c, const void *vectors, long n, float theta
         hipLaunchKernelGGL(k_clear_counters, dim3(1), dim3(1), 0, st, found);
         if (attempt == 0) {
             CLUSTER_TRY(hipMemsetAsync(rows + (size_t)n * d * eb, 0, (size_t)SISO_PAD_ROWS * d * eb, st), "clear pad rows");
+            const dim3 four_rows((unsigned)((n + 3) / 4));
+            const int vec = (size_t)d * eb % 16 == 0 && (((uintptr_t)vectors | (uintptr_t)rows) & 15) == 0 ? 1 : 0;
             if (c->dtype == SISO_F32)
-                hipLaunchKernelGGL(k_stage_vectors<float>, dim3((unsigned)n), dim3(256), 0, st, (const float *)vectors,
-                                   (float *)rows, inv, d, bad_at);
+                hipLaunchKernelGGL(k_stage_vectors<float>, four_rows, dim3(256), 0, st, (const float *)vectors,
+                                   (float *)rows, inv, n, d, vec, bad_at);
             else
-                hipLaunchKernelGGL(k_stage_vectors<bf16_t>, dim3((unsigned)n), dim3(256), 0, st, (const bf16_t *)vectors,
-                                   (bf16_t *)rows, inv, d, bad_at);
+                hipLaunchKernelGGL(k_stage_vectors<bf16_t>, four_rows, dim3(256), 0, st, (const bf16_t *)vectors,
+                                   (bf16_t *)rows, inv, n, d, vec, bad_at);
             hipLaunchKernelGGL(k_nan_fill, dim3(1), dim3(SISO_PAD_ROWS), 0, st, inv + n, SISO_PAD_ROWS);
         }
         CLUSTER_TRY(hipGetLastError(), "stage vectors");
