@@ -388,7 +388,8 @@ int siso_fp8_resync(siso_cache *copy, const siso_cache *master);
  * C_new becomes the cache, survivors keep their order; a lookup enqueued before
  * the call sees the old set, one enqueued after it the new one.
  * The similarity work (repository against cache, repository against itself)
- * runs on the GPU; the chain of decisions and the choice of the survivors are
+ * runs on the GPU (repositories against bf16 caches from 3e11 operations on are screened, see
+ * siso_lookup, which takes the same workspace; so are the samples of siso_t2h); the chain of decisions and the choice of the survivors are
  * bookkeeping on the host.  Nothing changes if an error is returned before the
  * update step (bad arguments, a non-finite row, a cluster size <= 0).
  * The new set is gathered into the second set of the cache's arrays (see
