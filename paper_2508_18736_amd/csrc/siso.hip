@@ -1359,9 +1359,10 @@ extern "C" int siso_import(siso_cache *c, const void *centroids, const float *me
     return SISO_OK;
 }
 
-static int choose_path(const siso_cache *c, long n) {
+// left: for what a screened lookup leaves over (k_lookup_few does not know how many queries that are)
+static int choose_path(const siso_cache *c, long n, bool left = false) {
     if (c->path != SISO_PATH_AUTO) return c->path;
-    if (siso_few_slices(c, n) > 0) return SISO_PATH_FEW;
+    if (!left && siso_few_slices(c, n) > 0) return SISO_PATH_FEW;
     if (siso_tile_preferred(c, n)) return SISO_PATH_SCALAR;
     if (n <= 64 && siso_skinny_slices(c, n) > 0) return SISO_PATH_SKINNY;
     if (siso_mfma_slices(c, n) > 0) return SISO_PATH_MFMA;
@@ -1465,7 +1466,7 @@ struct PlainLookup {
 // left: for what a screened lookup leaves over
 static int plan_plain(siso_cache *c, long n, u64 *static_keys, long static_cap, bool left, PlainLookup *p) {
     int slices = 1;
-    const int path = c->count > 0 ? choose_path(c, n) : SISO_PATH_SCALAR;
+    const int path = c->count > 0 ? choose_path(c, n, left) : SISO_PATH_SCALAR;
     if (c->dtype == SISO_FP8 && c->count > 0 && path == SISO_PATH_SCALAR && !siso_tile_preferred(c, n))
         return siso_fail(c, SISO_EINVAL, "siso_lookup: the 8-bit storage has no scalar kernel");
     if (c->count > 0) {

@@ -347,6 +347,22 @@ def test_unaligned_queries(siso):
                 assert torch.equal(out[0], want[0]) and (out[1] - want[1]).abs().max() <= 2 * TOL
 
 
+@pytest.mark.parametrize("n", [1, 20, 32])
+def test_few_unaligned_queries(siso, n):
+    """Single precision takes queries at any alignment, screened or not, also as few of them as a kernel of their own serves; what
+    the bytes say nothing about is left to the kernel that knows how many such queries there are."""
+    print(f"case: screen few unaligned queries n={n}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    for d in (128, 130, 384):
+        c = torch.randn(3000, d, device=DEV, generator=g)
+        q = torch.empty(n * d + 1, device=DEV)[1:].view(n, d).copy_(rows_near(g, c, n, 0.3, torch.float32))
+        q[n // 2] *= 1e-18  # (a length that the bound says nothing about)
+        cache = make(siso, c, "f32")
+        idx, sim, hit = cache.lookup(q, 0.85)
+        check(idx, sim, q, c)
+        assert torch.equal(hit, (sim > 0.85).to(torch.uint8))
+
+
 def test_lookup_update_without_room_is_the_two_calls(siso):
     """Up to 256 queries of single precision that would be screened, but for the room (under capture nothing is allocated):
     siso_lookup_update returns the bits of siso_lookup, and of the screened lookup."""
