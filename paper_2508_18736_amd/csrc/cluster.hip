@@ -180,7 +180,7 @@ __global__ void k_graph_join(const int *__restrict__ pairs, const u64 *__restric
     for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < n_pairs; p += (long)gridDim.x * blockDim.x)
         uf_join(parent, pairs[2 * p], pairs[2 * p + 1]);
 }
-__global__ void k_graph_roots(const int *__restrict__ parent, int *root, int *size_of, long n) {
+__global__ void k_graph_roots(int *parent, int *root, int *size_of, long n) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int r = uf_find(parent, (int)i);

@@ -787,7 +787,7 @@ __global__ void k_uf_hook(const int *__restrict__ pairs, long n_pairs, long K, i
     uf_join(parent, a, b);
 }
 
-__global__ void k_uf_roots(const int *__restrict__ parent, const unsigned char *__restrict__ touched, int *root, int *members_of,
+__global__ void k_uf_roots(int *parent, const unsigned char *__restrict__ touched, int *root, int *members_of,
                            long K) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= K) return;

@@ -520,21 +520,30 @@ __device__ __forceinline__ void flush_staged_pairs(const int *stage, int *staged
 }
 
 // Lock-free union-find: parent[i] <= i, the lowest index of a group is its root.  Parents only ever decrease, so every
-// retry makes progress and the loops end.
-__device__ __forceinline__ int uf_find(const int *parent, int x) {
+// retry makes progress and the loops end.  A search leaves every other row that it passes below its grandparent, so that the
+// searches of a long chain shorten it for each other: after the first pass (uf_first) rows that are only near their
+// predecessors are one chain as long as the group (one of 20,000 rows in row order, all of siso_merge_apply: 13.4 ms without, 6.8 so,
+// 6.8 for the same chain over rows in any order; 50 chains of 1,000 1,120 and 720 us).
+__device__ __forceinline__ int uf_find(int *parent, int x) {
     int p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
     while (p != x) {
-        x = p;
+        const int g = __atomic_load_n(parent + p, __ATOMIC_RELAXED);
+        if (g == p) return p;
+        atomicMin(parent + x, g);  // (x is no root any more: only searches write there)
+        x = g;
         p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
     }
     return x;
 }
 // A first pass over all pairs, in a launch of its own, leaves every row below the lowest row it is paired with (parents of
 // freshly made trees only): that is all there is to do in a group whose rows are all paired with each other, and no pair of it
-// goes through uf_join, whose every step waits for memory behind the caches.
+// searches for its roots, whose every step waits for memory behind the caches; nor does a pair of which one row hangs below the other.
 __device__ __forceinline__ void uf_first(int *parent, int a, int b) { atomicMin(parent + (a > b ? a : b), a > b ? b : a); }
 __device__ __forceinline__ void uf_join(int *parent, int a, int b) {
-    if (a == b || *(volatile int *)(parent + a) == *(volatile int *)(parent + b)) return;  // (old values will do: what is joined stays joined)
+    if (a == b) return;
+    // (old values will do: what is joined stays joined)
+    const int pa = *(volatile int *)(parent + a), pb = *(volatile int *)(parent + b);
+    if (pa == pb || pa == b || pb == a) return;
     for (;;) {
         a = uf_find(parent, a);
         b = uf_find(parent, b);

@@ -1,6 +1,8 @@
 """The kernels behind the calls that fold and rebuild: updates with many members, group merges and clusterings at the
 edges of their scans, lists and waves, against plain torch in 64 bits (and the host's walk over the pairs)."""
 
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -157,3 +159,34 @@ def test_a_log_with_more_pairs_than_room_is_searched_again(siso):
     labels, clusters, total = cache.cluster(x, 0.95, 2)
     assert total == 1600 * 1599 // 2 and clusters == 1
     assert (labels[:1600] == 0).all() and (labels[1600:] == -1).all()
+
+
+@pytest.mark.parametrize("order", ["forward", "backward", "shuffled"])
+def test_long_chains_in_row_order(siso, order):
+    """Rows that are only near their predecessors (a log that drifts in time): the groups are chains in row order, and finding
+    them takes no longer than for the same chains over rows in any order."""
+    K, d = 60000, 16
+    print(f"case: merge_apply chains in row order, pairs {order}", flush=True)
+    r = np.random.default_rng(1)
+    pairs = np.stack([np.arange(K - 1), np.arange(1, K)], 1).astype(np.int32)
+    pairs = pairs[(pairs[:, 1] % 20000 != 0)]  # three chains
+    pairs = pairs[::-1] if order == "backward" else r.permutation(pairs) if order == "shuffled" else pairs
+    cents = rows_of(K, d, "f32", 8)
+    cache = siso.SisoCache(d, K, siso.F32)
+    cache.load(cents)
+    # a last pair that is none: the call is refused once the groups are known, so its time is theirs
+    took = []
+    for rows in (r.permutation(K).astype(np.int32), np.arange(K, dtype=np.int32)):
+        p = torch.from_numpy(np.concatenate([rows[pairs], [[0, K]]]).astype(np.int32)).to(DEV)
+        each = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            begin = time.perf_counter()
+            with pytest.raises(siso.SisoError):
+                cache.merge_apply(p)
+            each.append(time.perf_counter() - begin)
+        took.append(min(each))
+    assert took[1] < 3 * took[0], took
+    surv = cache.merge_apply(torch.from_numpy(np.ascontiguousarray(pairs)).to(DEV)).cpu().numpy()
+    assert np.array_equal(surv, np.arange(K) // 20000) and cache.count == 3
+    assert cache.export()[2].tolist() == [20000] * 3
