@@ -189,6 +189,9 @@ int siso_few_slices(const siso_cache *c, long n) {
     const int rb = few_row_bytes(c);
     // (with two blocks, rows of 4 KiB, 16 at a time, lose: 100,000 x 1,024, n 32: 107.8 / 120.8)
     if (rb % 16 != 0 || rb < 256 || (n > 16 && rb >= 4096) || few_lds(n <= 16 ? 1 : 2, few_waves(n), rb, few_far(c, n) ? 8 : 4) > 160 * 1024) return 0;
+    // (rows about 8 KiB apart, 16 of them in a load, from beyond that cache: 52,000 x 1,984 and up to 131,072 x 2,112 take 4 to 20 % longer than
+    // tiles, 60,000 x 2,112, n 16, 111 / 129; 48,000 x 2,000 106 / 101, 65,536 x 1,900 114 / 111, 57,444 x 2,176 112 / 115, 103,400 x 2,176 213 / 181)
+    if (rb > 7700 && rb < 8600 && c->count * (long)rb > (384l << 20)) return 0;
     const long each = 16 * few_waves(n), want = (c->count + each - 1) / each;
     return (int)(want < FEW_WORKGROUPS ? want : FEW_WORKGROUPS);
 }

@@ -49,3 +49,29 @@ def test_few_queries_of_rows_without_a_length():
     idx, sim, hit = (x.cpu() for x in cache.lookup(q, 0.5))
     assert idx[:2].tolist() == [10, 20] and hit.tolist() == [1, 1, 0, 0]
     assert sim[2] == 0 and torch.isnan(sim[3])
+
+
+def test_rows_about_8_kib_apart_are_left_to_the_tiles():
+    """60,000 rows of 2,112 elements: not slower than the tiled kernel (where a load of 16 such rows would be)."""
+    K, d, n = 60000, 2112, 16
+    print(f"case: few {K} x {d}", flush=True)
+    rows = torch.randn(K, d, device=DEV)
+    q = rows[:n] + 0.1
+    out = (torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV), torch.empty(n, dtype=torch.uint8, device=DEV))
+    caches, took = [], [[], []]
+    for path in (siso.PATH_AUTO, siso.PATH_SCALAR):
+        caches.append(siso.SisoCache(d, K, siso.F32))
+        caches[-1].set_lookup_path(path)
+        caches[-1].load(rows)
+    for i in range(12):
+        for cache, t in zip(caches, took):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(8):
+                cache.lookup(q, 0.5, *out)
+            end.record()
+            torch.cuda.synchronize()
+            if i >= 2:
+                t.append(begin.elapsed_time(end))
+            assert out[0].tolist() == list(range(n))
+    assert sorted(took[0])[5] < 1.08 * sorted(took[1])[5], took
