@@ -345,6 +345,9 @@ __device__ __forceinline__ int fold_list(const int *list, int from, int to, cons
     if (from >= to) return 0;
     to = __builtin_amdgcn_readfirstlane(to);  // (the same for the whole block)
     T raw[M][UPD_MAXE_T];
+    unsigned col[UPD_MAXE_T];  // (in bytes, 32 bits: the rows' addresses stay in scalar registers, and the kernels need no scratch)
+#pragma unroll
+    for (int e = 0; e < UPD_MAXE_T; ++e) col[e] = (unsigned)(t + e * 256 < d ? t + e * 256 : 0) * (unsigned)sizeof(T);
     // (without a condition, also behind the last member: the registers of a load that may not happen are copied at the
     // end of the round, which waits for it)
     auto ask = [&](int p) __attribute__((always_inline)) {
@@ -355,7 +358,7 @@ __device__ __forceinline__ int fold_list(const int *list, int from, int to, cons
         for (int m = 0; m < M; ++m) {
             const T *at = Q + (size_t)__builtin_amdgcn_readfirstlane(row[m]) * d;
 #pragma unroll
-            for (int e = 0; e < UPD_MAXE_T; ++e) raw[m][e] = at[(unsigned)(t + e * 256 < d ? t + e * 256 : 0)];
+            for (int e = 0; e < UPD_MAXE_T; ++e) raw[m][e] = *(const T *)((const char *)at + col[e]);
         }
     };
     if (AHEAD) ask(from);

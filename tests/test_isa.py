@@ -39,3 +39,13 @@ def test_the_mfma_kernels_keep_everything_in_registers():
     assert len(pipe) >= 10 and any("k_lookup_wide" in k for k in sizes)
     spilled = {k: v for k, v in sizes.items() if v}
     assert not spilled, spilled
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_the_kernels_of_updates_and_merges_keep_everything_in_registers():
+    """An update folds members with the next ones on their way, under the registers of four blocks per compute unit: what does
+    not fit there would go through memory."""
+    sizes = isa_check.private_segment_sizes(isa_check.device_asm("siso.hip"))
+    assert sum("k_update" in k for k in sizes) >= 4
+    spilled = {k: v for k, v in sizes.items() if v}
+    assert not spilled, spilled
