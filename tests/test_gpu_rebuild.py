@@ -64,6 +64,27 @@ def test_an_update_with_many_members(siso, dtype, d, n, targets):
     assert ((got_c[touched].double() - ref).abs() <= eps * ref.abs() + 1e-4 * eps + 1e-6).all()
 
 
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 768, 250), ("f32", 1024, 251), ("bf16", 100, 5000), ("f32", 33, 4100), ("bf16", 1030, 300)])
+def test_an_update_with_one_to_ten_members_each(siso, dtype, d, n):
+    """Centroid k has 1 + k % 10 members: as many as are folded at a time, one more, one less, with the first and without."""
+    print(f"case: update {dtype} d={d} n={n}, few members each", flush=True)
+    idx = torch.repeat_interleave(torch.arange(n), torch.arange(n) % 10 + 1)[:n].int().to(DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    idx = idx[torch.randperm(n, device=DEV, generator=g)].contiguous()
+    cents, q = rows_of(n, d, dtype, 5), rows_of(n, d, dtype, 6)
+    cache = siso.SisoCache(d, n, siso_dtype(dtype))
+    cache.load(cents)
+    cache.update(q, idx)
+    at = idx.long()
+    weight = 1 + torch.bincount(at, minlength=n).double()[:, None]
+    want = unit(cents.double()).index_add_(0, at, unit(q.double())) / weight
+    _, mean, size = cache.export()
+    assert torch.equal(size.long(), weight[:, 0].long())
+    # at most 11 additions and a division of numbers below 11, each rounded to 2^-24, and an error of 2 * 2^-24 in every unit row
+    assert (mean.double() - want).abs().max() < 20 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("dtype,d,K,sizes", [
     ("bf16", 64, 4096, [2, 3, 4, 5, 8, 9, 17]), ("f32", 100, 4097, [64, 1024, 1025]), ("bf16", 1032, 300, [2, 7]),
     ("f32", 33, 4095, [1300, 1700, 2]), ("bf16", 768, 17, [17]), ("bf16", 300, 8193, [2] * 1500 + [33] * 20)])
