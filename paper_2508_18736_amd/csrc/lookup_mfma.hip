@@ -1603,11 +1603,14 @@ int siso_topk_fp8_collect(siso_cache *c, long n, int slices, const float *tau, i
 // ----------------------------------------------------------------------------
 int siso_pairs_mfma_supported(const siso_cache *c, long count) {
     if (c->opt_merge_config == 1) return 0;  // 1 = force the kernel of lookup_tile.hip
-    // Few rows are few pairs of tiles for 256 compute units: the smaller tiles of lookup_tile.hip serve more of them (a search with its
-    // read-back, no pairs / rows in groups of four, us, tiled against pipelined: 1,500 x 768 29.0 / 40.0 against 39.8 / 45.3,
-    // 2,500 37.3 / 59.7 against 40.4 / 44.7, 3,000 40.6 / 66.4 against 40.4 / 44.9, 4,000 54.4 / 97.9 against 43.7 / 45.5; x 256 2,000
-    // 26.4 / 44.1 against 29.4 / 34.6, 3,000 29.5 / 59.3 against 29.4 / 34.0; x 1,024 3,000 45.8 / 68.5 against 46.3 / 50.2)
-    if (c->opt_merge_config == 0 && count < 2800) return 0;
+    // Few rows are few pairs of tiles for 256 compute units: the smaller tiles of lookup_tile.hip serve more of them, most of all where the
+    // products of long rows are what takes the time (a search with its read-back, no pairs / rows in groups of eight, us, tiled against
+    // pipelined: 1,500 x 768 29.0 / 40.0 against 39.8 / 45.3, 2,500 37.3 / 59.7 against 40.4 / 44.7, 2,816 39.4 / 75.7 against 42.5 / 48.6,
+    // 2,900 41.4 / 79.0 against 42.2 / 48.4, 4,000 54.4 / 97.9 against 43.7 / 45.5; x 256 2,900 30.5 / 73.9 against 30.9 / 37.6; x 1,024
+    // 2,816 43.4 / 77.5 against 47.3 / 53.3, 2,900 46.2 / 81.3 against 47.3 / 53.2; x 2,048 2,900 63.5 / 92.9 against 67.7 / 73.5, 3,200
+    // 64.2 / 103 against 67.9 / 73.9, 3,300 73.3 / 108 against 69.9 / 75.0; x 4,096 2,900 98.4 / 121 against 109 / 115, 3,300 117 / 145
+    // against 111 / 117)
+    if (c->opt_merge_config == 0 && count < (c->dim <= 1024 ? 2900 : 3300)) return 0;
     return c->dtype == SISO_BF16 && c->dim % 64 == 0 && c->dim >= 128 && count >= 2;
 }
 

@@ -1,6 +1,8 @@
 """GPU parity of the centroid update, the pair search and the group merge against the
 CPU oracle, through the C ABI."""
 
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -242,6 +244,33 @@ def test_merge_pairs_and_groups_match_oracle(siso, oracle, dtype, dim, groups, c
     out = cache.lookup(to_dev(qs, dtype), 0.9)
     ora = oracle.lookup_rows(to_host(cache.export()[0], dtype), qs, 0.9, dtype)
     check_lookup(out, ora, 0.9, dtype, "lookup after merge")
+
+
+@pytest.mark.parametrize("K,dim", [(2800, 4096), (2899, 1024), (2900, 1024), (3299, 1088), (3300, 1088)])
+def test_default_pair_search_of_few_thousand_rows(siso, K, dim):
+    """On both sides of the lines between the tiled kernel and the pipelined one: the pairs of the tiled kernel, and no search of rows
+    without pairs that takes longer than it."""
+    print(f"case: default pair search K={K} dim={dim}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K)
+    rows = torch.randn(K, dim, device=DEV, generator=g)
+    cache = siso.SisoCache(dim, K, siso.BF16)
+    cache.load(rows.bfloat16())
+    took = {0: [], 1: []}
+    for _ in range(20):
+        for config in took:
+            cache.set_option("merge_config", config)
+            begin = time.perf_counter()
+            assert cache.merge(0.9, 10)[1] == 0
+            took[config].append(time.perf_counter() - begin)
+    assert min(took[0]) < 1.1 * min(took[1]), (min(took[0]), min(took[1]))
+    cache.load((rows[torch.arange(K, device=DEV) // 5] + 0.1 * torch.randn(K, dim, device=DEV, generator=g)).bfloat16())
+    got = []
+    for config in took:
+        cache.set_option("merge_config", config)
+        pairs, total = cache.merge(0.9, 4 * K)
+        got.append(sorted_pairs(pairs.cpu().numpy()))
+        assert total == len(got[-1]) == K // 5 * 10 + (K % 5) * (K % 5 - 1) // 2
+    assert np.array_equal(*got)
 
 
 def test_merge_apply_chains_and_errors(siso, oracle):
