@@ -275,6 +275,7 @@ def test_crowded_rows_do_not_pay_twice(siso):
                                                 ("bf16", 30000, 768, 16384, True), ("bf16", 65536, 768, 4096, False),
                                                 ("bf16", 400000, 128, 8192, False), ("bf16", 200000, 192, 8192, False),
                                                 ("bf16", 200000, 320, 8192, True), ("f32", 1250, 1000, 0, False), ("f32", 2000, 384, 0, True),
+                                                ("f32", 1500, 768, 0, True), ("f32", 1499, 1024, 0, False), ("f32", 1500, 640, 0, False),
                                                 ("bf16", 14000, 128, 0, False), ("bf16", 10000, 256, 0, False), ("bf16", 6553, 768, 0, True)])
 def test_small_caches_are_not_screened(siso, dtype, K, d, n, wanted):
     """Each query costs its candidates, whatever its products take, and short bf16 rows are filled up: up to twice the time on
@@ -625,6 +626,40 @@ def test_lookups_above_a_floor(siso, dtype, K, n, d):
             cache.set_option("screen", screen)
             cache.load(c)
             stats = cache.refresh(q, sizes, theta, K + n // 4)
+            ends.append((stats, *(x.clone() for x in cache.export() + cache.export_meta())))
+        assert ends[0][0] == ends[1][0]
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(ends[0][1:], ends[1][1:]))
+
+
+def test_tables_and_refreshes_between_the_lines_are_screened(siso):
+    """32,768 x 768 bf16 by 6,600 (3.3e11 operations): half of what a lookup is screened from, enough for one with a floor, which thresholds
+    below 0.5 are not.  The bytes of the rows alone are 25 MB."""
+    import numpy as np
+    print("case: floor, default options", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    K, d, n = 32768, 768, 6600
+    c = rows_near(g, torch.randn(K // 8, d, device=DEV, generator=g), K, 0.1, torch.bfloat16)
+    q = torch.cat([rows_near(g, c, n // 2, 0.45, torch.bfloat16), torch.randn(n - n // 2, d, device=DEV, generator=g).bfloat16()])
+    best = (unit(q) @ unit(c).T).max(1).values
+    sizes = torch.randint(1, 40, (n,), device=DEV, generator=g).float()
+    for floor, screened in ((0.9, True), (0.45, False)):
+        th = np.array([floor, 0.95], np.float32)
+        for i, t in enumerate(th):
+            while (best - float(t)).abs().min() <= 2 * TOL:
+                t = th[i] = t + np.float32(1e-4)
+        cache = make(siso, c, "bf16", screen=0)
+        assert not cache.screened(n)
+        torch.cuda.synchronize()
+        room = torch.cuda.mem_get_info()[0]
+        got = cache.t2h(q, th)
+        assert (room - torch.cuda.mem_get_info()[0] >= K * d) == screened
+        assert got.tolist() == [int((best > float(t)).sum()) for t in th]
+        ends = []
+        for screen in (0, 2):
+            cache = siso.SisoCache(d, K + n, siso.BF16)
+            cache.set_option("screen", screen)
+            cache.load(c)
+            stats = cache.refresh(q, sizes, floor, K + n // 4)
             ends.append((stats, *(x.clone() for x in cache.export() + cache.export_meta())))
         assert ends[0][0] == ends[1][0]
         assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(ends[0][1:], ends[1][1:]))
