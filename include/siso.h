@@ -388,13 +388,17 @@ int siso_fp8_resync(siso_cache *copy, const siso_cache *master);
  * C_new becomes the cache, survivors keep their order; a lookup enqueued before
  * the call sees the old set, one enqueued after it the new one.
  * The similarity work (repository against cache, repository against itself)
- * runs on the GPU (repositories against bf16 caches from 3e11 operations on are screened, see
- * siso_lookup, which takes the same workspace; so are the samples of siso_t2h); the chain of decisions and the choice of the survivors are
+ * runs on the GPU; the chain of decisions and the choice of the survivors are
  * bookkeeping on the host.  Nothing changes if an error is returned before the
  * update step (bad arguments, a non-finite row, a cluster size <= 0).
  * The new set is gathered into the second set of the cache's arrays (see
  * siso_merge_apply), which then becomes the cache: nothing is copied back.
  * Its temporaries (the repository once more) are kept as siso_merge_apply's.  Synchronises.
+ * The lookup of the repository is screened where siso_lookup would be, and with theta_c >= 0.5 on bf16
+ * caches from 3e11 operations on instead of 7.5e11 (768 rows and 2.2e7 elements as there): what does not
+ * exceed theta_c need not be told apart.  It takes, and grows, the workspace of screened lookups,
+ * which stays until siso_destroy (see siso_lookup); siso_reserve asks for it only where siso_lookup would
+ * be screened.  Without it all products are formed.
  *
  * siso_export_meta: copy out cluster_size [count] floats and access_count
  * [count] unsigned ints (device pointers, either may be NULL).  Asynchronous.
@@ -498,7 +502,8 @@ long siso_choose_communities(const int *pairs, long n_pairs, long n, int min_siz
  *   out_hits: HOST pointer, m counts: out_hits[j] = number of sample queries
  *             whose top-1 similarity exceeds thetas[j] (strictly, compared as
  *             floats like the hit test of siso_lookup); h(theta_j) = out_hits[j] / n.
- * One lookup serves all thresholds (the similarity does not depend on them).
+ * One lookup serves all thresholds (the similarity does not depend on them); it is screened as that of
+ * siso_refresh, with the lowest threshold in the place of theta_c, and takes the same workspace.
  * Its temporaries are kept as siso_merge_apply's.  Synchronises.
  */
 int siso_t2h(siso_cache *c, const void *queries, long n, const float *thetas, int m, long *out_hits);

@@ -32,7 +32,7 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *                     64-deep fp8 MFMA (their default), 1, 2, 3 = the same on the 16-deep one
  *   "tiles_per_slice" 0 = default; >0 = centroid tiles one workgroup walks through
  *   "merge_config"    0 = default (see "screen"; otherwise bf16 rows whose dimension is a multiple of 64, at least 128: the eight-wave MFMA pair
- *                     search from 4,097 rows on; else the general tiled one); 1 = the general tiled pair search; bf16 rows
+ *                     search from 2,900 rows on, of more than 1,024 elements from 3,300; else the general tiled one); 1 = the general tiled pair search; bf16 rows
  *                     of such a dimension: 2 = the four-wave MFMA pair search (128x128 per wave), 3 = the
  *                     eight-wave one at any number of rows
  *   "mfma_qblock"     0 = default; 1, 2, 4, 8, 16, 32 = query tiles that share an XCD's centroid tiles
