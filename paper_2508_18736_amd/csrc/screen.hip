@@ -779,13 +779,12 @@ __global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, co
 // longest list decided (4,096 queries, 30 % misses: 65 to 78 us; so 48).
 // First step, a wave for each query: the bound, with the cosine of the listed row of the highest upper end (the bound is
 // then no longer short of the best by twice the error but by once); the listed rows that reach it go to one list of all
-// queries.  Queries that are left to the other kernels are numbered and their rows gathered.  Sixteen queries take their room in the
-// list together: the additions queue for one counter, 10 ns each (6,553 queries four at a time 23.0 us, so 10.7).
+// queries.  Queries that are left to the other kernels are numbered and their rows gathered.  PICK_WAVES queries take their room in the
+// list together: the additions queue for one counter, 10 ns each (see screen_launch).
 struct ScreenWork {
     int q, row;
 };
-#define PICK_WAVES 16
-template <typename T>
+template <typename T, int PICK_WAVES>
 __global__ __launch_bounds__(PICK_WAVES * 64) void k_screen_pick(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
                                                      long n, int d, int vec, const unsigned *__restrict__ low,
                                                      const int *__restrict__ cnt, const uint2 *__restrict__ list,
@@ -1436,8 +1435,16 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
         }
     }
     siso_prof_end(c);
-    hipLaunchKernelGGL(k_screen_pick<T>, dim3((unsigned)((n + PICK_WAVES - 1) / PICK_WAVES)), dim3(PICK_WAVES * 64), 0, c->stream, queries, cent, c->invn, n, d, vec, r.low, r.cnt, r.list, r.totals,
-                       most_lost, r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
+    // Sixteen queries to a workgroup, of few queries four: those are as many workgroups as the chip has work for (lookups of queries that mostly hit, us,
+    // four / sixteen: 60,000 x 384 fp32 n 200 65.1 / 66.6, 300 70.6 / 72.6, 700 80.6 / 82.3, 1,000 90.8 / 91.9; a third of them
+    // misses: 300 74.2 / 74.8, 1,000 96.5 / 95.6, 8,192 310.9 / 305.7; the step alone for 6,553 rows of a refresh, 65,536 x 768 bf16, 23.0 / 10.7)
+    auto pick = [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        hipLaunchKernelGGL((k_screen_pick<T, W>), dim3((unsigned)((n + W - 1) / W)), dim3(W * 64), 0, c->stream, queries, cent, c->invn, n, d, vec,
+                           r.low, r.cnt, r.list, r.totals, most_lost, r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
+    };
+    if (n < 1000) pick(IC<4>{});
+    else pick(IC<16>{});
     hipLaunchKernelGGL(k_screen_score<T>, dim3((unsigned)(n < 4096 ? (n + 1) / 2 : 2048)), block, 0, c->stream, queries, cent, c->invn, d, vec,
                        r.totals, r.work, r.work_room, r.qinv, r.best);
     hipLaunchKernelGGL(k_screen_write, dim3((unsigned)((n + 255) / 256)), block, 0, c->stream, n, q_base, r.cnt, r.best, tl, out_idx, out_sim,
@@ -1523,7 +1530,8 @@ int siso_screen_wanted(const siso_cache *c, long n) {
 // A floor leaves queries that miss without candidates, so smaller lookups are ahead (bf16; a lookup with the rest of its call, us,
 // without -> with): a refresh of 40,000 x 768 by 5,000 rows 656 -> 639, of 100,000 x 1,024 by 2,500 912 -> 811, of 200,000 x 256 by 5,000
 // 1,041 -> 973, of 65,536 x 768 by 6,553 (553 us of it all products) 140 less; 3,276 samples of a table against 65,536 x 768
-// 372 -> 357; behind the line 1,638 rows against 65,536 x 768 432 -> 445, 3,276 against 65,536 x 384 220 -> 262.
+// 372 -> 357; whole tables right above the line, without -> with: 40,000 x 768 by 4,964 326 -> 263, 65,536 x 384 by 6,059 309 -> 246, 100,000 x
+// 1,024 by 1,489 305 -> 282, 200,000 x 256 by 2,978 325 -> 293; behind the line 1,638 rows against 65,536 x 768 432 -> 445, 3,276 against 65,536 x 384 220 -> 262.
 int siso_screen_above_wanted(const siso_cache *c, long n, float floor) {
     if (siso_screen_wanted(c, n)) return 1;
     if (!(floor >= SCREEN_LEAST_FLOOR) || c->dtype != SISO_BF16 || c->opt_screen == 2 || c->dim > SISO_SCREEN_DIM || c->dim < 128) return 0;
