@@ -416,8 +416,10 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
         return siso_check_hip(c, hipGetLastError(), "k_report");
     };
     // What the plan needs of a large cache's rows goes to the host first, which works on it while the searches run, and what is left
-    // behind them is a look at the numbers and copies (a refresh of 65,536 x 768 by 6,553 rows 925 -> 838 us; of 20,000 by 2,000 no
-    // different: a launch and an event more).
+    // behind them is a look at the numbers and copies; small ones do not make up for a launch and an event more (us, all at the end / ahead, x 256
+    // bf16 by a tenth and by 20 rows: 1,000 94 / 99, 99 / 107; 4,000 111 / 113, 109 / 113; 8,000 129 / 131, 122 / 128; 12,000 147 / 148,
+    // 137 / 140; 16,384 177 / 164, 151 / 155; 20,000 210 / 190, 168 / 167; 30,000 280 / 245, 206 / 200; fp32 x 768: 8,000 201 / 197, 16,384
+    // 283 / 271, 65,536 951 / 893).
     const bool ahead = K0 >= 16384;
     if (ahead) {
         const int rc = report(0, K0);
