@@ -334,8 +334,11 @@ __device__ __forceinline__ bool fold_member(const float (&x)[UPD_MAXE_T], float 
 // list, with the arithmetic of fold_member.  A block alone works through its members one round after the other: four at a time, their rows
 // asked for when their turn had come, took 0.37 us a member, eight with the next eight on their way 0.28 (a centroid with 200 of 300
 // members, 768 elements: the update 91.6 -> 65.6 us; k_finalize_update has few members and is quicker with four, none ahead; 8,192 queries on 1,000 x 128 rows, lookup and update, 118.8 -> 93.5).
+// OFFSETS: 32-bit offsets in bytes leave the rows' addresses in scalar registers, without which k_update<bf16, 4> needs scratch (4,096 queries
+// of 65,536 x 768, all apart, 18.5 -> 16.6 us); for long rows, and four at a time, they are not worth their own registers (4,096 Zipf queries
+// of 20,000 x 2,048 fp32 154 -> 163).
 // sums: FOLD_SUMS of them.
-template <typename T, int UPD_MAXE_T, int M, bool AHEAD>
+template <typename T, int UPD_MAXE_T, int M, bool AHEAD, bool OFFSETS>
 __device__ __forceinline__ int fold_list(const int *list, int from, int to, const T *__restrict__ Q, int d,
                                          float (&acc)[UPD_MAXE_T], float *sums) {
     static_assert(2 * 4 * M <= FOLD_SUMS, "two buffers of a sum for every wave and member");
@@ -345,7 +348,7 @@ __device__ __forceinline__ int fold_list(const int *list, int from, int to, cons
     if (from >= to) return 0;
     to = __builtin_amdgcn_readfirstlane(to);  // (the same for the whole block)
     T raw[M][UPD_MAXE_T];
-    unsigned col[UPD_MAXE_T];  // (in bytes, 32 bits: the rows' addresses stay in scalar registers, and the kernels need no scratch)
+    unsigned col[UPD_MAXE_T];
 #pragma unroll
     for (int e = 0; e < UPD_MAXE_T; ++e) col[e] = (unsigned)(t + e * 256 < d ? t + e * 256 : 0) * (unsigned)sizeof(T);
     // (without a condition, also behind the last member: the registers of a load that may not happen are copied at the
@@ -358,7 +361,10 @@ __device__ __forceinline__ int fold_list(const int *list, int from, int to, cons
         for (int m = 0; m < M; ++m) {
             const T *at = Q + (size_t)__builtin_amdgcn_readfirstlane(row[m]) * d;
 #pragma unroll
-            for (int e = 0; e < UPD_MAXE_T; ++e) raw[m][e] = *(const T *)((const char *)at + col[e]);
+            for (int e = 0; e < UPD_MAXE_T; ++e) {
+                if constexpr (OFFSETS) raw[m][e] = *(const T *)((const char *)at + col[e]);
+                else raw[m][e] = at[(unsigned)(t + e * 256 < d ? t + e * 256 : 0)];
+            }
         }
     };
     if (AHEAD) ask(from);
@@ -407,8 +413,8 @@ __device__ __forceinline__ int fold_list(const int *list, int from, int to, cons
 template <typename T, int UPD_MAXE_T>
 __device__ __forceinline__ int fold_some(const int *list, int from, int to, const T *__restrict__ Q, int d, float (&acc)[UPD_MAXE_T],
                                          float *sums) {
-    if (UPD_MAXE_T <= 4 && to - from <= 4) return fold_list<T, UPD_MAXE_T, 4, false>(list, from, to, Q, d, acc, sums);
-    return fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 8 : 2, true>(list, from, to, Q, d, acc, sums);
+    if (UPD_MAXE_T <= 4 && to - from <= 4) return fold_list<T, UPD_MAXE_T, 4, false, true>(list, from, to, Q, d, acc, sums);
+    return fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 8 : 2, true, UPD_MAXE_T <= 4>(list, from, to, Q, d, acc, sums);
 }
 
 // The end of an update, by the block that leads centroid k: acc = the sum of its `members` unit-length members
@@ -741,7 +747,7 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     __syncthreads();
     if (list[0] != (int)me) return;  // an earlier member leads this centroid (uniform over the block)
     int members = fold_member<UPD_MAXE_T>(x_me, acc, sh) ? 1 : 0;
-    members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 4 : 2, false>(list, 1, all, Q, d, acc, sums);
+    members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 4 : 2, false, false>(list, 1, all, Q, d, acc, sums);
     if (members == 0) return;
     float stored[UPD_MAXE_T];
     const bool rewritten = update_write<T, UPD_MAXE_T>(k, d, size_old, members, m_old, acc, cent, mean, size, invn, sh, stored);
