@@ -779,12 +779,13 @@ __global__ __launch_bounds__(256) void k_screen_seed(const T *__restrict__ Q, co
 // longest list decided (4,096 queries, 30 % misses: 65 to 78 us; so 48).
 // First step, a wave for each query: the bound, with the cosine of the listed row of the highest upper end (the bound is
 // then no longer short of the best by twice the error but by once); the listed rows that reach it go to one list of all
-// queries.  Queries that are left to the other kernels are numbered and their rows gathered.  PICK_WAVES queries take their room in the
-// list together: the additions queue for one counter, 10 ns each (see screen_launch).
+// queries.  Queries that are left to the other kernels are numbered and their rows gathered.  The queries of a workgroup take their room
+// in the list together: the additions queue for one counter, 10 ns each (how many there are: screen_launch).
 struct ScreenWork {
     int q, row;
 };
-template <typename T, int PICK_WAVES>
+#define PICK_WAVES 16  // at most
+template <typename T>
 __global__ __launch_bounds__(PICK_WAVES * 64) void k_screen_pick(const T *__restrict__ Q, const T *__restrict__ cent, const float *__restrict__ invn,
                                                      long n, int d, int vec, const unsigned *__restrict__ low,
                                                      const int *__restrict__ cnt, const uint2 *__restrict__ list,
@@ -794,8 +795,8 @@ __global__ __launch_bounds__(PICK_WAVES * 64) void k_screen_pick(const T *__rest
     __shared__ u32x4_t sh_q[PICK_WAVES][SISO_SCREEN_DIM * sizeof(T) / 16];
     __shared__ int sh_n[PICK_WAVES];
     __shared__ int sh_base;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long q = (long)blockIdx.x * PICK_WAVES + wave;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const long q = (long)blockIdx.x * waves + wave;
     const T *qrow = Q + (size_t)(q < n ? q : 0) * d;
     const uint2 *ql = list + (size_t)(q < n ? q : 0) * SCREEN_LIST;
     const uint2 e0 = ql[lane];  // (beyond the list: anything, not looked at)
@@ -831,8 +832,7 @@ __global__ __launch_bounds__(PICK_WAVES * 64) void k_screen_pick(const T *__rest
     __syncthreads();
     if (threadIdx.x == 0) {
         int more = 0;
-#pragma unroll
-        for (int w = 0; w < PICK_WAVES; ++w) more += sh_n[w];
+        for (int w = 0; w < waves; ++w) more += sh_n[w];
         sh_base = more > 0 ? atomicAdd(totals, more) : 0;
         if (all && blockIdx.x == 0) totals[1] = (int)n;
     }
@@ -1438,13 +1438,10 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
     // Sixteen queries to a workgroup, of few queries four: those are as many workgroups as the chip has work for (lookups of queries that mostly hit, us,
     // four / sixteen: 60,000 x 384 fp32 n 200 65.1 / 66.6, 300 70.6 / 72.6, 700 80.6 / 82.3, 1,000 90.8 / 91.9; a third of them
     // misses: 300 74.2 / 74.8, 1,000 96.5 / 95.6, 8,192 310.9 / 305.7; the step alone for 6,553 rows of a refresh, 65,536 x 768 bf16, 23.0 / 10.7)
-    auto pick = [&](auto waves) {
-        constexpr int W = decltype(waves)::value;
-        hipLaunchKernelGGL((k_screen_pick<T, W>), dim3((unsigned)((n + W - 1) / W)), dim3(W * 64), 0, c->stream, queries, cent, c->invn, n, d, vec,
-                           r.low, r.cnt, r.list, r.totals, most_lost, r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
-    };
-    if (n < 1000) pick(IC<4>{});
-    else pick(IC<16>{});
+    const unsigned pick_waves = n < 1000 ? 4u : PICK_WAVES;
+    hipLaunchKernelGGL(k_screen_pick<T>, dim3((unsigned)((n + pick_waves - 1) / pick_waves)), dim3(pick_waves * 64), 0, c->stream,
+                       queries, cent, c->invn, n, d, vec, r.low, r.cnt, r.list, r.totals,
+                       most_lost, r.work, r.work_room, r.best, r.qinv, r.plain_of, (T *)r.plain_rows);
     hipLaunchKernelGGL(k_screen_score<T>, dim3((unsigned)(n < 4096 ? (n + 1) / 2 : 2048)), block, 0, c->stream, queries, cent, c->invn, d, vec,
                        r.totals, r.work, r.work_room, r.qinv, r.best);
     hipLaunchKernelGGL(k_screen_write, dim3((unsigned)((n + 255) / 256)), block, 0, c->stream, n, q_base, r.cnt, r.best, tl, out_idx, out_sim,
