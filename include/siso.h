@@ -132,9 +132,10 @@ long siso_count(const siso_cache *c);
  * values as ever; of two rows whose similarities are within the rounding of each other
  * either may be named.  A batch whose queries are near too many rows (rows with a common
  * direction, queries that miss) is given up early and looked up without the bytes.
- * Screening takes a workspace of a byte per element of the cache (its dimension rounded up
- * to a multiple of 128, at least 256) and 10 to 22 KB per query, of at most 16,384: 1.4 GB for
- * 1,048,576 rows of 1,024.  It is kept until siso_destroy.  A call that cannot have it goes
+ * Screening takes a byte per element of the cache (its dimension rounded up to a multiple of
+ * 128, at least 256) and a workspace of 10 to 22 KB per query, of at most 16,384: 1.4 GB for
+ * 1,048,576 rows of 1,024.  Both are kept until siso_destroy, and a call writes the bytes of
+ * those rows anew that have changed since the last.  A call that cannot have them goes
  * without, and such a size is not asked for again until siso_reserve; the workspace of a lookup
  * that was captured in a graph stays as it is when a larger call needs more.
  */

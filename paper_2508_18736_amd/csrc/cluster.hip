@@ -84,7 +84,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_cluster_rows(const T *__restrict__ vec, const float *__restrict__ vinv,
                                                        const int *__restrict__ first, const int *__restrict__ member,
                                                        T *cent, float *mean, int *size, float *invn, float *locality,
-                                                       unsigned *access, int *rep, int d) {
+                                                       unsigned *access, unsigned *version, int *rep, int d) {
     __shared__ float sh[4];
     __shared__ float sh_mean[SISO_MAX_DIM];
     __shared__ float sh_best[4];
@@ -123,6 +123,7 @@ __global__ __launch_bounds__(256) void k_cluster_rows(const T *__restrict__ vec,
         invn[k] = inv_length(c2);
         locality[k] = count;
         access[k] = 0u;
+        raise_version_once(version, k);
     }
     if (!rep) return;
     // the member closest to the centroid: cosine(x_j, m) = <x_j, m> / (|x_j| |m|), and |m| is the same for
@@ -644,10 +645,10 @@ static long cluster_impl(siso_cache *c, const void *vectors, long n, float theta
     if (clusters > 0) {
         if (c->dtype == SISO_F32)
             hipLaunchKernelGGL(k_cluster_rows<float>, dim3((unsigned)clusters), dim3(256), 0, st, (const float *)rows, inv, first,
-                               member, (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, out_representative, d);
+                               member, (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, c->version, out_representative, d);
         else
             hipLaunchKernelGGL(k_cluster_rows<bf16_t>, dim3((unsigned)clusters), dim3(256), 0, st, (const bf16_t *)rows, inv, first,
-                               member, (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, out_representative, d);
+                               member, (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, c->version, out_representative, d);
         CLUSTER_TRY(hipGetLastError(), "k_cluster_rows");
     }
     hipLaunchKernelGGL(k_nan_fill, dim3(1), dim3(SISO_PAD_ROWS), 0, st, c->invn + clusters, SISO_PAD_ROWS);

@@ -123,12 +123,14 @@ __global__ __launch_bounds__(256) void k_refresh_gather(const int *__restrict__ 
                                                          const float *__restrict__ repo_invn,
                                                          const float *__restrict__ repo_size,
                                                          const float *__restrict__ loc, T *cent2, float *mean2,
-                                                         int *size2, float *invn2, float *loc2, unsigned *acc2, int d) {
+                                                         int *size2, float *invn2, float *loc2, unsigned *acc2,
+                                                         unsigned *version2, int d) {
     const long j = blockIdx.x;
     const long s = src[j];
     if (threadIdx.x == 0) {
         loc2[j] = loc[j];
         acc2[j] = 0u;
+        raise_version_once(version2, j);
     }
     if (s < K0) {
         for (int e = threadIdx.x; e < d; e += 256) {
@@ -510,11 +512,11 @@ static int refresh_impl(siso_cache *c, const void *repo, const float *repo_size,
         if (c->dtype == SISO_F32)
             hipLaunchKernelGGL(k_refresh_gather<float>, dim3((unsigned)live), dim3(256), 0, st, d_src, K0, (const float *)c->cent,
                                c->mean, c->size, c->invn, (const float *)d_rows, d_rinv, repo_size, d_loc2, (float *)c->cent_b,
-                               c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, d);
+                               c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, c->version_b, d);
         else
             hipLaunchKernelGGL(k_refresh_gather<bf16_t>, dim3((unsigned)live), dim3(256), 0, st, d_src, K0, (const bf16_t *)c->cent,
                                c->mean, c->size, c->invn, (const bf16_t *)d_rows, d_rinv, repo_size, d_loc2, (bf16_t *)c->cent_b,
-                               c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, d);
+                               c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, c->version_b, d);
         REFRESH_TRY(hipGetLastError(), "k_refresh_gather");
         siso_swap_sets(c);  // lookups enqueued from here on see the new set
     }

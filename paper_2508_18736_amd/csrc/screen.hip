@@ -59,16 +59,22 @@ __device__ __forceinline__ unsigned pack_bytes(float a, float b, float c, float 
 }
 
 // One workgroup per 32 rows, a wave for eight of them, which it holds in registers: NCH times four elements a lane.
+// The bytes of 32 rows lie in the order in which the matrix cores take them: for every 32 elements of the dimension a KiB, 16 bytes
+// for each lane of a wave (lane l: row l % 32, elements 16 (l / 32) to 16 (l / 32) + 15), so that whatever reads a fragment reads one
+// unbroken KiB, from memory as well as from LDS.  They are put in that order in LDS (a pad of 128 bytes behind 512, of 16 more behind 1,024: all
+// 64 banks for the 16 runs that a row's lanes write) and leave it 16 bytes a lane.
 // ROWS: rows of the cache, meta = (scale, error, error for lower ends, 1 / scale); a block with a row that cannot be judged
 // (past the end, non-finite, length near the ends of the range) has an infinite error for lower ends, and one with a
 // length near the ends of the range is never ruled out.  Otherwise queries, each with its own scale.
+#define BYTE_IMAGE_HALF (512 + 128)
+#define BYTE_IMAGE_STEP (2 * BYTE_IMAGE_HALF - 128 + 16)
 template <typename T, int NCH, bool ROWS>
-__device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict__ src, const float *__restrict__ invn, long have,
+__device__ __forceinline__ void write_bytes_block(unsigned char *image, long blk, const T *__restrict__ src, const float *__restrict__ invn, long have,
                                                   int vec, signed char *__restrict__ codes, float4 *__restrict__ meta,
                                                   ScreenQuery *__restrict__ qm, unsigned *__restrict__ low, u64 *__restrict__ seed,
                                                   int *__restrict__ cnt, int *__restrict__ near, float *__restrict__ largest,
                                                   int *__restrict__ totals, int d, int dp, float least) {
-    constexpr int R = 8;
+    constexpr int R = 8, STEP = BYTE_IMAGE_STEP, HALF = BYTE_IMAGE_HALF;
     __shared__ float sh[4][4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long r0 = blk * 32 + wave * R;
@@ -191,7 +197,7 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
         to = most > 0.f ? 127.f / most : 0.f;
     }
     float err = 0.f;
-    signed char *dst = codes + (size_t)r0 * dp + lane * 4;
+    unsigned char *const dst = image + (lane >> 3) * STEP + (lane >> 2 & 1) * HALF + wave * R * 16 + (lane & 3) * 4;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         if constexpr (!ROWS) {
@@ -210,9 +216,8 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
                 const float r = fmaf(x, by, SCREEN_ROUND - f[i]);
                 off2 = fmaf(r, r, off2);
             }
-            if (c * 256 + lane * 4 < dp) *(unsigned *)(dst + c * 256) = pack_bytes(f[0], f[1], f[2], f[3]);
+            *(unsigned *)(dst + c * 8 * STEP + j * 16) = pack_bytes(f[0], f[1], f[2], f[3]);
         }
-        dst += dp;
         const float e = scale * sqrtf(wave_sum(off2)) * 1.0005f + 1e-6f;
         err = fmaxf(err, e);
         if (!ROWS && lane == 0) {
@@ -228,6 +233,7 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
     }
     if constexpr (!ROWS) {
         if (blk == 0 && threadIdx.x < 3) totals[threadIdx.x] = 0;
+        __syncthreads();
     } else {
         if (lane == 0) {
             sh[1][wave] = err;
@@ -241,6 +247,9 @@ __device__ __forceinline__ void write_bytes_block(long blk, const T *__restrict_
             meta[blk] = make_float4(scale, err + pl, err + un, 127.f / most);
         }
     }
+    unsigned char *const out = (unsigned char *)codes + (size_t)blk * 32 * dp;
+    for (int i = threadIdx.x; i < 2 * dp; i += 256)
+        *(u32x4_t *)(out + 16 * i) = *(const u32x4_t *)(image + (i >> 6) * STEP + (i >> 5 & 1) * HALF + (i & 31) * 16);
 }
 
 // Which rows of the cache a launch of k_screen_bytes writes, in tiles of 256 (eight workgroups): all; those that are looked at
@@ -250,6 +259,9 @@ struct ScreenTiles {
     int part, ahead, some, stride;  // part 0, 1, 2
 };
 // Blocks below row_blocks: rows of the cache; the others: queries.  PARTS: tiles.part is not 0.
+// made (or NULL): what the bytes of 32 rows were made from, the count of ByteRows and the number of rows.  They are left as they are where
+// that is still so: of 60,000 x 384 fp32 rows between two batches of 1,000 queries that move their centroids 16 us (the queries' bytes among them) instead of 28, of 1,048,576 x 1,024
+// bf16 between two of 16,384 173 instead of 590.
 template <typename T, int NCH, bool PARTS>
 __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows, const float *__restrict__ invn, long K,
                                                       unsigned row_blocks, int row_vec, signed char *__restrict__ codes,
@@ -257,7 +269,9 @@ __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows
                                                       signed char *__restrict__ qcodes, ScreenQuery *__restrict__ qm,
                                                       unsigned *__restrict__ low, u64 *__restrict__ seed, int *__restrict__ cnt,
                                                       int *__restrict__ near, float *__restrict__ largest, int *__restrict__ totals,
-                                                      int d, int dp, ScreenTiles tiles, int most_lost, float least) {
+                                                      int d, int dp, ScreenTiles tiles, int most_lost, float least,
+                                                      const unsigned *__restrict__ version, u64 *__restrict__ made) {
+    __shared__ __attribute__((aligned(16))) unsigned char image[NCH * 8 * BYTE_IMAGE_STEP];
     if (blockIdx.x < row_blocks) {
         long blk = blockIdx.x;
         if constexpr (PARTS) {
@@ -271,10 +285,17 @@ __global__ __launch_bounds__(256) void k_screen_bytes(const T *__restrict__ rows
                 blk = tile * 8 + blk % 8;
             }
         }
-        write_bytes_block<T, NCH, true>(blk, rows, invn, K, row_vec, codes, meta, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+        if (made) {
+            const long have = K - blk * 32;
+            const u64 from = ((u64)version[blk] << 8) + (u64)(have < 0 ? 0 : have > 32 ? 32 : have);
+            if (made[blk] == from) return;
+            __syncthreads();  // (everyone has read it)
+            if (threadIdx.x == 0) made[blk] = from;
+        }
+        write_bytes_block<T, NCH, true>(image, blk, rows, invn, K, row_vec, codes, meta, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                         nullptr, d, dp, least);
     } else {
-        write_bytes_block<T, NCH, false>(blockIdx.x - row_blocks, queries, nullptr, n, query_vec, qcodes, nullptr, qm, low, seed, cnt,
+        write_bytes_block<T, NCH, false>(image, blockIdx.x - row_blocks, queries, nullptr, n, query_vec, qcodes, nullptr, qm, low, seed, cnt,
                                          near, largest, totals, d, dp, least);
     }
 }
@@ -293,26 +314,23 @@ template <class Src, class Fold>
 __device__ __forceinline__ void byte_stream(unsigned char *smem, int dp, int pairs, Src &src, Fold &&fold) {
     typedef ByteCfg Cfg;
     constexpr int WC = Cfg::WC, WQ = Cfg::WQ, NWC = Cfg::NWC, BC = Cfg::BC, NW = Cfg::NW, STAGE = Cfg::STAGE, NLA = Cfg::NLA,
-                  NL = Cfg::NL, RB = Cfg::RB, CPR = Cfg::CPR, RPI = Cfg::RPI, RP = Cfg::RP, KK = Cfg::KK, SUB = 32 * Cfg::RB;
+                  NL = Cfg::NL, RB = Cfg::RB, KK = Cfg::KK, SUB = 32 * Cfg::RB;
+    static_assert(KK == 4 && SUB == KK * 1024, "a slab is four fragments deep");
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wc = wave % NWC, wq = wave / NWC;
-    const int h = lane >> 5, l32 = lane & 31;
     const int nk = dp / RB, T = pairs * nk;
+    // (a slab of 32 rows is four KiB in a row; load j of a wave takes KiB j * NW + wave of a tile)
     unsigned off[NLA];
-    const int lr = lane / CPR, slot = lane % CPR;
 #pragma unroll
     for (int j = 0; j < NLA; ++j) {
-        const int row = (j * NW + wave) * RPI + lr;
-        off[j] = (unsigned)(row * dp + ((slot ^ ((row / RP) % CPR)) * 16));
+        const int kib = j * NW + wave;
+        off[j] = (unsigned)(kib / KK * 32 * dp + kib % KK * 1024 + lane * 16);
     }
-    const int sw = (l32 / RP) % CPR;
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    const unsigned row_a = lds0 + (unsigned)(((wc * WC) * 32 + l32) * RB);
-    const unsigned row_b = lds0 + (unsigned)(BC * RB + ((wq * WQ) * 32 + l32) * RB);
-    unsigned so[KK];
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) so[kk] = (unsigned)(((kk * 2 + h) ^ sw) * 16);
+    const unsigned row_a = lds0 + (unsigned)(wc * WC * SUB + lane * 16);
+    const unsigned row_b = lds0 + (unsigned)(BC * RB + wq * WQ * SUB + lane * 16);
+    constexpr unsigned so[KK] = {0, 1024, 2048, 3072};
 
     int ld_t = 0, ld_ks = 0;
     unsigned ld_off = 0;
@@ -324,7 +342,7 @@ __device__ __forceinline__ void byte_stream(unsigned char *smem, int dp, int pai
         unsigned o = off[j % NLA];
         asm volatile("" : "+v"(o));
         unsigned char *sb = smem + ld_off + wave * 1024;
-        const size_t k = (size_t)ld_ks * RB;
+        const size_t k = (size_t)ld_ks * SUB;
         if constexpr (j < NLA) gload_lds16((const char *)src.c + k + o, sb + j * NW * 1024);
         else gload_lds16((const char *)src.q + k + o, sb + BC * RB + (j - NLA) * NW * 1024);
         if constexpr (j == NL - 1) {
@@ -1201,6 +1219,13 @@ __global__ __launch_bounds__(256) void k_screen_pairs_check(const T *__restrict_
 // ---------------------------------------------------------------------------------------------------------------------
 namespace {
 
+struct ByteStore {  // see ByteRows
+    signed char *codes;
+    float4 *meta;
+    u64 *made;
+    size_t bytes;
+};
+
 struct ScreenRoom {
     signed char *codes, *qcodes;
     float4 *meta;
@@ -1241,15 +1266,26 @@ long pairs_in_doubt(const siso_cache *c, long rows) {
     return most < 65536 ? 65536 : most > 16777216 ? 16777216 : (long)most;
 }
 
-// for lookups of up to n queries (n = 0: for a pair search)
+ByteStore byte_store(char *base, const siso_cache *c, long rows) {
+    Carver a{base};
+    ByteStore s;
+    s.made = a.take<u64>((size_t)up256(rows) / 32);
+    s.meta = a.take<float4>((size_t)up256(rows) / 32 + 8);
+    s.codes = a.take<signed char>((size_t)up256(rows) * byte_dim(c->dim));
+    s.bytes = a.used;
+    return s;
+}
+
+// for lookups of up to n queries (n = 0: for a pair search, with the bytes of its rows)
 ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
     const int d = c->dim;
     const int dp = byte_dim(d);
     const long q = up256(n < SISO_SCREEN_PIECE ? n : SISO_SCREEN_PIECE);
     Carver a{base};
     ScreenRoom r;
-    r.codes = a.take<signed char>((size_t)up256(rows) * dp);
-    r.meta = a.take<float4>((size_t)up256(rows) / 32 + 8);
+    const size_t pair_rows = n == 0 ? (size_t)up256(rows) : 0;
+    r.codes = a.take<signed char>(pair_rows * dp);
+    r.meta = a.take<float4>(pair_rows / 32 + 8);
     r.qcodes = a.take<signed char>((size_t)q * dp);
     r.qm = a.take<ScreenQuery>(q);
     r.low = a.take<unsigned>(q);
@@ -1324,8 +1360,8 @@ bool make_room(siso_cache *c, ScreenSpace &room, size_t bytes, std::vector<char 
 
 // rows (those of `tiles`, if with_rows) and n queries to bytes
 template <typename T>
-int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *invn, long count, bool with_rows, const T *queries, long n,
-                const ScreenTiles &tiles, int most_lost, float least) {
+int write_bytes(siso_cache *c, const ScreenRoom &r, const ByteStore &s, const unsigned *version, const T *rows, const float *invn, long count,
+                bool with_rows, const T *queries, long n, const ScreenTiles &tiles, int most_lost, float least) {
     const int d = c->dim, dp = byte_dim(d);
     const long all = up256(count) / 256;
     const unsigned row_blocks = !with_rows ? 0u : 8u * (unsigned)(tiles.part == 0 ? all : tiles.part == 1 ? tiles.ahead + tiles.some : all - tiles.ahead);
@@ -1333,8 +1369,9 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const T *rows, const float *
     const size_t four = 4 * sizeof(T);  // rows that are whole runs of four elements, aligned to them
     const int rv = d % 4 == 0 && (uintptr_t)rows % four == 0 ? 1 : 0, qv = d % 4 == 0 && (uintptr_t)queries % four == 0 ? 1 : 0;
 #define SISO_LAUNCH_BYTES2(NCH, PARTS)                                                                                        \
-    hipLaunchKernelGGL((k_screen_bytes<T, NCH, PARTS>), grid, block, 0, c->stream, rows, invn, count, row_blocks, rv, r.codes, r.meta, \
-                       queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.totals, d, dp, tiles, most_lost, least)
+    hipLaunchKernelGGL((k_screen_bytes<T, NCH, PARTS>), grid, block, 0, c->stream, rows, invn, count, row_blocks, rv, s.codes, s.meta, \
+                       queries, n, qv, r.qcodes, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.totals, d, dp, tiles, most_lost, least, \
+                       version, s.made)
 #define SISO_LAUNCH_BYTES(NCH)                      \
     if (tiles.part == 0) SISO_LAUNCH_BYTES2(NCH, false); \
     else SISO_LAUNCH_BYTES2(NCH, true)
@@ -1356,6 +1393,8 @@ template <typename T>
 int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
                   float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain, float floor) {
     const ScreenRoom r = screen_room(c->screen.at, c, c->count, n);
+    const ByteStore s = byte_store(c->bytes.at, c, c->bytes.rows);
+    const unsigned *version = c->version;
     const int d = c->dim, dp = byte_dim(d);
     const long tiles = up256(c->count) / 256, nqt = up256(n) / 256;
     static bool attr_done = false;
@@ -1405,14 +1444,14 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
     // The bytes of the rows that are looked at first, and the others only once the batch is not given up (of more queries they are
     // the smaller part: 500 / n of the time that all products take in bf16).
     ScreenTiles which = {with_rows && whole && ahead > 0 && n <= 8192 ? 1 : 0, (int)ahead, (int)some, some > 0 ? (int)(tiles / some) : 1};
-    int rc = write_bytes<T>(c, r, cent, c->invn, c->count, with_rows, queries, n, which, most_lost, least);
+    int rc = write_bytes<T>(c, r, s, version, cent, c->invn, c->count, with_rows, queries, n, which, most_lost, least);
     if (rc != SISO_OK) return rc;
     if (some > 0) {
-        hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, r.codes,
-                           r.meta, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, 0L, c->count, dp, 1, (int)some, (int)nqt, 1, which.stride,
+        hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, s.codes,
+                           s.meta, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, 0L, c->count, dp, 1, (int)some, (int)nqt, 1, which.stride,
                            lost, most_lost);
         hipLaunchKernelGGL((k_screen_seed<T, false>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.qm,
-                           r.meta, r.seed, r.cnt, r.list, r.low, crowd);
+                           s.meta, r.seed, r.cnt, r.list, r.low, crowd);
     }
     siso_prof_begin(c);
     for (int part = ahead > 0 ? 0 : 1; part < 2; ++part) {
@@ -1421,15 +1460,15 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
         BytePlan p;
         if (!siso_byte_plan(c, rows, n, dp, SCREEN_TILES, &p)) return siso_fail(c, SISO_EINVAL, "screened lookup: no plan");
         hipLaunchKernelGGL(k_screen_lookup<false>, dim3((unsigned)p.grid), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes,
-                           r.codes + (size_t)row0 * dp, r.meta + t0 * 8, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, row0, rows,
+                           s.codes + (size_t)row0 * dp, s.meta + t0 * 8, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, row0, rows,
                            dp,
                            p.tiles_per_slice, p.slices, p.nqt, p.qb, 1, lost, most_lost);
         if (part == 0) {
             hipLaunchKernelGGL((k_screen_seed<T, true>), fours, block, 0, c->stream, queries, cent, c->invn, n, c->count, d, vec, r.qm,
-                               r.meta, r.seed, r.cnt, r.list, r.low, crowd);
+                               s.meta, r.seed, r.cnt, r.list, r.low, crowd);
             if (which.part == 1) {
                 which.part = 2;
-                rc = write_bytes<T>(c, r, cent, c->invn, c->count, true, queries, 0, which, most_lost, least);
+                rc = write_bytes<T>(c, r, s, version, cent, c->invn, c->count, true, queries, 0, which, most_lost, least);
                 if (rc != SISO_OK) return rc;
             }
         }
@@ -1462,7 +1501,8 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
         attr_done = true;
     }
     hipLaunchKernelGGL(k_screen_clear, dim3(1), dim3(1), 0, c->stream, r.maybe_count);
-    const int rc = write_bytes<T>(c, r, rows, invn, count, true, rows, 0, ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f);
+    const ByteStore s{r.codes, r.meta, nullptr, 0};  // (rows of any origin: their bytes serve this search alone)
+    const int rc = write_bytes<T>(c, r, s, nullptr, rows, invn, count, true, rows, 0, ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f);
     if (rc != SISO_OK) return rc;
     int qb = 8;
     while (qb > 1 && qb > up256(count) / 256) qb >>= 1;
@@ -1493,7 +1533,7 @@ int pairs_launch(siso_cache *c, const T *rows, const float *invn, long count, fl
 
 }  // namespace
 
-// Is a lookup worth it?  The bytes of the rows are written for every call (they may have changed), and six small kernels
+// Is a lookup worth it?  The bytes of rows that have changed are written (here: of all), and six small kernels
 // stand around the products.  Lookups alone, no misses / 30 % / 60 % misses, us, without -> with:
 //   fp32  1,000 x 8,000 x 384      75 -> 69 / 72 -> 73 / 73 -> 75          300 x 16,000 x 384     54 -> 64 / 54 -> 69 / 54 -> 72
 //         1,000 x 16,000 x 384    118 -> 72 / 118 -> 77                    2,000 x 2,000 x 768    77 -> 88 / 75 -> 101 / 75 -> 111
@@ -1542,7 +1582,35 @@ extern "C" int siso_screened(const siso_cache *c, long n) {
     return n == 0 ? siso_screen_pairs_wanted(c, c->count, 1.f) : siso_screen_wanted(c, n);
 }
 
+// Room for the bytes of `rows` rows of the cache, which are then made by the next lookup (nothing made from is recorded there).
+static bool byte_room(siso_cache *c, long rows) {
+    ByteRows &b = c->bytes;
+    if (rows <= b.rows) return true;
+    if (capturing(c) || (b.refused != 0 && rows >= b.refused)) return false;
+    const size_t bytes = byte_store(nullptr, c, rows).bytes;
+    char *larger = nullptr;
+    if ((c->opt_screen_room > 0 && bytes > (size_t)c->opt_screen_room << 10) || !take(&larger, bytes)) {
+        b.refused = rows;
+        return false;
+    }
+    // (the old ones go: nothing but their recorded launches needs them)
+    bool ok = hipMemsetAsync(larger, 0, (size_t)up256(rows) / 32 * sizeof(u64), c->stream) == hipSuccess;
+    if (ok && b.at && !b.recorded) ok = hipStreamSynchronize(c->stream) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        (void)hipFree(larger);
+        return false;
+    }
+    if (b.at && b.recorded) c->screen_kept->push_back(b.at);  // (room for it: siso_screen_lookup)
+    else if (b.at) (void)hipFree(b.at);
+    b.at = larger;
+    b.rows = rows;
+    b.recorded = 0;
+    return true;
+}
+
 static bool lookup_room(siso_cache *c, long rows, long n) {
+    if (!byte_room(c, rows)) return false;
     const char *before = c->screen.at;
     const bool room = make_room(c, c->screen, screen_room(nullptr, c, rows, n).bytes, c->screen_recorded ? c->screen_kept : nullptr);
     if (c->screen.at != before) c->screen_recorded = 0;
@@ -1551,12 +1619,12 @@ static bool lookup_room(siso_cache *c, long rows, long n) {
 
 int siso_screen_room(siso_cache *c, long n) {
     // (what siso_reserve was asked for does not allocate afterwards, with or without room)
-    if (n <= c->screen_reserved) return screen_room(nullptr, c, c->count, n).bytes <= c->screen.cap;
+    if (n <= c->screen_reserved) return c->count <= c->bytes.rows && screen_room(nullptr, c, c->count, n).bytes <= c->screen.cap;
     return lookup_room(c, c->count, n);
 }
 
 void siso_screen_reserve(siso_cache *c, long n) {
-    c->screen.refused = c->screen_pairs.refused = 0;
+    c->screen.refused = c->screen_pairs.refused = c->bytes.refused = 0;
     (void)lookup_room(c, c->capacity, n);
     if (n > c->screen_reserved) c->screen_reserved = n;
 }
@@ -1570,12 +1638,13 @@ void siso_screen_done(siso_cache *c) {
     (void)hipStreamSynchronize(c->stream);
     (void)hipFree(c->screen_pairs.at);
     c->screen_pairs = ScreenSpace{nullptr, 0, 0};
-    c->screen.refused = 0;
+    c->screen.refused = c->bytes.refused = 0;
 }
 
 void siso_screen_release(siso_cache *c) {
     if (c->screen.at) (void)hipFree(c->screen.at);
     if (c->screen_pairs.at) (void)hipFree(c->screen_pairs.at);
+    if (c->bytes.at) (void)hipFree(c->bytes.at);
     if (c->screen_kept)
         for (char *room : *c->screen_kept) (void)hipFree(room);
     delete c->screen_kept;
@@ -1584,14 +1653,14 @@ void siso_screen_release(siso_cache *c) {
 int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
                        float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain, float floor) {
     // A graph that records the launches goes on using the workspace when a larger call has outgrown it.
-    if (!c->screen_recorded && capturing(c)) {
+    if ((!c->screen_recorded || !c->bytes.recorded) && capturing(c)) {
         try {
             if (!c->screen_kept) c->screen_kept = new std::vector<char *>;
-            c->screen_kept->reserve(c->screen_kept->size() + 1);
+            c->screen_kept->reserve(c->screen_kept->size() + 2);  // (the bytes, and what stands around them)
         } catch (const std::bad_alloc &) {
             return siso_fail(c, SISO_ENOMEM, "siso_lookup: note of a recorded workspace");
         }
-        c->screen_recorded = 1;
+        c->screen_recorded = c->bytes.recorded = 1;
     }
     return c->dtype == SISO_F32 ? screen_launch<float>(c, (const float *)queries, n, with_rows, whole, tl, q_base, out_idx, out_sim, out_hit,
                                                        access, owner, members, plain, floor)

@@ -87,7 +87,7 @@ __device__ __forceinline__ float block_sum256(float v, float *sh) {
 template <typename T>
 __global__ __launch_bounds__(256) void k_load_rows(const T *__restrict__ src, const int *__restrict__ counts, T *cent,
                                                     float *mean, int *size, float *invn, float *locality,
-                                                    unsigned *access, long K, int d, int vec) {
+                                                    unsigned *access, unsigned *version, long K, int d, int vec) {
     constexpr int EPC = 16 / (int)sizeof(T);
     const long k = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -152,6 +152,7 @@ __global__ __launch_bounds__(256) void k_load_rows(const T *__restrict__ src, co
         invn[k] = inv;
         locality[k] = (float)(s < 1 ? 1 : s);
         access[k] = 0;
+        raise_version_once(version, k);
     }
 }
 
@@ -160,7 +161,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_import_rows(const T *__restrict__ src, const float *__restrict__ src_mean,
                                                       const int *__restrict__ src_size, const float *__restrict__ src_loc,
                                                       const unsigned *__restrict__ src_acc, T *cent, float *mean, int *size,
-                                                      float *invn, float *locality, unsigned *access, int d) {
+                                                      float *invn, float *locality, unsigned *access, unsigned *version, int d) {
     __shared__ float sh[4];
     const long k = blockIdx.x;
     float ss = 0.f;
@@ -177,6 +178,7 @@ __global__ __launch_bounds__(256) void k_import_rows(const T *__restrict__ src, 
         invn[k] = inv_length(n2);
         locality[k] = src_loc ? src_loc[k] : (float)s;
         access[k] = src_acc ? src_acc[k] : 0u;
+        raise_version_once(version, k);
     }
 }
 
@@ -469,8 +471,8 @@ __device__ __forceinline__ bool update_write(int k, int d, int size_old, int mem
 // of k_update_mark, or NULL: then every block finds out by itself whether it is the first member.
 template <typename T, int UPD_MAXE_T>
 __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T *__restrict__ Q, const int *__restrict__ idx,
-                                                 const unsigned char *__restrict__ hit, long n, T *cent, float *mean,
-                                                 int *size, float *invn, long count, int d, u64 *bad, int *owner,
+                                                 const unsigned char *__restrict__ hit, int n, T *cent, float *mean,
+                                                 int *size, float *invn, unsigned *version, int count, int d, u64 *bad, int *owner,
                                                  int *marked) {
     __shared__ float sh[4];
     __shared__ float sums[FOLD_SUMS];
@@ -520,6 +522,7 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
         if (t == 0) {     // leave them as they were found
             owner[k] = UPD_NO_OWNER;
             marked[k] = 0;
+            raise_version(version, k);  // (here: its address would take registers that the folding needs)
         }
     }
     float acc[UPD_MAXE_T];
@@ -540,6 +543,7 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
         if (mask >> lane & 1) list[before + __popcll(mask & ((1ull << lane) - 1))] = t;
         __syncthreads();
         if (list[0] != (int)me) return;  // an earlier member leads this centroid
+        if (t == 0) raise_version(version, k);
         if (fold_member<UPD_MAXE_T>(x_me, acc, sh)) ++members;
         members += fold_some<T, UPD_MAXE_T>(list, 1, all, Q, d, acc, sums);
     } else {
@@ -628,7 +632,7 @@ template <typename T, int UPD_MAXE_T>
 __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q, const u64 *__restrict__ keys, long n, long K,
                                                           int d, int slices, float theta, int vec, int *out_idx,
                                                           float *out_sim, unsigned char *out_hit, unsigned *access, T *cent,
-                                                          float *mean, int *size, float *invn, u64 *board,
+                                                          float *mean, int *size, float *invn, unsigned *version, u64 *board,
                                                           int spin_limit, u64 *gave_up, const float *__restrict__ q_inv,
                                                           unsigned char *copy_codes, float *copy_scale, float *copy_inv,
                                                           int *copy_size) {
@@ -746,6 +750,7 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     if (m) list[before + __popcll(mask & ((1ull << lane) - 1))] = t;
     __syncthreads();
     if (list[0] != (int)me) return;  // an earlier member leads this centroid (uniform over the block)
+    if (t == 0) raise_version(version, k);
     int members = fold_member<UPD_MAXE_T>(x_me, acc, sh) ? 1 : 0;
     members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 4 : 2, false, false>(list, 1, all, Q, d, acc, sums);
     if (members == 0) return;
@@ -825,7 +830,7 @@ __global__ __launch_bounds__(256) void k_group_mean(const int *__restrict__ root
                                                      long K, const int *__restrict__ members_of,
                                                      const int *__restrict__ first, const int *__restrict__ list,
                                                      T *cent, float *mean, int *size, float *invn,
-                                                     float *locality, unsigned *access, int d, int rows_per_block) {
+                                                     float *locality, unsigned *access, unsigned *version, int d, int rows_per_block) {
     __shared__ float sh[4];
     __shared__ u64 masks[4];
     __shared__ int raw[GROUP_LIST_MAX], sorted[GROUP_LIST_MAX];
@@ -952,7 +957,10 @@ __global__ __launch_bounds__(256) void k_group_mean(const int *__restrict__ root
                     }
                 }
                 const float c2 = block_sum256(cs, sh);
-                if (t == 0) invn[r] = inv_length(c2);
+                if (t == 0) {
+                    invn[r] = inv_length(c2);
+                    raise_version(version, r);
+                }
             }
         }
         __syncthreads();  // the lists of this group have been read
@@ -1045,7 +1053,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(const int *__restrict__ roo
                                                       const float *__restrict__ locality,
                                                       const unsigned *__restrict__ access, T *cent2, float *mean2,
                                                       int *size2, float *invn2, float *locality2, unsigned *access2,
-                                                      int d) {
+                                                      unsigned *version2, int d) {
     const long i = blockIdx.x;
     if (root[i] != (int)i) return;
     const long p = newpos[i];
@@ -1058,6 +1066,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(const int *__restrict__ roo
         invn2[p] = invn[i];
         locality2[p] = locality[i];
         access2[p] = access[i];
+        raise_version_once(version2, p);
     }
 }
 
@@ -1160,6 +1169,12 @@ void siso_arena_done(siso_cache *c) {
     }
 }
 
+static bool make_versions(siso_cache *c, unsigned **version, int first_byte) {  // (0 is nobody's: bytes that are not made yet)
+    if (c->dtype == SISO_FP8) return true;  // (never screened)
+    const size_t bytes = ((size_t)c->capacity + 255) / 256 * 8 * sizeof(unsigned);
+    return hipMalloc((void **)version, bytes) == hipSuccess && hipMemset(*version, first_byte, bytes) == hipSuccess;
+}
+
 int siso_second_set(siso_cache *c) {
     if (c->cent_b) return SISO_OK;
     const size_t cells = (size_t)c->capacity * c->dim;
@@ -1172,6 +1187,7 @@ int siso_second_set(siso_cache *c) {
     ok = ok && hipMemset(c->invn_b, 0, ((size_t)c->capacity + SISO_PAD_ROWS) * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->locality_b, (size_t)c->capacity * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->access_b, (size_t)c->capacity * sizeof(unsigned)) == hipSuccess;
+    ok = ok && make_versions(c, &c->version_b, 0x81);
     ok = ok && hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -1181,6 +1197,8 @@ int siso_second_set(siso_cache *c) {
         if (c->invn_b) (void)hipFree(c->invn_b);
         if (c->locality_b) (void)hipFree(c->locality_b);
         if (c->access_b) (void)hipFree(c->access_b);
+        if (c->version_b) (void)hipFree(c->version_b);
+        c->version_b = nullptr;
         c->cent_b = nullptr;
         c->mean_b = nullptr;
         c->size_b = nullptr;
@@ -1200,6 +1218,7 @@ void siso_swap_sets(siso_cache *c) {
     std::swap(c->invn, c->invn_b);
     std::swap(c->locality, c->locality_b);
     std::swap(c->access, c->access_b);
+    std::swap(c->version, c->version_b);
 }
 
 extern "C" int siso_create_ex(int dim, long capacity, int dtype, siso_cache **out) {
@@ -1232,6 +1251,7 @@ extern "C" int siso_create_ex(int dim, long capacity, int dtype, siso_cache **ou
     ok = ok && hipMemset(c->invn, 0, ((size_t)capacity + SISO_PAD_ROWS) * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->locality, (size_t)capacity * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->access, (size_t)capacity * sizeof(unsigned)) == hipSuccess;
+    ok = ok && make_versions(c, &c->version, 0x01);
     // (behind the four counters: the board of siso_lookup_update, one slot per query of a small batch)
     ok = ok && hipMalloc((void **)&c->counters, (4 + SISO_FOLD_BOARD) * sizeof(u64)) == hipSuccess;
     ok = ok && hipHostMalloc((void **)&c->host_pin, 4 * sizeof(u64), hipHostMallocDefault) == hipSuccess;
@@ -1267,6 +1287,8 @@ extern "C" void siso_destroy(siso_cache *c) {
     if (c->invn_b) (void)hipFree(c->invn_b);
     if (c->locality_b) (void)hipFree(c->locality_b);
     if (c->access_b) (void)hipFree(c->access_b);
+    if (c->version) (void)hipFree(c->version);
+    if (c->version_b) (void)hipFree(c->version_b);
     if (c->keys) (void)hipFree(c->keys);
     if (c->scale) (void)hipFree(c->scale);
     if (c->fp8_q) (void)hipFree(c->fp8_q);
@@ -1342,10 +1364,10 @@ extern "C" int siso_load(siso_cache *c, const void *centroids, const int *counts
         const int vec = (c->dim * elem_bytes(c->dtype)) % 16 == 0 && ((uintptr_t)centroids & 15) == 0 ? 1 : 0;
         if (c->dtype == SISO_F32)
             hipLaunchKernelGGL(k_load_rows<float>, grid, dim3(256), 0, c->stream, (const float *)centroids, counts,
-                               (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, k, c->dim, vec);
+                               (float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, c->version, k, c->dim, vec);
         else
             hipLaunchKernelGGL(k_load_rows<bf16_t>, grid, dim3(256), 0, c->stream, (const bf16_t *)centroids, counts,
-                               (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, k, c->dim, vec);
+                               (bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access, c->version, k, c->dim, vec);
         HIP_TRY(c, hipGetLastError());
     }
     hipLaunchKernelGGL(k_fill_nan, dim3(1), dim3(SISO_PAD_ROWS), 0, c->stream, c->invn + k, SISO_PAD_ROWS);
@@ -1364,11 +1386,11 @@ extern "C" int siso_import(siso_cache *c, const void *centroids, const float *me
         if (c->dtype == SISO_F32)
             hipLaunchKernelGGL(k_import_rows<float>, dim3((unsigned)k), dim3(256), 0, c->stream, (const float *)centroids,
                                means, counts, cluster_size, access_count, (float *)c->cent, c->mean, c->size, c->invn,
-                               c->locality, c->access, c->dim);
+                               c->locality, c->access, c->version, c->dim);
         else
             hipLaunchKernelGGL(k_import_rows<bf16_t>, dim3((unsigned)k), dim3(256), 0, c->stream, (const bf16_t *)centroids,
                                means, counts, cluster_size, access_count, (bf16_t *)c->cent, c->mean, c->size, c->invn,
-                               c->locality, c->access, c->dim);
+                               c->locality, c->access, c->version, c->dim);
         HIP_TRY(c, hipGetLastError());
     }
     hipLaunchKernelGGL(k_fill_nan, dim3(1), dim3(SISO_PAD_ROWS), 0, c->stream, c->invn + k, SISO_PAD_ROWS);
@@ -1563,7 +1585,7 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
 #define SISO_LAUNCH_FOLD(T, E)                                                                                            \
     hipLaunchKernelGGL((k_finalize_update<T, E>), dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, keys, n, c->count, \
                        c->dim, slices, tl.v[0], vec, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr, \
-                       (T *)tgt->cent, tgt->mean, tgt->size, tgt->invn, c->counters + 4, spin_limit, c->counters,         \
+                       (T *)tgt->cent, tgt->mean, tgt->size, tgt->invn, tgt->version, c->counters + 4, spin_limit, c->counters, \
                        ms ? (const float *)c->fp8_qinv : (const float *)nullptr, ms ? (unsigned char *)c->cent : nullptr, \
                        ms ? c->scale : nullptr, ms ? c->invn : nullptr, ms ? c->size : nullptr)
         if (tgt->dtype == SISO_F32) {
@@ -1673,7 +1695,7 @@ static int update_hits_impl(siso_cache *c, const void *queries, const int *idx, 
         }
 #define SISO_LAUNCH_UPDATE(T, E, QP)                                                                            \
     hipLaunchKernelGGL((k_update<T, E>), grid, block, 0, c->stream, QP, idx + off, h, m, (T *)c->cent, c->mean, \
-                       c->size, c->invn, c->count, c->dim, c->counters, owner, marked)
+                       c->size, c->invn, c->version, c->count, c->dim, c->counters, owner, marked)
         if (c->dtype == SISO_F32) {
             if (c->dim <= 1024) SISO_LAUNCH_UPDATE(float, 4, qf);
             else SISO_LAUNCH_UPDATE(float, 16, qf);
@@ -1855,7 +1877,7 @@ extern "C" int siso_merge_apply(siso_cache *c, const int *pairs, long n_pairs, i
         const dim3 grid((unsigned)((K + per - 1) / per)), block(256);
 #define SISO_LAUNCH_MEAN(T, E)                                                                                           \
     hipLaunchKernelGGL((k_group_mean<T, E>), grid, block, 0, c->stream, root, touched, K, members_of, first, list, (T *)c->cent, \
-                       c->mean, c->size, c->invn, c->locality, c->access, d, per)
+                       c->mean, c->size, c->invn, c->locality, c->access, c->version, d, per)
         if (c->dtype == SISO_F32) {
             if (d <= 1024) SISO_LAUNCH_MEAN(float, 4);
             else SISO_LAUNCH_MEAN(float, 16);
@@ -1875,11 +1897,11 @@ extern "C" int siso_merge_apply(siso_cache *c, const int *pairs, long n_pairs, i
         if (c->dtype == SISO_F32)
             hipLaunchKernelGGL(k_gather_rows<float>, dim3((unsigned)K), dim3(256), 0, c->stream, root, newpos,
                                (const float *)c->cent, c->mean, c->size, c->invn, c->locality, c->access,
-                               (float *)c->cent_b, c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, d);
+                               (float *)c->cent_b, c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, c->version_b, d);
         else
             hipLaunchKernelGGL(k_gather_rows<bf16_t>, dim3((unsigned)K), dim3(256), 0, c->stream, root, newpos,
                                (const bf16_t *)c->cent, c->mean, c->size, c->invn, c->locality, c->access,
-                               (bf16_t *)c->cent_b, c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, d);
+                               (bf16_t *)c->cent_b, c->mean_b, c->size_b, c->invn_b, c->locality_b, c->access_b, c->version_b, d);
         rc = siso_check_hip(c, hipGetLastError(), "k_gather_rows");
         if (rc == SISO_OK) siso_swap_sets(c);
     }

@@ -40,6 +40,18 @@ struct ScreenSpace {
     size_t refused;  // the smallest size that could not be had (0 = none): not asked for again until siso_reserve or a release
 };
 
+// The cache's rows as bytes (screen.hip), kept from one screened lookup to the next.  Every set of arrays has a count for every 32
+// rows (`version`), which each kernel that writes a stored row raises (raise_version), and the bytes carry the counts that they
+// were made from, so that a lookup writes anew only what has changed since.  All of that lives on the device, where the
+// order of the stream, a captured graph's launches among them, is the order in which rows are written and read.  The
+// counts of the two sets begin far apart: what was made from one is never taken for the other.
+struct ByteRows {
+    char *at;  // room for the bytes of `rows` rows, or NULL; see byte_store in screen.hip
+    long rows;
+    long refused;  // the smallest number of rows that found no room (0 = none): not asked for again until siso_reserve or a release
+    int recorded;  // a graph refers to them: outgrown, they stay until the cache goes (screen_kept)
+};
+
 struct siso_cache {
     int dim;
     long capacity;
@@ -55,7 +67,8 @@ struct siso_cache {
     float *invn;  // [capacity] 1 / |stored centroid| (0 for a zero row, NaN for a non-finite row)
     float *locality;   // [capacity] cluster_size of Algorithm 1: grows by merges, decays by 1.1 per refresh
     unsigned *access;  // [capacity] access_count of Algorithm 1: hits since the last refresh; SISO_ACCESS_INF = infinity
-    // A second set of the six arrays, allocated the first time a call rebuilds the cache (group merge, refresh):
+    unsigned *version; // see ByteRows: [capacity / 32, of whole tiles of 256 rows]; NULL for an 8-bit cache
+    // A second set of the seven arrays, allocated the first time a call rebuilds the cache (group merge, refresh):
     // the new set is gathered there and the two sets change places, so nothing is copied back and such calls
     // allocate nothing afterwards.
     void *cent_b;
@@ -64,6 +77,7 @@ struct siso_cache {
     float *invn_b;
     float *locality_b;
     unsigned *access_b;
+    unsigned *version_b;
 
     // large update batches: first member and number of members per centroid, [capacity] each, allocated at
     // the first such batch; between calls every entry is back at (INT_MAX, 0)
@@ -117,6 +131,7 @@ struct siso_cache {
     // screened lookups and pair searches (screen.hip): bytes of rows and queries, bounds, lists; grown on demand.  Two
     // workspaces, so that a pair search does not move what a captured lookup refers to.
     ScreenSpace screen, screen_pairs;
+    ByteRows bytes;
     long screen_reserved;  // batches that siso_reserve has sized `screen` for, or tried to: their lookups leave it as it is
     int screen_recorded;  // a graph holds a screened lookup on `screen`: outgrown, it stays until the cache goes (screen_kept)
     std::vector<char *> *screen_kept;
@@ -353,6 +368,12 @@ __device__ __forceinline__ float row_product(const T *qrow, const u32x4_t *sh_q,
     float sum[1];
     row_products<T, 1>(qrows, chunks, vec, rows, d, lane, sum);
     return wave_sum(sum[0]);
+}
+
+// By one thread for a stored row that its block writes (see ByteRows); _once: in a launch that writes all rows from the first on.
+__device__ __forceinline__ void raise_version(unsigned *version, long row) { atomicAdd(version + (row >> 5), 1u); }
+__device__ __forceinline__ void raise_version_once(unsigned *version, long row) {
+    if ((row & 31) == 0) raise_version(version, row);
 }
 
 // The thresholds of a call travel as kernel arguments (nothing to allocate or copy): out_hit[q * m + j] = 1 where

@@ -1,0 +1,128 @@
+"""The rows of a cache as bytes are kept from one screened lookup to the next: behind everything that changes rows, and behind
+graphs replayed in between, a lookup names what it names on a fresh cache that holds the same rows."""
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
+THETA = 0.85
+
+
+@pytest.fixture(scope="module")
+def siso():
+    from paper_2508_18736_amd import siso as m
+    return m
+
+
+def rows(g, n, d, dtype, base=None):
+    x = torch.randn(n, d, device=DEV, generator=g)
+    if base is not None:
+        x = 0.1 * x / d ** 0.5 + torch.nn.functional.normalize(base[torch.randint(0, base.shape[0], (n,), device=DEV, generator=g)].float(), dim=1)
+    return (x * (0.5 + torch.rand(n, 1, device=DEV, generator=g))).to(TYPES[dtype])
+
+
+def make(siso, capacity, d, dtype):
+    cache = siso.SisoCache(d, capacity, siso.F32 if dtype == "f32" else siso.BF16)
+    cache.set_option("screen", 1)
+    return cache
+
+
+def as_fresh(siso, cache, d, dtype, q, what):
+    """The lookup on this cache, bit for bit what a cache gives that has just been loaded with its rows."""
+    c = cache.export()[0]
+    other = make(siso, c.shape[0], d, dtype)
+    other.load(c)
+    got, want = cache.lookup(q, THETA), other.lookup(q, THETA)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b), what
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [128, 300, 768])
+def test_behind_every_change_of_rows(siso, dtype, d):
+    print(f"case: kept bytes {dtype} d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(d)
+    K = 3000
+    cache = make(siso, 4000, d, dtype)
+    c = rows(g, K, d, dtype, rows(g, 300, d, dtype))
+    cache.load(c)
+    q = torch.cat([rows(g, 400, d, dtype, c), rows(g, 100, d, dtype)])
+    as_fresh(siso, cache, d, dtype, q, "load")
+    as_fresh(siso, cache, d, dtype, q, "nothing")
+    for n in (1, 64, 300, 500):
+        cache.lookup_update(q[:n], THETA)
+        as_fresh(siso, cache, d, dtype, q, f"update of {n}")
+    idx = torch.randint(0, K, (200,), device=DEV, generator=g, dtype=torch.int32)
+    cache.update(rows(g, 200, d, dtype), idx)
+    as_fresh(siso, cache, d, dtype, q, "update")
+    for k in (2011, 33, 3999, 31, 2048, 2047, 1):  # rows that are left behind the last one, and come back
+        cache.load(rows(g, k, d, dtype, c))
+        as_fresh(siso, cache, d, dtype, q, f"load of {k}")
+    cache.load(c)
+    snapshot = cache.export() + cache.export_meta()
+    cache.lookup_update(q, THETA)
+    cache.lookup(q, THETA)
+    cache.import_state(*snapshot)
+    as_fresh(siso, cache, d, dtype, q, "import")
+    pairs, _ = cache.merge(0.9, 1 << 20)
+    cache.merge_apply(pairs)
+    assert cache.count < K
+    as_fresh(siso, cache, d, dtype, q, "merge")
+    for seed in range(3):  # the two sets of arrays in turn
+        cache.refresh(rows(g, 200, d, dtype), torch.ones(200, device=DEV), 0.9, 2000)
+        as_fresh(siso, cache, d, dtype, q, f"refresh {seed}")
+        cache.lookup_update(q, 0.3)
+        as_fresh(siso, cache, d, dtype, q, f"update behind refresh {seed}")
+    cache.cluster(rows(g, 2500, d, dtype, c[:300]), 0.86, 2)
+    as_fresh(siso, cache, d, dtype, q, "cluster")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_behind_replayed_graphs(siso, dtype):
+    """A recorded step and a recorded lookup, replayed with other steps and a load in between, before and behind a growth of the room."""
+    print(f"case: kept bytes graph {dtype}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    d, K, n = 256, 2000, 300
+    cache = make(siso, 6000, d, dtype)
+    c = rows(g, K, d, dtype, rows(g, 200, d, dtype))
+    cache.load(c)
+    q, p = rows(g, n, d, dtype, c), rows(g, n, d, dtype, c)
+    out = [(torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV), torch.empty(n, dtype=torch.uint8, device=DEV)) for _ in range(2)]
+    cache.reserve(n)
+    cache.lookup_update(q, THETA)
+    side = torch.cuda.Stream()
+    cache.set_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        cache.lookup_update(q, THETA, *out[0])
+        cache.lookup(p, THETA, *out[1])
+    for seed in range(4):
+        q.copy_(rows(g, n, d, dtype, c))
+        p.copy_(rows(g, n, d, dtype, c))
+        torch.cuda.synchronize()
+        other = make(siso, 6000, d, dtype)
+        snapshot = cache.export() + cache.export_meta()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        other.import_state(*snapshot)
+        want = [other.lookup_update(q, THETA), other.lookup(p, THETA)]
+        torch.cuda.synchronize()
+        for a, b in zip(out, want):
+            for x, y in zip(a, b):
+                assert torch.equal(x, y), seed
+        if seed == 1:
+            more = rows(g, 5000, d, dtype, c)
+            torch.cuda.synchronize()
+            cache.load(more)  # (bytes for more rows than the recorded launches know of)
+            cache.lookup(q, THETA)
+            torch.cuda.synchronize()
+            cache.load(more[:K])
+            torch.cuda.synchronize()
+        if seed == 2:
+            cache.update(rows(g, 100, d, dtype), torch.randint(0, K, (100,), device=DEV, generator=g, dtype=torch.int32))
+            torch.cuda.synchronize()
+            as_fresh(siso, cache, d, dtype, q, "update between replays")
