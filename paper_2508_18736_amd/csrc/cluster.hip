@@ -657,6 +657,7 @@ static long cluster_impl(siso_cache *c, const void *vectors, long n, float theta
         CLUSTER_TRY(hipMemcpyAsync(out_label, label.data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, st), "labels");
     CLUSTER_TRY(hipStreamSynchronize(st), "siso_cluster: synchronize");
     c->count = clusters;
+    siso_bytes_all_behind(c);
     if (out_stats) {
         out_stats[0] = n_pairs;
         out_stats[1] = members;

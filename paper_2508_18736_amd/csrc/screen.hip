@@ -1366,6 +1366,7 @@ int write_bytes(siso_cache *c, const ScreenRoom &r, const ByteStore &s, const un
     const long all = up256(count) / 256;
     const unsigned row_blocks = !with_rows ? 0u : 8u * (unsigned)(tiles.part == 0 ? all : tiles.part == 1 ? tiles.ahead + tiles.some : all - tiles.ahead);
     const dim3 grid(row_blocks + (unsigned)(up256(n) / 32)), block(256);
+    if (s.made && with_rows) c->bytes.written = 1;
     const size_t four = 4 * sizeof(T);  // rows that are whole runs of four elements, aligned to them
     const int rv = d % 4 == 0 && (uintptr_t)rows % four == 0 ? 1 : 0, qv = d % 4 == 0 && (uintptr_t)queries % four == 0 ? 1 : 0;
 #define SISO_LAUNCH_BYTES2(NCH, PARTS)                                                                                        \
@@ -1446,6 +1447,10 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
     ScreenTiles which = {with_rows && whole && ahead > 0 && n <= 8192 ? 1 : 0, (int)ahead, (int)some, some > 0 ? (int)(tiles / some) : 1};
     int rc = write_bytes<T>(c, r, s, version, cent, c->invn, c->count, with_rows, queries, n, which, most_lost, least);
     if (rc != SISO_OK) return rc;
+    if (with_rows && which.part == 0 && !capturing(c)) {
+        c->bytes.behind = 0;
+        c->bytes.forgone = 0;
+    }
     if (some > 0) {
         hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, s.codes,
                            s.meta, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, 0L, c->count, dp, 1, (int)some, (int)nqt, 1, which.stride,
@@ -1606,7 +1611,124 @@ static bool byte_room(siso_cache *c, long rows) {
     b.at = larger;
     b.rows = rows;
     b.recorded = 0;
+    siso_bytes_all_behind(c);
     return true;
+}
+
+ByteView siso_byte_view(const siso_cache *c) {
+    if (!c->bytes.at || c->bytes.rows < c->count) return ByteView{nullptr, nullptr, nullptr, 0};  // (rows that they have no room for are not written to them)
+    const ByteStore s = byte_store(c->bytes.at, c, c->bytes.rows);
+    return ByteView{s.codes, s.meta, s.made, byte_dim(c->dim)};
+}
+
+unsigned *siso_counted(const siso_cache *c) { return c->bytes.written || capturing(c) ? c->version : nullptr; }
+
+// A graph that records launches over the bytes or the workspace goes on using them when a larger call has outgrown them.
+static int note_recorded(siso_cache *c, bool workspace) {
+    if ((!workspace || c->screen_recorded) && c->bytes.recorded) return SISO_OK;
+    try {
+        if (!c->screen_kept) c->screen_kept = new std::vector<char *>;
+        c->screen_kept->reserve(c->screen_kept->size() + 2);  // (the bytes, and what stands around them)
+    } catch (const std::bad_alloc &) {
+        return siso_fail(c, SISO_ENOMEM, "siso_lookup: note of a recorded workspace");
+    }
+    if (workspace) c->screen_recorded = 1;
+    c->bytes.recorded = 1;
+    return SISO_OK;
+}
+
+// ---- few queries over the bytes (lookup_bytes.hip)
+static bool few_lists_room(siso_cache *c) {
+    if (c->few.best) return true;
+    if (capturing(c)) return false;
+    FewLists f;
+    auto layout = [&](Carver a) {
+        f.best = a.take<u64>(SISO_FEW);
+        f.table = a.take<u64>(SISO_FEW_WORKGROUPS * SISO_FEW);
+        f.call = a.take<unsigned>(1);
+        f.cnt = a.take<int>(SISO_FEW);
+        f.rows = a.take<uint2>((size_t)SISO_FEW * SISO_FEW_LIST);
+        f.slots = a.take<unsigned>((size_t)SISO_FEW * SISO_FEW_WORKGROUPS * SISO_FEW_SLOTS);
+        return a.used;
+    };
+    const size_t bytes = layout(Carver{nullptr});
+    char *at = nullptr;
+    int *flooded = nullptr;
+    if (!take(&at, bytes)) return false;
+    bool ok = hipHostMalloc((void **)&flooded, sizeof(int), hipHostMallocDefault) == hipSuccess;
+    ok = ok && hipMemsetAsync(at, 0, bytes, c->stream) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        if (flooded) (void)hipHostFree(flooded);
+        (void)hipFree(at);
+        return false;
+    }
+    *flooded = 0;
+    layout(Carver{at});
+    c->few = f;
+    c->few_flooded = flooded;
+    return true;
+}
+
+// Steps of n queries (lookup and fold), a third of which miss, the rows as they are stored / the bytes, us:
+//   768:   30,000 n 1 22 / 19, n 64 25 / 77;  60,000 n 1 23 / 25, n 32 25 / 34, n 64 26 / 80;  80,000 n 1 35 / 26;  100,000 n 1 35 / 27, n 8 38 / 32,
+//          n 32 38 / 35, n 64 38 / 65;  120,000 n 32 39 / 38;  150,000 n 1 51 / 32, n 32 52 / 40, n 64 52 / 44;
+//          262,144 n 1 69 / 43, n 8 70 / 47, n 32 73 / 51, n 64 74 / 57 (none misses: 72 / 50);  400,000 n 1 102 / 60, n 64 109 / 77
+//   1,024: 60,000 n 1 26 / 26, n 64 30 / 128;  100,000 n 1 44 / 32, n 64 47 / 89;  200,000 n 1 81 / 44, n 64 83 / 65;  400,000 n 1 138 / 84, n 64 140 / 115
+//   384:   100,000 n 1 23 / 19, n 64 25 / 31;  200,000 n 1 36 / 26, n 64 38 / 35;  400,000 n 1 55 / 36, n 64 61 / 46
+//   256:   100,000 n 64 22 / 25;  200,000 n 1 28 / 22, n 64 30 / 30;  400,000 n 1 44 / 29, n 64 46 / 38.     128: 2,000,000 n 64 96 / 115
+// Two kernels with longer chains of round trips stand against half of the reading; and with few rows a workgroup has
+// little to go by: with one or two blocks for each wave the bounds of 33 queries and more come too late for its lists.
+int siso_bytes_few_wanted(const siso_cache *c, long n) {
+    if (c->dtype != SISO_BF16 || n < 1 || n > SISO_FEW || c->count < 1 || c->count > SISO_FEW_MOST_ROWS) return 0;
+    if (c->dim % 64 != 0 || c->dim < 128 || c->dim > SISO_SCREEN_DIM) return 0;
+    if (c->opt_screen == 4) return 1;
+    if (c->opt_screen != 0 || c->path != SISO_PATH_AUTO || c->opt_mfma_config != 0 || c->opt_tiles_per_slice != 0 || c->opt_mfma_qblock != 0) return 0;
+    const double elements = (double)c->count * c->dim;
+    if (c->dim < 256) return 0;
+    return n <= 8 ? elements >= 6.5e7 : n <= 32 ? elements >= 1e8 : elements >= 1e8 && c->count >= 140000;
+}
+
+int siso_bytes_few_room(siso_cache *c, long n) {
+    const bool forced = c->opt_screen == 4, recording = capturing(c);
+    // Lists that found no room, of some call since the last one that was looked at: the next 64 lookups go over the rows as they are stored,
+    // twice as many whenever that is seen again.  (Rows that lists flood on give the same results at one and a half to twice the time.)
+    if (!forced && c->few_flooded && *(volatile int *)c->few_flooded != 0) {
+        *(volatile int *)c->few_flooded = 0;
+        c->few_rests = c->few_rests == 0 ? 64 : c->few_rests < 4096 ? 2 * c->few_rests : c->few_rests;
+        c->few_rest = c->few_rests;
+    }
+    if (!forced && c->few_rest > 0) {
+        --c->few_rest;
+        return 0;
+    }
+    if (!byte_room(c, c->count) || !few_lists_room(c)) return 0;
+    ByteRows &b = c->bytes;
+    // (single rows that an update could not bring up to date stay behind until then, 64 calls at most)
+    const bool due = ++b.calls >= 64;
+    if (b.behind > 0 || recording || due) {
+        // Rows that have changed are written as bytes once lookups have read as much for want of that: a lookup over the bytes reads one byte an
+        // element less, and to write them takes three.  (A graph may be replayed behind any change, and records it always.)
+        const double elements = (double)c->count * c->dim, blocks = (double)b.behind * 32 < (double)c->count ? (double)b.behind * 32 * c->dim : elements;
+        if (!forced && !recording && b.behind > 0) {
+            b.forgone += elements;
+            if (b.forgone < 2 * blocks) return 0;
+        }
+        if (recording && note_recorded(c, false) != SISO_OK) return 0;
+        const ScreenRoom none = screen_room(nullptr, c, c->count, 0);
+        const ByteStore s = byte_store(b.at, c, b.rows);
+        const int rc = c->dtype == SISO_F32 ? write_bytes<float>(c, none, s, c->version, (const float *)c->cent, c->invn, c->count, true, (const float *)c->cent, 0,
+                                                                 ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f)
+                                            : write_bytes<bf16_t>(c, none, s, c->version, (const bf16_t *)c->cent, c->invn, c->count, true, (const bf16_t *)c->cent, 0,
+                                                                  ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f);
+        if (rc != SISO_OK) return 0;
+        if (!recording) {
+            b.behind = 0;
+            b.forgone = 0;
+            b.calls = 0;
+        }
+    }
+    return 1;
 }
 
 static bool lookup_room(siso_cache *c, long rows, long n) {
@@ -1629,6 +1751,11 @@ void siso_screen_reserve(siso_cache *c, long n) {
     if (n > c->screen_reserved) c->screen_reserved = n;
 }
 
+void siso_bytes_few_reserve(siso_cache *c) {
+    c->bytes.refused = 0;
+    if (byte_room(c, c->capacity)) (void)few_lists_room(c);
+}
+
 int siso_screen_pairs_room(siso_cache *c, long rows) {
     return make_room(c, c->screen_pairs, screen_room(nullptr, c, rows, 0).bytes, nullptr);
 }
@@ -1645,6 +1772,8 @@ void siso_screen_release(siso_cache *c) {
     if (c->screen.at) (void)hipFree(c->screen.at);
     if (c->screen_pairs.at) (void)hipFree(c->screen_pairs.at);
     if (c->bytes.at) (void)hipFree(c->bytes.at);
+    if (c->few.best) (void)hipFree(c->few.best);
+    if (c->few_flooded) (void)hipHostFree(c->few_flooded);
     if (c->screen_kept)
         for (char *room : *c->screen_kept) (void)hipFree(room);
     delete c->screen_kept;
@@ -1652,15 +1781,9 @@ void siso_screen_release(siso_cache *c) {
 
 int siso_screen_lookup(siso_cache *c, const void *queries, long n, bool with_rows, bool whole, const ThetaList &tl, long q_base, int *out_idx,
                        float *out_sim, unsigned char *out_hit, unsigned *access, int *owner, int *members, ScreenPlain *plain, float floor) {
-    // A graph that records the launches goes on using the workspace when a larger call has outgrown it.
-    if ((!c->screen_recorded || !c->bytes.recorded) && capturing(c)) {
-        try {
-            if (!c->screen_kept) c->screen_kept = new std::vector<char *>;
-            c->screen_kept->reserve(c->screen_kept->size() + 2);  // (the bytes, and what stands around them)
-        } catch (const std::bad_alloc &) {
-            return siso_fail(c, SISO_ENOMEM, "siso_lookup: note of a recorded workspace");
-        }
-        c->screen_recorded = c->bytes.recorded = 1;
+    if (capturing(c)) {
+        const int rc = note_recorded(c, true);
+        if (rc != SISO_OK) return rc;
     }
     return c->dtype == SISO_F32 ? screen_launch<float>(c, (const float *)queries, n, with_rows, whole, tl, q_base, out_idx, out_sim, out_hit,
                                                        access, owner, members, plain, floor)

@@ -427,7 +427,7 @@ __device__ __forceinline__ int fold_some(const int *list, int from, int to, cons
 template <typename T, int UPD_MAXE_T>
 __device__ __forceinline__ bool update_write(int k, int d, int size_old, int members, const float (&m_old)[UPD_MAXE_T],
                                              const float (&acc)[UPD_MAXE_T], T *cent, float *mean, int *size, float *invn,
-                                             float *sh, float (&stored)[UPD_MAXE_T]) {
+                                             float *sh, float (&stored)[UPD_MAXE_T], float &inv) {
     const int t = threadIdx.x;
     const float n_old = (float)size_old;
     const float n_new = n_old + (float)members;
@@ -461,8 +461,8 @@ __device__ __forceinline__ bool update_write(int k, int d, int size_old, int mem
             cs = __fmaf_rn(back, back, cs);
         }
     }
-    const float c2 = block_sum256(cs, sh);
-    if (t == 0) invn[k] = inv_length(c2);
+    inv = inv_length(block_sum256(cs, sh));
+    if (t == 0) invn[k] = inv;
     return true;
 }
 
@@ -602,8 +602,45 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
         }
     }
     if (members == 0) return;
-    float stored[UPD_MAXE_T];
-    update_write<T, UPD_MAXE_T>(k, d, size_old, members, m_old, acc, cent, mean, size, invn, sh, stored);
+    float stored[UPD_MAXE_T], inv;
+    update_write<T, UPD_MAXE_T>(k, d, size_old, members, m_old, acc, cent, mean, size, invn, sh, stored, inv);
+}
+
+// The bytes of a rewritten row follow in place (see ByteRows): x = this thread's elements (t + 256 e) of the stored row, inv = 1 / its length, block = the scale and
+// the errors of its 32 rows.  Where the scale does not fit the row any more, or there are no bytes, only the count of the rows goes up (k_finalize_update), and
+// whoever writes bytes next writes all 32 rows anew.  Otherwise the counts of the rows and of the bytes go up alike: bytes that were current stay
+// so, and bytes that were not do not become so.
+template <int E>
+__device__ __forceinline__ void follow_bytes(const float (&x)[E], float inv, int k, int d, const ByteView &bytes, const float4 &block, float *sh) {
+    const int t = threadIdx.x;
+    // An element beyond the scale counts as its largest, and what that leaves out as error, up to half as much again as rounding leaves of
+    // a row on average (steps of block.x, each off by 12^-1/2 of one).
+    const float by = inv * block.w;
+    float off2 = 0.f;
+    int code[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const float y = fminf(fmaxf(rintf(x[e] * by), -127.f), 127.f), off = fmaf(x[e], by, -y);
+        off2 = fmaf(off, off, off2);
+        code[e] = (int)y;
+    }
+    off2 = block_sum256f(off2, sh);
+    const bool fits = inv > 1e-15f && inv < 1e15f && block.y < INFINITY && off2 <= 2.25f / 12.f * (float)d;
+    if (fits) {
+        signed char *row = bytes.codes + (size_t)(k >> 5) * 32 * bytes.dp + (k & 31) * 16;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int col = t + e * 256;
+            if (col < d) row[(col >> 5) * 1024 + ((col >> 4) & 1) * 512 + (col & 15)] = (signed char)code[e];
+        }
+        if (t == 0) {
+            const float err = block.x * sqrtf(off2) * 1.0005f + 1e-6f;
+            unsigned *errs = (unsigned *)(bytes.meta + (k >> 5));  // (not negative: they compare as integers)
+            atomicMax(errs + 1, __float_as_uint(err));
+            atomicMax(errs + 2, __float_as_uint(err));
+            atomicAdd(bytes.made + (k >> 5), (u64)1 << 8);
+        }
+    }
 }
 
 // ============================================================================
@@ -628,14 +665,132 @@ __global__ __launch_bounds__(256, UPD_MAXE_T <= 4 ? 4 : 2) void k_update(const T
 __device__ __forceinline__ u64 board_entry(bool hit, int idx) {
     return (1ull << 63) | ((u64)(hit ? 1 : 0) << 32) | (u64)(unsigned)idx;
 }
-template <typename T, int UPD_MAXE_T>
+// LISTED: behind k_bytes_few.  What that has left of query q - the rows whose cosine may be the largest, by workgroup and in the query's list -
+// is judged once more by the largest lower end of all, and multiplied: 32 rows at a time, a wave for each, with the instruction and in the order
+// of k_lookup_pipe, so that the key is the one which that kernel's workgroups would have left.  (Rows of other blocks are not written
+// meanwhile: a block folds when all have been heard of, and they are by then done with their rows.)
+// (All columns of the instruction are the one query.  A lane supplies row `row`, one of the wave's 32 by lane % 32, and gets the products of sixteen.)
+#define LISTED_ROWS 1024  // rows that are gathered before they are multiplied
+typedef __bf16 listed_frag __attribute__((ext_vector_type(8)));
+typedef float listed_acc __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ u64 listed_key(const listed_acc &acc, float w, int row) {
+    const int h = (threadIdx.x & 63) >> 5;
+    u64 key = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+    const int from = 8 * (i >> 2) + 4 * h + (i & 3);
+    const float v = acc[i] * __shfl(w, from);
+    const u64 k = pack_key(v, (unsigned)__shfl(row, from));
+    if (v > -INFINITY && k > key) key = k;
+    }
+    const LanePair<u64> both = lane_pair<32>(key);
+    return both.a > both.b ? both.a : both.b;
+}
+// Many rows: each wave loads its own from memory, 32 bytes of each at a time.
+__device__ __forceinline__ u64 listed_product(const bf16_t *__restrict__ cent, const float *__restrict__ invn, int row, const u32x4_t *sh_q, int d) {
+    constexpr int AHEAD = 6;  // groups of four steps on their way together
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const bf16_t *at = cent + (size_t)row * d + h * 8;
+    const float w = invn[row];
+    listed_acc acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int e0 = 0; e0 < d; e0 += 64 * AHEAD) {
+    u32x4_t x[AHEAD][4];
+#pragma unroll
+    for (int g = 0; g < AHEAD; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int e = e0 + g * 64 + i * 16;
+            x[g][i] = *(const u32x4_t *)(at + (e < d ? e : 0));
+        }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < AHEAD; ++g) {
+        if (e0 + g * 64 >= d) break;  // (d is a multiple of 64)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(listed_frag, x[g][i]),
+                                                          __builtin_bit_cast(listed_frag, sh_q[(e0 + g * 64 + i * 16) / 8 + h]), acc, 0, 0, 0);
+    }
+    }
+    return listed_key(acc, w, row);
+}
+// Up to LISTED_FEW rows, what mostly is left: all waves bring them to LDS, whole rows at a time (in the wave's own loads they took 5 us of 13),
+// a pad of 16 bytes behind each, and a wave for 32 of them multiplies.
+#define LISTED_FEW 64
+#define LISTED_LDS(d) (LISTED_FEW * (2 * (d) + 16))
+__device__ __forceinline__ u64 listed_products_few(const bf16_t *__restrict__ cent, const float *__restrict__ invn, const int *sh_rows, int many,
+                                               const u32x4_t *sh_q, int d, unsigned char *room) {
+    constexpr int AHEAD = 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, pitch = 2 * d + 16;
+    const int mine = wave * 32 + (lane & 31) < many ? wave * 32 + (lane & 31) : 0;  // this lane's row
+    const int row = sh_rows[mine];
+    const float w = invn[row];
+    for (int r0 = wave; r0 < many; r0 += 4 * AHEAD) {
+    u32x4_t x[AHEAD][2];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) {
+        const bf16_t *at = cent + (size_t)sh_rows[r0 + 4 * k < many ? r0 + 4 * k : r0] * d;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) x[k][c] = *(const u32x4_t *)(at + ((lane + 64 * c) * 8 < d ? (lane + 64 * c) * 8 : 0));
+    }
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            if (r0 + 4 * k < many && (lane + 64 * c) * 8 < d) *(u32x4_t *)(room + (size_t)(r0 + 4 * k) * pitch + (lane + 64 * c) * 16) = x[k][c];
+    }
+    __syncthreads();
+    if (wave * 32 >= many) return 0;
+    listed_acc acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const unsigned char *at = room + (size_t)mine * pitch + h * 16;
+    u32x4_t x[4], q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+    x[i] = *(const u32x4_t *)(at + i * 32);
+    q[i] = sh_q[i * 2 + h];
+    }
+    for (int e = 64; e <= d; e += 64) {  // (the next four steps are read while four are multiplied)
+    u32x4_t y[4], p[4];
+    const int n = e < d ? e : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        y[i] = *(const u32x4_t *)(at + n * 2 + i * 32);
+        p[i] = sh_q[(n + i * 16) / 8 + h];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(listed_frag, x[i]), __builtin_bit_cast(listed_frag, q[i]), acc, 0, 0, 0);
+        x[i] = y[i];
+        q[i] = p[i];
+    }
+    }
+    return listed_key(acc, w, row);
+}
+
+// BYTES: the bytes of the rows that are rewritten follow.  (Types of their own, not conditions: arguments and code that are not needed cost 1 % of a
+// small step.)
+struct FoldPlain {
+    static constexpr bool LISTED = false, BYTES = false;
+};
+struct FoldBytes {
+    static constexpr bool LISTED = false, BYTES = true;
+    ByteView bytes;
+};
+struct FoldListed {
+    static constexpr bool LISTED = true, BYTES = true;
+    ByteView bytes;
+    FewLists few;
+    int fold;  // 0 = a lookup and nothing else
+};
+template <typename T, int UPD_MAXE_T, class More>
 __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q, const u64 *__restrict__ keys, long n, long K,
                                                           int d, int slices, float theta, int vec, int *out_idx,
                                                           float *out_sim, unsigned char *out_hit, unsigned *access, T *cent,
                                                           float *mean, int *size, float *invn, unsigned *version, u64 *board,
                                                           int spin_limit, u64 *gave_up, const float *__restrict__ q_inv,
                                                           unsigned char *copy_codes, float *copy_scale, float *copy_inv,
-                                                          int *copy_size) {
+                                                          int *copy_size, More more) {
+    constexpr bool LISTED = More::LISTED, BYTES = More::BYTES;
     constexpr int EPC = 16 / (int)sizeof(T);
     __shared__ float sh[4];
     __shared__ float sh_f[4];
@@ -645,6 +800,12 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     __shared__ float sums[FOLD_SUMS];
     __shared__ int list[SISO_FOLD_BOARD];
     __shared__ int sh_all;
+    __shared__ u32x4_t sh_q[LISTED ? SISO_SCREEN_DIM / EPC : 1];
+    __shared__ int sh_rows[LISTED ? LISTED_ROWS : 1];
+    __shared__ unsigned sh_upper[LISTED ? LISTED_ROWS : 1];
+    __shared__ int sh_rows_n;
+    __shared__ unsigned sh_low[4];
+    extern __shared__ __attribute__((aligned(16))) unsigned char listed_room[];  // LISTED: LISTED_LDS(d)
     const long me = blockIdx.x;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const T *qrow = Q + (size_t)me * d;
@@ -662,14 +823,38 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
         for (int e = t * EPC; e < d; e += 256 * EPC) {
             const u32x4_t v = *(const u32x4_t *)(qrow + e);
             ss += chunk_dot(v, v, T());
+            if constexpr (LISTED) sh_q[e / EPC] = v;
         }
     } else {
         for (int e = t; e < d; e += 256) ss += widen(qrow[e]) * widen(qrow[e]);
     }
     u64 key = 0;
-    for (int s = t; s < slices; s += 256) {
-        const u64 k2 = keys[(size_t)me * slices + s];
-        key = k2 > key ? k2 : key;
+    unsigned entry[6], low = 0;
+    int listed = 0, named = 0, words = 0;
+    uint2 place = make_uint2(0, 0);
+    if constexpr (LISTED) {  // all of it in one round trip
+        static_assert(SISO_FEW_WORKGROUPS <= 256 && SISO_FEW_SLOTS == 8, "a workgroup's words to a thread");
+        words = SISO_FEW_SLOTS * 64 / (n <= 8 ? 8 : n <= 32 ? 32 : 64);
+        const u32x4_t *from = (const u32x4_t *)(more.few.slots + ((size_t)me * slices + (t < slices ? t : 0)) * words);
+        const u32x4_t e0 = from[0], e1 = from[1];
+        place = more.few.rows[(size_t)me * SISO_FEW_LIST + t];
+        listed = more.few.cnt[me];
+        key = more.few.best[me];
+        low = t >= slices || e0[0] == ordered_bits(INFINITY) ? 0 : e0[0];  // (of a query that lists nothing: +inf)
+        named = t >= slices ? 0 : (int)e0[1] < words - 2 ? (int)e0[1] : words - 2;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) entry[i] = i < 2 ? e0[2 + i] : e1[i - 2];
+        if (t == 0) sh_rows_n = 0;
+    } else {
+        for (int s = t; s < slices; s += 256) {
+            const u64 k2 = keys[(size_t)me * slices + s];
+            key = k2 > key ? k2 : key;
+        }
+    }
+    if constexpr (LISTED) {
+        asm volatile("" ::"v"(listed));  // (has arrived: it is emptied behind the barrier)
+        low = wave_fold(low, [](unsigned a, unsigned b) __attribute__((always_inline)) { return a > b ? a : b; });
+        if (lane == 0) sh_low[wave] = low;
     }
     ss = wave_sum(ss);
     key = wave_max(key);
@@ -681,6 +866,126 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     const float qi = q_inv ? q_inv[me] : inv_length((sh_f[0] + sh_f[1]) + (sh_f[2] + sh_f[3]));
 #pragma unroll
     for (int w = 0; w < 4; ++w) key = sh_k[w] > key ? sh_k[w] : key;
+    if constexpr (LISTED) {
+        if (t == 0) {  // (everyone has read them)
+            more.few.cnt[me] = 0;
+            more.few.best[me] = 0;
+            if (me == 0) *more.few.call += 1;
+        }
+        low = max(max(sh_low[0], sh_low[1]), max(sh_low[2], sh_low[3]));
+        float bound = unordered_bits(low);
+        auto multiply = [&](int many) {
+            for (int g = wave * 32; g < many; g += 128) {
+                const u64 k2 = listed_product((const bf16_t *)cent, invn, sh_rows[g + (lane & 31) < many ? g + (lane & 31) : g], sh_q, d);
+                key = k2 > key ? k2 : key;
+            }
+        };
+        // the rows that this thread has been given and that reach the bound: of workgroup t, and every 256th of the list
+        const int places = listed < SISO_FEW_LIST ? listed : SISO_FEW_LIST;
+        auto each = [&](auto &&take) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+                if (i < named && few_upper(entry[i]) >= bound) take((int)few_row(entry[i], (unsigned)t, (unsigned)slices), entry[i]);
+            for (int i = 6; i < named; i += 4) {
+                const u32x4_t e = *(const u32x4_t *)(more.few.slots + ((size_t)me * slices + t) * words + 2 + i);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (i + k < named && few_upper(e[k]) >= bound) take((int)few_row(e[k], (unsigned)t, (unsigned)slices), e[k]);
+            }
+            for (int i = t; i < places; i += 256) {
+                const uint2 e = i < 256 ? place : more.few.rows[(size_t)me * SISO_FEW_LIST + i];
+                if (few_upper(e.y) >= bound) take((int)e.x, e.y);
+            }
+        };
+        int own = 0;
+        each([&](int row, unsigned e) __attribute__((always_inline)) {
+            const int to = atomicAdd(&sh_rows_n, 1);
+            if (to < LISTED_ROWS) {
+                sh_rows[to] = row;
+                sh_upper[to] = e & 8191u;
+            }
+            ++own;
+        });
+        __syncthreads();
+        int all_rows = sh_rows_n;
+        if (all_rows > LISTED_FEW) {
+            // Rather many: the bound is short of the best by as much as the bytes may be off.  The cosine of the row of the highest upper end, as
+            // k_screen_pick forms it, is not, and rows that cannot reach that are left out.
+            u64 high = 0;
+            const int kept = all_rows < LISTED_ROWS ? all_rows : LISTED_ROWS;
+            for (int i = t; i < kept; i += 256) {
+                const u64 k2 = (u64)sh_upper[i] << 32 | (unsigned)i;
+                high = k2 > high ? k2 : high;
+            }
+            high = wave_max(high);
+            if (lane == 0) sh_k[wave] = high;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < 4; ++w) high = sh_k[w] > high ? sh_k[w] : high;
+            const int best_row = sh_rows[(unsigned)high];
+            const float cosine = row_product<bf16_t>((const bf16_t *)qrow, sh_q, 1, (const bf16_t *)cent + (size_t)best_row * d, d, lane) * qi * invn[best_row];
+            if (cosine == cosine) bound = fmaxf(bound, cosine - 2e-5f);
+            __syncthreads();
+            if (t == 0) sh_rows_n = 0;
+            __syncthreads();
+            own = 0;
+            each([&](int row, unsigned) __attribute__((always_inline)) {
+                const int to = atomicAdd(&sh_rows_n, 1);
+                if (to < LISTED_ROWS) sh_rows[to] = row;
+                ++own;
+            });
+            __syncthreads();
+            all_rows = sh_rows_n;
+        }
+        if (all_rows <= LISTED_FEW) {
+            const u64 k2 = all_rows > 0 ? listed_products_few((const bf16_t *)cent, invn, sh_rows, all_rows, sh_q, d, listed_room) : 0;
+            key = k2 > key ? k2 : key;
+        } else if (all_rows <= LISTED_ROWS) {
+            multiply(all_rows);
+        } else {  // more than LDS holds: one part of them after the other, by their numbers
+            int before = own;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(before, off);
+                if (lane >= off) before += o;
+            }
+            if (lane == 63) list[wave] = before;
+            __syncthreads();
+            before -= own;
+            for (int w = 0; w < wave; ++w) before += list[w];
+            for (int from = 0; from < all_rows; from += LISTED_ROWS) {
+                int number = before - from;
+                each([&](int row, unsigned) __attribute__((always_inline)) {
+                    if (number >= 0 && number < LISTED_ROWS) sh_rows[number] = row;
+                    ++number;
+                });
+                __syncthreads();
+                multiply(all_rows - from < LISTED_ROWS ? all_rows - from : LISTED_ROWS);
+                __syncthreads();
+            }
+        }
+        if (lane == 0) sh_k[wave] = key;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 4; ++w) key = sh_k[w] > key ? sh_k[w] : key;
+        if (qi == 0.f) {  // without a single element: all products are 0, and the first row that has a length, or none, is named
+            bool none = true;
+            for (int e = t; e < d; e += 256) none = none && (__float_as_uint(widen(qrow[e])) << 1) == 0;
+            if (!__syncthreads_or(!none)) {
+                key = 0;
+                for (long r0 = 0; r0 < K && key == 0; r0 += 256) {
+                    const bool ok = r0 + t < K && invn[r0 + t] == invn[r0 + t];
+                    __syncthreads();
+                    if (lane == 0) masks[wave] = 0;
+                    const u64 mask = __ballot(ok);
+                    if (lane == 0) masks[wave] = mask;
+                    __syncthreads();
+                    for (int w = 3; w >= 0; --w)
+                        if (masks[w] != 0) key = pack_key(0.f, (unsigned)(r0 + 64 * w + __ffsll((long long)masks[w]) - 1));
+                }
+            }
+        }
+    }
     long best_i = -1;
     float best_s = -INFINITY;
     const bool finite_q = qi == qi;
@@ -693,11 +998,13 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     if (t == 0) {
         out_idx[me] = (int)best_i;
         out_sim[me] = best_s;
-        out_hit[me] = hit ? 1 : 0;
+        if (out_hit) out_hit[me] = hit ? 1 : 0;
         if (hit && access && access[best_i] != SISO_ACCESS_INF) atomicAdd(&access[best_i], 1u);
         __hip_atomic_store(board + me, board_entry(hit, (int)best_i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!hit) return;
+    if constexpr (LISTED)
+        if (!more.fold) return;
     // --- k_update for query `me`: its centroid's mean and weight, on their way during the wait
     const int k = (int)best_i;
     float x_me[UPD_MAXE_T], m_old[UPD_MAXE_T];
@@ -707,6 +1014,11 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
         m_old[e] = mean[(size_t)k * d + (col < d ? col : 0)];
     }
     const int size_old = size[k];
+    float4 block = make_float4(0.f, 0.f, 0.f, 0.f);  // what the bytes of the centroid's 32 rows are made with
+    if constexpr (BYTES) block = more.bytes.meta[k >> 5];
+    // (without bytes to keep step with, that the count changes is all that is asked of it: a store, where 256 additions to the one line of a small
+    // cache's counts are 2 us)
+    const unsigned counted = BYTES || !version ? 0u : version[k >> 5];
 #pragma unroll
     for (int e = 0; e < UPD_MAXE_T; ++e) {
         x_me[e] = t + e * 256 < d ? widen(xr[e]) : 0.f;
@@ -750,12 +1062,17 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     if (m) list[before + __popcll(mask & ((1ull << lane) - 1))] = t;
     __syncthreads();
     if (list[0] != (int)me) return;  // an earlier member leads this centroid (uniform over the block)
-    if (t == 0) raise_version(version, k);
+    if (t == 0) {
+        if constexpr (BYTES) raise_version(version, k);
+        else if (version) version[k >> 5] = counted + 1;
+    }
     int members = fold_member<UPD_MAXE_T>(x_me, acc, sh) ? 1 : 0;
     members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 4 : 2, false, false>(list, 1, all, Q, d, acc, sums);
     if (members == 0) return;
-    float stored[UPD_MAXE_T];
-    const bool rewritten = update_write<T, UPD_MAXE_T>(k, d, size_old, members, m_old, acc, cent, mean, size, invn, sh, stored);
+    float stored[UPD_MAXE_T], inv;
+    const bool rewritten = update_write<T, UPD_MAXE_T>(k, d, size_old, members, m_old, acc, cent, mean, size, invn, sh, stored, inv);
+    if constexpr (BYTES)
+        if (rewritten) follow_bytes<UPD_MAXE_T>(stored, inv, k, d, more.bytes, block, sh);
     if (copy_codes) {  // the 8-bit copy follows
         if (t == 0) copy_size[k] = size_old + members;
         if (rewritten) fp8_store_row<UPD_MAXE_T>(stored, d, copy_codes + (size_t)k * d, copy_scale + k, copy_inv + k, sh);
@@ -1219,6 +1536,7 @@ void siso_swap_sets(siso_cache *c) {
     std::swap(c->locality, c->locality_b);
     std::swap(c->access, c->access_b);
     std::swap(c->version, c->version_b);
+    siso_bytes_all_behind(c);
 }
 
 extern "C" int siso_create_ex(int dim, long capacity, int dtype, siso_cache **out) {
@@ -1335,7 +1653,7 @@ extern "C" int siso_set_option(siso_cache *c, const char *name, long value) {
     if (!strcmp(name, "mfma_config")) c->opt_mfma_config = (int)value;
     else if (!strcmp(name, "tiles_per_slice")) c->opt_tiles_per_slice = (int)value;
     else if (!strcmp(name, "merge_config")) c->opt_merge_config = (int)value;
-    else if (!strcmp(name, "screen") && value <= 3) c->opt_screen = (int)value;
+    else if (!strcmp(name, "screen") && value <= 4) c->opt_screen = (int)value;
     else if (!strcmp(name, "screen_room")) c->opt_screen_room = (int)value;
     else if (!strcmp(name, "mfma_qblock")) c->opt_mfma_qblock = (int)value;
     else if (!strcmp(name, "fold_spin_limit")) c->opt_fold_spin_limit = (int)value;
@@ -1373,6 +1691,7 @@ extern "C" int siso_load(siso_cache *c, const void *centroids, const int *counts
     hipLaunchKernelGGL(k_fill_nan, dim3(1), dim3(SISO_PAD_ROWS), 0, c->stream, c->invn + k, SISO_PAD_ROWS);
     HIP_TRY(c, hipGetLastError());
     c->count = k;
+    siso_bytes_all_behind(c);
     return SISO_OK;
 }
 
@@ -1396,6 +1715,7 @@ extern "C" int siso_import(siso_cache *c, const void *centroids, const float *me
     hipLaunchKernelGGL(k_fill_nan, dim3(1), dim3(SISO_PAD_ROWS), 0, c->stream, c->invn + k, SISO_PAD_ROWS);
     HIP_TRY(c, hipGetLastError());
     c->count = k;
+    siso_bytes_all_behind(c);
     return SISO_OK;
 }
 
@@ -1476,6 +1796,7 @@ extern "C" int siso_reserve(siso_cache *c, long n) {
     if (c->dtype == SISO_FP8) return siso_fp8_ensure_batch(c, n);
     // (no room for the bytes of a screened lookup is no error: such lookups then go without)
     if (siso_screen_wanted(&full, n)) siso_screen_reserve(c, n);
+    if (siso_bytes_few_wanted(&full, n < SISO_FEW ? n : SISO_FEW)) siso_bytes_few_reserve(c);
     if (n > 256) return ensure_update_notes(c);
     return SISO_OK;
 }
@@ -1579,21 +1900,25 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
     if (board_emptied && row_keys == SISO_KEY_ROWS) {
         const siso_cache *ms = c->fold_master;  // the bf16 cache behind an 8-bit copy, or NULL
         siso_cache *tgt = ms ? const_cast<siso_cache *>(ms) : c;
+        // (bytes of rows of up to 1,024 elements, if they are current, or nearly so: otherwise they are left behind)
+        const ByteView bytes = tgt->bytes.behind == 0 ? siso_byte_view(tgt) : ByteView{nullptr, nullptr, nullptr, 0};
         // the end of the lookup and the update of its hits as one kernel (see k_finalize_update)
         // polls of the board (a microsecond or two each) before a block gives up
         const int spin_limit = c->opt_fold_spin_limit >= 0 ? c->opt_fold_spin_limit : 1 << 18;
-#define SISO_LAUNCH_FOLD(T, E)                                                                                            \
-    hipLaunchKernelGGL((k_finalize_update<T, E>), dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, keys, n, c->count, \
+#define SISO_LAUNCH_FOLD(T, E, MORE, ...)                                                                                 \
+    hipLaunchKernelGGL((k_finalize_update<T, E, MORE>), dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, keys, n, c->count, \
                        c->dim, slices, tl.v[0], vec, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr, \
-                       (T *)tgt->cent, tgt->mean, tgt->size, tgt->invn, tgt->version, c->counters + 4, spin_limit, c->counters, \
+                       (T *)tgt->cent, tgt->mean, tgt->size, tgt->invn, siso_counted(tgt), c->counters + 4, spin_limit, c->counters, \
                        ms ? (const float *)c->fp8_qinv : (const float *)nullptr, ms ? (unsigned char *)c->cent : nullptr, \
-                       ms ? c->scale : nullptr, ms ? c->invn : nullptr, ms ? c->size : nullptr)
+                       ms ? c->scale : nullptr, ms ? c->invn : nullptr, ms ? c->size : nullptr, MORE{__VA_ARGS__})
         if (tgt->dtype == SISO_F32) {
-            if (c->dim <= 1024) SISO_LAUNCH_FOLD(float, 4);
-            else SISO_LAUNCH_FOLD(float, 16);
+            if (bytes.codes) SISO_LAUNCH_FOLD(float, 4, FoldBytes, bytes);
+            else if (c->dim <= 1024) SISO_LAUNCH_FOLD(float, 4, FoldPlain);
+            else SISO_LAUNCH_FOLD(float, 16, FoldPlain);
         } else {
-            if (c->dim <= 1024) SISO_LAUNCH_FOLD(bf16_t, 4);
-            else SISO_LAUNCH_FOLD(bf16_t, 16);
+            if (bytes.codes) SISO_LAUNCH_FOLD(bf16_t, 4, FoldBytes, bytes);
+            else if (c->dim <= 1024) SISO_LAUNCH_FOLD(bf16_t, 4, FoldPlain);
+            else SISO_LAUNCH_FOLD(bf16_t, 16, FoldPlain);
         }
 #undef SISO_LAUNCH_FOLD
         HIP_TRY(c, hipGetLastError());
@@ -1617,6 +1942,31 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
     return siso_check_hip(c, hipGetLastError(), "k_lookup_finalize");
 }
 
+// Few queries over the bytes of the rows: two kernels, the second of which folds the hits if the caller is about to.
+static int few_lookup(siso_cache *c, const void *queries, long n, float theta, int count_index, int *out_idx, float *out_sim,
+                      unsigned char *out_hit, int *folded) {
+    const bool fold = folded && out_hit;
+    const ByteView bytes = siso_byte_view(c);
+    c->board_to_clear = fold ? c->counters + 4 : nullptr;
+    siso_prof_begin(c);
+    const int rc = siso_bytes_few_launch(c, queries, n, bytes);
+    siso_prof_end(c);
+    c->board_to_clear = nullptr;
+    if (rc != SISO_OK) return rc;
+    static bool attr_done = false;
+    if (!attr_done) {
+        HIP_TRY(c, hipFuncSetAttribute((const void *)k_finalize_update<bf16_t, 4, FoldListed>, hipFuncAttributeMaxDynamicSharedMemorySize, LISTED_LDS(SISO_SCREEN_DIM)));
+        attr_done = true;
+    }
+    hipLaunchKernelGGL((k_finalize_update<bf16_t, 4, FoldListed>), dim3((unsigned)n), dim3(256), LISTED_LDS(c->dim), c->stream, (const bf16_t *)queries, (const u64 *)nullptr, n,
+                       c->count, c->dim, siso_bytes_few_workgroups(c), theta, 1, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr,
+                       (bf16_t *)c->cent, c->mean, c->size, c->invn, c->version, c->counters + 4,
+                       c->opt_fold_spin_limit >= 0 ? c->opt_fold_spin_limit : 1 << 18, c->counters, (const float *)nullptr, (unsigned char *)nullptr,
+                       (float *)nullptr, (float *)nullptr, (int *)nullptr, FoldListed{bytes, c->few, fold ? 1 : 0});
+    if (fold) *folded = 1;
+    return siso_check_hip(c, hipGetLastError(), "k_finalize_update");
+}
+
 int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *thetas, int m, int count_index,
                      int *out_idx, float *out_sim, unsigned char *out_hit, u64 *static_keys, long static_cap, int *folded, float floor) {
     if (folded) *folded = 0;
@@ -1632,6 +1982,8 @@ int siso_lookup_impl(siso_cache *c, const void *queries, long n, const float *th
         owner = c->upd_owner;
         members = c->upd_members;
     }
+    if (!static_keys && m == 1 && siso_mfma_aligned(queries) && siso_bytes_few_wanted(c, n) && siso_bytes_few_room(c, n))
+        return few_lookup(c, queries, n, thetas[0], count_index, out_idx, out_sim, out_hit, folded);
     PlainLookup plain;
     // (not on the static keys: the bytes live in a workspace that other calls share and a larger one moves)
     const bool screen = siso_screen_above_wanted(c, n, floor);
@@ -1705,6 +2057,7 @@ static int update_hits_impl(siso_cache *c, const void *queries, const int *idx, 
         }
 #undef SISO_LAUNCH_UPDATE
         HIP_TRY(c, hipGetLastError());
+        siso_bytes_behind(c, m);
     }
     return SISO_OK;
 }

@@ -45,11 +45,38 @@ struct ScreenSpace {
 // were made from, so that a lookup writes anew only what has changed since.  All of that lives on the device, where the
 // order of the stream, a captured graph's launches among them, is the order in which rows are written and read.  The
 // counts of the two sets begin far apart: what was made from one is never taken for the other.
+struct ByteView {  // where they lie
+    signed char *codes;  // NULL: nowhere
+    float4 *meta;        // for 32 rows: scale, error, error for lower ends, 1 / scale
+    u64 *made;           // for 32 rows: the count they were made from << 8 | how many of them there were
+    int dp;              // bytes of a row
+};
 struct ByteRows {
     char *at;  // room for the bytes of `rows` rows, or NULL; see byte_store in screen.hip
     long rows;
     long refused;  // the smallest number of rows that found no room (0 = none): not asked for again until siso_reserve or a release
     int recorded;  // a graph refers to them: outgrown, they stay until the cache goes (screen_kept)
+    // How many rows may have changed since all bytes were current (an estimate of the host's, that only the choice of a route goes
+    // by), and how many elements lookups have read as they are stored that would have gone over the bytes.
+    long behind;
+    double forgone;
+    int written;  // some bytes have been made, or are by a recorded launch
+    int calls;  // lookups over them since they were written
+};
+
+// A lookup of few queries over the bytes (lookup_bytes.hip, k_finalize_update), per query; best and cnt are left as they were found, all zeros.
+#define SISO_FEW 64
+#define SISO_FEW_WORKGROUPS 256
+#define SISO_FEW_SLOTS 8  // words of a workgroup for each of 64 queries; of 32 twice, of eight as many times: its largest lower end, how many rows it names, and those that need no place in the list
+#define SISO_FEW_LIST 2048   // places
+#define SISO_FEW_MOST_ROWS (32L * 256 * SISO_FEW_WORKGROUPS)
+struct FewLists {
+    u64 *best;        // largest key of the blocks that were multiplied as they are stored
+    u64 *table;       // [SISO_FEW_WORKGROUPS][SISO_FEW]: number of the call << 32 | the largest lower end (ordered bits) that a workgroup knows
+    unsigned *call;   // the number of the call
+    int *cnt;         // rows in the list
+    uint2 *rows;      // [SISO_FEW_LIST]: row, entry
+    unsigned *slots;  // for as many workgroups as there are: [query][workgroup][words]
 };
 
 struct siso_cache {
@@ -132,6 +159,9 @@ struct siso_cache {
     // workspaces, so that a pair search does not move what a captured lookup refers to.
     ScreenSpace screen, screen_pairs;
     ByteRows bytes;
+    FewLists few;  // room for them from few.best on, or NULL
+    int *few_flooded;  // pinned: a workgroup found no room for its lists; such lookups are better off on the rows as they are stored:
+    long few_rest, few_rests;  // as many more of them, and how many that were the last time
     long screen_reserved;  // batches that siso_reserve has sized `screen` for, or tried to: their lookups leave it as it is
     int screen_recorded;  // a graph holds a screened lookup on `screen`: outgrown, it stays until the cache goes (screen_kept)
     std::vector<char *> *screen_kept;
@@ -370,6 +400,19 @@ __device__ __forceinline__ float row_product(const T *qrow, const u32x4_t *sh_q,
     return wave_sum(sum[0]);
 }
 
+// A row that a workgroup of k_bytes_few names, in 32 bits: the query, the row's number in the workgroup, and the upper end of its cosine in thirteen
+// bits, rounded up (the largest stands for anything above).
+__device__ __forceinline__ unsigned few_upper_bits(float v) {
+    const float x = (v + 1.25f) * (8191.f / 2.5f);
+    return x >= 8190.f ? 8191u : x <= 0.f ? 1u : (unsigned)x + 1u;
+}
+__device__ __forceinline__ float few_upper(unsigned e) {
+    return (e & 8191u) == 8191u ? INFINITY : (float)(e & 8191u) * (2.5f / 8191.f) - 1.25f + 1e-6f;
+}
+__device__ __forceinline__ unsigned few_row(unsigned e, unsigned workgroup, unsigned workgroups) {  // (32 rows to a block, eight blocks to a round)
+    return (((e >> 18) & 255u) * workgroups + workgroup) * 32u + ((e >> 13) & 31u);
+}
+
 // By one thread for a stored row that its block writes (see ByteRows); _once: in a launch that writes all rows from the first on.
 __device__ __forceinline__ void raise_version(unsigned *version, long row) { atomicAdd(version + (row >> 5), 1u); }
 __device__ __forceinline__ void raise_version_once(unsigned *version, long row) {
@@ -605,6 +648,27 @@ int siso_few_slices(const siso_cache *c, long n);
 int siso_few_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys);
 int siso_skinny_slices(const siso_cache *c, long n);
 int siso_skinny_launch(siso_cache *c, const void *queries, long n, int slices, u64 *keys, int *row_keys);
+
+// Up to SISO_FEW queries over the bytes of bf16 rows (lookup_bytes.hip): fills c->few, which k_finalize_update goes on with.
+int siso_bytes_few_workgroups(const siso_cache *c);
+int siso_bytes_few_launch(siso_cache *c, const void *queries, long n, const ByteView &v);
+// Is a lookup of n queries to go that way?  If so: room and bytes for it (may synchronise and allocate, not under capture); 0 = without.
+int siso_bytes_few_wanted(const siso_cache *c, long n);
+int siso_bytes_few_room(siso_cache *c, long n);
+void siso_bytes_few_reserve(siso_cache *c);
+// The host's note that rows of the cache are about to be written by something that leaves the bytes behind (see ByteRows).
+inline void siso_bytes_behind(siso_cache *c, long rows) {
+    c->bytes.behind = c->bytes.behind + rows < c->capacity ? c->bytes.behind + rows : c->capacity;
+}
+inline void siso_bytes_all_behind(siso_cache *c) {
+    c->bytes.behind = c->capacity;
+    c->bytes.forgone = 0;
+    c->few_rest = c->few_rests = 0;  // (other rows: perhaps no flood)
+}
+ByteView siso_byte_view(const siso_cache *c);
+// The counts of the rows for a launch that raises them, or NULL where nobody can ask: no bytes have been made yet (those that come are made from all rows),
+// and no graph records the launch, to be replayed when there are.
+unsigned *siso_counted(const siso_cache *c);
 
 // Top-k lookups, first phase: groups[q * ng + g].x = the largest scaled product <q, c> / |c| among the 16 rows of group g
 // (-inf if none is finite), its lowest four bits replaced by the row's number in the group; .y = the second largest (its

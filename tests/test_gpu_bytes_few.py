@@ -1,0 +1,171 @@
+"""Lookups of up to 64 bf16 queries over the bytes of the rows, forced on by an option, against the kernel that reads the rows as
+they are stored: the same bits, whatever the rows and queries, with and without the fold of the hits."""
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+SKINNY = 3
+THETA = 0.85
+
+
+@pytest.fixture(scope="module")
+def siso():
+    from paper_2508_18736_amd import siso as m
+    return m
+
+
+def pair(siso, c, capacity=None):
+    """Two caches of the same rows: over the bytes, and as they are stored."""
+    out = []
+    for screen in (4, 2):
+        cache = siso.SisoCache(c.shape[1], capacity or c.shape[0], siso.BF16)
+        cache.set_option("screen", screen)
+        if screen == 2:
+            cache.set_lookup_path(SKINNY)
+        cache.load(c)
+        out.append(cache)
+    return out
+
+
+def mixture(g, K, d, common=0.0, per=16):
+    """Rows in groups around directions that share a common part (mean cosine `common`), of random lengths."""
+    unit = torch.nn.functional.normalize
+    base = unit(torch.randn(-(-K // per), d, device=DEV, generator=g), dim=1) * (1 - common) ** 0.5
+    base = unit(base + common ** 0.5 * unit(torch.randn(1, d, device=DEV, generator=g), dim=1), dim=1)
+    c = base[torch.randint(0, base.shape[0], (K,), device=DEV, generator=g)] + 0.08 / d ** 0.5 * torch.randn(K, d, device=DEV, generator=g)
+    return (c * (0.5 + torch.rand(K, 1, device=DEV, generator=g))).bfloat16()
+
+
+def queries(g, c, n, common=0.0):
+    q = c[torch.randint(0, c.shape[0], (n,), device=DEV, generator=g)].float() + 0.05 / c.shape[1] ** 0.5 * torch.randn(n, c.shape[1], device=DEV, generator=g)
+    miss = torch.rand(n, device=DEV, generator=g) < 0.4
+    other = torch.randn(n, c.shape[1], device=DEV, generator=g)
+    if common:
+        other = mixture(g, max(n, 32), c.shape[1], 0.0)[:n].float() + c.float().mean(0)
+    return torch.where(miss[:, None], other, q).bfloat16()
+
+
+def same(a, b, what):
+    for x, y in zip(a, b):
+        assert torch.equal(x, y) or torch.equal(x.nan_to_num(nan=7.0), y.nan_to_num(nan=7.0)), what
+
+
+@pytest.mark.parametrize("K,n,d", [(1, 1, 128), (31, 2, 256), (32, 33, 192), (33, 64, 320), (257, 7, 384), (2048, 64, 448), (8191, 32, 512),
+                                   (20000, 64, 640), (65537, 31, 768), (65536 * 2 + 5, 64, 768), (70001, 1, 832), (70000, 40, 960), (90000, 64, 1024),
+                                   (100003, 3, 1024)])
+@pytest.mark.parametrize("common", [0.0, 0.7])
+def test_the_same_bits(siso, K, n, d, common):
+    print(f"case: few over bytes K={K} n={n} d={d} common={common}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K + n)
+    c = mixture(g, K, d, common)
+    a, b = pair(siso, c)
+    for seed in range(2):
+        q = queries(g, c, n, common)
+        same(a.lookup(q, THETA), b.lookup(q, THETA), "lookup")
+    for seed in range(5):
+        q = queries(g, c, n, common)
+        same(a.lookup_update(q, THETA), b.lookup_update(q, THETA), f"step {seed}")
+    same(a.export() + a.export_meta(), b.export() + b.export_meta(), "state")
+    assert a.bad_indices() == 0
+
+
+def test_rows_and_queries_that_bytes_say_nothing_about(siso):
+    print("case: few over bytes, odd rows", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(2)
+    K, d, n = 9000, 768, 40
+    c = mixture(g, K, d)
+    c[5] = 0
+    c[77, 3] = float("nan")
+    c[200] *= 1e-20
+    c[300, 9] = float("inf")
+    c[400] *= 1e18
+    c[8999] = 0
+    c[1000:1100] = c[1000]  # equal rows: the lowest
+    a, b = pair(siso, c)
+    q = queries(g, c, n)
+    same(a.lookup(q, THETA), b.lookup(q, THETA), "odd rows")
+    q[0] = 0
+    q[1, 5] = float("nan")
+    q[2] = c[1050]
+    q[3] = c[200] * 1e15
+    same(a.lookup(q, THETA), b.lookup(q, THETA), "odd queries")
+    same(a.lookup_update(q, THETA), b.lookup_update(q, THETA), "odd queries, folded")
+    q[4] = c[500] * 1e-19  # a length near the end of the range: nothing of the batch goes by the bytes
+    q[5] = 1e-30
+    same(a.lookup(q, THETA), b.lookup(q, THETA), "odd lengths")
+    q = queries(g, c, n)
+    same(a.lookup_update(q, THETA), b.lookup_update(q, THETA), "behind them")
+    c[0], c[1] = float("nan"), 0  # the first row with a weight
+    a, b = pair(siso, c)
+    q[0] = 0
+    same(a.lookup(q, THETA), b.lookup(q, THETA), "a query of zeros")
+
+
+@pytest.mark.parametrize("d", [128, 768])
+def test_rows_close_together(siso, d):
+    """More rows near the best than the lists hold: every workgroup that finds no room multiplies its rows as they are stored."""
+    print(f"case: few over bytes, crowded d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    for K, common, n in ((40000, 0.98, 64), (40000, 0.9, 1), (9000, 1.0, 33)):
+        c = mixture(g, K, d, common, per=1)
+        a, b = pair(siso, c)
+        q = queries(g, c, n, common)
+        same(a.lookup(q, THETA), b.lookup(q, THETA), "lookup")
+        same(a.lookup_update(q, THETA), b.lookup_update(q, THETA), "step")
+        q = queries(g, c, n, common)
+        same(a.lookup(q, THETA), b.lookup(q, THETA), "lookup behind it")
+
+
+def test_rows_that_change(siso):
+    """Updates of every size, loads, rows whose largest element outgrows the scale of its block, and replays of a recorded step:
+    blocks whose bytes are behind are multiplied as they are stored, or written anew."""
+    print("case: few over bytes, changing rows", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(4)
+    K, d = 12000, 384
+    c = mixture(g, K, d)
+    a, b = pair(siso, c)
+    for seed, n in enumerate((64, 300, 1, 5, 64)):
+        q = queries(g, c, n)
+        if seed == 3:  # spikes
+            q = torch.zeros(n, d, device=DEV, dtype=torch.bfloat16)
+            q[:, 7] = 1
+        idx = torch.randint(0, K, (n,), device=DEV, generator=g, dtype=torch.int32)
+        for cache in (a, b):
+            cache.update(q, idx)
+        p = queries(g, c, 64)
+        p[:5, 7] += 20
+        same(a.lookup(p, THETA), b.lookup(p, THETA), f"update {seed}")
+        same(a.lookup_update(p, 0.3), b.lookup_update(p, 0.3), f"step {seed}")
+        same(a.lookup(p, THETA), b.lookup(p, THETA), f"behind step {seed}")
+    q, out = queries(g, c, 64), [[torch.empty(64, dtype=t, device=DEV) for t in (torch.int32, torch.float32, torch.uint8)] for _ in range(2)]
+    graphs = []
+    torch.cuda.synchronize()
+    for cache, o in zip((a, b), out):
+        side = torch.cuda.Stream()
+        cache.set_stream(side)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            cache.lookup_update(q, THETA, *o)
+        graphs.append(graph)
+    for seed in range(5):
+        q.copy_(queries(g, c, 64))
+        more = mixture(g, K, d)
+        torch.cuda.synchronize()
+        if seed == 2:
+            a.load(more)
+            b.load(more)
+        if seed == 3:
+            a.update(q, out[1][0])
+            b.update(q, out[1][0])
+        torch.cuda.synchronize()
+        for graph in graphs:
+            graph.replay()
+        torch.cuda.synchronize()
+        same(*out, f"replay {seed}")
+    same(a.export(), b.export(), "state behind the replays")
+    torch.cuda.synchronize()
+    got = a.lookup(q, THETA), b.lookup(q, THETA)  # (on two streams)
+    torch.cuda.synchronize()
+    same(*got, "behind the replays")
