@@ -1309,6 +1309,7 @@ ScreenRoom screen_room(char *base, const siso_cache *c, long rows, long n) {
 }
 
 bool capturing(const siso_cache *c) {
+    if (c->stream == nullptr) return false;  // (the null stream cannot be captured, and to ask takes 0.2 us)
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
     return status != hipStreamCaptureStatusNone;
