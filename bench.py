@@ -315,11 +315,13 @@ def main():
     screened = cache.screened(nb)  # (products of bytes; the rows that can be the closest formed anew in single precision)
     peak_tflops = PEAK_FP8_TFLOPS if fp8 else PEAK_INT8_TFLOPS if screened else PEAK_BF16_TFLOPS
     if streaming:
+        if screened:  # (a lookup over the rows' bytes reads one byte an element)
+            eb = 1.0
         bytes_alg = K * d * eb + nb * d * eb + K * 4.0  # centroids + queries + inverse lengths, read once
         roof = {"bound": "hbm", "achieved": bytes_alg / avg_s / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": bytes_alg / avg_s / 1e9 / PEAK_HBM_GBS, "traffic": measured_traffic(name + ("_fp8" if fp8 else "")),
                 "algorithmic_bytes": bytes_alg, "kernel_ms": avg_s * 1e3,
-                "launches": launches,
+                "launches": launches, "screened": screened,
                 # the same bytes over the whole step (every kernel, launch and gap of it): the streaming target
                 "step_frac": bytes_alg / (dt / steps) / 1e9 / PEAK_HBM_GBS}
         if graph_ms:

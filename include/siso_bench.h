@@ -47,7 +47,8 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *   "screen"          0 = default (large lookups and pair searches of fp32 and bf16 caches rule most rows out by products
  *                     of bytes, see siso_lookup and siso_merge); 1 = wherever the kernels can (dimensions up to 1,024; pair searches
  *                     at thresholds from 0.25 on) and to the end; 2 = never; 3 = wherever the kernels can, a batch
- *                     given up as by default once too many of its queries are near too many rows
+ *                     given up as by default once too many of its queries are near too many rows; 4 = as 0, but lookups of
+ *                     up to 64 bf16 queries over the bytes of the rows wherever those kernels can
  *   "screen_room"     0 = default; > 0 = KiB that a workspace of those products may take: what needs more goes without
  *                     (what the calls do by themselves where memory is short)
  *   "second_set"      1 = allocate now the second set of arrays that siso_merge_apply and siso_refresh

@@ -1585,7 +1585,7 @@ int siso_screen_above_wanted(const siso_cache *c, long n, float floor) {
 
 extern "C" int siso_screened(const siso_cache *c, long n) {
     if (!c || n < 0) return SISO_EINVAL;
-    return n == 0 ? siso_screen_pairs_wanted(c, c->count, 1.f) : siso_screen_wanted(c, n);
+    return n == 0 ? siso_screen_pairs_wanted(c, c->count, 1.f) : siso_screen_wanted(c, n) || siso_bytes_few_wanted(c, n);
 }
 
 // Room for the bytes of `rows` rows of the cache, which are then made by the next lookup (nothing made from is recorded there).
