@@ -1638,6 +1638,8 @@ static int note_recorded(siso_cache *c, bool workspace) {
     return SISO_OK;
 }
 
+bool siso_bytes_may_record(siso_cache *c) { return !capturing(c) || note_recorded(c, false) == SISO_OK; }
+
 // ---- few queries over the bytes (lookup_bytes.hip)
 static bool few_lists_room(siso_cache *c) {
     if (c->few.best) return true;

@@ -1901,7 +1901,8 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
         const siso_cache *ms = c->fold_master;  // the bf16 cache behind an 8-bit copy, or NULL
         siso_cache *tgt = ms ? const_cast<siso_cache *>(ms) : c;
         // (bytes of rows of up to 1,024 elements, if they are current, or nearly so: otherwise they are left behind)
-        const ByteView bytes = tgt->bytes.behind == 0 ? siso_byte_view(tgt) : ByteView{nullptr, nullptr, nullptr, 0};
+        ByteView bytes = tgt->bytes.behind == 0 ? siso_byte_view(tgt) : ByteView{nullptr, nullptr, nullptr, 0};
+        if (bytes.codes && !siso_bytes_may_record(tgt)) bytes.codes = nullptr;
         // the end of the lookup and the update of its hits as one kernel (see k_finalize_update)
         // polls of the board (a microsecond or two each) before a block gives up
         const int spin_limit = c->opt_fold_spin_limit >= 0 ? c->opt_fold_spin_limit : 1 << 18;

@@ -666,6 +666,9 @@ inline void siso_bytes_all_behind(siso_cache *c) {
     c->few_rest = c->few_rests = 0;  // (other rows: perhaps no flood)
 }
 ByteView siso_byte_view(const siso_cache *c);
+// Before every launch that is given the address of the bytes: a graph that records it goes on using them, so they stay when they are outgrown.  False: that
+// could not be noted, and the launch has to do without them.
+bool siso_bytes_may_record(siso_cache *c);
 // The counts of the rows for a launch that raises them, or NULL where nobody can ask: no bytes have been made yet (those that come are made from all rows),
 // and no graph records the launch, to be replayed when there are.
 unsigned *siso_counted(const siso_cache *c);

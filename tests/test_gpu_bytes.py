@@ -8,6 +8,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 TYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
 THETA = 0.85
+SKINNY = 3
 
 
 @pytest.fixture(scope="module")
@@ -126,3 +127,68 @@ def test_behind_replayed_graphs(siso, dtype):
             cache.update(rows(g, 100, d, dtype), torch.randint(0, K, (100,), device=DEV, generator=g, dtype=torch.int32))
             torch.cuda.synchronize()
             as_fresh(siso, cache, d, dtype, q, "update between replays")
+
+
+@pytest.mark.parametrize("copy", [False, True])
+def test_bytes_that_a_recorded_fold_writes_to_stay(siso, copy):
+    """A step whose lookup goes over the stored rows (here: more than 64 queries, or an 8-bit copy) writes the bytes of the rows it folds.  A graph that
+    holds it refers to them: they stay when the cache outgrows them, which is looked at before the graph is replayed, and replays then leave the rows and the
+    later lookups that they leave on a cache without bytes."""
+    print(f"case: kept bytes of a recorded fold, copy={copy}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(17)
+    d, K, capacity, n = 256, 40000, 200000, 64 if copy else 100
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()  # (all but torch's own)
+
+    c, more = rows(g, K, d, "bf16", rows(g, 4000, d, "bf16")), rows(g, capacity, d, "bf16")
+    q, few = rows(g, n, d, "bf16", c), rows(g, 64, d, "bf16", c)
+    out = [(torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV), torch.empty(n, dtype=torch.uint8, device=DEV)) for _ in range(2)]
+    caches, others, graphs = [], [], []
+    main, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    for screen, o in zip((4, 2), out):
+        cache = siso.SisoCache(d, capacity, siso.BF16)
+        cache.set_option("screen", screen)
+        cache.load(c)
+        cache.lookup(few, THETA)  # (of the first: makes its bytes)
+        other = siso.SisoCache(d, capacity, siso.FP8) if copy else None
+        if copy:
+            other.load(c)
+        for stream in (main, side):
+            torch.cuda.synchronize()
+            for x in filter(None, (cache, other)):
+                x.set_stream(stream)
+            step = (lambda: other.lookup_update_with(cache, q, THETA, *o)) if copy else (lambda: cache.lookup_update(q, THETA, *o))
+            if stream is main:
+                step()
+            else:
+                graphs.append(torch.cuda.CUDAGraph())
+                with torch.cuda.graph(graphs[-1], stream=side):
+                    step()
+        for x in filter(None, (cache, other)):
+            x.set_stream(main)
+        caches.append(cache)
+        others.append(other)
+    torch.cuda.synchronize()
+    caches[0].load(more)
+    before = free()
+    caches[0].lookup(few, THETA)  # (bytes for all of the capacity: 51 MB, and the 10 MB of before stay)
+    assert before - free() > capacity * d
+    caches[1].load(more)
+    for cache in caches:
+        cache.load(c)
+    for seed in range(4):
+        q.copy_(rows(g, n, d, "bf16", c))
+        torch.cuda.synchronize()
+        for graph in graphs:
+            graph.replay()
+            torch.cuda.synchronize()
+        for x, y in zip(*out):
+            assert torch.equal(x, y), seed
+        assert out[0][2].sum() > 0
+        for x, y in zip(caches[0].export(), caches[1].export()):
+            assert torch.equal(x, y), seed
+        caches[1].set_lookup_path(SKINNY)  # (the kernel with the same sums)
+        for x, y in zip(caches[0].lookup(few, THETA), caches[1].lookup(few, THETA)):
+            assert torch.equal(x, y), seed
