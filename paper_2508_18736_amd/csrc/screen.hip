@@ -1705,8 +1705,9 @@ int siso_bytes_few_room(siso_cache *c, long n) {
         --c->few_rest;
         return 0;
     }
-    if (!byte_room(c, c->count) || !few_lists_room(c)) return 0;
     ByteRows &b = c->bytes;
+    // (what siso_reserve was asked for does not allocate afterwards, with or without room)
+    if (n <= c->few_reserved ? b.rows < c->count || !c->few.best : !byte_room(c, c->count) || !few_lists_room(c)) return 0;
     // (single rows that an update could not bring up to date stay behind until then, 64 calls at most)
     const bool due = ++b.calls >= 64;
     if (b.behind > 0 || recording || due) {
@@ -1754,9 +1755,15 @@ void siso_screen_reserve(siso_cache *c, long n) {
     if (n > c->screen_reserved) c->screen_reserved = n;
 }
 
-void siso_bytes_few_reserve(siso_cache *c) {
+void siso_bytes_few_reserve(siso_cache *c, long n) {
+    siso_cache full = *c;
+    full.count = c->capacity < SISO_FEW_MOST_ROWS ? c->capacity : SISO_FEW_MOST_ROWS;
+    bool wanted = false;  // (by any batch of up to n: the rule asks for more rows from nine and from 33 queries on)
+    for (const long least : {1L, 9L, 33L}) wanted = wanted || (least <= n && siso_bytes_few_wanted(&full, least));
+    if (!wanted) return;
     c->bytes.refused = 0;
-    if (byte_room(c, c->capacity)) (void)few_lists_room(c);
+    if (byte_room(c, full.count)) (void)few_lists_room(c);
+    if (n > c->few_reserved) c->few_reserved = n;
 }
 
 int siso_screen_pairs_room(siso_cache *c, long rows) {

@@ -1796,7 +1796,7 @@ extern "C" int siso_reserve(siso_cache *c, long n) {
     if (c->dtype == SISO_FP8) return siso_fp8_ensure_batch(c, n);
     // (no room for the bytes of a screened lookup is no error: such lookups then go without)
     if (siso_screen_wanted(&full, n)) siso_screen_reserve(c, n);
-    if (siso_bytes_few_wanted(&full, n < SISO_FEW ? n : SISO_FEW)) siso_bytes_few_reserve(c);
+    siso_bytes_few_reserve(c, n);
     if (n > 256) return ensure_update_notes(c);
     return SISO_OK;
 }

@@ -162,6 +162,7 @@ struct siso_cache {
     FewLists few;  // room for them from few.best on, or NULL
     int *few_flooded;  // pinned: a workgroup found no room for its lists; such lookups are better off on the rows as they are stored:
     long few_rest, few_rests;  // as many more of them, and how many that were the last time
+    long few_reserved;  // batches that siso_reserve has made room for such lookups for, or tried to: they do not ask for any
     long screen_reserved;  // batches that siso_reserve has sized `screen` for, or tried to: their lookups leave it as it is
     int screen_recorded;  // a graph holds a screened lookup on `screen`: outgrown, it stays until the cache goes (screen_kept)
     std::vector<char *> *screen_kept;
@@ -655,7 +656,7 @@ int siso_bytes_few_launch(siso_cache *c, const void *queries, long n, const Byte
 // Is a lookup of n queries to go that way?  If so: room and bytes for it (may synchronise and allocate, not under capture); 0 = without.
 int siso_bytes_few_wanted(const siso_cache *c, long n);
 int siso_bytes_few_room(siso_cache *c, long n);
-void siso_bytes_few_reserve(siso_cache *c);
+void siso_bytes_few_reserve(siso_cache *c, long n);
 // The host's note that rows of the cache are about to be written by something that leaves the bytes behind (see ByteRows).
 inline void siso_bytes_behind(siso_cache *c, long rows) {
     c->bytes.behind = c->bytes.behind + rows < c->capacity ? c->bytes.behind + rows : c->capacity;

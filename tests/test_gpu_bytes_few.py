@@ -169,3 +169,34 @@ def test_rows_that_change(siso):
     got = a.lookup(q, THETA), b.lookup(q, THETA)  # (on two streams)
     torch.cuda.synchronize()
     same(*got, "behind the replays")
+
+
+def free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()  # (all but torch's own)
+
+
+@pytest.mark.parametrize("capacity,K,d,n,batches", [(100000, 90000, 768, 64, (1, 8)), (139999, 135000, 768, 64, (9, 32)), (280000, 275000, 256, 8, (1, 8)),
+                                                    (2097153, 260000, 256, 1000, (1, 64))])
+@pytest.mark.parametrize("refused", [False, True])
+def test_a_reservation_serves_every_smaller_batch(siso, capacity, K, d, n, batches, refused):
+    """Also the batches that go over the bytes from fewer rows on than the reserved one, a cache that holds fewer rows than it can, and a reservation
+    that found no room: none of them allocates."""
+    print(f"case: few over bytes, reserved capacity={capacity} n={n} refused={refused}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    cache = siso.SisoCache(d, capacity, siso.BF16)
+    c = torch.randn(K, d, device=DEV, generator=g).bfloat16()
+    cache.load(c)
+    assert all(cache.screened(b) for b in batches[:1])
+    if refused:
+        cache.set_option("screen_room", 1)
+    before = free()
+    cache.reserve(n)
+    assert (before - free() >= K * d) == (not refused)
+    cache.set_option("screen_room", 0)
+    before = free()
+    for b in batches:
+        q = queries(g, c, b)
+        for _ in range(6):
+            cache.lookup_update(q, THETA)
+    assert abs(before - free()) < 2 << 20  # (a reservation of the driver's)
