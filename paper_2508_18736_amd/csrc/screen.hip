@@ -1643,7 +1643,7 @@ bool siso_bytes_may_record(siso_cache *c) { return !capturing(c) || note_recorde
 // ---- few queries over the bytes (lookup_bytes.hip)
 static bool few_lists_room(siso_cache *c) {
     if (c->few.best) return true;
-    if (capturing(c)) return false;
+    if (capturing(c) || c->few_refused) return false;
     FewLists f;
     auto layout = [&](Carver a) {
         f.best = a.take<u64>(SISO_FEW);
@@ -1657,13 +1657,17 @@ static bool few_lists_room(siso_cache *c) {
     const size_t bytes = layout(Carver{nullptr});
     char *at = nullptr;
     int *flooded = nullptr;
-    if (!take(&at, bytes)) return false;
+    if ((c->opt_screen_room > 0 && bytes > (size_t)c->opt_screen_room << 10) || !take(&at, bytes)) {
+        c->few_refused = 1;
+        return false;
+    }
     bool ok = hipHostMalloc((void **)&flooded, sizeof(int), hipHostMallocDefault) == hipSuccess;
     ok = ok && hipMemsetAsync(at, 0, bytes, c->stream) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         if (flooded) (void)hipHostFree(flooded);
         (void)hipFree(at);
+        c->few_refused = 1;
         return false;
     }
     *flooded = 0;
@@ -1762,6 +1766,7 @@ void siso_bytes_few_reserve(siso_cache *c, long n) {
     for (const long least : {1L, 9L, 33L}) wanted = wanted || (least <= n && siso_bytes_few_wanted(&full, least));
     if (!wanted) return;
     c->bytes.refused = 0;
+    c->few_refused = 0;
     if (byte_room(c, full.count)) (void)few_lists_room(c);
     if (n > c->few_reserved) c->few_reserved = n;
 }
@@ -1776,6 +1781,7 @@ void siso_screen_done(siso_cache *c) {
     (void)hipFree(c->screen_pairs.at);
     c->screen_pairs = ScreenSpace{nullptr, 0, 0};
     c->screen.refused = c->bytes.refused = 0;
+    c->few_refused = 0;
 }
 
 void siso_screen_release(siso_cache *c) {

@@ -160,6 +160,7 @@ struct siso_cache {
     ScreenSpace screen, screen_pairs;
     ByteRows bytes;
     FewLists few;  // room for them from few.best on, or NULL
+    int few_refused;  // there was none: not asked for again until siso_reserve or a release
     int *few_flooded;  // pinned: a workgroup found no room for its lists; such lookups are better off on the rows as they are stored:
     long few_rest, few_rests;  // as many more of them, and how many that were the last time
     long few_reserved;  // batches that siso_reserve has made room for such lookups for, or tried to: they do not ask for any

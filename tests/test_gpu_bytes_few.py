@@ -200,3 +200,27 @@ def test_a_reservation_serves_every_smaller_batch(siso, capacity, K, d, n, batch
         for _ in range(6):
             cache.lookup_update(q, THETA)
     assert abs(before - free()) < 2 << 20  # (a reservation of the driver's)
+
+
+def test_lists_without_room_are_not_asked_for_again(siso):
+    """Room for the bytes (1 MiB) and none for the lists (1.7 MiB): the rows as they are stored, also when there would be room, until siso_reserve."""
+    print("case: few over bytes, no room for lists", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    c = mixture(g, 4096, 256)
+    a, b = pair(siso, c)
+    q = queries(g, c, 64)
+    want = b.lookup(q, THETA)
+    a.set_option("screen", 2)
+    a.reserve(64)  # (keys)
+    a.set_option("screen", 4)
+    a.set_option("screen_room", 1200)
+    before = free()
+    same(a.lookup(q, THETA), want, "no room")
+    with_bytes = free()
+    a.set_option("screen_room", 0)
+    for _ in range(3):
+        same(a.lookup(q, THETA), want, "not asked for again")
+    assert free() == with_bytes
+    a.reserve(64)
+    assert free() < with_bytes <= before
+    same(a.lookup(q, THETA), want, "room")
