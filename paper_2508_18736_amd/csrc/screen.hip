@@ -1593,22 +1593,42 @@ static bool byte_room(siso_cache *c, long rows) {
     ByteRows &b = c->bytes;
     if (rows <= b.rows) return true;
     if (capturing(c) || (b.refused != 0 && rows >= b.refused)) return false;
-    const size_t bytes = byte_store(nullptr, c, rows).bytes;
+    const size_t room = (size_t)c->opt_screen_room << 10;  // (0: as there is)
+    auto take_rows = [&](long count, size_t beside) {
+        const size_t bytes = byte_store(nullptr, c, count).bytes;
+        char *at = nullptr;
+        if ((room > 0 && bytes + beside > room) || !take(&at, bytes)) return (char *)nullptr;
+        if (hipMemsetAsync(at, 0, (size_t)up256(count) / 32 * sizeof(u64), c->stream) == hipSuccess) return at;
+        (void)hipGetLastError();
+        (void)hipFree(at);
+        return (char *)nullptr;
+    };
+    const long had = b.rows;
     char *larger = nullptr;
-    if ((c->opt_screen_room > 0 && bytes > (size_t)c->opt_screen_room << 10) || !take(&larger, bytes)) {
+    if (room == 0 || byte_store(nullptr, c, rows).bytes <= room) {
+        larger = take_rows(rows, b.at ? byte_store(nullptr, c, had).bytes : 0);
+        // (the old ones go: nothing but their recorded launches needs them)
+        if (b.at && larger && b.recorded) {
+            c->screen_kept->push_back(b.at);  // (room for it: note_recorded)
+        } else if (b.at && !b.recorded) {
+            if (hipStreamSynchronize(c->stream) != hipSuccess) {
+                (void)hipGetLastError();
+                if (larger) (void)hipFree(larger);
+                return false;
+            }
+            (void)hipFree(b.at);
+            if (!larger) {  // not beside them: perhaps in their place
+                larger = take_rows(rows, 0);
+                b.at = larger ? nullptr : take_rows(had, 0);
+                b.rows = b.at ? had : 0;
+                siso_bytes_all_behind(c);
+            }
+        }
+    }
+    if (!larger) {
         b.refused = rows;
         return false;
     }
-    // (the old ones go: nothing but their recorded launches needs them)
-    bool ok = hipMemsetAsync(larger, 0, (size_t)up256(rows) / 32 * sizeof(u64), c->stream) == hipSuccess;
-    if (ok && b.at && !b.recorded) ok = hipStreamSynchronize(c->stream) == hipSuccess;
-    if (!ok) {
-        (void)hipGetLastError();
-        (void)hipFree(larger);
-        return false;
-    }
-    if (b.at && b.recorded) c->screen_kept->push_back(b.at);  // (room for it: siso_screen_lookup)
-    else if (b.at) (void)hipFree(b.at);
     b.at = larger;
     b.rows = rows;
     b.recorded = 0;

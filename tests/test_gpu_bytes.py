@@ -192,3 +192,42 @@ def test_bytes_that_a_recorded_fold_writes_to_stay(siso, copy):
         caches[1].set_lookup_path(SKINNY)  # (the kernel with the same sums)
         for x, y in zip(caches[0].lookup(few, THETA), caches[1].lookup(few, THETA)):
             assert torch.equal(x, y), seed
+
+
+@pytest.mark.parametrize("room,grows", [(0, True), (55, True), (40, False)])
+def test_bytes_that_grow(siso, room, grows):
+    """Beside the bytes of before (10 MB), in their place where both do not fit, or not at all: then those of before serve as many rows as before."""
+    print(f"case: growing bytes, room={room}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(19)
+    d, K, capacity = 256, 40000, 200000
+    c = rows(g, capacity, d, "bf16", rows(g, 4000, d, "bf16"))
+    q = rows(g, 64, d, "bf16", c[:K])
+    caches = []
+    for screen in (4, 2):
+        caches.append(siso.SisoCache(d, capacity, siso.BF16))
+        caches[-1].set_option("screen", screen)
+        caches[-1].set_lookup_path(SKINNY)
+
+    def step(k, what):
+        for cache in caches:
+            cache.load(c[:k])
+        for _ in range(2):
+            for x, y in zip(caches[0].lookup_update(q, THETA), caches[1].lookup_update(q, THETA)):
+                assert torch.equal(x, y), what
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()  # (all but torch's own)
+
+    step(K, "few rows")
+    caches[1].reserve(64)
+    caches[0].set_option("screen", 2)
+    caches[0].reserve(64)  # (keys)
+    caches[0].set_option("screen", 4)
+    caches[0].set_option("screen_room", room << 10)
+    before = free()
+    step(capacity, "all rows")
+    more = before - free()
+    assert 36 << 20 < more < 45 << 20 if grows else abs(more) < 4 << 20
+    step(K, "few rows again")
+    assert abs(before - more - free()) < 4 << 20
