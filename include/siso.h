@@ -263,7 +263,10 @@ int siso_update_hits(siso_cache *c, const void *queries, const int *idx, const u
  * and is counted by siso_bad_indices.  On a GPU of its own all workgroups are resident
  * together and none has been seen to; a kernel of another stream that fills the GPU for
  * longer than that can bring it about, on a cache of any type: siso_lookup and
- * siso_update_hits, the two calls, wait for nothing.  Other batches run the two calls.  Asynchronous;
+ * siso_update_hits, the two calls, wait for nothing.  Steps of up to 64 queries that go over
+ * the rows' bytes (see siso_lookup) need 47 to 146 KB of LDS for each query while they wait, a
+ * compute unit each from 512 dimensions on: there a kernel that holds most units' LDS is enough, and
+ * where the stream may not use as many units (a partition, a mask) the step runs as the two calls.  Other batches run the two calls.  Asynchronous;
  * allocates what siso_lookup and siso_update_hits would (siso_reserve avoids that).
  */
 int siso_lookup_update(siso_cache *c, const void *queries, long n, float threshold, int *out_idx, float *out_sim,

@@ -38,6 +38,8 @@ int siso_set_lookup_path(siso_cache *c, int path);
  *   "mfma_qblock"     0 = default; 1, 2, 4, 8, 16, 32 = query tiles that share an XCD's centroid tiles
  *   "fold_spin_limit" -1 = default; >= 0: how often a workgroup of siso_lookup_update's one-kernel end looks at the
  *                     board before it gives up (0: at once - for tests of that path)
+ *   "fold_units"      0 = default; > 0: compute units that all workgroups of such an end over bytes have to fit on at once, else the
+ *                     lookup and the update are two calls (by default as many as the stream may use)
  *   "stream_hint"     0 = default (the centroid loads of a lookup are marked non-temporal when the batch is one
  *                     tile of queries and the centroids exceed 288 MiB, or, four-wave kernel, when they exceed
  *                     288 MiB); 1 = always, 2 = never

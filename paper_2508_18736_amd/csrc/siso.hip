@@ -718,6 +718,7 @@ __device__ __forceinline__ u64 listed_product(const bf16_t *__restrict__ cent, c
 // a pad of 16 bytes behind each, and a wave for 32 of them multiplies.
 #define LISTED_FEW 64
 #define LISTED_LDS(d) (LISTED_FEW * (2 * (d) + 16))
+#define LISTED_STATIC (14 * 1024)  // and what else the kernel keeps there, 13,952 bytes
 __device__ __forceinline__ u64 listed_products_few(const bf16_t *__restrict__ cent, const float *__restrict__ invn, const int *sh_rows, int many,
                                                const u32x4_t *sh_q, int d, unsigned char *room) {
     constexpr int AHEAD = 4;
@@ -1632,6 +1633,7 @@ extern "C" void siso_destroy(siso_cache *c) {
 extern "C" int siso_set_stream(siso_cache *c, void *hip_stream) {
     if (!c) return SISO_EINVAL;
     c->stream = (hipStream_t)hip_stream;
+    c->units = 0;
     return SISO_OK;
 }
 
@@ -1657,6 +1659,7 @@ extern "C" int siso_set_option(siso_cache *c, const char *name, long value) {
     else if (!strcmp(name, "screen_room")) c->opt_screen_room = (int)value;
     else if (!strcmp(name, "mfma_qblock")) c->opt_mfma_qblock = (int)value;
     else if (!strcmp(name, "fold_spin_limit")) c->opt_fold_spin_limit = (int)value;
+    else if (!strcmp(name, "fold_units")) c->opt_fold_units = (int)value;
     else if (!strcmp(name, "topk_room")) c->opt_topk_room = (int)value;
     else if (!strcmp(name, "stream_hint") && value <= 2) c->opt_stream_hint = (int)value;
     else if (!strcmp(name, "second_set")) return value ? siso_second_set(c) : SISO_OK;
@@ -1943,10 +1946,28 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
     return siso_check_hip(c, hipGetLastError(), "k_lookup_finalize");
 }
 
-// Few queries over the bytes of the rows: two kernels, the second of which folds the hits if the caller is about to.
+// Compute units that the cache's stream may use: of a partitioned chip, or of a stream with a mask, fewer than 256.
+static int stream_units(siso_cache *c) {
+    if (c->units > 0) return c->units;
+    int units = 0;
+    if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) units = 0;
+    unsigned mask[16] = {0};
+    int masked = 0;
+    if (hipExtStreamGetCUMask(c->stream, 16, mask) == hipSuccess)
+        for (const unsigned m : mask) masked += __builtin_popcount(m);
+    (void)hipGetLastError();
+    if (masked > 0 && masked < units) units = masked;
+    c->units = units > 0 ? units : 1;
+    return c->units;
+}
+
+// Few queries over the bytes of the rows: two kernels, the second of which folds the hits if the caller is about to.  Its workgroups wait for
+// each other, so it does that only where all of them fit on the chip at once, with the LDS that the gathered rows take (up to 146 KB: a compute
+// unit each); otherwise the caller's update does.
 static int few_lookup(siso_cache *c, const void *queries, long n, float theta, int count_index, int *out_idx, float *out_sim,
                       unsigned char *out_hit, int *folded) {
-    const bool fold = folded && out_hit;
+    const int units = c->opt_fold_units > 0 ? c->opt_fold_units : stream_units(c);
+    const bool fold = folded && out_hit && n <= (long)units * ((160 * 1024) / (LISTED_LDS(c->dim) + LISTED_STATIC));
     const ByteView bytes = siso_byte_view(c);
     c->board_to_clear = fold ? c->counters + 4 : nullptr;
     siso_prof_begin(c);

@@ -176,6 +176,8 @@ struct siso_cache {
     int opt_merge_config;
     int opt_mfma_qblock;
     int opt_fold_spin_limit;  // -1 = default
+    int opt_fold_units;
+    int units;  // compute units that `stream` may use, 0 = not asked yet
     int opt_topk_room;        // KiB that topk_groups may take
     int opt_stream_hint;      // 0 = default; 1 = mark the centroid loads of the eight-wave lookups as streaming, 2 = never
 

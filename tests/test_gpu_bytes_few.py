@@ -224,3 +224,46 @@ def test_lists_without_room_are_not_asked_for_again(siso):
     a.reserve(64)
     assert free() < with_bytes <= before
     same(a.lookup(q, THETA), want, "room")
+
+
+@pytest.mark.parametrize("d,n,units,folds", [(1024, 64, 63, False), (1024, 64, 64, True), (768, 3, 2, False), (256, 64, 21, False), (256, 64, 22, True), (768, 64, 0, True)])
+def test_workgroups_that_do_not_fit_together_do_not_wait_for_each_other(siso, d, n, units, folds):
+    """With a limit of zero looks at the board a fold gives up on every hit; the two calls wait for nothing."""
+    print(f"case: few over bytes on {units} units, d={d} n={n}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(d)
+    c = mixture(g, 5000, d)
+    a, b = pair(siso, c)
+    a.set_option("fold_units", units)
+    a.set_option("fold_spin_limit", 0)
+    q = queries(g, c, n)
+    before = a.export()
+    got, want = a.lookup_update(q, THETA), b.lookup_update(q, THETA)
+    same(got, want, "step")
+    hits = int(want[2].sum().item())
+    assert hits > 0 and a.bad_indices() == (hits if folds else 0)
+    same(a.export(), before if folds else b.export(), "state")
+    if not folds:
+        same(a.lookup_update(q, THETA), b.lookup_update(q, THETA), "step behind it")
+        same(a.export(), b.export(), "state behind it")
+
+
+def test_the_units_of_a_stream_are_asked_for_under_capture(siso):
+    print("case: few over bytes, stream set under capture", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(12)
+    c = mixture(g, 5000, 512)
+    a, b = pair(siso, c)
+    q = queries(g, c, 64)
+    for cache in (a, b):
+        cache.lookup(q, THETA)
+    out = [torch.empty(64, dtype=t, device=DEV) for t in (torch.int32, torch.float32, torch.uint8)]
+    main, graph = torch.cuda.current_stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        a.set_stream(torch.cuda.current_stream())
+        a.lookup_update(q, THETA, *out)
+    a.set_stream(main)
+    for seed in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        same(out, b.lookup_update(q, THETA), f"replay {seed}")
+    same(a.export(), b.export(), "state")
