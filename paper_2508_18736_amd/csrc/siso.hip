@@ -768,17 +768,22 @@ __device__ __forceinline__ u64 listed_products_few(const bf16_t *__restrict__ ce
     return listed_key(acc, w, row);
 }
 
-// BYTES: the bytes of the rows that are rewritten follow.  (Types of their own, not conditions: arguments and code that are not needed cost 1 % of a
-// small step.)
-struct FoldPlain {
-    static constexpr bool LISTED = false, BYTES = false;
+// What the kernel does beside that, as types and not as conditions: arguments, loads and code that are not needed cost 1 to 2 % of a small step.
+struct FoldPlain {  // nobody asks about changed rows (no bytes have been made, and no graph records the launch)
+    static constexpr bool LISTED = false, BYTES = false, COUNTED = false;
 };
-struct FoldBytes {
-    static constexpr bool LISTED = false, BYTES = true;
+struct FoldCounted {  // the counts of the rows that are rewritten change (see ByteRows)
+    static constexpr bool LISTED = false, BYTES = false, COUNTED = true;
+    unsigned *version;
+};
+struct FoldBytes {  // and their bytes follow
+    static constexpr bool LISTED = false, BYTES = true, COUNTED = true;
+    unsigned *version;
     ByteView bytes;
 };
 struct FoldListed {
-    static constexpr bool LISTED = true, BYTES = true;
+    static constexpr bool LISTED = true, BYTES = true, COUNTED = true;
+    unsigned *version;
     ByteView bytes;
     FewLists few;
     int fold;  // 0 = a lookup and nothing else
@@ -787,11 +792,11 @@ template <typename T, int UPD_MAXE_T, class More>
 __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q, const u64 *__restrict__ keys, long n, long K,
                                                           int d, int slices, float theta, int vec, int *out_idx,
                                                           float *out_sim, unsigned char *out_hit, unsigned *access, T *cent,
-                                                          float *mean, int *size, float *invn, unsigned *version, u64 *board,
+                                                          float *mean, int *size, float *invn, u64 *board,
                                                           int spin_limit, u64 *gave_up, const float *__restrict__ q_inv,
                                                           unsigned char *copy_codes, float *copy_scale, float *copy_inv,
                                                           int *copy_size, More more) {
-    constexpr bool LISTED = More::LISTED, BYTES = More::BYTES;
+    constexpr bool LISTED = More::LISTED, BYTES = More::BYTES, COUNTED = More::COUNTED;
     constexpr int EPC = 16 / (int)sizeof(T);
     __shared__ float sh[4];
     __shared__ float sh_f[4];
@@ -999,7 +1004,7 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     if (t == 0) {
         out_idx[me] = (int)best_i;
         out_sim[me] = best_s;
-        if (out_hit) out_hit[me] = hit ? 1 : 0;
+        if (!LISTED || out_hit) out_hit[me] = hit ? 1 : 0;  // (a lookup alone may do without)
         if (hit && access && access[best_i] != SISO_ACCESS_INF) atomicAdd(&access[best_i], 1u);
         __hip_atomic_store(board + me, board_entry(hit, (int)best_i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -1019,7 +1024,8 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     if constexpr (BYTES) block = more.bytes.meta[k >> 5];
     // (without bytes to keep step with, that the count changes is all that is asked of it: a store, where 256 additions to the one line of a small
     // cache's counts are 2 us)
-    const unsigned counted = BYTES || !version ? 0u : version[k >> 5];
+    unsigned counted = 0;
+    if constexpr (COUNTED && !BYTES) counted = more.version[k >> 5];
 #pragma unroll
     for (int e = 0; e < UPD_MAXE_T; ++e) {
         x_me[e] = t + e * 256 < d ? widen(xr[e]) : 0.f;
@@ -1064,8 +1070,8 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
     __syncthreads();
     if (list[0] != (int)me) return;  // an earlier member leads this centroid (uniform over the block)
     if (t == 0) {
-        if constexpr (BYTES) raise_version(version, k);
-        else if (version) version[k >> 5] = counted + 1;
+        if constexpr (BYTES) raise_version(more.version, k);
+        else if constexpr (COUNTED) more.version[k >> 5] = counted + 1;
     }
     int members = fold_member<UPD_MAXE_T>(x_me, acc, sh) ? 1 : 0;
     members += fold_list<T, UPD_MAXE_T, UPD_MAXE_T <= 4 ? 4 : 2, false, false>(list, 1, all, Q, d, acc, sums);
@@ -1903,26 +1909,30 @@ static int plain_lookup(siso_cache *c, const PlainLookup &plan, const void *quer
     if (board_emptied && row_keys == SISO_KEY_ROWS) {
         const siso_cache *ms = c->fold_master;  // the bf16 cache behind an 8-bit copy, or NULL
         siso_cache *tgt = ms ? const_cast<siso_cache *>(ms) : c;
-        // (bytes of rows of up to 1,024 elements, if they are current, or nearly so: otherwise they are left behind)
-        ByteView bytes = tgt->bytes.behind == 0 ? siso_byte_view(tgt) : ByteView{nullptr, nullptr, nullptr, 0};
+        // Bytes (rows of up to 1,024 elements) follow where small lookups go over them, if they are current, or nearly so.  Otherwise they are left behind, as
+        // those of fp32 rows are: the screened lookups that these serve write changed rows anew in any case, and to follow takes 2 to 3 % of a step (of 64
+        // queries against 60,000 x 384 41.3 us without bytes, 41.6 so, 42.2 following).
+        ByteView bytes = tgt->dtype == SISO_BF16 && tgt->bytes.behind == 0 ? siso_byte_view(tgt) : ByteView{nullptr, nullptr, nullptr, 0};
         if (bytes.codes && !siso_bytes_may_record(tgt)) bytes.codes = nullptr;
+        unsigned *const version = c->dim <= SISO_SCREEN_DIM ? siso_counted(tgt) : nullptr;
         // the end of the lookup and the update of its hits as one kernel (see k_finalize_update)
         // polls of the board (a microsecond or two each) before a block gives up
         const int spin_limit = c->opt_fold_spin_limit >= 0 ? c->opt_fold_spin_limit : 1 << 18;
 #define SISO_LAUNCH_FOLD(T, E, MORE, ...)                                                                                 \
     hipLaunchKernelGGL((k_finalize_update<T, E, MORE>), dim3(qblocks), dim3(256), 0, c->stream, (const T *)queries, keys, n, c->count, \
                        c->dim, slices, tl.v[0], vec, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr, \
-                       (T *)tgt->cent, tgt->mean, tgt->size, tgt->invn, siso_counted(tgt), c->counters + 4, spin_limit, c->counters, \
+                       (T *)tgt->cent, tgt->mean, tgt->size, tgt->invn, c->counters + 4, spin_limit, c->counters,         \
                        ms ? (const float *)c->fp8_qinv : (const float *)nullptr, ms ? (unsigned char *)c->cent : nullptr, \
                        ms ? c->scale : nullptr, ms ? c->invn : nullptr, ms ? c->size : nullptr, MORE{__VA_ARGS__})
         if (tgt->dtype == SISO_F32) {
-            if (bytes.codes) SISO_LAUNCH_FOLD(float, 4, FoldBytes, bytes);
-            else if (c->dim <= 1024) SISO_LAUNCH_FOLD(float, 4, FoldPlain);
-            else SISO_LAUNCH_FOLD(float, 16, FoldPlain);
+            if (c->dim > 1024) SISO_LAUNCH_FOLD(float, 16, FoldPlain);
+            else if (version) SISO_LAUNCH_FOLD(float, 4, FoldCounted, version);
+            else SISO_LAUNCH_FOLD(float, 4, FoldPlain);
         } else {
-            if (bytes.codes) SISO_LAUNCH_FOLD(bf16_t, 4, FoldBytes, bytes);
-            else if (c->dim <= 1024) SISO_LAUNCH_FOLD(bf16_t, 4, FoldPlain);
-            else SISO_LAUNCH_FOLD(bf16_t, 16, FoldPlain);
+            if (c->dim > 1024) SISO_LAUNCH_FOLD(bf16_t, 16, FoldPlain);
+            else if (bytes.codes) SISO_LAUNCH_FOLD(bf16_t, 4, FoldBytes, tgt->version, bytes);
+            else if (version) SISO_LAUNCH_FOLD(bf16_t, 4, FoldCounted, version);
+            else SISO_LAUNCH_FOLD(bf16_t, 4, FoldPlain);
         }
 #undef SISO_LAUNCH_FOLD
         HIP_TRY(c, hipGetLastError());
@@ -1982,9 +1992,9 @@ static int few_lookup(siso_cache *c, const void *queries, long n, float theta, i
     }
     hipLaunchKernelGGL((k_finalize_update<bf16_t, 4, FoldListed>), dim3((unsigned)n), dim3(256), LISTED_LDS(c->dim), c->stream, (const bf16_t *)queries, (const u64 *)nullptr, n,
                        c->count, c->dim, siso_bytes_few_workgroups(c), theta, 1, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr,
-                       (bf16_t *)c->cent, c->mean, c->size, c->invn, c->version, c->counters + 4,
+                       (bf16_t *)c->cent, c->mean, c->size, c->invn, c->counters + 4,
                        c->opt_fold_spin_limit >= 0 ? c->opt_fold_spin_limit : 1 << 18, c->counters, (const float *)nullptr, (unsigned char *)nullptr,
-                       (float *)nullptr, (float *)nullptr, (int *)nullptr, FoldListed{bytes, c->few, fold ? 1 : 0});
+                       (float *)nullptr, (float *)nullptr, (int *)nullptr, FoldListed{c->version, bytes, c->few, fold ? 1 : 0});
     if (fold) *folded = 1;
     return siso_check_hip(c, hipGetLastError(), "k_finalize_update");
 }

@@ -231,3 +231,55 @@ def test_bytes_that_grow(siso, room, grows):
     assert 36 << 20 < more < 45 << 20 if grows else abs(more) < 4 << 20
     step(K, "few rows again")
     assert abs(before - more - free()) < 4 << 20
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16", "copy"])
+@pytest.mark.parametrize("d", [256, 384, 1024])
+def test_small_folds_over_rows_with_bytes(siso, kind, d):
+    """Steps whose lookup goes over the stored rows, on a cache that has bytes: current ones (which follow, if they are bf16), ones that an update has left
+    behind, and none yet.  Later lookups over the bytes name what they name on a fresh cache."""
+    print(f"case: small folds, {kind} d={d}", flush=True)
+    dtype = "f32" if kind == "f32" else "bf16"
+    g = torch.Generator(device=DEV).manual_seed(d + 1)
+    K = 6000
+    c = rows(g, K, d, dtype, rows(g, 600, d, dtype))
+    cache, twin = make(siso, K, d, dtype), make(siso, K, d, dtype)
+    copies = [siso.SisoCache(d, K, siso.FP8) if kind == "copy" else None for _ in range(2)]
+    for x, y in zip((cache, twin), copies):
+        x.load(c)
+        if y is not None:
+            y.load(c)
+    big = torch.cat([rows(g, 400, d, dtype, c), rows(g, 100, d, dtype)])
+
+    def step(x, y, q):
+        return x.lookup_update(q, 0.5) if y is None else y.lookup_update_with(x, q, 0.5)
+
+    def small(what):
+        for n in (1, 64, 128, 200 if kind == "f32" else 100, 7):
+            q = rows(g, n, d, dtype, c)
+            q[::5, 7] += 3 * q[::5].float().norm(dim=1).to(q.dtype)  # (rows whose largest element outgrows the scale of their bytes)
+            cache.set_option("screen", 2)
+            twin.set_option("screen", 2)
+            for a, b in zip(step(cache, copies[0], q), step(twin, copies[1], q)):
+                assert torch.equal(a, b), (what, n)
+            cache.set_option("screen", 1)
+            as_fresh(siso, cache, d, dtype, big, f"{what}, {n}")
+            if dtype == "bf16":
+                cache.set_option("screen", 4)
+                cache.lookup(big[:64], THETA)
+                cache.set_option("screen", 1)
+        for a, b in zip(cache.export(), twin.export()):
+            assert torch.equal(a, b), what
+
+    for n in (1, 100):  # (no bytes yet)
+        for x, y in zip((cache, twin), copies):
+            x.set_option("screen", 2)
+            step(x, y, big[:n])
+    cache.set_option("screen", 1)
+    cache.lookup(big, THETA)
+    small("current")
+    idx, q = torch.randint(0, K, (50,), device=DEV, generator=g, dtype=torch.int32), rows(g, 50, d, dtype)
+    for x in (cache, twin):
+        x.update(q, idx)
+    for _ in range(2):
+        small("behind an update")
