@@ -287,26 +287,40 @@ __global__ __launch_bounds__(FEW_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
         have = more;
     }
     few_barrier();
+    // Places in a query's list are asked for once by a workgroup, for all of its rows that its slots have no room for.  (Asked for row by row, they were
+    // additions to 64 words by everyone: 4.3 ms of a lookup of 32 queries against 131,072 x 768 rows with a mean cosine of 0.8.)
     const int collected = flags[0];
+    int *place_s = (int *)scale_s, *far_s = (int *)err_s;  // (both are in registers)
+    if (t < 64) far_s[t] = 0;
     if (collected > STAGE) {
         if (t == 0) flags[2] = 1;
     } else {
         for (int i = t; i < collected; i += FEW_WAVES * 64) {
             const unsigned e = stage[i], q = e >> 26;
-            if (few_upper(e) < unordered_bits(low_s[q])) continue;
-            const int slot = 2 + atomicAdd(cnt_s + q, 1);
-            if (slot < SLOTS) {
-                slot_s[q * SLOTS + slot] = e;
-            } else {
-                const int far = atomicAdd(lists.cnt + q, 1);
-                if (far < SISO_FEW_LIST) lists.rows[(size_t)q * SISO_FEW_LIST + far] = make_uint2(few_row(e, blockIdx.x, gridDim.x), e);
-                else flags[2] = 1;
-            }
+            const bool reaches = few_upper(e) >= unordered_bits(low_s[q]);
+            const int slot = reaches ? 2 + atomicAdd(cnt_s + q, 1) : 0;
+            if (reaches && slot < SLOTS) slot_s[q * SLOTS + slot] = e;
+            if (!reaches || slot < SLOTS) stage[i] = 0;  // (an upper end is never 0)
+        }
+        few_barrier();
+        const int far = t < n ? cnt_s[t] - (SLOTS - 2) : 0;
+        if (far > 0) {
+            place_s[t] = atomicAdd(lists.cnt + t, far);
+            if (place_s[t] + far > SISO_FEW_LIST) flags[2] = 1;
+        }
+        few_barrier();
+        for (int i = t; i < collected; i += FEW_WAVES * 64) {
+            const unsigned e = stage[i], q = e >> 26;
+            if (e == 0) continue;
+            const int at = place_s[q] + atomicAdd(far_s + q, 1);
+            if (at < SISO_FEW_LIST) lists.rows[(size_t)q * SISO_FEW_LIST + at] = make_uint2(few_row(e, blockIdx.x, gridDim.x), e);
         }
     }
     __syncthreads();
-    for (int i = t; i < n * SLOTS; i += FEW_WAVES * 64) lists.slots[((size_t)(i / SLOTS) * gridDim.x + blockIdx.x) * SLOTS + i % SLOTS] = i % SLOTS == 0 ? low_s[i / SLOTS] : i % SLOTS == 1 ? (unsigned)cnt_s[i / SLOTS] : slot_s[i];
-    if (flags[2] != 0) {
+    const bool flood = flags[2] != 0;  // (then all its rows are multiplied below, and it names none)
+    for (int i = t; i < n * SLOTS; i += FEW_WAVES * 64)
+        lists.slots[((size_t)(i / SLOTS) * gridDim.x + blockIdx.x) * SLOTS + i % SLOTS] = i % SLOTS == 0 ? low_s[i / SLOTS] : i % SLOTS == 1 ? (flood ? 0u : (unsigned)cnt_s[i / SLOTS]) : slot_s[i];
+    if (flood) {
         as_stored = ~0u;
         if (t == 0 && flooded) __hip_atomic_store(flooded, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }

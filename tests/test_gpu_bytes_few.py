@@ -267,3 +267,16 @@ def test_the_units_of_a_stream_are_asked_for_under_capture(siso):
         torch.cuda.synchronize()
         same(out, b.lookup_update(q, THETA), f"replay {seed}")
     same(a.export(), b.export(), "state")
+
+
+@pytest.mark.parametrize("K,d,common,n", [(131072, 768, 0.8, 32), (140001, 768, 0.6, 64), (64000, 1024, 0.8, 8), (64000, 1024, 0.6, 8), (100000, 256, 0.9, 33), (262144, 384, 0.8, 1)])
+def test_rows_that_fill_the_lists_in_part(siso, K, d, common, n):
+    """Some workgroups find places in a query's list, others do not and multiply their rows as they are stored, in turn over several calls."""
+    print(f"case: few over bytes, lists that fill K={K} d={d} n={n}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(K + d)
+    c = mixture(g, K, d, common)
+    a, b = pair(siso, c)
+    for seed in range(4):
+        q = queries(g, c, n, common)
+        same(a.lookup_update(q, THETA), b.lookup_update(q, THETA), f"step {seed}")
+    same(a.export(), b.export(), "state")
