@@ -1718,6 +1718,10 @@ int siso_bytes_few_wanted(const siso_cache *c, long n) {
 
 int siso_bytes_few_room(siso_cache *c, long n) {
     const bool forced = c->opt_screen == 4, recording = capturing(c);
+    // A graph holds one way for good: over the bytes every replay would write changed rows as bytes (8 to 18 us), and could not turn back on rows that lists
+    // flood on (3 to 13 times the time).  Replays of a step of 64 against 262,144 x 768 75 us as they are stored, 66 over the bytes; of 64 against 140,001 x 1,024
+    // 60 and 74, of eight against 64,000 x 1,024 33 and 39.
+    if (recording && !forced) return 0;
     // Lists that found no room, of some call since the last one that was looked at: the next 64 lookups go over the rows as they are stored,
     // twice as many whenever that is seen again.  (Rows that lists flood on give the same results at one and a half to twice the time.)
     if (!forced && c->few_flooded && *(volatile int *)c->few_flooded != 0) {
@@ -1736,7 +1740,7 @@ int siso_bytes_few_room(siso_cache *c, long n) {
     const bool due = ++b.calls >= 64;
     if (b.behind > 0 || recording || due) {
         // Rows that have changed are written as bytes once lookups have read as much for want of that: a lookup over the bytes reads one byte an
-        // element less, and to write them takes three.  (A graph may be replayed behind any change, and records it always.)
+        // element less, and to write them takes three.  (A graph, where it is told to go this way, may be replayed behind any change, and records it always.)
         const double elements = (double)c->count * c->dim, blocks = (double)b.behind * 32 < (double)c->count ? (double)b.behind * 32 * c->dim : elements;
         if (!forced && !recording && b.behind > 0) {
             b.forgone += elements;

@@ -280,3 +280,52 @@ def test_rows_that_fill_the_lists_in_part(siso, K, d, common, n):
         q = queries(g, c, n, common)
         same(a.lookup_update(q, THETA), b.lookup_update(q, THETA), f"step {seed}")
     same(a.export(), b.export(), "state")
+
+
+def took(f, reps):
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(3):
+        a.record()
+        for _ in range(reps):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def test_a_recorded_step_goes_over_the_stored_rows(siso):
+    """A graph cannot turn back once its lists flood: recorded on rows without a common direction and replayed on rows with one, it takes the time of the rows as
+    they are stored (over the bytes five times that; the line is far above what machines and runs differ by), with the same results."""
+    print("case: few over bytes, recorded by default", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(21)
+    K, d, n = 140001, 768, 64
+    c, crowded = mixture(g, K, d), mixture(g, K, d, 0.8)
+    q, main = queries(g, c, n), torch.cuda.current_stream()
+    times, out = [], []
+    for screen in (0, 2):
+        cache = siso.SisoCache(d, K, siso.BF16)
+        cache.set_option("screen", screen)
+        cache.load(c)
+        assert cache.screened(n) == (screen == 0)
+        for _ in range(6):
+            cache.lookup_update(q, THETA)
+        out.append([torch.empty(n, dtype=t, device=DEV) for t in (torch.int32, torch.float32, torch.uint8)])
+        torch.cuda.synchronize()
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        cache.set_stream(side)
+        with torch.cuda.graph(graph, stream=side):
+            cache.lookup_update(q, THETA, *out[-1])
+        cache.set_stream(main)
+        cache.load(crowded)
+        p = queries(torch.Generator(device=DEV).manual_seed(22), crowded, n, 0.8)
+        q.copy_(p)
+        torch.cuda.synchronize()
+        times.append(took(graph.replay, 20))
+        q.copy_(queries(torch.Generator(device=DEV).manual_seed(23), crowded, n, 0.8))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+    same(out[0], out[1], "replays")
+    assert times[0] < 2 * times[1], times
