@@ -1448,10 +1448,7 @@ int screen_launch(siso_cache *c, const T *queries, long n, bool with_rows, bool 
     ScreenTiles which = {with_rows && whole && ahead > 0 && n <= 8192 ? 1 : 0, (int)ahead, (int)some, some > 0 ? (int)(tiles / some) : 1};
     int rc = write_bytes<T>(c, r, s, version, cent, c->invn, c->count, with_rows, queries, n, which, most_lost, least);
     if (rc != SISO_OK) return rc;
-    if (with_rows && which.part == 0 && !capturing(c)) {
-        c->bytes.behind = 0;
-        c->bytes.forgone = 0;
-    }
+    if (with_rows && which.part == 0 && !capturing(c)) siso_bytes_current(c);
     if (some > 0) {
         hipLaunchKernelGGL(k_screen_lookup<true>, dim3((unsigned)(some * nqt)), dim3(ByteCfg::NT), SCREEN_LDS, c->stream, r.qcodes, s.codes,
                            s.meta, r.qm, r.low, r.seed, r.cnt, r.near, r.largest, r.list, 0L, c->count, dp, 1, (int)some, (int)nqt, 1, which.stride,
@@ -1736,30 +1733,31 @@ int siso_bytes_few_room(siso_cache *c, long n) {
     ByteRows &b = c->bytes;
     // (what siso_reserve was asked for does not allocate afterwards, with or without room)
     if (n <= c->few_reserved ? b.rows < c->count || !c->few.best : !byte_room(c, c->count) || !few_lists_room(c)) return 0;
-    // (single rows that an update could not bring up to date stay behind until then, 64 calls at most)
-    const bool due = ++b.calls >= 64;
-    if (b.behind > 0 || recording || due) {
+    if (b.behind > 0 || recording || b.served >= 64) {  // (single rows that a fold could not bring up to date stay behind for 64 lookups at most)
         // Rows that have changed are written as bytes once lookups have read as much for want of that: a lookup over the bytes reads one byte an
-        // element less, and to write them takes three.  (A graph, where it is told to go this way, may be replayed behind any change, and records it always.)
+        // element less, and to write them takes three, and 8 to 18 us however few they are.  So if fewer than 16 lookups went over what was written
+        // last (an update behind each, say), twice as many go over the stored rows before the next time: a lookup and its update, 64 queries against
+        // 262,144 x 768 as they are stored 73 us, with the bytes written each time 76; against 140,001 x 1,024 57 and 82.
+        // (A graph, where it is told to go this way, may be replayed behind any change, and records it always.)
         const double elements = (double)c->count * c->dim, blocks = (double)b.behind * 32 < (double)c->count ? (double)b.behind * 32 * c->dim : elements;
         if (!forced && !recording && b.behind > 0) {
             b.forgone += elements;
-            if (b.forgone < 2 * blocks) return 0;
+            ++b.waited;
+            if (b.forgone < 2 * blocks || b.waited < b.wait) return 0;
         }
         if (recording && note_recorded(c, false) != SISO_OK) return 0;
         const ScreenRoom none = screen_room(nullptr, c, c->count, 0);
         const ByteStore s = byte_store(b.at, c, b.rows);
-        const int rc = c->dtype == SISO_F32 ? write_bytes<float>(c, none, s, c->version, (const float *)c->cent, c->invn, c->count, true, (const float *)c->cent, 0,
-                                                                 ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f)
-                                            : write_bytes<bf16_t>(c, none, s, c->version, (const bf16_t *)c->cent, c->invn, c->count, true, (const bf16_t *)c->cent, 0,
-                                                                  ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f);
+        const int rc = write_bytes<bf16_t>(c, none, s, c->version, (const bf16_t *)c->cent, c->invn, c->count, true, (const bf16_t *)c->cent, 0,
+                                           ScreenTiles{0, 0, 0, 1}, SCREEN_WHOLE, 0.f);
         if (rc != SISO_OK) return 0;
         if (!recording) {
-            b.behind = 0;
-            b.forgone = 0;
-            b.calls = 0;
+            b.wait = b.served >= 16 ? 0 : b.wait == 0 ? 8 : b.wait < 512 ? 2 * b.wait : b.wait;
+            b.served = 0;
+            siso_bytes_current(c);
         }
     }
+    ++b.served;
     return 1;
 }
 

@@ -57,11 +57,13 @@ struct ByteRows {
     long refused;  // the smallest number of rows that found no room (0 = none): not asked for again until siso_reserve or a release
     int recorded;  // a graph refers to them: outgrown, they stay until the cache goes (screen_kept)
     // How many rows may have changed since all bytes were current (an estimate of the host's, that only the choice of a route goes
-    // by), and how many elements lookups have read as they are stored that would have gone over the bytes.
+    // by), how many elements small lookups have read as they are stored since then that would have gone over the bytes, and how many of
+    // them there were, and have to be before the bytes are written for the next.
     long behind;
     double forgone;
+    int waited, wait;
     int written;  // some bytes have been made, or are by a recorded launch
-    int calls;  // lookups over them since they were written
+    int served;  // small lookups over them since they were written for one
 };
 
 // A lookup of few queries over the bytes (lookup_bytes.hip, k_finalize_update), per query; best and cnt are left as they were found, all zeros.
@@ -664,9 +666,16 @@ void siso_bytes_few_reserve(siso_cache *c, long n);
 inline void siso_bytes_behind(siso_cache *c, long rows) {
     c->bytes.behind = c->bytes.behind + rows < c->capacity ? c->bytes.behind + rows : c->capacity;
 }
-inline void siso_bytes_all_behind(siso_cache *c) {
-    c->bytes.behind = c->capacity;
+inline void siso_bytes_current(siso_cache *c) {
+    c->bytes.behind = 0;
     c->bytes.forgone = 0;
+    c->bytes.waited = 0;
+}
+inline void siso_bytes_all_behind(siso_cache *c) {
+    siso_bytes_current(c);
+    c->bytes.behind = c->capacity;
+    c->bytes.wait = 0;
+    c->bytes.served = 16;  // (what was written has served its time)
     c->few_rest = c->few_rests = 0;  // (other rows: perhaps no flood)
 }
 ByteView siso_byte_view(const siso_cache *c);

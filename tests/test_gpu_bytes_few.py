@@ -329,3 +329,51 @@ def test_a_recorded_step_goes_over_the_stored_rows(siso):
         torch.cuda.synchronize()
     same(out[0], out[1], "replays")
     assert times[0] < 2 * times[1], times
+
+
+def kernel_us(cache, f, reps):
+    """Time of the kernel that reads the rows, over the bytes about half of what it takes over the stored ones."""
+    cache.profile_enable(1)
+    for _ in range(reps):
+        f()
+    ms, times = cache.profile_read()
+    cache.profile_enable(0)
+    return ms / times * 1e3
+
+
+def test_which_way_lookups_go_by_default(siso):
+    """Steps that fold their hits go over the bytes from the second one behind a load on, steps of two calls over the stored rows (the bytes would be
+    written each time), lookups alone over the bytes again."""
+    print("case: few over bytes, ways by default", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(24)
+    K, d, n = 262144, 768, 64
+    c = mixture(g, K, d)
+    q = queries(g, c, n)
+    cache, plain = siso.SisoCache(d, K, siso.BF16), siso.SisoCache(d, K, siso.BF16)
+    plain.set_option("screen", 2)
+    for x in (cache, plain):
+        x.load(c)
+        x.reserve(n)
+
+    def two(x=cache):
+        idx, sim, hit = x.lookup(q, THETA)
+        x.update(q, idx, hit)
+        return idx, sim, hit
+
+    stored = kernel_us(plain, lambda: plain.lookup(q, THETA), 20)
+    for load in range(2):
+        for x in (cache, plain):
+            x.load(c)
+        cache.lookup_update(q, THETA)
+        plain.lookup_update(q, THETA)
+        for step in range(70):  # (through the writing behind 64 lookups)
+            same(cache.lookup_update(q, THETA), plain.lookup_update(q, THETA), f"step {step}")
+        assert kernel_us(cache, lambda: cache.lookup_update(q, THETA), 20) < 0.8 * stored
+        for _ in range(20):
+            plain.lookup_update(q, THETA)
+        for step in range(40):
+            same(two(), two(plain), f"two calls {step}")
+        assert kernel_us(cache, two, 20) > 0.85 * stored
+        for _ in range(130):  # (twice as many as the 60 steps have come to)
+            cache.lookup(q, THETA)
+        assert kernel_us(cache, lambda: cache.lookup(q, THETA), 20) < 0.8 * stored
