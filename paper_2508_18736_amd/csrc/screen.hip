@@ -1585,7 +1585,9 @@ extern "C" int siso_screened(const siso_cache *c, long n) {
     return n == 0 ? siso_screen_pairs_wanted(c, c->count, 1.f) : siso_screen_wanted(c, n) || siso_bytes_few_wanted(c, n);
 }
 
-// Room for the bytes of `rows` rows of the cache, which are then made by the next lookup (nothing made from is recorded there).
+// Room for the bytes of `rows` rows of the cache, which are then made by the next lookup (nothing made from is recorded there).  Of a cache that
+// is nearly full: for all it can hold, if that is to be had, so that the last eighth does not move them once more (a first refresh of 65,536
+// rows x 768 by 6,553, 1.87 ms, was 0.09 of it longer than with one room for bytes and workspace).
 static bool byte_room(siso_cache *c, long rows) {
     ByteRows &b = c->bytes;
     if (rows <= b.rows) return true;
@@ -1600,10 +1602,13 @@ static bool byte_room(siso_cache *c, long rows) {
         (void)hipFree(at);
         return (char *)nullptr;
     };
-    const long had = b.rows;
+    const long had = b.rows, full = c->capacity - rows <= rows / 8 ? c->capacity : rows;
+    long count = full;
     char *larger = nullptr;
     if (room == 0 || byte_store(nullptr, c, rows).bytes <= room) {
-        larger = take_rows(rows, b.at ? byte_store(nullptr, c, had).bytes : 0);
+        const size_t beside = b.at ? byte_store(nullptr, c, had).bytes : 0;
+        larger = take_rows(full, beside);
+        if (!larger && full > rows) larger = take_rows(count = rows, beside);
         // (the old ones go: nothing but their recorded launches needs them)
         if (b.at && larger && b.recorded) {
             c->screen_kept->push_back(b.at);  // (room for it: note_recorded)
@@ -1615,7 +1620,7 @@ static bool byte_room(siso_cache *c, long rows) {
             }
             (void)hipFree(b.at);
             if (!larger) {  // not beside them: perhaps in their place
-                larger = take_rows(rows, 0);
+                larger = take_rows(count = rows, 0);
                 b.at = larger ? nullptr : take_rows(had, 0);
                 b.rows = b.at ? had : 0;
                 siso_bytes_all_behind(c);
@@ -1627,7 +1632,7 @@ static bool byte_room(siso_cache *c, long rows) {
         return false;
     }
     b.at = larger;
-    b.rows = rows;
+    b.rows = count;
     b.recorded = 0;
     siso_bytes_all_behind(c);
     return true;

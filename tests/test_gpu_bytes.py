@@ -233,6 +233,33 @@ def test_bytes_that_grow(siso, room, grows):
     assert abs(before - more - free()) < 4 << 20
 
 
+@pytest.mark.parametrize("room,moves", [(0, False), (52, True)])
+def test_bytes_of_a_cache_that_is_nearly_full(siso, room, moves):
+    """They have room for all it can hold (54 MB), so the last rows do not move them; where that is not to be had, for the rows that there are (48 MB)."""
+    print(f"case: bytes of a nearly full cache, room={room}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(23)
+    d, K, capacity = 1024, 48000, 54000
+    c = rows(g, capacity, d, "bf16", rows(g, 4000, d, "bf16"))
+    q = rows(g, 300, d, "bf16", c[:K])
+    cache = make(siso, capacity, d, "bf16")
+    cache.load(c[:K])
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()  # (all but torch's own)
+
+    cache.set_option("screen_room", room << 10)
+    before = free()
+    cache.lookup(q, THETA)
+    first = free()
+    assert before - first > K * d
+    cache.set_option("screen_room", 0)
+    cache.load(c)
+    cache.lookup(q, THETA)
+    assert (free() < first - (2 << 20)) == moves
+    as_fresh(siso, cache, d, "bf16", q, "all rows")
+
+
 @pytest.mark.parametrize("kind", ["f32", "bf16", "copy"])
 @pytest.mark.parametrize("d", [256, 384, 1024])
 def test_small_folds_over_rows_with_bytes(siso, kind, d):
