@@ -132,10 +132,11 @@ long siso_count(const siso_cache *c);
  * values as ever; of two rows whose similarities are within the rounding of each other
  * either may be named.  A batch whose queries are near too many rows (rows with a common
  * direction, queries that miss) is given up early and looked up without the bytes.
- * Batches of up to 64 bf16 queries against many rows (256 dimensions and more; 6.5e7 elements for
- * up to eight queries, 1e8 for more, and 140,000 rows for more than 32) go over the same bytes once they are
- * current, which is when two such lookups have read the rows for want of them; their results are the
- * same bits either way.
+ * Batches of up to 64 bf16 queries against many rows (256 dimensions and more; more than 6.7e7 elements for
+ * up to eight queries and 1.0e8 for more, from 17 queries on also more than 131,072 rows, from 33 on against more than
+ * 896 dimensions 196,608) go over the same bytes once they are current.  All of the rows are written as bytes for the second such
+ * lookup behind a load, single rows that have changed once lookups over the stored rows have read twice as many elements, later
+ * where few lookups come between the changes; a graph records such a lookup over the stored rows.  Results are the same bits either way.
  * Screening takes a byte per element of the cache (its dimension rounded up to a multiple of
  * 128, at least 256) and a workspace of 10 to 22 KB per query, of at most 16,384: 1.4 GB for
  * 1,048,576 rows of 1,024.  Both are kept until siso_destroy, and a call writes the bytes of

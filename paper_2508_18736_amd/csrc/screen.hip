@@ -1699,15 +1699,20 @@ static bool few_lists_room(siso_cache *c) {
     return true;
 }
 
-// Steps of n queries (lookup and fold), a third of which miss, the rows as they are stored / the bytes, us:
-//   768:   30,000 n 1 22 / 19, n 64 25 / 77;  60,000 n 1 23 / 25, n 32 25 / 34, n 64 26 / 80;  80,000 n 1 35 / 26;  100,000 n 1 35 / 27, n 8 38 / 32,
-//          n 32 38 / 35, n 64 38 / 65;  120,000 n 32 39 / 38;  150,000 n 1 51 / 32, n 32 52 / 40, n 64 52 / 44;
-//          262,144 n 1 69 / 43, n 8 70 / 47, n 32 73 / 51, n 64 74 / 57 (none misses: 72 / 50);  400,000 n 1 102 / 60, n 64 109 / 77
-//   1,024: 60,000 n 1 26 / 26, n 64 30 / 128;  100,000 n 1 44 / 32, n 64 47 / 89;  200,000 n 1 81 / 44, n 64 83 / 65;  400,000 n 1 138 / 84, n 64 140 / 115
-//   384:   100,000 n 1 23 / 19, n 64 25 / 31;  200,000 n 1 36 / 26, n 64 38 / 35;  400,000 n 1 55 / 36, n 64 61 / 46
-//   256:   100,000 n 64 22 / 25;  200,000 n 1 28 / 22, n 64 30 / 30;  400,000 n 1 44 / 29, n 64 46 / 38.     128: 2,000,000 n 64 96 / 115
+// Steps of n queries (lookup and fold), the rows as they are stored / the bytes, us, if none, 30 % and 60 % of the queries miss:
+//   768:   30,000 (60 %) n 1 19 / 17, n 8 22 / 27, n 64 23 / 35;  60,000 (60 %) n 1 21 / 24, n 8 23 / 31, n 64 24 / 41
+//          88,000 n 8 36 / 29, 33, 32;  132,000 n 9 49 / 33, 35, 35, n 32 49 / 35, 38, 41, n 64 50 / 38, 43, 45;  196,608 n 64 54 / 43, 49, 49;  400,000 n 1 102 / 60, n 64 109 / 77
+//   896:   115,000 n 16 42 / 32, 36, 43, n 32 42 / 34, 44, 40;  132,000 n 32 55 / 36, 41, 43;  196,608 n 33 59 / 48, 54, 60, n 64 60 / 49, 57, 59
+//   960:   105,000 n 9 43 / 34, 38, 40, n 32 43 / 36, 44, 45;  140,000 n 64 60 / 48, 63, 62;  196,608 n 64 63 / 57, 70, 80;  198,000 n 64 75 / 58, 75, 73
+//   1,024: 64,000 n 1 26 / 26, 26, 26, n 8 28 / 27, 31, 35;  66,000 n 8 44 / 29, 32, 35;  131,072 n 16 47 / 37, 44, 46, n 32 47 / 39, 44, 52;  131,073 n 32 63 / 39, 47, 49
+//          140,000 n 64 64 / 48, 64, 65;  180,000 n 64 66 / 59, 73, 77;  198,000 n 64 81 / 58, 74, 78;  262,144 n 64 87 / 72, 87, 88;  400,000 n 1 138 / 84, n 64 140 / 115
+//   512:   131,000 n 1 27 / 24, 24, 23, n 8 28 / 26, 27, 28;  197,000 n 9 46 / 31, 32, 32, n 64 45 / 36, 39, 39
+//   384:   176,000 n 8 29 / 26, 27, 27;  264,000 n 64 43 / 36, 39, 38.     256: 266,000 n 8 33 / 26, 27, 27;  394,000 n 64 43 / 35, 36, 36.     128: 2,000,000 n 64 96 / 115
 // Two kernels with longer chains of round trips stand against half of the reading; and with few rows a workgroup has
-// little to go by: with one or two blocks for each wave the bounds of 33 queries and more come too late for its lists.
+// little to go by: with one or two blocks for each wave the bounds of 33 queries and more come too late for its lists.  Over the stored rows a
+// step takes as long as 256 workgroups with whole tiles of 256 rows do: up to 65,536 rows the time of one tile, up to 131,072 of two, and so on.  The lines lie
+// where such a tile is added: 65,536 rows of 1,024, 131,072 of 768.  Beyond 896 elements the lists of 33 queries and more have the least room (LDS holds the
+// queries), and one tile more is needed.
 int siso_bytes_few_wanted(const siso_cache *c, long n) {
     if (c->dtype != SISO_BF16 || n < 1 || n > SISO_FEW || c->count < 1 || c->count > SISO_FEW_MOST_ROWS) return 0;
     if (c->dim % 64 != 0 || c->dim < 128 || c->dim > SISO_SCREEN_DIM) return 0;
@@ -1715,7 +1720,8 @@ int siso_bytes_few_wanted(const siso_cache *c, long n) {
     if (c->opt_screen != 0 || c->path != SISO_PATH_AUTO || c->opt_mfma_config != 0 || c->opt_tiles_per_slice != 0 || c->opt_mfma_qblock != 0) return 0;
     const double elements = (double)c->count * c->dim;
     if (c->dim < 256) return 0;
-    return n <= 8 ? elements >= 6.5e7 : n <= 32 ? elements >= 1e8 : elements >= 1e8 && c->count >= 140000;
+    if (n <= 8) return elements > 65536. * 1024;
+    return elements > 131072. * 768 && (n <= 16 || c->count > (n > 32 && c->dim > 896 ? 196608 : 131072));
 }
 
 int siso_bytes_few_room(siso_cache *c, long n) {
@@ -1789,8 +1795,8 @@ void siso_screen_reserve(siso_cache *c, long n) {
 void siso_bytes_few_reserve(siso_cache *c, long n) {
     siso_cache full = *c;
     full.count = c->capacity < SISO_FEW_MOST_ROWS ? c->capacity : SISO_FEW_MOST_ROWS;
-    bool wanted = false;  // (by any batch of up to n: the rule asks for more rows from nine and from 33 queries on)
-    for (const long least : {1L, 9L, 33L}) wanted = wanted || (least <= n && siso_bytes_few_wanted(&full, least));
+    bool wanted = false;  // (by any batch of up to n: the rule asks for more rows from nine, 17 and 33 queries on)
+    for (const long least : {1L, 9L, 17L, 33L}) wanted = wanted || (least <= n && siso_bytes_few_wanted(&full, least));
     if (!wanted) return;
     c->bytes.refused = 0;
     c->few_refused = 0;

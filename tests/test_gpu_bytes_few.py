@@ -177,7 +177,7 @@ def free():
 
 
 @pytest.mark.parametrize("capacity,K,d,n,batches", [(100000, 90000, 768, 64, (1, 8)), (139999, 135000, 768, 64, (9, 32)), (280000, 275000, 256, 8, (1, 8)),
-                                                    (2097153, 260000, 256, 1000, (1, 64))])
+                                                    (2097153, 270000, 256, 1000, (1, 64))])
 @pytest.mark.parametrize("refused", [False, True])
 def test_a_reservation_serves_every_smaller_batch(siso, capacity, K, d, n, batches, refused):
     """Also the batches that go over the bytes from fewer rows on than the reserved one, a cache that holds fewer rows than it can, and a reservation
@@ -200,6 +200,17 @@ def test_a_reservation_serves_every_smaller_batch(siso, capacity, K, d, n, batch
         for _ in range(6):
             cache.lookup_update(q, THETA)
     assert abs(before - free()) < 2 << 20  # (a reservation of the driver's)
+
+
+@pytest.mark.parametrize("K,d,over,stored", [(65536, 1024, (), (1, 8, 64)), (65537, 1024, (1, 8), (9, 64)), (131072, 768, (8,), (9, 64)), (131073, 768, (9, 64), ()),
+                                             (131072, 1024, (8, 16), (17, 64)), (131073, 1024, (17, 32), (33, 64)), (196608, 896, (33, 64), ()),
+                                             (196608, 960, (32,), (33,)), (196609, 960, (33, 64), ())])
+def test_where_small_lookups_go_over_bytes(siso, K, d, over, stored):
+    """On both sides of every line: where steps over the bytes take longer, with few or many misses, they stay with the stored rows."""
+    print(f"case: lines of small lookups K={K} d={d}", flush=True)
+    cache = siso.SisoCache(d, K, siso.BF16)
+    cache.load(torch.ones(K, d, dtype=torch.bfloat16, device=DEV))
+    assert [n for n in over + stored if cache.screened(n)] == list(over)
 
 
 def test_lists_without_room_are_not_asked_for_again(siso):
