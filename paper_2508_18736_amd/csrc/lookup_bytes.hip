@@ -90,7 +90,9 @@ __global__ __launch_bounds__(FEW_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     const unsigned call = lists.call[none];
     describe(have ? b : 0);
     // steps on their way: a whole block of rows, or half of one where the registers end (128 KiB for a compute unit are enough)
-        constexpr int R = KS <= (WQ == 1 ? 24 : 16) ? KS : KS / 2;
+    // (33 queries and more, 640 elements and more: five to fourteen registers that the products do not use wait in scratch memory, written once before the
+    // rounds and read behind the products of one at most.)
+    constexpr int R = KS <= (WQ == 1 ? 24 : 16) ? KS : KS / 2;
     i32x4 a[R];
     // Buffer loads: where there is no next block the lanes' offset lies behind all rows, and the instruction fetches nothing.  (A branch
     // around it would be two copies of the products, and of their registers.)

@@ -678,10 +678,10 @@ __device__ __forceinline__ u64 listed_key(const listed_acc &acc, float w, int ro
     u64 key = 0;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-    const int from = 8 * (i >> 2) + 4 * h + (i & 3);
-    const float v = acc[i] * __shfl(w, from);
-    const u64 k = pack_key(v, (unsigned)__shfl(row, from));
-    if (v > -INFINITY && k > key) key = k;
+        const int from = 8 * (i >> 2) + 4 * h + (i & 3);
+        const float v = acc[i] * __shfl(w, from);
+        const u64 k = pack_key(v, (unsigned)__shfl(row, from));
+        if (v > -INFINITY && k > key) key = k;
     }
     const LanePair<u64> both = lane_pair<32>(key);
     return both.a > both.b ? both.a : both.b;
@@ -694,23 +694,23 @@ __device__ __forceinline__ u64 listed_product(const bf16_t *__restrict__ cent, c
     const float w = invn[row];
     listed_acc acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int e0 = 0; e0 < d; e0 += 64 * AHEAD) {
-    u32x4_t x[AHEAD][4];
+        u32x4_t x[AHEAD][4];
 #pragma unroll
-    for (int g = 0; g < AHEAD; ++g)
+        for (int g = 0; g < AHEAD; ++g)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = e0 + g * 64 + i * 16;
-            x[g][i] = *(const u32x4_t *)(at + (e < d ? e : 0));
+            for (int i = 0; i < 4; ++i) {
+                const int e = e0 + g * 64 + i * 16;
+                x[g][i] = *(const u32x4_t *)(at + (e < d ? e : 0));
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < AHEAD; ++g) {
+            if (e0 + g * 64 >= d) break;  // (d is a multiple of 64)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(listed_frag, x[g][i]),
+                                                              __builtin_bit_cast(listed_frag, sh_q[(e0 + g * 64 + i * 16) / 8 + h]), acc, 0, 0, 0);
         }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < AHEAD; ++g) {
-        if (e0 + g * 64 >= d) break;  // (d is a multiple of 64)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(listed_frag, x[g][i]),
-                                                          __builtin_bit_cast(listed_frag, sh_q[(e0 + g * 64 + i * 16) / 8 + h]), acc, 0, 0, 0);
-    }
     }
     return listed_key(acc, w, row);
 }
@@ -727,18 +727,18 @@ __device__ __forceinline__ u64 listed_products_few(const bf16_t *__restrict__ ce
     const int row = sh_rows[mine];
     const float w = invn[row];
     for (int r0 = wave; r0 < many; r0 += 4 * AHEAD) {
-    u32x4_t x[AHEAD][2];
+        u32x4_t x[AHEAD][2];
 #pragma unroll
-    for (int k = 0; k < AHEAD; ++k) {
-        const bf16_t *at = cent + (size_t)sh_rows[r0 + 4 * k < many ? r0 + 4 * k : r0] * d;
+        for (int k = 0; k < AHEAD; ++k) {
+            const bf16_t *at = cent + (size_t)sh_rows[r0 + 4 * k < many ? r0 + 4 * k : r0] * d;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) x[k][c] = *(const u32x4_t *)(at + ((lane + 64 * c) * 8 < d ? (lane + 64 * c) * 8 : 0));
-    }
+            for (int c = 0; c < 2; ++c) x[k][c] = *(const u32x4_t *)(at + ((lane + 64 * c) * 8 < d ? (lane + 64 * c) * 8 : 0));
+        }
 #pragma unroll
-    for (int k = 0; k < AHEAD; ++k)
+        for (int k = 0; k < AHEAD; ++k)
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-            if (r0 + 4 * k < many && (lane + 64 * c) * 8 < d) *(u32x4_t *)(room + (size_t)(r0 + 4 * k) * pitch + (lane + 64 * c) * 16) = x[k][c];
+            for (int c = 0; c < 2; ++c)
+                if (r0 + 4 * k < many && (lane + 64 * c) * 8 < d) *(u32x4_t *)(room + (size_t)(r0 + 4 * k) * pitch + (lane + 64 * c) * 16) = x[k][c];
     }
     __syncthreads();
     if (wave * 32 >= many) return 0;
@@ -747,23 +747,23 @@ __device__ __forceinline__ u64 listed_products_few(const bf16_t *__restrict__ ce
     u32x4_t x[4], q[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-    x[i] = *(const u32x4_t *)(at + i * 32);
-    q[i] = sh_q[i * 2 + h];
+        x[i] = *(const u32x4_t *)(at + i * 32);
+        q[i] = sh_q[i * 2 + h];
     }
     for (int e = 64; e <= d; e += 64) {  // (the next four steps are read while four are multiplied)
-    u32x4_t y[4], p[4];
-    const int n = e < d ? e : 0;
+        u32x4_t y[4], p[4];
+        const int n = e < d ? e : 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        y[i] = *(const u32x4_t *)(at + n * 2 + i * 32);
-        p[i] = sh_q[(n + i * 16) / 8 + h];
-    }
+        for (int i = 0; i < 4; ++i) {
+            y[i] = *(const u32x4_t *)(at + n * 2 + i * 32);
+            p[i] = sh_q[(n + i * 16) / 8 + h];
+        }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(listed_frag, x[i]), __builtin_bit_cast(listed_frag, q[i]), acc, 0, 0, 0);
-        x[i] = y[i];
-        q[i] = p[i];
-    }
+        for (int i = 0; i < 4; ++i) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(listed_frag, x[i]), __builtin_bit_cast(listed_frag, q[i]), acc, 0, 0, 0);
+            x[i] = y[i];
+            q[i] = p[i];
+        }
     }
     return listed_key(acc, w, row);
 }
