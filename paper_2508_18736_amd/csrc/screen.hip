@@ -1730,12 +1730,15 @@ int siso_bytes_few_room(siso_cache *c, long n) {
     // flood on (3 to 13 times the time).  Replays of a step of 64 against 262,144 x 768 75 us as they are stored, 66 over the bytes; of 64 against 140,001 x 1,024
     // 60 and 74, of eight against 64,000 x 1,024 33 and 39.
     if (recording && !forced) return 0;
-    // Lists that found no room, of some call since the last one that was looked at: the next 64 lookups go over the rows as they are stored,
-    // twice as many whenever that is seen again.  (Rows that lists flood on give the same results at one and a half to twice the time.)
+    // Lists that found no room, or that were too long to be worth it (LISTED_MANY), of some call since the last one that was looked at: the next 64 lookups go over
+    // the rows as they are stored, twice as many whenever that is seen again before 4,096 have gone over the bytes.  (Rows with a common direction give the same
+    // results at up to eight times the time: mean cosine 0.8, 32 queries against 131,073 x 768 161 us, 46 over the stored rows and by this rule; eight against
+    // 66,000 x 1,024 155 and 41; 0.6 65 and 41.  Below that it turns over gradually: 0.4, 64 against 140,001 x 768 52 and 47, against 262,144 x 768 61 and 69.)
     if (!forced && c->few_flooded && *(volatile int *)c->few_flooded != 0) {
         *(volatile int *)c->few_flooded = 0;
-        c->few_rests = c->few_rests == 0 ? 64 : c->few_rests < 4096 ? 2 * c->few_rests : c->few_rests;
+        c->few_rests = c->few_rests == 0 || c->few_went >= 4096 ? 64 : c->few_rests < 4096 ? 2 * c->few_rests : c->few_rests;
         c->few_rest = c->few_rests;
+        c->few_went = 0;
     }
     if (!forced && c->few_rest > 0) {
         --c->few_rest;
@@ -1769,6 +1772,7 @@ int siso_bytes_few_room(siso_cache *c, long n) {
         }
     }
     ++b.served;
+    ++c->few_went;
     return 1;
 }
 

@@ -717,6 +717,10 @@ __device__ __forceinline__ u64 listed_product(const bf16_t *__restrict__ cent, c
 // Up to LISTED_FEW rows, what mostly is left: all waves bring them to LDS, whole rows at a time (in the wave's own loads they took 5 us of 13),
 // a pad of 16 bytes behind each, and a wave for 32 of them multiplies.
 #define LISTED_FEW 64
+// Rows of one query that take longer than the bytes save, 0.1 us each (a step of eight against 66,000 x 1,024, mean cosine 0.6, up to 591 of them: 66 us,
+// 41 over the stored rows): the host hears of them as of lists that found no room.  Rows without a common direction leave up to 330, a
+// mean cosine of 0.4 mostly fewer than 260.
+#define LISTED_MANY 512
 #define LISTED_LDS(d) (LISTED_FEW * (2 * (d) + 16))
 #define LISTED_STATIC (14 * 1024)  // and what else the kernel keeps there, 13,952 bytes
 __device__ __forceinline__ u64 listed_products_few(const bf16_t *__restrict__ cent, const float *__restrict__ invn, const int *sh_rows, int many,
@@ -787,6 +791,7 @@ struct FoldListed {
     ByteView bytes;
     FewLists few;
     int fold;  // 0 = a lookup and nothing else
+    int *flooded;
 };
 template <typename T, int UPD_MAXE_T, class More>
 __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q, const u64 *__restrict__ keys, long n, long K,
@@ -943,6 +948,7 @@ __global__ __launch_bounds__(256) void k_finalize_update(const T *__restrict__ Q
             __syncthreads();
             all_rows = sh_rows_n;
         }
+        if (all_rows > LISTED_MANY && t == 0) __hip_atomic_store(more.flooded, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (all_rows <= LISTED_FEW) {
             const u64 k2 = all_rows > 0 ? listed_products_few((const bf16_t *)cent, invn, sh_rows, all_rows, sh_q, d, listed_room) : 0;
             key = k2 > key ? k2 : key;
@@ -1994,7 +2000,7 @@ static int few_lookup(siso_cache *c, const void *queries, long n, float theta, i
                        c->count, c->dim, siso_bytes_few_workgroups(c), theta, 1, out_idx, out_sim, out_hit, count_index >= 0 ? c->access : nullptr,
                        (bf16_t *)c->cent, c->mean, c->size, c->invn, c->counters + 4,
                        c->opt_fold_spin_limit >= 0 ? c->opt_fold_spin_limit : 1 << 18, c->counters, (const float *)nullptr, (unsigned char *)nullptr,
-                       (float *)nullptr, (float *)nullptr, (int *)nullptr, FoldListed{c->version, bytes, c->few, fold ? 1 : 0});
+                       (float *)nullptr, (float *)nullptr, (int *)nullptr, FoldListed{c->version, bytes, c->few, fold ? 1 : 0, c->few_flooded});
     if (fold) *folded = 1;
     return siso_check_hip(c, hipGetLastError(), "k_finalize_update");
 }

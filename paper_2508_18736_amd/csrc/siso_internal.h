@@ -163,8 +163,9 @@ struct siso_cache {
     ByteRows bytes;
     FewLists few;  // room for them from few.best on, or NULL
     int few_refused;  // there was none: not asked for again until siso_reserve or a release
-    int *few_flooded;  // pinned: a workgroup found no room for its lists; such lookups are better off on the rows as they are stored:
+    int *few_flooded;  // pinned: a workgroup found no room for its lists, or a query was left with very many rows; such lookups are better off on the rows as they are stored:
     long few_rest, few_rests;  // as many more of them, and how many that were the last time
+    long few_went;  // lookups over the bytes since then
     long few_reserved;  // batches that siso_reserve has made room for such lookups for, or tried to: they do not ask for any
     long screen_reserved;  // batches that siso_reserve has sized `screen` for, or tried to: their lookups leave it as it is
     int screen_recorded;  // a graph holds a screened lookup on `screen`: outgrown, it stays until the cache goes (screen_kept)
@@ -676,7 +677,7 @@ inline void siso_bytes_all_behind(siso_cache *c) {
     c->bytes.behind = c->capacity;
     c->bytes.wait = 0;
     c->bytes.served = 16;  // (what was written has served its time)
-    c->few_rest = c->few_rests = 0;  // (other rows: perhaps no flood)
+    c->few_rest = c->few_rests = c->few_went = 0;  // (other rows: perhaps no flood)
 }
 ByteView siso_byte_view(const siso_cache *c);
 // Before every launch that is given the address of the bytes: a graph that records it goes on using them, so they stay when they are outgrown.  False: that

@@ -352,6 +352,29 @@ def kernel_us(cache, f, reps):
     return ms / times * 1e3
 
 
+@pytest.mark.parametrize("K,d,n,common", [(66000, 1024, 8, 0.6), (262144, 768, 64, 0.6), (140001, 768, 32, 0.8)])
+def test_lookups_that_leave_many_rows_turn_to_the_stored_rows(siso, K, d, n, common):
+    """Rows with a common direction, whether the lists run over or are only long: most of a stream of lookups goes over the rows as they are stored."""
+    print(f"case: few over bytes, long lists by default K={K} d={d} n={n} common={common}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(26)
+    c = mixture(g, K, d, common)
+    q = [queries(g, c, n, common) for _ in range(8)]
+    caches = []
+    for screen in (0, 2):
+        caches.append(siso.SisoCache(d, K, siso.BF16))
+        caches[-1].set_option("screen", screen)
+        caches[-1].load(c)
+        assert caches[-1].screened(n) == (screen == 0)
+    for seed in range(100):
+        same(caches[0].lookup(q[seed % 8], THETA), caches[1].lookup(q[seed % 8], THETA), f"lookup {seed}")
+    for _ in range(200):
+        for x in q:
+            caches[0].lookup(x, THETA)
+        torch.cuda.synchronize()
+    times = [kernel_us(cache, lambda: [cache.lookup(x, THETA) for x in q], 40) for cache in caches]
+    assert 0.85 * times[1] < times[0] < 1.25 * times[1], times
+
+
 def test_which_way_lookups_go_by_default(siso):
     """Steps that fold their hits go over the bytes from the second one behind a load on, steps of two calls over the stored rows (the bytes would be
     written each time), lookups alone over the bytes again."""
